@@ -258,8 +258,8 @@ int april_sample_rows_logprobs(april_ctx* ctx, const float* logits, int32_t n_ro
 
 /* april_sample_rows for callers that cannot allocate device memory (code under HIP graph
  * capture rules, tight serving loops, harnesses that forbid hipMalloc): same arguments, same
- * result, but every temporary (row keys, result staging, control word, the per-row maxima of
- * 64-logit groups) lives in a static device array of 4 MiB + 16.25 KiB that the library holds on
+ * result, but every temporary (row keys, result staging, control word, the per-row maxima and sums
+ * of 64-logit groups) lives in a static device array of 12 MiB + 16.25 KiB that the library holds on
  * every GPU it runs on until the process ends; the call makes no hipMalloc / hipFree.
  * Limits: n_rows <= 1024 and n_rows * (vocab / 64) <= 1048576 (APRIL_EINVAL beyond).
  * All calls on one GPU share that array and it keeps the last call's contents: calls that

@@ -68,7 +68,8 @@ constexpr size_t NOALLOC_MAX_ROWS = 1024;
 constexpr size_t NOALLOC_MAX_GROUP_MAX = (size_t)1 << 20;        // floats: n_rows * (vocab / 64) may not exceed this
 constexpr size_t NOALLOC_OFF_CTL = 0, NOALLOC_OFF_REQ = 256, NOALLOC_OFF_GEN = NOALLOC_OFF_REQ + 8 * NOALLOC_MAX_ROWS,
                  NOALLOC_OFF_OUT = NOALLOC_OFF_GEN + 4 * NOALLOC_MAX_ROWS, NOALLOC_OFF_GM = NOALLOC_OFF_OUT + 4 * NOALLOC_MAX_ROWS,
-                 NOALLOC_BYTES = NOALLOC_OFF_GM + 4 * NOALLOC_MAX_GROUP_MAX;
+                 NOALLOC_OFF_GS = NOALLOC_OFF_GM + 4 * NOALLOC_MAX_GROUP_MAX,      // group sums (categorical sampler)
+                 NOALLOC_BYTES = NOALLOC_OFF_GS + 8 * NOALLOC_MAX_GROUP_MAX;
 static_assert(NOALLOC_OFF_GM % 256 == 0, "group maxima start on a 256-byte boundary");
 static __device__ __align__(256) unsigned char scratch[NOALLOC_BYTES];
 constexpr int MAX_DEVICES = 64;
@@ -137,6 +138,7 @@ struct april_ctx {
   float *x_res = nullptr, *qkv = nullptr, *q_rot = nullptr, *proj = nullptr, *gu = nullptr, *logits = nullptr;
   float* group_max = nullptr;  // per row, maxima of groups of lmhead_group_cols() logits (MFMA LM head)
   int* group_idx = nullptr;    // ... and the column of each maximum (greedy sampling without logits)
+  double* group_sum = nullptr; // ... and the sum of its exponentials (log-probabilities, categorical sampling), or null
   bool write_logits = true;    // false: greedy sampling from the group records alone, the LM head writes no logits
   void *h_act = nullptr, *attn_out = nullptr, *act = nullptr, *hf = nullptr;
   float *rope_cos = nullptr, *rope_sin = nullptr;
@@ -187,6 +189,8 @@ struct april_ctx {
   bool weights_valid = true;     // false between a resume of the weights' memory and the next april_update_weights
   int device = 0;                // HIP device the context lives on
   unsigned char* scratch_dev = nullptr;   // this device's copy of the static scratch array
+  char* sr_ws = nullptr;         // workspace of april_sample_rows, grown on demand (at most about 64 MiB, or one row's records)
+  size_t sr_ws_bytes = 0;
 
   // pending resume
   std::vector<Entry> pending;
@@ -667,10 +671,13 @@ void forward(april_ctx* c, RowCtx rows, RowCtx srows, const int* gather, double 
   {
     ProfScope p(c, KC_GEMM_LMHEAD, (double)V * d * e + SB * d * e, 2.0 * SB * V * d);
     // more than 128 sampling rows: the tiled kernel reads the head once per 256 rows instead of
-    // once per 128 (same bits either way)
+    // once per 128 (same bits either way).  (The categorical sampler wants fp64 exponentials, which
+    // launch_group_records takes from the logits below.)
+    const GroupOut go{c->group_max, c->group_idx, c->cfg.sampler == APRIL_SAMPLER_CATEGORICAL ? nullptr : c->group_sum,
+                      1.0f / sampler_cfg(c).temperature};
     if (c->use_mfma && c->group_max && c->tile_gemm && srows.max_rows > 128 && d % 32 == 0)
-      launch_gemm_tile_logits(st, srows, (const bf16_t*)c->hf, c->lm_head_s, lg_out, c->group_max, V, d, c->group_idx);
-    else if (c->use_mfma && c->group_max) launch_gemm_mfma_logits(st, srows, (const bf16_t*)c->hf, c->lm_head_s, lg_out, c->group_max, V, d, c->group_idx);
+      launch_gemm_tile_logits(st, srows, (const bf16_t*)c->hf, c->lm_head_s, lg_out, go, V, d);
+    else if (c->use_mfma && c->group_max) launch_gemm_mfma_logits(st, srows, (const bf16_t*)c->hf, c->lm_head_s, lg_out, go, V, d);
     else if (c->use_mfma) launch_gemm_mfma(st, srows, (const bf16_t*)c->hf, c->lm_head_s, c->logits, V, d, 1, 0);
     else if (c->bf16) launch_gemm_ref<bf16_t, true>(st, srows, (const bf16_t*)c->hf, (const bf16_t*)c->lm_head, c->logits, V, d);
     else launch_gemm_ref<float, false>(st, srows, (const float*)c->hf, (const float*)c->lm_head, c->logits, V, d);
@@ -680,8 +687,10 @@ void forward(april_ctx* c, RowCtx rows, RowCtx srows, const int* gather, double 
     ProfScope p(c, KC_SAMPLE, fused ? SB * (V / 64) * 8.0 : SB * V * 4.0, 0);
     const SamplerCfg sc = sampler_cfg(c);
     Watch w = c->cfg.debug_logits ? c->dwatch : Watch{};
-    launch_sample(st, srows, c->ds, c->d_ctrl, c->logits, V, sc, w, 1, nullptr, nullptr, nullptr, c->group_max,
-                  lmhead_group_cols(), nullptr, c->group_max ? c->group_idx : nullptr);
+    if (c->group_sum && sc.kind == APRIL_SAMPLER_CATEGORICAL)
+      launch_group_records(st, c->logits, srows.ctl, srows.max_rows, V, 2, sc.temperature, c->group_max, c->group_sum);
+    launch_sample(st, srows, c->ds, c->d_ctrl, lg_out, V, sc, w, 1, nullptr, nullptr, nullptr, c->group_max,
+                  lmhead_group_cols(), nullptr, c->group_max ? c->group_idx : nullptr, c->group_sum);
   }
 }
 
@@ -932,13 +941,16 @@ int april_init(const april_model_cfg* cfg, const april_tensor* weights, int32_t 
   }
   const size_t SR = ((size_t)S + 31) / 32 * 32;
   TRY(dev_alloc(c, &c->logits, SR * V));
-  if (c->use_mfma && V % lmhead_group_cols() == 0) {
-    TRY(dev_alloc(c, &c->group_max, SR * (V / lmhead_group_cols())));
-    TRY(dev_alloc(c, &c->group_idx, SR * (V / lmhead_group_cols())));
-    // the fused sampler must not write logits: greedy sampling needs only the group records;
-    // parity mode, log-probabilities and the candidate search of the sampling modes read logits
+  if (c->use_mfma) {
+    const size_t n_groups = ceil_div(V, lmhead_group_cols());
+    TRY(dev_alloc(c, &c->group_max, SR * n_groups));
+    TRY(dev_alloc(c, &c->group_idx, SR * n_groups));
+    if (g.logprobs || g.sampler == APRIL_SAMPLER_CATEGORICAL) TRY(dev_alloc(c, &c->group_sum, SR * n_groups));
+    // the fused sampler must not write logits: greedy sampling (with or without log-probabilities)
+    // needs only the group records; parity mode, the candidate search and the categorical
+    // sampler read logits
     const char* wl = getenv("APRIL_WRITE_LOGITS");
-    c->write_logits = g.debug_logits || g.logprobs || g.sampler != APRIL_SAMPLER_GREEDY || (wl && !strcmp(wl, "1"));
+    c->write_logits = g.debug_logits || g.sampler != APRIL_SAMPLER_GREEDY || (wl && !strcmp(wl, "1"));
   }
   TRY(dev_alloc_bytes(c, &c->h_act, M * d * e));
   TRY(dev_alloc_bytes(c, &c->attn_out, M * nq * e));
@@ -1009,6 +1021,7 @@ void april_destroy(april_ctx* c) {
   if (c->stream) hipStreamSynchronize(c->stream);
   for (void* p : c->allocs) hipFree(p);
   for (auto& r : c->vm_regions) { if (r.mapped) vm_unmap_region(r); hipMemAddressFree(r.va, r.bytes); }
+  if (c->sr_ws) hipFree(c->sr_ws);
   if (c->h_ctrl) hipHostFree(c->h_ctrl);
   if (c->h_slot_arrays) hipHostFree(c->h_slot_arrays);
   if (c->h_req) hipHostFree(c->h_req);
@@ -1268,36 +1281,50 @@ int april_debug_logits(april_ctx* c, int64_t request_id, int32_t gen_index, floa
 static int sample_rows_impl(april_ctx* c, const float* logits, int32_t n_rows, const int64_t* request_ids,
                             const int32_t* gen_index, int32_t* out_tokens, float* out_logprobs) {
   if (!c || !logits || !request_ids || !gen_index || !out_tokens || n_rows <= 0) return APRIL_EINVAL;
-  long long* d_req = nullptr; int *d_gen = nullptr, *d_out = nullptr, *d_n = nullptr;
-  float *d_gm = nullptr, *d_lp = nullptr;
-  auto release = [&]() { hipFree(d_req); hipFree(d_gen); hipFree(d_out); hipFree(d_n); hipFree(d_gm); hipFree(d_lp); };
-  auto run = [&]() -> int {
-    HIPCHK(c, hipMalloc((void**)&d_req, n_rows * sizeof(long long)));
-    HIPCHK(c, hipMalloc((void**)&d_gen, n_rows * sizeof(int)));
-    HIPCHK(c, hipMalloc((void**)&d_out, n_rows * sizeof(int)));
-    HIPCHK(c, hipMalloc((void**)&d_n, 2 * sizeof(int)));
-    if (out_logprobs) HIPCHK(c, hipMalloc((void**)&d_lp, n_rows * sizeof(float)));
-    HIPCHK(c, hipMemset(d_n, 0, 2 * sizeof(int)));
-    HIPCHK(c, hipMemcpy(d_req, request_ids, n_rows * sizeof(long long), hipMemcpyHostToDevice));
-    HIPCHK(c, hipMemcpy(d_gen, gen_index, n_rows * sizeof(int), hipMemcpyHostToDevice));
-    HIPCHK(c, hipMemcpy(d_n, &n_rows, sizeof(int), hipMemcpyHostToDevice));
-    RowCtx rc{nullptr, nullptr, reinterpret_cast<const int2*>(d_n), n_rows};
-    const SamplerCfg sc = sampler_cfg(c);
-    // same candidate search as the rollout path: group maxima first when the vocabulary allows
-    const int grp = lmhead_group_cols();
-    if (c->dm.vocab % grp == 0) {
-      HIPCHK(c, hipMalloc((void**)&d_gm, (size_t)n_rows * (c->dm.vocab / grp) * sizeof(float)));
-      launch_group_max(c->stream, logits, n_rows, c->dm.vocab, grp, d_gm);
-    }
-    launch_sample(c->stream, rc, c->ds, nullptr, logits, c->dm.vocab, sc, Watch{}, 0, d_req, d_gen, d_out, d_gm, grp, d_lp);
+  // The temporaries stay with the context (until april_destroy) and rows go through in parts that keep
+  // them within 64 MiB: allocating and releasing them took 8 calls that synchronise the device, about 70 of
+  // the 700 us of a call for 192 rows of 152 k logits.  Records of one part: row keys (packed: one
+  // copy in, one copy out), then the group records.
+  const int V = c->dm.vocab, grp = lmhead_group_cols(), n_groups = ceil_div(V, grp);
+  const SamplerCfg sc = sampler_cfg(c);
+  // sums: the categorical sampler's (fp64 exponentials) serve the log-probabilities too
+  const int sums = sc.kind == APRIL_SAMPLER_CATEGORICAL ? 2 : (out_logprobs ? 1 : 0);
+  const size_t row_bytes = (size_t)n_groups * (sums ? 12 : 4) + 24;
+  const int part_rows = (int)std::max<size_t>(1, std::min<size_t>({(size_t)n_rows, 16384, ((size_t)64 << 20) / row_bytes}));
+  const size_t off_gen = 8 + (size_t)part_rows * 8, off_out = off_gen + (size_t)part_rows * 4, off_lp = off_out + (size_t)part_rows * 4;
+  const size_t off_gs = (off_lp + (size_t)part_rows * 4 + 255) / 256 * 256, off_gm = off_gs + (sums ? (size_t)part_rows * n_groups * 8 : 0);
+  const size_t need = off_gm + (size_t)part_rows * n_groups * 4;
+  if (need > c->sr_ws_bytes) {
     HIPCHK(c, hipStreamSynchronize(c->stream));
-    HIPCHK(c, hipMemcpy(out_tokens, d_out, n_rows * sizeof(int), hipMemcpyDeviceToHost));
-    if (out_logprobs) HIPCHK(c, hipMemcpy(out_logprobs, d_lp, n_rows * sizeof(float), hipMemcpyDeviceToHost));
-    return APRIL_OK;
-  };
-  const int rc_ = run();
-  release();
-  return rc_;
+    if (c->sr_ws) { hipFree(c->sr_ws); c->sr_ws = nullptr; c->sr_ws_bytes = 0; }
+    if (hipMalloc((void**)&c->sr_ws, need) != hipSuccess) return fail(c, APRIL_ENOMEM, "sampler workspace (%zu bytes)", need);
+    c->sr_ws_bytes = need;
+  }
+  char* w = c->sr_ws;
+  std::vector<char> stage(off_lp + (size_t)part_rows * 4);
+  for (int r0 = 0; r0 < n_rows; r0 += part_rows) {
+    const int n = std::min(part_rows, n_rows - r0);
+    const int ctl[2] = {n, 0};
+    memcpy(stage.data(), ctl, 8);
+    memcpy(stage.data() + 8, request_ids + r0, (size_t)n * 8);
+    memcpy(stage.data() + off_gen, gen_index + r0, (size_t)n * 4);
+    // (hipMemcpy on the null stream: also orders this call behind the caller's work on that stream,
+    // which may still be producing the logits)
+    HIPCHK(c, hipMemcpy(w, stage.data(), off_out, hipMemcpyHostToDevice));
+    const float* lg = logits + (size_t)r0 * V;
+    float* gm = reinterpret_cast<float*>(w + off_gm);
+    double* gs = sums ? reinterpret_cast<double*>(w + off_gs) : nullptr;
+    float* lp = out_logprobs ? reinterpret_cast<float*>(w + off_lp) : nullptr;
+    launch_group_records(c->stream, lg, nullptr, n, V, sums, sc.temperature, gm, gs);
+    launch_sample(c->stream, RowCtx{nullptr, nullptr, reinterpret_cast<const int2*>(w), n}, c->ds, nullptr, lg, V, sc, Watch{}, 0,
+                  reinterpret_cast<const long long*>(w + 8), reinterpret_cast<const int*>(w + off_gen),
+                  reinterpret_cast<int*>(w + off_out), gm, grp, lp, nullptr, gs);
+    HIPCHK(c, hipMemcpyAsync(stage.data() + off_out, w + off_out, off_lp + (lp ? (size_t)part_rows * 4 : 0) - off_out, hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(c, hipStreamSynchronize(c->stream));
+    memcpy(out_tokens + r0, stage.data() + off_out, (size_t)n * 4);
+    if (lp) memcpy(out_logprobs + r0, stage.data() + off_lp, (size_t)n * 4);
+  }
+  return APRIL_OK;
 }
 int april_sample_rows(april_ctx* c, const float* logits, int32_t n_rows, const int64_t* request_ids,
                       const int32_t* gen_index, int32_t* out_tokens) {
@@ -1314,31 +1341,37 @@ int april_sample_rows_logprobs(april_ctx* c, const float* logits, int32_t n_rows
 int april_sample_rows_noalloc(april_ctx* c, const float* logits, int32_t n_rows, const int64_t* request_ids,
                               const int32_t* gen_index, int32_t* out_tokens) {
   if (!c || !logits || !request_ids || !gen_index || !out_tokens || n_rows <= 0) return APRIL_EINVAL;
-  const int grp = lmhead_group_cols();
-  const bool use_gm = c->dm.vocab % grp == 0;
+  const int grp = lmhead_group_cols(), V = c->dm.vocab;
+  const size_t n_records = (size_t)n_rows * ceil_div(V, grp);
   if ((size_t)n_rows > NOALLOC_MAX_ROWS)
     return fail(c, APRIL_EINVAL, "april_sample_rows_noalloc: %d rows, at most %zu", n_rows, NOALLOC_MAX_ROWS);
-  if (use_gm && (size_t)n_rows * (size_t)(c->dm.vocab / grp) > NOALLOC_MAX_GROUP_MAX)
-    return fail(c, APRIL_EINVAL, "april_sample_rows_noalloc: rows x vocab/%d = %zu exceeds the scratch (%zu)", grp,
-                (size_t)n_rows * (size_t)(c->dm.vocab / grp), NOALLOC_MAX_GROUP_MAX);
+  if (V % grp == 0 && n_records > NOALLOC_MAX_GROUP_MAX)
+    return fail(c, APRIL_EINVAL, "april_sample_rows_noalloc: rows x vocab/%d = %zu exceeds the scratch (%zu)", grp, n_records, NOALLOC_MAX_GROUP_MAX);
+  // (a vocabulary that 64 does not divide has no such limit: beyond the scratch the sampler reads whole rows)
+  const bool use_gm = n_records <= NOALLOC_MAX_GROUP_MAX;
   if (!c->scratch_dev) return fail(c, APRIL_EDEVICE, "scratch address was not resolved at april_init");
   unsigned char* sp = c->scratch_dev;
-  int* d_n = reinterpret_cast<int*>(sp + NOALLOC_OFF_CTL);
-  long long* d_req = reinterpret_cast<long long*>(sp + NOALLOC_OFF_REQ);
-  int* d_gen = reinterpret_cast<int*>(sp + NOALLOC_OFF_GEN);
-  int* d_out = reinterpret_cast<int*>(sp + NOALLOC_OFF_OUT);
-  float* d_gm = use_gm ? reinterpret_cast<float*>(sp + NOALLOC_OFF_GM) : nullptr;
-  hipStream_t st = c->stream;
-  const int ctl[2] = {n_rows, 0};                 // {rows, stop flag}: the array keeps the last call's contents
-  HIPCHK(c, hipMemcpyAsync(d_n, ctl, sizeof ctl, hipMemcpyHostToDevice, st));
-  HIPCHK(c, hipMemcpyAsync(d_req, request_ids, n_rows * sizeof(long long), hipMemcpyHostToDevice, st));
-  HIPCHK(c, hipMemcpyAsync(d_gen, gen_index, n_rows * sizeof(int), hipMemcpyHostToDevice, st));
-  RowCtx rc{nullptr, nullptr, reinterpret_cast<const int2*>(d_n), n_rows};
   const SamplerCfg sc = sampler_cfg(c);
-  if (use_gm) launch_group_max(st, logits, n_rows, c->dm.vocab, grp, d_gm);
-  launch_sample(st, rc, c->ds, nullptr, logits, c->dm.vocab, sc, Watch{}, 0, d_req, d_gen, d_out, d_gm, grp);
-  HIPCHK(c, hipMemcpyAsync(out_tokens, d_out, n_rows * sizeof(int), hipMemcpyDeviceToHost, st));
+  const int sums = use_gm && sc.kind == APRIL_SAMPLER_CATEGORICAL ? 2 : 0;
+  float* d_gm = use_gm ? reinterpret_cast<float*>(sp + NOALLOC_OFF_GM) : nullptr;
+  double* d_gs = sums ? reinterpret_cast<double*>(sp + NOALLOC_OFF_GS) : nullptr;
+  int* d_out = reinterpret_cast<int*>(sp + NOALLOC_OFF_OUT);
+  hipStream_t st = c->stream;
+  // control word and row keys through the context's pinned staging buffer, one copy, and the tokens
+  // back the same way (three pageable copies in and one out were 20 of a 5-row call's 62 us)
+  char* hs = reinterpret_cast<char*>(c->h_stage);
+  const int ctl[2] = {n_rows, 0};                 // {rows, stop flag}: the array keeps the last call's contents
+  memcpy(hs + NOALLOC_OFF_CTL, ctl, sizeof ctl);
+  memcpy(hs + NOALLOC_OFF_REQ, request_ids, n_rows * sizeof(long long));
+  memcpy(hs + NOALLOC_OFF_GEN, gen_index, n_rows * sizeof(int));
+  HIPCHK(c, hipMemcpyAsync(sp, hs, NOALLOC_OFF_GEN + n_rows * sizeof(int), hipMemcpyHostToDevice, st));
+  RowCtx rc{nullptr, nullptr, reinterpret_cast<const int2*>(sp + NOALLOC_OFF_CTL), n_rows};
+  if (use_gm) launch_group_records(st, logits, nullptr, n_rows, V, sums, sc.temperature, d_gm, d_gs);
+  launch_sample(st, rc, c->ds, nullptr, logits, V, sc, Watch{}, 0, reinterpret_cast<const long long*>(sp + NOALLOC_OFF_REQ),
+                reinterpret_cast<const int*>(sp + NOALLOC_OFF_GEN), d_out, d_gm, grp, nullptr, nullptr, d_gs);
+  HIPCHK(c, hipMemcpyAsync(hs + NOALLOC_OFF_OUT, d_out, n_rows * sizeof(int), hipMemcpyDeviceToHost, st));
   HIPCHK(c, hipStreamSynchronize(st));
+  memcpy(out_tokens, hs + NOALLOC_OFF_OUT, n_rows * sizeof(int));
   return APRIL_OK;
 }
 

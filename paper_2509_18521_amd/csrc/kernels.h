@@ -38,6 +38,45 @@ __device__ inline float rope_second(float a, float b, float c, float s) { return
 // result is rounded to bf16 right after, and the division was most of the SwiGLU epilogue.
 __device__ inline float silu_mul(float g, float u) { return g * u * __builtin_amdgcn_rcpf(1.0f + __expf(-g)); }
 
+// Record of one row's 64-column group of logits, from the two 32-column accumulator tiles of an LM
+// head wavefront (a, b; `two` = false: the vocabulary ends after the first): the maximum, the lowest
+// column that holds it, and - when `want_sum` - the sum of exp((l - maximum) * inv_t) over the group,
+// exponentials in fp32, added in fp64 in one fixed order.  nhalf: 4 * (lane / 32).  Both halves of a
+// lane pair return the group's values.  Shared by every LM head kernel, so all leave the same bits.
+__device__ __forceinline__ void group64_record(const f32x16& a, const f32x16& b, bool two, int nhalf, bool want_sum,
+                                               float inv_t, float& max_out, int& col_out, double& sum_out) {
+  float bv = -INFINITY;
+  int bn = 0;
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+#pragma unroll
+    for (int e = 0; e < 4; ++e)                   // increasing column: a strict comparison keeps the first maximum
+      if (a[4 * q + e] > bv) { bv = a[4 * q + e]; bn = 8 * q + nhalf + e; }
+  if (two) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (b[4 * q + e] > bv) { bv = b[4 * q + e]; bn = 32 + 8 * q + nhalf + e; }
+  }
+  const float ov = __shfl_xor(bv, 32, 64);
+  const int on = __shfl_xor(bn, 32, 64);
+  if (ov > bv || (ov == bv && on < bn)) { bv = ov; bn = on; }
+  max_out = bv;
+  col_out = bn;
+  if (want_sum) {
+    const float ref = bv == -INFINITY ? 0.f : bv;          // a group of -inf sums to zero, not to NaN
+    double s = 0.0;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) s += (double)__expf((a[e] - ref) * inv_t);
+    if (two) {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) s += (double)__expf((b[e] - ref) * inv_t);
+    }
+    sum_out = s + __shfl_xor(s, 32, 64);
+  }
+}
+
 // --- scheduler / allocator -------------------------------------------------
 // check_only = 1: only the "N complete => stop" test (end of a chunk of iterations).
 // row_cap / ctx_cap: the bounds the host sized this iteration's launches for (live rows, longest
@@ -56,6 +95,14 @@ void launch_free_slots(hipStream_t st, Ctrl* ctrl, Slots s, const int* slot_list
                        int* free_stack);
 void launch_init_free_stack(hipStream_t st, int* free_stack, int n_blocks);
 void launch_fill_i32(hipStream_t st, int* p, int v, size_t n);
+
+// Group records an LM head leaves: arrays [rows][ceil(V / lmhead_group_cols())].
+struct GroupOut {
+  float* max;        // maximum of the group
+  int* col;          // column inside the group that holds it, the lowest on ties (nullable)
+  double* sum;       // sum of exp((l - maximum) * inv_t) (nullable: not wanted)
+  float inv_t;
+};
 
 // --- model ------------------------------------------------------------------
 template <typename T>
@@ -165,15 +212,14 @@ bool launch_gemm_tile_swiglu_chain(hipStream_t st, RowCtx rc, const bf16_t* x, c
 bool launch_gemm_tile_chain_f32(hipStream_t st, RowCtx rc, const bf16_t* x, const bf16_t* Wp, float* out, int N, int K,
                                 int ksplit, size_t partial_stride);
 void launch_gemm_tile_logits(hipStream_t st, RowCtx rc, const bf16_t* x, const bf16_t* Wp, float* logits,
-                             float* group_max, int V, int K, int* group_idx = nullptr);
-// LM head: logits fp32 [rows][V] plus, per row, the maximum of every group of
-// lmhead_group_cols() consecutive logits (group_max [rows][V / group]); V % 64 == 0.
-// group_idx (nullable, same shape): the column inside the group that holds the maximum, the
-// lowest one on ties.  logits may be null: nothing but the group records is written then (all
-// the greedy sampler needs).
+                             const GroupOut& go, int V, int K);
+// LM head: logits fp32 [rows][V] plus, per row, records of every group of lmhead_group_cols()
+// consecutive logits (the last group of a vocabulary that is not a multiple of it is short).
+// logits may be null: nothing but the group records is written then (all the greedy sampler
+// needs, with or without log-probabilities).
 int lmhead_group_cols();
 void launch_gemm_mfma_logits(hipStream_t st, RowCtx rc, const bf16_t* x, const bf16_t* Wp, float* logits,
-                             float* group_max, int V, int K, int* group_idx = nullptr);
+                             const GroupOut& go, int V, int K);
 void launch_shuffle_weights(hipStream_t st, const bf16_t* src, bf16_t* dst, int N, int K);
 
 void launch_rope_table(hipStream_t st, float* cos_t, float* sin_t, int max_pos, int head_dim,
@@ -191,13 +237,21 @@ struct SamplerCfg {
 // (standalone sampler; req_ids/gen_idx arrays given explicitly).
 // group_max (nullable): per row the maxima of groups of `group` consecutive logits, as
 // written by launch_gemm_mfma_logits; lets the sampler look at a few groups only.
+// group_sum (nullable, with group_max): the groups' sums of exp((l - maximum) / T), which the
+// categorical sampler (fp64 exponentials: launch_group_records) and the log-probabilities need;
+// without it they read the whole row.
 // out_logprobs (nullable, update = 0): log softmax(logits / temperature)[token]; with update = 1
 // the log-probability goes to s.logprob when that array exists.
 void launch_sample(hipStream_t st, RowCtx rc, Slots s, Ctrl* ctrl, const float* logits, int vocab,
                    SamplerCfg sc, Watch w, int update, const long long* req_ids,
                    const int* gen_idx, int* out_tokens, const float* group_max, int group,
-                   float* out_logprobs = nullptr, const int* group_idx = nullptr);
+                   float* out_logprobs = nullptr, const int* group_idx = nullptr,
+                   const double* group_sum = nullptr);
 
-void launch_group_max(hipStream_t st, const float* logits, int n_rows, int V, int group, float* out);
+// Group records (groups of 64, the last one short if 64 does not divide V) of logits that are in
+// memory: maxima, and with `sums` 1 / 2 the sums of exp((l - maximum) / T) with fp32 / fp64
+// exponentials.  ctl (nullable): device {rows, stop}; n_rows bounds the launch.
+void launch_group_records(hipStream_t st, const float* logits, const int2* ctl, int n_rows, int V, int sums,
+                          float temperature, float* group_max, double* group_sum);
 
 }  // namespace april

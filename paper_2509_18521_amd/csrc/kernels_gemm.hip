@@ -43,6 +43,7 @@ struct NormFuse {
   int ssq_stride;        // rows per n-tile slab
   int n_ssq;             // consumer: number of slabs (= d_model / 32)
   float inv_d, eps;      // consumer
+  GroupOut go;           // EPI_LOGITS: group records
 };
 
 constexpr int KW4 = 4;       // wavefronts of a workgroup (template parameter KW); they split the k range among themselves
@@ -74,7 +75,11 @@ __device__ inline void gemm_group(const bf16x8* __restrict__ w0, const bf16x8* _
     if (NT > 1) wp[NT - 1] = w1 + (size_t)nt0 * KT * 64 + lane;
   } else {
 #pragma unroll
-    for (int i = 0; i < NT; ++i) wp[i] = w0 + (size_t)(nt0 + i) * KT * 64 + lane;
+    for (int i = 0; i < NT; ++i) {
+      int nt = nt0 + i;
+      if (EPI == EPI_LOGITS && nt >= (N >> 5)) nt = (N >> 5) - 1;   // vocabulary of an odd number of tiles: read, never written
+      wp[i] = w0 + (size_t)nt * KT * 64 + lane;
+    }
   }
   const bf16x8* xp[MTC];
 #pragma unroll
@@ -199,41 +204,31 @@ __device__ inline void gemm_group(const bf16x8* __restrict__ w0, const bf16x8* _
 
   const int mloc = lane & 31, nhalf = (lane >> 5) << 2;
   if (EPI == EPI_LOGITS) {
-    // per row: the maximum over this wavefront's NT*32 output columns (a group of the sampler's
-    // candidate search) and the column that holds it, the lowest one on ties: with those two the
-    // greedy sampler needs no logits at all.  (nf.ssq carries the index array here, or null.)
-    int* gidx = reinterpret_cast<int*>(nf.ssq);
+    // per row: the record of this wavefront's 64 output columns - maximum, its column, sum of
+    // exponentials.  With those the greedy sampler and its log-probabilities need no logits at all.
+    const bool two = nt0 + 1 < (N >> 5);
 #pragma unroll
     for (int jq = 0; jq < JT; ++jq) {
-      const int j = j0 + jq;
-      float bv = -INFINITY;
-      int bn = 0;
-#pragma unroll
-      for (int i = 0; i < NT; ++i)
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {             // increasing column: a strict comparison keeps the first maximum
-            const float v = res[i][jq][4 * q + e];
-            if (v > bv) { bv = v; bn = i * 32 + 8 * q + nhalf + e; }
-          }
-      const float ov = __shfl_xor(bv, 32, 64);
-      const int on = __shfl_xor(bn, 32, 64);
-      if (ov > bv || (ov == bv && on < bn)) { bv = ov; bn = on; }
-      const int m = (mt0 + j) * 32 + mloc;
+      float bv;
+      int bn;
+      double s = 0.0;
+      group64_record(res[0][jq], res[NT - 1][jq], two, nhalf, nf.go.sum != nullptr, nf.go.inv_t, bv, bn, s);
+      const int m = (mt0 + j0 + jq) * 32 + mloc;
       if (m < rows && lane < 32) {
-        const size_t gi = (size_t)m * (N / (32 * NT)) + nt0 / NT;
-        reinterpret_cast<float*>(act)[gi] = bv;
-        if (gidx) gidx[gi] = bn;
+        const size_t gi = (size_t)m * ((N + 63) >> 6) + (nt0 >> 1);
+        nf.go.max[gi] = bv;
+        if (nf.go.col) nf.go.col[gi] = bn;
+        if (nf.go.sum) nf.go.sum[gi] = s;
       }
     }
   }
   if (EPI == EPI_F32 || (EPI == EPI_LOGITS && out != nullptr)) {
 #pragma unroll
-    for (int i = 0; i < NT; ++i)
+    for (int i = 0; i < NT; ++i) {
+      if (EPI == EPI_LOGITS && nt0 + i >= (N >> 5)) continue;
 #pragma unroll
       for (int jq = 0; jq < JT; ++jq) {
-      const int j = j0 + jq;
+        const int j = j0 + jq;
         const int m = (mt0 + j) * 32 + mloc;
         float inv = 1.0f;
         if (NORM_IN && nf.ssq != nullptr) {          // fused norm: a k-split partial scales like the sum
@@ -251,6 +246,7 @@ __device__ inline void gemm_group(const bf16x8* __restrict__ w0, const bf16x8* _
           }
         }
       }
+    }
   } else if (EPI == EPI_RESID) {
     // out = residual stream (updated in place), act = gain-scaled bf16 copy for the next GEMM
 #pragma unroll
@@ -360,7 +356,7 @@ __global__ __launch_bounds__(64 * KW) void gemm_mfma_kernel(RowCtx rc, const bf1
 
 void launch_gemm_mfma(hipStream_t st, RowCtx rc, const bf16_t* x, const bf16_t* Wp, float* out, int N, int K,
                       int ksplit, size_t partial_stride, const float* ssq, int ssq_stride, float eps) {
-  const NormFuse nf{nullptr, const_cast<float*>(ssq), ssq_stride, K >> 5, 1.0f / (float)K, eps};
+  const NormFuse nf{nullptr, const_cast<float*>(ssq), ssq_stride, K >> 5, 1.0f / (float)K, eps, {}};
   constexpr int MT = 4;
   const int n_tiles = N >> 5;
   const int m_groups = ceil_div(ceil_div(rc.max_rows, 32), MT);
@@ -388,14 +384,13 @@ void launch_gemm_mfma(hipStream_t st, RowCtx rc, const bf16_t* x, const bf16_t* 
 int lmhead_group_cols() { return 64; }
 
 void launch_gemm_mfma_logits(hipStream_t st, RowCtx rc, const bf16_t* x, const bf16_t* Wp, float* logits,
-                             float* group_max, int V, int K, int* group_idx) {
+                             const GroupOut& go, int V, int K) {
   constexpr int MT = 4;
   const int n_tiles = V >> 5;
-  dim3 grid(ceil_div(n_tiles / 2, KW4), 1, ceil_div(ceil_div(rc.max_rows, 32), MT));
+  dim3 grid(ceil_div(ceil_div(n_tiles, 2), KW4), 1, ceil_div(ceil_div(rc.max_rows, 32), MT));
   hipLaunchKernelGGL((gemm_mfma_kernel<2, MT, EPI_LOGITS, false>), grid, dim3(64 * KW4), 0, st, rc,
-                     reinterpret_cast<const bf16x8*>(x), reinterpret_cast<const bf16x8*>(Wp), nullptr, logits,
-                     reinterpret_cast<bf16_t*>(group_max), V, K, 1, (size_t)0,
-                     NormFuse{nullptr, reinterpret_cast<float*>(group_idx), 0, 0, 0.f, 0.f});
+                     reinterpret_cast<const bf16x8*>(x), reinterpret_cast<const bf16x8*>(Wp), nullptr, logits, nullptr,
+                     V, K, 1, (size_t)0, NormFuse{nullptr, nullptr, 0, 0, 0.f, 0.f, go});
 }
 
 void launch_gemm_mfma_swiglu(hipStream_t st, RowCtx rc, const bf16_t* x, const bf16_t* Wg, const bf16_t* Wu,
@@ -403,7 +398,7 @@ void launch_gemm_mfma_swiglu(hipStream_t st, RowCtx rc, const bf16_t* x, const b
   constexpr int MT = 4;
   const int n_tiles = F >> 5;
   dim3 grid(n_tiles, 1, ceil_div(ceil_div(rc.max_rows, 32), MT));
-  NormFuse nf{nullptr, const_cast<float*>(ssq), ssq_stride, K >> 5, 1.0f / (float)K, eps};
+  NormFuse nf{nullptr, const_cast<float*>(ssq), ssq_stride, K >> 5, 1.0f / (float)K, eps, {}};
   hipLaunchKernelGGL((gemm_mfma_kernel<2, MT, EPI_SWIGLU, true>), grid, dim3(64 * KW4), 0, st, rc,
                      reinterpret_cast<const bf16x8*>(x), reinterpret_cast<const bf16x8*>(Wg),
                      reinterpret_cast<const bf16x8*>(Wu), nullptr, act, F, K, 1, (size_t)0, nf);
@@ -416,7 +411,7 @@ void launch_gemm_mfma_resid(hipStream_t st, RowCtx rc, const bf16_t* x, const bf
   const int n_tiles = N >> 5, m_tiles = ceil_div(rc.max_rows, 32);
   const bf16x8* xv = reinterpret_cast<const bf16x8*>(x);
   const bf16x8* wv = reinterpret_cast<const bf16x8*>(Wp);
-  NormFuse nf{gain, ssq, ssq_stride, 0, 0.f, 0.f};
+  NormFuse nf{gain, ssq, ssq_stride, 0, 0.f, 0.f, {}};
   // few n-tiles: one m-tile per workgroup for more workgroups (the weights are small then);
   // also while that stays within 512 workgroups (2560 columns at 129-192 rows: 13.3 us
   // against 14.1 us on average over a run)

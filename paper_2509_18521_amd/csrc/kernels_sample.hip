@@ -9,6 +9,12 @@
 // maximum is a logit), so only the groups whose maximum reaches it are read again.
 // Without group maxima (or if a candidate list overflows) a 4-pass radix select over
 // the whole row is used.
+//
+// Categorical sampling and the log-probabilities need sums over the whole row.  With one workgroup
+// per row reading the row again they took 55-94 us of every decode iteration (1-380 rows of
+// 152 k logits: latency at one row, 2 TB/s at many).  They now add per-group sums of exponentials
+// that whoever has the logits in registers leaves (LM head epilogue: fp32 exponentials, fp64 sums)
+// or that launch_group_records takes in one coalesced pass over all rows at once.
 #include "kernels.h"
 
 namespace april {
@@ -189,10 +195,12 @@ __global__ __launch_bounds__(SAMPLE_THREADS) void sample_kernel(RowCtx rc, Slots
                                                                 Watch w, int update, const long long* req_ids,
                                                                 const int* gen_idx, int* out_tokens,
                                                                 const float* group_max, int group,
-                                                                float* out_logprobs, const int* group_idx) {
+                                                                float* out_logprobs, const int* group_idx,
+                                                                const double* group_sum) {
   const int r = blockIdx.x;
   ROW_GUARD(rc, r);
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  const bool have_logits = logits != nullptr;
   const float* lg = logits + (size_t)r * V;
   __shared__ SampleShared sh;
 
@@ -207,15 +215,16 @@ __global__ __launch_bounds__(SAMPLE_THREADS) void sample_kernel(RowCtx rc, Slots
     req = req_ids[r];
     g = gen_idx[r];
   }
-  const int n_groups = group_max ? V / group : 0;
+  const int n_groups = group_max ? (V + group - 1) / group : 0;
   const float* gm = group_max ? group_max + (size_t)r * n_groups : nullptr;
+  const double* gs = group_sum ? group_sum + (size_t)r * n_groups : nullptr;
 
   if (sc.kind == 0 || (sc.kind == 1 && sc.top_k <= 1)) {
     // ---- greedy: maximum, lowest index on ties --------------------------------------
     if (gm) {
       const int gi = block_argmax(gm, n_groups, sh);               // lowest group holding the maximum
       // the column inside the group: left by the LM head, else looked up in the logits
-      const int li = group_idx ? group_idx[(size_t)r * n_groups + gi] : block_argmax(lg + (size_t)gi * group, group, sh);
+      const int li = group_idx ? group_idx[(size_t)r * n_groups + gi] : block_argmax(lg + (size_t)gi * group, min(group, V - gi * group), sh);
       __syncthreads();
       if (tid == 0) sh.choice = gi * group + li;
       __syncthreads();
@@ -224,15 +233,20 @@ __global__ __launch_bounds__(SAMPLE_THREADS) void sample_kernel(RowCtx rc, Slots
     }
   } else if (sc.kind == 2) {
     // ---- temperature sampling over the whole vocabulary: inverse CDF in index order ----------
-    // Thread t owns the indices [t * chunk, (t + 1) * chunk): its partial sum of exp((l - max) / T),
-    // an exclusive scan over the threads (wavefront scans, then wavefront totals in order), and the
-    // thread whose range holds the crossing of u * total walks its range.
+    // Thread t owns the units [t * chunk, (t + 1) * chunk) (groups when their sums are there, else
+    // single indices): its partial sum of exp((l - max) / T), an exclusive scan over the threads
+    // (wavefront scans, then wavefront totals in order), and the thread whose range holds the
+    // crossing of u * total finds the unit; a wavefront then walks a group's logits together.
     const float M = gm ? block_max_f32(gm, n_groups, sh) : block_max_f32(lg, V, sh);
     const double invT = 1.0 / (double)sc.temperature;
-    const int chunk = (V + SAMPLE_THREADS - 1) / SAMPLE_THREADS;
-    const int i0 = tid * chunk, i1 = (i0 + chunk < V) ? i0 + chunk : V;
+    const int units = gs ? n_groups : V;
+    const int chunk = (units + SAMPLE_THREADS - 1) / SAMPLE_THREADS;
+    const int i0 = tid * chunk, i1 = (i0 + chunk < units) ? i0 + chunk : units;
+    auto mass = [&](int i) {
+      return gs ? gs[i] * exp(((double)gm[i] - (double)M) * invT) : exp(((double)lg[i] - (double)M) * invT);
+    };
     double part = 0.0;
-    for (int i = i0; i < i1; ++i) part += exp(((double)lg[i] - (double)M) * invT);
+    for (int i = i0; i < i1; ++i) part += mass(i);
     double incl = part;                                     // inclusive scan inside the wavefront
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
@@ -254,16 +268,30 @@ __global__ __launch_bounds__(SAMPLE_THREADS) void sample_kernel(RowCtx rc, Slots
     const double u = (double)(w0 >> 8) * (1.0 / 16777216.0);
     const double target = u * total;                        // cumulative / total > u  <=>  cumulative > u * total
     const double lo = before + incl - part, hi = before + incl;
-    if (tid == 0) sh.choice = V - 1;                        // rounding leaves no crossing: the last index
+    if (tid == 0) { sh.choice = V - 1; sh.hot[0] = -1; }    // rounding leaves no crossing: the last index
     __syncthreads();
     if (i0 < i1 && lo <= target && hi > target) {
-      double c = lo;
+      double c = lo, below = lo;
       int pick = i1 - 1;
       for (int i = i0; i < i1; ++i) {
-        c += exp(((double)lg[i] - (double)M) * invT);
+        below = c;
+        c += mass(i);
         if (c > target) { pick = i; break; }
       }
-      sh.choice = pick;
+      if (gs) { sh.hot[0] = pick; sh.total_d = below; } else sh.choice = pick;
+    }
+    __syncthreads();
+    if (gs && wid == 0 && sh.hot[0] >= 0) {
+      // the group's logits, one per lane; its last index if rounding leaves no crossing inside it
+      const int first = sh.hot[0] * group, n = min(group, V - first);
+      double c = lane < n ? exp(((double)lg[first + lane] - (double)M) * invT) : 0.0;
+#pragma unroll
+      for (int off = 1; off < 64; off <<= 1) {
+        const double o = __shfl_up(c, off, 64);
+        if (lane >= off) c += o;
+      }
+      const unsigned long long hit = __ballot(lane < n && sh.total_d + c > target);
+      if (lane == 0) sh.choice = first + (hit ? __ffsll((long long)hit) - 1 : n - 1);
     }
     __syncthreads();
   } else {
@@ -285,6 +313,7 @@ __global__ __launch_bounds__(SAMPLE_THREADS) void sample_kernel(RowCtx rc, Slots
         const int n_hot = sh.n_hot;
         for (int e = tid; e < n_hot * group; e += SAMPLE_THREADS) {
           const int idx = sh.hot[e / group] * group + e % group;
+          if (idx >= V) continue;
           const unsigned key = f2key(lg[idx]);
           if (key >= tau) {
             const int p = atomicAdd(&sh.cnt, 1);
@@ -413,9 +442,14 @@ __global__ __launch_bounds__(SAMPLE_THREADS) void sample_kernel(RowCtx rc, Slots
     const float M = gm ? block_max_f32(gm, n_groups, sh) : block_max_f32(lg, V, sh);
     const float invT = 1.0f / sc.temperature;
     double part = 0.0;
-    for (int i = tid; i < V; i += SAMPLE_THREADS) part += (double)__expf((lg[i] - M) * invT);
+    if (gs) {
+      for (int i = tid; i < n_groups; i += SAMPLE_THREADS) part += gs[i] * exp((double)((gm[i] - M) * invT));
+    } else {
+      for (int i = tid; i < V; i += SAMPLE_THREADS) part += (double)__expf((lg[i] - M) * invT);
+    }
     const double Z = block_sum_f64(part, sh);
-    if (tid == 0) *lp_dst = (float)((double)((lg[tok_final] - M) * invT) - log(Z));
+    // the greedy choice is the row's maximum: its logit need not have been written
+    if (tid == 0) *lp_dst = (float)((double)((have_logits ? lg[tok_final] - M : 0.f) * invT) - log(Z));
   }
 
   if (tid == 0) {
@@ -442,28 +476,91 @@ __global__ __launch_bounds__(SAMPLE_THREADS) void sample_kernel(RowCtx rc, Slots
   }
 }
 
-// Maxima of groups of `group` consecutive logits (what the LM-head GEMM epilogue leaves),
-// for callers that bring their own logits.
-__global__ __launch_bounds__(256) void group_max_kernel(const float* logits, int n_rows, int V, int group, float* out) {
-  const int n_groups = V / group;
-  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= (size_t)n_rows * n_groups) return;
-  const size_t r = i / n_groups, gi = i % n_groups;
-  const float* p = logits + r * V + gi * group;
-  float m = p[0];
-  for (int j = 1; j < group; ++j) m = fmaxf(m, p[j]);
-  out[i] = m;
+// Group records of logits in memory.  16 lanes own a group of 64 logits (4 consecutive ones each), a
+// wavefront takes 4 groups per load and GR_STEPS loads in flight, so the pass streams.  (Before, one
+// thread per group walked 64 consecutive floats, and each thread of the row's workgroup 149 of them,
+// twice: a call for 192 rows of 152 k logits took 724 us with the categorical sampler and
+// log-probabilities, 94 us now; 5 rows with top-k 62 us, 42 us now.)  Rows start at any multiple of 4 bytes.  KEYS: maxima in
+// the order of f2key (NaN above everything), as the whole-row searches compare; else fmaxf.
+constexpr int GR_STEPS = 4;
+template <int SUMS, bool KEYS>
+__global__ __launch_bounds__(256) void group_records_kernel(const float* logits, const int2* ctl, int n_rows, int V,
+                                                            double inv_t, float* group_max, double* group_sum) {
+  const int r = blockIdx.y;
+  if (ctl != nullptr) {
+    const int2 v = *ctl;
+    n_rows = v.y ? 0 : v.x;
+  }
+  if (r >= n_rows) return;
+  typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+  const int n_groups = (V + 63) >> 6, lane = threadIdx.x & 63, sub = lane & 15;
+  const int g0 = ((int)blockIdx.x * 4 + (int)(threadIdx.x >> 6)) * (4 * GR_STEPS) + (lane >> 4);
+  const float* row = logits + (size_t)r * V;
+  float v[GR_STEPS][4];
+#pragma unroll
+  for (int s = 0; s < GR_STEPS; ++s) {
+    const int i = (g0 + 4 * s) * 64 + sub * 4;
+    if (i + 4 <= V) {
+      const f32x4u q = *reinterpret_cast<const f32x4u*>(row + i);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) v[s][j] = q[j];
+    } else {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) v[s][j] = i + j < V ? row[i + j] : -INFINITY;
+    }
+  }
+#pragma unroll
+  for (int s = 0; s < GR_STEPS; ++s) {
+    const int g = g0 + 4 * s;
+    float m;
+    if (KEYS) {
+      unsigned k = f2key(v[s][0]);
+      m = v[s][0];
+      auto take = [&](float x) { const unsigned kx = f2key(x); if (kx > k) { k = kx; m = x; } };
+#pragma unroll
+      for (int j = 1; j < 4; ++j) take(v[s][j]);
+#pragma unroll
+      for (int off = 8; off > 0; off >>= 1) take(__shfl_xor(m, off, 64));
+    } else {
+      m = fmaxf(fmaxf(v[s][0], v[s][1]), fmaxf(v[s][2], v[s][3]));
+#pragma unroll
+      for (int off = 8; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
+    }
+    double sum = 0.0;
+    if (SUMS) {
+      const float ref = m == -INFINITY ? 0.f : m;            // a group of -inf sums to zero, not to NaN
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        sum += SUMS == 2 ? exp(((double)v[s][j] - (double)ref) * inv_t) : (double)__expf((v[s][j] - ref) * (float)inv_t);
+#pragma unroll
+      for (int off = 8; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
+    }
+    if (sub == 0 && g < n_groups) {
+      group_max[(size_t)r * n_groups + g] = m;
+      if (SUMS) group_sum[(size_t)r * n_groups + g] = sum;
+    }
+  }
 }
-void launch_group_max(hipStream_t st, const float* logits, int n_rows, int V, int group, float* out) {
-  const size_t n = (size_t)n_rows * (V / group);
-  hipLaunchKernelGGL(group_max_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, logits, n_rows, V, group, out);
+void launch_group_records(hipStream_t st, const float* logits, const int2* ctl, int n_rows, int V, int sums,
+                          float temperature, float* group_max, double* group_sum) {
+  // grid.y holds the rows: at most 65535 of them per launch
+  const double inv_t = sums == 2 ? 1.0 / (double)temperature : (double)(1.0f / temperature);
+  dim3 grid(ceil_div((V + 63) / 64, 16 * GR_STEPS), n_rows);
+#define GR_LAUNCH(S, K) hipLaunchKernelGGL((group_records_kernel<S, K>), grid, dim3(256), 0, st, logits, ctl, n_rows, V, inv_t, group_max, group_sum)
+  const bool keys = V % 64 != 0;
+  switch (sums) {
+    case 0: if (keys) GR_LAUNCH(0, true); else GR_LAUNCH(0, false); break;
+    case 1: if (keys) GR_LAUNCH(1, true); else GR_LAUNCH(1, false); break;
+    default: if (keys) GR_LAUNCH(2, true); else GR_LAUNCH(2, false); break;
+  }
+#undef GR_LAUNCH
 }
 
 void launch_sample(hipStream_t st, RowCtx rc, Slots s, Ctrl* ctrl, const float* logits, int vocab, SamplerCfg sc,
                    Watch w, int update, const long long* req_ids, const int* gen_idx, int* out_tokens,
-                   const float* group_max, int group, float* out_logprobs, const int* group_idx) {
+                   const float* group_max, int group, float* out_logprobs, const int* group_idx, const double* group_sum) {
   hipLaunchKernelGGL(sample_kernel, dim3(rc.max_rows), dim3(SAMPLE_THREADS), 0, st, rc, s, ctrl, logits, vocab,
-                     sc, w, update, req_ids, gen_idx, out_tokens, group_max, group, out_logprobs, group_idx);
+                     sc, w, update, req_ids, gen_idx, out_tokens, group_max, group, out_logprobs, group_idx, group_sum);
 }
 
 }  // namespace april
