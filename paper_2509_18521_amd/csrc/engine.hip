@@ -1735,6 +1735,8 @@ int april_rollout_step(april_ctx* c, const april_request* new_reqs, int32_t n_ne
         rows += nt; ++nseq; ++pi;
         chunk_max_ctx = std::max(chunk_max_ctx, nt);
       }
+      // longest walks over the keys first, so that the launch drains on short ones
+      std::stable_sort(h_items, h_items + n_items, [](const int4& a, const int4& b) { return a.w > b.w; });
       c->step_max_ctx = chunk_max_ctx;
       h_n[0] = rows; h_n[1] = nseq;
       HIPCHK(c, hipMemcpyAsync(c->d_pf_row_slot, h_row_slot, rows * sizeof(int), hipMemcpyHostToDevice, st));

@@ -523,172 +523,210 @@ __global__ __launch_bounds__(64) void attn_merge_kernel(RowCtx rc, int row_base,
 // positions of one (sequence, KV head) and streams the keys / values 0 .. last position of the
 // tile once, for all of them and for all query heads of the KV head.
 //
-// Same transposed products as the decode kernel (S^T = K . Q^T, O^T = V^T . P^T on
-// v_mfma_f32_16x16x32_bf16), with the 16 columns of a product holding (position, head) pairs:
-// column = position_in_tile * GP + head, GP = heads per KV head rounded up to a power of two.
-// A wavefront keeps CT = 4 column tiles (its own positions: 64 / GP of them), so a K / V tile
-// fetched once feeds four products; the four wavefronts of a workgroup take consecutive groups
-// of positions and walk the same K / V tiles (second and later readers hit the L1 / L2).
-// Every column runs its own online softmax over the 32-token tiles in order; positions beyond
-// the column's own are masked.  A sequence's result does not depend on what else is in the
-// chunk.  (Its summation order differs from the decode kernel's; so does the prefill GEMM's.)
-// Column tiles per wavefront, measured on 16384-row chunks of 512-token prompts, head_dim 128,
-// 4 query heads per KV head: 4 tiles 452 us per launch, 2 tiles (two wavefronts per SIMD) 511 us,
-// 1 tile 498 us.
+// Transposed products as in the decode kernel, on v_mfma_f32_32x32x16_bf16:
+//   S^T[token, column] = K . Q^T,  O^T[dim, column] = V^T . P^T,
+// column = position_in_tile * GP + head, GP = heads per KV head rounded up to a power of two.  A
+// wavefront owns PF_CT = 2 tiles of 32 columns (64 / GP positions), the four wavefronts of a
+// workgroup consecutive positions.  The pages of a stage of 64 tokens are copied to LDS as they lie
+// (global_load_lds, two stage buffers, two workgroups per compute unit), and a fragment read from
+// there feeds both column tiles: with one, the LDS reads alone would take the matrix cores' time.
+//
+// Row r of the first product is given the token 16 (r / 16) + 8 ((r / 4) % 2) + 4 ((r / 8) % 2) + r % 4
+// (an address permutation of the K fragment), so that the accumulator registers 8 s .. 8 s + 7 of a
+// lane are the tokens 16 s + 8 (lane / 32) .. + 7: converted to bf16 in place they are the B operand
+// of the second product, whose V fragment is then one 16-byte read.
+//
+// Every column runs its own online softmax, in base 2 with the scale folded into one multiply-add
+// per score.  The running maximum may lag the true one by up to 2^8: the accumulators are rescaled
+// only when a column's maximum passes its running one by more (probabilities are then at most 256,
+// which costs no precision in bf16 or fp32), by exactly 1 for the columns that did not.  Each
+// lane sums its own tokens' probabilities; the halves of a column meet once at the end.  Positions beyond
+// the column's own are masked, in the stages that hold any.  A column's result depends on its own
+// prefix only.  (Its summation order differs from the decode kernel's; so does the prefill GEMM's.)
+//
+// Measured per launch of 16 k rows, against a kernel on 16x16x32 products whose wavefronts each
+// loaded every K / V fragment from the caches and rescaled in every 32-token step: prompts of
+// 4500-8000 tokens, 32 + 8 heads of 128, 2123 -> 879 us (640 TFLOP/s: the exponentials and
+// conversions of two wavefronts per SIMD beside the products); 900-4400 tokens, 14 + 2 heads of 64,
+// 468 -> 162 us; 1-1999 tokens, 32 + 8 heads of 128, 574 -> 258 us.
 // ---------------------------------------------------------------------------
-#ifndef PF_CT
-#define PF_CT 4
+__device__ inline void copy_piece_to_lds(const bf16x8* src_lane, bf16x8* lds_base) {   // 64 lanes x 16 bytes
+#if defined(__HIP_DEVICE_COMPILE__)
+  __builtin_amdgcn_global_load_lds(src_lane, lds_base, 16, 0, 0);
+#else
+  (void)src_lane; (void)lds_base;
 #endif
+}
+constexpr int PF_CT = 2;                  // column tiles of 32 per wavefront
+constexpr int PF_STAGE = 64;              // tokens per stage
+
 template <int DH, int GP>
-__global__ __launch_bounds__(256) void attn_prefill_kernel(const int4* __restrict__ items, Slots s,
-                                                           const float* __restrict__ q_rot,
-                                                           const bf16_t* __restrict__ kv_pool, KVLayout L, int layer,
-                                                           int Hq, bf16_t* __restrict__ out) {
-  constexpr int KC = DH / 32, DT = DH / 16, CT = PF_CT;
-  constexpr int PPT = 16 / GP;            // positions per column tile
+__global__ __launch_bounds__(256, 2) void attn_prefill_kernel(const int4* __restrict__ items, Slots s,
+                                                              const float* __restrict__ q_rot,
+                                                              const bf16_t* __restrict__ kv_pool, KVLayout L, int layer,
+                                                              int Hq, bf16_t* __restrict__ out) {
+  constexpr int KC = DH / 16, DT = DH / 32, CT = PF_CT, NP = PF_STAGE / 16;
+  constexpr int PPT = 32 / GP;            // positions per column tile
   constexpr int PPW = CT * PPT;           // positions per wavefront
+  constexpr int PIECES = DH / 32;         // KiB of K (or V) per page
+  constexpr float RESCALE = 8.0f;
+  __shared__ bf16x8 lds[2][2][NP][PIECES * 64];      // [buffer][K | V][page][16-byte piece]
   const int4 it = items[blockIdx.x];      // {slot, first row of the sequence, tokens of the sequence, first position of the tile}
   const int slot = it.x, row0 = it.y, nt = it.z, q0 = it.w;
   const int kvh = blockIdx.y;
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), hh = lane & 15, g = lane >> 4;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), cl = lane & 31, hf = lane >> 5;
   const int Hkv = L.n_kv_heads, G = Hq / Hkv;
-  const int wq0 = q0 + wave * PPW;        // this wavefront's first position
-  if (wq0 >= nt) return;                  // (no workgroup barrier below)
-  const int wlast = min(nt, wq0 + PPW) - 1;
+  const int wq0 = q0 + wave * PPW;        // this wavefront's first position (it may lie beyond the sequence: it then only copies)
+  const int wlast = wq0 < nt ? min(nt, wq0 + PPW) - 1 : -1;
+  const int glast = min(nt, q0 + 4 * PPW) - 1;       // last position of the workgroup
   const size_t blk_elems = (size_t)16 * DH;
   const bf16_t* kbase = kv_pool + (size_t)layer * L.layer_stride;
   const bf16_t* vbase = kbase + L.kv_stride;
   const int* bt = s.block_table + (size_t)slot * s.max_blocks;
-  const int last_page = wlast >> 4;
+  const int last_page = glast >> 4;
+  const int n_stages = glast / PF_STAGE + 1;
 
-  // query fragments: column hh of tile ct = (position, head)
+  int my_page = bt[lane < last_page ? lane : last_page];     // page ids of 16 stages, one per lane
+  auto issue = [&](int st) {
+    const int buf = st & 1;
+    bf16x8* base = &lds[buf][0][0][0];
+#pragma unroll
+    for (int u = 0; u < 2 * NP * PIECES / 4; ++u) {
+      const int idx = wave + 4 * u;                           // piece of the stage: [K | V][page][KiB]
+      const int kv = idx / (NP * PIECES), pg = (idx / PIECES) % NP, sub = idx % PIECES;
+      int pl = st * NP + pg;
+      pl = pl < last_page ? pl : last_page;                   // pages past the end re-read the last one (masked)
+      const int page = __builtin_amdgcn_readlane(my_page, __builtin_amdgcn_readfirstlane(pl) & 63);
+      const bf16_t* src = (kv ? vbase : kbase) + ((size_t)page * Hkv + kvh) * blk_elems + sub * 512;
+      copy_piece_to_lds(reinterpret_cast<const bf16x8*>(src) + lane, base + idx * 64);
+    }
+  };
+  issue(0);
+
+  // query fragments: column cl of tile ct = (position, head); lane half hf holds dims 16 c + 8 hf .. + 7
   int qpos[CT];
   bool qok[CT];
   bf16x8 qf[CT][KC];
 #pragma unroll
   for (int ct = 0; ct < CT; ++ct) {
-    const int p = wq0 + ct * PPT + hh / GP, h = hh % GP;
+    const int p = wq0 + ct * PPT + cl / GP, h = cl % GP;
     qok[ct] = p < nt && h < G;
     qpos[ct] = p < nt ? p : nt - 1;
     const int hc = h < G ? h : G - 1;
-    const float* q = q_rot + (size_t)(row0 + qpos[ct]) * Hq * DH + (size_t)(kvh * G + hc) * DH + 8 * g;
+    const float* q = q_rot + (size_t)(row0 + qpos[ct]) * Hq * DH + (size_t)(kvh * G + hc) * DH + 8 * hf;
 #pragma unroll
     for (int c = 0; c < KC; ++c) {
-      const f32x4 a = *reinterpret_cast<const f32x4*>(q + 32 * c), b = *reinterpret_cast<const f32x4*>(q + 32 * c + 4);
+      const f32x4 a = *reinterpret_cast<const f32x4*>(q + 16 * c), b = *reinterpret_cast<const f32x4*>(q + 16 * c + 4);
 #pragma unroll
       for (int j = 0; j < 4; ++j) { qf[ct][c][j] = qok[ct] ? (bf16_t)a[j] : (bf16_t)0.f; qf[ct][c][4 + j] = qok[ct] ? (bf16_t)b[j] : (bf16_t)0.f; }
     }
   }
-  const float scale = 1.0f / sqrtf((float)DH);
+  const float c2 = 1.4426950408889634f / sqrtf((float)DH);   // scores to base-2 exponents
   float m_run[CT], l_run[CT];
-  f32x4 oacc[CT][DT];
+  f32x16 oacc[CT][DT];
 #pragma unroll
   for (int ct = 0; ct < CT; ++ct) {
     m_run[ct] = -INFINITY; l_run[ct] = 0.f;
 #pragma unroll
-    for (int d = 0; d < DT; ++d) oacc[ct][d] = f32x4{};
+    for (int d = 0; d < DT; ++d) oacc[ct][d] = f32x16{};
   }
+  // K fragment: this lane's row of the product is token kt of page cl / 16 (see above)
+  const int kt = (((cl >> 2) & 1) << 3) + (((cl >> 3) & 1) << 2) + (cl & 3);
+  const int k_piece = kt + 16 * hf, v_piece = cl * 2 + hf;
 
-  const int n_tiles = (wlast >> 5) + 1;
-  int my_page = bt[lane < last_page ? lane : last_page];     // page ids of tiles 0..31 (64 pages), one per lane
-  auto load_tile = [&](int tile, bf16x8 (&kk)[2][KC], bf16x4 (&vv)[2][DT]) {
-#pragma unroll
-    for (int p = 0; p < 2; ++p) {
-      int pl = 2 * tile + p;
-      pl = pl < last_page ? pl : last_page;                   // a missing second page re-reads the last one (masked)
-      const int page = __builtin_amdgcn_readlane(my_page, __builtin_amdgcn_readfirstlane(pl) & 63);
-      const size_t off = ((size_t)page * Hkv + kvh) * blk_elems;
-      const bf16x8* kp = reinterpret_cast<const bf16x8*>(kbase + off);
-      const bf16x4* vp = reinterpret_cast<const bf16x4*>(vbase + off);
-#pragma unroll
-      for (int c = 0; c < KC; ++c) kk[p][c] = kp[c * 64 + lane];
-#pragma unroll
-      for (int d = 0; d < DT; ++d) vv[p][d] = vp[(d * 16 + hh) * 4 + g];
-    }
-  };
-  bf16x8 kf[2][KC];
-  bf16x4 vf[2][DT];
-  load_tile(0, kf, vf);
-  for (int tile = 0; tile < n_tiles; ++tile) {
-    bf16x8 kn[2][KC];
-    bf16x4 vn[2][DT];
-    const int nxt = tile + 1 < n_tiles ? tile + 1 : tile;
-    if ((nxt & 31) == 0 && nxt != tile) {                     // the next tile opens a new group of 64 pages
-      const int i = nxt * 2 + lane;
-      my_page = bt[i < last_page ? i : last_page];
-    }
-    load_tile(nxt, kn, vn);
-    __builtin_amdgcn_sched_barrier(0);
-    const int t0 = tile * 32;
-    bf16x8 af[DT];
-#pragma unroll
-    for (int d = 0; d < DT; ++d)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) { af[d][j] = vf[0][d][j]; af[d][4 + j] = vf[1][d][j]; }
-#pragma unroll
-    for (int ct = 0; ct < CT; ++ct) {
-      if (t0 > __builtin_amdgcn_readfirstlane(wq0 + ct * PPT + PPT - 1)) continue;   // the tile lies beyond every position of this column tile
-      f32x4 sacc[2];
-#pragma unroll
-      for (int p = 0; p < 2; ++p) {
-        sacc[p] = f32x4{};
-#pragma unroll
-        for (int c = 0; c < KC; ++c) sacc[p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[p][c], qf[ct][c], sacc[p], 0, 0, 0);
+  for (int st = 0; st < n_stages; ++st) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    __builtin_amdgcn_s_waitcnt(0x0f70);          // vmcnt(0): this wavefront's copies of the stage have landed
+#endif
+    __builtin_amdgcn_s_barrier();                // everyone's have, and everyone is done with the other buffer
+    asm volatile("" ::: "memory");
+    if (st + 1 < n_stages) {
+      if (((st + 1) & 15) == 0) {                // the next stage opens a new group of 64 pages
+        const int i = (st + 1) * NP + lane;
+        my_page = bt[i < last_page ? i : last_page];
       }
-      float sv[8], mx = -INFINITY;
+      issue(st + 1);
+    }
+    const int buf = st & 1;
 #pragma unroll
-      for (int p = 0; p < 2; ++p)
+    for (int half = 0; half < PF_STAGE / 32; ++half) {
+      const int t0 = st * PF_STAGE + half * 32;
+      if (t0 > wlast) continue;                  // beyond every position of this wavefront
+      const bf16x8* kl = &lds[buf][0][half * 2 + (cl >> 4)][k_piece];
+      f32x16 sacc[CT];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int tok = t0 + p * 16 + 4 * g + i;
-          const float v = tok <= qpos[ct] ? sacc[p][i] * scale : -INFINITY;
-          sv[p * 4 + i] = v;
-          mx = fmaxf(mx, v);
+      for (int ct = 0; ct < CT; ++ct) sacc[ct] = f32x16{};
+#pragma unroll
+      for (int c = 0; c < KC; ++c) {
+        const bf16x8 kf = kl[(c >> 1) * 64 + 32 * (c & 1)];
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) sacc[ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[ct][c], sacc[ct], 0, 0, 0);
+      }
+      bf16x8 pf[CT][2];
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct) {
+        if (t0 + 31 > wq0 + ct * PPT) {          // some column of the tile does not see all 32 tokens
+#pragma unroll
+          for (int i = 0; i < 16; ++i)
+            if (t0 + 16 * (i >> 3) + 8 * hf + (i & 7) > qpos[ct]) sacc[ct][i] = -INFINITY;
         }
-      mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-      const float m_new = fmaxf(m_run[ct], mx);               // finite from the first tile on: token 0 is visible to every position
-      const float corr = __expf(m_run[ct] - m_new);
-      float rs = 0.f;
-      bf16x8 pf;
+        float mx = sacc[ct][0];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const float pe = __expf(sv[e] - m_new);
-        rs += pe;
-        pf[e] = (bf16_t)pe;
+        for (int i = 1; i < 16; ++i) mx = fmaxf(mx, sacc[ct][i]);
+        mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * c2;
+        const bool grow = mx > m_run[ct] + RESCALE;           // always in the first tile: token 0 is visible to every position
+        if (__any(grow)) {
+          const float corr = grow ? __builtin_amdgcn_exp2f(m_run[ct] - mx) : 1.0f;
+          m_run[ct] = grow ? mx : m_run[ct];
+          l_run[ct] *= corr;
+#pragma unroll
+          for (int d = 0; d < DT; ++d) oacc[ct][d] *= corr;
+        }
+        float rs[2] = {0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const float pe = __builtin_amdgcn_exp2f(__fmaf_rn(sacc[ct][i], c2, -m_run[ct]));
+          rs[i & 1] += pe;
+          pf[ct][i >> 3][i & 7] = (bf16_t)pe;
+        }
+        l_run[ct] += rs[0] + rs[1];
       }
-      rs += __shfl_xor(rs, 16, 64);
-      rs += __shfl_xor(rs, 32, 64);
-      l_run[ct] = l_run[ct] * corr + rs;
-      m_run[ct] = m_new;
 #pragma unroll
-      for (int d = 0; d < DT; ++d) {
-        oacc[ct][d] *= corr;
-        oacc[ct][d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[d], pf, oacc[ct][d], 0, 0, 0);
-      }
+      for (int d = 0; d < DT; ++d)
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+          const bf16x8 vf = lds[buf][1][half * 2 + k][d * 64 + v_piece];
+#pragma unroll
+          for (int ct = 0; ct < CT; ++ct) oacc[ct][d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[ct][k], oacc[ct][d], 0, 0, 0);
+        }
     }
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int p = 0; p < 2; ++p) {
-#pragma unroll
-      for (int c = 0; c < KC; ++c) kf[p][c] = kn[p][c];
-#pragma unroll
-      for (int d = 0; d < DT; ++d) vf[p][d] = vn[p][d];
-    }
+    asm volatile("" ::: "memory");
   }
   const int K = Hq * DH;
 #pragma unroll
   for (int ct = 0; ct < CT; ++ct) {
-    if (!qok[ct]) continue;
-    const float inv = 1.0f / l_run[ct];
-    const int r = row0 + qpos[ct], h = hh % GP;
+    const float inv = 1.0f / (l_run[ct] + __shfl_xor(l_run[ct], 32, 64));
+    const int r = row0 + qpos[ct], h = cl % GP;
 #pragma unroll
-    for (int d = 0; d < DT; ++d) {
-      bf16x4 ob;
+    for (int d = 0; d < DT; ++d)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) ob[i] = (bf16_t)(oacc[ct][d][i] * inv);
-      *reinterpret_cast<bf16x4*>(out + act_index<true>(r, (kvh * G + h) * DH + d * 16 + 4 * g, K)) = ob;
-    }
+      for (int q = 0; q < 4; q += 2) {
+        // the lane halves hold alternating groups of 4 dims: they trade one, so that each stores 8
+        // consecutive dims (16 bytes of the fragment-tiled layout)
+        union { bf16x4 v[2]; unsigned u[4]; bf16x8 w; } own, st8;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          own.v[0][e] = (bf16_t)(oacc[ct][d][4 * q + e] * inv);
+          own.v[1][e] = (bf16_t)(oacc[ct][d][4 * q + 4 + e] * inv);
+        }
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          const unsigned give = hf ? own.u[e] : own.u[2 + e], got = __shfl_xor((int)give, 32, 64);
+          st8.u[e] = hf ? got : own.u[e];
+          st8.u[2 + e] = hf ? own.u[2 + e] : got;
+        }
+        if (qok[ct]) *reinterpret_cast<bf16x8*>(out + act_index<true>(r, (kvh * G + h) * DH + d * 32 + 8 * (q + hf), K)) = st8.w;
+      }
   }
 }
 
@@ -696,7 +734,7 @@ __global__ __launch_bounds__(256) void attn_prefill_kernel(const int4* __restric
 int attn_prefill_tile(int group) {
   int gp = 1;
   while (gp < group) gp <<= 1;
-  return 4 * PF_CT * (16 / gp);
+  return 4 * PF_CT * (32 / gp);
 }
 
 void launch_attn_prefill(hipStream_t st, const int4* items, int n_items, Slots s, const float* q_rot,
