@@ -11,6 +11,8 @@
 //     the previous stage run from the other LDS buffer; one barrier per stage;
 //   * every output element is one accumulator chain over k-tiles 0..K/16-1 in order, whatever
 //     the tile shape or the number of rows: results do not depend on the batch.
+#include <type_traits>
+
 #include "kernels.h"
 
 namespace april {
@@ -26,19 +28,21 @@ __device__ inline void tile_epilogue(f32x16 (&acc)[NTW][MTW], int nt0, int mt0, 
                                      const float* row_scale = nullptr, int scale_m0 = 0, const GroupOut* go = nullptr) {
   const int mloc = lane & 31, nhalf = (lane >> 5) << 2;
   if (EPI == TEPI_LOGITS) {
-    // a group is an aligned pair of weight tiles, which is what one wavefront holds (NTW == 2, nt0 even)
-    static_assert(EPI != TEPI_LOGITS || NTW == 2, "one 64-column group per wavefront");
-    if (nt0 < n_tiles) {
-      const bool two = nt0 + 1 < n_tiles;
+    // a group is an aligned pair of weight tiles (nt0 even): this wavefront holds NTW / 2 of them
+    static_assert(EPI != TEPI_LOGITS || NTW % 2 == 0, "64-column groups");
+#pragma unroll
+    for (int i = 0; i < NTW; i += 2) {
+      if (nt0 + i >= n_tiles) continue;
+      const bool two = nt0 + i + 1 < n_tiles;
 #pragma unroll
       for (int j = 0; j < MTW; ++j) {
         float bv;
         int bn;
         double s = 0.0;
-        group64_record(acc[0][j], acc[NTW - 1][j], two, nhalf, go->sum != nullptr, go->inv_t, bv, bn, s);
+        group64_record(acc[i][j], acc[NTW > 1 ? i + 1 : 0][j], two, nhalf, go->sum != nullptr, go->inv_t, bv, bn, s);
         const int m = (mt0 + j) * 32 + mloc;
         if (m < rows && lane < 32) {
-          const size_t gi = (size_t)m * ((N + 63) >> 6) + (nt0 >> 1);
+          const size_t gi = (size_t)m * ((N + 63) >> 6) + ((nt0 + i) >> 1);
           go->max[gi] = bv;
           if (go->col) go->col[gi] = bn;
           if (go->sum) go->sum[gi] = s;
@@ -443,6 +447,122 @@ __device__ __forceinline__ void tile_dma_body(RowCtx rc, const bf16x8* __restric
                                m0 + wm * MTW, rows, n_tiles, N, lane, out, act, scaled ? row_scale : nullptr, m0 * 32, &tn.go);
 }
 
+// The large tile: 256 x 256 outputs on 4 wavefronts of 128 x 128, one per SIMD.  8 wavefronts of
+// 128 x 64 read 6 fragments from LDS for 8 products, which with the copies into LDS is all of the
+// LDS bandwidth the products leave time for; 128 x 128 reads 8 for 16.  With nothing else
+// on the SIMD the wavefront hides its own latencies: the fragments of the next k-tile are read while the
+// products of this one run, across the stage boundary too, and the copies of the stage R - 1 ahead are
+// spread over the second k-tile's products.  One barrier per stage, in its middle: it makes stage s + 1
+// readable (every wavefront has waited for its own copies of it) and the slot of stage s - 1 free.
+// Measured at 16384 rows, 8 wavefronts of 128 x 64 against this: 2 x 14336 x 4096 with SiLU 1213 -> 1328
+// TFLOP/s, 4096 x 14336 1192 -> 1329, 6144 x 4096 1126 -> 1246, 6144 x 2560 896 -> 980 (there 400 MB of
+// fp32 output are 15 % of the time); a library product of 16384^3 reaches 1555.  With the reads or copies
+// inside branches, or a burst of copies after the barrier, it was 5 % slower than the 8 wavefronts.
+// Same accumulator chain per element as every kernel here (k-tiles in order).  K % 32 == 0.
+template <int EPI>
+__global__ __launch_bounds__(256, 1) void gemm_big_kernel(RowCtx rc, const bf16x8* __restrict__ x,
+                                                          const bf16x8* __restrict__ w0, const bf16x8* __restrict__ w1,
+                                                          float* __restrict__ out, bf16_t* __restrict__ act, int N, int K,
+                                                          GroupOut go) {
+  constexpr int MT = 8, NT = 8, MTW = 4, NTW = 4, BK = 2, R = 4, FR = MT + NT, PER = FR * BK / 4;
+  __shared__ bf16x8 lds[R][BK][FR][64];
+  const int rows = rows_or_zero(rc);
+  const int m0 = blockIdx.y * MT;
+  if (m0 * 32 >= rows) return;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave >> 1, wn = wave & 1;
+  const int KT = K >> 4, n_stages = KT / BK;
+  const int m_last = (rows - 1) >> 5, n_tiles = N >> 5;
+  // Fragment slot t of a k-tile: activation tile m0 + t, then weight slots; weight slot i belongs to
+  // wavefront column i / NTW (SwiGLU: its first half gate tiles, its second half the up tiles of the
+  // same features).  Tiles past the end are clamped for the loads and never stored.
+  auto slot_base = [&](int t) -> const bf16x8* {
+    if (t < MT) return x + (size_t)min(m0 + t, m_last) * KT * 64;
+    const int i = t - MT;
+    if (EPI == TEPI_SWIGLU) {
+      constexpr int H = NTW / 2;
+      const int col = i / NTW, ii = i % NTW;
+      return (ii < H ? w0 : w1) + (size_t)min((int)blockIdx.x * (NT / 2) + col * H + (ii < H ? ii : ii - H), n_tiles - 1) * KT * 64;
+    }
+    return w0 + (size_t)min((int)blockIdx.x * NT + i, n_tiles - 1) * KT * 64;
+  };
+  const int skk = wave & 1, st0 = wave >> 1;             // this wavefront copies k-tile skk of slots st0, st0 + 2, ...
+  const bf16x8* src[PER];                               // wavefront-uniform: scalar registers
+#pragma unroll
+  for (int u = 0; u < PER; ++u) src[u] = slot_base(st0 + 2 * u) + skk * 64;
+  auto copy = [&](int s, int u) {
+    // scalar base + 32-bit lane offset
+    copy_fragment_to_lds(reinterpret_cast<const bf16x8*>(reinterpret_cast<const char*>(src[u]) + (unsigned)(s * (BK * 1024) + lane * 16)),
+                         &lds[s & (R - 1)][skk][st0 + 2 * u][0]);
+  };
+
+  f32x16 acc[NTW][MTW];
+#pragma unroll
+  for (int i = 0; i < NTW; ++i)
+#pragma unroll
+    for (int j = 0; j < MTW; ++j) acc[i][j] = f32x16{};
+#pragma unroll
+  for (int r = 0; r < R - 1; ++r)
+    if (r < n_stages) {
+#pragma unroll
+      for (int u = 0; u < PER; ++u) copy(r, u);
+    }
+  bf16x8 a[2][NTW], b[2][MTW];
+  auto read = [&](int s, int kk) {
+    a[kk][0] = lds[s & (R - 1)][kk][MT + wn * NTW][lane];      // in the order the products want them
+#pragma unroll
+    for (int j = 0; j < MTW; ++j) b[kk][j] = lds[s & (R - 1)][kk][wm * MTW + j][lane];
+#pragma unroll
+    for (int i = 1; i < NTW; ++i) a[kk][i] = lds[s & (R - 1)][kk][MT + wn * NTW + i][lane];
+  };
+  auto products = [&](int kk) {
+#pragma unroll
+    for (int i = 0; i < NTW; ++i)
+#pragma unroll
+      for (int j = 0; j < MTW; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[kk][i], b[kk][j], acc[i][j], 0, 0, 0);
+  };
+  if (n_stages > R - 2) wait_vector_memory<(R - 2) * PER>(); else wait_vector_memory<0>();
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  read(0, 0);
+  // One stage.  STEADY: stage s + R - 1 exists.  (Reading k-tile 0 of stage s + 1 past the end fetches a
+  // slot's old contents, which nothing uses: the code stays free of branches between the products.)
+  auto stage = [&](int s, auto steady) {
+    constexpr bool STEADY = decltype(steady)::value;
+    read(s, 1);
+    products(0);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {                        // LDS reads between the first products: back before the last ones end
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+    }
+    __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);
+    // stage s + 1 has landed when at most the copies of the stages s + 2 .. s + R - 2 are outstanding
+    wait_vector_memory<STEADY ? (R - 3) * PER : 0>();
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    if (STEADY) {
+#pragma unroll
+      for (int u = 0; u < PER; ++u) copy(s + R - 1, u);
+    }
+    read(s + 1, 0);
+    products(1);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      if (STEADY) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+    }
+    __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);
+    asm volatile("" ::: "memory");
+  };
+  int s = 0;
+  for (; s + R - 1 < n_stages; ++s) stage(s, std::true_type{});
+  for (; s < n_stages; ++s) stage(s, std::false_type{});
+  tile_epilogue<MTW, NTW, EPI>(acc, blockIdx.x * (EPI == TEPI_SWIGLU ? NT / 2 : NT) + wn * (EPI == TEPI_SWIGLU ? NTW / 2 : NTW),
+                               m0 + wm * MTW, rows, n_tiles, N, lane, out, act, nullptr, m0 * 32, &go);
+}
+
 template <int WGM, int WGN, int MTW, int NTW, int BK, int R, int EPI>
 __global__ __launch_bounds__(64 * WGM * WGN) __attribute__((amdgpu_waves_per_eu(2)))
 void gemm_tile_dma_kernel(RowCtx rc, const bf16x8* __restrict__ x, const bf16x8* __restrict__ w0,
@@ -495,13 +615,12 @@ bool launch_moe_tile_down(hipStream_t st, RowCtx rc, const int* cnt, const int* 
   return true;
 }
 
-// Tile shapes.  WIDE: 256 x 256 outputs on 8 wavefronts (2 per SIMD, each 128 x 64), ring of
-// 4 stages of 32 values of k (128 KiB LDS).  NARROW: 256 x 128 on 4 wavefronts, ring of 3
+// Tile shapes.  WIDE: 256 x 256 outputs on 4 wavefronts (gemm_big_kernel, 128 KiB LDS).  NARROW: 256 x 128 on 4 wavefronts, ring of 3
 // (72 KiB, two workgroups per CU) - for few or ragged weight tiles and for short batches.
 // REGS: register-staged fallback for K not a multiple of 32.  Measured on MI355X, 8192 x
-// (2 x 14336) x 4096 fused gate/up: REGS 0.84, NARROW 0.99, WIDE 1.03 PFLOP/s.  The choice
+// (2 x 14336) x 4096 fused gate/up: REGS 0.84, NARROW 0.99, WIDE 1.3 PFLOP/s.  The choice
 // changes no result (see the header comment).
-#define TILE_WIDE(EPI) gemm_tile_dma_kernel<2, 4, 4, 2, 2, 4, EPI>
+#define TILE_WIDE(EPI) gemm_big_kernel<EPI>
 #define TILE_NARROW(EPI) gemm_tile_dma_kernel<2, 2, 4, 2, 2, 3, EPI>
 #define TILE_REGS(EPI) gemm_tile_kernel<2, 2, 4, 2, 2, EPI>
 
@@ -520,7 +639,7 @@ void launch_gemm_tile(hipStream_t st, RowCtx rc, const bf16_t* x, const bf16_t* 
     hipLaunchKernelGGL((TILE_REGS(TEPI_F32)), grid, dim3(256), 0, st, rc, xv, wv, nullptr, out, nullptr, N, K);
   } else if (wide_tile(n_tiles, 8, m_tiles)) {
     dim3 grid(ceil_div(n_tiles, 8), ceil_div(m_tiles, 8));
-    hipLaunchKernelGGL((TILE_WIDE(TEPI_F32)), grid, dim3(512), 0, st, rc, xv, wv, nullptr, out, nullptr, N, K, GroupOut{});
+    hipLaunchKernelGGL((TILE_WIDE(TEPI_F32)), grid, dim3(256), 0, st, rc, xv, wv, nullptr, out, nullptr, N, K, GroupOut{});
   } else {
     dim3 grid(ceil_div(n_tiles, 4), ceil_div(m_tiles, 8));
     hipLaunchKernelGGL((TILE_NARROW(TEPI_F32)), grid, dim3(256), 0, st, rc, xv, wv, nullptr, out, nullptr, N, K, GroupOut{});
@@ -538,7 +657,7 @@ void launch_gemm_tile_swiglu(hipStream_t st, RowCtx rc, const bf16_t* x, const b
     hipLaunchKernelGGL((TILE_REGS(TEPI_SWIGLU)), grid, dim3(256), 0, st, rc, xv, gv, uv, nullptr, act, F, K);
   } else if (wide_tile(f_tiles, 4, m_tiles)) {
     dim3 grid(ceil_div(f_tiles, 4), ceil_div(m_tiles, 8));
-    hipLaunchKernelGGL((TILE_WIDE(TEPI_SWIGLU)), grid, dim3(512), 0, st, rc, xv, gv, uv, nullptr, act, F, K, GroupOut{});
+    hipLaunchKernelGGL((TILE_WIDE(TEPI_SWIGLU)), grid, dim3(256), 0, st, rc, xv, gv, uv, nullptr, act, F, K, GroupOut{});
   } else {
     dim3 grid(ceil_div(f_tiles, 2), ceil_div(m_tiles, 8));
     hipLaunchKernelGGL((TILE_NARROW(TEPI_SWIGLU)), grid, dim3(256), 0, st, rc, xv, gv, uv, nullptr, act, F, K, GroupOut{});
@@ -614,7 +733,7 @@ void launch_gemm_tile_logits(hipStream_t st, RowCtx rc, const bf16_t* x, const b
                              const GroupOut& go, int V, int K) {
   const int n_tiles = V >> 5, m_tiles = ceil_div(rc.max_rows, 32);
   dim3 grid(ceil_div(n_tiles, 8), ceil_div(m_tiles, 8));
-  hipLaunchKernelGGL((TILE_WIDE(TEPI_LOGITS)), grid, dim3(512), 0, st, rc, reinterpret_cast<const bf16x8*>(x),
+  hipLaunchKernelGGL((TILE_WIDE(TEPI_LOGITS)), grid, dim3(256), 0, st, rc, reinterpret_cast<const bf16x8*>(x),
                      reinterpret_cast<const bf16x8*>(Wp), nullptr, logits, nullptr, V, K, go);
 }
 
