@@ -557,7 +557,7 @@ void forward(april_ctx* c, RowCtx rows, RowCtx srows, const int* gather, double 
     }
     else if (c->use_mfma) launch_gemm_mfma(st, rc, (const bf16_t*)x, w_s, out, N, K, ks, stride, ssq, (int)c->m_cap, m.rms_eps);
     else if (c->bf16) launch_gemm_ref<bf16_t, true>(st, rc, (const bf16_t*)x, (const bf16_t*)w_plain, out, N, K);
-    else launch_gemm_ref<float, false>(st, rc, (const float*)x, (const float*)w_plain, out, N, K);
+    else launch_gemm_f32(st, rc, (const float*)x, (const float*)w_plain, out, N, K);
   };
   bool normed_by_down = false;       // the previous layer's down projection already did this layer's first norm
   for (int l = 0; l < m.n_layers; ++l) {
@@ -599,7 +599,7 @@ void forward(april_ctx* c, RowCtx rows, RowCtx srows, const int* gather, double 
     } else {
       ProfScope p(c, KC_ATTN, C * 2.0 * nkv * e + B * nq * (4.0 + e), 4.0 * C * nq);
       if (c->bf16) launch_attn_ref<bf16_t, true>(st, rows, c->ds, c->q_rot, (const bf16_t*)c->kv_pool, c->kvl, l, Hq, (bf16_t*)c->attn_out);
-      else launch_attn_ref<float, false>(st, rows, c->ds, c->q_rot, (const float*)c->kv_pool, c->kvl, l, Hq, (float*)c->attn_out);
+      else launch_attn_f32(st, rows, c->ds, c->q_rot, (const float*)c->kv_pool, c->kvl, l, Hq, (float*)c->attn_out);
     }
     // decode, dense MLP: the output projection adds into the residual stream itself and hands the
     // gate/up GEMM un-normalised activations plus per-row sums of squares (no norm launch)
@@ -680,7 +680,7 @@ void forward(april_ctx* c, RowCtx rows, RowCtx srows, const int* gather, double 
     else if (c->use_mfma && c->group_max) launch_gemm_mfma_logits(st, srows, (const bf16_t*)c->hf, c->lm_head_s, lg_out, go, V, d);
     else if (c->use_mfma) launch_gemm_mfma(st, srows, (const bf16_t*)c->hf, c->lm_head_s, c->logits, V, d, 1, 0);
     else if (c->bf16) launch_gemm_ref<bf16_t, true>(st, srows, (const bf16_t*)c->hf, (const bf16_t*)c->lm_head, c->logits, V, d);
-    else launch_gemm_ref<float, false>(st, srows, (const float*)c->hf, (const float*)c->lm_head, c->logits, V, d);
+    else launch_gemm_f32(st, srows, (const float*)c->hf, (const float*)c->lm_head, c->logits, V, d);
   }
   {
     const bool fused = c->group_max && !c->write_logits;

@@ -182,6 +182,11 @@ void launch_attn_merge(hipStream_t st, RowCtx rc, int row_base, KVLayout kvl, in
 template <typename T, bool XF>
 void launch_silu_mul(hipStream_t st, RowCtx rc, const float* gu, int F, T* act);
 
+// fp32 path: attention over the plain KV layout (mode 0), GEMM over row-major operands.
+void launch_attn_f32(hipStream_t st, RowCtx rc, Slots s, const float* q_rot, const float* kv_pool, KVLayout kvl,
+                     int layer, int n_q_heads, float* out);
+void launch_gemm_f32(hipStream_t st, RowCtx rc, const float* x, const float* W, float* out, int N, int K);
+
 // out[m][n] = sum_k x[m][k] W[n][k]; plain row-major W; reference path.
 template <typename T, bool XF>
 void launch_gemm_ref(hipStream_t st, RowCtx rc, const T* x, const T* W, float* out, int N, int K);

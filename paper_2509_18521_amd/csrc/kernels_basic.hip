@@ -477,7 +477,7 @@ template void launch_rope_append<bf16_t>(hipStream_t, RowCtx, Slots, const float
 
 // ---------------------------------------------------------------------------
 // Reference paged attention: one wavefront per (row, query head), one cached token
-// per loop trip, online softmax.  Correctness path (fp32 configuration, bring-up).
+// per loop trip, online softmax.  Correctness path of the bf16 KV cache (debug switch).
 // ---------------------------------------------------------------------------
 template <typename T, bool XF>
 __global__ __launch_bounds__(64) void attn_ref_kernel(RowCtx rc, Slots s, const float* q_rot, const T* kv_pool,
@@ -516,8 +516,94 @@ void launch_attn_ref(hipStream_t st, RowCtx rc, Slots s, const float* q_rot, con
   hipLaunchKernelGGL((attn_ref_kernel<T, XF>), dim3(rc.max_rows, n_q_heads), dim3(64), 0, st, rc, s, q_rot,
                      kv_pool, kvl, layer, n_q_heads, out);
 }
-template void launch_attn_ref<float, false>(hipStream_t, RowCtx, Slots, const float*, const float*, KVLayout, int, int, float*);
 template void launch_attn_ref<bf16_t, true>(hipStream_t, RowCtx, Slots, const float*, const bf16_t*, KVLayout, int, int, bf16_t*);
+
+// ---------------------------------------------------------------------------
+// fp32 paged attention: one wavefront per (row, query head), 64 cached tokens per step.  The scores
+// of a step are one token per lane (each lane walks its token's key), the weighted sum of the values
+// one dimension per lane with 64 / DH tokens at a time, the probabilities broadcast from their
+// lanes.  A step's maximum and sum are shuffle trees, steps are joined by the online softmax in
+// token order: the sum's order depends on the row's own length only, in prefill and decode alike.
+// One token per trip (6 dependent shuffles, 2 exponentials and 2 loads each) took 38 us per launch
+// at 32 rows of 33-128 tokens; this takes 6.5 us (both with the 2 us that a profiler adds).
+// ---------------------------------------------------------------------------
+template <int DH>
+__global__ __launch_bounds__(64) void attn_f32_kernel(RowCtx rc, Slots s, const float* q_rot, const float* kv_pool,
+                                                      KVLayout L, int layer, int Hq, float* out) {
+  constexpr int TG = DH < 64 ? 64 / DH : 1;        // tokens side by side in the value product
+  constexpr int DL = DH > 64 ? DH / 64 : 1;        // dimensions per lane there
+  const int r = blockIdx.x, a = blockIdx.y;
+  ROW_GUARD(rc, r);
+  const int slot = rc.row_slot[r], ctx = rc.row_pos[r] + 1, lane = threadIdx.x;
+  const int kvh = a / (Hq / L.n_kv_heads);
+  __shared__ f32x4 sq[DH / 4];
+  const f32x4* q = reinterpret_cast<const f32x4*>(q_rot + (size_t)r * Hq * DH + a * DH);
+  if (lane < DH / 4) sq[lane] = q[lane];
+  __syncthreads();
+  const float scale = 1.0f / sqrtf((float)DH);
+  const int* bt = s.block_table + (size_t)slot * s.max_blocks;
+  const int vd = (lane % (DH / DL)) * DL, vt = lane / (DH / DL);      // this lane's dimensions and token residue
+  float m = -INFINITY, l = 0.f, o[DL] = {};
+  for (int j0 = 0; j0 < ctx; j0 += 64) {
+    const int j = j0 + lane, n = min(64, ctx - j0);
+    const bool live = lane < n;
+    const int page = bt[(live ? j : ctx - 1) >> 4];
+    const f32x4* k = reinterpret_cast<const f32x4*>(kv_pool + L.at(layer, 0, page, kvh, (live ? j : ctx - 1) & 15, 0));
+    float acc[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int c = 0; c < DH / 4; ++c) {
+      const f32x4 kv = k[c], qv = sq[c];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[e] = __fmaf_rn(kv[e], qv[e], acc[e]);
+    }
+    const float sc = live ? ((acc[0] + acc[1]) + (acc[2] + acc[3])) * scale : -INFINITY;
+    float mx = sc;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
+    const float m_new = fmaxf(m, mx), corr = expf(m - m_new), p = live ? expf(sc - m_new) : 0.f;
+    l = l * corr + wave_sum(p);
+    m = m_new;
+    float add[DL] = {};
+    for (int t0 = 0; t0 < n; t0 += 16 * TG) {        // 16 loads in flight; tokens past the end add nothing
+      float v[16][DL], pt[16];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) {
+        const int tt = min(t0 + u * TG + vt, n - 1);
+        pt[u] = __shfl(p, tt, 64);
+        const int vp = __shfl(page, tt, 64);
+        const float* src = kv_pool + L.at(layer, 1, vp, kvh, (j0 + tt) & 15, vd);
+#pragma unroll
+        for (int e = 0; e < DL; ++e) v[u][e] = src[e];
+      }
+#pragma unroll
+      for (int u = 0; u < 16; ++u)
+#pragma unroll
+        for (int e = 0; e < DL; ++e)
+          add[e] = t0 + u * TG + vt < n ? __fmaf_rn(pt[u], v[u][e], add[e]) : add[e];
+    }
+#pragma unroll
+    for (int e = 0; e < DL; ++e) {
+#pragma unroll
+      for (int off = 32; off >= DH && off > 0; off >>= 1) add[e] += __shfl_xor(add[e], off, 64);
+      o[e] = o[e] * corr + add[e];
+    }
+  }
+  if (vt == 0) {
+#pragma unroll
+    for (int e = 0; e < DL; ++e) out[(size_t)r * Hq * DH + a * DH + vd + e] = o[e] / l;
+  }
+}
+void launch_attn_f32(hipStream_t st, RowCtx rc, Slots s, const float* q_rot, const float* kv_pool, KVLayout kvl, int layer,
+                     int n_q_heads, float* out) {
+  dim3 grid(rc.max_rows, n_q_heads);
+#define ATT_F32(DH) hipLaunchKernelGGL((attn_f32_kernel<DH>), grid, dim3(64), 0, st, rc, s, q_rot, kv_pool, kvl, layer, n_q_heads, out)
+  switch (kvl.head_dim) {
+    case 32: ATT_F32(32); break;
+    case 64: ATT_F32(64); break;
+    default: ATT_F32(128); break;
+  }
+#undef ATT_F32
+}
 
 // ---------------------------------------------------------------------------
 // act = silu(gate) * up from gu fp32 [rows][2F] (gate columns first, then up).
@@ -569,7 +655,67 @@ void launch_gemm_ref(hipStream_t st, RowCtx rc, const T* x, const T* W, float* o
   hipLaunchKernelGGL((gemm_ref_kernel<T, XF>), dim3(ceil_div(N, 4), ceil_div(rc.max_rows, 8)), dim3(256), 0, st,
                      rc, x, W, out, N, K);
 }
-template void launch_gemm_ref<float, false>(hipStream_t, RowCtx, const float*, const float*, float*, int, int);
 template void launch_gemm_ref<bf16_t, true>(hipStream_t, RowCtx, const bf16_t*, const bf16_t*, float*, int, int);
+
+// ---------------------------------------------------------------------------
+// fp32 GEMM: out[m][n] = sum_k x[m][k] W[n][k] on v_mfma_f32_16x16x4_f32 (full fp32 products and sums).
+// A workgroup owns 16 columns x 16 rows, its 4 wavefronts a quarter of k each; a lane fetches 4
+// consecutive k of its row of either operand (whole 64-byte pieces of the matrices, several steps in
+// flight) and the products take element j of both, each j in its own accumulator: short chains, added
+// pairwise, then the wavefronts through LDS.  An element's chain depends on K only.  One wavefront per
+// column with a 6-step shuffle sum per row took 11 us per launch on the 128-wide fp32
+// configuration (24 rows in decode, 768 in prefill); this takes 5.4 us.
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(256) void gemm_f32_kernel(RowCtx rc, const float* __restrict__ x, const float* __restrict__ W,
+                                                       float* __restrict__ out, int N, int K) {
+  typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+  __shared__ f32x4 red[3][64];
+  const int rows = rows_or_zero(rc);
+  const int m0 = blockIdx.y * 16, n0 = blockIdx.x * 16;
+  if (m0 >= rows) return;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), c = lane & 15, kq = (lane >> 4) * 4;
+  const float* wp = W + (size_t)min(n0 + c, N - 1) * K;
+  const float* xp = x + (size_t)min(m0 + c, rows - 1) * K;
+  const int steps = (K + 15) >> 4, s0 = steps * wave / 4, s1 = steps * (wave + 1) / 4;
+  auto fetch = [&](const float* p, int k) -> f32x4 {
+    if (k + 4 <= K) return *reinterpret_cast<const f32x4u*>(p + k);
+    f32x4 v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) if (k + e < K) v[e] = p[k + e];
+    return v;
+  };
+  f32x4 acc[4] = {f32x4{}, f32x4{}, f32x4{}, f32x4{}};
+  constexpr int U = 8;
+  for (int st = s0; st < s1; st += U) {
+    f32x4 a[U], b[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int k = min(st + u, s1 - 1) * 16 + kq;
+      a[u] = fetch(wp, k);
+      b[u] = fetch(xp, k);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (st + u < s1) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][e], b[u][e], acc[e], 0, 0, 0);
+      }
+  }
+  f32x4 v = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+  if (wave > 0) red[wave - 1][lane] = v;
+  __syncthreads();
+  if (wave > 0) return;
+  v = (v + red[0][lane]) + (red[1][lane] + red[2][lane]);
+  const int m = m0 + c, n = n0 + kq;                 // accumulator: column = row m of x, rows = 4 consecutive n
+  if (m < rows) {
+    float* o = out + (size_t)m * N + n;
+    if (n + 4 <= N) *reinterpret_cast<f32x4u*>(o) = v;
+    else
+      for (int e = 0; e < 4; ++e) if (n + e < N) o[e] = v[e];
+  }
+}
+void launch_gemm_f32(hipStream_t st, RowCtx rc, const float* x, const float* W, float* out, int N, int K) {
+  hipLaunchKernelGGL(gemm_f32_kernel, dim3(ceil_div(N, 16), ceil_div(rc.max_rows, 16)), dim3(256), 0, st, rc, x, W, out, N, K);
+}
 
 }  // namespace april

@@ -1,0 +1,45 @@
+"""The fp32 kernels against the oracle at ragged sizes: inner dimensions that 4 or 16 do not divide, one
+output column, contexts around the attention's steps of 64 tokens, every head size.
+Bound: a dot product of at most 200 fp32 terms of size about 1 (2^-24 x sqrt(200) relative), a dozen of
+them in a row, on logits of size below 10: 1e-4, as for the other fp32 comparisons."""
+import numpy as np
+import pytest
+
+import april_inputs as ai
+from gpu_common import have_gpu, make_engine, req_dicts
+from oracle.model import Decoder
+
+pytestmark = pytest.mark.gpu
+LENGTHS = [1, 2, 15, 17, 63, 64, 65, 127, 129, 200]
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _need_gpu():
+    if not have_gpu():
+        pytest.skip("no GPU")
+
+
+@pytest.mark.parametrize("head_dim,n_q,n_kv,d_model,d_ffn,vocab", [
+    (32, 3, 1, 40, 13, 37), (64, 2, 2, 8, 1, 1), (128, 4, 2, 72, 50, 130), (32, 4, 4, 128, 200, 257)])
+def test_ragged_fp32_models(head_dim, n_q, n_kv, d_model, d_ffn, vocab):
+    import paper_2509_18521_amd as ap
+    shape = ai.ModelShape(2, d_model, n_q, n_kv, head_dim, d_ffn, vocab, dtype=ai.DTYPE_FP32)
+    n, gen = len(LENGTHS), 4
+    w = ai.Workload("fp32", shape, 1, max(LENGTHS), n, n, gen, 0.0, 0.1, gen, gen, ai.SAMPLER_GREEDY, 0, 1, 7)
+    weights = ai.make_weights(shape, w.seed)
+    rng = np.random.default_rng(d_model)
+    reqs = [ai.Request(i, rng.integers(0, vocab, t, dtype=np.int32), gen) for i, t in enumerate(LENGTHS)]
+    forced = {i: rng.integers(0, vocab, gen, dtype=np.int32) for i in range(n)}
+    dec = Decoder(shape, weights)
+    ctx = make_engine(w, weights, debug=True)
+    try:
+        for r in reqs:
+            ap.april_debug_watch(ctx, r.request_id, 0, gen)
+        ap.april_rollout_step(ctx, req_dicts(reqs, forced), n, n, gen)
+        for r in reqs:
+            ref = dec.forward_block(np.concatenate([r.tokens, forced[r.request_id][:-1]]), dec.new_cache())[-gen:]
+            for g in range(gen):
+                got, _ = ap.april_debug_logits(ctx, r.request_id, g, vocab)
+                assert np.max(np.abs(got - ref[g])) <= 1e-4, (len(r.tokens), g)
+    finally:
+        ap.april_destroy(ctx)
