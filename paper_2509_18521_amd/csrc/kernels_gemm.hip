@@ -51,16 +51,15 @@ constexpr int KW4 = 4;       // wavefronts of a workgroup (template parameter KW
 // One workgroup: NT weight tiles x MTC activation tiles over k-tiles [k0, k1).  Each of
 // the KW wavefronts accumulates a quarter of the k range, the partial accumulators are
 // summed through LDS in a fixed tree order, wavefront 0 runs the epilogue.
-template <int NT, int MTC, int EPI, bool INTRA, int KW>
+template <int NT, int MTC, int EPI, bool INTRA, int KW, int KH>
 __device__ inline void gemm_group(const bf16x8* __restrict__ w0, const bf16x8* __restrict__ w1,
                                   const bf16x8* __restrict__ x, int KT, int k0, int k1, int nt0, int mt0,
                                   int rows, int N, float* __restrict__ out, bf16_t* __restrict__ act,
                                   float* red, float* ssp, const NormFuse& nf) {
-  // k-tiles per fetch group: two groups fill the register file (4 VGPRs per fragment).  The
-  // next group is requested before the MFMAs of the current one, so a wavefront whose k range
-  // fits in two groups has all of it in flight at once, and a longer range streams with one
-  // group always in flight behind the arithmetic.
-  constexpr int KH = (NT + MTC) <= 4 ? 8 : ((NT + MTC) == 5 ? 7 : ((NT + MTC) == 6 ? 5 : 3));
+  // KH k-tiles per fetch group, two groups in registers (4 VGPRs per fragment).  The next group is
+  // requested before the MFMAs of the current one, so a wavefront whose k range fits in two
+  // groups has all of it in flight at once, and a longer range streams with one group always in
+  // flight behind the arithmetic.
   // the wavefront index is uniform: keep it (and the k range derived from it) in scalar registers
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   f32x16 acc[NT][MTC];
@@ -250,31 +249,32 @@ __device__ inline void gemm_group(const bf16x8* __restrict__ w0, const bf16x8* _
   } else if (EPI == EPI_RESID) {
     // out = residual stream (updated in place), act = gain-scaled bf16 copy for the next GEMM
 #pragma unroll
-    for (int jq = 0; jq < JT; ++jq) {
-      const int j = j0 + jq;
-      const int m = (mt0 + j) * 32 + mloc;
-      float ss = 0.f;
-      if (m < rows) {
+    for (int i = 0; i < NT; ++i)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int n = nt0 * 32 + 8 * q + nhalf;
-          float* xr = out + (size_t)m * N + n;
-          f32x4 v = *reinterpret_cast<const f32x4*>(xr);
-          const f32x4 gn = *reinterpret_cast<const f32x4*>(nf.gain + n);
-          bf16x4 h;
+      for (int jq = 0; jq < JT; ++jq) {
+        const int m = (mt0 + j0 + jq) * 32 + mloc;
+        float ss = 0.f;
+        if (m < rows) {
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            v[e] += res[0][jq][4 * q + e];
-            ss += v[e] * v[e];
-            h[e] = (bf16_t)(v[e] * gn[e]);
+          for (int q = 0; q < 4; ++q) {
+            const int n = (nt0 + i) * 32 + 8 * q + nhalf;
+            float* xr = out + (size_t)m * N + n;
+            f32x4 v = *reinterpret_cast<const f32x4*>(xr);
+            const f32x4 gn = *reinterpret_cast<const f32x4*>(nf.gain + n);
+            bf16x4 h;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              v[e] += res[i][jq][4 * q + e];
+              ss += v[e] * v[e];
+              h[e] = (bf16_t)(v[e] * gn[e]);
+            }
+            *reinterpret_cast<f32x4*>(xr) = v;
+            *reinterpret_cast<bf16x4*>(act + act_index<true>(m, n, N)) = h;
           }
-          *reinterpret_cast<f32x4*>(xr) = v;
-          *reinterpret_cast<bf16x4*>(act + act_index<true>(m, n, N)) = h;
         }
+        ss += __shfl_xor(ss, 32, 64);
+        if (m < rows && lane < 32) nf.ssq[(size_t)(nt0 + i) * nf.ssq_stride + m] = ss;
       }
-      ss += __shfl_xor(ss, 32, 64);
-      if (m < rows && lane < 32) nf.ssq[(size_t)nt0 * nf.ssq_stride + m] = ss;
-    }
   } else if (EPI == EPI_SWIGLU) {
     // acc[0] = gate tile, acc[1] = up tile of features [nt0*32, nt0*32+32); N is F here.
 #pragma unroll
@@ -305,80 +305,76 @@ __device__ inline void gemm_group(const bf16x8* __restrict__ w0, const bf16x8* _
   }
 }
 
-// grid: x = n-tile group, y = k-split across workgroups, z = group of MT m-tiles.
-// INTRA: the 4 wavefronts of a workgroup split the k range of one n-tile group (few
-// n-tiles, or fused SwiGLU); otherwise each wavefront owns its own n-tile group.
-template <int NT, int MT, int EPI, bool INTRA, int KW = KW4>
-__global__ __launch_bounds__(64 * KW) void gemm_mfma_kernel(RowCtx rc, const bf16x8* __restrict__ x,
-                                                           const bf16x8* __restrict__ w0,
-                                                           const bf16x8* __restrict__ w1, float* __restrict__ out,
-                                                           bf16_t* __restrict__ act, int N, int K, int ksplit,
-                                                           size_t partial_stride, NormFuse nf) {
+// INTRA: the 4 wavefronts of a workgroup split the k range of one n-tile group (few n-tiles, or
+// fused SwiGLU); otherwise each wavefront owns its own n-tile group.  KH: k-tiles per fetch group, OCC:
+// workgroups per compute unit the registers are cut for.  No template argument but EPI changes a bit.
+// Grids.  NEAR (1-D): the m-groups of one weight tile re-read that tile, so they are placed 8
+// workgroup ids apart: same XCD (ids are dealt to the 8 XCDs in turn), same moment, one HBM read:
+// id = ((tile / 8) * m_groups + m_group) * 8 + tile % 8.  Else x = k slice (F32) or n-tile group, y = the
+// other, z = m-group: consecutive workgroups go to consecutive XCDs, so with 8 (4) slices every XCD
+// works on one (two) k slices and pulls only that slice of the activations into its L2.
+constexpr int fetch_depth(int kh, int full, int part) { return part >= full ? kh : (kh * full / part < 8 ? kh * full / part : 8); }
+template <int NT, int MT, int EPI, bool INTRA, int KH, int OCC, bool NEAR>
+__global__ __launch_bounds__(64 * KW4, OCC) void gemm_mfma_kernel(RowCtx rc, const bf16x8* __restrict__ x,
+                                                                  const bf16x8* __restrict__ w0,
+                                                                  const bf16x8* __restrict__ w1, float* __restrict__ out,
+                                                                  bf16_t* __restrict__ act, int N, int K, int ksplit,
+                                                                  size_t partial_stride, NormFuse nf) {
+  constexpr int KW = KW4;
   __shared__ float red[INTRA ? KW * MT * 16 * 64 : 1];
   __shared__ float ssp[(INTRA && (EPI == EPI_SWIGLU || EPI == EPI_F32)) ? KW * MT * 32 : 1];
   const int rows = rows_or_zero(rc);
-  // EPI_RESID: 1-D launch.  The m-groups of one weight tile re-read that tile, so they are
-  // placed 8 workgroup ids apart: same XCD (ids are dealt to the 8 XCDs in turn), same moment,
-  // one HBM read.  Id = ((tile / 8) * m_groups + m_group) * 8 + tile % 8.
-  int bx = blockIdx.x, by = blockIdx.y, bz = blockIdx.z, ks = ksplit;
-  if (EPI == EPI_RESID) {
-    const int m_groups = ksplit;                  // (this launch has no k split: the field carries the m-group count)
-    const int rem = bx % (8 * m_groups);
-    by = (bx / (8 * m_groups)) * 8 + (rem & 7);
+  constexpr bool SLICES = INTRA && EPI == EPI_F32;
+  int bgrp = SLICES ? blockIdx.y : blockIdx.x, bz = blockIdx.z;
+  const int sidx = SLICES ? blockIdx.x : 0;
+  if (NEAR) {
+    const int m_groups = ceil_div(ceil_div(rc.max_rows, 32), MT);
+    const int rem = (int)blockIdx.x % (8 * m_groups);
+    bgrp = ((int)blockIdx.x / (8 * m_groups)) * 8 + (rem & 7);
     bz = rem >> 3;
-    bx = 0;
-    ks = 1;
-    if (by >= (N >> 5)) return;
   }
   const int mt0 = bz * MT;
   if (mt0 * 32 >= rows) return;
   const int KT = K >> 4;
-  // Split-k launches put the k split in blockIdx.x: consecutive workgroups go to consecutive
-  // XCDs, so with 8 (4) splits every XCD works on one (two) k slices and pulls only that slice
-  // of the activations into its L2 instead of all of them.
-  constexpr bool SPLIT_FIRST = INTRA && (EPI == EPI_F32 || EPI == EPI_RESID);
-  const int bgrp = SPLIT_FIRST ? by : bx;
   const int grp = INTRA ? bgrp : bgrp * KW + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int nt0 = (EPI == EPI_SWIGLU) ? grp : grp * NT;
-  if (!INTRA && nt0 >= (N >> 5)) return;
-  const int sidx = SPLIT_FIRST ? bx : by;
-  const int k0 = (int)((long long)KT * sidx / ks), k1 = (int)((long long)KT * (sidx + 1) / ks);
-  float* o = out ? out + (EPI == EPI_RESID ? (size_t)0 : sidx * partial_stride) : nullptr;
+  if (nt0 >= (N >> 5)) return;
+  const int k0 = (int)((long long)KT * sidx / ksplit), k1 = (int)((long long)KT * (sidx + 1) / ksplit);
+  float* o = out ? out + sidx * partial_stride : nullptr;
   int mtc = ceil_div(rows, 32) - mt0;
   if (mtc > MT) mtc = MT;
+  // (a last group of fewer m-tiles fetches more k-tiles at once in the same registers)
   switch (mtc) {
-    case 1: gemm_group<NT, 1, EPI, INTRA, KW>(w0, w1, x, KT, k0, k1, nt0, mt0, rows, N, o, act, red, ssp, nf); break;
-    case 2: gemm_group<NT, (MT >= 2 ? 2 : 1), EPI, INTRA, KW>(w0, w1, x, KT, k0, k1, nt0, mt0, rows, N, o, act, red, ssp, nf); break;
-    case 3: gemm_group<NT, (MT >= 3 ? 3 : 1), EPI, INTRA, KW>(w0, w1, x, KT, k0, k1, nt0, mt0, rows, N, o, act, red, ssp, nf); break;
-    default: gemm_group<NT, MT, EPI, INTRA, KW>(w0, w1, x, KT, k0, k1, nt0, mt0, rows, N, o, act, red, ssp, nf); break;
+    case 1: gemm_group<NT, 1, EPI, INTRA, KW, fetch_depth(KH, NT + MT, NT + 1)>(w0, w1, x, KT, k0, k1, nt0, mt0, rows, N, o, act, red, ssp, nf); break;
+    case 2: gemm_group<NT, (MT >= 2 ? 2 : 1), EPI, INTRA, KW, fetch_depth(KH, NT + MT, NT + 2)>(w0, w1, x, KT, k0, k1, nt0, mt0, rows, N, o, act, red, ssp, nf); break;
+    case 3: gemm_group<NT, (MT >= 3 ? 3 : 1), EPI, INTRA, KW, fetch_depth(KH, NT + MT, NT + 3)>(w0, w1, x, KT, k0, k1, nt0, mt0, rows, N, o, act, red, ssp, nf); break;
+    default: gemm_group<NT, MT, EPI, INTRA, KW, KH>(w0, w1, x, KT, k0, k1, nt0, mt0, rows, N, o, act, red, ssp, nf); break;
   }
 }
 
+// Split-k projections (qkv, down).  What bounds them: a compute unit alone pulls about 50 GB/s from
+// HBM, so the launch wants every unit busy with the same amount; beyond that the re-reads, the
+// activations once per n-tile group and the weights once per m-group, at L2 speed.  So the tile of a
+// workgroup grows with the rows: one n-tile where they are few (two workgroups per unit), two up to
+// 128 rows, then 4 x 3 or 4 x 4 tiles (weights read once) where a k slice is long enough to pay for the
+// wider reduction, and 2 x 3 with two workgroups per unit otherwise and beyond 256 rows.
+// us per launch, two n-tiles x four m-tiles for all / as here: 4096 x 14336 in 4 slices at 160, 192, 256,
+// 384 rows 51.5, 53.6, 59.0, 82.8 / 36.8, 38.8, 43.6, 67.9 (LDS-tiled kernel: 57 at 230); 2560 x 9728 in 6:
+// 26.8, 28.9, 32.4, 45.8 / 22.1, 23.3, 26.5, 39.8; 6144 x 4096 in 2: 21.7, 25.6, 32.6, 45.5 / 24.1,
+// 25.3, 27.9, 36.5; 6144 x 2560 in 2 at 256, 384: 24.2, 33.9 / 22.1, 27.2; one n-tile, five k-tiles per
+// fetch / as here: 1152 x 896 in 4 at 64, 96 rows 5.0, 5.8 / 4.5, 5.0.
 void launch_gemm_mfma(hipStream_t st, RowCtx rc, const bf16_t* x, const bf16_t* Wp, float* out, int N, int K,
                       int ksplit, size_t partial_stride, const float* ssq, int ssq_stride, float eps) {
   const NormFuse nf{nullptr, const_cast<float*>(ssq), ssq_stride, K >> 5, 1.0f / (float)K, eps, {}};
-  constexpr int MT = 4;
-  const int n_tiles = N >> 5;
-  const int m_groups = ceil_div(ceil_div(rc.max_rows, 32), MT);
-  const bf16x8* xv = reinterpret_cast<const bf16x8*>(x);
-  const bf16x8* wv = reinterpret_cast<const bf16x8*>(Wp);
-  if (n_tiles >= 2048 && n_tiles % 2 == 0 && ssq == nullptr) {
-    // plenty of n-tiles (LM head): one wavefront per pair of tiles, whole k range
-    dim3 grid(ceil_div(n_tiles / 2, KW4), ksplit, m_groups);
-    hipLaunchKernelGGL((gemm_mfma_kernel<2, MT, EPI_F32, false>), grid, dim3(64 * KW4), 0, st, rc, xv, wv, nullptr,
-                       out, nullptr, N, K, ksplit, partial_stride, nf);
-  } else if (n_tiles % 2 == 0 && (n_tiles / 2) * ksplit >= 128) {
-    // wide matrices: two n-tiles per workgroup, so every activation fragment feeds two MFMAs
-    // (the activation re-reads from L2 bound these shapes: 1.3-1.4x faster at 64-384 rows of
-    // a 2560- or 4096-wide model).  Every output element keeps its summation chain.
-    dim3 grid(ksplit, n_tiles / 2, m_groups);
-    hipLaunchKernelGGL((gemm_mfma_kernel<2, MT, EPI_F32, true>), grid, dim3(64 * KW4), 0, st, rc, xv, wv, nullptr,
-                       out, nullptr, N, K, ksplit, partial_stride, nf);
-  } else {
-    dim3 grid(ksplit, n_tiles, m_groups);
-    hipLaunchKernelGGL((gemm_mfma_kernel<1, MT, EPI_F32, true>), grid, dim3(64 * KW4), 0, st, rc, xv, wv, nullptr,
-                       out, nullptr, N, K, ksplit, partial_stride, nf);
-  }
+  const int n_tiles = N >> 5, m_tiles = ceil_div(rc.max_rows, 32), slice = K / ksplit;
+#define GEMM_F32(NT, MT, KH, OCC)                                                                                         hipLaunchKernelGGL((gemm_mfma_kernel<NT, MT, EPI_F32, true, KH, OCC, false>), dim3(ksplit, n_tiles / NT, ceil_div(m_tiles, MT)),                      dim3(64 * KW4), 0, st, rc, reinterpret_cast<const bf16x8*>(x), reinterpret_cast<const bf16x8*>(Wp), nullptr,                      out, nullptr, N, K, ksplit, partial_stride, nf)
+  if (n_tiles % 2 != 0 || (n_tiles / 2) * ksplit < 128) GEMM_F32(1, 4, 3, 2);
+  else if (m_tiles <= 4) GEMM_F32(2, 4, 5, 1);
+  else if (n_tiles % 4 == 0 && m_tiles <= 6 && slice >= 1536) GEMM_F32(4, 3, 3, 1);
+  else if (n_tiles % 4 == 0 && (m_tiles == 7 || m_tiles == 8) && slice >= 1024) GEMM_F32(4, 4, 2, 1);
+  else if (n_tiles % 4 == 0 && m_tiles > 8 && (n_tiles / 4) * ksplit >= 112) GEMM_F32(4, 3, 3, 1);
+  else GEMM_F32(2, 3, 3, 2);
+#undef GEMM_F32
 }
 
 int lmhead_group_cols() { return 64; }
@@ -388,44 +384,60 @@ void launch_gemm_mfma_logits(hipStream_t st, RowCtx rc, const bf16_t* x, const b
   constexpr int MT = 4;
   const int n_tiles = V >> 5;
   dim3 grid(ceil_div(ceil_div(n_tiles, 2), KW4), 1, ceil_div(ceil_div(rc.max_rows, 32), MT));
-  hipLaunchKernelGGL((gemm_mfma_kernel<2, MT, EPI_LOGITS, false>), grid, dim3(64 * KW4), 0, st, rc,
+  hipLaunchKernelGGL((gemm_mfma_kernel<2, MT, EPI_LOGITS, false, 5, 1, false>), grid, dim3(64 * KW4), 0, st, rc,
                      reinterpret_cast<const bf16x8*>(x), reinterpret_cast<const bf16x8*>(Wp), nullptr, logits, nullptr,
                      V, K, 1, (size_t)0, NormFuse{nullptr, nullptr, 0, 0, 0.f, 0.f, go});
 }
 
+// Fused gate/up, rows below what the LDS-tiled kernel takes (see forward()).  Workgroups of few row tiles
+// at three (two) per compute unit: an MLP of 9728 features is 304 workgroups, which at one per unit ran in two
+// rounds.  us per launch, four m-tiles at one per unit / as here: 2560 x 9728 at 32, 64, 96 rows 30.7,
+// 37.3, 42.5 / 27.3, 32.8, 35.1, at 320, 384 rows 74.2, 81.1 / 59.4, 69.0; 4096 x 14336 at 32, 64 rows
+// 48.4, 57.1 / 45.5, 53.5; 896 x 4864 at 64, 96, 192, 256 rows 9.9, 11.1, 15.2, 20.1 / 9.9, 10.2, 12.6, 14.8.
+// NEAR where the weight tiles alone are more than a round of one workgroup per unit.
 void launch_gemm_mfma_swiglu(hipStream_t st, RowCtx rc, const bf16_t* x, const bf16_t* Wg, const bf16_t* Wu,
                              bf16_t* act, int F, int K, const float* ssq, int ssq_stride, float eps) {
-  constexpr int MT = 4;
-  const int n_tiles = F >> 5;
-  dim3 grid(n_tiles, 1, ceil_div(ceil_div(rc.max_rows, 32), MT));
+  const int n_tiles = F >> 5, m_tiles = ceil_div(rc.max_rows, 32);
   NormFuse nf{nullptr, const_cast<float*>(ssq), ssq_stride, K >> 5, 1.0f / (float)K, eps, {}};
-  hipLaunchKernelGGL((gemm_mfma_kernel<2, MT, EPI_SWIGLU, true>), grid, dim3(64 * KW4), 0, st, rc,
-                     reinterpret_cast<const bf16x8*>(x), reinterpret_cast<const bf16x8*>(Wg),
-                     reinterpret_cast<const bf16x8*>(Wu), nullptr, act, F, K, 1, (size_t)0, nf);
+#define GEMM_SW(MT, KH, OCC, NEAR, grid)                                                                               \
+  hipLaunchKernelGGL((gemm_mfma_kernel<2, MT, EPI_SWIGLU, true, KH, OCC, NEAR>), grid, dim3(64 * KW4), 0, st, rc,      \
+                     reinterpret_cast<const bf16x8*>(x), reinterpret_cast<const bf16x8*>(Wg),                          \
+                     reinterpret_cast<const bf16x8*>(Wu), nullptr, act, F, K, 1, (size_t)0, nf)
+  const int tiles8 = ceil_div(n_tiles, 8) * 8;
+  if (m_tiles <= 1) GEMM_SW(1, 4, 3, false, dim3(n_tiles));
+  else if (n_tiles <= 256) GEMM_SW(2, 2, 3, false, dim3(n_tiles, 1, ceil_div(m_tiles, 2)));
+  else if (m_tiles <= 3) GEMM_SW(2, 2, 3, true, dim3(tiles8 * ceil_div(m_tiles, 2)));
+  else GEMM_SW(3, 3, 2, true, dim3(tiles8 * ceil_div(m_tiles, 3)));
+#undef GEMM_SW
 }
 
 // x_res += x . W^T (whole k range per workgroup, no partials); act = bf16(x_res * gain) in the
 // fragment order of the next GEMM; ssq[n_tile][row] = sum of squares of the tile's 32 columns.
+// As many workgroups as fit one per compute unit (256): few rows per workgroup where there are few
+// n-tiles; of the row tiles that give that number of groups the largest (two groups of 3 + 1
+// m-tiles are faster than 2 + 2: 14.8 against 17.0 us).  us per launch before (one m-tile up to 512 workgroups,
+// else four) / as here: 2560 x 4096 at 128, 160, 256 rows 17.9, 17.2, 23.5 / 14.8, 14.5, 18.3;
+// 4096 x 4096 at 96, 128, 256, 320, 384 rows 18.6, 18.8, 24.5, 35.2, 43.0 / 15.4, 16.0, 24.5, 21.2, 24.2.
 void launch_gemm_mfma_resid(hipStream_t st, RowCtx rc, const bf16_t* x, const bf16_t* Wp, float* x_res,
                             const float* gain, bf16_t* act, float* ssq, int ssq_stride, int N, int K) {
   const int n_tiles = N >> 5, m_tiles = ceil_div(rc.max_rows, 32);
-  const bf16x8* xv = reinterpret_cast<const bf16x8*>(x);
-  const bf16x8* wv = reinterpret_cast<const bf16x8*>(Wp);
-  NormFuse nf{gain, ssq, ssq_stride, 0, 0.f, 0.f, {}};
-  // few n-tiles: one m-tile per workgroup for more workgroups (the weights are small then);
-  // also while that stays within 512 workgroups (2560 columns at 129-192 rows: 13.3 us
-  // against 14.1 us on average over a run)
-  const int tiles8 = ceil_div(n_tiles, 8) * 8;
-  if (n_tiles * ceil_div(m_tiles, 4) < 128 || n_tiles * m_tiles <= 512) {
-    // (8 wavefronts per workgroup for the long k range of the down projection were measured:
-    // 14.0 us against 12.9 us)
-    hipLaunchKernelGGL((gemm_mfma_kernel<1, 1, EPI_RESID, true>), dim3(tiles8 * m_tiles), dim3(64 * KW4), 0, st, rc,
-                       xv, wv, nullptr, x_res, act, N, K, m_tiles, (size_t)0, nf);
-  } else {
-    const int mg = ceil_div(m_tiles, 4);
-    hipLaunchKernelGGL((gemm_mfma_kernel<1, 4, EPI_RESID, true>), dim3(tiles8 * mg), dim3(64 * KW4), 0, st, rc, xv, wv,
-                       nullptr, x_res, act, N, K, mg, (size_t)0, nf);
-  }
+  const NormFuse nf{gain, ssq, ssq_stride, 0, 0.f, 0.f, {}};
+#define GEMM_RESID(NT, MT, KH, OCC)                                                                                     \
+  hipLaunchKernelGGL((gemm_mfma_kernel<NT, MT, EPI_RESID, true, KH, OCC, true>),                                        \
+                     dim3(ceil_div(n_tiles / NT, 8) * 8 * ceil_div(m_tiles, MT)), dim3(64 * KW4), 0, st, rc,            \
+                     reinterpret_cast<const bf16x8*>(x), reinterpret_cast<const bf16x8*>(Wp), nullptr, x_res, act, N, K, \
+                     1, (size_t)0, nf)
+  const int most = 256 / n_tiles > 0 ? 256 / n_tiles : 1;                // groups of rows
+  const int groups = ceil_div(m_tiles, ceil_div(m_tiles, most));
+  int mt = ceil_div(m_tiles, most);
+  while (mt < 4 && ceil_div(m_tiles, mt + 1) == groups) ++mt;
+  if (groups == m_tiles) mt = 1;
+  if (mt == 1) GEMM_RESID(1, 1, 8, 1);
+  else if (mt == 2) GEMM_RESID(1, 2, 4, 2);
+  else if (mt == 3) GEMM_RESID(1, 3, 4, 2);
+  else if (mt == 4 || n_tiles % 2 != 0) GEMM_RESID(1, 4, 3, 2);
+  else GEMM_RESID(2, 3, 4, 1);
+#undef GEMM_RESID
 }
 
 }  // namespace april
