@@ -542,7 +542,12 @@ void forward(april_ctx* c, RowCtx rows, RowCtx srows, const int* gather, double 
   // across workgroups: its consumers then read a single partial.  The choice follows the kind
   // of pass, never the number of rows, so a rollout's arithmetic does not depend on the batch.
   const bool tile = c->use_mfma && c->tile_gemm && gather != nullptr;
-  const int sq = tile ? 1 : c->s_qkv, so = tile ? 1 : c->s_o, sd = tile ? 1 : c->s_down, sr = tile ? 1 : c->s_router;
+  // (o and down add into the residual stream themselves: no partials for the norm after them)
+  const int sq = tile ? 1 : c->s_qkv, so = tile ? 0 : c->s_o, sd = tile && !c->moe ? 0 : c->s_down, sr = tile ? 1 : c->s_router;
+  auto gemm_resid_tile = [&](int kc, const void* x, const bf16_t* w_s, int N, int K) {
+    ProfScope p(c, kc, (double)N * K * e + B * K * e + B * N * 8.0, 2.0 * B * N * K);
+    launch_gemm_tile_resid(st, rows, (const bf16_t*)x, w_s, c->x_res, N, K);
+  };
   auto gemm = [&](int kc, RowCtx rc, const void* x, const void* w_plain, const bf16_t* w_s, float* out, int N, int K,
                   int ks, size_t stride, double rowsB, const float* ssq = nullptr) {
     ProfScope p(c, kc, (double)N * K * e + rowsB * K * e + rowsB * N * 4.0, 2.0 * rowsB * N * K);
@@ -555,21 +560,30 @@ void forward(april_ctx* c, RowCtx rows, RowCtx srows, const int* gather, double 
   for (int l = 0; l < m.n_layers; ++l) {
     const LayerW& L = c->layers[l];
     if (!normed_by_down) norm(rows, l == 0 ? 0 : sd, L.attn_norm, c->h_act, nullptr, B, true);
-    gemm(KC_GEMM_QKV, rows, c->h_act, L.wqkv, L.wqkv_s, c->qkv, nqkv, d, sq, c->qkv_stride, B,
-         normed_by_down ? c->ssq : nullptr);
+    // prefill: rotary + KV append in the projection's epilogue, queries as bf16 rows (in q_rot's memory)
+    bf16_t* q16 = reinterpret_cast<bf16_t*>(c->q_rot);
+    const bool pf_attn = c->attn_mfma && gather != nullptr && c->prefill_tiled;
+    bool roped = false;
+    if (tile && pf_attn) {
+      ProfScope p(c, KC_GEMM_QKV, (double)nqkv * d * e + B * d * e + B * nqkv * e, 2.0 * B * nqkv * d);
+      roped = launch_gemm_tile_qkv(st, rows, (const bf16_t*)c->h_act, L.wqkv_s, nqkv, d,
+                                   QkvOut{c->ds.block_table, c->max_blocks, c->rope_cos, c->rope_sin, q16, (bf16_t*)c->kv_pool, c->kvl, l, Hq});
+    }
+    if (!roped) gemm(KC_GEMM_QKV, rows, c->h_act, L.wqkv, L.wqkv_s, c->qkv, nqkv, d, sq, c->qkv_stride, B,
+                     normed_by_down ? c->ssq : nullptr);
     normed_by_down = false;
     // decode iterations: rotary + KV append are done inside the attention kernel
     const bool fuse_rope = c->attn_mfma && c->fuse_rope && gather == nullptr;
-    if (!fuse_rope) {
+    if (!fuse_rope && !roped) {
       ProfScope p(c, KC_ROPE, B * (nqkv * 4.0 + nq * 4.0 + 2 * nkv * e), 0);
-      if (c->bf16) launch_rope_append<bf16_t>(st, rows, c->ds, c->qkv, sq, c->qkv_stride, c->rope_cos, c->rope_sin, c->q_rot, (bf16_t*)c->kv_pool, c->kvl, l, Hq);
+      if (c->bf16) launch_rope_append<bf16_t>(st, rows, c->ds, c->qkv, sq, c->qkv_stride, c->rope_cos, c->rope_sin, c->q_rot, (bf16_t*)c->kv_pool, c->kvl, l, Hq, pf_attn ? q16 : nullptr);
       else launch_rope_append<float>(st, rows, c->ds, c->qkv, sq, c->qkv_stride, c->rope_cos, c->rope_sin, c->q_rot, (float*)c->kv_pool, c->kvl, l, Hq);
     }
-    if (c->attn_mfma && gather != nullptr && c->prefill_tiled) {
+    if (pf_attn) {
       // prefill: one workgroup per tile of query positions, the keys / values of a prompt are
       // streamed once per tile instead of once per row
       ProfScope p(c, KC_ATTN, C * 2.0 * nkv * e + B * nq * (4.0 + e), 4.0 * C * nq);
-      launch_attn_prefill(st, c->d_pf_items, c->pf_n_items, c->ds, c->q_rot, (const bf16_t*)c->kv_pool, c->kvl, l, Hq,
+      launch_attn_prefill(st, c->d_pf_items, c->pf_n_items, c->ds, q16, (const bf16_t*)c->kv_pool, c->kvl, l, Hq,
                           (bf16_t*)c->attn_out);
     } else if (c->attn_mfma) {
       const int gs = std::min(c->attn_max_splits, std::max(1, ceil_div(c->step_max_ctx, c->attn_chunk)));
@@ -601,7 +615,8 @@ void forward(april_ctx* c, RowCtx rows, RowCtx srows, const int* gather, double 
       launch_gemm_mfma_resid(st, rows, (const bf16_t*)c->attn_out, L.wo_s, c->x_res, L.mlp_norm, (bf16_t*)c->h_act,
                              c->ssq, c->m_cap, d, nq);
     } else {
-      gemm(KC_GEMM_O, rows, c->attn_out, L.wo, L.wo_s, c->proj, d, nq, so, c->proj_stride, B);
+      if (tile) gemm_resid_tile(KC_GEMM_O, c->attn_out, L.wo_s, d, nq);
+      else gemm(KC_GEMM_O, rows, c->attn_out, L.wo, L.wo_s, c->proj, d, nq, so, c->proj_stride, B);
       // (routed experts in prefill gather token rows: they get a plain [row][d] copy as well)
       norm(rows, so, L.mlp_norm, c->h_act, nullptr, B, false, c->moe && tile && c->moe_tile ? c->h_rows : nullptr);
     }
@@ -653,6 +668,8 @@ void forward(april_ctx* c, RowCtx rows, RowCtx srows, const int* gather, double 
       launch_gemm_mfma_resid(st, rows, (const bf16_t*)c->act, L.wd_s, c->x_res, c->layers[l + 1].attn_norm,
                              (bf16_t*)c->h_act, c->ssq, c->m_cap, d, F);
       normed_by_down = true;
+    } else if (tile) {
+      gemm_resid_tile(KC_GEMM_DOWN, c->act, L.wd_s, d, F);
     } else {
       gemm(KC_GEMM_DOWN, rows, c->act, L.wd, L.wd_s, c->proj, d, F, sd, c->proj_stride, B);
     }

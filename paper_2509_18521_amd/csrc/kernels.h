@@ -144,10 +144,11 @@ void launch_moe_gateup(hipStream_t st, RowCtx rc, const int* cnt, const int* bas
 void launch_moe_down(hipStream_t st, RowCtx rc, const int* cnt, const int* base, const int* group_expert,
                      const bf16_t* act, const bf16_t* Wd, float* out, int E, int top_k, int Fe, int d, int tall_rows);
 
+// q_bf16 (nullable): the rotated queries go there, rounded to bf16, instead of q_rot.
 template <typename T>
 void launch_rope_append(hipStream_t st, RowCtx rc, Slots s, const float* qkv, int n_partials,
                         size_t partial_stride, const float* rope_cos, const float* rope_sin,
-                        float* q_rot, T* kv_pool, KVLayout kvl, int layer, int n_q_heads);
+                        float* q_rot, T* kv_pool, KVLayout kvl, int layer, int n_q_heads, bf16_t* q_bf16 = nullptr);
 
 template <typename T, bool XF>
 void launch_attn_ref(hipStream_t st, RowCtx rc, Slots s, const float* q_rot, const T* kv_pool,
@@ -170,10 +171,10 @@ void launch_attn_decode(hipStream_t st, RowCtx rc, int row_base, Slots s, const 
                         const float* rope_cos, const float* rope_sin, const int4* items = nullptr);
 // Causal attention over prefill rows, one workgroup per (item, KV head); an item = {slot, first
 // row of the sequence in the row arrays, tokens of the sequence, first position of the tile},
-// tiles of attn_prefill_tile(query heads per KV head) positions.  q_rot and the pages must hold
-// the rotated queries / keys and the values of every row (launch_rope_append first).
+// tiles of attn_prefill_tile(query heads per KV head) positions.  q (bf16 rows) and the pages must hold
+// the rotated queries / keys and the values of every row (launch_gemm_tile_qkv or launch_rope_append first).
 int attn_prefill_tile(int group);
-void launch_attn_prefill(hipStream_t st, const int4* items, int n_items, Slots s, const float* q_rot,
+void launch_attn_prefill(hipStream_t st, const int4* items, int n_items, Slots s, const bf16_t* q,
                          const bf16_t* kv_pool, KVLayout kvl, int layer, int n_q_heads, bf16_t* out);
 // Merge of the KV-split partials (needed after launch_attn_decode whenever grid_splits > 1).
 void launch_attn_merge(hipStream_t st, RowCtx rc, int row_base, KVLayout kvl, int n_q_heads, bf16_t* out,
@@ -205,7 +206,20 @@ void launch_gemm_mfma_swiglu(hipStream_t st, RowCtx rc, const bf16_t* x, const b
                              int ssq_stride = 0, float eps = 0.f);
 void launch_gemm_mfma_resid(hipStream_t st, RowCtx rc, const bf16_t* x, const bf16_t* Wp, float* x_res,
                             const float* gain, bf16_t* act, float* ssq, int ssq_stride, int N, int K);
-// LDS-tiled GEMM for tall activations (prefill); single pass over k, no partials.
+// LDS-tiled GEMMs for tall activations (prefill); single pass over k, no partials.  _resid: added into
+// the fp32 residual stream x_res [rows][N].  _qkv: rotary embedding and KV append in the epilogue,
+// rotated queries as bf16 rows (false, nothing launched: shapes it does not take).
+struct QkvOut {
+  const int* block_table;
+  int max_blocks;
+  const float *rope_cos, *rope_sin;    // [pos][head_dim / 2]
+  bf16_t* q;                           // [rows][n_q_heads * head_dim]
+  bf16_t* kv_pool;
+  KVLayout kvl;
+  int layer, n_q_heads;
+};
+void launch_gemm_tile_resid(hipStream_t st, RowCtx rc, const bf16_t* x, const bf16_t* Wp, float* x_res, int N, int K);
+bool launch_gemm_tile_qkv(hipStream_t st, RowCtx rc, const bf16_t* x, const bf16_t* Wp, int N, int K, const QkvOut& qo);
 void launch_gemm_tile(hipStream_t st, RowCtx rc, const bf16_t* x, const bf16_t* Wp, float* out, int N, int K);
 void launch_gemm_tile_swiglu(hipStream_t st, RowCtx rc, const bf16_t* x, const bf16_t* Wg, const bf16_t* Wu,
                              bf16_t* act, int F, int K);

@@ -562,7 +562,7 @@ constexpr int PF_STAGE = 64;              // tokens per stage
 
 template <int DH, int GP>
 __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(const int4* __restrict__ items, Slots s,
-                                                              const float* __restrict__ q_rot,
+                                                              const bf16_t* __restrict__ qb,
                                                               const bf16_t* __restrict__ kv_pool, KVLayout L, int layer,
                                                               int Hq, bf16_t* __restrict__ out) {
   constexpr int KC = DH / 16, DT = DH / 32, CT = PF_CT, NP = PF_STAGE / 16;
@@ -613,12 +613,11 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(const int4* __rest
     qok[ct] = p < nt && h < G;
     qpos[ct] = p < nt ? p : nt - 1;
     const int hc = h < G ? h : G - 1;
-    const float* q = q_rot + (size_t)(row0 + qpos[ct]) * Hq * DH + (size_t)(kvh * G + hc) * DH + 8 * hf;
+    const bf16_t* q = qb + (size_t)(row0 + qpos[ct]) * Hq * DH + (size_t)(kvh * G + hc) * DH + 8 * hf;
 #pragma unroll
     for (int c = 0; c < KC; ++c) {
-      const f32x4 a = *reinterpret_cast<const f32x4*>(q + 16 * c), b = *reinterpret_cast<const f32x4*>(q + 16 * c + 4);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) { qf[ct][c][j] = qok[ct] ? (bf16_t)a[j] : (bf16_t)0.f; qf[ct][c][4 + j] = qok[ct] ? (bf16_t)b[j] : (bf16_t)0.f; }
+      const bf16x8 v = *reinterpret_cast<const bf16x8*>(q + 16 * c);
+      qf[ct][c] = qok[ct] ? v : bf16x8{};
     }
   }
   const float c2 = 1.4426950408889634f / sqrtf((float)DH);   // scores to base-2 exponents
@@ -737,14 +736,14 @@ int attn_prefill_tile(int group) {
   return 4 * PF_CT * (32 / gp);
 }
 
-void launch_attn_prefill(hipStream_t st, const int4* items, int n_items, Slots s, const float* q_rot,
+void launch_attn_prefill(hipStream_t st, const int4* items, int n_items, Slots s, const bf16_t* q,
                          const bf16_t* kv_pool, KVLayout kvl, int layer, int n_q_heads, bf16_t* out) {
   if (n_items <= 0) return;
   dim3 grid(n_items, kvl.n_kv_heads);
   const int G = n_q_heads / kvl.n_kv_heads;
   int gp = 1;
   while (gp < G) gp <<= 1;
-#define ATT_PF(DH, GP) hipLaunchKernelGGL((attn_prefill_kernel<DH, GP>), grid, dim3(256), 0, st, items, s, q_rot, kv_pool, kvl, layer, n_q_heads, out)
+#define ATT_PF(DH, GP) hipLaunchKernelGGL((attn_prefill_kernel<DH, GP>), grid, dim3(256), 0, st, items, s, q, kv_pool, kvl, layer, n_q_heads, out)
 #define ATT_PF_G(DH) switch (gp) { case 1: ATT_PF(DH, 1); break; case 2: ATT_PF(DH, 2); break; case 4: ATT_PF(DH, 4); break; \
                                    case 8: ATT_PF(DH, 8); break; default: ATT_PF(DH, 16); break; }
   switch (kvl.head_dim) {

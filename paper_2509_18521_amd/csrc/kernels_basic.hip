@@ -430,7 +430,7 @@ template <typename T>
 __global__ __launch_bounds__(256) void rope_append_kernel(RowCtx rc, Slots s, const float* qkv, int n_partials,
                                                           size_t partial_stride, const float* rope_cos,
                                                           const float* rope_sin, float* q_rot, T* kv_pool,
-                                                          KVLayout L, int layer, int Hq) {
+                                                          KVLayout L, int layer, int Hq, bf16_t* q_bf16) {
   const int r = blockIdx.x;
   ROW_GUARD(rc, r);
   const int slot = rc.row_slot[r], pos = rc.row_pos[r];
@@ -452,8 +452,9 @@ __global__ __launch_bounds__(256) void rope_append_kernel(RowCtx rc, Slots s, co
     const float c = cs[i], sI = sn[i];
     const float ra = rope_first(a, b, c, sI), rb = rope_second(a, b, c, sI);
     if (hd < Hq) {
-      q_rot[(size_t)r * nq + hd * dh + i] = ra;
-      q_rot[(size_t)r * nq + hd * dh + i + half] = rb;
+      const size_t at = (size_t)r * nq + hd * dh + i;
+      if (q_bf16 != nullptr) { q_bf16[at] = (bf16_t)ra; q_bf16[at + half] = (bf16_t)rb; }
+      else { q_rot[at] = ra; q_rot[at + half] = rb; }
     } else {
       const int kh = hd - Hq;
       kv_pool[L.at(layer, 0, page, kh, t, i)] = from_f32<T>(ra);
@@ -468,12 +469,12 @@ __global__ __launch_bounds__(256) void rope_append_kernel(RowCtx rc, Slots s, co
 template <typename T>
 void launch_rope_append(hipStream_t st, RowCtx rc, Slots s, const float* qkv, int n_partials, size_t partial_stride,
                         const float* rope_cos, const float* rope_sin, float* q_rot, T* kv_pool, KVLayout kvl,
-                        int layer, int n_q_heads) {
+                        int layer, int n_q_heads, bf16_t* q_bf16) {
   hipLaunchKernelGGL(rope_append_kernel<T>, dim3(rc.max_rows), dim3(256), 0, st, rc, s, qkv, n_partials,
-                     partial_stride, rope_cos, rope_sin, q_rot, kv_pool, kvl, layer, n_q_heads);
+                     partial_stride, rope_cos, rope_sin, q_rot, kv_pool, kvl, layer, n_q_heads, q_bf16);
 }
-template void launch_rope_append<float>(hipStream_t, RowCtx, Slots, const float*, int, size_t, const float*, const float*, float*, float*, KVLayout, int, int);
-template void launch_rope_append<bf16_t>(hipStream_t, RowCtx, Slots, const float*, int, size_t, const float*, const float*, float*, bf16_t*, KVLayout, int, int);
+template void launch_rope_append<float>(hipStream_t, RowCtx, Slots, const float*, int, size_t, const float*, const float*, float*, float*, KVLayout, int, int, bf16_t*);
+template void launch_rope_append<bf16_t>(hipStream_t, RowCtx, Slots, const float*, int, size_t, const float*, const float*, float*, bf16_t*, KVLayout, int, int, bf16_t*);
 
 // ---------------------------------------------------------------------------
 // Reference paged attention: one wavefront per (row, query head), one cached token

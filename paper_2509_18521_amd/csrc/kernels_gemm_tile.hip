@@ -17,7 +17,7 @@
 
 namespace april {
 
-enum { TEPI_F32 = 0, TEPI_SWIGLU = 1, TEPI_LOGITS = 2 };   // LOGITS: F32 (optional) + records of 64-column groups
+enum { TEPI_F32 = 0, TEPI_SWIGLU = 1, TEPI_LOGITS = 2, TEPI_RESID = 3, TEPI_QKV = 4 };   // RESID: out += result; LOGITS: F32 (optional) + records of 64-column groups
 
 // Epilogue of one wavefront: accumulator tile = out^T (lane l, register e:
 // n = 8*(e/4) + 4*(l/32) + e%4, m = l%32).  nt0: first weight tile (SwiGLU: first feature
@@ -50,7 +50,7 @@ __device__ inline void tile_epilogue(f32x16 (&acc)[NTW][MTW], int nt0, int mt0, 
       }
     }
   }
-  if (EPI == TEPI_F32 || (EPI == TEPI_LOGITS && out != nullptr)) {
+  if (EPI == TEPI_F32 || EPI == TEPI_RESID || (EPI == TEPI_LOGITS && out != nullptr)) {
 #pragma unroll
     for (int i = 0; i < NTW; ++i) {
       const int nt = nt0 + i;
@@ -63,7 +63,9 @@ __device__ inline void tile_epilogue(f32x16 (&acc)[NTW][MTW], int nt0, int mt0, 
           for (int q = 0; q < 4; ++q) {
             const int n = nt * 32 + 8 * q + nhalf;
             f32x4 v = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
-            *reinterpret_cast<f32x4*>(out + (size_t)m * N + n) = v;
+            f32x4* o = reinterpret_cast<f32x4*>(out + (size_t)m * N + n);
+            if (EPI == TEPI_RESID) v = *o + v;
+            *o = v;
           }
         }
       }
@@ -91,6 +93,86 @@ __device__ inline void tile_epilogue(f32x16 (&acc)[NTW][MTW], int nt0, int mt0, 
             }
             *reinterpret_cast<bf16x4*>(act + act_index<true>(m, f, N)) = v;
           }
+        }
+      }
+    }
+  }
+}
+
+// Epilogue of the prefill QKV projection: rotary embedding of q and k, q to a bf16 row array, k and v to
+// their pages - what a separate pass over the fp32 projection (rope_append_kernel) did, with the same
+// operations.  A wavefront holds 128 columns (NTW = 4 tiles), which are whole heads, and both members of
+// a rotation pair sit in the same lane: tiles i and i + DH / 64, or for DH = 32 registers e and e + 8.
+// The separate pass took 232 us per 16384 rows of 32 + 2 x 8 heads of 128 (400 MB in, 335 MB out,
+// bandwidth); with it and the residual additions of the two other projections (TEPI_RESID: the norm after
+// them reads one array instead of two and writes none but its result, 130 -> 80 us) in the epilogues, prefill
+// of 21 k tokens through three such layers went from 19.0 to 18.0 ms.
+template <int MTW, int DH>
+__device__ inline void qkv_epilogue(f32x16 (&acc)[4][MTW], int nt0, int mt0, int rows, int n_tiles, int lane, const RowCtx& rc,
+                                    const QkvOut& qo) {
+  constexpr int TH = DH / 32, HALF = DH / 2;            // tiles per head
+  const int mloc = lane & 31, hf = lane >> 5;
+  const int nq = qo.n_q_heads * DH, nkv = qo.kvl.n_kv_heads * DH;
+#pragma unroll
+  for (int j = 0; j < MTW; ++j) {
+    const int m = (mt0 + j) * 32 + mloc;
+    const bool ok = m < rows;
+    const int mr = ok ? m : rows - 1;
+    const int slot = rc.row_slot[mr], pos = rc.row_pos[mr];
+    const int page = qo.block_table[(size_t)slot * qo.max_blocks + (pos >> 4)], tok = pos & 15;
+#pragma unroll
+    for (int h = 0; h < 4 / TH; ++h) {
+      const int col0 = (nt0 + h * TH) * 32;             // first column of the head (wavefront-uniform)
+      if (col0 >= n_tiles * 32) continue;
+      if (col0 < nq + nkv) {
+        const float* cs = qo.rope_cos + (size_t)pos * HALF + 4 * hf;
+        const float* sn = qo.rope_sin + (size_t)pos * HALF + 4 * hf;
+        constexpr int PAIRS = TH > 1 ? TH / 2 : 1, QN = TH > 1 ? 4 : 2;
+#pragma unroll
+        for (int p = 0; p < PAIRS; ++p)
+#pragma unroll
+          for (int q = 0; q < QN; ++q) {
+            const f32x4 c = *reinterpret_cast<const f32x4*>(cs + 32 * p + 8 * q), s = *reinterpret_cast<const f32x4*>(sn + 32 * p + 8 * q);
+            f32x16& ta = acc[h * TH + p][j];
+            f32x16& tb = acc[h * TH + p + (TH > 1 ? TH / 2 : 0)][j];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const int ra = 4 * q + e, rb = 4 * q + e + (TH > 1 ? 0 : 8);
+              const float a = ta[ra], b = tb[rb];
+              ta[ra] = rope_first(a, b, c[e], s[e]);
+              tb[rb] = rope_second(a, b, c[e], s[e]);
+            }
+          }
+        const bool is_q = col0 < nq;
+        bf16_t* dst = is_q ? qo.q + (size_t)mr * nq + col0
+                           : qo.kv_pool + qo.kvl.at(qo.layer, 0, page, (col0 - nq) / DH, tok, 0);
+#pragma unroll
+        for (int i = 0; i < TH; ++i)
+#pragma unroll
+          for (int q = 0; q < 4; q += 2) {
+            // the lane halves hold alternating groups of 4 columns: they trade one, so that each stores 8
+            union { bf16x4 v[2]; unsigned u[4]; bf16x8 w; } own, st8;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              own.v[0][e] = (bf16_t)acc[h * TH + i][j][4 * q + e];
+              own.v[1][e] = (bf16_t)acc[h * TH + i][j][4 * q + 4 + e];
+            }
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+              const unsigned give = hf ? own.u[e] : own.u[2 + e], got = __shfl_xor((int)give, 32, 64);
+              st8.u[e] = hf ? got : own.u[e];
+              st8.u[2 + e] = hf ? own.u[2 + e] : got;
+            }
+            // page layout of K: [d / 32][token + 16 ((d % 32) / 8)][d % 8]
+            if (ok) *reinterpret_cast<bf16x8*>(dst + (is_q ? i * 32 + 8 * (q + hf) : i * 512 + 128 * (q + hf))) = st8.w;
+          }
+      } else {
+        bf16_t* dst = qo.kv_pool + qo.kvl.at(qo.layer, 1, page, (col0 - nq - nkv) / DH, tok, 0);   // [d][token]
+        if (ok) {
+#pragma unroll
+          for (int i = 0; i < TH; ++i)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) dst[(i * 32 + 8 * (e >> 2) + 4 * hf + (e & 3)) * 16] = (bf16_t)acc[h * TH + i][j][e];
         }
       }
     }
@@ -448,11 +530,11 @@ __device__ __forceinline__ void tile_dma_body(RowCtx rc, const bf16x8* __restric
 // fp32 output are 15 % of the time); a library product of 16384^3 reaches 1555.  With the reads or copies
 // inside branches, or a burst of copies after the barrier, it was 5 % slower than the 8 wavefronts.
 // Same accumulator chain per element as every kernel here (k-tiles in order).  K % 32 == 0.
-template <int EPI>
+template <int EPI, int DH = 0>
 __global__ __launch_bounds__(256, 1) void gemm_big_kernel(RowCtx rc, const bf16x8* __restrict__ x,
                                                           const bf16x8* __restrict__ w0, const bf16x8* __restrict__ w1,
                                                           float* __restrict__ out, bf16_t* __restrict__ act, int N, int K,
-                                                          GroupOut go) {
+                                                          GroupOut go, QkvOut qo) {
   constexpr int MT = 8, NT = 8, MTW = 4, NTW = 4, BK = 2, R = 4, FR = MT + NT, PER = FR * BK / 4;
   __shared__ bf16x8 lds[R][BK][FR][64];
   const int rows = rows_or_zero(rc);
@@ -548,6 +630,10 @@ __global__ __launch_bounds__(256, 1) void gemm_big_kernel(RowCtx rc, const bf16x
   int s = 0;
   for (; s + R - 1 < n_stages; ++s) stage(s, std::true_type{});
   for (; s < n_stages; ++s) stage(s, std::false_type{});
+  if constexpr (EPI == TEPI_QKV) {
+    qkv_epilogue<MTW, DH>(acc, blockIdx.x * NT + wn * NTW, m0 + wm * MTW, rows, n_tiles, lane, rc, qo);
+    return;
+  }
   tile_epilogue<MTW, NTW, EPI>(acc, blockIdx.x * (EPI == TEPI_SWIGLU ? NT / 2 : NT) + wn * (EPI == TEPI_SWIGLU ? NTW / 2 : NTW),
                                m0 + wm * MTW, rows, n_tiles, N, lane, out, act, nullptr, m0 * 32, &go);
 }
@@ -619,20 +705,42 @@ static bool wide_tile(int units, int per_wide, int m_tiles) {
   return wgs >= 128 && ceil_div(units, per_wide) * per_wide * 20 <= units * 23;   // <= 15 % padding
 }
 
-void launch_gemm_tile(hipStream_t st, RowCtx rc, const bf16_t* x, const bf16_t* Wp, float* out, int N, int K) {
+template <int EPI>
+static void launch_tile(hipStream_t st, RowCtx rc, const bf16_t* x, const bf16_t* Wp, float* out, int N, int K) {
   const int n_tiles = N >> 5, m_tiles = ceil_div(rc.max_rows, 32);
   const bf16x8* xv = reinterpret_cast<const bf16x8*>(x);
   const bf16x8* wv = reinterpret_cast<const bf16x8*>(Wp);
   if (K % 32 != 0) {
     dim3 grid(ceil_div(n_tiles, 4), ceil_div(m_tiles, 8));
-    hipLaunchKernelGGL((TILE_REGS(TEPI_F32)), grid, dim3(256), 0, st, rc, xv, wv, nullptr, out, nullptr, N, K);
+    hipLaunchKernelGGL((TILE_REGS(EPI)), grid, dim3(256), 0, st, rc, xv, wv, nullptr, out, nullptr, N, K);
   } else if (wide_tile(n_tiles, 8, m_tiles)) {
     dim3 grid(ceil_div(n_tiles, 8), ceil_div(m_tiles, 8));
-    hipLaunchKernelGGL((TILE_WIDE(TEPI_F32)), grid, dim3(256), 0, st, rc, xv, wv, nullptr, out, nullptr, N, K, GroupOut{});
+    hipLaunchKernelGGL((TILE_WIDE(EPI)), grid, dim3(256), 0, st, rc, xv, wv, nullptr, out, nullptr, N, K, GroupOut{}, QkvOut{});
   } else {
     dim3 grid(ceil_div(n_tiles, 4), ceil_div(m_tiles, 8));
-    hipLaunchKernelGGL((TILE_NARROW(TEPI_F32)), grid, dim3(256), 0, st, rc, xv, wv, nullptr, out, nullptr, N, K, GroupOut{});
+    hipLaunchKernelGGL((TILE_NARROW(EPI)), grid, dim3(256), 0, st, rc, xv, wv, nullptr, out, nullptr, N, K, GroupOut{});
   }
+}
+void launch_gemm_tile(hipStream_t st, RowCtx rc, const bf16_t* x, const bf16_t* Wp, float* out, int N, int K) {
+  launch_tile<TEPI_F32>(st, rc, x, Wp, out, N, K);
+}
+void launch_gemm_tile_resid(hipStream_t st, RowCtx rc, const bf16_t* x, const bf16_t* Wp, float* x_res, int N, int K) {
+  launch_tile<TEPI_RESID>(st, rc, x, Wp, x_res, N, K);
+}
+bool launch_gemm_tile_qkv(hipStream_t st, RowCtx rc, const bf16_t* x, const bf16_t* Wp, int N, int K, const QkvOut& qo) {
+  if (K % 32 != 0 || qo.kvl.mode != 1) return false;
+  dim3 grid(ceil_div(N >> 5, 8), ceil_div(ceil_div(rc.max_rows, 32), 8));
+#define QKV_LAUNCH(DH)                                                                                                 \
+  hipLaunchKernelGGL((gemm_big_kernel<TEPI_QKV, DH>), grid, dim3(256), 0, st, rc, reinterpret_cast<const bf16x8*>(x),  \
+                     reinterpret_cast<const bf16x8*>(Wp), nullptr, nullptr, nullptr, N, K, GroupOut{}, qo)
+  switch (qo.kvl.head_dim) {
+    case 32: QKV_LAUNCH(32); break;
+    case 64: QKV_LAUNCH(64); break;
+    case 128: QKV_LAUNCH(128); break;
+    default: return false;
+  }
+#undef QKV_LAUNCH
+  return true;
 }
 
 void launch_gemm_tile_swiglu(hipStream_t st, RowCtx rc, const bf16_t* x, const bf16_t* Wg, const bf16_t* Wu,
@@ -646,7 +754,7 @@ void launch_gemm_tile_swiglu(hipStream_t st, RowCtx rc, const bf16_t* x, const b
     hipLaunchKernelGGL((TILE_REGS(TEPI_SWIGLU)), grid, dim3(256), 0, st, rc, xv, gv, uv, nullptr, act, F, K);
   } else if (wide_tile(f_tiles, 4, m_tiles)) {
     dim3 grid(ceil_div(f_tiles, 4), ceil_div(m_tiles, 8));
-    hipLaunchKernelGGL((TILE_WIDE(TEPI_SWIGLU)), grid, dim3(256), 0, st, rc, xv, gv, uv, nullptr, act, F, K, GroupOut{});
+    hipLaunchKernelGGL((TILE_WIDE(TEPI_SWIGLU)), grid, dim3(256), 0, st, rc, xv, gv, uv, nullptr, act, F, K, GroupOut{}, QkvOut{});
   } else {
     dim3 grid(ceil_div(f_tiles, 2), ceil_div(m_tiles, 8));
     hipLaunchKernelGGL((TILE_NARROW(TEPI_SWIGLU)), grid, dim3(256), 0, st, rc, xv, gv, uv, nullptr, act, F, K, GroupOut{});
@@ -659,12 +767,12 @@ void launch_gemm_tile_swiglu(hipStream_t st, RowCtx rc, const bf16_t* x, const b
 // Measured on MI355X, fused gate/up of a 4096 x 14336 (2560 x 9728) MLP, event pairs around eager
 // launches: at a row bound of 128 the half-height tile takes 76 (43) us against 84 (53) us for the
 // skinny kernel (tie at 96, slower at 64); at 256 the full tile 91 (60) us against 132 (67) us;
-// beyond 256 rows (two row groups) it only pays where the weight tiles alone fill the chip.
+// beyond 256 rows (two row groups) it does not pay.
 // A ring deeper than 3 stages made these variants 1.8x slower (the plain kernel does not care).
 bool launch_gemm_tile_swiglu_chain(hipStream_t st, RowCtx rc, const bf16_t* x, const bf16_t* Wg, const bf16_t* Wu,
                                    bf16_t* act, int F, int K, const float* ssq, int ssq_stride, float eps) {
   if (K % 128 != 0 || F % 32 != 0) return false;     // quarter boundaries on stage boundaries (BK = 2)
-  if (rc.max_rows > 256 && F < 12288) return false;
+  if (rc.max_rows > 256) return false;               // (14336 x 4096 at 320, 384 rows: 140-151, 143 us here, 130, 144-147 on the skinny kernel)
   if (rc.max_rows <= 128) {
     // half-height tile (128 rows x 64 features, 2 x 2 accumulator tiles per wavefront)
     dim3 grid(ceil_div(F >> 5, 2), 1);
@@ -703,7 +811,7 @@ void launch_gemm_tile_logits(hipStream_t st, RowCtx rc, const bf16_t* x, const b
   const int n_tiles = V >> 5, m_tiles = ceil_div(rc.max_rows, 32);
   dim3 grid(ceil_div(n_tiles, 8), ceil_div(m_tiles, 8));
   hipLaunchKernelGGL((TILE_WIDE(TEPI_LOGITS)), grid, dim3(256), 0, st, rc, reinterpret_cast<const bf16x8*>(x),
-                     reinterpret_cast<const bf16x8*>(Wp), nullptr, logits, nullptr, V, K, go);
+                     reinterpret_cast<const bf16x8*>(Wp), nullptr, logits, nullptr, V, K, go, QkvOut{});
 }
 
 }  // namespace april

@@ -1,0 +1,50 @@
+"""The row count picks the tiles of the decode projections (1 to 4 m-tiles per workgroup, 1 to 4 n-tiles,
+the LDS-tiled gate/up): every choice keeps each output's summation chain.  Requests of one class (same
+prompt, same forced tokens) must get bit-identical logits wherever they sit in a batch of whatever
+size - every row tile of it, its last row - and when they run among three others only."""
+import numpy as np
+import pytest
+
+import april_inputs as ai
+from gpu_common import class_forced_tokens, have_gpu, make_engine, run_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _need_gpu():
+    if not have_gpu():
+        pytest.skip("no GPU")
+
+
+@pytest.mark.parametrize("name,sizes", [
+    ("cfg2_small_bf16", (33, 65, 97, 161, 257)),
+    ("cfg4_8b_bf16", (40, 70, 100, 128, 170, 200, 256, 290, 384))])
+def test_a_row_keeps_its_bits_in_every_tile(name, sizes):
+    import paper_2509_18521_amd as ap
+    base = ai.WORKLOADS[name]
+    shape = ai.reduced(base, n_layers=1, vocab=2080).shape          # (an odd number of vocabulary tiles)
+    classes, gen = 31, 2
+    weights = ai.make_weights(shape, base.seed)
+    alone = None
+    for n in (4,) + sizes:
+        w = ai.Workload(f"{name}_tiles_{n}", shape, classes, 5, n, n, gen, 0.7, 0.1, gen, gen, ai.SAMPLER_GREEDY, 0, 1, base.seed)
+        reqs = ai.make_requests(w, n)
+        ctoks = class_forced_tokens(w, classes)
+        forced = {r.request_id: ctoks[r.request_id % classes][:gen] for r in reqs}
+        watched = sorted(set(r for r in range(n) if r % classes < 4) | {n - 1})
+        ctx = make_engine(w, weights, debug=True, max_inflight=n)
+        try:
+            for rid in watched:
+                ap.april_debug_watch(ctx, rid, 0, gen)
+            run_gpu(ctx, reqs, n, n, gen, 1, forced=forced)
+            got = {(rid, i): ap.april_debug_logits(ctx, rid, i, shape.vocab)[0] for rid in watched for i in range(gen)}
+        finally:
+            ap.april_destroy(ctx)
+        if alone is None:
+            alone = got
+        for (rid, i), row in got.items():
+            if rid % classes < 4:
+                assert np.array_equal(row, alone[(rid % classes, i)]), (n, rid, i)
+            else:
+                assert np.isfinite(row).all(), (n, rid, i)
