@@ -679,14 +679,13 @@ void forward(april_ctx* c, RowCtx rows, RowCtx srows, const int* gather, double 
   float* lg_out = c->write_logits ? c->logits : nullptr;
   {
     ProfScope p(c, KC_GEMM_LMHEAD, (double)V * d * e + SB * d * e, 2.0 * SB * V * d);
-    // more than 128 sampling rows: the tiled kernel reads the head once per 256 rows instead of
-    // once per 128 (same bits either way).  (The categorical sampler wants fp64 exponentials, which
-    // launch_group_records takes from the logits below.)
+    // (the categorical sampler wants fp64 exponentials, which launch_group_records takes from the logits below)
     const GroupOut go{c->group_max, c->group_idx, c->cfg.sampler == APRIL_SAMPLER_CATEGORICAL ? nullptr : c->group_sum,
                       1.0f / sampler_cfg(c).temperature};
-    if (c->use_mfma && c->group_max && c->tile_gemm && srows.max_rows > 128 && d % 32 == 0)
-      launch_gemm_tile_logits(st, srows, (const bf16_t*)c->hf, c->lm_head_s, lg_out, go, V, d);
-    else if (c->use_mfma && c->group_max) launch_gemm_mfma_logits(st, srows, (const bf16_t*)c->hf, c->lm_head_s, lg_out, go, V, d);
+    if (c->use_mfma) {
+      if (!(c->tile_gemm && launch_gemm_tile_logits(st, srows, (const bf16_t*)c->hf, c->lm_head_s, lg_out, go, V, d)))
+        launch_gemm_mfma_logits(st, srows, (const bf16_t*)c->hf, c->lm_head_s, lg_out, go, V, d);
+    }
     else if (c->bf16) launch_gemm_ref<bf16_t, true>(st, srows, (const bf16_t*)c->hf, (const bf16_t*)c->lm_head, c->logits, V, d);
     else launch_gemm_f32(st, srows, (const float*)c->hf, (const float*)c->lm_head, c->logits, V, d);
   }

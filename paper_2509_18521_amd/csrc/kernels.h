@@ -225,7 +225,7 @@ void launch_gemm_tile_swiglu(hipStream_t st, RowCtx rc, const bf16_t* x, const b
                              bf16_t* act, int F, int K);
 bool launch_gemm_tile_swiglu_chain(hipStream_t st, RowCtx rc, const bf16_t* x, const bf16_t* Wg, const bf16_t* Wu,
                                    bf16_t* act, int F, int K, const float* ssq, int ssq_stride, float eps);
-void launch_gemm_tile_logits(hipStream_t st, RowCtx rc, const bf16_t* x, const bf16_t* Wp, float* logits,
+bool launch_gemm_tile_logits(hipStream_t st, RowCtx rc, const bf16_t* x, const bf16_t* Wp, float* logits,
                              const GroupOut& go, int V, int K);
 // LM head: logits fp32 [rows][V] plus, per row, records of every group of lmhead_group_cols()
 // consecutive logits (the last group of a vocabulary that is not a multiple of it is short).

@@ -343,6 +343,16 @@ struct TileMoe {
   size_t w_expert_stride;      // bf16x8 units between the experts' matrices
 };
 
+// (weight tile group, row group) of a workgroup.  LM head: a 1-D grid with the row groups of one weight
+// tile group 8 ids apart - same XCD, same moment, one HBM read of the head instead of one per row group.
+// Else x = weight tile group, y = row group.
+template <int EPI>
+__device__ __forceinline__ int2 tile_of_block(const RowCtx& rc, int MT) {
+  if (EPI != TEPI_LOGITS) return make_int2(blockIdx.x, blockIdx.y);
+  const int mg = ceil_div(ceil_div(rc.max_rows, 32), MT), rem = (int)blockIdx.x % (8 * mg);
+  return make_int2(((int)blockIdx.x / (8 * mg)) * 8 + (rem & 7), rem >> 3);
+}
+
 template <int WGM, int WGN, int MTW, int NTW, int BK, int R, int EPI, bool CHAIN, bool MOE = false>
 __device__ __forceinline__ void tile_dma_body(RowCtx rc, const bf16x8* __restrict__ x, const bf16x8* __restrict__ w0,
                                               const bf16x8* __restrict__ w1, float* __restrict__ out,
@@ -354,7 +364,8 @@ __device__ __forceinline__ void tile_dma_body(RowCtx rc, const bf16x8* __restric
   static_assert(EPI != TEPI_SWIGLU || NTW % 2 == 0, "gate/up pairs");
   static_assert(R >= 3 && (R - 2) * PER < 64, "ring depth");
   __shared__ bf16x8 lds[R][BK][FR][64];
-  const int bx = blockIdx.x, by = blockIdx.y;
+  const int2 at = tile_of_block<EPI>(rc, MT);
+  const int bx = at.x, by = at.y;
   int rows = rows_or_zero(rc);
   const int m0 = by * MT;
   if constexpr (MOE) {
@@ -367,7 +378,7 @@ __device__ __forceinline__ void tile_dma_body(RowCtx rc, const bf16x8* __restric
     w0 += (size_t)e * mo.w_expert_stride;
     if (w1 != nullptr) w1 += (size_t)e * mo.w_expert_stride;
   } else {
-    if (m0 * 32 >= rows) return;
+    if (m0 * 32 >= rows || (EPI == TEPI_LOGITS && bx * NT * 32 >= N)) return;
   }
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave / WGN, wn = wave % WGN;
@@ -538,8 +549,9 @@ __global__ __launch_bounds__(256, 1) void gemm_big_kernel(RowCtx rc, const bf16x
   constexpr int MT = 8, NT = 8, MTW = 4, NTW = 4, BK = 2, R = 4, FR = MT + NT, PER = FR * BK / 4;
   __shared__ bf16x8 lds[R][BK][FR][64];
   const int rows = rows_or_zero(rc);
-  const int m0 = blockIdx.y * MT;
-  if (m0 * 32 >= rows) return;
+  const int2 at = tile_of_block<EPI>(rc, MT);
+  const int bx = at.x, m0 = at.y * MT;
+  if (m0 * 32 >= rows || (EPI == TEPI_LOGITS && bx * NT * 32 >= N)) return;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave >> 1, wn = wave & 1;
   const int KT = K >> 4, n_stages = KT / BK;
@@ -553,9 +565,9 @@ __global__ __launch_bounds__(256, 1) void gemm_big_kernel(RowCtx rc, const bf16x
     if (EPI == TEPI_SWIGLU) {
       constexpr int H = NTW / 2;
       const int col = i / NTW, ii = i % NTW;
-      return (ii < H ? w0 : w1) + (size_t)min((int)blockIdx.x * (NT / 2) + col * H + (ii < H ? ii : ii - H), n_tiles - 1) * KT * 64;
+      return (ii < H ? w0 : w1) + (size_t)min(bx * (NT / 2) + col * H + (ii < H ? ii : ii - H), n_tiles - 1) * KT * 64;
     }
-    return w0 + (size_t)min((int)blockIdx.x * NT + i, n_tiles - 1) * KT * 64;
+    return w0 + (size_t)min(bx * NT + i, n_tiles - 1) * KT * 64;
   };
   const int skk = wave & 1, st0 = wave >> 1;             // this wavefront copies k-tile skk of slots st0, st0 + 2, ...
   const bf16x8* src[PER];                               // wavefront-uniform: scalar registers
@@ -631,10 +643,10 @@ __global__ __launch_bounds__(256, 1) void gemm_big_kernel(RowCtx rc, const bf16x
   for (; s + R - 1 < n_stages; ++s) stage(s, std::true_type{});
   for (; s < n_stages; ++s) stage(s, std::false_type{});
   if constexpr (EPI == TEPI_QKV) {
-    qkv_epilogue<MTW, DH>(acc, blockIdx.x * NT + wn * NTW, m0 + wm * MTW, rows, n_tiles, lane, rc, qo);
+    qkv_epilogue<MTW, DH>(acc, bx * NT + wn * NTW, m0 + wm * MTW, rows, n_tiles, lane, rc, qo);
     return;
   }
-  tile_epilogue<MTW, NTW, EPI>(acc, blockIdx.x * (EPI == TEPI_SWIGLU ? NT / 2 : NT) + wn * (EPI == TEPI_SWIGLU ? NTW / 2 : NTW),
+  tile_epilogue<MTW, NTW, EPI>(acc, bx * (EPI == TEPI_SWIGLU ? NT / 2 : NT) + wn * (EPI == TEPI_SWIGLU ? NTW / 2 : NTW),
                                m0 + wm * MTW, rows, n_tiles, N, lane, out, act, nullptr, m0 * 32, &go);
 }
 
@@ -803,15 +815,34 @@ bool launch_gemm_tile_swiglu_chain(hipStream_t st, RowCtx rc, const bf16_t* x, c
   return true;
 }
 
-// LM head for many rows: logits plus the group records.  Same accumulation chain
-// per element as the skinny LM-head kernel (k-tiles in order, one accumulator), so the choice
-// between the two changes no bit.  Needs K % 32 == 0.
-void launch_gemm_tile_logits(hipStream_t st, RowCtx rc, const bf16_t* x, const bf16_t* Wp, float* logits,
+// LM head: logits (optional) plus the group records.  One accumulation chain per element whatever the
+// tile (k-tiles in order): the choice changes no bit.  False (nothing launched): the skinny kernel is
+// the one to use.
+// The head is read once (from HBM: its bound up to about 200 rows) and every row group's workgroups run
+// beside each other (tile_of_block).  us per launch, skinny | 64 x 256 | 128 x 256 | 256 x 256 tile:
+//                 7 rows          64 rows             128 rows             192 rows        384 rows
+//   128256 x 4096 179 | 191       192 | 189 | 195     239 | 224 | 195      278 | 239       394 | 443 (500 with the row groups a grid apart)
+//   151936 x 2560 146 | 142       167 | 150 | 158     214 | 178 | 163      212 | 213       306 | 358 (394)
+//   151936 x 2048 123 | 125       137 | 131 | 139     173 | 138 | 138      163 | 177       244 | 299 (330)
+//   151936 x 896   49 | 45         56 | 49 | 53        77 | 58 | 58         79 | 101       117 | 164 (169)
+//   32032 x 1184   15 | 16         18 | 16 | 24        25 | 18 | 25         26 | 36         36 | 41
+bool launch_gemm_tile_logits(hipStream_t st, RowCtx rc, const bf16_t* x, const bf16_t* Wp, float* logits,
                              const GroupOut& go, int V, int K) {
-  const int n_tiles = V >> 5, m_tiles = ceil_div(rc.max_rows, 32);
-  dim3 grid(ceil_div(n_tiles, 8), ceil_div(m_tiles, 8));
-  hipLaunchKernelGGL((TILE_WIDE(TEPI_LOGITS)), grid, dim3(256), 0, st, rc, reinterpret_cast<const bf16x8*>(x),
-                     reinterpret_cast<const bf16x8*>(Wp), nullptr, logits, nullptr, V, K, go, QkvOut{});
+  if (K % 32 != 0) return false;
+  const int groups = ceil_div(V >> 5, 8), rows = rc.max_rows;            // 256-column groups
+  if (rows <= 32 && (K >= 3072 || groups < 256)) return false;
+#define LM_LAUNCH(KERNEL, MT, ...)                                                                                      \
+  hipLaunchKernelGGL((KERNEL), dim3(ceil_div(groups, 8) * 8 * ceil_div(ceil_div(rows, 32), MT)), dim3(256), 0, st, rc,  \
+                     reinterpret_cast<const bf16x8*>(x), reinterpret_cast<const bf16x8*>(Wp), nullptr, logits, nullptr, V, K, __VA_ARGS__)
+#define LM_64 gemm_tile_dma_kernel<1, 4, 2, 2, 2, 4, TEPI_LOGITS>
+#define LM_128 gemm_tile_dma_kernel<1, 4, 4, 2, 2, 3, TEPI_LOGITS>
+  if (rows <= 64 || (rows <= 128 && groups < 256)) LM_LAUNCH(LM_64, 2, go);
+  else if (rows <= 128 || rows > 256 || K < 3072) LM_LAUNCH(LM_128, 4, go);
+  else LM_LAUNCH(TILE_WIDE(TEPI_LOGITS), 8, go, QkvOut{});
+#undef LM_64
+#undef LM_128
+#undef LM_LAUNCH
+  return true;
 }
 
 }  // namespace april
