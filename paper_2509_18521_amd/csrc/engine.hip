@@ -50,6 +50,24 @@ struct SlotH {
   std::vector<int> forced;
 };
 
+// Per-slot block, host and device, in units of n_slots ints: request ids (2), then what is uploaded only,
+// then the five arrays that a step reads back, in that order.
+enum { SLOTS_REQ = 0, SLOTS_PROMPT = 2, SLOTS_LIMIT = 3, SLOTS_GEN = 4, SLOTS_STATE = 5, SLOTS_KV = 6, SLOTS_BLOCKS = 7,
+       SLOTS_FINISH = 8, SLOTS_ARRAYS = 9 };
+constexpr int XFER_INTS = 1 << 18, XFER_ITEMS = 4096;
+
+// What one prefill chunk uploads, in one copy.  Offsets in ints (items on 16 bytes).
+struct PrefillBlock {
+  int rows, nseq, n_items;
+  int items() const { return 4; }                                   // after {rows, stop = 0, nseq, stop = 0}
+  int srow_slot() const { return items() + 4 * n_items; }
+  int srow_pos() const { return srow_slot() + nseq; }
+  int gather() const { return srow_pos() + nseq; }
+  int row_slot() const { return gather() + nseq; }
+  int row_pos() const { return row_slot() + rows; }
+  int size() const { return row_pos() + rows; }
+};
+
 struct Entry {
   long long req = -1;
   int slot = -1;                 // -1: token-level entry without a slot
@@ -120,18 +138,20 @@ struct april_ctx {
   int watch_rows_cap = 0, watch_rows_used = 0, n_watch = 0, watch_cap = 2048;
   std::map<std::pair<long long, int>, int> watch_row_of;
 
-  // prefill staging (device) + pinned host staging
+  // prefill staging (device) + pinned host staging: one block per chunk, see PrefillBlock
   int prefill_cap = 0;
-  int *d_pf_row_slot = nullptr, *d_pf_row_pos = nullptr, *d_pf_nrows = nullptr;
-  int *d_pf_srow_slot = nullptr, *d_pf_srow_pos = nullptr, *d_pf_nsrows = nullptr, *d_pf_gather = nullptr;
-  int4* d_pf_items = nullptr;    // query tiles of the chunk's sequences (prefill attention)
+  int* d_pf = nullptr;
+  const int4* pf_items = nullptr;   // query tiles of the chunk's sequences (prefill attention), inside d_pf
   int pf_n_items = 0, pf_items_cap = 0;
   bool prefill_tiled = true;     // query-tiled prefill attention (APRIL_PREFILL_ATTN=rows: one workgroup per row)
   int *d_list_a = nullptr, *d_list_b = nullptr;
   int* h_stage = nullptr;        // pinned
   size_t h_stage_ints = 0;
-  int* h_slot_arrays = nullptr;  // pinned: mirrors for D2H/H2D of per-slot ints
-  long long* h_req = nullptr;    // pinned
+  int* h_slot_arrays = nullptr;  // pinned mirror of the per-slot block (SLOTS_* offsets)
+  int* d_slot_arrays = nullptr;
+  int* h_xfer = nullptr;         // pinned: tokens / log-probabilities on their way (launch_xfer), XFER_INTS ints
+  XferItem* h_xfer_items = nullptr;
+  bool xfer_pending = false;     // an upload may still be reading them
 
   // workspaces
   int m_cap = 0;
@@ -583,7 +603,7 @@ void forward(april_ctx* c, RowCtx rows, RowCtx srows, const int* gather, double 
       // prefill: one workgroup per tile of query positions, the keys / values of a prompt are
       // streamed once per tile instead of once per row
       ProfScope p(c, KC_ATTN, C * 2.0 * nkv * e + B * nq * (4.0 + e), 4.0 * C * nq);
-      launch_attn_prefill(st, c->d_pf_items, c->pf_n_items, c->ds, q16, (const bf16_t*)c->kv_pool, c->kvl, l, Hq,
+      launch_attn_prefill(st, c->pf_items, c->pf_n_items, c->ds, q16, (const bf16_t*)c->kv_pool, c->kvl, l, Hq,
                           (bf16_t*)c->attn_out);
     } else if (c->attn_mfma) {
       const int gs = std::min(c->attn_max_splits, std::max(1, ceil_div(c->step_max_ctx, c->attn_chunk)));
@@ -711,18 +731,44 @@ int upload_slot_tables(april_ctx* c) {
   // host mirrors are authoritative between steps
   const int S = c->n_slots;
   int* a = c->h_slot_arrays;
+  long long* req = reinterpret_cast<long long*>(a + SLOTS_REQ * S);
   for (int i = 0; i < S; ++i) {
     const SlotH& s = c->slots[i];
-    a[0 * S + i] = s.prompt_len; a[1 * S + i] = s.gen; a[2 * S + i] = s.limit;
-    a[3 * S + i] = s.state; a[4 * S + i] = s.kv_len; a[5 * S + i] = s.n_blocks;
-    a[6 * S + i] = 0;
-    c->h_req[i] = s.req;
+    req[i] = s.req;
+    a[SLOTS_PROMPT * S + i] = s.prompt_len; a[SLOTS_GEN * S + i] = s.gen; a[SLOTS_LIMIT * S + i] = s.limit;
+    a[SLOTS_STATE * S + i] = s.state; a[SLOTS_KV * S + i] = s.kv_len; a[SLOTS_BLOCKS * S + i] = s.n_blocks;
+    a[SLOTS_FINISH * S + i] = 0;
   }
-  int* dst[7] = {c->ds.prompt_len, c->ds.gen, c->ds.limit, c->ds.state, c->ds.kv_len, c->ds.n_blocks, c->ds.finish_iter};
-  for (int k = 0; k < 7; ++k)
-    HIPCHK(c, hipMemcpyAsync(dst[k], a + k * S, S * sizeof(int), hipMemcpyHostToDevice, c->stream));
-  HIPCHK(c, hipMemcpyAsync(c->ds.req_id, c->h_req, S * sizeof(long long), hipMemcpyHostToDevice, c->stream));
+  HIPCHK(c, hipMemcpyAsync(c->d_slot_arrays, a, (size_t)SLOTS_ARRAYS * S * sizeof(int), hipMemcpyHostToDevice, c->stream));
   return APRIL_OK;
+}
+
+// Many host <-> device pieces through the pinned transfer buffer, as many per launch as it holds.
+struct XferPiece { int* dev; int* host; size_t n; };
+int xfer(april_ctx* c, const std::vector<XferPiece>& pieces, bool to_device) {
+  int n_items = 0, used = 0;
+  std::vector<std::pair<int*, int>> out;            // download: (host destination, item)
+  if (c->xfer_pending) { HIPCHK(c, hipStreamSynchronize(c->stream)); c->xfer_pending = false; }
+  auto flush = [&](bool last) -> int {
+    if (n_items == 0) return APRIL_OK;
+    launch_xfer(c->stream, c->h_xfer_items, n_items, c->h_xfer, to_device);
+    if (!to_device || !last) HIPCHK(c, hipStreamSynchronize(c->stream));
+    else c->xfer_pending = true;
+    for (auto& o : out) memcpy(o.first, c->h_xfer + c->h_xfer_items[o.second].off, (size_t)c->h_xfer_items[o.second].n * sizeof(int));
+    out.clear();
+    n_items = used = 0;
+    return APRIL_OK;
+  };
+  for (const XferPiece& p : pieces)
+    for (size_t at = 0; at < p.n;) {
+      if (n_items == XFER_ITEMS || used == XFER_INTS) { int rc = flush(false); if (rc != APRIL_OK) return rc; }
+      const int n = (int)std::min<size_t>(p.n - at, XFER_INTS - used);
+      c->h_xfer_items[n_items] = XferItem{p.dev + at, used, n};
+      if (to_device) memcpy(c->h_xfer + used, p.host + at, (size_t)n * sizeof(int));
+      else out.push_back({p.host + at, n_items});
+      ++n_items; used += n; at += n;
+    }
+  return flush(true);
 }
 
 }  // namespace
@@ -862,10 +908,12 @@ int april_init(const april_model_cfg* cfg, const april_tensor* weights, int32_t 
   c->slots.assign(S, SlotH());
   c->ds.max_blocks = c->max_blocks;
   c->ds.max_ctx = c->max_ctx;
-  TRY(dev_alloc(c, &c->ds.req_id, S));
-  TRY(dev_alloc(c, &c->ds.prompt_len, S)); TRY(dev_alloc(c, &c->ds.gen, S)); TRY(dev_alloc(c, &c->ds.limit, S));
-  TRY(dev_alloc(c, &c->ds.state, S)); TRY(dev_alloc(c, &c->ds.kv_len, S)); TRY(dev_alloc(c, &c->ds.n_blocks, S));
-  TRY(dev_alloc(c, &c->ds.finish_iter, S));
+  TRY(dev_alloc(c, &c->d_slot_arrays, (size_t)SLOTS_ARRAYS * S));
+  c->ds.req_id = reinterpret_cast<long long*>(c->d_slot_arrays + (size_t)SLOTS_REQ * S);
+  {
+    int** arrays[7] = {&c->ds.prompt_len, &c->ds.limit, &c->ds.gen, &c->ds.state, &c->ds.kv_len, &c->ds.n_blocks, &c->ds.finish_iter};
+    for (int k = 0; k < 7; ++k) *arrays[k] = c->d_slot_arrays + (size_t)(SLOTS_PROMPT + k) * S;
+  }
   TRY(dev_alloc(c, &c->ds.block_table, (size_t)S * c->max_blocks));
   TRY(dev_alloc(c, &c->ds.tokens, (size_t)S * c->max_ctx));
   c->ds.forced = nullptr;
@@ -879,8 +927,9 @@ int april_init(const april_model_cfg* cfg, const april_tensor* weights, int32_t 
   if (g.n_samples_per_prompt > 1) { TRY(dev_alloc(c, &c->ds.group, S)); TRY(dev_alloc(c, &c->ds.grp_left, S)); }
   TRY(dev_alloc(c, &c->d_ctrl, 1));
   HIPTRY(hipHostMalloc((void**)&c->h_ctrl, sizeof(Ctrl)));
-  HIPTRY(hipHostMalloc((void**)&c->h_slot_arrays, (size_t)8 * S * sizeof(int)));
-  HIPTRY(hipHostMalloc((void**)&c->h_req, (size_t)S * sizeof(long long)));
+  HIPTRY(hipHostMalloc((void**)&c->h_slot_arrays, (size_t)SLOTS_ARRAYS * S * sizeof(int)));
+  HIPTRY(hipHostMalloc((void**)&c->h_xfer, (size_t)XFER_INTS * sizeof(int)));
+  HIPTRY(hipHostMalloc((void**)&c->h_xfer_items, XFER_ITEMS * sizeof(XferItem)));
   TRY(dev_alloc(c, &c->d_row_slot, S)); TRY(dev_alloc(c, &c->d_row_pos, S));
   TRY(dev_alloc(c, &c->d_list_a, 2048)); TRY(dev_alloc(c, &c->d_list_b, 2048));
 
@@ -983,12 +1032,9 @@ int april_init(const april_model_cfg* cfg, const april_tensor* weights, int32_t 
   TRY(dev_alloc(c, &c->rope_cos, (size_t)g.max_ctx * g.head_dim / 2, false));
   TRY(dev_alloc(c, &c->rope_sin, (size_t)g.max_ctx * g.head_dim / 2, false));
   launch_rope_table(c->stream, c->rope_cos, c->rope_sin, g.max_ctx, g.head_dim, g.rope_theta);
-  TRY(dev_alloc(c, &c->d_pf_row_slot, M)); TRY(dev_alloc(c, &c->d_pf_row_pos, M));
-  TRY(dev_alloc(c, &c->d_pf_nrows, 2)); TRY(dev_alloc(c, &c->d_pf_nsrows, 2));   // {rows, stop = 0}
-  TRY(dev_alloc(c, &c->d_pf_srow_slot, S)); TRY(dev_alloc(c, &c->d_pf_srow_pos, S)); TRY(dev_alloc(c, &c->d_pf_gather, S));
   c->pf_items_cap = (int)(M / 16 + S + 16);
-  TRY(dev_alloc(c, &c->d_pf_items, (size_t)c->pf_items_cap));
   c->h_stage_ints = 2 * M + 8 * (size_t)S + 64 + 4 * (size_t)c->pf_items_cap;
+  TRY(dev_alloc(c, &c->d_pf, c->h_stage_ints));
   HIPTRY(hipHostMalloc((void**)&c->h_stage, c->h_stage_ints * sizeof(int)));
 
   // ---- parity-mode capture ----------------------------------------------------------
@@ -1031,7 +1077,8 @@ void april_destroy(april_ctx* c) {
   if (c->sr_ws) hipFree(c->sr_ws);
   if (c->h_ctrl) hipHostFree(c->h_ctrl);
   if (c->h_slot_arrays) hipHostFree(c->h_slot_arrays);
-  if (c->h_req) hipHostFree(c->h_req);
+  if (c->h_xfer) hipHostFree(c->h_xfer);
+  if (c->h_xfer_items) hipHostFree(c->h_xfer_items);
   if (c->h_stage) hipHostFree(c->h_stage);
   if (c->h_snaps) hipHostFree(c->h_snaps);
   for (auto& ev : c->ev_pool) { hipEventDestroy(ev.first); hipEventDestroy(ev.second); }
@@ -1636,17 +1683,25 @@ int april_rollout_step(april_ctx* c, const april_request* new_reqs, int32_t n_ne
   bool device_touched = false;          // the step has started to change per-slot device state
   april_buffer* nb = nullptr;
   auto body = [&]() -> int {
-  for (Upload& u : uploads) {
-    HIPCHK(c, hipMemcpyAsync(c->ds.tokens + (size_t)u.slot * c->max_ctx, u.tokens.data(), u.tokens.size() * sizeof(int), hipMemcpyHostToDevice, st));
-    if (c->ds.logprob && !u.logprobs.empty())
-      HIPCHK(c, hipMemcpyAsync(c->ds.logprob + (size_t)u.slot * c->max_ctx, u.logprobs.data(), u.logprobs.size() * sizeof(float), hipMemcpyHostToDevice, st));
-    if (u.has_forced) {
-      launch_fill_i32(st, c->ds.forced + (size_t)u.slot * c->max_ctx, -1, (size_t)c->max_ctx);
-      if (!u.forced.empty())
-        HIPCHK(c, hipMemcpyAsync(c->ds.forced + (size_t)u.slot * c->max_ctx, u.forced.data(), u.forced.size() * sizeof(int), hipMemcpyHostToDevice, st));
+  {
+    std::vector<XferPiece> pieces;
+    bool forced = false;
+    for (Upload& u : uploads) {
+      pieces.push_back({c->ds.tokens + (size_t)u.slot * c->max_ctx, u.tokens.data(), u.tokens.size()});
+      if (c->ds.logprob && !u.logprobs.empty())
+        pieces.push_back({reinterpret_cast<int*>(c->ds.logprob) + (size_t)u.slot * c->max_ctx, reinterpret_cast<int*>(u.logprobs.data()), u.logprobs.size()});
+      if (u.has_forced) {
+        launch_fill_i32(st, c->ds.forced + (size_t)u.slot * c->max_ctx, -1, (size_t)c->max_ctx);
+        if (!u.forced.empty()) {
+          HIPCHK(c, hipMemcpyAsync(c->ds.forced + (size_t)u.slot * c->max_ctx, u.forced.data(), u.forced.size() * sizeof(int), hipMemcpyHostToDevice, st));
+          forced = true;
+        }
+      }
     }
+    int rc = xfer(c, pieces, true);
+    if (rc != APRIL_OK) return rc;
+    if (forced) HIPCHK(c, hipStreamSynchronize(st));   // those sources are pageable host vectors
   }
-  HIPCHK(c, hipStreamSynchronize(st));   // the upload sources are pageable host vectors
 
   // ---- run ------------------------------------------------------------------------------
   double t_prefill = 0, t_decode = 0;
@@ -1666,8 +1721,7 @@ int april_rollout_step(april_ctx* c, const april_request* new_reqs, int32_t n_ne
     hc.n_rows = 0; hc.finished = D; hc.n_target = N_units; hc.stop = 0; hc.iter = 0; hc.stop_iter = -1;
     hc.free_top = c->free_pages_host; hc.error = 0; hc.n_slots = c->n_slots; hc.eos_token = c->cfg.eos_token;
     hc.n_watch = c->n_watch; hc.inflight = (int)inflight.size(); hc.n_preempted = 0; hc.sum_live = 0; hc.sum_ctx = 0; hc.iter_ctx = 0; hc.sum_experts = 0;
-    HIPCHK(c, hipMemcpyAsync(c->d_ctrl, &hc, sizeof(Ctrl), hipMemcpyHostToDevice, st));
-    HIPCHK(c, hipStreamSynchronize(st));
+    HIPCHK(c, hipMemcpyAsync(c->d_ctrl, &hc, sizeof(Ctrl), hipMemcpyHostToDevice, st));   // (pinned; next written by the read-back behind it)
 
     // Upper bound on the iterations of this step when only length limits end rollouts:
     // the (N - D)-th smallest remaining length.  With an EOS token the device may stop
@@ -1722,42 +1776,42 @@ int april_rollout_step(april_ctx* c, const april_request* new_reqs, int32_t n_ne
     // prefill in chunks of whole sequences
     size_t pi = 0;
     while (pi < prefill_slots.size()) {
-      int rows = 0, nseq = 0, chunk_max_ctx = 1;
-      int* hs = c->h_stage;
-      int* h_row_slot = hs; int* h_row_pos = hs + c->m_cap;
-      int* h_ss = hs + 2 * (size_t)c->m_cap; int* h_sp = h_ss + c->n_slots; int* h_g = h_sp + c->n_slots;
-      int* h_list = h_g + c->n_slots; int* h_need = h_list + c->n_slots; int* h_n = h_need + c->n_slots;
-      int4* h_items = reinterpret_cast<int4*>(hs + 2 * (size_t)c->m_cap + 8 * (size_t)c->n_slots + 64);
+      // the sequences of this chunk, then its block in one copy
+      PrefillBlock pb{0, 0, 0};
+      int chunk_max_ctx = 1;
+      const size_t first = pi;
       const int q_tile = attn_prefill_tile(c->dm.n_q_heads / c->dm.n_kv_heads);
-      int n_items = 0;
       while (pi < prefill_slots.size()) {
-        const int s = prefill_slots[pi];
-        const SlotH& sh = c->slots[s];
+        const SlotH& sh = c->slots[prefill_slots[pi]];
         const int nt = sh.prompt_len + sh.gen;
-        if (rows + nt > c->prefill_cap && nseq > 0) break;
-        for (int q0 = 0; q0 < nt && n_items < c->pf_items_cap; q0 += q_tile) h_items[n_items++] = int4{s, rows, nt, q0};
-        for (int p = 0; p < nt; ++p) { h_row_slot[rows + p] = s; h_row_pos[rows + p] = p; }
-        h_ss[nseq] = s; h_sp[nseq] = nt - 1; h_g[nseq] = rows + nt - 1;
-        h_list[nseq] = s; h_need[nseq] = ceil_div(nt, blk);
-        rows += nt; ++nseq; ++pi;
+        if (pb.rows + nt > c->prefill_cap && pb.nseq > 0) break;
+        pb.rows += nt; ++pb.nseq; ++pi;
+        pb.n_items += ceil_div(nt, q_tile);
         chunk_max_ctx = std::max(chunk_max_ctx, nt);
       }
+      if (pb.n_items > c->pf_items_cap || (size_t)pb.size() > c->h_stage_ints)
+        return fail(c, APRIL_EDEVICE, "prefill chunk of %d rows exceeds its staging block", pb.rows);
+      const int rows = pb.rows, nseq = pb.nseq;
+      int* hs = c->h_stage;
+      hs[0] = rows; hs[1] = 0; hs[2] = nseq; hs[3] = 0;
+      int4* h_items = reinterpret_cast<int4*>(hs + pb.items());
+      for (int q = 0, row = 0, item = 0; q < nseq; ++q) {
+        const int s = prefill_slots[first + q];
+        const int nt = c->slots[s].prompt_len + c->slots[s].gen;
+        for (int q0 = 0; q0 < nt; q0 += q_tile) h_items[item++] = int4{s, row, nt, q0};
+        for (int p = 0; p < nt; ++p) { hs[pb.row_slot() + row + p] = s; hs[pb.row_pos() + row + p] = p; }
+        hs[pb.srow_slot() + q] = s; hs[pb.srow_pos() + q] = nt - 1; hs[pb.gather() + q] = row + nt - 1;
+        row += nt;
+      }
       // longest walks over the keys first, so that the launch drains on short ones
-      std::stable_sort(h_items, h_items + n_items, [](const int4& a, const int4& b) { return a.w > b.w; });
+      std::stable_sort(h_items, h_items + pb.n_items, [](const int4& a, const int4& b) { return a.w > b.w; });
       c->step_max_ctx = chunk_max_ctx;
-      h_n[0] = rows; h_n[1] = nseq;
-      HIPCHK(c, hipMemcpyAsync(c->d_pf_row_slot, h_row_slot, rows * sizeof(int), hipMemcpyHostToDevice, st));
-      HIPCHK(c, hipMemcpyAsync(c->d_pf_row_pos, h_row_pos, rows * sizeof(int), hipMemcpyHostToDevice, st));
-      HIPCHK(c, hipMemcpyAsync(c->d_pf_srow_slot, h_ss, nseq * sizeof(int), hipMemcpyHostToDevice, st));
-      HIPCHK(c, hipMemcpyAsync(c->d_pf_srow_pos, h_sp, nseq * sizeof(int), hipMemcpyHostToDevice, st));
-      HIPCHK(c, hipMemcpyAsync(c->d_pf_gather, h_g, nseq * sizeof(int), hipMemcpyHostToDevice, st));
-      HIPCHK(c, hipMemcpyAsync(c->d_pf_nrows, h_n, sizeof(int), hipMemcpyHostToDevice, st));
-      HIPCHK(c, hipMemcpyAsync(c->d_pf_nsrows, h_n + 1, sizeof(int), hipMemcpyHostToDevice, st));
-      HIPCHK(c, hipMemcpyAsync(c->d_pf_items, h_items, n_items * sizeof(int4), hipMemcpyHostToDevice, st));
-      c->pf_n_items = n_items;
-      RowCtx prc{c->d_pf_row_slot, c->d_pf_row_pos, reinterpret_cast<const int2*>(c->d_pf_nrows), rows};
-      RowCtx src{c->d_pf_srow_slot, c->d_pf_srow_pos, reinterpret_cast<const int2*>(c->d_pf_nsrows), nseq};
-      forward(c, prc, src, c->d_pf_gather, rows, 0);
+      HIPCHK(c, hipMemcpyAsync(c->d_pf, hs, (size_t)pb.size() * sizeof(int), hipMemcpyHostToDevice, st));
+      c->pf_items = reinterpret_cast<const int4*>(c->d_pf + pb.items());
+      c->pf_n_items = pb.n_items;
+      RowCtx prc{c->d_pf + pb.row_slot(), c->d_pf + pb.row_pos(), reinterpret_cast<const int2*>(c->d_pf), rows};
+      RowCtx src{c->d_pf + pb.srow_slot(), c->d_pf + pb.srow_pos(), reinterpret_cast<const int2*>(c->d_pf + 2), nseq};
+      forward(c, prc, src, c->d_pf + pb.gather(), rows, 0);
       HIPCHK(c, hipStreamSynchronize(st));     // staging buffers are reused by the next chunk
     }
     HIPCHK(c, hipMemcpyAsync(c->h_ctrl, c->d_ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, st));
@@ -1866,11 +1920,9 @@ int april_rollout_step(april_ctx* c, const april_request* new_reqs, int32_t n_ne
 
     // ---- read back per-slot state --------------------------------------------------------
     const int S = c->n_slots;
-    int* srcs[5] = {c->ds.gen, c->ds.state, c->ds.kv_len, c->ds.n_blocks, c->ds.finish_iter};
-    for (int k = 0; k < 5; ++k)
-      HIPCHK(c, hipMemcpyAsync(c->h_slot_arrays + k * S, srcs[k], S * sizeof(int), hipMemcpyDeviceToHost, st));
+    HIPCHK(c, hipMemcpyAsync(c->h_slot_arrays + (size_t)SLOTS_GEN * S, c->ds.gen, (size_t)5 * S * sizeof(int), hipMemcpyDeviceToHost, st));
     HIPCHK(c, hipStreamSynchronize(st));
-    memcpy(snap.data(), c->h_slot_arrays, 5 * S * sizeof(int));
+    memcpy(snap.data(), c->h_slot_arrays + (size_t)SLOTS_GEN * S, (size_t)5 * S * sizeof(int));
     c->free_pages_host = c->h_ctrl->free_top;
   }
 
@@ -1900,18 +1952,17 @@ int april_rollout_step(april_ctx* c, const april_request* new_reqs, int32_t n_ne
   nb = new_buffer(c);
   std::vector<int> release;             // slots whose rollout is returned now
   int delivered = 0;                    // units: rollouts (G = 1) or groups
+  std::vector<XferPiece> results;       // tokens and log-probabilities of `release`
   auto deliver_slot = [&](int s) -> int {
     SlotH& sh = c->slots[s];
     c->r_req.push_back(sh.req);
     c->r_group.push_back(sh.group);
     c->r_tokens.emplace_back((size_t)sh.gen);
-    if (sh.gen > 0)
-      HIPCHK(c, hipMemcpyAsync(c->r_tokens.back().data(), c->ds.tokens + (size_t)s * c->max_ctx + sh.prompt_len,
-                               (size_t)sh.gen * sizeof(int), hipMemcpyDeviceToHost, st));
+    // (the vectors' storage stays where it is when the outer vectors grow)
+    results.push_back({c->ds.tokens + (size_t)s * c->max_ctx + sh.prompt_len, c->r_tokens.back().data(), (size_t)sh.gen});
     c->r_logprobs.emplace_back(c->ds.logprob ? (size_t)sh.gen : 0);
-    if (c->ds.logprob && sh.gen > 0)
-      HIPCHK(c, hipMemcpyAsync(c->r_logprobs.back().data(), c->ds.logprob + (size_t)s * c->max_ctx,
-                               (size_t)sh.gen * sizeof(float), hipMemcpyDeviceToHost, st));
+    if (c->ds.logprob)
+      results.push_back({reinterpret_cast<int*>(c->ds.logprob) + (size_t)s * c->max_ctx, reinterpret_cast<int*>(c->r_logprobs.back().data()), (size_t)sh.gen});
     c->r_ntok.push_back(sh.gen);
     c->r_nres.push_back(sh.n_resumes);
     release.push_back(s);
@@ -1974,7 +2025,7 @@ int april_rollout_step(april_ctx* c, const april_request* new_reqs, int32_t n_ne
       if (it == gindex.end() || !g_delivered[it->second]) nb->entries.push_back(e);
     }
   }
-  HIPCHK(c, hipStreamSynchronize(st));
+  { int rc = xfer(c, results, false); if (rc != APRIL_OK) return rc; }
   // complete rollouts that stay keep their tokens (slot) but no KV pages
   {
     std::vector<int> to_free = release;

@@ -96,6 +96,11 @@ void launch_free_slots(hipStream_t st, Ctrl* ctrl, Slots s, const int* slot_list
 void launch_init_free_stack(hipStream_t st, int* free_stack, int n_blocks);
 void launch_fill_i32(hipStream_t st, int* p, int v, size_t n);
 
+// Copies between device arrays and one pinned host buffer, many pieces in one launch (the kernel reads /
+// writes the host memory itself): item = `n` ints at `dev` <-> buf + off.  `items` and `buf` are pinned.
+struct XferItem { int* dev; int off, n; };
+void launch_xfer(hipStream_t st, const XferItem* items, int n_items, int* buf, bool to_device);
+
 // Group records an LM head leaves: arrays [rows][ceil(V / lmhead_group_cols())].
 struct GroupOut {
   float* max;        // maximum of the group

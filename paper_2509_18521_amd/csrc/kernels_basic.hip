@@ -283,6 +283,26 @@ void launch_fill_i32(hipStream_t st, int* p, int v, size_t n) {
 }
 
 // ---------------------------------------------------------------------------
+// Token and log-probability arrays of many slots <-> one pinned host buffer.  A step moved them with one
+// pageable copy per rollout and array, 8 us of host time and 3 us on the stream each: 950 copies in
+// a step of 384 rollouts (7 ms of 170), 0.7 of 3.7 ms in the smallest configuration.  The host side
+// of a transfer is bound by the link, so one wavefront per 64 consecutive ints with several in flight is enough.
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(256) void xfer_kernel(const XferItem* items, int* buf, int to_device) {
+  const XferItem it = items[blockIdx.x];
+  int* host = buf + it.off;
+  const int stride = gridDim.y * 256;
+  for (int i = blockIdx.y * 256 + threadIdx.x; i < it.n; i += stride) {
+    if (to_device) it.dev[i] = host[i];
+    else host[i] = it.dev[i];
+  }
+}
+void launch_xfer(hipStream_t st, const XferItem* items, int n_items, int* buf, bool to_device) {
+  if (n_items <= 0) return;
+  hipLaunchKernelGGL(xfer_kernel, dim3(n_items, 8), dim3(256), 0, st, items, buf, to_device ? 1 : 0);
+}
+
+// ---------------------------------------------------------------------------
 // Embedding gather: x_res[r] = E[token at (slot, pos)]
 // ---------------------------------------------------------------------------
 template <typename T>
