@@ -167,7 +167,7 @@ struct april_ctx {
   // bf16 MFMA attention: split-KV workspace
   bool attn_mfma = false, fuse_rope = true, tile_gemm = true, fuse_norm = true, fuse_down = false;
   bool moe_tile = true;         // prefill: expert GEMMs on the LDS-tiled kernel
-  bf16_t* h_rows = nullptr;     // plain [row][d] copy of the MLP input (routed experts, prefill)
+  bf16_t* h_rows = nullptr;     // plain [row][d] copy of the MLP input (routed experts)
   int moe_tall_rows = 2048;     // expert GEMMs: 4 m-tiles per workgroup from this row bound (prefill), 2 below
   int tile_decode_rows = 0;     // decode gate/up goes through the LDS-tiled kernel from this bound on the rows in flight (0 = never)
   float* ssq = nullptr;         // [d_model / 32][m_cap] per-row partial sums of squares (fused norm)
@@ -637,8 +637,8 @@ void forward(april_ctx* c, RowCtx rows, RowCtx srows, const int* gather, double 
     } else {
       if (tile) gemm_resid_tile(KC_GEMM_O, c->attn_out, L.wo_s, d, nq);
       else gemm(KC_GEMM_O, rows, c->attn_out, L.wo, L.wo_s, c->proj, d, nq, so, c->proj_stride, B);
-      // (routed experts in prefill gather token rows: they get a plain [row][d] copy as well)
-      norm(rows, so, L.mlp_norm, c->h_act, nullptr, B, false, c->moe && tile && c->moe_tile ? c->h_rows : nullptr);
+      // (routed experts gather token rows: they get a plain [row][d] copy as well)
+      norm(rows, so, L.mlp_norm, c->h_act, nullptr, B, false, c->moe ? c->h_rows : nullptr);
     }
     if (c->moe) {
       const int E = c->n_experts, Fe = c->d_expert, tk = c->top_k_experts;
@@ -657,7 +657,7 @@ void forward(april_ctx* c, RowCtx rows, RowCtx srows, const int* gather, double 
         ProfScope p(c, KC_MOE_GATEUP, hit * 2.0 * Fe * d * e + B * tk * (d + Fe) * e, 4.0 * B * tk * Fe * d);
         if (!(moe_tiled && launch_moe_tile_gateup(st, rows, c->moe_cnt, c->moe_base, c->moe_group, c->moe_src, c->h_rows,
                                                   L.eg_s, L.eu_s, c->moe_act, Fe, d, n_groups)))
-          launch_moe_gateup(st, rows, c->moe_cnt, c->moe_base, c->moe_group, c->moe_src, (const bf16_t*)c->h_act, L.eg_s, L.eu_s, c->moe_act, E, tk, Fe, d, tall);
+          launch_moe_gateup(st, rows, c->moe_cnt, c->moe_base, c->moe_group, c->moe_src, c->h_rows, L.eg_s, L.eu_s, c->moe_act, E, tk, Fe, d, tall);
       }
       {
         ProfScope p(c, KC_MOE_DOWN, hit * 1.0 * Fe * d * e + B * tk * (Fe * e + d * 4.0), 2.0 * B * tk * Fe * d);
@@ -993,7 +993,7 @@ int april_init(const april_model_cfg* cfg, const april_tensor* weights, int32_t 
     TRY(dev_alloc(c, &c->moe_group, c->moe_p_cap / 64 + 1));
     TRY(dev_alloc(c, &c->moe_act, (size_t)c->moe_p_cap * Fe));
     TRY(dev_alloc(c, &c->moe_out, (size_t)c->moe_p_cap * d));
-    if (c->moe_tile) TRY(dev_alloc(c, &c->h_rows, M * d));
+    TRY(dev_alloc(c, &c->h_rows, M * d));
   }
   const size_t SR = ((size_t)S + 31) / 32 * 32;
   TRY(dev_alloc(c, &c->logits, SR * V));

@@ -136,7 +136,7 @@ int moe_group_count(int max_rows, int top_k, int E, int align);
 // packed rows (the dispatch must have aligned the expert segments to that), one accumulator chain
 // per output element.  Return false (nothing launched) for shapes they do not take.
 int moe_tile_rows();
-// (gate/up: h_rows is the plain [row][d] copy of the normalised activations that
+// (gate/up, here and below: h_rows is the plain [row][d] copy of the normalised activations that
 // launch_add_rmsnorm writes on request; its rows are gathered through src_row)
 bool launch_moe_tile_gateup(hipStream_t st, RowCtx rc, const int* cnt, const int* base, const int* group_expert,
                             const int* src_row, const bf16_t* h_rows, const bf16_t* Wg, const bf16_t* Wu, bf16_t* act,
@@ -144,7 +144,7 @@ bool launch_moe_tile_gateup(hipStream_t st, RowCtx rc, const int* cnt, const int
 bool launch_moe_tile_down(hipStream_t st, RowCtx rc, const int* cnt, const int* base, const int* group_expert,
                           const bf16_t* act, const bf16_t* Wd, float* out, int Fe, int d, int n_groups);
 void launch_moe_gateup(hipStream_t st, RowCtx rc, const int* cnt, const int* base, const int* group_expert,
-                       const int* src_row, const bf16_t* h, const bf16_t* Wg, const bf16_t* Wu, bf16_t* act, int E,
+                       const int* src_row, const bf16_t* h_rows, const bf16_t* Wg, const bf16_t* Wu, bf16_t* act, int E,
                        int top_k, int Fe, int d, int tall_rows);
 void launch_moe_down(hipStream_t st, RowCtx rc, const int* cnt, const int* base, const int* group_expert,
                      const bf16_t* act, const bf16_t* Wd, float* out, int E, int top_k, int Fe, int d, int tall_rows);

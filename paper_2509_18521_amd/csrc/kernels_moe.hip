@@ -25,10 +25,14 @@ __global__ __launch_bounds__(64) void moe_route_kernel(RowCtx rc, const float* l
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     const int e = lane + 64 * j;
-    float a = -INFINITY;
+    // up to 8 partials (the split-k bound) requested together, added in order
+    float part[8], a = -INFINITY;
+#pragma unroll
+    for (int p = 0; p < 8; ++p) part[p] = logits[min(p, n_partials - 1) * partial_stride + (size_t)r * E + min(e, E - 1)];
     if (e < E) {
       a = 0.f;
-      for (int p = 0; p < n_partials; ++p) a += logits[p * partial_stride + (size_t)r * E + e];
+#pragma unroll
+      for (int p = 0; p < 8; ++p) if (p < n_partials) a += part[p];
     }
     v[j] = a;
     mx = fmaxf(mx, a);
@@ -86,6 +90,7 @@ void launch_moe_route(hipStream_t st, RowCtx rc, const float* logits, int n_part
 // the worst case, five of six workgroups of a decode launch - and nearly all of a prefill
 // launch - found nothing to do after a dependent load.
 // Placement inside an expert's batch is arbitrary (LDS atomics); values never depend on it.
+// (One thread adding up the 128 segments was 5 of 15 us.)
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(1024) void moe_dispatch_kernel(RowCtx rc, const int* ids, int E, int top_k, int* cnt,
                                                             int* base, int* pos_of, int* src_row, int p_cap,
@@ -98,12 +103,31 @@ __global__ __launch_bounds__(1024) void moe_dispatch_kernel(RowCtx rc, const int
   const int n = rows * top_k;
   for (int a = tid; a < n; a += 1024) atomicAdd(&s_cnt[ids[a]], 1);
   __syncthreads();
-  if (tid == 0) {
-    int acc = 0;
-    int hit = 0;
-    for (int e = 0; e < E; ++e) { s_base[e] = acc; acc += (s_cnt[e] + align - 1) / align * align; hit += s_cnt[e] > 0; }
-    s_base[E] = acc;
-    if (ctrl != nullptr) ctrl->sum_experts += hit;
+  if (tid < 64) {
+    // exclusive prefix sum of the aligned segments: lane l owns experts 4 l .. 4 l + 3 (E <= 256)
+    int own[4], sum = 0, hit = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int n_e = 4 * tid + j < E ? s_cnt[4 * tid + j] : 0;
+      own[j] = (n_e + align - 1) / align * align;
+      sum += own[j];
+      hit += n_e > 0;
+    }
+    int incl = sum;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const int o = __shfl_up(incl, off, 64);
+      if (tid >= off) incl += o;
+      hit += __shfl_xor(hit, off, 64);
+    }
+    int acc = incl - sum;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      if (4 * tid + j <= E) s_base[4 * tid + j] = acc;
+      acc += own[j];
+    }
+    if (tid == 63 && E == 256) s_base[256] = acc;
+    if (tid == 0 && ctrl != nullptr) ctrl->sum_experts += hit;
   }
   __syncthreads();
   const int total = s_base[E];
@@ -143,97 +167,100 @@ void launch_moe_dispatch(hipStream_t st, RowCtx rc, const int* ids, int E, int t
 //   GATHER = true : the B operand rows are token rows looked up through src_row (gate/up);
 //   GATHER = false: the B operand is the packed fragment-tiled activation (down).
 // ---------------------------------------------------------------------------
+// The weights are the traffic (1.2 GB of a layer of 128 experts of 3 x 768 x 2048, about ten rows each), so
+// the kernel is cut for many workgroups per compute unit: a group that has rows for one m-tile only
+// runs the one-tile body (half the registers of the two-tile one), k-tiles are fetched in two
+// alternating groups, and token rows are gathered from a plain [row][K] copy - out of the
+// fragment-tiled layout a gathered row uses 16 bytes of every 128-byte line it touches, which at ten rows
+// was more traffic than the weights.  At 160-240 rows, 8 of those 128 experts per row: gate/up 169 -> 144 us
+// (5.6 TB/s), down 107 -> 80 us (5.0 TB/s).
 constexpr int MOE_KW = 4;
 
-template <int NT, int MT, bool SWIGLU>
-__global__ __launch_bounds__(64 * MOE_KW) void moe_gemm_kernel(const int* stop, const int* cnt, const int* base,
-                                                              const int* __restrict__ group_expert,
-                                                              const int* src_row, const bf16x8* __restrict__ x,
-                                                              const bf16x8* __restrict__ w0,
-                                                              const bf16x8* __restrict__ w1, size_t w_expert_stride,
-                                                              float* __restrict__ out, bf16_t* __restrict__ act,
-                                                              int N, int K, int x_cols) {
-  constexpr int KU = MT > 2 ? 4 : 8;            // k-tiles requested together (register budget)
-  __shared__ float red[(MOE_KW - 1) * NT * MT * 16 * 64];
-  if (stop != nullptr && *stop != 0) return;
-  const int e = group_expert[blockIdx.y];
-  if (e < 0) return;
-  const int rows_e = cnt[e];
-  const int p0 = base[e];                       // first packed row of this expert (multiple of MT * 32)
-  const int mt0 = (int)blockIdx.y * MT - (p0 >> 5);   // first m-tile of this group inside the expert's batch
-  if (mt0 * 32 >= rows_e) return;
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int KT = K >> 4;
-  const int nt0 = SWIGLU ? blockIdx.x : blockIdx.x * NT;
-  int mtc = ((rows_e + 31) >> 5) - mt0;
-  if (mtc > MT) mtc = MT;
+struct MoeArgs {
+  const int* src_row;
+  const bf16x8* x;
+  const bf16x8 *w0, *w1;
+  size_t w_expert_stride;
+  float* out;
+  bf16_t* act;
+  int N, K;
+};
 
-  f32x16 acc[NT][MT];
+template <int NT, int MTC, bool SWIGLU, int KH>
+__device__ __forceinline__ void moe_group(const MoeArgs& ma, int e, int rows_e, int p0, int mt0, float* red) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int N = ma.N, KT = ma.K >> 4;
+  const int nt0 = SWIGLU ? blockIdx.x : blockIdx.x * NT;
+  f32x16 acc[NT][MTC];
 #pragma unroll
   for (int i = 0; i < NT; ++i)
 #pragma unroll
-    for (int j = 0; j < MT; ++j) acc[i][j] = f32x16{};
+    for (int j = 0; j < MTC; ++j) acc[i][j] = f32x16{};
   const bf16x8* wp[NT];
-  const bf16x8* we0 = w0 + (size_t)e * w_expert_stride;
+  const bf16x8* we0 = ma.w0 + (size_t)e * ma.w_expert_stride;
   if (SWIGLU) {
     wp[0] = we0 + (size_t)nt0 * KT * 64 + lane;
-    wp[NT - 1] = w1 + (size_t)e * w_expert_stride + (size_t)nt0 * KT * 64 + lane;
+    wp[NT - 1] = ma.w1 + (size_t)e * ma.w_expert_stride + (size_t)nt0 * KT * 64 + lane;
   } else {
 #pragma unroll
     for (int i = 0; i < NT; ++i) wp[i] = we0 + (size_t)(nt0 + i) * KT * 64 + lane;
   }
-  // B operand pointers: either a token row of the un-packed activation (gathered per lane)
-  // or the packed tile
-  const bf16x8* xp[MT];
-  bool xok[MT];
+  // B operand: a token row of the plain activation copy (gathered per lane; a k-tile of a row is two
+  // 16-byte pieces; rows past the expert's repeat its last one, never written), or the packed tile
+  const bf16x8* xp[MTC];
+  constexpr int XS = SWIGLU ? 2 : 64;
 #pragma unroll
-  for (int j = 0; j < MT; ++j) {
-    xok[j] = j < mtc;
-    xp[j] = x;
+  for (int j = 0; j < MTC; ++j) {
     if (SWIGLU) {
-      int row = -1;
-      if (j < mtc) row = src_row[p0 + (mt0 + j) * 32 + (lane & 31)];
-      xok[j] = row >= 0;
-      if (row < 0) row = 0;
-      // fragment-tiled token activation [rows][x_cols]: element (row, k) -> act_index<true>
-      xp[j] = x + ((size_t)(row >> 5) * (x_cols >> 4) * 64 + (row & 31) + ((lane >> 5) << 5));
-    } else if (j < mtc) {
-      xp[j] = x + ((size_t)((p0 >> 5) + mt0 + j) * KT * 64 + lane);
+      const int row = ma.src_row[p0 + min((mt0 + j) * 32 + (lane & 31), rows_e - 1)];
+      xp[j] = ma.x + ((size_t)(row < 0 ? 0 : row) * KT * 2 + (lane >> 5));
+    } else {
+      xp[j] = ma.x + ((size_t)((p0 >> 5) + mt0 + j) * KT * 64 + lane);
     }
   }
-  const int len = KT;
-  const int kb = (int)((long long)len * wave / MOE_KW), ke = (int)((long long)len * (wave + 1) / MOE_KW);
-  for (int kt = kb; kt < ke; kt += KU) {
-    bf16x8 a[KU][NT], b[KU][MT];
+  const int kb = (int)((long long)KT * wave / MOE_KW), ke = (int)((long long)KT * (wave + 1) / MOE_KW);
+  bf16x8 a[2][KH][NT], b[2][KH][MTC];
+  auto fetch = [&](int g, int kt) {
 #pragma unroll
-    for (int u = 0; u < KU; ++u) {
-      const size_t k = (size_t)(kt + u < ke ? kt + u : ke - 1) * 64;
+    for (int u = 0; u < KH; ++u) {
+      const size_t k = (size_t)(kt + u < ke ? kt + u : ke - 1);
 #pragma unroll
-      for (int i = 0; i < NT; ++i) a[u][i] = wp[i][k];
+      for (int i = 0; i < NT; ++i) a[g][u][i] = wp[i][k * 64];
 #pragma unroll
-      for (int j = 0; j < MT; ++j) b[u][j] = xok[j] ? xp[j][k] : bf16x8{};
+      for (int j = 0; j < MTC; ++j) b[g][u][j] = xp[j][k * XS];
     }
-    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto multiply = [&](int g, int kt) {
 #pragma unroll
-    for (int u = 0; u < KU; ++u) {
+    for (int u = 0; u < KH; ++u)
       if (kt + u < ke) {
 #pragma unroll
         for (int i = 0; i < NT; ++i)
 #pragma unroll
-          for (int j = 0; j < MT; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[u][i], b[u][j], acc[i][j], 0, 0, 0);
+          for (int j = 0; j < MTC; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[g][u][i], b[g][u][j], acc[i][j], 0, 0, 0);
       }
+  };
+  if (kb < ke) {
+    fetch(0, kb);
+    for (int kt = kb; kt < ke; kt += 2 * KH) {
+      fetch(1, kt + KH);
+      __builtin_amdgcn_sched_barrier(0);
+      multiply(0, kt);
+      if (kt + 2 * KH < ke) fetch(0, kt + 2 * KH);
+      __builtin_amdgcn_sched_barrier(0);
+      multiply(1, kt + KH);
     }
   }
-  constexpr int NREG = NT * MT * 16;
+  constexpr int NREG = NT * MTC * 16;
   if (wave != 0) {
     float* dst = red + (size_t)(wave - 1) * NREG * 64 + lane;
 #pragma unroll
     for (int i = 0; i < NT; ++i)
 #pragma unroll
-      for (int j = 0; j < MT; ++j)
+      for (int j = 0; j < MTC; ++j)
 #pragma unroll
-        for (int q = 0; q < 16; ++q) dst[((i * MT + j) * 16 + q) * 64] = acc[i][j][q];
+        for (int q = 0; q < 16; ++q) dst[((i * MTC + j) * 16 + q) * 64] = acc[i][j][q];
   }
   __syncthreads();
   if (wave != 0) return;
@@ -243,14 +270,13 @@ __global__ __launch_bounds__(64 * MOE_KW) void moe_gemm_kernel(const int* stop, 
 #pragma unroll
     for (int i = 0; i < NT; ++i)
 #pragma unroll
-      for (int j = 0; j < MT; ++j)
+      for (int j = 0; j < MTC; ++j)
 #pragma unroll
-        for (int q = 0; q < 16; ++q) acc[i][j][q] += src[((i * MT + j) * 16 + q) * 64];
+        for (int q = 0; q < 16; ++q) acc[i][j][q] += src[((i * MTC + j) * 16 + q) * 64];
   }
   const int mloc = lane & 31, nhalf = (lane >> 5) << 2;
 #pragma unroll
-  for (int j = 0; j < MT; ++j) {
-    if (j >= mtc) continue;
+  for (int j = 0; j < MTC; ++j) {
     const int ml = (mt0 + j) * 32 + mloc;            // row inside the expert's batch
     if (ml >= rows_e) continue;
     const int p = p0 + ml;                           // packed row
@@ -264,7 +290,7 @@ __global__ __launch_bounds__(64 * MOE_KW) void moe_gemm_kernel(const int* stop, 
           const float g = acc[0][j][4 * q + t], u = acc[NT - 1][j][4 * q + t];
           v[t] = (bf16_t)silu_mul(g, u);
         }
-        *reinterpret_cast<bf16x4*>(act + act_index<true>(p, f, N)) = v;
+        *reinterpret_cast<bf16x4*>(ma.act + act_index<true>(p, f, N)) = v;
       }
     } else {
 #pragma unroll
@@ -273,41 +299,56 @@ __global__ __launch_bounds__(64 * MOE_KW) void moe_gemm_kernel(const int* stop, 
         for (int q = 0; q < 4; ++q) {
           const int n = (nt0 + i) * 32 + 8 * q + nhalf;
           f32x4 v = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
-          *reinterpret_cast<f32x4*>(out + (size_t)p * N + n) = v;
+          *reinterpret_cast<f32x4*>(ma.out + (size_t)p * N + n) = v;
         }
     }
   }
 }
 
+// (fetch groups of 6 / 4 k-tiles at two workgroups per compute unit; 4 / 2 at three, 8 / 5 at two and 2 / 1 at
+// four: within 3 %)
+template <int NT, int MT, bool SWIGLU>
+__global__ __launch_bounds__(64 * MOE_KW, MT > 2 ? 1 : 2) void moe_gemm_kernel(const int* stop, const int* cnt, const int* base,
+                                                                     const int* __restrict__ group_expert, MoeArgs ma) {
+  __shared__ float red[(MOE_KW - 1) * NT * MT * 16 * 64];
+  if (stop != nullptr && *stop != 0) return;
+  const int e = group_expert[blockIdx.y];
+  if (e < 0) return;
+  const int rows_e = cnt[e];
+  const int p0 = base[e];                       // first packed row of this expert (multiple of MT * 32)
+  const int mt0 = (int)blockIdx.y * MT - (p0 >> 5);   // first m-tile of this group inside the expert's batch
+  if (mt0 * 32 >= rows_e) return;
+  const int mtc = ((rows_e + 31) >> 5) - mt0;
+  if (mtc == 1) moe_group<NT, 1, SWIGLU, 6>(ma, e, rows_e, p0, mt0, red);
+  else if (MT == 2 || mtc == 2) moe_group<NT, 2, SWIGLU, MT == 2 ? 4 : 2>(ma, e, rows_e, p0, mt0, red);
+  else if (mtc == 3) moe_group<NT, (MT > 2 ? 3 : 1), SWIGLU, 2>(ma, e, rows_e, p0, mt0, red);
+  else moe_group<NT, MT, SWIGLU, 2>(ma, e, rows_e, p0, mt0, red);
+}
+
+template <bool SWIGLU>
+static void launch_moe_gemm(hipStream_t st, RowCtx rc, int n_groups_x, int align, int top_k, int E, const int* cnt, const int* base,
+                            const int* group_expert, const MoeArgs& ma) {
+  dim3 grid(n_groups_x, moe_group_count(rc.max_rows, top_k, E, align));
+  const int* stop = reinterpret_cast<const int*>(rc.ctl) + 1;
+  if (align == 128) hipLaunchKernelGGL((moe_gemm_kernel<2, 4, SWIGLU>), grid, dim3(64 * MOE_KW), 0, st, stop, cnt, base, group_expert, ma);
+  else hipLaunchKernelGGL((moe_gemm_kernel<2, 2, SWIGLU>), grid, dim3(64 * MOE_KW), 0, st, stop, cnt, base, group_expert, ma);
+}
+
 void launch_moe_gateup(hipStream_t st, RowCtx rc, const int* cnt, const int* base, const int* group_expert,
-                       const int* src_row, const bf16_t* h, const bf16_t* Wg, const bf16_t* Wu, bf16_t* act, int E,
+                       const int* src_row, const bf16_t* h_rows, const bf16_t* Wg, const bf16_t* Wu, bf16_t* act, int E,
                        int top_k, int Fe, int d, int tall_rows) {
   // tall batches (prefill): 4 m-tiles per workgroup, so an expert's weight tile is fetched half as
   // often; the summation chain of an output element does not depend on the grouping
-  const int align = moe_group_rows(rc.max_rows, tall_rows);
-  dim3 grid(Fe >> 5, moe_group_count(rc.max_rows, top_k, E, align));
-  const int* stop = reinterpret_cast<const int*>(rc.ctl) + 1;
-  const bf16x8 *hv = reinterpret_cast<const bf16x8*>(h), *gv = reinterpret_cast<const bf16x8*>(Wg), *uv = reinterpret_cast<const bf16x8*>(Wu);
-  if (align == 128)
-    hipLaunchKernelGGL((moe_gemm_kernel<2, 4, true>), grid, dim3(64 * MOE_KW), 0, st, stop, cnt, base, group_expert, src_row,
-                       hv, gv, uv, (size_t)Fe * d / 8, nullptr, act, Fe, d, d);
-  else
-    hipLaunchKernelGGL((moe_gemm_kernel<2, 2, true>), grid, dim3(64 * MOE_KW), 0, st, stop, cnt, base, group_expert, src_row,
-                       hv, gv, uv, (size_t)Fe * d / 8, nullptr, act, Fe, d, d);
+  launch_moe_gemm<true>(st, rc, Fe >> 5, moe_group_rows(rc.max_rows, tall_rows), top_k, E, cnt, base, group_expert,
+                        MoeArgs{src_row, reinterpret_cast<const bf16x8*>(h_rows), reinterpret_cast<const bf16x8*>(Wg),
+                                reinterpret_cast<const bf16x8*>(Wu), (size_t)Fe * d / 8, nullptr, act, Fe, d});
 }
 
 void launch_moe_down(hipStream_t st, RowCtx rc, const int* cnt, const int* base, const int* group_expert,
                      const bf16_t* act, const bf16_t* Wd, float* out, int E, int top_k, int Fe, int d, int tall_rows) {
-  const int align = moe_group_rows(rc.max_rows, tall_rows);
-  dim3 grid((d >> 5) / 2, moe_group_count(rc.max_rows, top_k, E, align));
-  const int* stop = reinterpret_cast<const int*>(rc.ctl) + 1;
-  const bf16x8 *av = reinterpret_cast<const bf16x8*>(act), *wv = reinterpret_cast<const bf16x8*>(Wd);
-  if (align == 128)
-    hipLaunchKernelGGL((moe_gemm_kernel<2, 4, false>), grid, dim3(64 * MOE_KW), 0, st, stop, cnt, base, group_expert, nullptr,
-                       av, wv, nullptr, (size_t)d * Fe / 8, out, nullptr, d, Fe, Fe);
-  else
-    hipLaunchKernelGGL((moe_gemm_kernel<2, 2, false>), grid, dim3(64 * MOE_KW), 0, st, stop, cnt, base, group_expert, nullptr,
-                       av, wv, nullptr, (size_t)d * Fe / 8, out, nullptr, d, Fe, Fe);
+  launch_moe_gemm<false>(st, rc, (d >> 5) / 2, moe_group_rows(rc.max_rows, tall_rows), top_k, E, cnt, base, group_expert,
+                         MoeArgs{nullptr, reinterpret_cast<const bf16x8*>(act), reinterpret_cast<const bf16x8*>(Wd), nullptr,
+                                 (size_t)d * Fe / 8, out, nullptr, d, Fe});
 }
 
 }  // namespace april
