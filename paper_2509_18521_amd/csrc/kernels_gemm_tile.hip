@@ -711,6 +711,20 @@ bool launch_moe_tile_down(hipStream_t st, RowCtx rc, const int* cnt, const int* 
 #define TILE_NARROW(EPI) gemm_tile_dma_kernel<2, 2, 4, 2, 2, 3, EPI>
 #define TILE_REGS(EPI) gemm_tile_kernel<2, 2, 4, 2, 2, EPI>
 
+// SMALL: 64 rows x 32 columns (SwiGLU: 32 features) on 2 wavefronts, ring of 16 stages, and MID: 128 x 64 on 4,
+// ring of 12 (8), for passes of few rows: there a workgroup of the larger tiles walks k alone at two
+// stages per memory latency, whatever the rows.  SMALL while its workgroups are at most one per compute unit, MID
+// while they are at most two (SwiGLU, 128 KiB of LDS: one; at 300 workgroups it loses 13-19 %).  us, NARROW or
+// WIDE / as here: 2560 x 9728 at 37, 256, 512, 1024 rows 146, 150, 150, 153 / 45, 64, 65, 127; 896 x 4864
+// at 37, 512, 2048 rows 73, 77, 77 / 24, 24, 36; 4096 x 4096 at 128, 512 rows 65, 68 / 21, 33; gate/up of
+// 2560 x 9728 at 64, 128 rows 45, 46 / 28, 28, of 896 x 4864 at 37, 256 rows 17, 18 / 8, 12.
+#define TILE_SMALL(EPI) gemm_tile_dma_kernel<2, 1, 1, 1, 2, 16, EPI>
+#define TILE_SMALL_SWIGLU gemm_tile_dma_kernel<2, 1, 1, 2, 2, 16, TEPI_SWIGLU>
+#define TILE_MID(EPI) gemm_tile_dma_kernel<2, 2, 2, 1, 2, 12, EPI>
+#define TILE_MID_SWIGLU gemm_tile_dma_kernel<2, 2, 2, 2, 2, 8, TEPI_SWIGLU>
+static bool small_tile(int units, int m_tiles) { return (long long)units * ceil_div(m_tiles, 2) <= 256; }
+static bool mid_tile(int units, int m_tiles, int most) { return (long long)ceil_div(units, 2) * ceil_div(m_tiles, 4) <= most; }
+
 // units: weight tiles (plain) or feature tiles (SwiGLU); per_wide: units per WIDE workgroup
 static bool wide_tile(int units, int per_wide, int m_tiles) {
   const int wgs = ceil_div(units, per_wide) * ceil_div(m_tiles, 8);
@@ -725,6 +739,10 @@ static void launch_tile(hipStream_t st, RowCtx rc, const bf16_t* x, const bf16_t
   if (K % 32 != 0) {
     dim3 grid(ceil_div(n_tiles, 4), ceil_div(m_tiles, 8));
     hipLaunchKernelGGL((TILE_REGS(EPI)), grid, dim3(256), 0, st, rc, xv, wv, nullptr, out, nullptr, N, K);
+  } else if (small_tile(n_tiles, m_tiles)) {
+    hipLaunchKernelGGL((TILE_SMALL(EPI)), dim3(n_tiles, ceil_div(m_tiles, 2)), dim3(128), 0, st, rc, xv, wv, nullptr, out, nullptr, N, K, GroupOut{});
+  } else if (mid_tile(n_tiles, m_tiles, 512)) {
+    hipLaunchKernelGGL((TILE_MID(EPI)), dim3(ceil_div(n_tiles, 2), ceil_div(m_tiles, 4)), dim3(256), 0, st, rc, xv, wv, nullptr, out, nullptr, N, K, GroupOut{});
   } else if (wide_tile(n_tiles, 8, m_tiles)) {
     dim3 grid(ceil_div(n_tiles, 8), ceil_div(m_tiles, 8));
     hipLaunchKernelGGL((TILE_WIDE(EPI)), grid, dim3(256), 0, st, rc, xv, wv, nullptr, out, nullptr, N, K, GroupOut{}, QkvOut{});
@@ -764,6 +782,10 @@ void launch_gemm_tile_swiglu(hipStream_t st, RowCtx rc, const bf16_t* x, const b
   if (K % 32 != 0) {
     dim3 grid(ceil_div(f_tiles, 2), ceil_div(m_tiles, 8));
     hipLaunchKernelGGL((TILE_REGS(TEPI_SWIGLU)), grid, dim3(256), 0, st, rc, xv, gv, uv, nullptr, act, F, K);
+  } else if (small_tile(f_tiles, m_tiles)) {
+    hipLaunchKernelGGL((TILE_SMALL_SWIGLU), dim3(f_tiles, ceil_div(m_tiles, 2)), dim3(128), 0, st, rc, xv, gv, uv, nullptr, act, F, K, GroupOut{});
+  } else if (mid_tile(f_tiles, m_tiles, 256)) {
+    hipLaunchKernelGGL((TILE_MID_SWIGLU), dim3(ceil_div(f_tiles, 2), ceil_div(m_tiles, 4)), dim3(256), 0, st, rc, xv, gv, uv, nullptr, act, F, K, GroupOut{});
   } else if (wide_tile(f_tiles, 4, m_tiles)) {
     dim3 grid(ceil_div(f_tiles, 4), ceil_div(m_tiles, 8));
     hipLaunchKernelGGL((TILE_WIDE(TEPI_SWIGLU)), grid, dim3(256), 0, st, rc, xv, gv, uv, nullptr, act, F, K, GroupOut{}, QkvOut{});

@@ -1,0 +1,40 @@
+"""The rows of a prefill pass pick its GEMM tiles (64 x 32, 128 x 64, 256 x 128, 256 x 256): a prompt's logits
+keep their bits alone and among however many others, at inner dimensions that fill the stage rings
+only partly."""
+import numpy as np
+import pytest
+
+import april_inputs as ai
+from gpu_common import have_gpu, make_engine, req_dicts
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _need_gpu():
+    if not have_gpu():
+        pytest.skip("no GPU")
+
+
+@pytest.mark.parametrize("d_model,d_ffn,head_dim,n_q", [(64, 96, 32, 1), (160, 4128, 64, 3), (1024, 2080, 128, 4)])
+def test_prompt_bits_do_not_depend_on_the_pass(d_model, d_ffn, head_dim, n_q):
+    import paper_2509_18521_amd as ap
+    shape = ai.ModelShape(2, d_model, n_q, 1, head_dim, d_ffn, 512)
+    weights = ai.make_weights(shape, 3)
+    rng = np.random.default_rng(d_model)
+    prompts = [rng.integers(0, shape.vocab, t, dtype=np.int32) for t in (5, 33, 64)]
+    alone = None
+    for n in (3, 6, 12, 24, 48, 120, 200):
+        w = ai.Workload("tiles", shape, 1, 64, n, n, 1, 0.0, 0.1, 1, 1, ai.SAMPLER_GREEDY, 0, 1, 3)
+        reqs = [ai.Request(i, prompts[i % 3], 1) for i in range(n)]
+        ctx = make_engine(w, weights, debug=True, max_inflight=n)
+        try:
+            for i in range(n):
+                ap.april_debug_watch(ctx, i, 0, 1)
+            ap.april_rollout_step(ctx, req_dicts(reqs), n, n, 1)
+            got = [ap.april_debug_logits(ctx, i, 0, shape.vocab)[0] for i in range(n)]
+        finally:
+            ap.april_destroy(ctx)
+        alone = alone or got
+        for i, row in enumerate(got):
+            assert np.isfinite(row).all() and np.array_equal(row, alone[i % 3]), (n, i)
