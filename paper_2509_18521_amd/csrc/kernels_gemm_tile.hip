@@ -343,12 +343,12 @@ struct TileMoe {
   size_t w_expert_stride;      // bf16x8 units between the experts' matrices
 };
 
-// (weight tile group, row group) of a workgroup.  LM head: a 1-D grid with the row groups of one weight
-// tile group 8 ids apart - same XCD, same moment, one HBM read of the head instead of one per row group.
+// (weight tile group, row group) of a workgroup.  NEAR (LM head, decode gate/up): a 1-D grid with the row groups
+// of one weight tile group 8 ids apart - same XCD, same moment, one HBM read instead of one per row group.
 // Else x = weight tile group, y = row group.
-template <int EPI>
+template <bool NEAR>
 __device__ __forceinline__ int2 tile_of_block(const RowCtx& rc, int MT) {
-  if (EPI != TEPI_LOGITS) return make_int2(blockIdx.x, blockIdx.y);
+  if (!NEAR) return make_int2(blockIdx.x, blockIdx.y);
   const int mg = ceil_div(ceil_div(rc.max_rows, 32), MT), rem = (int)blockIdx.x % (8 * mg);
   return make_int2(((int)blockIdx.x / (8 * mg)) * 8 + (rem & 7), rem >> 3);
 }
@@ -364,7 +364,7 @@ __device__ __forceinline__ void tile_dma_body(RowCtx rc, const bf16x8* __restric
   static_assert(EPI != TEPI_SWIGLU || NTW % 2 == 0, "gate/up pairs");
   static_assert(R >= 3 && (R - 2) * PER < 64, "ring depth");
   __shared__ bf16x8 lds[R][BK][FR][64];
-  const int2 at = tile_of_block<EPI>(rc, MT);
+  const int2 at = tile_of_block<EPI == TEPI_LOGITS || CHAIN>(rc, MT);
   const int bx = at.x, by = at.y;
   int rows = rows_or_zero(rc);
   const int m0 = by * MT;
@@ -378,7 +378,7 @@ __device__ __forceinline__ void tile_dma_body(RowCtx rc, const bf16x8* __restric
     w0 += (size_t)e * mo.w_expert_stride;
     if (w1 != nullptr) w1 += (size_t)e * mo.w_expert_stride;
   } else {
-    if (m0 * 32 >= rows || (EPI == TEPI_LOGITS && bx * NT * 32 >= N)) return;
+    if (m0 * 32 >= rows || (EPI == TEPI_LOGITS && bx * NT * 32 >= N) || (CHAIN && bx * (NT / 2) * 32 >= N)) return;
   }
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave / WGN, wn = wave % WGN;
@@ -549,7 +549,7 @@ __global__ __launch_bounds__(256, 1) void gemm_big_kernel(RowCtx rc, const bf16x
   constexpr int MT = 8, NT = 8, MTW = 4, NTW = 4, BK = 2, R = 4, FR = MT + NT, PER = FR * BK / 4;
   __shared__ bf16x8 lds[R][BK][FR][64];
   const int rows = rows_or_zero(rc);
-  const int2 at = tile_of_block<EPI>(rc, MT);
+  const int2 at = tile_of_block<EPI == TEPI_LOGITS>(rc, MT);
   const int bx = at.x, m0 = at.y * MT;
   if (m0 * 32 >= rows || (EPI == TEPI_LOGITS && bx * NT * 32 >= N)) return;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -798,42 +798,29 @@ void launch_gemm_tile_swiglu(hipStream_t st, RowCtx rc, const bf16_t* x, const b
 // Decode with many rows in flight: fused gate/up + SiLU*mul with the skinny kernel's summation
 // chains (see CHAIN above) and, when ssq is set, the folded RMSNorm of that kernel.  Returns
 // false (nothing launched) when the shape does not allow it.
-// Measured on MI355X, fused gate/up of a 4096 x 14336 (2560 x 9728) MLP, event pairs around eager
-// launches: at a row bound of 128 the half-height tile takes 76 (43) us against 84 (53) us for the
-// skinny kernel (tie at 96, slower at 64); at 256 the full tile 91 (60) us against 132 (67) us;
-// beyond 256 rows (two row groups) it does not pay.
+// Workgroups of 64 features and all the rows up to 256: 128 (2 x 2 accumulator tiles per wavefront), 192 (a
+// quarter less matrix work and LDS traffic than the full tile would spend on rows that are not there), 256 on 8
+// wavefronts (4 wavefronts of 128 x 64 with both accumulator sets need the whole register file each: 105 against
+// 97 us).  Beyond, several row groups beside each other (tile_of_block): of 128 rows where they all fit
+// two per compute unit, else of 192.  us per launch, skinny kernel | here, 9728 x 2560 at 96, 128, 192, 256, 320,
+// 384 rows: 34, 40, 48, 58, 60, 70 | 38, 38, 43, 45, 52, 53; 14336 x 4096: 69, 78, 94, 119, 130, 147 | 61, 62, 70,
+// 77, 127, 128 (row groups a grid apart: 148, 137).
 // A ring deeper than 3 stages made these variants 1.8x slower (the plain kernel does not care).
 bool launch_gemm_tile_swiglu_chain(hipStream_t st, RowCtx rc, const bf16_t* x, const bf16_t* Wg, const bf16_t* Wu,
                                    bf16_t* act, int F, int K, const float* ssq, int ssq_stride, float eps) {
   if (K % 128 != 0 || F % 32 != 0) return false;     // quarter boundaries on stage boundaries (BK = 2)
-  if (rc.max_rows > 256) return false;               // (14336 x 4096 at 320, 384 rows: 140-151, 143 us here, 130, 144-147 on the skinny kernel)
-  if (rc.max_rows <= 128) {
-    // half-height tile (128 rows x 64 features, 2 x 2 accumulator tiles per wavefront)
-    dim3 grid(ceil_div(F >> 5, 2), 1);
-    hipLaunchKernelGGL((gemm_tile_chain_kernel<2, 2, 2, 2, 2, 3, TEPI_SWIGLU>), grid, dim3(256), 0, st, rc,
-                       reinterpret_cast<const bf16x8*>(x), reinterpret_cast<const bf16x8*>(Wg),
-                       reinterpret_cast<const bf16x8*>(Wu), nullptr, act, F, K,
-                       TileNorm{ssq, ssq_stride, K >> 5, 1.0f / (float)K, eps, {}});
-    return true;
-  }
-  const int f_tiles = F >> 5, m_tiles = ceil_div(rc.max_rows, 32);
+  const int units = ceil_div(F >> 5, 2), m_tiles = ceil_div(rc.max_rows, 32);
   const TileNorm tn{ssq, ssq_stride, K >> 5, 1.0f / (float)K, eps, {}};
-  if (rc.max_rows <= 192) {
-    // 192-row tile (3 accumulator row tiles per wavefront): a quarter less matrix work and LDS
-    // traffic than the full tile would spend on rows that are not there
-    dim3 grid(ceil_div(f_tiles, 2), 1);
-    hipLaunchKernelGGL((gemm_tile_chain_kernel<2, 2, 3, 2, 2, 3, TEPI_SWIGLU>), grid, dim3(256), 0, st, rc,
-                       reinterpret_cast<const bf16x8*>(x), reinterpret_cast<const bf16x8*>(Wg),
-                       reinterpret_cast<const bf16x8*>(Wu), nullptr, act, F, K, tn);
-    return true;
-  }
-  // 256 rows x 64 features on 8 wavefronts of 64 x 64: with both accumulator sets a wavefront
-  // stays within 160 registers, so two or three run per SIMD (4 wavefronts of 128 x 64 need
-  // the whole register file each: 105 against 97 us per launch on the 4096 x 14336 MLP)
-  dim3 grid(ceil_div(f_tiles, 2), ceil_div(m_tiles, 8));
-  hipLaunchKernelGGL((gemm_tile_chain_kernel<4, 2, 2, 2, 2, 3, TEPI_SWIGLU>), grid, dim3(512), 0, st, rc,
-                     reinterpret_cast<const bf16x8*>(x), reinterpret_cast<const bf16x8*>(Wg),
-                     reinterpret_cast<const bf16x8*>(Wu), nullptr, act, F, K, tn);
+#define CHAIN_LAUNCH(WGM, MTW)                                                                                         \
+  hipLaunchKernelGGL((gemm_tile_chain_kernel<WGM, 2, MTW, 2, 2, 3, TEPI_SWIGLU>), dim3(ceil_div(units, 8) * 8 * ceil_div(m_tiles, WGM * MTW)), \
+                     dim3(64 * WGM * 2), 0, st, rc, reinterpret_cast<const bf16x8*>(x), reinterpret_cast<const bf16x8*>(Wg), \
+                     reinterpret_cast<const bf16x8*>(Wu), nullptr, act, F, K, tn)
+  if (rc.max_rows <= 128) CHAIN_LAUNCH(2, 2);
+  else if (rc.max_rows <= 192) CHAIN_LAUNCH(2, 3);
+  else if (rc.max_rows <= 256) CHAIN_LAUNCH(4, 2);
+  else if (units * ceil_div(m_tiles, 4) <= 512) CHAIN_LAUNCH(2, 2);
+  else CHAIN_LAUNCH(2, 3);
+#undef CHAIN_LAUNCH
   return true;
 }
 
