@@ -544,9 +544,9 @@ void forward(april_ctx* c, RowCtx rows, RowCtx srows, const int* gather, double 
   const int nq = Hq * dh, nkv = Hkv * dh, nqkv = nq + 2 * nkv;
   const double e = (double)c->esz;
   {
-    ProfScope p(c, KC_EMBED, B * d * (e + 4), 0);
-    if (c->bf16) launch_embed<bf16_t>(st, rows, c->ds, (const bf16_t*)c->tok_emb, c->x_res, d);
-    else launch_embed<float>(st, rows, c->ds, (const float*)c->tok_emb, c->x_res, d);
+    ProfScope p(c, KC_EMBED, B * d * (2 * e + 4), 0);      // with the first layer's norm
+    if (c->bf16) launch_embed_norm<bf16_t, true>(st, rows, c->ds, (const bf16_t*)c->tok_emb, c->x_res, c->layers[0].attn_norm, (bf16_t*)c->h_act, d, m.rms_eps);
+    else launch_embed_norm<float, false>(st, rows, c->ds, (const float*)c->tok_emb, c->x_res, c->layers[0].attn_norm, (float*)c->h_act, d, m.rms_eps);
   }
   // mlp_in = true: the partials are the previous layer's MLP output (for routed experts: the
   // top-k expert outputs of each row, gathered and weighted)
@@ -579,7 +579,7 @@ void forward(april_ctx* c, RowCtx rows, RowCtx srows, const int* gather, double 
   bool normed_by_down = false;       // the previous layer's down projection already did this layer's first norm
   for (int l = 0; l < m.n_layers; ++l) {
     const LayerW& L = c->layers[l];
-    if (!normed_by_down) norm(rows, l == 0 ? 0 : sd, L.attn_norm, c->h_act, nullptr, B, true);
+    if (l > 0 && !normed_by_down) norm(rows, sd, L.attn_norm, c->h_act, nullptr, B, true);
     // prefill: rotary + KV append in the projection's epilogue, queries as bf16 rows (in q_rot's memory)
     bf16_t* q16 = reinterpret_cast<bf16_t*>(c->q_rot);
     const bool pf_attn = c->attn_mfma && gather != nullptr && c->prefill_tiled;

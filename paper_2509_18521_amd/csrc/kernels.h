@@ -110,8 +110,9 @@ struct GroupOut {
 };
 
 // --- model ------------------------------------------------------------------
-template <typename T>
-void launch_embed(hipStream_t st, RowCtx rc, Slots s, const T* emb, float* x_res, int d);
+// x_res = embedding of each row's token; h = rmsnorm(x_res) * gain (the first layer's norm).
+template <typename T, bool XF>
+void launch_embed_norm(hipStream_t st, RowCtx rc, Slots s, const T* emb, float* x_res, const float* gain, T* h, int d, float eps);
 
 // x_res += sum of partials (if any); h = rmsnorm(x_res) * gain.  gather (nullable):
 // input row index of output row r.

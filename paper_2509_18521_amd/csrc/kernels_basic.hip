@@ -303,25 +303,6 @@ void launch_xfer(hipStream_t st, const XferItem* items, int n_items, int* buf, b
 }
 
 // ---------------------------------------------------------------------------
-// Embedding gather: x_res[r] = E[token at (slot, pos)]
-// ---------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(256) void embed_kernel(RowCtx rc, Slots s, const T* emb, float* x_res, int d) {
-  const int r = blockIdx.x;
-  ROW_GUARD(rc, r);
-  const int slot = rc.row_slot[r], pos = rc.row_pos[r];
-  const int tok = s.tokens[(size_t)slot * s.max_ctx + pos];
-  const T* e = emb + (size_t)tok * d;
-  for (int i = threadIdx.x; i < d; i += blockDim.x) x_res[(size_t)r * d + i] = to_f32(e[i]);
-}
-template <typename T>
-void launch_embed(hipStream_t st, RowCtx rc, Slots s, const T* emb, float* x_res, int d) {
-  hipLaunchKernelGGL(embed_kernel<T>, dim3(rc.max_rows), dim3(256), 0, st, rc, s, emb, x_res, d);
-}
-template void launch_embed<float>(hipStream_t, RowCtx, Slots, const float*, float*, int);
-template void launch_embed<bf16_t>(hipStream_t, RowCtx, Slots, const bf16_t*, float*, int);
-
-// ---------------------------------------------------------------------------
 // Residual add (deterministic sum of split-K partials) + RMSNorm.
 // One workgroup per output row; each thread owns up to 4 chunks of 8 columns.
 // ---------------------------------------------------------------------------
@@ -422,6 +403,64 @@ void launch_add_rmsnorm(hipStream_t st, RowCtx rc, float* x_res, const float* pa
 }
 template void launch_add_rmsnorm<float, false>(hipStream_t, RowCtx, float*, const float*, int, size_t, const float*, float*, int, float, const int*, const int*, const float*, float*);
 template void launch_add_rmsnorm<bf16_t, true>(hipStream_t, RowCtx, float*, const float*, int, size_t, const float*, bf16_t*, int, float, const int*, const int*, const float*, bf16_t*);
+
+// ---------------------------------------------------------------------------
+// Embedding gather + the first layer's RMSNorm: x_res[r] = E[token at (slot, pos)], h = rmsnorm(x_res) * gain.
+// Two launches before (an embedding launch is 5 us of an iteration, all latency: slot -> token -> row); the
+// sums are add_rmsnorm_kernel's, in its order.
+// ---------------------------------------------------------------------------
+template <typename T, bool XF>
+__global__ __launch_bounds__(256) void embed_norm_kernel(RowCtx rc, Slots s, const T* emb, float* x_res, const float* gain,
+                                                         T* h, int d, float eps) {
+  const int r = blockIdx.x;
+  ROW_GUARD(rc, r);
+  const int slot = rc.row_slot[r], pos = rc.row_pos[r];
+  const T* e = emb + (size_t)s.tokens[(size_t)slot * s.max_ctx + pos] * d;
+  __shared__ float sh[4];
+  typedef T T8 __attribute__((ext_vector_type(8)));
+  float v[4][8], ss = 0.f;
+  const int nchunk = d >> 3;
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    const int ch = threadIdx.x + c * 256;
+    if (ch < nchunk) {
+      const T8 ev = *reinterpret_cast<const T8*>(e + ch * 8);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) v[c][j] = to_f32(ev[j]);
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    const int ch = threadIdx.x + c * 256;
+    if (ch < nchunk) {
+      float* xp = x_res + (size_t)r * d + ch * 8;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) { xp[j] = v[c][j]; ss += v[c][j] * v[c][j]; }
+    }
+  }
+  ss = wave_sum(ss);
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = ss;
+  __syncthreads();
+  ss = sh[0] + sh[1] + sh[2] + sh[3];
+  const float rinv = 1.0f / sqrtf(ss / (float)d + eps);
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    const int ch = threadIdx.x + c * 256;
+    if (ch < nchunk) {
+      T* hp = h + act_index<XF>(r, ch * 8, d);
+      T8 hv;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) hv[j] = from_f32<T>(v[c][j] * rinv * gain[ch * 8 + j]);
+      *reinterpret_cast<T8*>(hp) = hv;
+    }
+  }
+}
+template <typename T, bool XF>
+void launch_embed_norm(hipStream_t st, RowCtx rc, Slots s, const T* emb, float* x_res, const float* gain, T* h, int d, float eps) {
+  hipLaunchKernelGGL((embed_norm_kernel<T, XF>), dim3(rc.max_rows), dim3(256), 0, st, rc, s, emb, x_res, gain, h, d, eps);
+}
+template void launch_embed_norm<float, false>(hipStream_t, RowCtx, Slots, const float*, float*, const float*, float*, int, float);
+template void launch_embed_norm<bf16_t, true>(hipStream_t, RowCtx, Slots, const bf16_t*, float*, const float*, bf16_t*, int, float);
 
 // ---------------------------------------------------------------------------
 // Rotary tables, computed once in double precision: cos/sin[pos][i], i < head_dim/2,
