@@ -38,3 +38,28 @@ def test_prompt_bits_do_not_depend_on_the_pass(d_model, d_ffn, head_dim, n_q):
         alone = alone or got
         for i, row in enumerate(got):
             assert np.isfinite(row).all() and np.array_equal(row, alone[i % 3]), (n, i)
+
+
+@pytest.mark.parametrize("experts", [32, 64, 160])
+def test_expert_groups_take_every_row_once(experts):
+    """Routed experts: the number of row groups picks how many of them an XCD takes in a row (0 below 64
+    groups); neither that nor a ragged last round may leave out or mix up a row."""
+    import paper_2509_18521_amd as ap
+    shape = ai.ModelShape(2, 320, 5, 1, 64, 0, 512, n_experts=experts, experts_per_tok=4, d_expert_ffn=160)
+    weights = ai.make_weights(shape, 5)
+    rng = np.random.default_rng(experts)
+    prompts = [rng.integers(0, shape.vocab, t, dtype=np.int32) for t in (5, 33, 64)]
+    alone = None
+    for n in (3, 24, 60, 200):
+        w = ai.Workload("experts", shape, 1, 64, n, n, 1, 0.0, 0.1, 1, 1, ai.SAMPLER_GREEDY, 0, 1, 5)
+        ctx = make_engine(w, weights, debug=True, max_inflight=n)
+        try:
+            for i in range(n):
+                ap.april_debug_watch(ctx, i, 0, 1)
+            ap.april_rollout_step(ctx, req_dicts([ai.Request(i, prompts[i % 3], 1) for i in range(n)]), n, n, 1)
+            got = [ap.april_debug_logits(ctx, i, 0, shape.vocab)[0] for i in range(n)]
+        finally:
+            ap.april_destroy(ctx)
+        alone = alone or got
+        for i, row in enumerate(got):
+            assert np.isfinite(row).all() and np.array_equal(row, alone[i % 3]), (n, i)
