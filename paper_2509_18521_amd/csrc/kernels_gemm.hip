@@ -314,6 +314,8 @@ __device__ inline void gemm_group(const bf16x8* __restrict__ w0, const bf16x8* _
 // other, z = m-group: consecutive workgroups go to consecutive XCDs, so with 8 (4) slices every XCD
 // works on one (two) k slices and pulls only that slice of the activations into its L2.
 constexpr int fetch_depth(int kh, int full, int part) { return part >= full ? kh : (kh * full / part < 8 ? kh * full / part : 8); }
+// k-tiles that a wavefront with `len` of them requests in fetch groups of kh: groups go in pairs, the last one past the end too.
+__device__ inline int fetched(int len, int kh) { return (len + 2 * kh - 1) / (2 * kh) * (2 * kh); }
 template <int NT, int MT, int EPI, bool INTRA, int KH, int OCC, bool NEAR>
 __global__ __launch_bounds__(64 * KW4, OCC) void gemm_mfma_kernel(RowCtx rc, const bf16x8* __restrict__ x,
                                                                   const bf16x8* __restrict__ w0,
@@ -343,37 +345,65 @@ __global__ __launch_bounds__(64 * KW4, OCC) void gemm_mfma_kernel(RowCtx rc, con
   float* o = out ? out + sidx * partial_stride : nullptr;
   int mtc = ceil_div(rows, 32) - mt0;
   if (mtc > MT) mtc = MT;
-  // (a last group of fewer m-tiles fetches more k-tiles at once in the same registers)
+  // A last group of fewer m-tiles fetches more k-tiles at once in the same registers.  The 2 x 4 tile of the split-k
+  // projections has room for one more: used where less is then requested past the slice's end (16 k-tiles per wavefront
+  // and 64 rows: groups of 8 fetch 16, groups of 7 fetch 28; 2048 x 8192 in 8 slices 11.5 against 12.4 us per launch).
+  constexpr bool ONE_MORE = EPI == EPI_F32 && NT == 2 && OCC == 1;
+  const int per = (k1 - k0 + KW - 1) / KW;
+#define GROUP(MTC, DEPTH) gemm_group<NT, (MT >= MTC ? MTC : 1), EPI, INTRA, KW, DEPTH>(w0, w1, x, KT, k0, k1, nt0, mt0, rows, N, o, act, red, ssp, nf)
+  constexpr int D1 = fetch_depth(KH, NT + MT, NT + 1), D2 = fetch_depth(KH, NT + MT, NT + 2), D3 = fetch_depth(KH, NT + MT, NT + 3);
   switch (mtc) {
-    case 1: gemm_group<NT, 1, EPI, INTRA, KW, fetch_depth(KH, NT + MT, NT + 1)>(w0, w1, x, KT, k0, k1, nt0, mt0, rows, N, o, act, red, ssp, nf); break;
-    case 2: gemm_group<NT, (MT >= 2 ? 2 : 1), EPI, INTRA, KW, fetch_depth(KH, NT + MT, NT + 2)>(w0, w1, x, KT, k0, k1, nt0, mt0, rows, N, o, act, red, ssp, nf); break;
-    case 3: gemm_group<NT, (MT >= 3 ? 3 : 1), EPI, INTRA, KW, fetch_depth(KH, NT + MT, NT + 3)>(w0, w1, x, KT, k0, k1, nt0, mt0, rows, N, o, act, red, ssp, nf); break;
-    default: gemm_group<NT, MT, EPI, INTRA, KW, KH>(w0, w1, x, KT, k0, k1, nt0, mt0, rows, N, o, act, red, ssp, nf); break;
+    case 1: GROUP(1, D1); break;
+    case 2:
+      if (ONE_MORE && fetched(per, D2 + 1) < fetched(per, D2)) GROUP(2, D2 + (ONE_MORE ? 1 : 0));
+      else GROUP(2, D2);
+      break;
+    case 3:
+      if (ONE_MORE && fetched(per, D3 + 1) < fetched(per, D3)) GROUP(3, D3 + (ONE_MORE ? 1 : 0));
+      else GROUP(3, D3);
+      break;
+    default: GROUP(MT, KH); break;
   }
+#undef GROUP
 }
 
 // Split-k projections (qkv, down).  What bounds them: a compute unit alone pulls about 50 GB/s from
 // HBM, so the launch wants every unit busy with the same amount; beyond that the re-reads, the
 // activations once per n-tile group and the weights once per m-group, at L2 speed.  So the tile of a
-// workgroup grows with the rows: one n-tile where they are few (two workgroups per unit), two up to
-// 128 rows, then 4 x 3 or 4 x 4 tiles (weights read once) where a k slice is long enough to pay for the
-// wider reduction, and 2 x 3 with two workgroups per unit otherwise and beyond 256 rows.
-// us per launch, two n-tiles x four m-tiles for all / as here: 4096 x 14336 in 4 slices at 160, 192, 256,
-// 384 rows 51.5, 53.6, 59.0, 82.8 / 36.8, 38.8, 43.6, 67.9 (LDS-tiled kernel: 57 at 230); 2560 x 9728 in 6:
-// 26.8, 28.9, 32.4, 45.8 / 22.1, 23.3, 26.5, 39.8; 6144 x 4096 in 2: 21.7, 25.6, 32.6, 45.5 / 24.1,
-// 25.3, 27.9, 36.5; 6144 x 2560 in 2 at 256, 384: 24.2, 33.9 / 22.1, 27.2; one n-tile, five k-tiles per
-// fetch / as here: 1152 x 896 in 4 at 64, 96 rows 5.0, 5.8 / 4.5, 5.0.
+// workgroup grows with the rows.  us per launch, N x K in ksplit slices (rows: one side / the other):
+//   * one n-tile (two workgroups per unit) where two give less than half a workgroup per unit: 1152 x 896 in 4
+//     at 64 rows 4.3 / 2 x 4 tiles 6.1.
+//   * up to 128 rows 2 x 4, the weights once: 4096 x 14336 in 4 at 128 rows 33.5 / 2 x 3 in two m-groups 37.9.
+//   * slices below 1536 (few k-tiles per wavefront do not pay for the wider reduction): 2 x 3 at two workgroups
+//     per unit.  Slices of 1280 at 160 rows 17.8 / 4 x 3 18.5, of 1621 22.4 / 21.7; of 1024 at 288, 512 rows 24.9,
+//     38.4 / 30.8, 45.0.  For 7 and 8 m-tiles 4 x 4 down to slices of 1024: 19.5 / 22.5 (682: 16.5 / 16.5).
+//   * longer slices, weights once: 4 x 3 to 192 rows, 4 x 4 to 256 (4096 x 14336: 38.7 / 2 x 3 45.5, 43.3 / 60.5).
+//     Except 5 m-tiles over at most 96 workgroups of 4 n-tiles, where the units left over take the fifth m-tile beside
+//     2 x 4: 6144 x 4096 in 2 21.8 / 23.6 (4096 x 14336 in 4, 128 workgroups: 50.7 / 36.4).
+//   * 257-384 rows: 4 x 3 from 112 workgroups per m-group, else 2 x 3: 7168 x 5120 in 2 (112) at 320 rows 46.2 / 49.5,
+//     6144 x 4096 in 2 (96) 34.5 / 41.6.
+//   * beyond: 4 x 4 or 4 x 3, whichever has fewer m-tiles in its rounds of one workgroup per unit: 4096 x 14336 in 4
+//     at 512, 1024 rows 77, 144 / 94, 171; 10240 x 8192 in 1 at 512 rows 4 x 3 116 / 4 x 4 133.
+// Against two n-tiles x four m-tiles for all: 4096 x 14336 in 4 slices at 160, 192, 256, 384 rows 50.7, 51.5, 55.2, 79.3 /
+// 36.4, 38.7, 43.3, 66.3; 2560 x 9728 in 6: 26.9, 28.3, 32.3, 46.0 / 21.7, 22.9, 26.0, 39.1.
 void launch_gemm_mfma(hipStream_t st, RowCtx rc, const bf16_t* x, const bf16_t* Wp, float* out, int N, int K,
                       int ksplit, size_t partial_stride, const float* ssq, int ssq_stride, float eps) {
   const NormFuse nf{nullptr, const_cast<float*>(ssq), ssq_stride, K >> 5, 1.0f / (float)K, eps, {}};
-  const int n_tiles = N >> 5, m_tiles = ceil_div(rc.max_rows, 32), slice = K / ksplit;
-#define GEMM_F32(NT, MT, KH, OCC)                                                                                         hipLaunchKernelGGL((gemm_mfma_kernel<NT, MT, EPI_F32, true, KH, OCC, false>), dim3(ksplit, n_tiles / NT, ceil_div(m_tiles, MT)),                      dim3(64 * KW4), 0, st, rc, reinterpret_cast<const bf16x8*>(x), reinterpret_cast<const bf16x8*>(Wp), nullptr,                      out, nullptr, N, K, ksplit, partial_stride, nf)
+  const int n_tiles = N >> 5, m_tiles = ceil_div(rc.max_rows, 32), slice = K / ksplit, per_group = n_tiles / 4 * ksplit;
+  const bool quads = n_tiles % 4 == 0, long_slices = quads && slice >= 1536;
+  auto round_tiles = [&](int mt) { return ceil_div(ceil_div(m_tiles, mt) * per_group, 256) * mt; };
+#define GEMM_F32(NT, MT, KH, OCC)                                                                                       \
+  hipLaunchKernelGGL((gemm_mfma_kernel<NT, MT, EPI_F32, true, KH, OCC, false>),                                         \
+                     dim3(ksplit, n_tiles / NT, ceil_div(m_tiles, MT)), dim3(64 * KW4), 0, st, rc,                      \
+                     reinterpret_cast<const bf16x8*>(x), reinterpret_cast<const bf16x8*>(Wp), nullptr, out, nullptr, N, \
+                     K, ksplit, partial_stride, nf)
   if (n_tiles % 2 != 0 || (n_tiles / 2) * ksplit < 128) GEMM_F32(1, 4, 3, 2);
-  else if (m_tiles <= 4) GEMM_F32(2, 4, 5, 1);
-  else if (n_tiles % 4 == 0 && m_tiles <= 6 && slice >= 1536) GEMM_F32(4, 3, 3, 1);
-  else if (n_tiles % 4 == 0 && (m_tiles == 7 || m_tiles == 8) && slice >= 1024) GEMM_F32(4, 4, 2, 1);
-  else if (n_tiles % 4 == 0 && m_tiles > 8 && (n_tiles / 4) * ksplit >= 112) GEMM_F32(4, 3, 3, 1);
-  else GEMM_F32(2, 3, 3, 2);
+  else if (m_tiles <= 4 || (m_tiles == 5 && long_slices && per_group <= 96)) GEMM_F32(2, 4, 5, 1);
+  else if (m_tiles <= 6 && long_slices) GEMM_F32(4, 3, 3, 1);
+  else if ((m_tiles == 7 || m_tiles == 8) && quads && slice >= 1024) GEMM_F32(4, 4, 2, 1);
+  else if (!long_slices || (m_tiles <= 12 && per_group < 112)) GEMM_F32(2, 3, 3, 2);
+  else if (m_tiles <= 12 || round_tiles(3) < round_tiles(4)) GEMM_F32(4, 3, 3, 1);
+  else GEMM_F32(4, 4, 2, 1);
 #undef GEMM_F32
 }
 

@@ -48,3 +48,8 @@ def test_a_row_keeps_its_bits_in_every_tile(name, sizes):
                 assert np.array_equal(row, alone[(rid % classes, i)]), (n, rid, i)
             else:
                 assert np.isfinite(row).all(), (n, rid, i)
+
+
+def test_a_row_keeps_its_bits_beyond_384_rows():
+    """More m-groups than the tile rules of smaller batches know: 4 x 4 and 4 x 3 split-k tiles by rounds."""
+    test_a_row_keeps_its_bits_in_every_tile("cfg4_8b_bf16", (400, 450, 520, 800))
