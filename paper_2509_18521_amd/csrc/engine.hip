@@ -863,8 +863,9 @@ int april_init(const april_model_cfg* cfg, const april_tensor* weights, int32_t 
   c->fuse_down = fd && !strcmp(fd, "1");
   // decode gate/up on the LDS-tiled kernel from this row bound (us per launch, skinny / tiled: 9728 features of
   // 2560 at 96, 128 rows 35.1 / 38.0, 39.0 / 38.1; 14336 of 4096 at 64, 96 rows 53.5 / 60.9, 69 / 61.2; 4864 of
-  // 896 at 128, 256 rows 11.2 / 17.0, 14.8 / 19.2)
-  c->tile_decode_rows = g.d_ffn >= 12288 ? 96 : (g.d_ffn >= 8192 ? 128 : 0);
+  // 896 at 128, 256 rows 11.2 / 17.0, 14.8 / 19.2; 8960 of 1536 at 128 rows 24.8 / 25.3, 11008 of 4096 at 96 rows 53.3 / 57.7;
+  // at 64 rows 18944 of 3584 64.8 / 69.4, 28672 of 8192 201 / 183)
+  c->tile_decode_rows = g.d_ffn >= 24576 ? 64 : (g.d_ffn >= 12288 ? 96 : (g.d_ffn >= 8192 ? 128 : 0));
   if (const char* td = getenv("APRIL_TILE_DECODE_ROWS")) c->tile_decode_rows = atoi(td);   // debug switch
   if (const char* mt = getenv("APRIL_MOE_TALL_ROWS")) c->moe_tall_rows = atoi(mt);          // debug switch
   if (const char* mt = getenv("APRIL_MOE_TILE")) c->moe_tile = strcmp(mt, "0") != 0;

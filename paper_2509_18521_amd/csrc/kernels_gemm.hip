@@ -424,7 +424,9 @@ void launch_gemm_mfma_logits(hipStream_t st, RowCtx rc, const bf16_t* x, const b
 // rounds.  us per launch, four m-tiles at one per unit / as here: 2560 x 9728 at 32, 64, 96 rows 30.7,
 // 37.3, 42.5 / 27.3, 32.8, 35.1, at 320, 384 rows 74.2, 81.1 / 59.4, 69.0; 4096 x 14336 at 32, 64 rows
 // 48.4, 57.1 / 45.5, 53.5; 896 x 4864 at 64, 96, 192, 256 rows 9.9, 11.1, 15.2, 20.1 / 9.9, 10.2, 12.6, 14.8.
-// NEAR where the weight tiles alone are more than a round of one workgroup per unit.
+// NEAR where the weight tiles alone are more than a round of one workgroup per unit, and where their number is no multiple
+// of 8, which in grid order puts the row groups of one tile on different XCDs: 3104 x 1184 (97 tiles) at 160, 256, 512 rows
+// 12.6, 14.7, 24.9 / 10.6, 11.3, 17.5; 4864 x 896 (152 tiles) at 160, 256, 512 rows 10.6, 13.2, 18.8, NEAR 10.9, 14.6, 20.5.
 void launch_gemm_mfma_swiglu(hipStream_t st, RowCtx rc, const bf16_t* x, const bf16_t* Wg, const bf16_t* Wu,
                              bf16_t* act, int F, int K, const float* ssq, int ssq_stride, float eps) {
   const int n_tiles = F >> 5, m_tiles = ceil_div(rc.max_rows, 32);
@@ -435,8 +437,8 @@ void launch_gemm_mfma_swiglu(hipStream_t st, RowCtx rc, const bf16_t* x, const b
                      reinterpret_cast<const bf16x8*>(Wu), nullptr, act, F, K, 1, (size_t)0, nf)
   const int tiles8 = ceil_div(n_tiles, 8) * 8;
   if (m_tiles <= 1) GEMM_SW(1, 4, 3, false, dim3(n_tiles));
-  else if (n_tiles <= 256) GEMM_SW(2, 2, 3, false, dim3(n_tiles, 1, ceil_div(m_tiles, 2)));
-  else if (m_tiles <= 3) GEMM_SW(2, 2, 3, true, dim3(tiles8 * ceil_div(m_tiles, 2)));
+  else if (n_tiles <= 256 && n_tiles % 8 == 0) GEMM_SW(2, 2, 3, false, dim3(n_tiles, 1, ceil_div(m_tiles, 2)));
+  else if (n_tiles <= 256 || m_tiles <= 3) GEMM_SW(2, 2, 3, true, dim3(tiles8 * ceil_div(m_tiles, 2)));
   else GEMM_SW(3, 3, 2, true, dim3(tiles8 * ceil_div(m_tiles, 3)));
 #undef GEMM_SW
 }

@@ -825,8 +825,9 @@ void launch_gemm_tile_swiglu(hipStream_t st, RowCtx rc, const bf16_t* x, const b
 // Workgroups of 64 features and all the rows up to 256: 128 (2 x 2 accumulator tiles per wavefront), 192 (a
 // quarter less matrix work and LDS traffic than the full tile would spend on rows that are not there), 256 on 8
 // wavefronts (4 wavefronts of 128 x 64 with both accumulator sets need the whole register file each: 105 against
-// 97 us).  Beyond, several row groups beside each other (tile_of_block): of 128 rows where they all fit
-// two per compute unit, else of 192.  us per launch, skinny kernel | here, 9728 x 2560 at 96, 128, 192, 256, 320,
+// 97 us).  Up to 384, several row groups beside each other (tile_of_block): of 128 rows where they all fit
+// two per compute unit, else of 192.  Beyond, of 256, or of 192 where that is less in rounds (two workgroups
+// per unit of 192 rows, one of 256): 14336 x 4096 at 512, 1024 rows 135, 264, of 192 178, 347; 9728 x 2560 at 512 rows 85, of 192 81.  us per launch, skinny kernel | here, 9728 x 2560 at 96, 128, 192, 256, 320,
 // 384 rows: 34, 40, 48, 58, 60, 70 | 38, 38, 43, 45, 52, 53; 14336 x 4096: 69, 78, 94, 119, 130, 147 | 61, 62, 70,
 // 77, 127, 128 (row groups a grid apart: 148, 137).
 // A ring deeper than 3 stages made these variants 1.8x slower (the plain kernel does not care).
@@ -842,8 +843,9 @@ bool launch_gemm_tile_swiglu_chain(hipStream_t st, RowCtx rc, const bf16_t* x, c
   if (rc.max_rows <= 128) CHAIN_LAUNCH(2, 2);
   else if (rc.max_rows <= 192) CHAIN_LAUNCH(2, 3);
   else if (rc.max_rows <= 256) CHAIN_LAUNCH(4, 2);
-  else if (units * ceil_div(m_tiles, 4) <= 512) CHAIN_LAUNCH(2, 2);
-  else CHAIN_LAUNCH(2, 3);
+  else if (rc.max_rows <= 384 && units * ceil_div(m_tiles, 4) <= 512) CHAIN_LAUNCH(2, 2);
+  else if (rc.max_rows <= 384 || ceil_div(units * ceil_div(m_tiles, 6), 512) * 12 < ceil_div(units * ceil_div(m_tiles, 8), 256) * 8) CHAIN_LAUNCH(2, 3);
+  else CHAIN_LAUNCH(4, 2);
 #undef CHAIN_LAUNCH
   return true;
 }

@@ -17,18 +17,13 @@ def _need_gpu():
         pytest.skip("no GPU")
 
 
-@pytest.mark.parametrize("name,sizes", [
-    ("cfg2_small_bf16", (33, 65, 97, 161, 257)),
-    ("cfg4_8b_bf16", (40, 70, 100, 128, 170, 200, 256, 290, 384))])
-def test_a_row_keeps_its_bits_in_every_tile(name, sizes):
+def check_bits(shape, seed, sizes):
     import paper_2509_18521_amd as ap
-    base = ai.WORKLOADS[name]
-    shape = ai.reduced(base, n_layers=1, vocab=2080).shape          # (an odd number of vocabulary tiles)
     classes, gen = 31, 2
-    weights = ai.make_weights(shape, base.seed)
+    weights = ai.make_weights(shape, seed)
     alone = None
     for n in (4,) + sizes:
-        w = ai.Workload(f"{name}_tiles_{n}", shape, classes, 5, n, n, gen, 0.7, 0.1, gen, gen, ai.SAMPLER_GREEDY, 0, 1, base.seed)
+        w = ai.Workload(f"tiles_{n}", shape, classes, 5, n, n, gen, 0.7, 0.1, gen, gen, ai.SAMPLER_GREEDY, 0, 1, seed)
         reqs = ai.make_requests(w, n)
         ctoks = class_forced_tokens(w, classes)
         forced = {r.request_id: ctoks[r.request_id % classes][:gen] for r in reqs}
@@ -50,6 +45,23 @@ def test_a_row_keeps_its_bits_in_every_tile(name, sizes):
                 assert np.isfinite(row).all(), (n, rid, i)
 
 
-def test_a_row_keeps_its_bits_beyond_384_rows():
-    """More m-groups than the tile rules of smaller batches know: 4 x 4 and 4 x 3 split-k tiles by rounds."""
-    test_a_row_keeps_its_bits_in_every_tile("cfg4_8b_bf16", (400, 450, 520, 800))
+@pytest.mark.parametrize("name,sizes", [
+    ("cfg2_small_bf16", (33, 65, 97, 161, 257)),
+    ("cfg4_8b_bf16", (40, 70, 100, 128, 170, 200, 256, 290, 384))])
+def test_a_row_keeps_its_bits_in_every_tile(name, sizes):
+    base = ai.WORKLOADS[name]
+    check_bits(ai.reduced(base, n_layers=1, vocab=2080).shape, base.seed, sizes)          # (an odd number of vocabulary tiles)
+
+
+@pytest.mark.parametrize("name,sizes", [("cfg4_8b_bf16", (400, 450, 520, 800)), ("cfg3_mid_bf16", (450, 520))])
+def test_a_row_keeps_its_bits_beyond_384_rows(name, sizes):
+    """More m-groups than the tile rules of smaller batches know: split-k and gate/up tiles by rounds."""
+    base = ai.WORKLOADS[name]
+    check_bits(ai.reduced(base, n_layers=1, vocab=2080).shape, base.seed, sizes)
+
+
+@pytest.mark.parametrize("d_model,n_q,n_kv,head_dim,d_ffn,sizes", [
+    (1184, 20, 4, 64, 3104, (40, 70, 170, 330)),     # 97 feature tiles: no multiple of the 8 XCDs
+    (128, 4, 2, 32, 24576, (24, 40, 70))])           # the LDS-tiled gate/up from 64 rows
+def test_a_row_keeps_its_bits_in_gate_up(d_model, n_q, n_kv, head_dim, d_ffn, sizes):
+    check_bits(ai.ModelShape(1, d_model, n_q, n_kv, head_dim, d_ffn, 2080), 5, sizes)
