@@ -450,6 +450,11 @@ void launch_gemm_mfma_swiglu(hipStream_t st, RowCtx rc, const bf16_t* x, const b
 // m-tiles are faster than 2 + 2: 14.8 against 17.0 us).  us per launch before (one m-tile up to 512 workgroups,
 // else four) / as here: 2560 x 4096 at 128, 160, 256 rows 17.9, 17.2, 23.5 / 14.8, 14.5, 18.3;
 // 4096 x 4096 at 96, 128, 256, 320, 384 rows 18.6, 18.8, 24.5, 35.2, 43.0 / 15.4, 16.0, 24.5, 21.2, 24.2.
+// Where even one group leaves more than a third of the units idle, three m-tiles go one to a workgroup if that is at
+// most two per unit: 5120 x 5120 (160 n-tiles) at 96 rows 23.4 (one group of 3: 26.2), 5632 x 5632 (176) 31.0 (28.9).
+// Rows that need more than 4 m-tiles per group: 2 x 3 at one workgroup per unit, unless that takes a second round on some
+// XCD where 1 x 4 at two per unit fills most of one: 5120 x 5120 at 288, 320, 384, 448 rows 2 x 3 31.1, 47.4, 55.2, 51.9,
+// 1 x 4 36.9, 40.8, 49.2, 55.9; 896 x 896 at 1536, 2048 rows 10.3, 17.1 and 12.4, 13.9.
 void launch_gemm_mfma_resid(hipStream_t st, RowCtx rc, const bf16_t* x, const bf16_t* Wp, float* x_res,
                             const float* gain, bf16_t* act, float* ssq, int ssq_stride, int N, int K) {
   const int n_tiles = N >> 5, m_tiles = ceil_div(rc.max_rows, 32);
@@ -462,12 +467,14 @@ void launch_gemm_mfma_resid(hipStream_t st, RowCtx rc, const bf16_t* x, const bf
   const int most = 256 / n_tiles > 0 ? 256 / n_tiles : 1;                // groups of rows
   const int groups = ceil_div(m_tiles, ceil_div(m_tiles, most));
   int mt = ceil_div(m_tiles, most);
-  while (mt < 4 && ceil_div(m_tiles, mt + 1) == groups) ++mt;
-  if (groups == m_tiles) mt = 1;
+  while (mt < 4 && (groups > 1 || mt != 3) && ceil_div(m_tiles, mt + 1) == groups) ++mt;
+  if (groups == m_tiles || (groups == 1 && m_tiles == 3 && n_tiles * 3 <= 512)) mt = 1;
+  const int pairs = ceil_div(n_tiles / 2, 8) * ceil_div(m_tiles, 3), singles = ceil_div(n_tiles, 8) * ceil_div(m_tiles, 4);   // workgroups per XCD
+  if (mt > 4 && (n_tiles % 2 != 0 || (m_tiles > 8 && pairs > 32 && singles >= 48 && singles <= 64))) mt = 4;
   if (mt == 1) GEMM_RESID(1, 1, 8, 1);
   else if (mt == 2) GEMM_RESID(1, 2, 4, 2);
   else if (mt == 3) GEMM_RESID(1, 3, 4, 2);
-  else if (mt == 4 || n_tiles % 2 != 0) GEMM_RESID(1, 4, 3, 2);
+  else if (mt == 4) GEMM_RESID(1, 4, 3, 2);
   else GEMM_RESID(2, 3, 4, 1);
 #undef GEMM_RESID
 }

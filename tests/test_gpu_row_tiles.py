@@ -65,3 +65,8 @@ def test_a_row_keeps_its_bits_beyond_384_rows(name, sizes):
     (128, 4, 2, 32, 24576, (24, 40, 70))])           # the LDS-tiled gate/up from 64 rows
 def test_a_row_keeps_its_bits_in_gate_up(d_model, n_q, n_kv, head_dim, d_ffn, sizes):
     check_bits(ai.ModelShape(1, d_model, n_q, n_kv, head_dim, d_ffn, 2080), 5, sizes)
+
+
+def test_a_row_keeps_its_bits_in_the_output_projection():
+    """5120 columns: one m-tile per workgroup at 96 rows, pairs of n-tiles at 288, single ones above."""
+    check_bits(ai.ModelShape(1, 5120, 40, 8, 128, 1024, 2080), 5, (70, 128, 280, 330))
