@@ -861,21 +861,32 @@ bool launch_gemm_tile_swiglu_chain(hipStream_t st, RowCtx rc, const bf16_t* x, c
 //   151936 x 2048 123 | 125       137 | 131 | 139     173 | 138 | 138      163 | 177       244 | 299 (330)
 //   151936 x 896   49 | 45         56 | 49 | 53        77 | 58 | 58         79 | 101       117 | 164 (169)
 //   32032 x 1184   15 | 16         18 | 16 | 24        25 | 18 | 25         26 | 36         36 | 41
+// From 129 to 256 rows the 256-row tile: for long products (K >= 3072), and for shorter ones where two groups of 128 rows are
+// more than one workgroup per unit and the 256-column groups fill one round (129 .. 256) or their last one; from 385 to 512
+// rows for more than 64 groups (32000 x 1024, 125 groups, at 512 rows 36 | 36 | 35; 4096 x 192, 16 groups, 7.8 | - | 8.8).  Its products up to K of 2048 on 8 wavefronts.  us at 256 rows, 128 x 256 | 256 x 256 on 4 | on 8 wavefronts:
+// 50304 x 768 (197 groups) 29 | 30 | 26, x 1600 55 | 49 | 48, x 2048 65 | 59 | 62; 40960 x 768 (160) 28 | 28 | 24; 32000 x 2048
+// (125) 42 | 50 | 50; 128256 x 1024 (501) 77 | 80 | 76, x 2048 151 | 138 | 140; 151936 x 896 (594) 83 | 97 | 89, x 2560 213 |
+// 217 | 222.  At 384, 512 rows: 32000 x 4096 113, 124 | 114, 114; 151936 x 896 117, 149 | 8: 142, 145; 128256 x 4096 383, 490 | 441, 457.
 bool launch_gemm_tile_logits(hipStream_t st, RowCtx rc, const bf16_t* x, const bf16_t* Wp, float* logits,
                              const GroupOut& go, int V, int K) {
   if (K % 32 != 0) return false;
   const int groups = ceil_div(V >> 5, 8), rows = rc.max_rows;            // 256-column groups
   if (rows <= 32 && (K >= 3072 || groups < 256)) return false;
-#define LM_LAUNCH(KERNEL, MT, ...)                                                                                      \
-  hipLaunchKernelGGL((KERNEL), dim3(ceil_div(groups, 8) * 8 * ceil_div(ceil_div(rows, 32), MT)), dim3(256), 0, st, rc,  \
+#define LM_LAUNCH(KERNEL, MT, THREADS, ...)                                                                              \
+  hipLaunchKernelGGL((KERNEL), dim3(ceil_div(groups, 8) * 8 * ceil_div(ceil_div(rows, 32), MT)), dim3(THREADS), 0, st, rc, \
                      reinterpret_cast<const bf16x8*>(x), reinterpret_cast<const bf16x8*>(Wp), nullptr, logits, nullptr, V, K, __VA_ARGS__)
 #define LM_64 gemm_tile_dma_kernel<1, 4, 2, 2, 2, 4, TEPI_LOGITS>
 #define LM_128 gemm_tile_dma_kernel<1, 4, 4, 2, 2, 3, TEPI_LOGITS>
-  if (rows <= 64 || (rows <= 128 && groups < 256)) LM_LAUNCH(LM_64, 2, go);
-  else if (rows <= 128 || rows > 256 || K < 3072) LM_LAUNCH(LM_128, 4, go);
-  else LM_LAUNCH(TILE_WIDE(TEPI_LOGITS), 8, go, QkvOut{});
+#define LM_256 gemm_tile_dma_kernel<2, 4, 4, 2, 2, 4, TEPI_LOGITS>
+  const bool full = (groups > 128 && groups <= 256) || groups % 256 == 0 || groups % 256 >= 230;
+  const bool tall = (rows > 128 && rows <= 256 && (K >= 3072 || full)) || (rows > 384 && rows <= 512 && groups > 64);
+  if (rows <= 64 || (rows <= 128 && groups < 256)) LM_LAUNCH(LM_64, 2, 256, go);
+  else if (!tall) LM_LAUNCH(LM_128, 4, 256, go);
+  else if (K <= 2048) LM_LAUNCH(LM_256, 8, 512, go);
+  else LM_LAUNCH(TILE_WIDE(TEPI_LOGITS), 8, 256, go, QkvOut{});
 #undef LM_64
 #undef LM_128
+#undef LM_256
 #undef LM_LAUNCH
   return true;
 }

@@ -70,3 +70,9 @@ def test_a_row_keeps_its_bits_in_gate_up(d_model, n_q, n_kv, head_dim, d_ffn, si
 def test_a_row_keeps_its_bits_in_the_output_projection():
     """5120 columns: one m-tile per workgroup at 96 rows, pairs of n-tiles at 288, single ones above."""
     check_bits(ai.ModelShape(1, 5120, 40, 8, 128, 1024, 2080), 5, (70, 128, 280, 330))
+
+
+@pytest.mark.parametrize("vocab,sizes", [(33024, (140, 250, 400)), (8224, (140, 400))])
+def test_a_row_keeps_its_bits_in_the_lm_head(vocab, sizes):
+    """129 groups of 256 columns: the 256-row tile on 8 wavefronts from 129 rows; 33 groups: never."""
+    check_bits(ai.ModelShape(1, 160, 2, 1, 64, 96, vocab), 5, sizes)
