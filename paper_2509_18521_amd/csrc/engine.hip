@@ -1370,7 +1370,9 @@ static int sample_rows_impl(april_ctx* c, const float* logits, int32_t n_rows, c
     float* gm = reinterpret_cast<float*>(w + off_gm);
     double* gs = sums ? reinterpret_cast<double*>(w + off_gs) : nullptr;
     float* lp = out_logprobs ? reinterpret_cast<float*>(w + off_lp) : nullptr;
-    launch_group_records(c->stream, lg, nullptr, n, V, sums, sc.temperature, gm, gs);
+    const bool records = sums || sc.kind != APRIL_SAMPLER_TOPK || sc.top_k <= 1 || topk_in_groups(V, sc.top_k);
+    if (records) launch_group_records(c->stream, lg, nullptr, n, V, sums, sc.temperature, gm, gs);
+    else gm = nullptr;
     launch_sample(c->stream, RowCtx{nullptr, nullptr, reinterpret_cast<const int2*>(w), n}, c->ds, nullptr, lg, V, sc, Watch{}, 0,
                   reinterpret_cast<const long long*>(w + 8), reinterpret_cast<const int*>(w + off_gen),
                   reinterpret_cast<int*>(w + off_out), gm, grp, lp, nullptr, gs);
@@ -1403,10 +1405,10 @@ int april_sample_rows_noalloc(april_ctx* c, const float* logits, int32_t n_rows,
   if (V % grp == 0 && n_records > NOALLOC_MAX_GROUP_MAX)
     return fail(c, APRIL_EINVAL, "april_sample_rows_noalloc: rows x vocab/%d = %zu exceeds the scratch (%zu)", grp, n_records, NOALLOC_MAX_GROUP_MAX);
   // (a vocabulary that 64 does not divide has no such limit: beyond the scratch the sampler reads whole rows)
-  const bool use_gm = n_records <= NOALLOC_MAX_GROUP_MAX;
+  const SamplerCfg sc = sampler_cfg(c);
+  const bool use_gm = n_records <= NOALLOC_MAX_GROUP_MAX && (sc.kind != APRIL_SAMPLER_TOPK || sc.top_k <= 1 || topk_in_groups(V, sc.top_k));
   if (!c->scratch_dev) return fail(c, APRIL_EDEVICE, "scratch address was not resolved at april_init");
   unsigned char* sp = c->scratch_dev;
-  const SamplerCfg sc = sampler_cfg(c);
   const int sums = use_gm && sc.kind == APRIL_SAMPLER_CATEGORICAL ? 2 : 0;
   float* d_gm = use_gm ? reinterpret_cast<float*>(sp + NOALLOC_OFF_GM) : nullptr;
   double* d_gs = sums ? reinterpret_cast<double*>(sp + NOALLOC_OFF_GS) : nullptr;

@@ -297,7 +297,7 @@ __global__ __launch_bounds__(SAMPLE_THREADS) void sample_kernel(RowCtx rc, Slots
   } else {
     const int k = sc.top_k < V ? (sc.top_k < MAX_TOPK ? sc.top_k : MAX_TOPK) : (V < MAX_TOPK ? V : MAX_TOPK);
     bool have = false;
-    if (gm && n_groups >= k) {
+    if (gm && n_groups >= k && topk_in_groups(V, k)) {
       // ---- candidates from the groups whose maximum reaches the k-th largest maximum ---
       block_kth_largest(gm, n_groups, k, sh);
       const unsigned tau = sh.prefix;

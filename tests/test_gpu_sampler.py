@@ -54,6 +54,13 @@ def test_topk_sampler_matches_oracle(vocab, top_k, temperature, quant):
         ap.april_destroy(ctx)
 
 
+@pytest.mark.parametrize("vocab,top_k,quant", [(4095, 64, None), (4097, 64, 0.5), (4097, 33, None), (4097, 32, 0.5),
+                                               (6337, 50, 1.0), (6335, 50, 1.0), (8129, 64, 0.5)])
+def test_topk_search_of_ragged_vocabularies(vocab, top_k, quant):
+    """Either side of where the search turns from whole rows to groups (4096 logits, 2 k groups)."""
+    test_topk_sampler_matches_oracle(vocab, top_k, 1.0, quant)
+
+
 def test_greedy_sampler_lowest_index_on_ties():
     import torch
     rng = np.random.default_rng(5)
