@@ -228,7 +228,8 @@ int april_update_weights(april_ctx* ctx, const april_tensor* weights, int32_t n_
  * hardware; cfg.pausable = 1).  tags: APRIL_MEM_KV | APRIL_MEM_WEIGHTS.
  * april_memory_pause releases the physical memory behind the tagged buffers; their virtual
  * addresses stay reserved, so everything that holds those addresses (captured iteration graphs
- * included) remains valid.  april_memory_resume maps fresh physical memory at the same addresses.
+ * included) remains valid.  The workspace that april_sample_rows keeps is released too.
+ * april_memory_resume maps fresh physical memory at the same addresses.
  * Contents do not survive: after a KV pause every parked rollout keeps its tokens and is
  * re-prefilled when resumed (the pool comes back zeroed and entirely free); after a weights
  * pause april_update_weights must be called before the next step.  Call between steps only;
@@ -246,7 +247,9 @@ int april_debug_logits(april_ctx* ctx, int64_t request_id, int32_t gen_index,
 
 /* The sampler alone (Section 3.1 samples with a temperature; greedy / top-k are the
  * configured ones): logits is a DEVICE array [n_rows, vocab] of float; request_ids,
- * gen_index (host, [n_rows]) key the Philox stream; out_tokens host [n_rows]. */
+ * gen_index (host, [n_rows]) key the Philox stream; out_tokens host [n_rows].
+ * The context keeps the call's device workspace for the next call: at most 64 MiB (or what one row
+ * needs, 12 bytes per 64 logits, if that is more), until april_memory_pause or april_destroy. */
 int april_sample_rows(april_ctx* ctx, const float* logits, int32_t n_rows,
                       const int64_t* request_ids, const int32_t* gen_index, int32_t* out_tokens);
 

@@ -1272,6 +1272,7 @@ int april_memory_pause(april_ctx* c, int32_t tags) {
   HIPCHK(c, hipDeviceSynchronize());
   for (auto& r : c->vm_regions)
     if ((r.tag & tags) && r.mapped) vm_unmap_region(r);
+  if (c->sr_ws) { hipFree(c->sr_ws); c->sr_ws = nullptr; c->sr_ws_bytes = 0; }   // holds nothing between calls
   if ((tags & APRIL_MEM_KV) && !(c->paused_tags & APRIL_MEM_KV)) {
     // the K/V of every parked rollout is gone with the pool: they keep their tokens and are
     // re-prefilled when resumed

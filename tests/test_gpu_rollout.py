@@ -360,6 +360,32 @@ def test_memory_pause_and_resume_by_remapping(dtype, pool_mib):
         A.april_destroy(ctx)
 
 
+def test_memory_pause_releases_the_sampling_workspace():
+    """A call of april_sample_rows leaves its workspace (60 MiB here) with the context; a pause gives it back, and the next
+    call works without it."""
+    import torch
+    A = ap()
+    shape = ai.ModelShape(1, 32, 1, 1, 32, 32, 151936, dtype=ai.DTYPE_FP32)
+    cfg = A.make_cfg(shape, max_inflight=4, max_ctx=32, sampler=ai.SAMPLER_CATEGORICAL, temperature=0.8, seed=3, pausable=True)
+    ctx = A.april_init(cfg, A.pack_weights(shape, ai.make_weights(shape, 0)))
+    try:
+        n = 2200
+        logits = torch.randn((n, shape.vocab), generator=torch.Generator(device="cuda").manual_seed(2), device="cuda")
+        ids, idx = np.arange(n, dtype=np.int64), np.zeros(n, dtype=np.int32)
+        small = A.april_sample_rows(ctx, logits.data_ptr(), 1, ids, idx)
+        torch.cuda.synchronize()
+        A.april_memory_pause(ctx, A.APRIL_MEM_KV)
+        without = A.april_get_info(ctx)["hbm_free"]
+        A.april_memory_resume(ctx, A.APRIL_MEM_KV)
+        got = A.april_sample_rows(ctx, logits.data_ptr(), n, ids, idx)
+        A.april_memory_pause(ctx, A.APRIL_MEM_KV)
+        assert A.april_get_info(ctx)["hbm_free"] >= without - (4 << 20)
+        A.april_memory_resume(ctx, A.APRIL_MEM_KV)
+        assert np.array_equal(A.april_sample_rows(ctx, logits.data_ptr(), n, ids, idx), got) and got[0] == small[0]
+    finally:
+        A.april_destroy(ctx)
+
+
 @pytest.mark.parametrize("name", list(ai.WORKLOADS))
 def test_scheduling_bit_exact_at_all_five_configs(name):
     """Scheduling depends only on the forced lengths, so each configuration's N, N',
