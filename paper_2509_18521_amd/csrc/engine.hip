@@ -54,7 +54,7 @@ struct SlotH {
 // then the five arrays that a step reads back, in that order.
 enum { SLOTS_REQ = 0, SLOTS_PROMPT = 2, SLOTS_LIMIT = 3, SLOTS_GEN = 4, SLOTS_STATE = 5, SLOTS_KV = 6, SLOTS_BLOCKS = 7,
        SLOTS_FINISH = 8, SLOTS_ARRAYS = 9 };
-constexpr int XFER_INTS = 1 << 18, XFER_ITEMS = 4096;
+constexpr int XFER_MOST_INTS = 1 << 18;
 
 // What one prefill chunk uploads, in one copy.  Offsets in ints (items on 16 bytes).
 struct PrefillBlock {
@@ -149,8 +149,11 @@ struct april_ctx {
   size_t h_stage_ints = 0;
   int* h_slot_arrays = nullptr;  // pinned mirror of the per-slot block (SLOTS_* offsets)
   int* d_slot_arrays = nullptr;
-  int* h_xfer = nullptr;         // pinned: tokens / log-probabilities on their way (launch_xfer), XFER_INTS ints
+  // pinned: tokens / log-probabilities on their way (launch_xfer).  As many ints as all slots hold, at most
+  // XFER_MOST_INTS; one item per slot and array, which is all that a step's pieces come to between two launches.
   XferItem* h_xfer_items = nullptr;
+  int* h_xfer = nullptr;         // behind the items
+  int xfer_ints = 0;
   bool xfer_pending = false;     // an upload may still be reading them
 
   // workspaces
@@ -743,7 +746,7 @@ int upload_slot_tables(april_ctx* c) {
   return APRIL_OK;
 }
 
-// Many host <-> device pieces through the pinned transfer buffer, as many per launch as it holds.
+// Many host <-> device pieces (at most one per slot and array) through the pinned transfer buffer, as many per launch as it holds.
 struct XferPiece { int* dev; int* host; size_t n; };
 int xfer(april_ctx* c, const std::vector<XferPiece>& pieces, bool to_device) {
   int n_items = 0, used = 0;
@@ -761,8 +764,8 @@ int xfer(april_ctx* c, const std::vector<XferPiece>& pieces, bool to_device) {
   };
   for (const XferPiece& p : pieces)
     for (size_t at = 0; at < p.n;) {
-      if (n_items == XFER_ITEMS || used == XFER_INTS) { int rc = flush(false); if (rc != APRIL_OK) return rc; }
-      const int n = (int)std::min<size_t>(p.n - at, XFER_INTS - used);
+      if (used == c->xfer_ints) { int rc = flush(false); if (rc != APRIL_OK) return rc; }
+      const int n = (int)std::min<size_t>(p.n - at, c->xfer_ints - used);
       c->h_xfer_items[n_items] = XferItem{p.dev + at, used, n};
       if (to_device) memcpy(c->h_xfer + used, p.host + at, (size_t)n * sizeof(int));
       else out.push_back({p.host + at, n_items});
@@ -929,8 +932,10 @@ int april_init(const april_model_cfg* cfg, const april_tensor* weights, int32_t 
   TRY(dev_alloc(c, &c->d_ctrl, 1));
   HIPTRY(hipHostMalloc((void**)&c->h_ctrl, sizeof(Ctrl)));
   HIPTRY(hipHostMalloc((void**)&c->h_slot_arrays, (size_t)SLOTS_ARRAYS * S * sizeof(int)));
-  HIPTRY(hipHostMalloc((void**)&c->h_xfer, (size_t)XFER_INTS * sizeof(int)));
-  HIPTRY(hipHostMalloc((void**)&c->h_xfer_items, XFER_ITEMS * sizeof(XferItem)));
+  const size_t xfer_arrays = g.logprobs ? 2 : 1;
+  c->xfer_ints = (int)std::min<size_t>(XFER_MOST_INTS, xfer_arrays * S * c->max_ctx);
+  HIPTRY(hipHostMalloc((void**)&c->h_xfer_items, xfer_arrays * S * sizeof(XferItem) + (size_t)c->xfer_ints * sizeof(int)));
+  c->h_xfer = reinterpret_cast<int*>(c->h_xfer_items + xfer_arrays * S);
   TRY(dev_alloc(c, &c->d_row_slot, S)); TRY(dev_alloc(c, &c->d_row_pos, S));
   TRY(dev_alloc(c, &c->d_list_a, 2048)); TRY(dev_alloc(c, &c->d_list_b, 2048));
 
@@ -1078,7 +1083,6 @@ void april_destroy(april_ctx* c) {
   if (c->sr_ws) hipFree(c->sr_ws);
   if (c->h_ctrl) hipHostFree(c->h_ctrl);
   if (c->h_slot_arrays) hipHostFree(c->h_slot_arrays);
-  if (c->h_xfer) hipHostFree(c->h_xfer);
   if (c->h_xfer_items) hipHostFree(c->h_xfer_items);
   if (c->h_stage) hipHostFree(c->h_stage);
   if (c->h_snaps) hipHostFree(c->h_snaps);

@@ -1,5 +1,6 @@
-"""Token and log-probability transfers of a step through the pinned buffer: pieces longer than it, and
-buffers filled to the last item, come back whole (imported rollouts deliver what they brought)."""
+"""Token and log-probability transfers of a step through the pinned buffer, which holds what all slots hold up to 2^18
+ints: one rollout, the most a context admits (one piece per rollout and array), and more ints than the buffer, where
+pieces are split as it fills.  Imported rollouts deliver what they brought."""
 import numpy as np
 import pytest
 
@@ -15,7 +16,7 @@ def _need_gpu():
         pytest.skip("no GPU")
 
 
-@pytest.mark.parametrize("n,length", [(1, 1), (3, 700), (40, 7000)])
+@pytest.mark.parametrize("n,length", [(1, 1), (3, 700), (2048, 3), (40, 7000)])
 def test_imported_rollouts_come_back_whole(n, length):
     import paper_2509_18521_amd as ap
     shape = ai.ModelShape(1, 32, 1, 1, 32, 32, 64)
