@@ -120,3 +120,36 @@ def test_logprobs_without_logits(monkeypatch, vocab, n_target, n_over):
             assert abs(lps[g] - osampler.token_logprob(row, float(np.float32(0.9)), t)) <= LP_TOL
     finally:
         ap().april_destroy(ctx)
+
+
+@pytest.mark.parametrize("vocab", [1024, 1056, 6176])
+@pytest.mark.parametrize("n_target,n_over", [(13, 18), (110, 150)])
+@pytest.mark.parametrize("sampler,top_k", [(ai.SAMPLER_CATEGORICAL, 0), (ai.SAMPLER_TOPK, 5), (ai.SAMPLER_TOPK, 40)])
+def test_sampled_bf16_rollouts(vocab, n_target, n_over, sampler, top_k):
+    """Sampling modes of bf16 rollouts, in iterations whose row count falls (records of rows that are gone stay behind in
+    the arrays): every token and log-probability is the oracle sampler's on the logits row it was drawn from."""
+    shape = ai.ModelShape(1, 128, 4, 2, 32, 256, vocab)
+    w = ai.Workload("sampled", shape, 8, 9, n_target, n_over, 7, 1.4, 0.5, 1, 7, ai.SAMPLER_GREEDY, top_k, 2, 13)
+    weights = ai.make_weights(shape, w.seed)
+    reqs = ai.make_requests(w, ai.requests_needed(w))
+    T, steps = float(np.float32(0.8)), []
+    for debug in (True, False):
+        ctx = make_engine(w, weights, logprobs=True, temperature=0.8, debug=debug, sampler=sampler)
+        try:
+            for r in reqs if debug else []:
+                ap().april_debug_watch(ctx, r.request_id, 0, w.max_new)
+            steps.append(run_gpu(ctx, reqs, w.n_target, w.n_overprovision, w.max_new, w.steps))
+            for g in steps[0] if debug else []:
+                assert g["iters"] > 1 and g["sum_live"] < g["iters"] * n_over
+                for rid, toks, lps in zip(g["ids"], g["tokens"], g["logprobs"]):
+                    for i, t in enumerate(toks):
+                        row, chosen = ap().april_debug_logits(ctx, rid, i, vocab)
+                        u = uniform_for(w.seed, rid, i)
+                        want = (osampler.categorical_sample(row, T, u) if sampler == ai.SAMPLER_CATEGORICAL
+                                else osampler.top_k_sample(row, top_k, T, u))
+                        assert t == chosen == want, (rid, i)
+                        assert abs(lps[i] - osampler.token_logprob(row, T, t)) <= LP_TOL, (rid, i)
+        finally:
+            ap().april_destroy(ctx)
+    assert [g["tokens"] for g in steps[0]] == [g["tokens"] for g in steps[1]]
+    assert [g["logprobs"] for g in steps[0]] == [g["logprobs"] for g in steps[1]]
