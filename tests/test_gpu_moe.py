@@ -3,7 +3,7 @@ import numpy as np
 import pytest
 
 import april_inputs as ai
-from gpu_common import assert_schedule_equal, have_gpu, make_engine, run_gpu, run_oracle
+from gpu_common import assert_schedule_equal, class_forced_tokens, have_gpu, make_engine, run_gpu, run_oracle
 
 pytestmark = pytest.mark.gpu
 
@@ -109,15 +109,14 @@ def test_moe_resumed_equals_uninterrupted():
         ap().april_destroy(c2)
 
 
-def test_expert_gemm_grouping_changes_no_bit(monkeypatch):
-    """Decode batches beyond a row bound give a workgroup 4 m-tiles of an expert's rows instead of
-    2; the grouping is not part of any summation chain: forcing either for every decode launch
-    of a run leaves every logit bit-identical.  (Prefill passes run the LDS-tiled expert kernels,
-    whatever the bound.)"""
-    shape = ai.ModelShape(2, 128, 4, 2, 32, 0, 512, n_experts=32, experts_per_tok=2, d_expert_ffn=64)
-    w = ai.Workload("moe_group", shape, 6, 150, 6, 9, 6, 1.5, 0.3, 3, 6, ai.SAMPLER_GREEDY, 0, 2, 23)
-    weights = ai.make_weights(shape, w.seed)
-    reqs = ai.make_requests(w, ai.requests_needed(w))
+def check_grouping(monkeypatch, w, n, n_classes=None):
+    """Runs w with 4 m-tiles of an expert's rows per workgroup in every decode launch, then with 2, and compares the bits."""
+    weights = ai.make_weights(w.shape, w.seed)
+    reqs = ai.make_requests(w, n)
+    forced = None
+    if n_classes:
+        ctoks = class_forced_tokens(w, n_classes)
+        forced = {r.request_id: ctoks[r.request_id % n_classes][:w.max_new] for r in reqs}
     runs = []
     for tall in ("1", "1000000000"):              # always 4 m-tiles / always 2
         monkeypatch.setenv("APRIL_MOE_TALL_ROWS", tall)
@@ -125,12 +124,12 @@ def test_expert_gemm_grouping_changes_no_bit(monkeypatch):
         try:
             for r in reqs:
                 ap().april_debug_watch(ctx, r.request_id, 0, w.max_new)
-            got = run_gpu(ctx, reqs, w.n_target, w.n_overprovision, w.max_new, w.steps)
+            got = run_gpu(ctx, reqs, w.n_target, w.n_overprovision, w.max_new, w.steps, forced=forced)
             logits = {}
             for g in got:
                 for rid, toks in list(zip(g["ids"], g["tokens"])) + list(g["buffer_tokens"].items()):
                     for i in range(len(toks)):
-                        logits[(rid, i)] = ap().april_debug_logits(ctx, rid, i, shape.vocab)[0]
+                        logits[(rid, i)] = ap().april_debug_logits(ctx, rid, i, w.shape.vocab)[0]
             runs.append((got, logits))
         finally:
             ap().april_destroy(ctx)
@@ -139,3 +138,28 @@ def test_expert_gemm_grouping_changes_no_bit(monkeypatch):
     assert [g["tokens"] for g in a] == [g["tokens"] for g in b]
     assert la.keys() == lb.keys() and len(la) > 40
     assert all(np.array_equal(la[k], lb[k]) for k in la)
+    return a, la
+
+
+def test_expert_gemm_grouping_changes_no_bit(monkeypatch):
+    """Decode batches beyond a row bound give a workgroup 4 m-tiles of an expert's rows instead of
+    2; the grouping is not part of any summation chain.  Here an expert has at most 9 rows, one m-tile, which runs the
+    same body under either bound: the segments' alignment and the two steps' bookkeeping are what differs.
+    (Prefill passes run the LDS-tiled expert kernels, whatever the bound.)"""
+    shape = ai.ModelShape(2, 128, 4, 2, 32, 0, 512, n_experts=32, experts_per_tok=2, d_expert_ffn=64)
+    w = ai.Workload("moe_group", shape, 6, 150, 6, 9, 6, 1.5, 0.3, 3, 6, ai.SAMPLER_GREEDY, 0, 2, 23)
+    check_grouping(monkeypatch, w, ai.requests_needed(w))
+
+
+@pytest.mark.parametrize("n_classes", [2, 3, 5, 13])
+def test_expert_gemm_grouping_of_full_batches_changes_no_bit(monkeypatch, n_classes):
+    """200 rollouts of n_classes prompts, the same forced tokens within a class: its 100, 66, 40 or 15 rows take the same
+    experts, which get 4, 3, 2 or 1 m-tiles of rows (more where classes share one).  Same bits from workgroups
+    of 4 and of 2 m-tiles, and from every row of a class: also from the 64th on, where the groups of 2 part."""
+    shape = ai.ModelShape(2, 128, 4, 2, 32, 0, 512, n_experts=32, experts_per_tok=2, d_expert_ffn=64)
+    n, gen = 200, 4
+    w = ai.Workload("moe_full", shape, n_classes, 9, n, n, gen, 1.5, 0.1, gen, gen, ai.SAMPLER_GREEDY, 0, 1, 23)
+    got, logits = check_grouping(monkeypatch, w, n, n_classes)
+    assert got[0]["iters"] >= gen - 1 and got[0]["sum_live"] >= n * (gen - 1)
+    for (rid, i), row in logits.items():
+        assert np.isfinite(row).all() and np.array_equal(row, logits[(rid % n_classes, i)]), (rid, i)
