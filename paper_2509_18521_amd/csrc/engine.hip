@@ -9,6 +9,8 @@
 #include <cstdlib>
 #include <cstring>
 #include <map>
+#include <memory>
+#include <new>
 #include <string>
 #include <vector>
 
@@ -1341,7 +1343,7 @@ int april_debug_logits(april_ctx* c, int64_t request_id, int32_t gen_index, floa
 static int sample_rows_impl(april_ctx* c, const float* logits, int32_t n_rows, const int64_t* request_ids,
                             const int32_t* gen_index, int32_t* out_tokens, float* out_logprobs) {
   if (!c || !logits || !request_ids || !gen_index || !out_tokens || n_rows <= 0) return APRIL_EINVAL;
-  // The temporaries stay with the context (until april_destroy) and rows go through in parts that keep
+  // The temporaries stay with the context (until april_memory_pause or april_destroy) and rows go through in parts that keep
   // them within 64 MiB: allocating and releasing them took 8 calls that synchronise the device, about 70 of
   // the 700 us of a call for 192 rows of 152 k logits.  Records of one part: row keys (packed: one
   // copy in, one copy out), then the group records.
@@ -1361,16 +1363,18 @@ static int sample_rows_impl(april_ctx* c, const float* logits, int32_t n_rows, c
     c->sr_ws_bytes = need;
   }
   char* w = c->sr_ws;
-  std::vector<char> stage(off_lp + (size_t)part_rows * 4);
+  // (nothing may be thrown through this C entry)
+  std::unique_ptr<char[]> stage(new (std::nothrow) char[off_lp + (size_t)part_rows * 4]);
+  if (!stage) return fail(c, APRIL_ENOMEM, "sampler staging");
   for (int r0 = 0; r0 < n_rows; r0 += part_rows) {
     const int n = std::min(part_rows, n_rows - r0);
     const int ctl[2] = {n, 0};
-    memcpy(stage.data(), ctl, 8);
-    memcpy(stage.data() + 8, request_ids + r0, (size_t)n * 8);
-    memcpy(stage.data() + off_gen, gen_index + r0, (size_t)n * 4);
+    memcpy(stage.get(), ctl, 8);
+    memcpy(stage.get() + 8, request_ids + r0, (size_t)n * 8);
+    memcpy(stage.get() + off_gen, gen_index + r0, (size_t)n * 4);
     // (hipMemcpy on the null stream: also orders this call behind the caller's work on that stream,
     // which may still be producing the logits)
-    HIPCHK(c, hipMemcpy(w, stage.data(), off_out, hipMemcpyHostToDevice));
+    HIPCHK(c, hipMemcpy(w, stage.get(), off_out, hipMemcpyHostToDevice));
     const float* lg = logits + (size_t)r0 * V;
     float* gm = reinterpret_cast<float*>(w + off_gm);
     double* gs = sums ? reinterpret_cast<double*>(w + off_gs) : nullptr;
@@ -1381,10 +1385,10 @@ static int sample_rows_impl(april_ctx* c, const float* logits, int32_t n_rows, c
     launch_sample(c->stream, RowCtx{nullptr, nullptr, reinterpret_cast<const int2*>(w), n}, c->ds, nullptr, lg, V, sc, Watch{}, 0,
                   reinterpret_cast<const long long*>(w + 8), reinterpret_cast<const int*>(w + off_gen),
                   reinterpret_cast<int*>(w + off_out), gm, grp, lp, nullptr, gs);
-    HIPCHK(c, hipMemcpyAsync(stage.data() + off_out, w + off_out, off_lp + (lp ? (size_t)part_rows * 4 : 0) - off_out, hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(c, hipMemcpyAsync(stage.get() + off_out, w + off_out, off_lp + (lp ? (size_t)part_rows * 4 : 0) - off_out, hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
-    memcpy(out_tokens + r0, stage.data() + off_out, (size_t)n * 4);
-    if (lp) memcpy(out_logprobs + r0, stage.data() + off_lp, (size_t)n * 4);
+    memcpy(out_tokens + r0, stage.get() + off_out, (size_t)n * 4);
+    if (lp) memcpy(out_logprobs + r0, stage.get() + off_lp, (size_t)n * 4);
   }
   return APRIL_OK;
 }
