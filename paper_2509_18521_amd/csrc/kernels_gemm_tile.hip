@@ -5,12 +5,13 @@
 // consecutive bytes), but compute-bound, so it is organised around operand reuse:
 //   * a workgroup of WGM x WGN wavefronts owns a (WGM*MTW*32) x (WGN*NTW*32) output tile;
 //     each wavefront keeps MTW x NTW accumulator tiles;
-//   * the k loop advances in stages of BK k-tiles; the fragments of a stage go
-//     global -> registers -> LDS once per workgroup (every fragment is one contiguous 1 KiB
-//     piece; LDS reads are lane-consecutive 16-byte pieces, conflict-free) while the MFMAs of
-//     the previous stage run from the other LDS buffer; one barrier per stage;
+//   * the k loop advances in stages of BK k-tiles; the fragments of a stage go global -> LDS once
+//     per workgroup (every fragment is one contiguous 1 KiB piece; LDS reads are lane-consecutive
+//     16-byte pieces, conflict-free) while the MFMAs of earlier stages run from the ring's other
+//     slots; one barrier per stage;
 //   * every output element is one accumulator chain over k-tiles 0..K/16-1 in order, whatever
 //     the tile shape or the number of rows: results do not depend on the batch.
+// Every kernel here asks for K % 32 == 0, as april_init does of every inner dimension.
 #include <type_traits>
 
 #include "kernels.h"
@@ -179,114 +180,6 @@ __device__ inline void qkv_epilogue(f32x16 (&acc)[4][MTW], int nt0, int mt0, int
   }
 }
 
-template <int WGM, int WGN, int MTW, int NTW, int BK, int EPI>
-__global__ __launch_bounds__(64 * WGM * WGN) __attribute__((amdgpu_waves_per_eu(2)))
-void gemm_tile_kernel(RowCtx rc, const bf16x8* __restrict__ x,
-                                                                   const bf16x8* __restrict__ w0,
-                                                                   const bf16x8* __restrict__ w1,
-                                                                   float* __restrict__ out, bf16_t* __restrict__ act,
-                                                                   int N, int K) {
-  constexpr int NW = WGM * WGN, MT = WGM * MTW, NT = WGN * NTW, FR = MT + NT;
-  constexpr int PER = FR * BK / NW;             // fragments one wavefront stages per stage
-  static_assert(FR * BK % NW == 0 && NW % BK == 0, "staging split");
-  static_assert(EPI != TEPI_SWIGLU || NTW % 2 == 0, "gate/up pairs");
-  __shared__ bf16x8 lds[2][BK][FR][64];
-  const int rows = rows_or_zero(rc);
-  const int m0 = blockIdx.y * MT;
-  if (m0 * 32 >= rows) return;
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int wm = wave / WGN, wn = wave % WGN;
-  const int KT = K >> 4;
-  const int m_last = (rows - 1) >> 5;           // last activation tile that holds a live row
-  const int n_tiles = N >> 5;                   // SwiGLU: feature tiles (N = F)
-
-  // Fragment slot t of a stage: t < MT activation tile m0 + t, else weight slot t - MT.
-  // Weight slot i belongs to wavefront column i / NTW; plain: tile n0 + i; SwiGLU: the first
-  // half of a wavefront's slots are gate tiles, the second half the up tiles of the same
-  // features.  Tiles past the end are clamped for the loads and never stored.
-  auto slot_base = [&](int t) -> const bf16x8* {
-    if (t < MT) {
-      int mt = m0 + t;
-      if (mt > m_last) mt = m_last;
-      return x + (size_t)mt * KT * 64;
-    }
-    const int i = t - MT;
-    if (EPI == TEPI_SWIGLU) {
-      constexpr int H = NTW / 2;
-      const int col = i / NTW, ii = i % NTW;
-      int f = blockIdx.x * (NT / 2) + col * H + (ii < H ? ii : ii - H);
-      if (f >= n_tiles) f = n_tiles - 1;
-      return (ii < H ? w0 : w1) + (size_t)f * KT * 64;
-    }
-    int nt = blockIdx.x * NT + i;
-    if (nt >= n_tiles) nt = n_tiles - 1;
-    return w0 + (size_t)nt * KT * 64;
-  };
-
-  // staging: wavefront w moves k-tile (w % BK) of the slots t = w / BK + (NW / BK) * u
-  const int skk = wave % BK, st0 = wave / BK;
-  const bf16x8* src[PER];
-#pragma unroll
-  for (int u = 0; u < PER; ++u) src[u] = slot_base(st0 + (NW / BK) * u) + lane;
-  bf16x8 stg[PER];
-  auto stage_load = [&](int s) {
-    const int kt = s * BK + skk;
-    const bool live = kt < KT;                  // a k-tile past the end contributes zeros
-    const size_t off = (size_t)(live ? kt : KT - 1) * 64;
-#pragma unroll
-    for (int u = 0; u < PER; ++u) {
-      const bf16x8 v = src[u][off];
-      stg[u] = live ? v : bf16x8{};
-    }
-  };
-  auto stage_store = [&](int buf) {
-#pragma unroll
-    for (int u = 0; u < PER; ++u) lds[buf][skk][st0 + (NW / BK) * u][lane] = stg[u];
-  };
-
-  f32x16 acc[NTW][MTW];
-#pragma unroll
-  for (int i = 0; i < NTW; ++i)
-#pragma unroll
-    for (int j = 0; j < MTW; ++j) acc[i][j] = f32x16{};
-
-  const int n_stages = (KT + BK - 1) / BK;
-  stage_load(0);
-  stage_store(0);
-  __syncthreads();
-  for (int s = 0; s < n_stages; ++s) {
-    const int buf = s & 1;
-    const bool more = s + 1 < n_stages;
-    if (more) stage_load(s + 1);
-    // operand fragments of k-tile kk+1 are read from LDS while the MFMAs of k-tile kk run
-    bf16x8 a[2][NTW], b[2][MTW];
-#pragma unroll
-    for (int i = 0; i < NTW; ++i) a[0][i] = lds[buf][0][MT + wn * NTW + i][lane];
-#pragma unroll
-    for (int j = 0; j < MTW; ++j) b[0][j] = lds[buf][0][wm * MTW + j][lane];
-#pragma unroll
-    for (int kk = 0; kk < BK; ++kk) {
-      const int cur = kk & 1, nxt = cur ^ 1;
-      if (kk + 1 < BK) {
-#pragma unroll
-        for (int i = 0; i < NTW; ++i) a[nxt][i] = lds[buf][kk + 1][MT + wn * NTW + i][lane];
-#pragma unroll
-        for (int j = 0; j < MTW; ++j) b[nxt][j] = lds[buf][kk + 1][wm * MTW + j][lane];
-      }
-#pragma unroll
-      for (int i = 0; i < NTW; ++i)
-#pragma unroll
-        for (int j = 0; j < MTW; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[cur][i], b[cur][j], acc[i][j], 0, 0, 0);
-    }
-    if (more) stage_store(buf ^ 1);
-    __syncthreads();
-  }
-
-  tile_epilogue<MTW, NTW, EPI>(acc, blockIdx.x * (EPI == TEPI_SWIGLU ? NT / 2 : NT) + wn * (EPI == TEPI_SWIGLU ? NTW / 2 : NTW),
-                               m0 + wm * MTW, rows, n_tiles, N, lane, out, act);
-}
-
 // One wavefront-wide copy of 64 x 16 bytes from global memory (a per-lane address) to LDS
 // (a wavefront-uniform base; lane l lands at base + 16*l).  Device pass only: the host pass
 // has no such instruction to type-check.
@@ -305,7 +198,7 @@ __device__ inline void wait_vector_memory() {   // until at most LEFT vector-mem
 #endif
 }
 
-// Same tiling with the stage fragments copied global -> LDS by the memory pipeline itself
+// The stage fragments are copied global -> LDS by the memory pipeline itself
 // (global_load_lds_dwordx4: each lane's 16 bytes land at consecutive LDS addresses, which is
 // exactly the fragment layout), through a ring of R stage buffers.  Nothing is staged in
 // registers, so R - 1 stages of loads stay in flight behind the MFMAs.  Hand-placed waits:
@@ -728,12 +621,10 @@ bool launch_moe_tile_down(hipStream_t st, RowCtx rc, const int* cnt, const int* 
 
 // Tile shapes.  WIDE: 256 x 256 outputs on 4 wavefronts (gemm_big_kernel, 128 KiB LDS).  NARROW: 256 x 128 on 4 wavefronts, ring of 3
 // (72 KiB, two workgroups per CU) - for few or ragged weight tiles and for short batches.
-// REGS: register-staged fallback for K not a multiple of 32.  Measured on MI355X, 8192 x
-// (2 x 14336) x 4096 fused gate/up: REGS 0.84, NARROW 0.99, WIDE 1.3 PFLOP/s.  The choice
+// Measured on MI355X, 8192 x (2 x 14336) x 4096 fused gate/up: NARROW 0.99, WIDE 1.3 PFLOP/s.  The choice
 // changes no result (see the header comment).
 #define TILE_WIDE(EPI) gemm_big_kernel<EPI>
 #define TILE_NARROW(EPI) gemm_tile_dma_kernel<2, 2, 4, 2, 2, 3, EPI>
-#define TILE_REGS(EPI) gemm_tile_kernel<2, 2, 4, 2, 2, EPI>
 
 // SMALL: 64 rows x 32 columns (SwiGLU: 32 features) on 2 wavefronts, ring of 16 stages, and MID: 128 x 64 on 4,
 // ring of 12 (8), for passes of few rows: there a workgroup of the larger tiles walks k alone at two
@@ -760,10 +651,7 @@ static void launch_tile(hipStream_t st, RowCtx rc, const bf16_t* x, const bf16_t
   const int n_tiles = N >> 5, m_tiles = ceil_div(rc.max_rows, 32);
   const bf16x8* xv = reinterpret_cast<const bf16x8*>(x);
   const bf16x8* wv = reinterpret_cast<const bf16x8*>(Wp);
-  if (K % 32 != 0) {
-    dim3 grid(ceil_div(n_tiles, 4), ceil_div(m_tiles, 8));
-    hipLaunchKernelGGL((TILE_REGS(EPI)), grid, dim3(256), 0, st, rc, xv, wv, nullptr, out, nullptr, N, K);
-  } else if (small_tile(n_tiles, m_tiles)) {
+  if (small_tile(n_tiles, m_tiles)) {
     hipLaunchKernelGGL((TILE_SMALL(EPI)), dim3(n_tiles, ceil_div(m_tiles, 2)), dim3(128), 0, st, rc, xv, wv, nullptr, out, nullptr, N, K, GroupOut{});
   } else if (mid_tile(n_tiles, m_tiles, 512)) {
     hipLaunchKernelGGL((TILE_MID(EPI)), dim3(ceil_div(n_tiles, 2), ceil_div(m_tiles, 4)), dim3(256), 0, st, rc, xv, wv, nullptr, out, nullptr, N, K, GroupOut{});
@@ -782,7 +670,7 @@ void launch_gemm_tile_resid(hipStream_t st, RowCtx rc, const bf16_t* x, const bf
   launch_tile<TEPI_RESID>(st, rc, x, Wp, x_res, N, K);
 }
 bool launch_gemm_tile_qkv(hipStream_t st, RowCtx rc, const bf16_t* x, const bf16_t* Wp, int N, int K, const QkvOut& qo) {
-  if (K % 32 != 0 || qo.kvl.mode != 1) return false;
+  if (qo.kvl.mode != 1) return false;
   dim3 grid(ceil_div(N >> 5, 8), ceil_div(ceil_div(rc.max_rows, 32), 8));
 #define QKV_LAUNCH(DH)                                                                                                 \
   hipLaunchKernelGGL((gemm_big_kernel<TEPI_QKV, DH>), grid, dim3(256), 0, st, rc, reinterpret_cast<const bf16x8*>(x),  \
@@ -803,10 +691,7 @@ void launch_gemm_tile_swiglu(hipStream_t st, RowCtx rc, const bf16_t* x, const b
   const bf16x8* xv = reinterpret_cast<const bf16x8*>(x);
   const bf16x8* gv = reinterpret_cast<const bf16x8*>(Wg);
   const bf16x8* uv = reinterpret_cast<const bf16x8*>(Wu);
-  if (K % 32 != 0) {
-    dim3 grid(ceil_div(f_tiles, 2), ceil_div(m_tiles, 8));
-    hipLaunchKernelGGL((TILE_REGS(TEPI_SWIGLU)), grid, dim3(256), 0, st, rc, xv, gv, uv, nullptr, act, F, K);
-  } else if (small_tile(f_tiles, m_tiles)) {
+  if (small_tile(f_tiles, m_tiles)) {
     hipLaunchKernelGGL((TILE_SMALL_SWIGLU), dim3(f_tiles, ceil_div(m_tiles, 2)), dim3(128), 0, st, rc, xv, gv, uv, nullptr, act, F, K, GroupOut{});
   } else if (mid_tile(f_tiles, m_tiles, 256)) {
     hipLaunchKernelGGL((TILE_MID_SWIGLU), dim3(ceil_div(f_tiles, 2), ceil_div(m_tiles, 4)), dim3(256), 0, st, rc, xv, gv, uv, nullptr, act, F, K, GroupOut{});
@@ -869,7 +754,6 @@ bool launch_gemm_tile_swiglu_chain(hipStream_t st, RowCtx rc, const bf16_t* x, c
 // 217 | 222.  At 384, 512 rows: 32000 x 4096 113, 124 | 114, 114; 151936 x 896 117, 149 | 8: 142, 145; 128256 x 4096 383, 490 | 441, 457.
 bool launch_gemm_tile_logits(hipStream_t st, RowCtx rc, const bf16_t* x, const bf16_t* Wp, float* logits,
                              const GroupOut& go, int V, int K) {
-  if (K % 32 != 0) return false;
   const int groups = ceil_div(V >> 5, 8), rows = rc.max_rows;            // 256-column groups
   if (rows <= 32 && (K >= 3072 || groups < 256)) return false;
 #define LM_LAUNCH(KERNEL, MT, THREADS, ...)                                                                              \
