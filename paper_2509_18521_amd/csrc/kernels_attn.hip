@@ -24,7 +24,7 @@
 // the last KV split computes the new token's rotated key and its value, stores them in the
 // page as bf16, and substitutes exactly those bf16 values into the fragments of the tile
 // that holds the position, so the products are bit-identical to reading them back.
-// (Prefill keeps the separate rope/append kernel: its rows attend to each other's new keys.)
+// (Prefill rows attend to each other's new keys: there the QKV projection's epilogue rotates and appends.)
 //
 // KV page layout (written by rope_append_kernel or here, mode 1), per (page, KV head):
 //   K: MFMA A-fragment order  [d/32][lane = t + 16*((d%32)/8)][d%8]   -> 1 KiB coalesced loads
@@ -537,8 +537,8 @@ __global__ __launch_bounds__(64) void attn_merge_kernel(RowCtx rc, int row_base,
 // of the second product, whose V fragment is then one 16-byte read.
 //
 // Every column runs its own online softmax, in base 2 with the scale folded into one multiply-add
-// per score.  The running maximum may lag the true one by up to 2^8: the accumulators are rescaled
-// only when a column's maximum passes its running one by more (probabilities are then at most 256,
+// per score.  The running maximum may lag the true one by up to 2^8 (the conditional rescaling known from
+// published flash-attention kernels): the accumulators are rescaled only when a column's maximum passes its running one by more (probabilities are then at most 256,
 // which costs no precision in bf16 or fp32), by exactly 1 for the columns that did not.  Each
 // lane sums its own tokens' probabilities; the halves of a column meet once at the end.  Positions beyond
 // the column's own are masked, in the stages that hold any.  A column's result depends on its own

@@ -437,7 +437,7 @@ void launch_gemm_mfma_swiglu(hipStream_t st, RowCtx rc, const bf16_t* x, const b
                      reinterpret_cast<const bf16x8*>(Wu), nullptr, act, F, K, 1, (size_t)0, nf)
   const int tiles8 = ceil_div(n_tiles, 8) * 8;
   if (m_tiles <= 1) GEMM_SW(1, 4, 3, false, dim3(n_tiles));
-  else if (n_tiles <= 256 && n_tiles % 8 == 0) GEMM_SW(2, 2, 3, false, dim3(n_tiles, 1, ceil_div(m_tiles, 2)));
+  else if (n_tiles <= 256 && (m_tiles <= 2 || n_tiles % 8 == 0)) GEMM_SW(2, 2, 3, false, dim3(n_tiles, 1, ceil_div(m_tiles, 2)));
   else if (n_tiles <= 256 || m_tiles <= 3) GEMM_SW(2, 2, 3, true, dim3(tiles8 * ceil_div(m_tiles, 2)));
   else GEMM_SW(3, 3, 2, true, dim3(tiles8 * ceil_div(m_tiles, 3)));
 #undef GEMM_SW
