@@ -110,12 +110,11 @@ def class_parity(w, steps, min_rows, skip_positions=None):
 def test_dense_wide_layer_many_rows(name, n_target, n_over):
     """One layer of configuration 3 (d 2560, F 9728) / 4 (d 4096, F 14336), 192 or 300 rollouts
     in flight, two steps (the second decodes resumed rollouts next to a fresh prefill).
-    Decode launches reached (rocprofv3 kernel trace of this test): qkv and down through
-    gemm_mfma_kernel<2,4,EPI_F32,true> with 2-3 m-groups; the output projection through
-    gemm_mfma_kernel<1,4,EPI_RESID,true>; gate/up through gemm_tile_chain_kernel<2,2,3,2,2,3>
-    (192 rows) and <4,2,2,2,2,3> (300 rows of configuration 4: two row groups) or, for 300 rows of configuration
-    3, gemm_mfma_kernel<2,4,EPI_SWIGLU,true> with three m-groups; the LM head through the
-    tall-batch kernel."""
+    Decode launches reached (rocprofv3 kernel trace of this file): qkv and down through
+    gemm_mfma_kernel<2,3 / 4,3 / 4,4,EPI_F32,...> with one to four m-groups; the output projection through
+    its residual epilogue with one to three m-tiles or pairs of n-tiles; gate/up through
+    gemm_tile_chain_kernel<2,2,3,2,2,3> (192 rows; 300 rows of configuration 4 in two row groups) or, for 300 rows of
+    configuration 3, <2,2,2,2,2,3> in three; the LM head on 128- and 256-row tiles."""
     base = ai.WORKLOADS[name]
     shape = ai.reduced(base, n_layers=1, vocab=8192).shape
     w = ai.Workload(f"{name}_L1_{n_over}", shape, 37, 7, n_target, n_over, 5, 1.45, 0.2, 3, 5,
@@ -128,13 +127,11 @@ def test_dense_wide_layer_many_rows(name, n_target, n_over):
 @pytest.mark.parametrize("name,n_over", [("cfg3_mid_bf16", 150), ("cfg3_mid_bf16", 230), ("cfg3_mid_bf16", 300),
                                          ("cfg4_8b_bf16", 230), ("cfg4_8b_bf16", 300)])
 def test_wide_layer_batch_size_changes_no_bit(name, n_over):
-    """At the widths of configurations 3 and 4 the row count picks the kernels: qkv and down on the
-    skinny kernel with one or several m-groups, except the down projection of configuration 4,
-    which above 128 rows runs on the LDS-tiled kernel with the same summation chains (long k
-    slices that fall on stage boundaries); the output projection with
-    one or four m-tiles per workgroup; gate/up on the skinny kernel (4 rows, and 300 of
-    configuration 3), the 192-row LDS tile (150) or the 256-row one (230, and 300 of
-    configuration 4); the LM head skinny or tall.  Each choice keeps every output element's
+    """At the widths of configurations 3 and 4 the row count picks the kernels and tiles: qkv and down on
+    2 x 4 (n-tiles x m-tiles) for 4 rows, 2 x 3, 4 x 3 or 4 x 4 above; the output projection with one to four m-tiles
+    per workgroup; gate/up on the skinny kernel (4 rows), or the LDS-tiled one in one 192-row (150) or 256-row
+    tile (230), or row groups of 128 (300 of configuration 3) or 192 (300 of configuration 4); the LM head skinny or on
+    128- and 256-row tiles.  Each choice keeps every output element's
     summation chain, so the first four requests must get bit-identical logits whether they run
     alone or among n_over rollouts (teacher-forced tokens: both runs feed the same sequences)."""
     base = ai.WORKLOADS[name]
