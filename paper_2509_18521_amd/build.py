@@ -11,6 +11,7 @@ OBJ_DIR = os.path.join(PKG, "_build")
 SOURCES = ["engine.hip", "kernels_basic.hip", "kernels_gemm.hip", "kernels_gemm_tile.hip", "kernels_attn.hip", "kernels_moe.hip", "kernels_sample.hip"]
 FLAGS = ["-O3", "--offload-arch=gfx950", "-fPIC", "-std=c++17",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+         "-mllvm", "-amdgpu-kernarg-preload-count=14",
          "-Wno-unused-command-line-argument", "-Wno-unused-value", "-Wno-unused-result"]
 
 

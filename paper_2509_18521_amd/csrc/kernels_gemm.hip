@@ -48,20 +48,60 @@ struct NormFuse {
 
 constexpr int KW4 = 4;       // wavefronts of a workgroup (template parameter KW); they split the k range among themselves
 
-// One workgroup: NT weight tiles x MTC activation tiles over k-tiles [k0, k1).  Each of
-// the KW wavefronts accumulates a quarter of the k range, the partial accumulators are
-// summed through LDS in a fixed tree order, wavefront 0 runs the epilogue.
-template <int NT, int MTC, int EPI, bool INTRA, int KW, int KH>
+// The products of one wavefront: NT weight tiles x MTC activation tiles over k-tiles [kb, ke), one accumulator
+// chain per element in ascending k.  D k-tiles are in flight in registers (4 VGPRs per fragment): a slot is
+// requested again as soon as its products are issued, every load unconditional (past the end the last k-tile once more),
+// so the wait counts are static.  `early` requests what the epilogue wants, behind the first D k-tiles.
+template <int NT, int MTC, int D, class Early>
+__device__ __forceinline__ void accumulate(const bf16x8* const (&wp)[NT], const bf16x8* const (&xp)[MTC], int kb, int ke,
+                                           f32x16 (&acc)[NT][MTC], Early early) {
+  bf16x8 a[D][NT], b[D][MTC];
+  auto fetch = [&](int u, int kt) {
+    const size_t k = (size_t)(kt < ke ? kt : ke - 1) * 64;
+#pragma unroll
+    for (int i = 0; i < NT; ++i) a[u][i] = wp[i][k];
+#pragma unroll
+    for (int j = 0; j < MTC; ++j) b[u][j] = xp[j][k];
+  };
+  auto multiply = [&](int u) {
+#pragma unroll
+    for (int i = 0; i < NT; ++i)
+#pragma unroll
+      for (int j = 0; j < MTC; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[u][i], b[u][j], acc[i][j], 0, 0, 0);
+  };
+  if (kb >= ke) { early(); return; }
+#pragma unroll
+  for (int u = 0; u < D; ++u) fetch(u, kb + u);
+  early();
+  __builtin_amdgcn_sched_barrier(0);            // all of it requested before the first product waits
+  int kt = kb;
+  for (; kt + D < ke; kt += D) {
+#pragma unroll
+    for (int u = 0; u < D; ++u) {
+      multiply(u);
+      fetch(u, kt + D + u);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < D; ++u)
+    if (kt + u < ke) multiply(u);
+}
+
+// One workgroup of the k-splitting kernels: NT weight tiles x MTC activation tiles over k-tiles [k0, k1).  Each of
+// the KW wavefronts accumulates a quarter of the k range; the partial accumulators meet in LDS, in wavefront order
+// ((0 + 1) + 2) + 3, and wavefront w finishes the registers 4 w .. 4 w + 3 of every tile: four 16-byte LDS reads
+// per tile and lane, and a quarter of the epilogue each.  HALF (gate/up): the tile's rows are 16 gate and 16 up features.
+template <int NT, int MTC, int EPI, int KW, int D, bool HALF>
 __device__ inline void gemm_group(const bf16x8* __restrict__ w0, const bf16x8* __restrict__ w1,
                                   const bf16x8* __restrict__ x, int KT, int k0, int k1, int nt0, int mt0,
                                   int rows, int N, float* __restrict__ out, bf16_t* __restrict__ act,
-                                  float* red, float* ssp, const NormFuse& nf) {
-  // KH k-tiles per fetch group, two groups in registers (4 VGPRs per fragment).  The next group is
-  // requested before the MFMAs of the current one, so a wavefront whose k range fits in two
-  // groups has all of it in flight at once, and a longer range streams with one group always in
-  // flight behind the arithmetic.
+                                  f32x4* red, float* ssp, const NormFuse& nf) {
+  static_assert(KW == 4 && MTC <= 4, "one register quarter per wavefront");
   // the wavefront index is uniform: keep it (and the k range derived from it) in scalar registers
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int mloc = lane & 31, nhalf = (lane >> 5) << 2;
   f32x16 acc[NT][MTC];
 #pragma unroll
   for (int i = 0; i < NT; ++i)
@@ -69,76 +109,53 @@ __device__ inline void gemm_group(const bf16x8* __restrict__ w0, const bf16x8* _
     for (int j = 0; j < MTC; ++j) acc[i][j] = f32x16{};
 
   const bf16x8* wp[NT];
-  if (EPI == EPI_SWIGLU) {
+  if (HALF) {
+    wp[0] = (mloc < 16 ? w0 : w1) + (size_t)(nt0 >> 1) * KT * 64 + ((nt0 & 1) * 16 + (mloc & 15) + (lane & 32));
+  } else if (EPI == EPI_SWIGLU) {
     wp[0] = w0 + (size_t)nt0 * KT * 64 + lane;
     if (NT > 1) wp[NT - 1] = w1 + (size_t)nt0 * KT * 64 + lane;
   } else {
 #pragma unroll
-    for (int i = 0; i < NT; ++i) {
-      int nt = nt0 + i;
-      if (EPI == EPI_LOGITS && nt >= (N >> 5)) nt = (N >> 5) - 1;   // vocabulary of an odd number of tiles: read, never written
-      wp[i] = w0 + (size_t)nt * KT * 64 + lane;
-    }
+    for (int i = 0; i < NT; ++i) wp[i] = w0 + (size_t)(nt0 + i) * KT * 64 + lane;
   }
+  // (columns past the last row repeat it: never written, and a few rows then cost a few cache lines)
   const bf16x8* xp[MTC];
+  int mrow[MTC];                                // this lane's row of every tile
 #pragma unroll
-  for (int j = 0; j < MTC; ++j) xp[j] = x + (size_t)(mt0 + j) * KT * 64 + lane;
-
+  for (int j = 0; j < MTC; ++j) {
+    mrow[j] = min((mt0 + j) * 32 + mloc, rows - 1);
+    xp[j] = x + (size_t)(mt0 + j) * KT * 64 + ((mrow[j] & 31) | (lane & 32));
+  }
   const int len = k1 - k0;
-  const int kb = INTRA ? k0 + (int)((long long)len * wave / KW) : k0;
-  const int ke = INTRA ? k0 + (int)((long long)len * (wave + 1) / KW) : k1;
-  // A group past the end re-reads the final k-tile (loads stay unconditional and in flight
-  // together) and skips its MFMAs.
-  bf16x8 a[2][KH][NT], b[2][KH][MTC];
-  auto fetch = [&](int g, int kt) {
-#pragma unroll
-    for (int u = 0; u < KH; ++u) {
-      const size_t k = (size_t)(kt + u < ke ? kt + u : ke - 1) * 64;
-#pragma unroll
-      for (int i = 0; i < NT; ++i) a[g][u][i] = wp[i][k];
-#pragma unroll
-      for (int j = 0; j < MTC; ++j) b[g][u][j] = xp[j][k];
-    }
-  };
-  auto multiply = [&](int g, int kt) {
-#pragma unroll
-    for (int u = 0; u < KH; ++u) {
-      if (kt + u < ke) {
-#pragma unroll
-        for (int i = 0; i < NT; ++i)
-#pragma unroll
-          for (int j = 0; j < MTC; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[g][u][i], b[g][u][j], acc[i][j], 0, 0, 0);
-      }
-    }
-  };
-  // Fused norm (consumer side): wavefront w adds the slabs w, w + KW, ... of its rows, wavefront
-  // 0 later adds the four sums.  The first 8 slabs per wavefront are requested here and summed
-  // after the k loop, so their latency hides behind the operand stream.
-  constexpr bool NORM_IN = (EPI == EPI_SWIGLU || EPI == EPI_F32) && INTRA;
+  const int kb = k0 + (int)((long long)len * wave / KW), ke = k0 + (int)((long long)len * (wave + 1) / KW);
+
+  // Fused norm (consumer side): wavefront w adds the slabs w, w + KW, ... of its rows; the four sums are
+  // added later.  The first 8 slabs per wavefront are requested behind the first operands.
+  constexpr bool NORM_IN = EPI == EPI_SWIGLU || EPI == EPI_F32;
   float sq[NORM_IN ? MTC : 1][8];
-  if (NORM_IN && nf.ssq != nullptr) {
+  // residual epilogue: this lane's residual values and gains
+  f32x4 xr[EPI == EPI_RESID ? NT : 1][EPI == EPI_RESID ? MTC : 1], gn[EPI == EPI_RESID ? NT : 1];
+  auto early = [&]() {
+    if (NORM_IN && nf.ssq != nullptr) {
 #pragma unroll
-    for (int j = 0; j < MTC; ++j) {
-      const float* col = nf.ssq + (mt0 + j) * 32 + (lane & 31);
+      for (int j = 0; j < MTC; ++j)
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int t = wave + u * KW;
-        sq[j][u] = col[(size_t)(t < nf.n_ssq ? t : nf.n_ssq - 1) * nf.ssq_stride];
+        for (int u = 0; u < 8; ++u) {
+          const int t = wave + u * KW;
+          sq[j][u] = nf.ssq[(size_t)(t < nf.n_ssq ? t : nf.n_ssq - 1) * nf.ssq_stride + mrow[j]];
+        }
+    }
+    if (EPI == EPI_RESID) {
+#pragma unroll
+      for (int i = 0; i < NT; ++i) {
+        const int n = (nt0 + i) * 32 + 8 * wave + nhalf;
+        gn[i] = *reinterpret_cast<const f32x4*>(nf.gain + n);
+#pragma unroll
+        for (int j = 0; j < MTC; ++j) xr[i][j] = *reinterpret_cast<const f32x4*>(out + (size_t)mrow[j] * N + n);
       }
     }
-  }
-  if (kb < ke) {
-    fetch(0, kb);
-    for (int kt = kb; kt < ke; kt += 2 * KH) {
-      fetch(1, kt + KH);
-      __builtin_amdgcn_sched_barrier(0);        // both groups requested before the first MFMA waits
-      multiply(0, kt);
-      if (kt + 2 * KH < ke) fetch(0, kt + 2 * KH);
-      __builtin_amdgcn_sched_barrier(0);
-      multiply(1, kt + KH);
-    }
-  }
+  };
+  accumulate<NT, MTC, D>(wp, xp, kb, ke, acc, early);
 
   if (NORM_IN && nf.ssq != nullptr) {
 #pragma unroll
@@ -147,7 +164,7 @@ __device__ inline void gemm_group(const bf16x8* __restrict__ w0, const bf16x8* _
 #pragma unroll
       for (int u = 0; u < 8; ++u)
         if (wave + u * KW < nf.n_ssq) sacc += sq[j][u];
-      const float* col = nf.ssq + (mt0 + j) * 32 + (lane & 31);
+      const float* col = nf.ssq + mrow[j];
       // wide models have more than 8 slabs per wavefront: the rest in groups of 8 independent loads
       for (int t0 = wave + 8 * KW; t0 < nf.n_ssq; t0 += 8 * KW) {
         float more[8];
@@ -163,174 +180,138 @@ __device__ inline void gemm_group(const bf16x8* __restrict__ w0, const bf16x8* _
       if (lane < 32) ssp[(wave * MTC + j) * 32 + lane] = sacc;
     }
   }
-  // Reduction over the KW wavefronts through LDS, and the split of the epilogue: every wavefront
-  // publishes its partial tiles, then wavefront w adds the KW partials of activation tile j = w
-  // in wavefront order (0 + 1 + 2 + 3) and runs the epilogue of that tile, so up to KW tiles are
-  // finished in parallel.  One weight tile per round: the buffer holds KW x MTC accumulator tiles.
-  constexpr int NREG = MTC * 16;
-  constexpr int JT = INTRA ? 1 : MTC;           // activation tiles this wavefront finishes
-  f32x16 res[NT][JT];
-  if (INTRA) {
-    static_assert(!INTRA || MTC <= KW, "one activation tile per wavefront");
+  // res[i][j]: registers 4 wave .. 4 wave + 3 of tile (i, j); HALF: wavefronts 0 and 1 also take the up
+  // features, registers 4 (wave + 2) .., in up[j]
+  f32x4 res[NT][MTC], up[HALF ? MTC : 1];
+  constexpr bool ONE = NT * MTC <= 2;           // every tile in one round, else one weight tile per round
+  constexpr int TILES = (ONE ? NT : 1) * MTC;   // tiles of a round
+  auto sum4 = [&](int t, int q) {
+    const f32x4* src = red + (size_t)(t * 4 + q) * 64 + lane;
+    f32x4 v = src[0];
 #pragma unroll
-    for (int i = 0; i < NT; ++i) {
-      if (i > 0) __syncthreads();               // everyone has read the previous round
-      float* dst = red + (size_t)wave * NREG * 64 + lane;
+    for (int w = 1; w < KW; ++w) v += src[(size_t)w * TILES * 4 * 64];
+    return v;
+  };
 #pragma unroll
-      for (int jq = 0; jq < MTC; ++jq)
+  for (int i0 = 0; i0 < NT; i0 += ONE ? NT : 1) {
+    if (i0 > 0) __syncthreads();                // everyone has read the previous round
 #pragma unroll
-        for (int e = 0; e < 16; ++e) dst[(jq * 16 + e) * 64] = acc[i][jq][e];
-      __syncthreads();
-      if (wave < MTC) {
-        const float* src = red + (size_t)wave * 16 * 64 + lane;      // tile j = wave of wavefront 0's slab
+    for (int i = i0; i < (ONE ? NT : i0 + 1); ++i)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          float v = src[e * 64];
+      for (int j = 0; j < MTC; ++j)
 #pragma unroll
-          for (int w = 1; w < KW; ++w) v += src[(size_t)w * NREG * 64 + e * 64];
-          res[i][0][e] = v;
-        }
+        for (int q = 0; q < 4; ++q)
+          red[((size_t)wave * TILES + (i - i0) * MTC + j) * 256 + q * 64 + lane] =
+              f32x4{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+    __syncthreads();
+#pragma unroll
+    for (int i = i0; i < (ONE ? NT : i0 + 1); ++i)
+#pragma unroll
+      for (int j = 0; j < MTC; ++j) {
+        if (HALF && wave >= 2) continue;
+        res[i][j] = sum4((i - i0) * MTC + j, wave);
+        if (HALF) up[j] = sum4(j, wave + 2);
       }
-    }
-    if (wave >= MTC) return;
-  } else {
-#pragma unroll
-    for (int i = 0; i < NT; ++i)
-#pragma unroll
-      for (int jq = 0; jq < JT; ++jq) res[i][jq] = acc[i][jq];
   }
-  const int j0 = INTRA ? wave : 0;              // first (INTRA: only) activation tile of this wavefront
+  if (HALF && wave >= 2) return;
 
-  const int mloc = lane & 31, nhalf = (lane >> 5) << 2;
-  if (EPI == EPI_LOGITS) {
-    // per row: the record of this wavefront's 64 output columns - maximum, its column, sum of
-    // exponentials.  With those the greedy sampler and its log-probabilities need no logits at all.
-    const bool two = nt0 + 1 < (N >> 5);
+  float inv[MTC];
+  if (NORM_IN) {
 #pragma unroll
-    for (int jq = 0; jq < JT; ++jq) {
-      float bv;
-      int bn;
-      double s = 0.0;
-      group64_record(res[0][jq], res[NT - 1][jq], two, nhalf, nf.go.sum != nullptr, nf.go.inv_t, bv, bn, s);
-      const int m = (mt0 + j0 + jq) * 32 + mloc;
-      if (m < rows && lane < 32) {
-        const size_t gi = (size_t)m * ((N + 63) >> 6) + (nt0 >> 1);
-        nf.go.max[gi] = bv;
-        if (nf.go.col) nf.go.col[gi] = bn;
-        if (nf.go.sum) nf.go.sum[gi] = s;
-      }
-    }
-  }
-  if (EPI == EPI_F32 || (EPI == EPI_LOGITS && out != nullptr)) {
-#pragma unroll
-    for (int i = 0; i < NT; ++i) {
-      if (EPI == EPI_LOGITS && nt0 + i >= (N >> 5)) continue;
-#pragma unroll
-      for (int jq = 0; jq < JT; ++jq) {
-        const int j = j0 + jq;
-        const int m = (mt0 + j) * 32 + mloc;
-        float inv = 1.0f;
-        if (NORM_IN && nf.ssq != nullptr) {          // fused norm: a k-split partial scales like the sum
-          float ssum = ssp[j * 32 + mloc];
-#pragma unroll
-          for (int w = 1; w < KW; ++w) ssum += ssp[(w * MTC + j) * 32 + mloc];
-          inv = 1.0f / sqrtf(ssum * nf.inv_d + nf.eps);
-        }
-        if (m < rows) {
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const int n = (nt0 + i) * 32 + 8 * q + nhalf;
-            f32x4 v = {res[i][jq][4 * q] * inv, res[i][jq][4 * q + 1] * inv, res[i][jq][4 * q + 2] * inv, res[i][jq][4 * q + 3] * inv};
-            *reinterpret_cast<f32x4*>(out + (size_t)m * N + n) = v;
-          }
-        }
-      }
-    }
-  } else if (EPI == EPI_RESID) {
-    // out = residual stream (updated in place), act = gain-scaled bf16 copy for the next GEMM
-#pragma unroll
-    for (int i = 0; i < NT; ++i)
-#pragma unroll
-      for (int jq = 0; jq < JT; ++jq) {
-        const int m = (mt0 + j0 + jq) * 32 + mloc;
-        float ss = 0.f;
-        if (m < rows) {
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const int n = (nt0 + i) * 32 + 8 * q + nhalf;
-            float* xr = out + (size_t)m * N + n;
-            f32x4 v = *reinterpret_cast<const f32x4*>(xr);
-            const f32x4 gn = *reinterpret_cast<const f32x4*>(nf.gain + n);
-            bf16x4 h;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              v[e] += res[i][jq][4 * q + e];
-              ss += v[e] * v[e];
-              h[e] = (bf16_t)(v[e] * gn[e]);
-            }
-            *reinterpret_cast<f32x4*>(xr) = v;
-            *reinterpret_cast<bf16x4*>(act + act_index<true>(m, n, N)) = h;
-          }
-        }
-        ss += __shfl_xor(ss, 32, 64);
-        if (m < rows && lane < 32) nf.ssq[(size_t)(nt0 + i) * nf.ssq_stride + m] = ss;
-      }
-  } else if (EPI == EPI_SWIGLU) {
-    // acc[0] = gate tile, acc[1] = up tile of features [nt0*32, nt0*32+32); N is F here.
-#pragma unroll
-    for (int jq = 0; jq < JT; ++jq) {
-      const int j = j0 + jq;
-      const int m = (mt0 + j) * 32 + mloc;
-      float inv = 1.0f;
-      if (INTRA && nf.ssq != nullptr) {
+    for (int j = 0; j < MTC; ++j) {
+      inv[j] = 1.0f;
+      if (nf.ssq != nullptr) {                  // fused norm: a k-split partial scales like the sum
         float ssum = ssp[j * 32 + mloc];
 #pragma unroll
         for (int w = 1; w < KW; ++w) ssum += ssp[(w * MTC + j) * 32 + mloc];
-        inv = 1.0f / sqrtf(ssum * nf.inv_d + nf.eps);
+        inv[j] = 1.0f / sqrtf(__fmaf_rn(ssum, nf.inv_d, nf.eps));
       }
-      if (m < rows) {
+    }
+  }
+  if (EPI == EPI_F32) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int f = nt0 * 32 + 8 * q + nhalf;
-          bf16x4 v;
+    for (int i = 0; i < NT; ++i)
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const float g = res[0][jq][4 * q + e] * inv, u = res[NT - 1][jq][4 * q + e] * inv;
-            v[e] = (bf16_t)silu_mul(g, u);
-          }
-          *reinterpret_cast<bf16x4*>(act + act_index<true>(m, f, N)) = v;
+      for (int j = 0; j < MTC; ++j) {
+        const int m = (mt0 + j) * 32 + mloc;
+        if (m < rows) *reinterpret_cast<f32x4*>(out + (size_t)m * N + (nt0 + i) * 32 + 8 * wave + nhalf) = res[i][j] * inv[j];
+      }
+  } else if (EPI == EPI_RESID) {
+    // out = residual stream (updated in place), act = gain-scaled bf16 copy for the next GEMM
+#pragma unroll
+    for (int i = 0; i < NT; ++i) {
+      float ss[MTC];
+#pragma unroll
+      for (int j = 0; j < MTC; ++j) {
+        const int m = (mt0 + j) * 32 + mloc, n = (nt0 + i) * 32 + 8 * wave + nhalf;
+        const f32x4 v = xr[i][j] + res[i][j];
+        bf16x4 h;
+        ss[j] = 0.f;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          ss[j] = __fmaf_rn(v[e], v[e], ss[j]);      // (explicit: no instance may choose another contraction)
+          h[e] = (bf16_t)(v[e] * gn[i][e]);
         }
+        if (m < rows) {
+          *reinterpret_cast<f32x4*>(out + (size_t)m * N + n) = v;
+          *reinterpret_cast<bf16x4*>(act + act_index<true>(m, n, N)) = h;
+        }
+        ss[j] += __shfl_xor(ss[j], 32, 64);
+        if (lane < 32) ssp[((i * KW + wave) * MTC + j) * 32 + lane] = ss[j];
       }
+    }
+    // sum of squares of a row's 32 columns: the wavefronts' 8 columns each, in order
+    __syncthreads();
+    for (int t = threadIdx.x; t < NT * MTC * 32; t += 64 * KW) {
+      const int i = t / (MTC * 32), jm = t % (MTC * 32), m = mt0 * 32 + jm;
+      float s = ssp[i * KW * MTC * 32 + jm];
+#pragma unroll
+      for (int w = 1; w < KW; ++w) s += ssp[(i * KW + w) * MTC * 32 + jm];
+      if (m < rows) nf.ssq[(size_t)(nt0 + i) * nf.ssq_stride + m] = s;
+    }
+  } else {
+    // gate features in res[0] (HALF: of this tile's 16), up features in res[NT - 1] (up); N is F here
+#pragma unroll
+    for (int j = 0; j < MTC; ++j) {
+      const int m = (mt0 + j) * 32 + mloc, f = nt0 * (HALF ? 16 : 32) + 8 * wave + nhalf;
+      bf16x4 v;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float g = res[0][j][e] * inv[j], u = (HALF ? up[HALF ? j : 0][e] : res[NT - 1][j][e]) * inv[j];
+        v[e] = (bf16_t)silu_mul(g, u);
+      }
+      if (m < rows) *reinterpret_cast<bf16x4*>(act + act_index<true>(m, f, N)) = v;
     }
   }
 }
 
-// INTRA: the 4 wavefronts of a workgroup split the k range of one n-tile group (few n-tiles, or
-// fused SwiGLU); otherwise each wavefront owns its own n-tile group.  KH: k-tiles per fetch group, OCC:
+// The 4 wavefronts of a workgroup split the k range of one n-tile group.  D: k-tiles in flight with MT m-tiles, OCC:
 // workgroups per compute unit the registers are cut for.  No template argument but EPI changes a bit.
 // Grids.  NEAR (1-D): the m-groups of one weight tile re-read that tile, so they are placed 8
 // workgroup ids apart: same XCD (ids are dealt to the 8 XCDs in turn), same moment, one HBM read:
 // id = ((tile / 8) * m_groups + m_group) * 8 + tile % 8.  Else x = k slice (F32) or n-tile group, y = the
 // other, z = m-group: consecutive workgroups go to consecutive XCDs, so with 8 (4) slices every XCD
 // works on one (two) k slices and pulls only that slice of the activations into its L2.
-constexpr int fetch_depth(int kh, int full, int part) { return part >= full ? kh : (kh * full / part < 8 ? kh * full / part : 8); }
-// k-tiles that a wavefront with `len` of them requests in fetch groups of kh: groups go in pairs, the last one past the end too.
-__device__ inline int fetched(int len, int kh) { return (len + 2 * kh - 1) / (2 * kh) * (2 * kh); }
-template <int NT, int MT, int EPI, bool INTRA, int KH, int OCC, bool NEAR>
-__global__ __launch_bounds__(64 * KW4, OCC) void gemm_mfma_kernel(RowCtx rc, const bf16x8* __restrict__ x,
+// The leading arguments are what the first loads need: the compiler has them preloaded in scalar registers
+// (a chain of launches that read 8 MB each: 3.24 -> 2.88 us per launch).
+constexpr int ring_depth(int d, int full, int part) { return d * full / part < 16 ? d * full / part : 16; }
+template <int NT, int MT, int EPI, int D, int OCC, bool NEAR, bool HALF>
+__global__ __launch_bounds__(64 * KW4, OCC) void gemm_mfma_kernel(const int2* __restrict__ ctl, const bf16x8* __restrict__ x,
                                                                   const bf16x8* __restrict__ w0,
                                                                   const bf16x8* __restrict__ w1, float* __restrict__ out,
-                                                                  bf16_t* __restrict__ act, int N, int K, int ksplit,
-                                                                  size_t partial_stride, NormFuse nf) {
+                                                                  int max_rows, int N, int K, int ksplit,
+                                                                  bf16_t* __restrict__ act, size_t partial_stride, NormFuse nf) {
   constexpr int KW = KW4;
-  __shared__ float red[INTRA ? KW * MT * 16 * 64 : 1];
-  __shared__ float ssp[(INTRA && (EPI == EPI_SWIGLU || EPI == EPI_F32)) ? KW * MT * 32 : 1];
-  const int rows = rows_or_zero(rc);
-  constexpr bool SLICES = INTRA && EPI == EPI_F32;
+  constexpr int ROUND = NT * MT <= 2 ? NT * MT : (MT > 2 ? MT : 2);       // accumulator tiles that meet in LDS at once
+  __shared__ f32x4 red[KW * ROUND * 4 * 64];
+  __shared__ float ssp[(EPI == EPI_RESID ? NT : 1) * KW * MT * 32];
+  const int2 cv = *ctl;
+  const int rows = cv.y ? 0 : cv.x;             // none once the scheduler has ended the step
+  constexpr bool SLICES = EPI == EPI_F32;
   int bgrp = SLICES ? blockIdx.y : blockIdx.x, bz = blockIdx.z;
   const int sidx = SLICES ? blockIdx.x : 0;
   if (NEAR) {
-    const int m_groups = ceil_div(ceil_div(rc.max_rows, 32), MT);
+    const int m_groups = ceil_div(ceil_div(max_rows, 32), MT);
     const int rem = (int)blockIdx.x % (8 * m_groups);
     bgrp = ((int)blockIdx.x / (8 * m_groups)) * 8 + (rem & 7);
     bz = rem >> 3;
@@ -338,42 +319,112 @@ __global__ __launch_bounds__(64 * KW4, OCC) void gemm_mfma_kernel(RowCtx rc, con
   const int mt0 = bz * MT;
   if (mt0 * 32 >= rows) return;
   const int KT = K >> 4;
-  const int grp = INTRA ? bgrp : bgrp * KW + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int nt0 = (EPI == EPI_SWIGLU) ? grp : grp * NT;
-  if (nt0 >= (N >> 5)) return;
+  const int nt0 = (EPI == EPI_SWIGLU) ? bgrp : bgrp * NT;
+  if (nt0 >= (HALF ? N >> 4 : N >> 5)) return;
   const int k0 = (int)((long long)KT * sidx / ksplit), k1 = (int)((long long)KT * (sidx + 1) / ksplit);
   float* o = out ? out + sidx * partial_stride : nullptr;
   int mtc = ceil_div(rows, 32) - mt0;
   if (mtc > MT) mtc = MT;
-  // A last group of fewer m-tiles fetches more k-tiles at once in the same registers.  The 2 x 4 tile of the split-k
-  // projections has room for one more: used where less is then requested past the slice's end (16 k-tiles per wavefront
-  // and 64 rows: groups of 8 fetch 16, groups of 7 fetch 28; 2048 x 8192 in 8 slices 11.5 against 12.4 us per launch).
-  constexpr bool ONE_MORE = EPI == EPI_F32 && NT == 2 && OCC == 1;
+#define GROUP(MTC, DEPTH) gemm_group<NT, (MT >= MTC ? MTC : 1), EPI, KW, DEPTH, HALF>(w0, w1, x, KT, k0, k1, nt0, mt0, rows, N, o, act, red, ssp, nf)
+  constexpr int D1 = ring_depth(D, NT + MT, NT + 1), D2 = ring_depth(D, NT + MT, NT + 2), D3 = ring_depth(D, NT + MT, NT + 3);
   const int per = (k1 - k0 + KW - 1) / KW;
-#define GROUP(MTC, DEPTH) gemm_group<NT, (MT >= MTC ? MTC : 1), EPI, INTRA, KW, DEPTH>(w0, w1, x, KT, k0, k1, nt0, mt0, rows, N, o, act, red, ssp, nf)
-  constexpr int D1 = fetch_depth(KH, NT + MT, NT + 1), D2 = fetch_depth(KH, NT + MT, NT + 2), D3 = fetch_depth(KH, NT + MT, NT + 3);
+  // A last group of fewer m-tiles has more k-tiles in flight in the same registers; a short range, or one that D
+  // does not divide, fewer (what is requested past its end costs L1 bandwidth: 20 k-tiles 4.3 us with 16, 3.7 with 10).
+  auto asked = [&](int d) { return (per + d - 1) / d * d; };
   switch (mtc) {
-    case 1: GROUP(1, D1); break;
+    case 1:
+      if (per <= 4) GROUP(1, (D1 < 4 ? D1 : 4));
+      else if (per <= 7) GROUP(1, (D1 < 7 ? D1 : 7));
+      else if (per <= 10 || asked(10) < asked(D1)) GROUP(1, (D1 < 10 ? D1 : 10));
+      else GROUP(1, D1);
+      break;
     case 2:
-      if (ONE_MORE && fetched(per, D2 + 1) < fetched(per, D2)) GROUP(2, D2 + (ONE_MORE ? 1 : 0));
+      if (per <= 4) GROUP(2, (D2 < 4 ? D2 : 4));
+      else if (per <= 7) GROUP(2, (D2 < 7 ? D2 : 7));
       else GROUP(2, D2);
       break;
     case 3:
-      if (ONE_MORE && fetched(per, D3 + 1) < fetched(per, D3)) GROUP(3, D3 + (ONE_MORE ? 1 : 0));
+      if (MT == 3 && D == 5 && asked(4) < asked(5)) GROUP(3, 4);
       else GROUP(3, D3);
       break;
-    default: GROUP(MT, KH); break;
+    default: GROUP(MT, D); break;
   }
 #undef GROUP
 }
 
-// Split-k projections (qkv, down).  What bounds them: a compute unit alone pulls about 50 GB/s from
-// HBM, so the launch wants every unit busy with the same amount; beyond that the re-reads, the
-// activations once per n-tile group and the weights once per m-group, at L2 speed.  So the tile of a
-// workgroup grows with the rows.  us per launch, N x K in ksplit slices (rows: one side / the other):
-//   * one n-tile (two workgroups per unit) where two give less than half a workgroup per unit: 1152 x 896 in 4
-//     at 64 rows 4.3 / 2 x 4 tiles 6.1.
-//   * up to 128 rows 2 x 4, the weights once: 4096 x 14336 in 4 at 128 rows 33.5 / 2 x 3 in two m-groups 37.9.
+// LM head: each wavefront owns two weight tiles (64 columns, one record group) and all of k.
+constexpr int LM_MT = 4, LM_D = 10;
+template <int MTC, int D>
+__device__ inline void logits_group(const bf16x8* __restrict__ w0, const bf16x8* __restrict__ x, int KT, int nt0, int mt0,
+                                    int rows, int N, float* __restrict__ out, const GroupOut& go) {
+  const int lane = threadIdx.x & 63, mloc = lane & 31, nhalf = (lane >> 5) << 2;
+  f32x16 acc[2][MTC];
+  const bf16x8 *wp[2], *xp[MTC];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int nt = nt0 + i < (N >> 5) ? nt0 + i : (N >> 5) - 1;       // vocabulary of an odd number of tiles: read, never written
+    wp[i] = w0 + (size_t)nt * KT * 64 + lane;
+  }
+#pragma unroll
+  for (int j = 0; j < MTC; ++j) {
+    acc[0][j] = acc[1][j] = f32x16{};
+    xp[j] = x + (size_t)(mt0 + j) * KT * 64 + ((min((mt0 + j) * 32 + mloc, rows - 1) & 31) | (lane & 32));
+  }
+  accumulate<2, MTC, D>(wp, xp, 0, KT, acc, [] {});
+  // per row: the record of this wavefront's 64 output columns - maximum, its column, sum of
+  // exponentials.  With those the greedy sampler and its log-probabilities need no logits at all.
+  const bool two = nt0 + 1 < (N >> 5);
+#pragma unroll
+  for (int j = 0; j < MTC; ++j) {
+    float bv;
+    int bn;
+    double s = 0.0;
+    group64_record(acc[0][j], acc[1][j], two, nhalf, go.sum != nullptr, go.inv_t, bv, bn, s);
+    const int m = (mt0 + j) * 32 + mloc;
+    if (m >= rows) continue;
+    if (lane < 32) {
+      const size_t gi = (size_t)m * ((N + 63) >> 6) + (nt0 >> 1);
+      go.max[gi] = bv;
+      if (go.col) go.col[gi] = bn;
+      if (go.sum) go.sum[gi] = s;
+    }
+    if (out == nullptr) continue;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      if (nt0 + i >= (N >> 5)) continue;
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        *reinterpret_cast<f32x4*>(out + (size_t)m * N + (nt0 + i) * 32 + 8 * q + nhalf) =
+            f32x4{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+    }
+  }
+}
+__global__ __launch_bounds__(64 * KW4, 1) void gemm_logits_kernel(const int2* __restrict__ ctl, const bf16x8* __restrict__ x,
+                                                                  const bf16x8* __restrict__ w, float* __restrict__ out,
+                                                                  int N, int K, GroupOut go) {
+  const int2 cv = *ctl;
+  const int rows = cv.y ? 0 : cv.x, mt0 = blockIdx.z * LM_MT;
+  if (mt0 * 32 >= rows) return;
+  const int nt0 = ((int)blockIdx.x * KW4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) * 2, KT = K >> 4;
+  if (nt0 >= (N >> 5)) return;
+  const int mtc = ceil_div(rows, 32) - mt0;
+  if (mtc == 1) logits_group<1, ring_depth(LM_D, 2 + LM_MT, 3)>(w, x, KT, nt0, mt0, rows, N, out, go);
+  else if (mtc == 2) logits_group<2, ring_depth(LM_D, 2 + LM_MT, 4)>(w, x, KT, nt0, mt0, rows, N, out, go);
+  else if (mtc == 3) logits_group<3, ring_depth(LM_D, 2 + LM_MT, 5)>(w, x, KT, nt0, mt0, rows, N, out, go);
+  else logits_group<LM_MT, LM_D>(w, x, KT, nt0, mt0, rows, N, out, go);
+}
+
+// Split-k projections (qkv, down).  What bounds them: at few rows the latency of one pass (first loads, LDS, epilogue);
+// then a compute unit alone pulls about 50 GB/s from HBM, so the launch wants every unit busy with the same amount;
+// beyond that the re-reads, the activations once per n-tile group and the weights once per m-group, at L2 speed.  So the
+// tile of a workgroup grows with the rows.  us per launch, N x K in ksplit slices (rows: one side / the other):
+//   * matrices below 8 M elements, and odd n-tile counts: single tiles at three workgroups per unit up to 64 rows and, where
+//     they are at most 300 per m-tile, 128; then 1 x 2.  1152 x 896 in 4 at 96 rows 3.3 / 1 x 4 4.1, 896 x 4864 in 8 at 96, 128
+//     rows 6.1, 6.8 / 1 x 2 6.4, 7.6, 1792 x 1184 in 6 (336) at 96 rows 5.0 / 1 x 2 4.7, 2 x 4 7.0.  Beyond 128 rows pairs:
+//     2 x 2 for slices below 512, else 2 x 3: 1792 x 1184 at 192 rows 6.1 / 7.0, 896 x 4864 8.7 / 7.9.
+//   * larger ones, up to 64 rows 2 x 2 at two workgroups per unit: 6144 x 2560 in 2 at 32, 64 rows 9.1, 11.1 / 2 x 4 9.8, 11.9.
+//     96 and 128 rows 2 x 3: 12.4, 14.3 / 2 x 4 13.7, 15.0; but 2 x 4 for 128 rows of long slices that fill the units by
+//     themselves: 4096 x 14336 in 4 33.3 / 2 x 3 40.1.
 //   * slices below 1536 (few k-tiles per wavefront do not pay for the wider reduction): 2 x 3 at two workgroups
 //     per unit.  Slices of 1280 at 160 rows 17.8 / 4 x 3 18.5, of 1621 22.4 / 21.7; of 1024 at 288, 512 rows 24.9,
 //     38.4 / 30.8, 45.0.  For 7 and 8 m-tiles 4 x 4 down to slices of 1024: 19.5 / 22.5 (682: 16.5 / 16.5).
@@ -384,26 +435,32 @@ __global__ __launch_bounds__(64 * KW4, OCC) void gemm_mfma_kernel(RowCtx rc, con
 //     6144 x 4096 in 2 (96) 34.5 / 41.6.
 //   * beyond: 4 x 4 or 4 x 3, whichever has fewer m-tiles in its rounds of one workgroup per unit: 4096 x 14336 in 4
 //     at 512, 1024 rows 77, 144 / 94, 171; 10240 x 8192 in 1 at 512 rows 4 x 3 116 / 4 x 4 133.
-// Against two n-tiles x four m-tiles for all: 4096 x 14336 in 4 slices at 160, 192, 256, 384 rows 50.7, 51.5, 55.2, 79.3 /
-// 36.4, 38.7, 43.3, 66.3; 2560 x 9728 in 6: 26.9, 28.3, 32.3, 46.0 / 21.7, 22.9, 26.0, 39.1.
+// Fetch groups of k-tiles in alternation, a reduction that one wavefront per m-tile finished, epilogue operands requested after
+// it and no preloaded arguments / as here, at 1, 32, 96 rows: 1152 x 896 3.5, 3.7, 4.1 / 2.7, 2.9, 3.3; 1792 x 1184 5.8, 5.9, 8.0 /
+// 3.6, 4.0, 5.0; 6144 x 2560 10.6, 10.8, 14.3 / 8.3, 9.1, 12.4; 2560 x 9728 12.7, 12.9, 16.9 / 11.2, 11.7, 15.2.
 void launch_gemm_mfma(hipStream_t st, RowCtx rc, const bf16_t* x, const bf16_t* Wp, float* out, int N, int K,
                       int ksplit, size_t partial_stride, const float* ssq, int ssq_stride, float eps) {
   const NormFuse nf{nullptr, const_cast<float*>(ssq), ssq_stride, K >> 5, 1.0f / (float)K, eps, {}};
   const int n_tiles = N >> 5, m_tiles = ceil_div(rc.max_rows, 32), slice = K / ksplit, per_group = n_tiles / 4 * ksplit;
   const bool quads = n_tiles % 4 == 0, long_slices = quads && slice >= 1536;
   auto round_tiles = [&](int mt) { return ceil_div(ceil_div(m_tiles, mt) * per_group, 256) * mt; };
-#define GEMM_F32(NT, MT, KH, OCC)                                                                                       \
-  hipLaunchKernelGGL((gemm_mfma_kernel<NT, MT, EPI_F32, true, KH, OCC, false>),                                         \
-                     dim3(ksplit, n_tiles / NT, ceil_div(m_tiles, MT)), dim3(64 * KW4), 0, st, rc,                      \
-                     reinterpret_cast<const bf16x8*>(x), reinterpret_cast<const bf16x8*>(Wp), nullptr, out, nullptr, N, \
-                     K, ksplit, partial_stride, nf)
-  if (n_tiles % 2 != 0 || (n_tiles / 2) * ksplit < 128) GEMM_F32(1, 4, 3, 2);
-  else if (m_tiles <= 4 || (m_tiles == 5 && long_slices && per_group <= 96)) GEMM_F32(2, 4, 5, 1);
-  else if (m_tiles <= 6 && long_slices) GEMM_F32(4, 3, 3, 1);
-  else if ((m_tiles == 7 || m_tiles == 8) && quads && slice >= 1024) GEMM_F32(4, 4, 2, 1);
-  else if (!long_slices || (m_tiles <= 12 && per_group < 112)) GEMM_F32(2, 3, 3, 2);
-  else if (m_tiles <= 12 || round_tiles(3) < round_tiles(4)) GEMM_F32(4, 3, 3, 1);
-  else GEMM_F32(4, 4, 2, 1);
+#define GEMM_F32(NT, MT, D, OCC)                                                                                        \
+  hipLaunchKernelGGL((gemm_mfma_kernel<NT, MT, EPI_F32, D, OCC, false, false>),                                         \
+                     dim3(ksplit, n_tiles / NT, ceil_div(m_tiles, MT)), dim3(64 * KW4), 0, st, rc.ctl,                  \
+                     reinterpret_cast<const bf16x8*>(x), reinterpret_cast<const bf16x8*>(Wp), nullptr, out,             \
+                     rc.max_rows, N, K, ksplit, nullptr, partial_stride, nf)
+  const bool pairs = n_tiles % 2 == 0, small = (long long)N * K < (8ll << 20);
+  if (!pairs || (small && m_tiles <= 4)) {
+    if (m_tiles <= 2 || (m_tiles <= 4 && n_tiles * ksplit <= 300)) GEMM_F32(1, 1, 12, 3);
+    else GEMM_F32(1, 2, 8, 3);
+  } else if (m_tiles <= 2 || (small && slice < 512)) GEMM_F32(2, 2, 6, 2);
+  else if ((m_tiles == 4 && slice >= 1536 && (n_tiles / 2) * ksplit >= 224) || (m_tiles == 5 && long_slices && per_group <= 96)) GEMM_F32(2, 4, 10, 1);
+  else if (m_tiles <= 4 || small) GEMM_F32(2, 3, 5, 2);
+  else if (m_tiles <= 6 && long_slices) GEMM_F32(4, 3, 6, 1);
+  else if ((m_tiles == 7 || m_tiles == 8) && quads && slice >= 1024) GEMM_F32(4, 4, 4, 1);
+  else if (!long_slices || (m_tiles <= 12 && per_group < 112)) GEMM_F32(2, 3, 5, 2);
+  else if (m_tiles <= 12 || round_tiles(3) < round_tiles(4)) GEMM_F32(4, 3, 6, 1);
+  else GEMM_F32(4, 4, 4, 1);
 #undef GEMM_F32
 }
 
@@ -411,38 +468,44 @@ int lmhead_group_cols() { return 64; }
 
 void launch_gemm_mfma_logits(hipStream_t st, RowCtx rc, const bf16_t* x, const bf16_t* Wp, float* logits,
                              const GroupOut& go, int V, int K) {
-  constexpr int MT = 4;
-  const int n_tiles = V >> 5;
-  dim3 grid(ceil_div(ceil_div(n_tiles, 2), KW4), 1, ceil_div(ceil_div(rc.max_rows, 32), MT));
-  hipLaunchKernelGGL((gemm_mfma_kernel<2, MT, EPI_LOGITS, false, 5, 1, false>), grid, dim3(64 * KW4), 0, st, rc,
-                     reinterpret_cast<const bf16x8*>(x), reinterpret_cast<const bf16x8*>(Wp), nullptr, logits, nullptr,
-                     V, K, 1, (size_t)0, NormFuse{nullptr, nullptr, 0, 0, 0.f, 0.f, go});
+  dim3 grid(ceil_div(ceil_div(V >> 5, 2), KW4), 1, ceil_div(ceil_div(rc.max_rows, 32), LM_MT));
+  hipLaunchKernelGGL(gemm_logits_kernel, grid, dim3(64 * KW4), 0, st, rc.ctl, reinterpret_cast<const bf16x8*>(x),
+                     reinterpret_cast<const bf16x8*>(Wp), logits, V, K, go);
 }
 
-// Fused gate/up, rows below what the LDS-tiled kernel takes (see forward()).  Workgroups of few row tiles
-// at three (two) per compute unit: an MLP of 9728 features is 304 workgroups, which at one per unit ran in two
-// rounds.  us per launch, four m-tiles at one per unit / as here: 2560 x 9728 at 32, 64, 96 rows 30.7,
-// 37.3, 42.5 / 27.3, 32.8, 35.1, at 320, 384 rows 74.2, 81.1 / 59.4, 69.0; 4096 x 14336 at 32, 64 rows
-// 48.4, 57.1 / 45.5, 53.5; 896 x 4864 at 64, 96, 192, 256 rows 9.9, 11.1, 15.2, 20.1 / 9.9, 10.2, 12.6, 14.8.
+// Fused gate/up, rows below what the LDS-tiled kernel takes (see forward()).  Row tiles and workgroups per unit so that the
+// launch comes close to one even round over the 256 units.  us per launch, F x K (rows: one side / the other):
+//   * one m-tile: tiles of 16 gate and 16 up features where whole ones fill at most half of a round, the first or the last:
+//     3104 x 1184 (97 tiles) at 1, 32 rows 5.5, 6.1 / 6.9, 7.6; 9728 x 2560 (304) at 1, 16, 32 rows 21.3, 22.1, 25.0 / 23.5, 24.0,
+//     25.6; where whole ones fill more, the activations read twice as often cost more: 5120 x 4096 (160) 21.5, 25.9 / 18.7, 21.2.
+//   * several m-tiles that together are no more than a round: one each.  3072 x 2048 (96) at 64 rows 9.8 / 2 x 2 12.4.
+//   * else 2 x 2: 4864 x 896 at 64 rows two workgroups per unit 8.1 / three 8.7.  Four m-tiles at one per unit against
+//     three: 9728 x 2560 at 64, 96 rows 37.3, 42.5 / 30.7, 33.4.
 // NEAR where the weight tiles alone are more than a round of one workgroup per unit, and where their number is no multiple
 // of 8, which in grid order puts the row groups of one tile on different XCDs: 3104 x 1184 (97 tiles) at 160, 256, 512 rows
 // 12.6, 14.7, 24.9 / 10.6, 11.3, 17.5; 4864 x 896 (152 tiles) at 160, 256, 512 rows 10.6, 13.2, 18.8, NEAR 10.9, 14.6, 20.5.
+// Before the kernel's ring, quarter epilogues and preloaded arguments / now, at 1, 32, 64 rows: 4864 x 896 7.5, 7.5, 8.9 / 5.8, 6.3,
+// 7.8; 3104 x 1184 8.8, 8.8, 10.5 / 5.4, 6.1, 7.7; 9728 x 2560 26.6, 26.6, 31.8 / 21.2, 24.9, 30.7 (a plain read of its 100 MB: 18).
 void launch_gemm_mfma_swiglu(hipStream_t st, RowCtx rc, const bf16_t* x, const bf16_t* Wg, const bf16_t* Wu,
                              bf16_t* act, int F, int K, const float* ssq, int ssq_stride, float eps) {
   const int n_tiles = F >> 5, m_tiles = ceil_div(rc.max_rows, 32);
   NormFuse nf{nullptr, const_cast<float*>(ssq), ssq_stride, K >> 5, 1.0f / (float)K, eps, {}};
-#define GEMM_SW(MT, KH, OCC, NEAR, grid)                                                                               \
-  hipLaunchKernelGGL((gemm_mfma_kernel<2, MT, EPI_SWIGLU, true, KH, OCC, NEAR>), grid, dim3(64 * KW4), 0, st, rc,      \
-                     reinterpret_cast<const bf16x8*>(x), reinterpret_cast<const bf16x8*>(Wg),                          \
-                     reinterpret_cast<const bf16x8*>(Wu), nullptr, act, F, K, 1, (size_t)0, nf)
-  const int tiles8 = ceil_div(n_tiles, 8) * 8;
-  if (m_tiles <= 1) GEMM_SW(1, 4, 3, false, dim3(n_tiles));
-  else if (n_tiles <= 256 && (m_tiles <= 2 || n_tiles % 8 == 0)) GEMM_SW(2, 2, 3, false, dim3(n_tiles, 1, ceil_div(m_tiles, 2)));
-  else if (n_tiles <= 256 || m_tiles <= 3) GEMM_SW(2, 2, 3, true, dim3(tiles8 * ceil_div(m_tiles, 2)));
-  else GEMM_SW(3, 3, 2, true, dim3(tiles8 * ceil_div(m_tiles, 3)));
+#define GEMM_SW(NT, MT, D, OCC, NEAR, grid)                                                                            \
+  hipLaunchKernelGGL((gemm_mfma_kernel<NT, MT, EPI_SWIGLU, D, OCC, NEAR, NT == 1>), grid, dim3(64 * KW4), 0, st,       \
+                     rc.ctl, reinterpret_cast<const bf16x8*>(x), reinterpret_cast<const bf16x8*>(Wg),                  \
+                     reinterpret_cast<const bf16x8*>(Wu), nullptr, rc.max_rows, F, K, 1, act, (size_t)0, nf)
+  const int tiles8 = ceil_div(n_tiles, 8) * 8, wgs = n_tiles * m_tiles;
+  if (wgs <= 128 || (m_tiles == 1 && (n_tiles - 1) % 256 < 128)) GEMM_SW(1, 1, 10, 3, false, dim3(2 * n_tiles, 1, m_tiles));
+  else if (m_tiles == 1 || (m_tiles <= 8 && wgs <= 256)) GEMM_SW(2, 1, 8, 3, false, dim3(n_tiles, 1, m_tiles));
+  else if (m_tiles <= 2 && n_tiles <= 256) GEMM_SW(2, 2, 8, 2, false, dim3(n_tiles));
+  else if (n_tiles <= 256 && n_tiles % 8 == 0) GEMM_SW(2, 2, 4, 3, false, dim3(n_tiles, 1, ceil_div(m_tiles, 2)));
+  else if (n_tiles <= 256 || m_tiles <= 3) GEMM_SW(2, 2, 4, 3, true, dim3(tiles8 * ceil_div(m_tiles, 2)));
+  else GEMM_SW(2, 3, 5, 2, true, dim3(tiles8 * ceil_div(m_tiles, 3)));
 #undef GEMM_SW
 }
 
+// (before the epilogue's operands were requested with the first k-tiles / now, at 1, 32, 96 rows: 896 x 896 4.0, 4.0, 4.0 /
+// 3.3, 3.5, 3.6; 1184 x 1280 6.4, 6.4, 6.3 / 3.7, 4.1, 4.1; 2560 x 4096 12.2, 12.2, 11.4 / 8.8, 11.4, 10.9)
 // x_res += x . W^T (whole k range per workgroup, no partials); act = bf16(x_res * gain) in the
 // fragment order of the next GEMM; ssq[n_tile][row] = sum of squares of the tile's 32 columns.
 // As many workgroups as fit one per compute unit (256): few rows per workgroup where there are few
@@ -459,11 +522,11 @@ void launch_gemm_mfma_resid(hipStream_t st, RowCtx rc, const bf16_t* x, const bf
                             const float* gain, bf16_t* act, float* ssq, int ssq_stride, int N, int K) {
   const int n_tiles = N >> 5, m_tiles = ceil_div(rc.max_rows, 32);
   const NormFuse nf{gain, ssq, ssq_stride, 0, 0.f, 0.f, {}};
-#define GEMM_RESID(NT, MT, KH, OCC)                                                                                     \
-  hipLaunchKernelGGL((gemm_mfma_kernel<NT, MT, EPI_RESID, true, KH, OCC, true>),                                        \
-                     dim3(ceil_div(n_tiles / NT, 8) * 8 * ceil_div(m_tiles, MT)), dim3(64 * KW4), 0, st, rc,            \
-                     reinterpret_cast<const bf16x8*>(x), reinterpret_cast<const bf16x8*>(Wp), nullptr, x_res, act, N, K, \
-                     1, (size_t)0, nf)
+#define GEMM_RESID(NT, MT, D, OCC)                                                                                      \
+  hipLaunchKernelGGL((gemm_mfma_kernel<NT, MT, EPI_RESID, D, OCC, true, false>),                                        \
+                     dim3(ceil_div(n_tiles / NT, 8) * 8 * ceil_div(m_tiles, MT)), dim3(64 * KW4), 0, st, rc.ctl,        \
+                     reinterpret_cast<const bf16x8*>(x), reinterpret_cast<const bf16x8*>(Wp), nullptr, x_res,           \
+                     rc.max_rows, N, K, 1, act, (size_t)0, nf)
   const int most = 256 / n_tiles > 0 ? 256 / n_tiles : 1;                // groups of rows
   const int groups = ceil_div(m_tiles, ceil_div(m_tiles, most));
   int mt = ceil_div(m_tiles, most);
@@ -471,11 +534,11 @@ void launch_gemm_mfma_resid(hipStream_t st, RowCtx rc, const bf16_t* x, const bf
   if (groups == m_tiles || (groups == 1 && m_tiles == 3 && n_tiles * 3 <= 512)) mt = 1;
   const int pairs = ceil_div(n_tiles / 2, 8) * ceil_div(m_tiles, 3), singles = ceil_div(n_tiles, 8) * ceil_div(m_tiles, 4);   // workgroups per XCD
   if (mt > 4 && (n_tiles % 2 != 0 || (m_tiles > 8 && pairs > 32 && singles >= 48 && singles <= 64))) mt = 4;
-  if (mt == 1) GEMM_RESID(1, 1, 8, 1);
-  else if (mt == 2) GEMM_RESID(1, 2, 4, 2);
-  else if (mt == 3) GEMM_RESID(1, 3, 4, 2);
-  else if (mt == 4) GEMM_RESID(1, 4, 3, 2);
-  else GEMM_RESID(2, 3, 4, 1);
+  if (mt == 1) GEMM_RESID(1, 1, 16, 1);
+  else if (mt == 2) GEMM_RESID(1, 2, 8, 2);
+  else if (mt == 3) GEMM_RESID(1, 3, 8, 2);
+  else if (mt == 4) GEMM_RESID(1, 4, 6, 2);
+  else GEMM_RESID(2, 3, 8, 1);
 #undef GEMM_RESID
 }
 

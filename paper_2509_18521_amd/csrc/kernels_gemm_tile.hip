@@ -373,7 +373,7 @@ __device__ __forceinline__ void tile_dma_body(RowCtx rc, const bf16x8* __restric
       float ssum = sw[0];
 #pragma unroll
       for (int w = 1; w < 4; ++w) ssum += sw[w];
-      row_scale[rl] = 1.0f / sqrtf(ssum * tn.inv_d + tn.eps);
+      row_scale[rl] = 1.0f / sqrtf(__fmaf_rn(ssum, tn.inv_d, tn.eps));
     }
     __syncthreads();
   }

@@ -76,3 +76,11 @@ def test_a_row_keeps_its_bits_in_the_output_projection():
 def test_a_row_keeps_its_bits_in_the_lm_head(vocab, sizes):
     """129 groups of 256 columns: the 256-row tile on 8 wavefronts from 129 rows; 33 groups: never."""
     check_bits(ai.ModelShape(1, 160, 2, 1, 64, 96, vocab), 5, sizes)
+
+
+@pytest.mark.parametrize("d_model,n_q,n_kv,head_dim,d_ffn,sizes", [
+    (128, 4, 2, 32, 1024, (40, 64, 100, 130, 250, 290)),      # gate/up on half and single tiles; k ranges of 2 k-tiles
+    (416, 5, 1, 64, 1056, (33, 65, 97, 129, 260)),            # odd counts of n-tiles everywhere
+    (1280, 20, 4, 64, 2080, (33, 65, 97, 129, 193, 260))])    # 65 feature tiles; split-k of 2 and 3 m-tiles per workgroup
+def test_a_row_keeps_its_bits_in_small_matrices(d_model, n_q, n_kv, head_dim, d_ffn, sizes):
+    check_bits(ai.ModelShape(1, d_model, n_q, n_kv, head_dim, d_ffn, 2080), 5, sizes)
