@@ -29,6 +29,8 @@
 // KV page layout (written by rope_append_kernel or here, mode 1), per (page, KV head):
 //   K: MFMA A-fragment order  [d/32][lane = t + 16*((d%32)/8)][d%8]   -> 1 KiB coalesced loads
 //   V: transposed             [d][t]                                 -> 8-byte loads, 512 B/wave coalesced
+#include <type_traits>
+
 #include "kernels.h"
 
 namespace april {
@@ -47,14 +49,15 @@ namespace april {
 // end on each of the three wide configurations (before the work list, on a grid launch, 2048-token
 // splits cost 4.5 % on a ragged batch).
 constexpr int att_split(int dh) { return dh == 64 ? ATT_SPLIT_64 : (dh == 128 ? ATT_SPLIT_128 : 1024); }
-// wavefronts per workgroup (8 for head_dim <= 64 was measured: 11.8 us against 10.6 us per launch)
+// wavefronts per workgroup (8 for head_dim 64: one row of 1000 tokens 7.2 against 7.5 us, but 192 rows of 40 tokens 11.0 against 6.7)
 #ifndef ATT_WAVES_128
 #define ATT_WAVES_128 4
 #endif
 constexpr int att_waves(int dh, bool fused) { return dh == 128 ? ATT_WAVES_128 : 4; }
 
-struct AttnFuse {              // inputs of the fused rotary + append (FUSED only)
-  const float* qkv;            // fp32 [n_partials][rows][(Hq + 2 Hkv) * dh] split-K partials of the QKV GEMM
+// q_src of the kernel: FUSED: the QKV GEMM's split-K partials, fp32 [n_partials][rows][(Hq + 2 Hkv) * dh]; else
+// the rotated queries, fp32 [rows][Hq * dh].
+struct AttnFuse {              // the rest of the fused rotary + append (FUSED only)
   int n_partials;
   size_t partial_stride;
   const float* rope_cos;       // [pos][dh/2]
@@ -63,9 +66,9 @@ struct AttnFuse {              // inputs of the fused rotary + append (FUSED onl
 
 template <int DH, bool FUSED>
 __global__ __launch_bounds__(64 * att_waves(DH, FUSED)) __attribute__((amdgpu_waves_per_eu(2))) void attn_decode_kernel(
-    RowCtx rc, int row_base, Slots s, const float* __restrict__ q_rot, bf16_t* kv_pool, KVLayout L, int layer,
-    int Hq, bf16_t* __restrict__ out, float* __restrict__ ws, int max_splits, AttnFuse fz,
-    const int4* __restrict__ items) {
+    const int4* __restrict__ items, const int2* __restrict__ ctl_p, const int* __restrict__ block_table,
+    const float* __restrict__ q_src, bf16_t* kv_pool, int max_blocks, int Hkv, int Hq, int layer, RowCtx rc, int row_base,
+    KVLayout L, bf16_t* __restrict__ out, float* __restrict__ ws, int max_splits, AttnFuse fz) {
   constexpr int KC = DH / 32;      // k-chunks of the QK product
   constexpr int DT = DH / 16;      // dim tiles of the PV product
   constexpr int REC = 32 + 16 * DH;   // floats of one partial result: m[16], l[16], o[16][DH]
@@ -73,7 +76,8 @@ __global__ __launch_bounds__(64 * att_waves(DH, FUSED)) __attribute__((amdgpu_wa
   constexpr int RS = DH + 4;          // padded row stride of O in LDS
   constexpr int LREC = 32 + 16 * RS;
   __shared__ float lds[ATT_WAVES * LREC];
-  __shared__ bf16_t s_knew[DH], s_vnew[DH];
+  constexpr int QS = DH + 8;          // padded row stride of the rotated queries
+  __shared__ __align__(16) bf16_t s_q[FUSED ? 16 * QS : 8], s_knew[DH], s_vnew[DH];
   // Workgroup ids are dealt to the 8 XCDs in turn, so with a row count that is a multiple of 8 the
   // plain mapping would put every (KV head, split) of a row on one XCD and a long row would
   // overload it.  Rotating the row index by the other two coordinates spreads a row's
@@ -86,11 +90,10 @@ __global__ __launch_bounds__(64 * att_waves(DH, FUSED)) __attribute__((amdgpu_wa
   // does not have, and the KV heads of one item go to different XCDs.
   int kvh, split, wr, slot, pos;
   if (items != nullptr) {
-    const int nkv = L.n_kv_heads;
-    const int item = (int)blockIdx.x / nkv;
-    kvh = (int)blockIdx.x - item * nkv;
+    const int item = (int)blockIdx.x / Hkv;
+    kvh = (int)blockIdx.x - item * Hkv;
     const int4 head = items[0], it = items[1 + item];
-    const int2 ctl = *rc.ctl;
+    const int2 ctl = *ctl_p;
     if (ctl.y || item >= head.x) return;
     wr = __builtin_amdgcn_readfirstlane(it.x);
     split = __builtin_amdgcn_readfirstlane(it.y);
@@ -111,7 +114,7 @@ __global__ __launch_bounds__(64 * att_waves(DH, FUSED)) __attribute__((amdgpu_wa
   const int n_splits = (ctx + ATT_SPLIT - 1) / ATT_SPLIT;
   if (split >= n_splits) return;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), hh = lane & 15, g = lane >> 4;
-  const int Hkv = L.n_kv_heads, G = Hq / Hkv;
+  const int G = Hq / Hkv;
   const int t_begin = split * ATT_SPLIT, t_end = min(ctx, t_begin + ATT_SPLIT);
   const int n_tiles = (t_end - t_begin + 31) >> 5;
   const int n_pages = (t_end - t_begin + 15) >> 4;
@@ -121,7 +124,7 @@ __global__ __launch_bounds__(64 * att_waves(DH, FUSED)) __attribute__((amdgpu_wa
 
   // page ids of this split: lane i holds page i (one vector load instead of a scalar
   // load per tile inside the loop)
-  const int* bt = s.block_table + (size_t)slot * s.max_blocks + (t_begin >> 4);
+  const int* bt = block_table + (size_t)slot * max_blocks + (t_begin >> 4);
   int my_page[PR];
 #pragma unroll
   for (int q = 0; q < PR; ++q) { const int i = q * 64 + lane; my_page[q] = bt[i < n_pages ? i : n_pages - 1]; }
@@ -148,136 +151,109 @@ __global__ __launch_bounds__(64 * att_waves(DH, FUSED)) __attribute__((amdgpu_wa
     }
   };
 
-  constexpr bool DEEP = DH <= 64;              // two tiles in flight behind the one being used
-  bf16x8 kf[2][KC], km[DEEP ? 2 : 1][KC];
-  bf16x4 vf[2][DT], vm[DEEP ? 2 : 1][DT];
+  // This wavefront's tiles wave, wave + ATT_WAVES, ...: R of them in flight, tile i in register slot i % R.
+  constexpr int R = 2;         // (head_dim 64, one row of 400 tokens: 5.45 us with 2, 5.85 with 3; 128 has no registers for 3)
+  bf16x8 kf[R][2][KC];
+  bf16x4 vf[R][2][DT];
+  const int cnt = (n_tiles - wave + ATT_WAVES - 1) / ATT_WAVES;      // (none: a clamped tile is requested, never used)
+  auto request = [&](int u, int i) { load_tile(min(wave + i * ATT_WAVES, n_tiles - 1), kf[u], vf[u]); };
   auto first_tiles = [&]() {
-    load_tile(wave < n_tiles ? wave : n_tiles - 1, kf, vf);
-    if constexpr (DEEP) {
-      // (an array reference of the right shape for the lambda)
-      auto& km2 = reinterpret_cast<bf16x8 (&)[2][KC]>(km);
-      auto& vm2 = reinterpret_cast<bf16x4 (&)[2][DT]>(vm);
-      load_tile(wave + ATT_WAVES < n_tiles ? wave + ATT_WAVES : n_tiles - 1, km2, vm2);
-    }
+    request(0, 0);
+#pragma unroll
+    for (int u = 1; u < R; ++u)
+      if (u < cnt) request(u, u);
   };
 
-  // Q^T fragments: lane holds q[head hh][32c + 8g .. +7]; heads beyond the group read
-  // the group's last head and are zeroed.
+  // Q^T fragments: lane holds q[head hh][32c + 8g .. +7]; heads beyond the group are zero.
   constexpr int HALF = DH / 2;
   const bool last_split = split == n_splits - 1;
   bf16x8 qf[KC];
   if (FUSED) {
-    // Order of requests: (1) the page ids (above), (2) everything that depends on the row only -
-    // the q partials, the rotary table, for the owner of the new token also its k / v partials -
-    // (3) the first KV tiles, which need the page ids.  Loads complete in order, so waiting for
-    // (2) does not wait for (3), and the rotation arithmetic runs while the tiles arrive.
-    // Narrow heads: (2) and (3) fit the register file together.  Wide heads: (2) for every k-chunk
-    // at once fits only while the tile registers are still free, so the rotation runs before (3)
-    // is requested - one round trip for all of (2) instead of one per k-chunk and partial.
-    constexpr bool ALL = true;
-    constexpr bool TILES_FIRST = DH <= 64;
-    constexpr int QC = ALL ? KC : 1;
-    constexpr int QB = DH <= 64 ? 4 : 2;        // partials requested together
-    const int hq = hh < G ? hh : G - 1;
-    const int ncol = (Hq + 2 * Hkv) * DH;
-    const float* qsrc = fz.qkv + (size_t)r * ncol + (size_t)(kvh * G + hq) * DH;
-    const float* ksrc = fz.qkv + (size_t)r * ncol + (size_t)(Hq + kvh) * DH;
-    const float* vsrc = fz.qkv + (size_t)r * ncol + (size_t)(Hq + Hkv + kvh) * DH;
+    // The workgroup sums the partials of its query heads and rotates them, one pair (i, i + DH / 2) of a head per
+    // thread, and with the last split the new token's key (rotated) and value too: "heads" G and G + 1.  Everyone
+    // then reads the bf16 queries from LDS.  Loads complete in order, and the partials are requested before the
+    // first tiles, which need the page ids: the rotation runs while the tiles arrive.  (With every wavefront summing
+    // all of its lanes' queries itself, in 16-byte pieces of 14 rows, the L1 traffic and the round trips of more than
+    // four partials were most of a short row's time.  Rows of 40 tokens, 14 + 2 heads of 64 in 4 partials, 20 + 4 in 6,
+    // 32 + 8 of 128 in 2, us per launch before / now: 1 row 5.2, 6.8, 6.0 / 4.3, 4.4, 5.2; 96 rows 5.6, 10.7, 13.6 /
+    // 4.7, 5.8, 11.9.)
+    constexpr int THREADS = 64 * ATT_WAVES, U = 2;
+    const int ncol = (Hq + 2 * Hkv) * DH, n_pairs = (last_split ? G + 2 : G) * HALF;
+    const float* src = q_src + (size_t)r * ncol;
     const float* cs = fz.rope_cos + (size_t)pos * HALF;
     const float* sn = fz.rope_sin + (size_t)pos * HALF;
-    const bool owner = last_split && wave == 0;         // computes and stores the new key / value
-    f32x4 la[QC][QB][2], lb[QC][QB][2], c4[QC][2], s4[QC][2];
-    float nka[QB], nkb[QB], nvv[QB], ncs = 0.f, nsn = 0.f;
-    auto request_q = [&](int c, int slot_c, int p0) {
-      const int d0 = 32 * c + 8 * g;            // 8 consecutive dims, all in the same half
-      const int i0 = d0 < HALF ? d0 : d0 - HALF;
+    const int tin = pos & 15, np = fz.n_partials, new_page = bt[(pos - t_begin) >> 4];     // (the last split's only)
+    constexpr int QB = 8;                     // partials requested together
+    auto trip = [&](int p0, auto first) {
+      const float* col[U];
+      float cv[U], sv[U], a[U], b[U], va[U][QB], vb[U][QB];
+      int hd[U], ii[U];
+      auto load = [&](int q0) {
 #pragma unroll
-      for (int u = 0; u < QB; ++u) {
-        const int p = p0 + u < fz.n_partials ? p0 + u : fz.n_partials - 1;
-        const float* q = qsrc + p * fz.partial_stride;
-        la[slot_c][u][0] = *reinterpret_cast<const f32x4*>(q + i0);
-        la[slot_c][u][1] = *reinterpret_cast<const f32x4*>(q + i0 + 4);
-        lb[slot_c][u][0] = *reinterpret_cast<const f32x4*>(q + i0 + HALF);
-        lb[slot_c][u][1] = *reinterpret_cast<const f32x4*>(q + i0 + HALF + 4);
+        for (int q = 0; q < QB; ++q)
+          if (q0 + q < np) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+              const float* c = col[u] + (size_t)(q0 + q) * fz.partial_stride;
+              va[u][q] = c[0]; vb[u][q] = c[HALF];
+            }
+          }
+      };
+      auto add = [&](int q0) {                // in the order p = 0, 1, ...
+#pragma unroll
+        for (int q = 0; q < QB; ++q)
+          if (q0 + q < np) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) { a[u] += va[u][q]; b[u] += vb[u][q]; }
+          }
+      };
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int e = min(p0 + u * THREADS + (int)threadIdx.x, n_pairs - 1);
+        hd[u] = e / HALF; ii[u] = e % HALF;
+        col[u] = src + (size_t)(hd[u] < G ? kvh * G + hd[u] : Hq + (hd[u] - G) * Hkv + kvh) * DH + ii[u];
+        cv[u] = cs[ii[u]]; sv[u] = sn[ii[u]];
+        a[u] = b[u] = 0.f;
       }
-      if (p0 == 0) {
-        c4[slot_c][0] = *reinterpret_cast<const f32x4*>(cs + i0);
-        c4[slot_c][1] = *reinterpret_cast<const f32x4*>(cs + i0 + 4);
-        s4[slot_c][0] = *reinterpret_cast<const f32x4*>(sn + i0);
-        s4[slot_c][1] = *reinterpret_cast<const f32x4*>(sn + i0 + 4);
+      load(0);
+      __builtin_amdgcn_sched_barrier(0);
+      if (first) first_tiles();
+      __builtin_amdgcn_sched_barrier(0);
+      add(0);
+      for (int q0 = QB; q0 < np; q0 += QB) { load(q0); add(q0); }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (p0 + u * THREADS + (int)threadIdx.x >= n_pairs) continue;
+        const int i = ii[u];
+        const bf16_t ra = (bf16_t)rope_first(a[u], b[u], cv[u], sv[u]), rb = (bf16_t)rope_second(a[u], b[u], cv[u], sv[u]);
+        if (hd[u] < G) {
+          s_q[hd[u] * QS + i] = ra;
+          s_q[hd[u] * QS + i + HALF] = rb;
+        } else {
+          // the new token, to LDS and to its page
+          const bool key = hd[u] == G;
+          const bf16_t x = key ? ra : (bf16_t)a[u], y = key ? rb : (bf16_t)b[u];
+          bf16_t* dst = key ? s_knew : s_vnew;
+          dst[i] = x;
+          dst[i + HALF] = y;
+          kv_pool[L.at(layer, key ? 0 : 1, new_page, kvh, tin, i)] = x;
+          kv_pool[L.at(layer, key ? 0 : 1, new_page, kvh, tin, i + HALF)] = y;
+        }
       }
     };
-    // new token, dim d = lane (+64 for the second pass of wide heads): pair index and partials
-    auto request_kv = [&](int d, int p0) {
-      const int i = d < HALF ? d : d - HALF;
-#pragma unroll
-      for (int u = 0; u < QB; ++u) {
-        const size_t po = (size_t)(p0 + u < fz.n_partials ? p0 + u : fz.n_partials - 1) * fz.partial_stride;
-        nka[u] = ksrc[po + i]; nkb[u] = ksrc[po + i + HALF]; nvv[u] = vsrc[po + d];
-      }
-      if (p0 == 0) { ncs = cs[i]; nsn = sn[i]; }
-    };
-    if constexpr (ALL) {
-#pragma unroll
-      for (int c = 0; c < KC; ++c) request_q(c, c, 0);
-      if (owner && lane < DH) request_kv(lane, 0);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    if constexpr (TILES_FIRST) {
-      first_tiles();
-      __builtin_amdgcn_sched_barrier(0);
-    }
+    trip(0, std::true_type{});
+    for (int p0 = U * THREADS; p0 < n_pairs; p0 += U * THREADS) trip(p0, std::false_type{});
+    __syncthreads();
 #pragma unroll
     for (int c = 0; c < KC; ++c) {
-      const int sc = ALL ? c : 0;
-      const bool lo = 32 * c + 8 * g < HALF;
-      f32x4 a[2] = {f32x4{}, f32x4{}}, b[2] = {f32x4{}, f32x4{}};
-      // partials are added in the order p = 0, 1, ... (as rope_append_kernel does); four at a
-      // time are requested together so that the additions do not serialise the loads
-      for (int p0 = 0; p0 < fz.n_partials; p0 += QB) {
-        if (!ALL || p0 > 0) request_q(c, sc, p0);
-#pragma unroll
-        for (int u = 0; u < QB; ++u)
-          if (p0 + u < fz.n_partials) { a[0] += la[sc][u][0]; a[1] += la[sc][u][1]; b[0] += lb[sc][u][0]; b[1] += lb[sc][u][1]; }
-      }
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const float av = a[j >> 2][j & 3], bv = b[j >> 2][j & 3], cv = c4[sc][j >> 2][j & 3], sv2 = s4[sc][j >> 2][j & 3];
-        const float rot = lo ? rope_first(av, bv, cv, sv2) : rope_second(av, bv, cv, sv2);
-        qf[c][j] = hh < G ? (bf16_t)rot : (bf16_t)0.f;
-      }
+      qf[c] = bf16x8{};
+      if (hh < G) qf[c] = *reinterpret_cast<const bf16x8*>(s_q + hh * QS + 32 * c + 8 * g);
     }
-    if constexpr (!TILES_FIRST) {
-      __builtin_amdgcn_sched_barrier(0);
-      first_tiles();
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    if (owner) {
-      // the new token: rotated key and value of this KV head, to the page and to LDS
-      const int page = s.block_table[(size_t)slot * s.max_blocks + (pos >> 4)], tin = pos & 15;
-      for (int d = lane; d < DH; d += 64) {
-        const bool lo = d < HALF;
-        float av = 0.f, bv = 0.f, vv = 0.f;
-        for (int p0 = 0; p0 < fz.n_partials; p0 += QB) {
-          if (!ALL || p0 > 0 || d >= 64) request_kv(d, p0);
-#pragma unroll
-          for (int u = 0; u < QB; ++u)
-            if (p0 + u < fz.n_partials) { av += nka[u]; bv += nkb[u]; vv += nvv[u]; }
-        }
-        const float rot = lo ? rope_first(av, bv, ncs, nsn) : rope_second(av, bv, ncs, nsn);
-        const bf16_t kb = (bf16_t)rot, vb = (bf16_t)vv;
-        s_knew[d] = kb;
-        s_vnew[d] = vb;
-        kv_pool[L.at(layer, 0, page, kvh, tin, d)] = kb;
-        kv_pool[L.at(layer, 1, page, kvh, tin, d)] = vb;
-      }
-    }
-    if (last_split) __syncthreads();
   } else {
     first_tiles();
     __builtin_amdgcn_sched_barrier(0);
     const int hq = hh < G ? hh : G - 1;
-    const float* q = q_rot + (size_t)r * Hq * DH + (size_t)(kvh * G + hq) * DH + 8 * g;
+    const float* q = q_src + (size_t)r * Hq * DH + (size_t)(kvh * G + hq) * DH + 8 * g;
     f32x4 qa[KC][2];
 #pragma unroll
     for (int c = 0; c < KC; ++c) {
@@ -289,16 +265,22 @@ __global__ __launch_bounds__(64 * att_waves(DH, FUSED)) __attribute__((amdgpu_wa
 #pragma unroll
       for (int j = 0; j < 8; ++j) qf[c][j] = hh < G ? (bf16_t)qa[c][j >> 2][j & 3] : (bf16_t)0.f;
   }
-  const float scale = 1.0f / sqrtf((float)DH);
+  // Softmax in base 2, the scale folded into one multiply-add per score.  The running maximum of a head may lag the
+  // true one by up to 2^8 (the conditional rescaling known from published flash-attention kernels; probabilities are
+  // then at most 256, which costs no precision in bf16 or fp32), so that a tile needs no shuffle unless a
+  // score passes it; each lane sums its own tokens' probabilities until the end.
+  const float c2 = 1.4426950408889634f / sqrtf((float)DH);
+  constexpr float RESCALE = 8.0f;
   float m_run = -INFINITY, l_run = 0.f;
   f32x4 oacc[DT];
 #pragma unroll
   for (int d = 0; d < DT; ++d) oacc[d] = f32x4{};
 
-  // One tile: scores, online softmax, PV; reads kf / vf.
-  auto compute_tile = [&](int tile) {
-    const int t0 = t_begin + tile * 32;
-    if (FUSED && last_split && tile == ((pos - t_begin) >> 5)) {
+  // Tile i of this wavefront, in slot u: scores, online softmax, PV.  last (a compile-time truth): it may be the
+  // split's last tile, the one with masked tokens and the new token.
+  auto compute_tile = [&](int u, int i, auto last) {
+    const int tile = wave + i * ATT_WAVES, t0 = t_begin + tile * 32;
+    if (FUSED && last && last_split && tile == n_tiles - 1) {
       // the tile that holds the new token: take its key / value from LDS (the page copy may
       // not be visible yet); same bf16 values as the page now holds
       const int pp = ((pos - t_begin) >> 4) & 1, tin = pos & 15;
@@ -307,9 +289,7 @@ __global__ __launch_bounds__(64 * att_waves(DH, FUSED)) __attribute__((amdgpu_wa
         if (p != pp) continue;
         if (hh == tin) {
 #pragma unroll
-          for (int c = 0; c < KC; ++c)
-#pragma unroll
-            for (int j = 0; j < 8; ++j) kf[p][c][j] = s_knew[32 * c + 8 * g + j];
+          for (int c = 0; c < KC; ++c) kf[u][p][c] = *reinterpret_cast<const bf16x8*>(s_knew + 32 * c + 8 * g);
         }
         if ((tin >> 2) == g) {
 #pragma unroll
@@ -317,7 +297,7 @@ __global__ __launch_bounds__(64 * att_waves(DH, FUSED)) __attribute__((amdgpu_wa
             const bf16_t nv = s_vnew[d * 16 + hh];
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-              if (j == (tin & 3)) vf[p][d][j] = nv;
+              if (j == (tin & 3)) vf[u][p][d][j] = nv;
           }
         }
       }
@@ -328,7 +308,7 @@ __global__ __launch_bounds__(64 * att_waves(DH, FUSED)) __attribute__((amdgpu_wa
       sacc[p] = f32x4{};
 #pragma unroll
       for (int c = 0; c < KC; ++c)
-        sacc[p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[p][c], qf[c], sacc[p], 0, 0, 0);
+        sacc[p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[u][p][c], qf[c], sacc[p], 0, 0, 0);
     }
     float sv[8];
     float mx = -INFINITY;
@@ -337,80 +317,68 @@ __global__ __launch_bounds__(64 * att_waves(DH, FUSED)) __attribute__((amdgpu_wa
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int tok = t0 + p * 16 + 4 * g + i;
-        const float v = tok < t_end ? sacc[p][i] * scale : -INFINITY;
+        const float v = !last || tok < t_end ? sacc[p][i] : -INFINITY;
         sv[p * 4 + i] = v;
         mx = fmaxf(mx, v);
       }
-    mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-    const float m_new = fmaxf(m_run, mx);
-    const float corr = __expf(m_run - m_new);
-    float rs = 0.f;
+    mx *= c2;
+    if (__any(mx > m_run + RESCALE)) {           // always in a wavefront's first tile
+      mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+      const bool grow = mx > m_run + RESCALE;    // the same for the four lanes of a head
+      const float corr = grow ? __builtin_amdgcn_exp2f(m_run - mx) : 1.0f;
+      m_run = grow ? mx : m_run;
+      l_run *= corr;
+#pragma unroll
+      for (int d = 0; d < DT; ++d) oacc[d] *= corr;
+    }
+    float rs[2] = {0.f, 0.f};
     bf16x8 pf;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      const float pe = __expf(sv[e] - m_new);
-      rs += pe;
+      const float pe = __builtin_amdgcn_exp2f(__fmaf_rn(sv[e], c2, -m_run));
+      rs[e & 1] += pe;
       pf[e] = (bf16_t)pe;
     }
-    rs += __shfl_xor(rs, 16, 64);
-    rs += __shfl_xor(rs, 32, 64);
-    l_run = l_run * corr + rs;
-    m_run = m_new;
+    l_run += rs[0] + rs[1];
 #pragma unroll
     for (int d = 0; d < DT; ++d) {
-      oacc[d] *= corr;
       bf16x8 af;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) { af[j] = vf[0][d][j]; af[4 + j] = vf[1][d][j]; }
+      for (int j = 0; j < 4; ++j) { af[j] = vf[u][0][d][j]; af[4 + j] = vf[u][1][d][j]; }
       oacc[d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, pf, oacc[d], 0, 0, 0);
     }
   };
-  // Steady state: the tile AHEAD tiles further on is requested before this one is used.  The
-  // tiles that have no such successor are peeled off below, so no wavefront ends its loop
-  // waiting for a load it will not use (that wait was a full memory latency per wavefront).
-  if (wave < n_tiles) {
-    constexpr int AHEAD = (DEEP ? 2 : 1) * ATT_WAVES;
-    int tile = wave;
-    for (; tile + AHEAD < n_tiles; tile += ATT_WAVES) {
-      bf16x8 kn[2][KC];
-      bf16x4 vn[2][DT];
-      load_tile(tile + AHEAD, kn, vn);
+  // Steady state: a slot is requested again as soon as its tile is done, R - 1 tiles in flight behind the one in
+  // use and no branch between them, so that every wait is for one tile only (with tiles moved from slot to slot
+  // a wavefront waited in each step for what it had requested in the step before: one row of 400 tokens, 14 + 2 heads of
+  // 64, 20 + 4 of 64, 32 + 4 of 128: 6.7, 8.3, 10.3 us per launch, with this loop and the start above 5.4, 5.4, 7.7; 192 rows of
+  // 1000 tokens 25.1, 45.5, 84.4 / 24.5, 42.3, 78.9).  The rest has no
+  // successor to request, and no wavefront ends waiting for a tile that it does not use.
+  int i = 0;
+  for (; i + 2 * R <= cnt; i += R) {
+#pragma unroll
+    for (int u = 0; u < R; ++u) {
+      compute_tile(u, i + u, std::false_type{});
       __builtin_amdgcn_sched_barrier(0);
-      compute_tile(tile);
+      request(u, i + R + u);
       __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int p = 0; p < 2; ++p) {
-#pragma unroll
-        for (int c = 0; c < KC; ++c) {
-          if constexpr (DEEP) { kf[p][c] = km[p][c]; km[p][c] = kn[p][c]; } else kf[p][c] = kn[p][c];
-        }
-#pragma unroll
-        for (int d = 0; d < DT; ++d) {
-          if constexpr (DEEP) { vf[p][d] = vm[p][d]; vm[p][d] = vn[p][d]; } else vf[p][d] = vn[p][d];
-        }
-      }
-    }
-    compute_tile(tile);                          // tile < n_tiles here: the loop leaves at least one
-    if constexpr (DEEP) {
-      if (tile + ATT_WAVES < n_tiles) {
-#pragma unroll
-        for (int p = 0; p < 2; ++p) {
-#pragma unroll
-          for (int c = 0; c < KC; ++c) kf[p][c] = km[p][c];
-#pragma unroll
-          for (int d = 0; d < DT; ++d) vf[p][d] = vm[p][d];
-        }
-        compute_tile(tile + ATT_WAVES);
-      }
     }
   }
+#pragma unroll
+  for (int q = 0; q < 2 * R - 1; ++q)
+    if (i + q < cnt) {
+      compute_tile(q % R, i + q, std::true_type{});
+      if (q < R - 1 && i + q + R < cnt) request(q % R, i + q + R);
+    }
 
   // ---- merge the wavefronts of this workgroup through LDS, in wavefront order -----------
   // Every wavefront publishes (m, l, O); then each merges its share of the dim tiles (tile d
   // goes to wavefront d % ATT_WAVES) and writes it out, so the tail of a workgroup's life is
   // shared by all of them.  Rows of O are padded by 4 floats in LDS: with a stride of DH floats
   // the 16 heads of a lane group would all hit the same banks.
+  l_run += __shfl_xor(l_run, 16, 64);
+  l_run += __shfl_xor(l_run, 32, 64);
   {
     float* my = lds + wave * LREC;
     if (g == 0) { my[hh] = m_run; my[16 + hh] = l_run; }
@@ -424,7 +392,7 @@ __global__ __launch_bounds__(64 * att_waves(DH, FUSED)) __attribute__((amdgpu_wa
   float wgt[ATT_WAVES], lsum = 0.f;
 #pragma unroll
   for (int w = 0; w < ATT_WAVES; ++w) {
-    wgt[w] = __expf(lds[w * LREC + hh] - M);
+    wgt[w] = __builtin_amdgcn_exp2f(lds[w * LREC + hh] - M);
     lsum += wgt[w] * lds[w * LREC + 16 + hh];
   }
   const int K = Hq * DH;
@@ -497,7 +465,7 @@ __global__ __launch_bounds__(64) void attn_merge_kernel(RowCtx rc, int row_base,
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
-      const float wgt = i0 + u < n_splits ? __expf(mi[u] - M) : 0.f;
+      const float wgt = i0 + u < n_splits ? __builtin_amdgcn_exp2f(mi[u] - M) : 0.f;
       lsum += wgt * li[u];
 #pragma unroll
       for (int d = 0; d < DT; ++d) acc[d] += o[u][d] * wgt;
@@ -764,10 +732,11 @@ void launch_attn_decode(hipStream_t st, RowCtx rc, int row_base, Slots s, const 
   // items: the scheduler's work list of this iteration (decode, row_base 0), or null
   dim3 grid(rc.max_rows, kvl.n_kv_heads, grid_splits);
   if (items != nullptr) grid = dim3((unsigned)rc.max_rows * grid_splits * kvl.n_kv_heads);
-  AttnFuse fz{fused_qkv, n_partials, partial_stride, rope_cos, rope_sin};
+  AttnFuse fz{n_partials, partial_stride, rope_cos, rope_sin};
 #define ATT_LAUNCH(DH, F)                                                                                    \
-  hipLaunchKernelGGL((attn_decode_kernel<DH, F>), grid, dim3(64 * att_waves(DH, F)), 0, st, rc, row_base, s, q_rot, kv_pool, kvl, layer, \
-                     n_q_heads, out, ws, max_splits, fz, items)
+  hipLaunchKernelGGL((attn_decode_kernel<DH, F>), grid, dim3(64 * att_waves(DH, F)), 0, st, items, rc.ctl, s.block_table,      \
+                     F ? fused_qkv : q_rot, kv_pool, s.max_blocks, kvl.n_kv_heads, n_q_heads, layer, rc, row_base, kvl, out, \
+                     ws, max_splits, fz)
   const bool fused = fused_qkv != nullptr;
   switch (kvl.head_dim) {
     case 32: if (fused) ATT_LAUNCH(32, true); else ATT_LAUNCH(32, false); break;
