@@ -261,9 +261,9 @@ int april_sample_rows_logprobs(april_ctx* ctx, const float* logits, int32_t n_ro
 
 /* april_sample_rows for callers that cannot allocate device memory (code under HIP graph
  * capture rules, tight serving loops, harnesses that forbid hipMalloc): same arguments, same
- * result, but every temporary (row keys, result staging, control word, the per-row maxima and sums
- * of 64-logit groups) lives in a static device array of 12 MiB + 16.25 KiB that the library holds on
- * every GPU it runs on until the process ends; the call makes no hipMalloc / hipFree.
+ * result, but the device temporaries (the per-row maxima and sums of 64-logit groups) live in a static
+ * device array of 12 MiB that the library holds on every GPU it runs on until the process ends, row
+ * keys and result in the context's pinned staging buffer; the call makes no hipMalloc / hipFree.
  * Limits: n_rows <= 1024 and n_rows * (vocab / 64) <= 1048576 (APRIL_EINVAL beyond).
  * All calls on one GPU share that array and it keeps the last call's contents: calls that
  * overlap on one GPU (other threads, other contexts) race; serialise them. */

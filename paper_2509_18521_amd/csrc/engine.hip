@@ -81,16 +81,12 @@ struct Entry {
 
 }  // namespace
 
-// Scratch of april_sample_rows_noalloc: staging of the row keys and of the result, the control
-// word, and the group maxima the sampler's candidate search needs.  One copy per GPU, held
+// Scratch of april_sample_rows_noalloc: the group records that the sampler's candidate search needs.  One copy per GPU, held
 // until the process ends; host code only ever uses the device address looked up at april_init.
 constexpr size_t NOALLOC_MAX_ROWS = 1024;
 constexpr size_t NOALLOC_MAX_GROUP_MAX = (size_t)1 << 20;        // floats: n_rows * (vocab / 64) may not exceed this
-constexpr size_t NOALLOC_OFF_CTL = 0, NOALLOC_OFF_REQ = 256, NOALLOC_OFF_GEN = NOALLOC_OFF_REQ + 8 * NOALLOC_MAX_ROWS,
-                 NOALLOC_OFF_OUT = NOALLOC_OFF_GEN + 4 * NOALLOC_MAX_ROWS, NOALLOC_OFF_GM = NOALLOC_OFF_OUT + 4 * NOALLOC_MAX_ROWS,
-                 NOALLOC_OFF_GS = NOALLOC_OFF_GM + 4 * NOALLOC_MAX_GROUP_MAX,      // group sums (categorical sampler)
+constexpr size_t NOALLOC_OFF_GM = 0, NOALLOC_OFF_GS = 4 * NOALLOC_MAX_GROUP_MAX,      // group sums (categorical sampler)
                  NOALLOC_BYTES = NOALLOC_OFF_GS + 8 * NOALLOC_MAX_GROUP_MAX;
-static_assert(NOALLOC_OFF_GM % 256 == 0, "group maxima start on a 256-byte boundary");
 static __device__ __align__(256) unsigned char scratch[NOALLOC_BYTES];
 constexpr int MAX_DEVICES = 64;
 static unsigned char* g_scratch_ptr[MAX_DEVICES];                // device address of `scratch` on each GPU, set by april_init
@@ -722,7 +718,7 @@ void forward(april_ctx* c, RowCtx rows, RowCtx srows, const int* gather, double 
     if (c->group_sum && sc.kind == APRIL_SAMPLER_CATEGORICAL)
       launch_group_records(st, c->logits, srows.ctl, srows.max_rows, V, 2, sc.temperature, c->group_max, c->group_sum);
     launch_sample(st, srows, c->ds, c->d_ctrl, lg_out, V, sc, w, 1, nullptr, nullptr, nullptr, c->group_max,
-                  lmhead_group_cols(), nullptr, c->group_max ? c->group_idx : nullptr, c->group_sum);
+                  nullptr, c->group_max ? c->group_idx : nullptr, c->group_sum);
   }
 }
 
@@ -1343,52 +1339,42 @@ int april_debug_logits(april_ctx* c, int64_t request_id, int32_t gen_index, floa
 static int sample_rows_impl(april_ctx* c, const float* logits, int32_t n_rows, const int64_t* request_ids,
                             const int32_t* gen_index, int32_t* out_tokens, float* out_logprobs) {
   if (!c || !logits || !request_ids || !gen_index || !out_tokens || n_rows <= 0) return APRIL_EINVAL;
-  // The temporaries stay with the context (until april_memory_pause or april_destroy) and rows go through in parts that keep
-  // them within 64 MiB: allocating and releasing them took 8 calls that synchronise the device, about 70 of
-  // the 700 us of a call for 192 rows of 152 k logits.  Records of one part: row keys (packed: one
-  // copy in, one copy out), then the group records.
-  const int V = c->dm.vocab, grp = lmhead_group_cols(), n_groups = ceil_div(V, grp);
+  // The group records' workspace stays with the context (until april_memory_pause or april_destroy) and rows go through in
+  // parts that keep it within 64 MiB: allocating and releasing it took 8 calls that synchronise the device, about 70 of
+  // the 700 us of a call for 192 rows of 152 k logits.  Row keys and results lie in the context's pinned staging
+  // buffer, which the kernels read and write themselves (a copy up and one down were 30 of the 92 us that were left).
+  const int V = c->dm.vocab, n_groups = ceil_div(V, lmhead_group_cols());
   const SamplerCfg sc = sampler_cfg(c);
   // sums: the categorical sampler's (fp64 exponentials) serve the log-probabilities too
   const int sums = sc.kind == APRIL_SAMPLER_CATEGORICAL ? 2 : (out_logprobs ? 1 : 0);
-  const size_t row_bytes = (size_t)n_groups * (sums ? 12 : 4) + 24;
-  const int part_rows = (int)std::max<size_t>(1, std::min<size_t>({(size_t)n_rows, 16384, ((size_t)64 << 20) / row_bytes}));
-  const size_t off_gen = 8 + (size_t)part_rows * 8, off_out = off_gen + (size_t)part_rows * 4, off_lp = off_out + (size_t)part_rows * 4;
-  const size_t off_gs = (off_lp + (size_t)part_rows * 4 + 255) / 256 * 256, off_gm = off_gs + (sums ? (size_t)part_rows * n_groups * 8 : 0);
-  const size_t need = off_gm + (size_t)part_rows * n_groups * 4;
+  const size_t row_bytes = (size_t)n_groups * (sums ? 12 : 4);
+  const int part_rows = (int)std::max<size_t>(1, std::min<size_t>({(size_t)n_rows, 16384, c->h_stage_ints * sizeof(int) / 20, ((size_t)64 << 20) / row_bytes}));
+  const size_t off_gm = sums ? (size_t)part_rows * n_groups * 8 : 0, need = off_gm + (size_t)part_rows * n_groups * 4;
   if (need > c->sr_ws_bytes) {
     HIPCHK(c, hipStreamSynchronize(c->stream));
     if (c->sr_ws) { hipFree(c->sr_ws); c->sr_ws = nullptr; c->sr_ws_bytes = 0; }
     if (hipMalloc((void**)&c->sr_ws, need) != hipSuccess) return fail(c, APRIL_ENOMEM, "sampler workspace (%zu bytes)", need);
     c->sr_ws_bytes = need;
   }
-  char* w = c->sr_ws;
-  // (nothing may be thrown through this C entry)
-  std::unique_ptr<char[]> stage(new (std::nothrow) char[off_lp + (size_t)part_rows * 4]);
-  if (!stage) return fail(c, APRIL_ENOMEM, "sampler staging");
+  float* gm = reinterpret_cast<float*>(c->sr_ws + off_gm);
+  double* gs = sums ? reinterpret_cast<double*>(c->sr_ws) : nullptr;
+  const bool records = sums || sc.kind != APRIL_SAMPLER_TOPK || sc.top_k <= 1 || topk_in_groups(V, sc.top_k);
+  long long* req = reinterpret_cast<long long*>(c->h_stage);
+  int *gen = reinterpret_cast<int*>(req + part_rows), *tok = gen + part_rows;
+  float* lp = out_logprobs ? reinterpret_cast<float*>(tok + part_rows) : nullptr;
+  // behind the caller's work on the null stream (and the streams that order with it), which may still be producing the logits
+  HIPCHK(c, hipStreamSynchronize(nullptr));
   for (int r0 = 0; r0 < n_rows; r0 += part_rows) {
     const int n = std::min(part_rows, n_rows - r0);
-    const int ctl[2] = {n, 0};
-    memcpy(stage.get(), ctl, 8);
-    memcpy(stage.get() + 8, request_ids + r0, (size_t)n * 8);
-    memcpy(stage.get() + off_gen, gen_index + r0, (size_t)n * 4);
-    // (hipMemcpy on the null stream: also orders this call behind the caller's work on that stream,
-    // which may still be producing the logits)
-    HIPCHK(c, hipMemcpy(w, stage.get(), off_out, hipMemcpyHostToDevice));
+    memcpy(req, request_ids + r0, (size_t)n * 8);
+    memcpy(gen, gen_index + r0, (size_t)n * 4);
     const float* lg = logits + (size_t)r0 * V;
-    float* gm = reinterpret_cast<float*>(w + off_gm);
-    double* gs = sums ? reinterpret_cast<double*>(w + off_gs) : nullptr;
-    float* lp = out_logprobs ? reinterpret_cast<float*>(w + off_lp) : nullptr;
-    const bool records = sums || sc.kind != APRIL_SAMPLER_TOPK || sc.top_k <= 1 || topk_in_groups(V, sc.top_k);
     if (records) launch_group_records(c->stream, lg, nullptr, n, V, sums, sc.temperature, gm, gs);
-    else gm = nullptr;
-    launch_sample(c->stream, RowCtx{nullptr, nullptr, reinterpret_cast<const int2*>(w), n}, c->ds, nullptr, lg, V, sc, Watch{}, 0,
-                  reinterpret_cast<const long long*>(w + 8), reinterpret_cast<const int*>(w + off_gen),
-                  reinterpret_cast<int*>(w + off_out), gm, grp, lp, nullptr, gs);
-    HIPCHK(c, hipMemcpyAsync(stage.get() + off_out, w + off_out, off_lp + (lp ? (size_t)part_rows * 4 : 0) - off_out, hipMemcpyDeviceToHost, c->stream));
+    launch_sample(c->stream, RowCtx{nullptr, nullptr, nullptr, n}, c->ds, nullptr, lg, V, sc, Watch{}, 0, req, gen, tok,
+                  records ? gm : nullptr, lp, nullptr, gs);
     HIPCHK(c, hipStreamSynchronize(c->stream));
-    memcpy(out_tokens + r0, stage.get() + off_out, (size_t)n * 4);
-    if (lp) memcpy(out_logprobs + r0, stage.get() + off_lp, (size_t)n * 4);
+    memcpy(out_tokens + r0, tok, (size_t)n * 4);
+    if (lp) memcpy(out_logprobs + r0, lp, (size_t)n * 4);
   }
   return APRIL_OK;
 }
@@ -1421,23 +1407,17 @@ int april_sample_rows_noalloc(april_ctx* c, const float* logits, int32_t n_rows,
   const int sums = use_gm && sc.kind == APRIL_SAMPLER_CATEGORICAL ? 2 : 0;
   float* d_gm = use_gm ? reinterpret_cast<float*>(sp + NOALLOC_OFF_GM) : nullptr;
   double* d_gs = sums ? reinterpret_cast<double*>(sp + NOALLOC_OFF_GS) : nullptr;
-  int* d_out = reinterpret_cast<int*>(sp + NOALLOC_OFF_OUT);
   hipStream_t st = c->stream;
-  // control word and row keys through the context's pinned staging buffer, one copy, and the tokens
-  // back the same way (three pageable copies in and one out were 20 of a 5-row call's 62 us)
-  char* hs = reinterpret_cast<char*>(c->h_stage);
-  const int ctl[2] = {n_rows, 0};                 // {rows, stop flag}: the array keeps the last call's contents
-  memcpy(hs + NOALLOC_OFF_CTL, ctl, sizeof ctl);
-  memcpy(hs + NOALLOC_OFF_REQ, request_ids, n_rows * sizeof(long long));
-  memcpy(hs + NOALLOC_OFF_GEN, gen_index, n_rows * sizeof(int));
-  HIPCHK(c, hipMemcpyAsync(sp, hs, NOALLOC_OFF_GEN + n_rows * sizeof(int), hipMemcpyHostToDevice, st));
-  RowCtx rc{nullptr, nullptr, reinterpret_cast<const int2*>(sp + NOALLOC_OFF_CTL), n_rows};
+  // row keys and tokens in the context's pinned staging buffer, which the kernels read and write themselves (three pageable
+  // copies in and one out were 20 of a 5-row call's 62 us, two pinned ones 15 of 42)
+  long long* req = reinterpret_cast<long long*>(c->h_stage);
+  int *gen = reinterpret_cast<int*>(req + n_rows), *tok = gen + n_rows;
+  memcpy(req, request_ids, n_rows * sizeof(long long));
+  memcpy(gen, gen_index, n_rows * sizeof(int));
   if (use_gm) launch_group_records(st, logits, nullptr, n_rows, V, sums, sc.temperature, d_gm, d_gs);
-  launch_sample(st, rc, c->ds, nullptr, logits, V, sc, Watch{}, 0, reinterpret_cast<const long long*>(sp + NOALLOC_OFF_REQ),
-                reinterpret_cast<const int*>(sp + NOALLOC_OFF_GEN), d_out, d_gm, grp, nullptr, nullptr, d_gs);
-  HIPCHK(c, hipMemcpyAsync(hs + NOALLOC_OFF_OUT, d_out, n_rows * sizeof(int), hipMemcpyDeviceToHost, st));
+  launch_sample(st, RowCtx{nullptr, nullptr, nullptr, n_rows}, c->ds, nullptr, logits, V, sc, Watch{}, 0, req, gen, tok, d_gm, nullptr, nullptr, d_gs);
   HIPCHK(c, hipStreamSynchronize(st));
-  memcpy(out_tokens, hs + NOALLOC_OFF_OUT, n_rows * sizeof(int));
+  memcpy(out_tokens, tok, n_rows * sizeof(int));
   return APRIL_OK;
 }
 

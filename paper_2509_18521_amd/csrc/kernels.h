@@ -269,7 +269,7 @@ struct SamplerCfg {
 // the log-probability goes to s.logprob when that array exists.
 void launch_sample(hipStream_t st, RowCtx rc, Slots s, Ctrl* ctrl, const float* logits, int vocab,
                    SamplerCfg sc, Watch w, int update, const long long* req_ids,
-                   const int* gen_idx, int* out_tokens, const float* group_max, int group,
+                   const int* gen_idx, int* out_tokens, const float* group_max,
                    float* out_logprobs = nullptr, const int* group_idx = nullptr,
                    const double* group_sum = nullptr);
 

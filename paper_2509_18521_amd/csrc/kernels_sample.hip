@@ -19,7 +19,8 @@
 
 namespace april {
 
-#define SAMPLE_THREADS 1024
+constexpr int ROWS_THREADS = 1024;     // workgroup of the whole-row kernel
+constexpr int REC_THREADS = 1024;      // ... and of the one that works from group records (256: 17.8 against 11.3 us for a top 50)
 #define MAX_TOPK 64
 #define MAX_HOT 1024
 #define MAX_CAND 2048
@@ -30,6 +31,8 @@ __device__ inline unsigned f2key(float f) {
   if (u == 0x80000000u) u = 0u;
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
+
+__device__ inline float key2f(unsigned k) { return __uint_as_float((k & 0x80000000u) ? k & 0x7fffffffu : ~k); }
 
 // Philox4x32-10 (Salmon et al., SC'11): first output word.
 __device__ inline unsigned philox4x32_10_word0(unsigned c0, unsigned c1, unsigned c2, unsigned c3,
@@ -46,13 +49,88 @@ __device__ inline unsigned philox4x32_10_word0(unsigned c0, unsigned c1, unsigne
   return c0;
 }
 
+// Reductions inside a wavefront on the DPP lanes of the vector unit: rotations by 8, 4, 2, 1 inside the rows of 16 lanes,
+// then the rows by scalar reads.  (A shuffle through the LDS unit is a round trip of 100 cycles and more, with 16
+// wavefronts asking at once; six of them were most of a block-wide step.)
+template <int N> __device__ inline int row_ror(int v) { return __builtin_amdgcn_update_dpp(0, v, 0x120 + N, 0xf, 0xf, false); }
+template <int N> __device__ inline double row_ror_f64(double v) {
+  union { double d; int i[2]; } x{v};
+  x.i[0] = row_ror<N>(x.i[0]);
+  x.i[1] = row_ror<N>(x.i[1]);
+  return x.d;
+}
+__device__ inline float as_f32(int v) { return __int_as_float(v); }
+// every lane: over its row of 16 lanes
+__device__ inline float row_max_f32(float v) {
+  v = fmaxf(v, as_f32(row_ror<8>(__float_as_int(v))));
+  v = fmaxf(v, as_f32(row_ror<4>(__float_as_int(v))));
+  v = fmaxf(v, as_f32(row_ror<2>(__float_as_int(v))));
+  return fmaxf(v, as_f32(row_ror<1>(__float_as_int(v))));
+}
+__device__ inline unsigned row_max_u32(unsigned v) {
+  v = max(v, (unsigned)row_ror<8>((int)v));
+  v = max(v, (unsigned)row_ror<4>((int)v));
+  v = max(v, (unsigned)row_ror<2>((int)v));
+  return max(v, (unsigned)row_ror<1>((int)v));
+}
+__device__ inline int row_min_i32(int v) {
+  v = min(v, row_ror<8>(v));
+  v = min(v, row_ror<4>(v));
+  v = min(v, row_ror<2>(v));
+  return min(v, row_ror<1>(v));
+}
+__device__ inline double row_sum_f64(double v) {
+  v += row_ror_f64<8>(v);
+  v += row_ror_f64<4>(v);
+  v += row_ror_f64<2>(v);
+  return v + row_ror_f64<1>(v);
+}
+__device__ inline double lane_f64(double v, int l) {
+  union { double d; int i[2]; } x{v};
+  x.i[0] = __builtin_amdgcn_readlane(x.i[0], l);
+  x.i[1] = __builtin_amdgcn_readlane(x.i[1], l);
+  return x.d;
+}
+// every lane: over the wavefront
+__device__ inline float wave_max_f32(float v) {
+  const int r = __float_as_int(row_max_f32(v));
+  return fmaxf(fmaxf(as_f32(__builtin_amdgcn_readlane(r, 0)), as_f32(__builtin_amdgcn_readlane(r, 16))),
+               fmaxf(as_f32(__builtin_amdgcn_readlane(r, 32)), as_f32(__builtin_amdgcn_readlane(r, 48))));
+}
+__device__ inline unsigned wave_max_u32(unsigned v) {
+  const int r = (int)row_max_u32(v);
+  return max(max((unsigned)__builtin_amdgcn_readlane(r, 0), (unsigned)__builtin_amdgcn_readlane(r, 16)),
+             max((unsigned)__builtin_amdgcn_readlane(r, 32), (unsigned)__builtin_amdgcn_readlane(r, 48)));
+}
+__device__ inline int wave_min_i32(int v) {
+  const int r = row_min_i32(v);
+  return min(min(__builtin_amdgcn_readlane(r, 0), __builtin_amdgcn_readlane(r, 16)),
+             min(__builtin_amdgcn_readlane(r, 32), __builtin_amdgcn_readlane(r, 48)));
+}
+__device__ inline double wave_sum_f64(double v) {
+  v = row_sum_f64(v);
+  return (lane_f64(v, 0) + lane_f64(v, 16)) + (lane_f64(v, 32) + lane_f64(v, 48));
+}
+// inclusive prefix sum over the lanes
+__device__ inline double wave_scan_f64(double v) {
+  const int lane = threadIdx.x & 63, l16 = lane & 15;
+  double o;
+  o = row_ror_f64<1>(v); if (l16 >= 1) v += o;
+  o = row_ror_f64<2>(v); if (l16 >= 2) v += o;
+  o = row_ror_f64<4>(v); if (l16 >= 4) v += o;
+  o = row_ror_f64<8>(v); if (l16 >= 8) v += o;
+  const double a = lane_f64(v, 15), b = lane_f64(v, 31), c = lane_f64(v, 47);
+  return v + (lane < 16 ? 0.0 : (lane < 32 ? a : (lane < 48 ? a + b : (a + b) + c)));
+}
+
 struct SampleShared {
   unsigned hist[256];
   unsigned prefix, krem, ntie;
   int cnt, choice, watch_row, n_hot, overflow;
-  unsigned cand_key[MAX_CAND];
-  int cand_idx[MAX_CAND];
+  // (descending order: larger key, then lower index, so the index is kept inverted and a pair compares as one number)
+  __align__(16) unsigned long long cand[MAX_CAND];
   int hot[MAX_HOT];
+  unsigned count[MAX_CAND];
   float sort_logit[MAX_TOPK];
   int sort_idx[MAX_TOPK];
   unsigned red_key[16];
@@ -67,14 +145,14 @@ struct SampleShared {
 __device__ inline float block_max_f32(const float* vals, int n, SampleShared& sh) {
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   float m = -INFINITY;
-  for (int i = tid; i < n; i += SAMPLE_THREADS) m = fmaxf(m, vals[i]);
+  for (int i = tid; i < n; i += ROWS_THREADS) m = fmaxf(m, vals[i]);
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
   __syncthreads();
   if (lane == 0) sh.red_f[wid] = m;
   __syncthreads();
   if (tid == 0) {
-    for (int x = 1; x < SAMPLE_THREADS / 64; ++x) m = fmaxf(m, sh.red_f[x]);
+    for (int x = 1; x < ROWS_THREADS / 64; ++x) m = fmaxf(m, sh.red_f[x]);
     sh.max_f = m;
   }
   __syncthreads();
@@ -91,25 +169,28 @@ __device__ inline double block_sum_f64(double v, SampleShared& sh) {
   __syncthreads();
   if (tid == 0) {
     double t = sh.red_d[0];
-    for (int x = 1; x < SAMPLE_THREADS / 64; ++x) t += sh.red_d[x];
+    for (int x = 1; x < ROWS_THREADS / 64; ++x) t += sh.red_d[x];
     sh.total_d = t;
   }
   __syncthreads();
   return sh.total_d;
 }
 
+__device__ inline unsigned long long cand_pair(unsigned key, int idx) { return ((unsigned long long)key << 32) | (unsigned)~idx; }
+
 // Key of the k-th largest of vals[0..n) (k <= n): 4 radix passes of 8 bits.  On return
 // sh.prefix = that key, sh.krem = how many entries equal to it belong to the top k,
 // sh.ntie = how many entries equal it.  All threads must call.  Up to 4 keys per thread are
-// kept in registers across the passes (n <= 4 * SAMPLE_THREADS reads memory once).
+// kept in registers across the passes (n <= 4 * NT reads memory once).  NT: threads of the workgroup, here and below.
+template <int NT>
 __device__ inline void block_kth_largest(const float* vals, int n, int k, SampleShared& sh) {
   const int tid = threadIdx.x;
-  const bool cached = n <= 4 * SAMPLE_THREADS;
+  const bool cached = n <= 4 * NT;
   unsigned ck[4] = {0u, 0u, 0u, 0u};
   if (cached) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const int i = tid + q * SAMPLE_THREADS;
+      const int i = tid + q * NT;
       if (i < n) ck[q] = f2key(vals[i]);
     }
   }
@@ -123,9 +204,9 @@ __device__ inline void block_kth_largest(const float* vals, int n, int k, Sample
     if (cached) {
 #pragma unroll
       for (int q = 0; q < 4; ++q)
-        if (tid + q * SAMPLE_THREADS < n && (ck[q] & mask_hi) == prefix) atomicAdd(&sh.hist[(ck[q] >> shift) & 255u], 1u);
+        if (tid + q * NT < n && (ck[q] & mask_hi) == prefix) atomicAdd(&sh.hist[(ck[q] >> shift) & 255u], 1u);
     } else {
-      for (int i = tid; i < n; i += SAMPLE_THREADS) {
+      for (int i = tid; i < n; i += NT) {
         const unsigned key = f2key(vals[i]);
         if ((key & mask_hi) == prefix) atomicAdd(&sh.hist[(key >> shift) & 255u], 1u);
       }
@@ -168,7 +249,7 @@ __device__ inline int block_argmax(const float* vals, int n, SampleShared& sh) {
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   unsigned bk = 0u;
   int bi = 0x7fffffff;
-  for (int i = tid; i < n; i += SAMPLE_THREADS) {
+  for (int i = tid; i < n; i += ROWS_THREADS) {
     const unsigned k = f2key(vals[i]);
     if (bi == 0x7fffffff || k > bk) { bk = k; bi = i; }     // ascending i: first maximum stays
   }
@@ -182,7 +263,7 @@ __device__ inline int block_argmax(const float* vals, int n, SampleShared& sh) {
   if (lane == 0) { sh.red_key[wid] = bk; sh.red_idx[wid] = bi; }
   __syncthreads();
   if (tid == 0) {
-    for (int x = 1; x < SAMPLE_THREADS / 64; ++x)
+    for (int x = 1; x < ROWS_THREADS / 64; ++x)
       if (sh.red_key[x] > bk || (sh.red_key[x] == bk && sh.red_idx[x] < bi)) { bk = sh.red_key[x]; bi = sh.red_idx[x]; }
     sh.choice = bi;
   }
@@ -190,61 +271,207 @@ __device__ inline int block_argmax(const float* vals, int n, SampleShared& sh) {
   return sh.choice;
 }
 
-__global__ __launch_bounds__(SAMPLE_THREADS) void sample_kernel(RowCtx rc, Slots s, Ctrl* ctrl,
-                                                                const float* logits, int V, SamplerCfg sc,
-                                                                Watch w, int update, const long long* req_ids,
-                                                                const int* gen_idx, int* out_tokens,
-                                                                const float* group_max, int group,
-                                                                float* out_logprobs, const int* group_idx,
-                                                                const double* group_sum) {
-  const int r = blockIdx.x;
-  ROW_GUARD(rc, r);
+// What a sampling row works on, requested at the kernel's start: nothing behind the choice waits for memory again.
+struct RowState {
+  int slot, pos, g, limit, state, forced, group, eos, iter;
+  long long req;
+};
+__device__ inline RowState load_row(const RowCtx& rc, const Slots& s, const Ctrl* ctrl, int r, int update,
+                                    const long long* req_ids, const int* gen_idx) {
+  RowState q{-1, 0, 0, 0, 0, -1, -1, -1, 0, 0};
+  if (update) {
+    q.slot = rc.row_slot[r];
+    q.pos = rc.row_pos[r];
+    q.eos = ctrl->eos_token;
+    q.iter = ctrl->iter;
+    q.g = s.gen[q.slot];
+    q.req = s.req_id[q.slot];
+    q.limit = s.limit[q.slot];
+    q.state = s.state[q.slot];
+    if (s.group != nullptr) q.group = s.group[q.slot];
+    if (s.forced != nullptr) q.forced = s.forced[(size_t)q.slot * s.max_ctx + q.g];
+  } else {
+    // (these may lie in host memory: 2.5 us away, and a scalar load would have every wait for a scalar load wait for it)
+    int at = r;
+    asm volatile("" : "+v"(at));
+    q.req = req_ids[at];
+    q.g = gen_idx[at];
+  }
+  return q;
+}
+// rc.ctl may be null (the caller states the rows)
+__device__ inline int sampling_rows(const RowCtx& rc) { return rc.ctl != nullptr ? rows_or_zero(rc) : rc.max_rows; }
+
+__device__ inline double uniform_draw(const SamplerCfg& sc, long long req, int g) {
+  const unsigned long long rid = (unsigned long long)req;
+  const unsigned w0 = philox4x32_10_word0((unsigned)(rid & 0xFFFFFFFFull), (unsigned)(rid >> 32), (unsigned)g, 0u,
+                                          (unsigned)(sc.seed & 0xFFFFFFFFull), (unsigned)(sc.seed >> 32));
+  return (double)(w0 >> 8) * (1.0 / 16777216.0);
+}
+
+// Parity-mode capture (all threads call).
+template <int NT>
+__device__ inline void capture_row(const Watch& w, const Ctrl* ctrl, const RowState& q, const float* lg, int V, int sampled, SampleShared& sh) {
+  if (w.req == nullptr || ctrl == nullptr) return;
+  const int tid = threadIdx.x;
+  if (tid == 0) {
+    int row = -1;
+    const int nw = ctrl->n_watch;
+    for (int i = 0; i < nw; ++i)
+      if (w.req[i] == q.req && q.g >= w.first[i] && q.g < w.first[i] + w.count[i]) row = w.row0[i] + (q.g - w.first[i]);
+    sh.watch_row = row;
+  }
+  __syncthreads();
+  const int row = sh.watch_row;
+  if (row >= 0) {
+    for (int i = tid; i < V; i += NT) w.logits[(size_t)row * V + i] = lg[i];
+    if (tid == 0) { w.sampled[row] = sampled; w.filled[row] = 1; }
+  }
+}
+// Token to the caller, or appended to its rollout (one thread).
+__device__ inline void finish_row(const Slots& s, Ctrl* ctrl, const RowState& q, int r, int update, int sampled, int tok, int* out_tokens) {
+  if (!update) { out_tokens[r] = sampled; return; }
+  s.tokens[(size_t)q.slot * s.max_ctx + q.pos + 1] = tok;
+  s.gen[q.slot] = q.g + 1;
+  s.kv_len[q.slot] = q.pos + 1;
+  int stt = q.state;
+  if (stt == SLOT_PREFILL) stt = SLOT_LIVE;
+  if (q.g + 1 >= q.limit || tok == q.eos) {
+    stt = SLOT_DONE;
+    s.finish_iter[q.slot] = q.iter;
+    // what the scheduler counts toward N: the rollout, or (instance-level completion,
+    // Section 3.2.3) its group once the last member is complete
+    if (q.group < 0) atomicAdd(&ctrl->finished, 1);
+    else if (atomicSub(&s.grp_left[q.group], 1) == 1) atomicAdd(&ctrl->finished, 1);
+  }
+  s.state[q.slot] = stt;
+}
+
+// Radix select of the row's top k into the candidate list (all threads call).
+template <int NT>
+__device__ inline void topk_whole_row(const float* lg, int V, int k, SampleShared& sh) {
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-  const bool have_logits = logits != nullptr;
+  block_kth_largest<NT>(lg, V, k, sh);
+  const unsigned thr = sh.prefix;
+  const int krem = (int)sh.krem, ntie = (int)sh.ntie;
+  if (tid == 0) sh.cnt = 0;
+  __syncthreads();
+  // everything above the threshold, plus the threshold ties with the lowest indices
+  for (int i = tid; i < V; i += NT) {
+    const unsigned key = f2key(lg[i]);
+    if (key > thr || (key == thr && ntie == krem)) {
+      const int p = atomicAdd(&sh.cnt, 1);
+      if (p < MAX_CAND) sh.cand[p] = cand_pair(key, i);
+    }
+  }
+  __syncthreads();
+  if (ntie == krem) return;
+  int last = -1;
+  for (int t = 0; t < krem; ++t) {
+    int best = 0x7fffffff;
+    for (int i = tid; i < V; i += NT)
+      if (i > last && f2key(lg[i]) == thr) { best = i; break; }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) { const int o = __shfl_xor(best, off, 64); best = o < best ? o : best; }
+    if (lane == 0) sh.red_idx[wid] = best;
+    __syncthreads();
+    if (tid == 0) {
+      for (int x = 1; x < NT / 64; ++x) best = sh.red_idx[x] < best ? sh.red_idx[x] : best;
+      const int p = sh.cnt++;
+      if (p < MAX_CAND) sh.cand[p] = cand_pair(thr, best);
+      sh.red_idx[0] = best;
+    }
+    __syncthreads();
+    last = sh.red_idx[0];
+    __syncthreads();
+  }
+}
+
+// sh.count[e] += the sum of f(entry e, entry j) over the n entries j of the candidate list, for every entry e.  128
+// entries at a time, an eighth of the list per group of 128 threads, four entries of it per round trip to LDS.  All
+// threads call; the counts (zero before) are complete behind the next barrier.
+template <class F>
+__device__ inline void count_pairs(SampleShared& sh, int n, F f) {
+  static_assert(ROWS_THREADS == 1024 && REC_THREADS == 1024, "eight groups of 128 threads");
+  const int per = (n + 31) / 32 * 4, j0 = (threadIdx.x >> 7) * per, j1 = min(n, j0 + per);
+  for (int e0 = 0; e0 < n; e0 += 128) {
+    const int e = e0 + (threadIdx.x & 127);
+    const unsigned long long own = sh.cand[e < n ? e : 0];
+    unsigned c = 0;
+    for (int j = j0; j < j1; j += 4) {          // (entries past the end of the list: zero, see fill)
+      const ulonglong2 x = *reinterpret_cast<const ulonglong2*>(sh.cand + j), y = *reinterpret_cast<const ulonglong2*>(sh.cand + j + 2);
+      c += (f(own, x.x) + f(own, x.y)) + (f(own, y.x) + f(own, y.y));
+    }
+    if (e < n && c != 0) atomicAdd(&sh.count[e], c);
+  }
+}
+// Up to three entries that come after every other, behind the list's end (one thread; no entry is zero).
+__device__ inline void fill_list(SampleShared& sh, int n) {
+  for (int j = n; j < (n + 3) / 4 * 4; ++j) sh.cand[j] = 0ull;
+}
+
+// The draw among the exact top k of the candidates: the rank of a candidate is its place in the descending order.
+// Result in sh.choice; all threads call, with the counts zero, and meet in it but not behind it.
+__device__ inline void draw_topk(int k, const SamplerCfg& sc, long long req, int g, SampleShared& sh) {
+  const int tid = threadIdx.x;
+  __syncthreads();
+  const int n_cand = sh.cnt < MAX_CAND ? sh.cnt : MAX_CAND;
+  if (tid == 0) fill_list(sh, n_cand);
+  __syncthreads();
+  count_pairs(sh, n_cand, [](unsigned long long own, unsigned long long x) { return x > own ? 1u : 0u; });
+  __syncthreads();
+  for (int c = tid; c < n_cand; c += ROWS_THREADS) {
+    const unsigned long long own = sh.cand[c];
+    const int rank = (int)sh.count[c];
+    if (rank < k) { sh.sort_logit[rank] = key2f((unsigned)(own >> 32)); sh.sort_idx[rank] = ~(int)(unsigned)own; }
+  }
+  __syncthreads();
+  if (tid >= 64) return;
+  // Lane j holds candidate j (k <= 64).  fp64 softmax over the candidates and its running sum; the token is the first
+  // candidate whose cumulative probability exceeds the uniform draw, the last candidate if none does.
+  const int n = n_cand < k ? n_cand : k;
+  const double T = (double)sc.temperature;
+  const double z = (double)sh.sort_logit[tid < n ? tid : 0] / T;
+  const double e = tid < n ? exp(z - lane_f64(z, 0)) : 0.0;
+  const double c = wave_scan_f64(e / wave_sum_f64(e));    // inclusive prefix sum over lanes <= tid
+  int keep = n;
+  double tot = 1.0;
+  if (sc.top_p > 0.f && sc.top_p < 1.f) {
+    // nucleus: the shortest prefix whose cumulative probability reaches top_p
+    const unsigned long long reach = __ballot(tid < n && c >= (double)sc.top_p);
+    keep = reach ? __ffsll((long long)reach) : n;
+    tot = lane_f64(c, __builtin_amdgcn_readfirstlane(keep - 1));      // mass of the nucleus: renormalise by it
+  }
+  const unsigned long long hit = __ballot(tid < keep && c > uniform_draw(sc, req, g) * tot);
+  if (tid == 0) sh.choice = sh.sort_idx[hit ? __ffsll((long long)hit) - 1 : keep - 1];
+}
+
+// ---------------------------------------------------------------------------
+// Sampling from the whole row: logits without group records (small and ragged vocabularies, the fp32 path).
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(ROWS_THREADS) void sample_rows_kernel(RowCtx rc, Slots s, Ctrl* ctrl, const float* logits, int V,
+                                                                     SamplerCfg sc, Watch w, int update,
+                                                                     const long long* req_ids, const int* gen_idx,
+                                                                     int* out_tokens, float* out_logprobs) {
+  const int r = blockIdx.x;
+  if (r >= sampling_rows(rc)) return;
+  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   const float* lg = logits + (size_t)r * V;
   __shared__ SampleShared sh;
-
-  int slot = -1, pos = 0, g = 0;
-  long long req = 0;
-  if (update) {
-    slot = rc.row_slot[r];
-    pos = rc.row_pos[r];
-    g = s.gen[slot];
-    req = s.req_id[slot];
-  } else {
-    req = req_ids[r];
-    g = gen_idx[r];
-  }
-  const int n_groups = group_max ? (V + group - 1) / group : 0;
-  const float* gm = group_max ? group_max + (size_t)r * n_groups : nullptr;
-  const double* gs = group_sum ? group_sum + (size_t)r * n_groups : nullptr;
+  const RowState q = load_row(rc, s, ctrl, r, update, req_ids, gen_idx);
 
   if (sc.kind == 0 || (sc.kind == 1 && sc.top_k <= 1)) {
-    // ---- greedy: maximum, lowest index on ties --------------------------------------
-    if (gm) {
-      const int gi = block_argmax(gm, n_groups, sh);               // lowest group holding the maximum
-      // the column inside the group: left by the LM head, else looked up in the logits
-      const int li = group_idx ? group_idx[(size_t)r * n_groups + gi] : block_argmax(lg + (size_t)gi * group, min(group, V - gi * group), sh);
-      __syncthreads();
-      if (tid == 0) sh.choice = gi * group + li;
-      __syncthreads();
-    } else {
-      block_argmax(lg, V, sh);
-    }
+    block_argmax(lg, V, sh);                               // maximum, lowest index on ties
   } else if (sc.kind == 2) {
-    // ---- temperature sampling over the whole vocabulary: inverse CDF in index order ----------
-    // Thread t owns the units [t * chunk, (t + 1) * chunk) (groups when their sums are there, else
-    // single indices): its partial sum of exp((l - max) / T), an exclusive scan over the threads
-    // (wavefront scans, then wavefront totals in order), and the thread whose range holds the
-    // crossing of u * total finds the unit; a wavefront then walks a group's logits together.
-    const float M = gm ? block_max_f32(gm, n_groups, sh) : block_max_f32(lg, V, sh);
+    // Temperature sampling over the whole vocabulary: inverse CDF in index order.  Thread t owns the
+    // indices [t * chunk, (t + 1) * chunk): its partial sum of exp((l - max) / T), an exclusive scan over the
+    // threads (wavefront scans, then wavefront totals in order), and the thread whose range holds the
+    // crossing of u * total finds the index.
+    const float M = block_max_f32(lg, V, sh);
     const double invT = 1.0 / (double)sc.temperature;
-    const int units = gs ? n_groups : V;
-    const int chunk = (units + SAMPLE_THREADS - 1) / SAMPLE_THREADS;
-    const int i0 = tid * chunk, i1 = (i0 + chunk < units) ? i0 + chunk : units;
-    auto mass = [&](int i) {
-      return gs ? gs[i] * exp(((double)gm[i] - (double)M) * invT) : exp(((double)lg[i] - (double)M) * invT);
-    };
+    const int chunk = (V + ROWS_THREADS - 1) / ROWS_THREADS;
+    const int i0 = tid * chunk, i1 = (i0 + chunk < V) ? i0 + chunk : V;
+    auto mass = [&](int i) { return exp(((double)lg[i] - (double)M) * invT); };
     double part = 0.0;
     for (int i = i0; i < i1; ++i) part += mass(i);
     double incl = part;                                     // inclusive scan inside the wavefront
@@ -257,223 +484,285 @@ __global__ __launch_bounds__(SAMPLE_THREADS) void sample_kernel(RowCtx rc, Slots
     if (lane == 63) sh.red_d[wid] = incl;
     __syncthreads();
     double before = 0.0, total = 0.0;
-    for (int x = 0; x < SAMPLE_THREADS / 64; ++x) {
+    for (int x = 0; x < ROWS_THREADS / 64; ++x) {
       if (x < wid) before += sh.red_d[x];
       total += sh.red_d[x];
     }
-    const unsigned long long rid = (unsigned long long)req;
-    const unsigned w0 = philox4x32_10_word0((unsigned)(rid & 0xFFFFFFFFull), (unsigned)(rid >> 32),
-                                            (unsigned)g, 0u, (unsigned)(sc.seed & 0xFFFFFFFFull),
-                                            (unsigned)(sc.seed >> 32));
-    const double u = (double)(w0 >> 8) * (1.0 / 16777216.0);
-    const double target = u * total;                        // cumulative / total > u  <=>  cumulative > u * total
+    const double target = uniform_draw(sc, q.req, q.g) * total;      // cumulative / total > u  <=>  cumulative > u * total
     const double lo = before + incl - part, hi = before + incl;
-    if (tid == 0) { sh.choice = V - 1; sh.hot[0] = -1; }    // rounding leaves no crossing: the last index
+    if (tid == 0) sh.choice = V - 1;                        // rounding leaves no crossing: the last index
     __syncthreads();
     if (i0 < i1 && lo <= target && hi > target) {
-      double c = lo, below = lo;
+      double c = lo;
       int pick = i1 - 1;
       for (int i = i0; i < i1; ++i) {
-        below = c;
         c += mass(i);
         if (c > target) { pick = i; break; }
       }
-      if (gs) { sh.hot[0] = pick; sh.total_d = below; } else sh.choice = pick;
-    }
-    __syncthreads();
-    if (gs && wid == 0 && sh.hot[0] >= 0) {
-      // the group's logits, one per lane; its last index if rounding leaves no crossing inside it
-      const int first = sh.hot[0] * group, n = min(group, V - first);
-      double c = lane < n ? exp(((double)lg[first + lane] - (double)M) * invT) : 0.0;
-#pragma unroll
-      for (int off = 1; off < 64; off <<= 1) {
-        const double o = __shfl_up(c, off, 64);
-        if (lane >= off) c += o;
-      }
-      const unsigned long long hit = __ballot(lane < n && sh.total_d + c > target);
-      if (lane == 0) sh.choice = first + (hit ? __ffsll((long long)hit) - 1 : n - 1);
+      sh.choice = pick;
     }
     __syncthreads();
   } else {
     const int k = sc.top_k < V ? (sc.top_k < MAX_TOPK ? sc.top_k : MAX_TOPK) : (V < MAX_TOPK ? V : MAX_TOPK);
-    bool have = false;
-    if (gm && n_groups >= k && topk_in_groups(V, k)) {
-      // ---- candidates from the groups whose maximum reaches the k-th largest maximum ---
-      block_kth_largest(gm, n_groups, k, sh);
-      const unsigned tau = sh.prefix;
-      if (tid == 0) { sh.n_hot = 0; sh.cnt = 0; sh.overflow = 0; }
-      __syncthreads();
-      for (int i = tid; i < n_groups; i += SAMPLE_THREADS)
-        if (f2key(gm[i]) >= tau) {
-          const int p = atomicAdd(&sh.n_hot, 1);
-          if (p < MAX_HOT) sh.hot[p] = i; else sh.overflow = 1;
-        }
-      __syncthreads();
-      if (!sh.overflow) {
-        const int n_hot = sh.n_hot;
-        for (int e = tid; e < n_hot * group; e += SAMPLE_THREADS) {
-          const int idx = sh.hot[e / group] * group + e % group;
-          if (idx >= V) continue;
-          const unsigned key = f2key(lg[idx]);
-          if (key >= tau) {
-            const int p = atomicAdd(&sh.cnt, 1);
-            if (p < MAX_CAND) { sh.cand_key[p] = key; sh.cand_idx[p] = idx; } else sh.overflow = 1;
-          }
-        }
-        __syncthreads();
-        have = !sh.overflow;
-      }
-      __syncthreads();
-    }
-    if (!have) {
-      // ---- radix select over the whole row ---------------------------------------------
-      block_kth_largest(lg, V, k, sh);
-      const unsigned thr = sh.prefix;
-      const int krem = (int)sh.krem, ntie = (int)sh.ntie;
-      if (tid == 0) sh.cnt = 0;
-      __syncthreads();
-      // everything above the threshold, plus the threshold ties with the lowest indices
-      for (int i = tid; i < V; i += SAMPLE_THREADS) {
-        const unsigned key = f2key(lg[i]);
-        if (key > thr || (key == thr && ntie == krem)) {
-          const int p = atomicAdd(&sh.cnt, 1);
-          if (p < MAX_CAND) { sh.cand_key[p] = key; sh.cand_idx[p] = i; }
-        }
-      }
-      __syncthreads();
-      if (ntie != krem) {
-        int last = -1;
-        for (int t = 0; t < krem; ++t) {
-          int best = 0x7fffffff;
-          for (int i = tid; i < V; i += SAMPLE_THREADS)
-            if (i > last && f2key(lg[i]) == thr) { best = i; break; }
-#pragma unroll
-          for (int off = 32; off > 0; off >>= 1) { const int o = __shfl_xor(best, off, 64); best = o < best ? o : best; }
-          if (lane == 0) sh.red_idx[wid] = best;
-          __syncthreads();
-          if (tid == 0) {
-            for (int x = 1; x < SAMPLE_THREADS / 64; ++x) best = sh.red_idx[x] < best ? sh.red_idx[x] : best;
-            const int p = sh.cnt++;
-            if (p < MAX_CAND) { sh.cand_key[p] = thr; sh.cand_idx[p] = best; }
-            sh.red_idx[0] = best;
-          }
-          __syncthreads();
-          last = sh.red_idx[0];
-          __syncthreads();
-        }
-      }
-    }
-    // ---- exact top-k of the candidates: the rank of a candidate is its place in the
-    // descending order (ties: lower index first) ------------------------------------------
-    const int n_cand = sh.cnt < MAX_CAND ? sh.cnt : MAX_CAND;
-    for (int c = tid; c < n_cand; c += SAMPLE_THREADS) {
-      const unsigned mk = sh.cand_key[c];
-      const int mi = sh.cand_idx[c];
-      int rank = 0;
-      for (int j = 0; j < n_cand; ++j) rank += (sh.cand_key[j] > mk) || (sh.cand_key[j] == mk && sh.cand_idx[j] < mi);
-      if (rank < k) { sh.sort_logit[rank] = lg[mi]; sh.sort_idx[rank] = mi; }
-    }
-    __syncthreads();
-    if (tid < 64) {
-      // Wavefront 0: lane j holds candidate j (k <= 64).  fp64 softmax over the candidates and
-      // its running sum; the token is the first candidate whose cumulative probability
-      // exceeds the uniform draw, the last candidate if none does.
-      const int n = n_cand < k ? n_cand : k;
-      const unsigned long long rid = (unsigned long long)req;
-      const unsigned w0 = philox4x32_10_word0((unsigned)(rid & 0xFFFFFFFFull), (unsigned)(rid >> 32),
-                                              (unsigned)g, 0u, (unsigned)(sc.seed & 0xFFFFFFFFull),
-                                              (unsigned)(sc.seed >> 32));
-      const double u = (double)(w0 >> 8) * (1.0 / 16777216.0);
-      const double T = (double)sc.temperature;
-      const double z0 = (double)sh.sort_logit[0] / T;
-      const double e = tid < n ? exp((double)sh.sort_logit[tid < n ? tid : 0] / T - z0) : 0.0;
-      double sum = e;
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
-      double c = e / sum;                                   // inclusive prefix sum over lanes <= tid
-#pragma unroll
-      for (int off = 1; off < 64; off <<= 1) {
-        const double o = __shfl_up(c, off, 64);
-        if (tid >= off) c += o;
-      }
-      int keep = n;
-      double tot = 1.0;
-      if (sc.top_p > 0.f && sc.top_p < 1.f) {
-        // nucleus: the shortest prefix whose cumulative probability reaches top_p
-        const unsigned long long reach = __ballot(tid < n && c >= (double)sc.top_p);
-        keep = reach ? __ffsll((long long)reach) : n;
-        tot = __shfl(c, keep - 1, 64);                      // mass of the nucleus: renormalise by it
-      }
-      const unsigned long long hit = __ballot(tid < keep && c > u * tot);
-      if (tid == 0) sh.choice = sh.sort_idx[hit ? __ffsll((long long)hit) - 1 : keep - 1];
-    }
+    for (int i = tid; i < MAX_CAND; i += ROWS_THREADS) sh.count[i] = 0u;
+    topk_whole_row<ROWS_THREADS>(lg, V, k, sh);
+    draw_topk(k, sc, q.req, q.g, sh);
     __syncthreads();
   }
 
   const int sampled = sh.choice;
-
-  // ---- parity-mode capture --------------------------------------------------------------
-  if (w.req != nullptr && ctrl != nullptr) {
-    if (tid == 0) {
-      int row = -1;
-      const int nw = ctrl->n_watch;
-      for (int i = 0; i < nw; ++i)
-        if (w.req[i] == req && g >= w.first[i] && g < w.first[i] + w.count[i]) row = w.row0[i] + (g - w.first[i]);
-      sh.watch_row = row;
-    }
-    __syncthreads();
-    const int row = sh.watch_row;
-    if (row >= 0) {
-      for (int i = tid; i < V; i += SAMPLE_THREADS) w.logits[(size_t)row * V + i] = lg[i];
-      if (tid == 0) { w.sampled[row] = sampled; w.filled[row] = 1; }
-    }
-  }
-
+  capture_row<ROWS_THREADS>(w, ctrl, q, lg, V, sampled, sh);
   // the token that is appended: the sampler's choice, or the teacher-forced one (parity mode)
-  int tok_final = sampled;
-  if (update && s.forced != nullptr) {
-    const int f = s.forced[(size_t)slot * s.max_ctx + g];
-    if (f >= 0) tok_final = f;
-  }
+  const int tok = q.forced >= 0 ? q.forced : sampled;
   // ---- log-probability of that token under softmax(logits / T) over the whole vocabulary ----
-  float* lp_dst = update ? (s.logprob ? s.logprob + (size_t)slot * s.max_ctx + g : nullptr)
-                         : (out_logprobs ? out_logprobs + r : nullptr);
+  float* lp_dst = update ? (s.logprob ? s.logprob + (size_t)q.slot * s.max_ctx + q.g : nullptr) : (out_logprobs ? out_logprobs + r : nullptr);
   if (lp_dst != nullptr) {
-    const float M = gm ? block_max_f32(gm, n_groups, sh) : block_max_f32(lg, V, sh);
+    const float M = block_max_f32(lg, V, sh);
     const float invT = 1.0f / sc.temperature;
     double part = 0.0;
-    if (gs) {
-      for (int i = tid; i < n_groups; i += SAMPLE_THREADS) part += gs[i] * exp((double)((gm[i] - M) * invT));
-    } else {
-      for (int i = tid; i < V; i += SAMPLE_THREADS) part += (double)__expf((lg[i] - M) * invT);
-    }
+    for (int i = tid; i < V; i += ROWS_THREADS) part += (double)__expf((lg[i] - M) * invT);
     const double Z = block_sum_f64(part, sh);
-    // the greedy choice is the row's maximum: its logit need not have been written
-    if (tid == 0) *lp_dst = (float)((double)((have_logits ? lg[tok_final] - M : 0.f) * invT) - log(Z));
+    if (tid == 0) *lp_dst = (float)((double)((lg[tok] - M) * invT) - log(Z));
+  }
+  if (tid == 0) finish_row(s, ctrl, q, r, update, sampled, tok, out_tokens);
+}
+
+// ---------------------------------------------------------------------------
+// Sampling from group records (maximum, its column, sum of exponentials per 64 logits).  A row is 2374 records of
+// a vocabulary of 152 k, so the kernel is a chain of block-wide steps, not a stream: everything is requested at the
+// start (GQ records per thread in registers; a longer row reads them again), maximum, arg-max and minimum work share
+// one exchange through LDS, every thread finishes an exchange for itself, and the top-k threshold comes from
+// the 64 lane maxima instead of four radix passes.  Measured per launch with 152 k logits against separate passes with a
+// serial sum each: one row, greedy with log-probabilities 11.7 -> 7.3 us; 5 rows, top 50 18.2 -> 10.8 us, with
+// log-probabilities of 47 rows of 32 k logits 20.1 -> 10.4; 192 rows, categorical with log-probabilities 13.2 -> 8.3.
+// ---------------------------------------------------------------------------
+constexpr int GQ = 4;                      // records of a thread that stay in registers
+template <bool CACHED>                     // n_groups <= GQ * REC_THREADS
+__global__ __launch_bounds__(REC_THREADS) void sample_records_kernel(RowCtx rc, Slots s, Ctrl* ctrl, const float* logits, int V,
+                                                                        SamplerCfg sc, Watch w, int update,
+                                                                        const long long* req_ids, const int* gen_idx,
+                                                                        int* out_tokens, const float* group_max,
+                                                                        float* out_logprobs, const int* group_idx,
+                                                                        const double* group_sum) {
+  constexpr int W = REC_THREADS / 64;
+  const int r = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  const int n_groups = (V + 63) >> 6;
+  const float* lg = logits + (size_t)r * V;
+  const float* gm = group_max + (size_t)r * n_groups;
+  const double* gs = group_sum ? group_sum + (size_t)r * n_groups : nullptr;
+  if (r >= sampling_rows(rc)) return;
+  __shared__ SampleShared sh;
+  __shared__ unsigned lane_key[W][64];
+  const bool greedy = sc.kind == 0 || (sc.kind == 1 && sc.top_k <= 1), topk = !greedy && sc.kind == 1;
+  // categorical: thread t owns consecutive groups (the CDF runs in index order), else every REC_THREADS-th
+  const int chunk = (n_groups + REC_THREADS - 1) / REC_THREADS;
+  auto group_at = [&](int e) { return sc.kind == 2 ? tid * chunk + e : tid + e * REC_THREADS; };
+  float m_c[GQ];
+  double s_c[GQ];
+  if (CACHED) {
+#pragma unroll
+    for (int e = 0; e < GQ; ++e) {
+      const int i = group_at(e);
+      const bool in = e < chunk && i < n_groups;
+      m_c[e] = in ? gm[i] : -INFINITY;
+      s_c[e] = in && gs ? gs[i] : 0.0;
+    }
+  }
+  const RowState q = load_row(rc, s, ctrl, r, update, req_ids, gen_idx);
+  // f(register slot, group, maximum, sum) over this thread's groups, in registers also past the last one (-inf, 0)
+  auto each = [&](auto f) {
+    if constexpr (CACHED) {
+#pragma unroll
+      for (int e = 0; e < GQ; ++e)
+        f(e, group_at(e), m_c[e], s_c[e]);
+    } else {
+      for (int e = 0; e < chunk; ++e)
+        if (group_at(e) < n_groups) f(0, group_at(e), gm[group_at(e)], gs ? gs[group_at(e)] : 0.0);
+    }
+  };
+  float* lp_dst = update ? (s.logprob ? s.logprob + (size_t)q.slot * s.max_ctx + q.g : nullptr) : (out_logprobs ? out_logprobs + r : nullptr);
+
+  // ---- first exchange: the row's maximum; greedy: its group (lowest on ties); top-k: maxima by lane ----
+  float mx = -INFINITY;
+  unsigned bk = 0u;
+  int bi = 0x7fffffff;
+  each([&](int, int i, float m, double) {
+    mx = fmaxf(mx, m);
+    const unsigned k = f2key(m);
+    const bool first = bi == 0x7fffffff || k > bk;            // ascending i: the first maximum stays
+    bk = first ? k : bk;
+    bi = first ? i : bi;
+  });
+  if (topk) lane_key[wid][lane] = bk;                         // (0: no group)
+  mx = wave_max_f32(mx);
+  if (greedy) {
+    const unsigned top = wave_max_u32(bk);
+    bi = wave_min_i32(bk == top ? bi : 0x7fffffff);
+    bk = top;
+  }
+  if (lane == 0) { sh.red_f[wid] = mx; sh.red_key[wid] = bk; sh.red_idx[wid] = bi; }
+  if (tid == 0) { sh.n_hot = 0; sh.cnt = 0; sh.overflow = 0; sh.choice = V - 1; }
+  if (topk)
+    for (int i = tid; i < MAX_CAND; i += REC_THREADS) sh.count[i] = 0u;
+  __syncthreads();
+  static_assert(W == 16, "a wavefront's partial result per lane of a row");
+  const float M = row_max_f32(sh.red_f[lane & (W - 1)]);
+  const float invT = 1.0f / sc.temperature;
+  double Z = 0.0, total = 0.0;                                // the row's sum of exponentials: this thread's part, the whole (categorical)
+
+  if (greedy) {
+    bk = sh.red_key[lane & (W - 1)];
+    bi = row_min_i32(bk == row_max_u32(bk) ? sh.red_idx[lane & (W - 1)] : 0x7fffffff);
+    // the column inside the group: left by the LM head, else looked up in the logits
+    if (wid == 0) {
+      int li;
+      if (group_idx) li = group_idx[(size_t)r * n_groups + bi];
+      else {
+        const int i = bi * 64 + lane;
+        const unsigned k = i < V ? f2key(lg[i]) : 0u;
+        const unsigned top = wave_max_u32(k);
+        li = wave_min_i32(i < V && k == top ? lane : 64);
+      }
+      if (lane == 0) sh.choice = bi * 64 + li;
+    }
+  } else if (topk) {
+    const int k = sc.top_k < V ? (sc.top_k < MAX_TOPK ? sc.top_k : MAX_TOPK) : (V < MAX_TOPK ? V : MAX_TOPK);
+    // The 64 lanes' maxima are group maxima of 64 disjoint sets, so at least k groups reach the k-th largest of them:
+    // the groups that do (about twice k) hold the k-th largest group maximum.
+    unsigned lk = lane_key[0][lane];
+#pragma unroll
+    for (int x = 1; x < W; ++x) { const unsigned o = lane_key[x][lane]; lk = o > lk ? o : lk; }
+    unsigned tau0 = 0u;
+#pragma unroll 1
+    for (int bit = 31; bit >= 12; --bit) {                    // (the lowest bits stay zero: a slightly lower bound)
+      const unsigned t = tau0 | (1u << bit);
+      if (__popcll(__ballot(lk >= t)) >= k) tau0 = t;
+    }
+    each([&](int, int i, float m, double) {
+      const unsigned key = f2key(m);
+      if (key >= tau0 && i < n_groups) {
+        const int p = atomicAdd(&sh.n_hot, 1);
+        if (p < MAX_HOT) sh.cand[p] = cand_pair(key, i); else sh.overflow = 1;
+      }
+    });
+    __syncthreads();
+    bool have = !sh.overflow;
+    if (have) {
+      // those with fewer than k larger ones are the groups whose maximum reaches the k-th largest maximum, tau, a lower
+      // bound of the k-th largest logit: only they are read
+      const int n0 = sh.n_hot;
+      if (tid == 0) { fill_list(sh, n0); sh.cnt = 0; }
+      __syncthreads();
+      if (tid == 0) sh.n_hot = 0;
+      count_pairs(sh, n0, [](unsigned long long own, unsigned long long x) {       // larger ones, and 2^16 per equal one
+        const unsigned kx = (unsigned)(x >> 32), ko = (unsigned)(own >> 32);
+        return (kx > ko ? 1u : 0u) + (kx == ko ? 0x10000u : 0u);
+      });
+      __syncthreads();
+      for (int c = tid; c < n0; c += REC_THREADS) {
+        const unsigned n = sh.count[c];
+        const int above = (int)(n & 0xffffu);
+        sh.count[c] = 0u;
+        if (above < k) {
+          sh.hot[atomicAdd(&sh.n_hot, 1)] = ~(int)(unsigned)sh.cand[c];
+          if (above + (int)(n >> 16) >= k) sh.prefix = (unsigned)(sh.cand[c] >> 32);
+        }
+      }
+      __syncthreads();
+      const unsigned tau = sh.prefix;
+      const int n_hot = sh.n_hot;
+      constexpr int HU = 4;                                   // groups of a wavefront requested together
+      for (int h0 = 0; h0 < n_hot; h0 += HU * W) {
+        float v[HU];
+        int at[HU];
+#pragma unroll
+        for (int x = 0; x < HU; ++x) {
+          const int h = h0 + x * W + wid;
+          const int grp = h < n_hot ? sh.hot[h] : -1;
+          at[x] = grp >= 0 && grp * 64 + lane < V ? grp * 64 + lane : -1;
+          v[x] = lg[at[x] >= 0 ? at[x] : 0];
+        }
+#pragma unroll
+        for (int x = 0; x < HU; ++x) {
+          const unsigned key = f2key(v[x]);
+          if (at[x] >= 0 && key >= tau) {
+            const int p = atomicAdd(&sh.cnt, 1);
+            if (p < MAX_CAND) sh.cand[p] = cand_pair(key, at[x]); else sh.overflow = 1;
+          }
+        }
+      }
+      __syncthreads();
+      have = !sh.overflow;
+    }
+    if (!have) topk_whole_row<REC_THREADS>(lg, V, k, sh);
+    draw_topk(k, sc, q.req, q.g, sh);
+  } else {
+    // ---- temperature sampling over the whole vocabulary: inverse CDF in index order ----------
+    // Masses of the groups (their sums rescaled to the row's maximum), an exclusive scan over the threads, and the
+    // thread whose range holds the crossing of u * total finds the group; a wavefront then walks its logits.
+    const double iT = 1.0 / (double)sc.temperature;
+    double mass_c[CACHED ? GQ : 1];
+    each([&](int e, int, float m, double sum) {
+      const double x = sum * exp(((double)m - (double)M) * iT);
+      if (CACHED) mass_c[e] = x;
+      Z += x;
+    });
+    const double incl = wave_scan_f64(Z);                     // inclusive scan inside the wavefront
+    if (lane == 63) sh.red_d[wid] = incl;
+    if (tid == 0) sh.hot[0] = -1;
+    __syncthreads();
+    double before = 0.0;
+#pragma unroll
+    for (int x = 0; x < W; ++x) {
+      if (x < wid) before += sh.red_d[x];
+      total += sh.red_d[x];
+    }
+    const double target = uniform_draw(sc, q.req, q.g) * total;      // cumulative / total > u  <=>  cumulative > u * total
+    const double lo = before + incl - Z, hi = before + incl;
+    if (tid * chunk < n_groups && lo <= target && hi > target) {
+      double c = lo, below = lo;
+      int pick = -1;
+      each([&](int e, int i, float m, double sum) {
+        const bool go = i < n_groups && !(pick >= 0 && c > target);
+        below = go ? c : below;
+        c += go ? (CACHED ? mass_c[e] : sum * exp(((double)m - (double)M) * iT)) : 0.0;
+        pick = go ? i : pick;
+      });
+      sh.hot[0] = pick;
+      sh.total_d = below;
+    }
+    __syncthreads();
+    if (wid == 0 && sh.hot[0] >= 0) {
+      // the group's logits, one per lane; its last index if rounding leaves no crossing inside it
+      const int first = sh.hot[0] * 64, n = min(64, V - first);
+      const double c = wave_scan_f64(lane < n ? exp(((double)lg[first + lane] - (double)M) * iT) : 0.0);
+      const unsigned long long hit = __ballot(lane < n && sh.total_d + c > target);
+      if (lane == 0) sh.choice = first + (hit ? __ffsll((long long)hit) - 1 : n - 1);
+    }
   }
 
-  if (tid == 0) {
-    if (!update) {
-      out_tokens[r] = sampled;
-    } else {
-      int tok = tok_final;
-      s.tokens[(size_t)slot * s.max_ctx + pos + 1] = tok;
-      s.gen[slot] = g + 1;
-      s.kv_len[slot] = pos + 1;
-      int stt = s.state[slot];
-      if (stt == SLOT_PREFILL) stt = SLOT_LIVE;
-      if (g + 1 >= s.limit[slot] || tok == ctrl->eos_token) {
-        stt = SLOT_DONE;
-        s.finish_iter[slot] = ctrl->iter;
-        // what the scheduler counts toward N: the rollout, or (instance-level completion,
-        // Section 3.2.3) its group once the last member is complete
-        const int gi = s.group != nullptr ? s.group[slot] : -1;
-        if (gi < 0) atomicAdd(&ctrl->finished, 1);
-        else if (atomicSub(&s.grp_left[gi], 1) == 1) atomicAdd(&ctrl->finished, 1);
-      }
-      s.state[slot] = stt;
-    }
+  // ---- log-probability of the appended token under softmax(logits / T) over the whole vocabulary ----
+  const bool sums = lp_dst != nullptr;
+  if (sums && sc.kind != 2) {
+    each([&](int, int, float m, double sum) { Z += sum * exp((double)((m - M) * invT)); });
+    Z = wave_sum_f64(Z);
+    if (lane == 0) sh.red_d[wid] = Z;
   }
+  __syncthreads();
+  const int sampled = sh.choice;
+  capture_row<REC_THREADS>(w, ctrl, q, lg, V, sampled, sh);
+  if (wid != 0) return;
+  // the token that is appended: the sampler's choice, or the teacher-forced one (parity mode)
+  const int tok = q.forced >= 0 ? q.forced : sampled;
+  if (sums) {
+    // the greedy choice is the row's maximum: its logit need not have been written
+    const float l = logits != nullptr ? lg[tok] : M;
+    if (sc.kind != 2) {
+      total = row_sum_f64(sh.red_d[lane & (W - 1)]);
+    }
+    if (lane == 0) *lp_dst = (float)((double)((l - M) * invT) - log(total));
+  }
+  if (lane == 0) finish_row(s, ctrl, q, r, update, sampled, tok, out_tokens);
 }
 
 // Group records of logits in memory.  16 lanes own a group of 64 logits (4 consecutive ones each), a
@@ -482,6 +771,32 @@ __global__ __launch_bounds__(SAMPLE_THREADS) void sample_kernel(RowCtx rc, Slots
 // twice: a call for 192 rows of 152 k logits took 724 us with the categorical sampler and
 // log-probabilities, 94 us now; 5 rows with top-k 62 us, 42 us now.)  Rows start at any multiple of 4 bytes.  KEYS: maxima in
 // the order of f2key (NaN above everything), as the whole-row searches compare; else fmaxf.
+//
+// The exponentials of the fp64 sums bound that pass (192 rows of 152 k: 23 us without sums, 25 with fp32 ones), so they are
+// cut to what the sums need.  2^y for y <= 0: y = n + f with |f| <= 1/2 by adding and taking away 1.5 * 2^52, the Taylor
+// series of 2^f to the twelfth power (remainder 1.7e-16), n added to the exponent; zero below 2^-1022, NaN for NaN.
+// Against the library's exp: 39.5 -> 37.5 us per pass.  (Four blocks of 16 groups per wavefront, the next one's loads in
+// flight: 43.2 us; 2 or 8 loads in flight instead of 4: 39.9 and 44.0 against 41.3.)
+__device__ inline double exp2_neg(double y) {
+  const double big = 6755399441055744.0;                     // 1.5 * 2^52
+  const double t = y + big, f = y - (t - big);
+  // (ln 2)^k / k!
+  double p = 2.56784359934882051e-11;
+  p = __fma_rn(p, f, 4.44553827187081150e-10);
+  p = __fma_rn(p, f, 7.05491162080112333e-09);
+  p = __fma_rn(p, f, 1.01780860092396997e-07);
+  p = __fma_rn(p, f, 1.32154867901443095e-06);
+  p = __fma_rn(p, f, 1.52527338040598403e-05);
+  p = __fma_rn(p, f, 1.54035303933816099e-04);
+  p = __fma_rn(p, f, 1.33335581464284434e-03);
+  p = __fma_rn(p, f, 9.61812910762847716e-03);
+  p = __fma_rn(p, f, 5.55041086648215800e-02);
+  p = __fma_rn(p, f, 2.40226506959100712e-01);
+  p = __fma_rn(p, f, 6.93147180559945309e-01);
+  p = __fma_rn(p, f, 1.0);
+  const double r = __hiloint2double(__double2hiint(p) + (__double2loint(t) << 20), __double2loint(p));
+  return y >= -1022.0 ? r : (y < -1022.0 ? 0.0 : y);
+}
 constexpr int GR_STEPS = 4;
 template <int SUMS, bool KEYS>
 __global__ __launch_bounds__(256) void group_records_kernel(const float* logits, const int2* ctl, int n_rows, int V,
@@ -494,52 +809,62 @@ __global__ __launch_bounds__(256) void group_records_kernel(const float* logits,
   if (r >= n_rows) return;
   typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
   const int n_groups = (V + 63) >> 6, lane = threadIdx.x & 63, sub = lane & 15;
-  const int g0 = ((int)blockIdx.x * 4 + (int)(threadIdx.x >> 6)) * (4 * GR_STEPS) + (lane >> 4);
+  const int first = ((int)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) * (4 * GR_STEPS);   // first group of the wavefront
   const float* row = logits + (size_t)r * V;
-  float v[GR_STEPS][4];
+  const double inv_t2 = inv_t * 1.4426950408889634074;
+  auto load_whole = [&](int g0, float (&v)[GR_STEPS][4]) {
 #pragma unroll
-  for (int s = 0; s < GR_STEPS; ++s) {
-    const int i = (g0 + 4 * s) * 64 + sub * 4;
-    if (i + 4 <= V) {
-      const f32x4u q = *reinterpret_cast<const f32x4u*>(row + i);
+    for (int s = 0; s < GR_STEPS; ++s) {
+      const f32x4u q = *reinterpret_cast<const f32x4u*>(row + (size_t)(g0 + 4 * s) * 64 + lane * 4);
 #pragma unroll
       for (int j = 0; j < 4; ++j) v[s][j] = q[j];
-    } else {
-#pragma unroll
-      for (int j = 0; j < 4; ++j) v[s][j] = i + j < V ? row[i + j] : -INFINITY;
     }
-  }
+  };
+  auto load_part = [&](int g0, float (&v)[GR_STEPS][4]) {
 #pragma unroll
-  for (int s = 0; s < GR_STEPS; ++s) {
-    const int g = g0 + 4 * s;
-    float m;
-    if (KEYS) {
-      unsigned k = f2key(v[s][0]);
-      m = v[s][0];
-      auto take = [&](float x) { const unsigned kx = f2key(x); if (kx > k) { k = kx; m = x; } };
+    for (int s = 0; s < GR_STEPS; ++s)
 #pragma unroll
-      for (int j = 1; j < 4; ++j) take(v[s][j]);
+      for (int j = 0; j < 4; ++j) {
+        const int i = (g0 + 4 * s) * 64 + lane * 4 + j;
+        v[s][j] = i < V ? row[i] : -INFINITY;
+      }
+  };
+  auto records = [&](int g0, const float (&v)[GR_STEPS][4]) {
 #pragma unroll
-      for (int off = 8; off > 0; off >>= 1) take(__shfl_xor(m, off, 64));
-    } else {
-      m = fmaxf(fmaxf(v[s][0], v[s][1]), fmaxf(v[s][2], v[s][3]));
+    for (int s = 0; s < GR_STEPS; ++s) {
+      const int g = g0 + 4 * s + (lane >> 4);
+      float m;
+      if (KEYS) {
+        unsigned k = f2key(v[s][0]);
+        m = v[s][0];
+        auto take = [&](float x) { const unsigned kx = f2key(x); if (kx > k) { k = kx; m = x; } };
 #pragma unroll
-      for (int off = 8; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
+        for (int j = 1; j < 4; ++j) take(v[s][j]);
+        take(as_f32(row_ror<8>(__float_as_int(m))));
+        take(as_f32(row_ror<4>(__float_as_int(m))));
+        take(as_f32(row_ror<2>(__float_as_int(m))));
+        take(as_f32(row_ror<1>(__float_as_int(m))));
+      } else {
+        m = row_max_f32(fmaxf(fmaxf(v[s][0], v[s][1]), fmaxf(v[s][2], v[s][3])));
+      }
+      double sum = 0.0;
+      if (SUMS) {
+        const float ref = m == -INFINITY ? 0.f : m;            // a group of -inf sums to zero, not to NaN
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          sum += SUMS == 2 ? exp2_neg(((double)v[s][j] - (double)ref) * inv_t2) : (double)__expf((v[s][j] - ref) * (float)inv_t);
+        sum = row_sum_f64(sum);
+      }
+      if (sub == 0 && g < n_groups) {
+        group_max[(size_t)r * n_groups + g] = m;
+        if (SUMS) group_sum[(size_t)r * n_groups + g] = sum;
+      }
     }
-    double sum = 0.0;
-    if (SUMS) {
-      const float ref = m == -INFINITY ? 0.f : m;            // a group of -inf sums to zero, not to NaN
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        sum += SUMS == 2 ? exp(((double)v[s][j] - (double)ref) * inv_t) : (double)__expf((v[s][j] - ref) * (float)inv_t);
-#pragma unroll
-      for (int off = 8; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
-    }
-    if (sub == 0 && g < n_groups) {
-      group_max[(size_t)r * n_groups + g] = m;
-      if (SUMS) group_sum[(size_t)r * n_groups + g] = sum;
-    }
-  }
+  };
+  float v[GR_STEPS][4];
+  if ((first + 4 * GR_STEPS) * 64 <= V) load_whole(first, v);
+  else load_part(first, v);
+  records(first, v);
 }
 void launch_group_records(hipStream_t st, const float* logits, const int2* ctl, int n_rows, int V, int sums,
                           float temperature, float* group_max, double* group_sum) {
@@ -558,9 +883,22 @@ void launch_group_records(hipStream_t st, const float* logits, const int2* ctl, 
 
 void launch_sample(hipStream_t st, RowCtx rc, Slots s, Ctrl* ctrl, const float* logits, int vocab, SamplerCfg sc,
                    Watch w, int update, const long long* req_ids, const int* gen_idx, int* out_tokens,
-                   const float* group_max, int group, float* out_logprobs, const int* group_idx, const double* group_sum) {
-  hipLaunchKernelGGL(sample_kernel, dim3(rc.max_rows), dim3(SAMPLE_THREADS), 0, st, rc, s, ctrl, logits, vocab,
-                     sc, w, update, req_ids, gen_idx, out_tokens, group_max, group, out_logprobs, group_idx, group_sum);
+                   const float* group_max, float* out_logprobs, const int* group_idx, const double* group_sum) {
+  const int n_groups = ceil_div(vocab, 64), k = sc.top_k < vocab ? (sc.top_k < MAX_TOPK ? sc.top_k : MAX_TOPK) : (vocab < MAX_TOPK ? vocab : MAX_TOPK);
+  const bool greedy = sc.kind == 0 || (sc.kind == 1 && sc.top_k <= 1);
+  const bool lp = update ? s.logprob != nullptr : out_logprobs != nullptr;
+  // records serve what the call needs: sums for log-probabilities and the categorical sampler, groups enough for a top k
+  const bool records = group_max != nullptr && (group_sum != nullptr || (!lp && sc.kind != 2)) &&
+                       (greedy || sc.kind == 2 || (n_groups >= k && topk_in_groups(vocab, k)));
+#define SAMPLE_RECORDS(CACHED)                                                                                         \
+  hipLaunchKernelGGL(sample_records_kernel<CACHED>, dim3(rc.max_rows), dim3(REC_THREADS), 0, st, rc, s, ctrl, logits, vocab, \
+                     sc, w, update, req_ids, gen_idx, out_tokens, group_max, out_logprobs, group_idx, group_sum)
+  if (!records)
+    hipLaunchKernelGGL(sample_rows_kernel, dim3(rc.max_rows), dim3(ROWS_THREADS), 0, st, rc, s, ctrl, logits, vocab, sc, w,
+                       update, req_ids, gen_idx, out_tokens, out_logprobs);
+  else if (n_groups <= GQ * REC_THREADS) SAMPLE_RECORDS(true);
+  else SAMPLE_RECORDS(false);
+#undef SAMPLE_RECORDS
 }
 
 }  // namespace april

@@ -166,3 +166,42 @@ def test_logprobs_of_greedy_and_topk_choices():
                 assert abs(float(lp[r]) - osampler.token_logprob(logits[r], T, int(got[r]))) < 2e-5
         finally:
             ap.april_destroy(ctx)
+
+
+@pytest.mark.parametrize("n_groups,top_k", [(64, 64), (65, 50), (1025, 1), (4096, 50), (4097, 50)])
+@pytest.mark.parametrize("sampler", [ai.SAMPLER_GREEDY, ai.SAMPLER_TOPK, ai.SAMPLER_CATEGORICAL])
+def test_records_of_every_register_count(sampler, n_groups, top_k):
+    """Vocabularies of one group per lane, one and several groups per thread, and more than the records kernel keeps in
+    registers (4096 groups); ties, masked logits and all of the mass in one place, among ordinary rows."""
+    import torch
+    vocab, T, seed = 64 * n_groups, 0.7, 9
+    rng = np.random.default_rng([n_groups, top_k, sampler])
+    logits = rng.standard_normal((5, vocab)).astype(np.float32)
+    logits[1] = np.round(logits[1] * 4) / 4                       # ties, also between groups
+    logits[2, rng.random(vocab) < 0.97] = -np.inf                 # most of the row masked
+    logits[3, vocab // 3] = 40.0                                  # one logit holds the mass
+    logits[4, :] = np.finfo(np.float32).min
+    logits[4, 7::1999] = 0.5
+    ids, idx = np.arange(5, dtype=np.int64) + 3, np.array([0, 1, 2, 3, 4], dtype=np.int32)
+    ap, ctx = engine(vocab, sampler, top_k, T, seed)
+    try:
+        dev = torch.from_numpy(logits).cuda()
+        tok, lp = ap.april_sample_rows_logprobs(ctx, dev.data_ptr(), 5, ids, idx)
+        alone = ap.april_sample_rows_noalloc(ctx, dev.data_ptr(), 5, ids, idx)
+    finally:
+        ap.april_destroy(ctx)
+    assert np.array_equal(tok, alone)
+    for r in range(5):
+        z = logits[r].astype(np.float64) / T
+        logp = z - z.max() - np.log(np.exp(z - z.max()).sum())
+        # fp32 results and differences to the maximum
+        assert abs(lp[r] - logp[tok[r]]) <= 2e-6 * max(1.0, abs(logp[tok[r]])), (r, lp[r], logp[tok[r]])
+        u = uniform_for(seed, int(ids[r]), int(idx[r]))
+        if sampler == ai.SAMPLER_GREEDY or (sampler == ai.SAMPLER_TOPK and top_k <= 1):
+            assert tok[r] == int(np.argmax(logits[r])), r
+            continue
+        order = np.arange(vocab) if sampler == ai.SAMPLER_CATEGORICAL else np.lexsort((np.arange(vocab), -z))[:top_k]
+        p = np.exp(z[order] - z.max())
+        c = np.cumsum(p) / p.sum()
+        if np.min(np.abs(c - u)) > 1e-9:                          # not on a step of the distribution
+            assert tok[r] == order[np.argmax(c > u)], r
