@@ -29,12 +29,12 @@ double now_s() {
 
 enum KernelClass {
   KC_SCHED = 0, KC_EMBED, KC_NORM, KC_GEMM_QKV, KC_ROPE, KC_ATTN, KC_GEMM_O, KC_GEMM_GATEUP, KC_SILU,
-  KC_GEMM_DOWN, KC_GEMM_LMHEAD, KC_SAMPLE, KC_MOE_ROUTE, KC_MOE_GATEUP, KC_MOE_DOWN, KC_ATTN_MERGE, KC_EVENT_EMPTY, KC_EVENT_NONE, KC_COUNT
+  KC_GEMM_DOWN, KC_GEMM_LMHEAD, KC_SAMPLE, KC_MOE_ROUTE, KC_MOE_GATEUP, KC_MOE_DOWN, KC_ATTN_MERGE, KC_FORWARD_F32, KC_EVENT_EMPTY, KC_EVENT_NONE, KC_COUNT
 };
 static_assert(KC_COUNT <= APRIL_KERNEL_CLASSES, "april_profile_get callers size their arrays with APRIL_KERNEL_CLASSES");
 const char* kKernelNames[KC_COUNT] = {"sched", "embed", "add_rmsnorm", "gemm_qkv", "rope_append", "attn_decode",
                                       "gemm_o", "gemm_gateup", "silu_mul", "gemm_down", "gemm_lmhead", "sample",
-                                      "moe_route", "moe_gateup", "moe_down", "attn_merge", "event_pair_empty_kernel", "event_pair_no_kernel"};
+                                      "moe_route", "moe_gateup", "moe_down", "attn_merge", "forward_f32", "event_pair_empty_kernel", "event_pair_no_kernel"};
 
 struct LayerW {
   float *attn_norm = nullptr, *mlp_norm = nullptr;
@@ -113,6 +113,8 @@ struct april_ctx {
   std::vector<LayerW> layers;
   float* final_norm = nullptr;
   void* lm_head = nullptr;
+  bool f32_rows = false;               // small fp32 model: decode passes run as one launch, a workgroup per row
+  F32Layer* d_f32_layers = nullptr;
   bf16_t* lm_head_s = nullptr;
   int64_t weight_bytes = 0, decode_weight_bytes = 0;
   std::vector<void*> allocs;
@@ -544,6 +546,16 @@ void forward(april_ctx* c, RowCtx rows, RowCtx srows, const int* gather, double 
   const int d = m.d_model, dh = m.head_dim, Hq = m.n_q_heads, Hkv = m.n_kv_heads, F = m.d_ffn, V = m.vocab;
   const int nq = Hq * dh, nkv = Hkv * dh, nqkv = nq + 2 * nkv;
   const double e = (double)c->esz;
+  if (c->f32_rows && gather == nullptr) {
+    {
+      ProfScope p(c, KC_FORWARD_F32, (double)c->decode_weight_bytes + C * 2.0 * m.n_layers * nkv * e + B * V * 4.0, 0);
+      launch_forward_f32(st, rows, c->ds, F32Model{c->d_f32_layers, (const float*)c->tok_emb, c->final_norm, (const float*)c->lm_head,
+                                                   c->rope_cos, c->rope_sin, (float*)c->kv_pool, c->kvl, m.n_layers, d, F, Hq, V, m.rms_eps, 0}, c->logits);
+    }
+    ProfScope p(c, KC_SAMPLE, B * V * 4.0, 0);
+    launch_sample(st, srows, c->ds, c->d_ctrl, c->logits, V, sampler_cfg(c), c->cfg.debug_logits ? c->dwatch : Watch{}, 1, nullptr, nullptr, nullptr, nullptr);
+    return;
+  }
   {
     ProfScope p(c, KC_EMBED, B * d * (2 * e + 4), 0);      // with the first layer's norm
     if (c->bf16) launch_embed_norm<bf16_t, true>(st, rows, c->ds, (const bf16_t*)c->tok_emb, c->x_res, c->layers[0].attn_norm, (bf16_t*)c->h_act, d, m.rms_eps);
@@ -575,6 +587,7 @@ void forward(april_ctx* c, RowCtx rows, RowCtx srows, const int* gather, double 
     if (tile) launch_gemm_tile(st, rc, (const bf16_t*)x, w_s, out, N, K);
     else if (c->use_mfma) launch_gemm_mfma(st, rc, (const bf16_t*)x, w_s, out, N, K, ks, stride, ssq, (int)c->m_cap, m.rms_eps);
     else if (c->bf16) launch_gemm_ref<bf16_t, true>(st, rc, (const bf16_t*)x, (const bf16_t*)w_plain, out, N, K);
+    else if (c->f32_rows) launch_gemm_f32_dot(st, rc, (const float*)x, (const float*)w_plain, out, N, K);
     else launch_gemm_f32(st, rc, (const float*)x, (const float*)w_plain, out, N, K);
   };
   bool normed_by_down = false;       // the previous layer's down projection already did this layer's first norm
@@ -708,6 +721,7 @@ void forward(april_ctx* c, RowCtx rows, RowCtx srows, const int* gather, double 
         launch_gemm_mfma_logits(st, srows, (const bf16_t*)c->hf, c->lm_head_s, lg_out, go, V, d);
     }
     else if (c->bf16) launch_gemm_ref<bf16_t, true>(st, srows, (const bf16_t*)c->hf, (const bf16_t*)c->lm_head, c->logits, V, d);
+    else if (c->f32_rows) launch_gemm_f32_dot(st, srows, (const float*)c->hf, (const float*)c->lm_head, c->logits, V, d);
     else launch_gemm_f32(st, srows, (const float*)c->hf, (const float*)c->lm_head, c->logits, V, d);
   }
   {
@@ -853,6 +867,7 @@ int april_init(const april_model_cfg* cfg, const april_tensor* weights, int32_t 
   c->esz = c->bf16 ? 2 : 4;
   const char* gm = getenv("APRIL_GEMM");
   c->use_mfma = c->bf16 && !(gm && !strcmp(gm, "ref"));
+  c->f32_rows = !c->bf16 && forward_f32_takes(d, F, g.n_q_heads, g.n_kv_heads, g.head_dim, V, g.max_inflight);
   const char* am = getenv("APRIL_ATTN");
   c->attn_mfma = c->bf16 && !(am && !strcmp(am, "ref"));
   if (moe && !(c->use_mfma && c->attn_mfma)) { delete c; return fail(nullptr, APRIL_EINVAL, "routed experts run on the MFMA path only"); }
@@ -900,6 +915,14 @@ int april_init(const april_model_cfg* cfg, const april_tensor* weights, int32_t 
   // ---- weights ------------------------------------------------------------------
   c->alloc_tag = g.pausable ? APRIL_MEM_WEIGHTS : 0;
   { int rc_w = load_weights(c, weights, n_weights); c->alloc_tag = 0; if (rc_w != APRIL_OK) return bail(rc_w); }
+  if (c->f32_rows) {
+    // (outside the weights' region: a pause of the weights drops that region's contents, and the addresses stay)
+    std::vector<F32Layer> fl;
+    for (const LayerW& L : c->layers)
+      fl.push_back(F32Layer{L.attn_norm, L.mlp_norm, (const float*)L.wqkv, (const float*)L.wo, (const float*)L.wgu, (const float*)L.wd});
+    TRY(dev_alloc(c, &c->d_f32_layers, fl.size(), false));
+    HIPTRY(hipMemcpy(c->d_f32_layers, fl.data(), fl.size() * sizeof(F32Layer), hipMemcpyHostToDevice));
+  }
   const size_t e = c->esz;
 
   // ---- scheduler state ------------------------------------------------------------

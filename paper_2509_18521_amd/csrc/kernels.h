@@ -34,6 +34,78 @@ __device__ inline int rows_or_zero(const RowCtx& rc) {
 __device__ inline float rope_first(float a, float b, float c, float s) { return __fmaf_rn(a, c, -__fmul_rn(b, s)); }
 __device__ inline float rope_second(float a, float b, float c, float s) { return __fmaf_rn(b, c, __fmul_rn(a, s)); }
 
+// ---------------------------------------------------------------------------
+// Reductions inside a wavefront on the DPP lanes of the vector unit: rotations by 8, 4, 2, 1 inside the rows of 16 lanes,
+// then the rows by scalar reads.  (A shuffle through the LDS unit is a round trip of 100 cycles and more, with 16
+// wavefronts asking at once; six of them were most of a block-wide step.)
+template <int N> __device__ inline int row_ror(int v) { return __builtin_amdgcn_update_dpp(0, v, 0x120 + N, 0xf, 0xf, false); }
+template <int N> __device__ inline double row_ror_f64(double v) {
+  union { double d; int i[2]; } x{v};
+  x.i[0] = row_ror<N>(x.i[0]);
+  x.i[1] = row_ror<N>(x.i[1]);
+  return x.d;
+}
+__device__ inline float as_f32(int v) { return __int_as_float(v); }
+// every lane: over its row of 16 lanes
+__device__ inline float row_max_f32(float v) {
+  v = fmaxf(v, as_f32(row_ror<8>(__float_as_int(v))));
+  v = fmaxf(v, as_f32(row_ror<4>(__float_as_int(v))));
+  v = fmaxf(v, as_f32(row_ror<2>(__float_as_int(v))));
+  return fmaxf(v, as_f32(row_ror<1>(__float_as_int(v))));
+}
+__device__ inline unsigned row_max_u32(unsigned v) {
+  v = max(v, (unsigned)row_ror<8>((int)v));
+  v = max(v, (unsigned)row_ror<4>((int)v));
+  v = max(v, (unsigned)row_ror<2>((int)v));
+  return max(v, (unsigned)row_ror<1>((int)v));
+}
+__device__ inline int row_min_i32(int v) {
+  v = min(v, row_ror<8>(v));
+  v = min(v, row_ror<4>(v));
+  v = min(v, row_ror<2>(v));
+  return min(v, row_ror<1>(v));
+}
+__device__ inline double row_sum_f64(double v) {
+  v += row_ror_f64<8>(v);
+  v += row_ror_f64<4>(v);
+  v += row_ror_f64<2>(v);
+  return v + row_ror_f64<1>(v);
+}
+__device__ inline double lane_f64(double v, int l) {
+  union { double d; int i[2]; } x{v};
+  x.i[0] = __builtin_amdgcn_readlane(x.i[0], l);
+  x.i[1] = __builtin_amdgcn_readlane(x.i[1], l);
+  return x.d;
+}
+// every lane: over the wavefront
+__device__ inline float wave_max_f32(float v) {
+  const int r = __float_as_int(row_max_f32(v));
+  return fmaxf(fmaxf(as_f32(__builtin_amdgcn_readlane(r, 0)), as_f32(__builtin_amdgcn_readlane(r, 16))),
+               fmaxf(as_f32(__builtin_amdgcn_readlane(r, 32)), as_f32(__builtin_amdgcn_readlane(r, 48))));
+}
+__device__ inline unsigned wave_max_u32(unsigned v) {
+  const int r = (int)row_max_u32(v);
+  return max(max((unsigned)__builtin_amdgcn_readlane(r, 0), (unsigned)__builtin_amdgcn_readlane(r, 16)),
+             max((unsigned)__builtin_amdgcn_readlane(r, 32), (unsigned)__builtin_amdgcn_readlane(r, 48)));
+}
+__device__ inline int wave_min_i32(int v) {
+  const int r = row_min_i32(v);
+  return min(min(__builtin_amdgcn_readlane(r, 0), __builtin_amdgcn_readlane(r, 16)),
+             min(__builtin_amdgcn_readlane(r, 32), __builtin_amdgcn_readlane(r, 48)));
+}
+__device__ inline double wave_sum_f64(double v) {
+  v = row_sum_f64(v);
+  return (lane_f64(v, 0) + lane_f64(v, 16)) + (lane_f64(v, 32) + lane_f64(v, 48));
+}
+__device__ inline float wave_sum_f32(float v) {
+  v += as_f32(row_ror<8>(__float_as_int(v)));
+  v += as_f32(row_ror<4>(__float_as_int(v)));
+  v += as_f32(row_ror<2>(__float_as_int(v)));
+  const int r = __float_as_int(v + as_f32(row_ror<1>(__float_as_int(v))));
+  return (as_f32(__builtin_amdgcn_readlane(r, 0)) + as_f32(__builtin_amdgcn_readlane(r, 16))) +
+         (as_f32(__builtin_amdgcn_readlane(r, 32)) + as_f32(__builtin_amdgcn_readlane(r, 48)));
+}
+
 // silu(g) * u with the hardware reciprocal (1 ulp) instead of a full-precision division: the
 // result is rounded to bf16 right after, and the division was most of the SwiGLU epilogue.
 __device__ inline float silu_mul(float g, float u) { return g * u * __builtin_amdgcn_rcpf(1.0f + __expf(-g)); }
@@ -193,6 +265,21 @@ void launch_silu_mul(hipStream_t st, RowCtx rc, const float* gu, int F, T* act);
 void launch_attn_f32(hipStream_t st, RowCtx rc, Slots s, const float* q_rot, const float* kv_pool, KVLayout kvl,
                      int layer, int n_q_heads, float* out);
 void launch_gemm_f32(hipStream_t st, RowCtx rc, const float* x, const float* W, float* out, int N, int K);
+// fp32 models of few weights: a decode pass from the tokens to the logits in one launch, a workgroup per row (K and V of
+// the new position appended), and the product that their prefill uses (its sums are the decode pass's; K % 4 == 0).
+struct F32Layer { const float *attn_norm, *mlp_norm, *wqkv, *wo, *wgu, *wd; };
+struct F32Model {
+  const F32Layer* layers;              // device array
+  const float *tok_emb, *final_norm, *lm_head, *rope_cos, *rope_sin;
+  float* kv_pool;
+  KVLayout kvl;
+  int n_layers, d, F, n_q_heads, vocab;
+  float eps;
+  int lds_floats;                      // (the launcher's)
+};
+bool forward_f32_takes(int d, int F, int n_q_heads, int n_kv_heads, int head_dim, int vocab, int max_rows);
+void launch_forward_f32(hipStream_t st, RowCtx rc, Slots s, F32Model m, float* logits);
+void launch_gemm_f32_dot(hipStream_t st, RowCtx rc, const float* x, const float* W, float* out, int N, int K);
 
 // out[m][n] = sum_k x[m][k] W[n][k]; plain row-major W; reference path.
 template <typename T, bool XF>

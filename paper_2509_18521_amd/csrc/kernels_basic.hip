@@ -7,11 +7,7 @@ namespace april {
 // ---------------------------------------------------------------------------
 // small helpers
 // ---------------------------------------------------------------------------
-__device__ inline float wave_sum(float v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
-}
+__device__ inline float wave_sum(float v) { return wave_sum_f32(v); }
 __device__ inline int wave_incl_scan(int v) {
   const int lane = threadIdx.x & 63;
 #pragma unroll
@@ -354,7 +350,7 @@ __global__ __launch_bounds__(256) void add_rmsnorm_kernel(RowCtx rc, float* x_re
         for (int j = 0; j < 8; ++j) xp[j] = v[c][j];
       }
 #pragma unroll
-      for (int j = 0; j < 8; ++j) ss += v[c][j] * v[c][j];
+      for (int j = 0; j < 8; ++j) ss = __fmaf_rn(v[c][j], v[c][j], ss);
     }
   }
   ss = wave_sum(ss);
@@ -435,7 +431,7 @@ __global__ __launch_bounds__(256) void embed_norm_kernel(RowCtx rc, Slots s, con
     if (ch < nchunk) {
       float* xp = x_res + (size_t)r * d + ch * 8;
 #pragma unroll
-      for (int j = 0; j < 8; ++j) { xp[j] = v[c][j]; ss += v[c][j] * v[c][j]; }
+      for (int j = 0; j < 8; ++j) { xp[j] = v[c][j]; ss = __fmaf_rn(v[c][j], v[c][j], ss); }
     }
   }
   ss = wave_sum(ss);
@@ -587,21 +583,13 @@ template void launch_attn_ref<bf16_t, true>(hipStream_t, RowCtx, Slots, const fl
 // One token per trip (6 dependent shuffles, 2 exponentials and 2 loads each) took 38 us per launch
 // at 32 rows of 33-128 tokens; this takes 6.5 us (both with the 2 us that a profiler adds).
 // ---------------------------------------------------------------------------
-template <int DH>
-__global__ __launch_bounds__(64) void attn_f32_kernel(RowCtx rc, Slots s, const float* q_rot, const float* kv_pool,
-                                                      KVLayout L, int layer, int Hq, float* out) {
+template <int DH, class Out>
+__device__ __forceinline__ void attn_f32_row(const f32x4* sq, const float* kv_pool, const int* bt, const KVLayout& L, int layer, int kvh,
+                                             int ctx, Out out) {
   constexpr int TG = DH < 64 ? 64 / DH : 1;        // tokens side by side in the value product
   constexpr int DL = DH > 64 ? DH / 64 : 1;        // dimensions per lane there
-  const int r = blockIdx.x, a = blockIdx.y;
-  ROW_GUARD(rc, r);
-  const int slot = rc.row_slot[r], ctx = rc.row_pos[r] + 1, lane = threadIdx.x;
-  const int kvh = a / (Hq / L.n_kv_heads);
-  __shared__ f32x4 sq[DH / 4];
-  const f32x4* q = reinterpret_cast<const f32x4*>(q_rot + (size_t)r * Hq * DH + a * DH);
-  if (lane < DH / 4) sq[lane] = q[lane];
-  __syncthreads();
+  const int lane = threadIdx.x & 63;
   const float scale = 1.0f / sqrtf((float)DH);
-  const int* bt = s.block_table + (size_t)slot * s.max_blocks;
   const int vd = (lane % (DH / DL)) * DL, vt = lane / (DH / DL);      // this lane's dimensions and token residue
   float m = -INFINITY, l = 0.f, o[DL] = {};
   for (int j0 = 0; j0 < ctx; j0 += 64) {
@@ -609,49 +597,77 @@ __global__ __launch_bounds__(64) void attn_f32_kernel(RowCtx rc, Slots s, const 
     const bool live = lane < n;
     const int page = bt[(live ? j : ctx - 1) >> 4];
     const f32x4* k = reinterpret_cast<const f32x4*>(kv_pool + L.at(layer, 0, page, kvh, (live ? j : ctx - 1) & 15, 0));
+    f32x4 kv[DH / 4];
+#pragma unroll
+    for (int c = 0; c < DH / 4; ++c) kv[c] = k[c];
+    // the values of the step are requested with its keys (heads of 64 and less: 32 or 64 registers)
+    auto value = [&](int t, int e) {                 // token t + vt of the step (t + TG - 1 lies in the page of t)
+      const int vp = __builtin_amdgcn_readlane(page, min(t, n - 1));
+      return kv_pool + L.at(layer, 1, vp, kvh, min(t + vt, n - 1) & 15, vd) + e;
+    };
+    constexpr int EARLY = DL == 1 ? 64 / TG : 0;
+    float ve[EARLY > 0 ? EARLY : 1];
+#pragma unroll
+    for (int u = 0; u < EARLY; ++u) ve[u] = *value(u * TG, 0);
     float acc[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int c = 0; c < DH / 4; ++c) {
-      const f32x4 kv = k[c], qv = sq[c];
+      const f32x4 qv = sq[c];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) acc[e] = __fmaf_rn(kv[e], qv[e], acc[e]);
+      for (int e = 0; e < 4; ++e) acc[e] = __fmaf_rn(kv[c][e], qv[e], acc[e]);
     }
     const float sc = live ? ((acc[0] + acc[1]) + (acc[2] + acc[3])) * scale : -INFINITY;
-    float mx = sc;
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
-    const float m_new = fmaxf(m, mx), corr = expf(m - m_new), p = live ? expf(sc - m_new) : 0.f;
-    l = l * corr + wave_sum(p);
+    const float m_new = fmaxf(m, wave_max_f32(sc)), corr = expf(m - m_new), p = live ? expf(sc - m_new) : 0.f;
+    l = __fmaf_rn(l, corr, wave_sum(p));
     m = m_new;
     float add[DL] = {};
-    for (int t0 = 0; t0 < n; t0 += 16 * TG) {        // 16 loads in flight; tokens past the end add nothing
-      float v[16][DL], pt[16];
+    if constexpr (EARLY > 0) {                       // (tokens past the end have probability 0 and add nothing)
 #pragma unroll
-      for (int u = 0; u < 16; ++u) {
-        const int tt = min(t0 + u * TG + vt, n - 1);
-        pt[u] = __shfl(p, tt, 64);
-        const int vp = __shfl(page, tt, 64);
-        const float* src = kv_pool + L.at(layer, 1, vp, kvh, (j0 + tt) & 15, vd);
-#pragma unroll
-        for (int e = 0; e < DL; ++e) v[u][e] = src[e];
+      for (int u = 0; u < EARLY; ++u) {
+        const float pt = __shfl(p, u * TG + vt, 64);
+        add[0] = u * TG + vt < n ? __fmaf_rn(pt, ve[u], add[0]) : add[0];
       }
+    } else {
+      for (int t0 = 0; t0 < n; t0 += 16 * TG) {      // 16 loads in flight
+        float v[16][DL], pt[16];
 #pragma unroll
-      for (int u = 0; u < 16; ++u)
+        for (int u = 0; u < 16; ++u) {
+          pt[u] = __shfl(p, min(t0 + u * TG + vt, n - 1), 64);
 #pragma unroll
-        for (int e = 0; e < DL; ++e)
-          add[e] = t0 + u * TG + vt < n ? __fmaf_rn(pt[u], v[u][e], add[e]) : add[e];
+          for (int e = 0; e < DL; ++e) v[u][e] = *value(t0 + u * TG, e);
+        }
+#pragma unroll
+        for (int u = 0; u < 16; ++u)
+#pragma unroll
+          for (int e = 0; e < DL; ++e)
+            add[e] = t0 + u * TG + vt < n ? __fmaf_rn(pt[u], v[u][e], add[e]) : add[e];
+      }
     }
 #pragma unroll
     for (int e = 0; e < DL; ++e) {
 #pragma unroll
       for (int off = 32; off >= DH && off > 0; off >>= 1) add[e] += __shfl_xor(add[e], off, 64);
-      o[e] = o[e] * corr + add[e];
+      o[e] = __fmaf_rn(o[e], corr, add[e]);
     }
   }
   if (vt == 0) {
 #pragma unroll
-    for (int e = 0; e < DL; ++e) out[(size_t)r * Hq * DH + a * DH + vd + e] = o[e] / l;
+    for (int e = 0; e < DL; ++e) out(vd + e, o[e] / l);
   }
+}
+template <int DH>
+__global__ __launch_bounds__(64) void attn_f32_kernel(RowCtx rc, Slots s, const float* q_rot, const float* kv_pool,
+                                                      KVLayout L, int layer, int Hq, float* out) {
+  const int r = blockIdx.x, a = blockIdx.y;
+  ROW_GUARD(rc, r);
+  const int slot = rc.row_slot[r], ctx = rc.row_pos[r] + 1, lane = threadIdx.x;
+  __shared__ f32x4 sq[DH / 4];
+  const f32x4* q = reinterpret_cast<const f32x4*>(q_rot + (size_t)r * Hq * DH + a * DH);
+  if (lane < DH / 4) sq[lane] = q[lane];
+  __syncthreads();
+  float* dst = out + (size_t)r * Hq * DH + a * DH;
+  attn_f32_row<DH>(sq, kv_pool, s.block_table + (size_t)slot * s.max_blocks, L, layer, a / (Hq / L.n_kv_heads), ctx,
+                   [&](int d, float v) { dst[d] = v; });
 }
 void launch_attn_f32(hipStream_t st, RowCtx rc, Slots s, const float* q_rot, const float* kv_pool, KVLayout kvl, int layer,
                      int n_q_heads, float* out) {
@@ -776,6 +792,204 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(RowCtx rc, const float* _
 }
 void launch_gemm_f32(hipStream_t st, RowCtx rc, const float* x, const float* W, float* out, int N, int K) {
   hipLaunchKernelGGL(gemm_f32_kernel, dim3(ceil_div(N, 16), ceil_div(rc.max_rows, 16)), dim3(256), 0, st, rc, x, W, out, N, K);
+}
+
+// ---------------------------------------------------------------------------
+// Small fp32 models.  A decode iteration of one is nothing but launches: the fp32 configuration (two layers of 128,
+// 24 rows) ran 22 kernels of 3-6 us for 1 MB of weights a layer.  Rows do not need each other, so here a workgroup takes a
+// row through the whole model - embedding to logits, 8 wavefronts, activations in LDS - and streams the weights from its L2 at
+// what one compute unit takes (30-50 bytes per clock).  That pays while a layer's weights take less than its launches did.
+// us per decode iteration at 1, 24, 96, 300 rows, separate launches / this: two layers of 1.05 MB 73, 85, 91, 124 / 52, 54, 59,
+// 110; four of 0.98 143, 163, 179, 239 / 113, 116, 114, 221; two of 1.24 88, 101, 107, 143 / 66, 70, 76, 146; two of 1.48
+// 80, 91, 105, 137 / 84, 91, 91, 175; two of 1.47 and a head of 1.3 82, 92, 106, 151 / 100, 103, 102, 195: the rule is forward_f32_takes.
+//
+// Dot products: 8 lanes, four consecutive k each per 32, an accumulator for each of the four, added pairwise, then over the
+// lanes by a fixed tree (32 lanes to a column spend three times the instructions: the pass was bound by them, 27 bytes per
+// clock).  The prefill product of such a model (gemm_f32_dot_kernel) and the decode row share it, and the
+// norms, the rotation and the attention are the prefill's code too: a re-prefilled rollout keeps its bits.
+// ---------------------------------------------------------------------------
+template <int CTRL> __device__ inline float dpp_add(float v) {
+  return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
+}
+// sum over 8 consecutive lanes, in all of them
+__device__ inline float sum8(const f32x4& acc) {
+  float v = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+  v = dpp_add<0xb1>(v);                       // the lanes of a pair, of a quad, the mirrored lane of the eight
+  v = dpp_add<0x4e>(v);
+  return dpp_add<0x141>(v);
+}
+__device__ inline void fma4(const f32x4& a, const f32x4& b, f32x4& acc) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) acc[e] = __fmaf_rn(a[e], b[e], acc[e]);
+}
+// f(n, W[n] . x) for the N rows of W, x in LDS; all wavefronts.  KC: pieces of 32 k per step, U columns per lane in flight.
+constexpr int ROW_THREADS = 512;
+template <int KC, int U, class F>
+__device__ __forceinline__ void row_gemv(const float* __restrict__ W, const float* xs, int N, int K, F f) {
+  constexpr int STEP = ROW_THREADS / 8;
+  const int l = threadIdx.x & 7, first = (int)(threadIdx.x >> 3);
+  const f32x4* x4 = reinterpret_cast<const f32x4*>(xs);
+  for (int n0 = first; n0 < N + first % 8; n0 += U * STEP) {       // (the same trips for the 8 columns of a wavefront)
+    f32x4 acc[U];
+    const float* wp[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) { acc[u] = f32x4{}; wp[u] = W + (size_t)min(n0 + u * STEP, N - 1) * K; }
+    for (int k0 = 4 * l; k0 < K + 4 * l; k0 += 32 * KC) {
+      f32x4 w[U][KC];
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int c = 0; c < KC; ++c) {
+          w[u][c] = f32x4{};
+          if (k0 + c * 32 < K) w[u][c] = *reinterpret_cast<const f32x4*>(wp[u] + k0 + c * 32);
+        }
+#pragma unroll
+      for (int c = 0; c < KC; ++c) {
+        const int k = k0 + c * 32;
+        const f32x4 x = k < K ? x4[k >> 2] : f32x4{};
+#pragma unroll
+        for (int u = 0; u < U; ++u) fma4(w[u][c], x, acc[u]);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int n = n0 + u * STEP;
+      const float v = sum8(acc[u]);
+      if (l == 0 && n < N) f(n, v);
+    }
+  }
+}
+// out[m][n] = x[m] . W[n] with the same sums: 32 columns x 4 rows per workgroup.
+__global__ __launch_bounds__(256) void gemm_f32_dot_kernel(RowCtx rc, const float* __restrict__ x, const float* __restrict__ W,
+                                                           float* __restrict__ out, int N, int K) {
+  constexpr int MT = 4;
+  const int rows = rows_or_zero(rc), m0 = blockIdx.y * MT;
+  if (m0 >= rows) return;
+  const int l = threadIdx.x & 7, n = blockIdx.x * 32 + (int)(threadIdx.x >> 3);
+  const float* wp = W + (size_t)min(n, N - 1) * K;
+  f32x4 acc[MT];
+#pragma unroll
+  for (int m = 0; m < MT; ++m) acc[m] = f32x4{};
+#pragma unroll 4
+  for (int k = 4 * l; k < K; k += 32) {
+    const f32x4 w = *reinterpret_cast<const f32x4*>(wp + k);
+    f32x4 xv[MT];
+#pragma unroll
+    for (int m = 0; m < MT; ++m) xv[m] = *reinterpret_cast<const f32x4*>(x + (size_t)min(m0 + m, rows - 1) * K + k);
+#pragma unroll
+    for (int m = 0; m < MT; ++m) fma4(w, xv[m], acc[m]);
+  }
+#pragma unroll
+  for (int m = 0; m < MT; ++m) {
+    const float v = sum8(acc[m]);
+    if (l == 0 && n < N && m0 + m < rows) out[(size_t)(m0 + m) * N + n] = v;
+  }
+}
+void launch_gemm_f32_dot(hipStream_t st, RowCtx rc, const float* x, const float* W, float* out, int N, int K) {
+  hipLaunchKernelGGL(gemm_f32_dot_kernel, dim3(ceil_div(N, 32), ceil_div(rc.max_rows, 4)), dim3(256), 0, st, rc, x, W, out, N, K);
+}
+
+template <int DH>
+__global__ __launch_bounds__(ROW_THREADS) void forward_f32_kernel(RowCtx rc, Slots s, F32Model m, float* logits) {
+  extern __shared__ __align__(16) float lds[];
+  const int r = blockIdx.x;
+  const int slot = rc.row_slot[r], pos = rc.row_pos[r];
+  ROW_GUARD(rc, r);
+  const int tid = threadIdx.x, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int d = m.d, F = m.F, Hq = m.n_q_heads, Hkv = m.kvl.n_kv_heads, nq = Hq * DH, nqkv = nq + 2 * Hkv * DH;
+  constexpr int HALF = DH / 2;
+  float *x = lds, *h = x + d, *qkv = h + d, *att = qkv + nqkv, *gu = qkv;       // (gate / up where the queries were)
+  __shared__ float part[4];
+  const int* row_bt = s.block_table + (size_t)slot * s.max_blocks;
+  const int page = row_bt[pos >> 4], tin = pos & 15;
+  int* bt = reinterpret_cast<int*>(lds) + m.lds_floats;       // the row's pages, for every layer's attention
+  for (int i = tid; i <= pos >> 4; i += ROW_THREADS) bt[i] = row_bt[i];
+  {
+    const float* e = m.tok_emb + (size_t)s.tokens[(size_t)slot * s.max_ctx + pos] * d;
+    for (int i = tid; i < d; i += ROW_THREADS) x[i] = e[i];
+  }
+  // h = rmsnorm(x) * gain, the sums of add_rmsnorm_kernel (8 columns per thread, 256 threads)
+  auto norm = [&](const float* gain) {
+    const bool own = tid < 256 && tid < (d >> 3);
+    float v[8], gn[8], ss = 0.f;
+    if (own) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) gn[j] = gain[tid * 8 + j];
+    }
+    __syncthreads();
+    if (tid < 256) {
+      if (own) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) { v[j] = x[tid * 8 + j]; ss = __fmaf_rn(v[j], v[j], ss); }
+      }
+      ss = wave_sum(ss);
+      if ((tid & 63) == 0) part[wid] = ss;
+    }
+    __syncthreads();
+    if (own) {
+      ss = part[0] + part[1] + part[2] + part[3];
+      const float rinv = 1.0f / sqrtf(ss / (float)d + m.eps);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) h[tid * 8 + j] = v[j] * rinv * gn[j];
+    }
+    __syncthreads();
+  };
+  for (int layer = 0; layer < m.n_layers; ++layer) {
+    const F32Layer L = m.layers[layer];
+    norm(L.attn_norm);
+    row_gemv<4, 4>(L.wqkv, h, nqkv, d, [&](int n, float v) { qkv[n] = v; });
+    __syncthreads();
+    // rotary embedding of q and the new key, append of key and value
+    for (int e = tid; e < (Hq + Hkv) * HALF; e += ROW_THREADS) {
+      const int hd = e / HALF, i = e % HALF;
+      const float a = qkv[hd * DH + i], b = qkv[hd * DH + i + HALF];
+      const float c = m.rope_cos[(size_t)pos * HALF + i], sn = m.rope_sin[(size_t)pos * HALF + i];
+      const float ra = rope_first(a, b, c, sn), rb = rope_second(a, b, c, sn);
+      if (hd < Hq) {
+        qkv[hd * DH + i] = ra;
+        qkv[hd * DH + i + HALF] = rb;
+      } else {
+        m.kv_pool[m.kvl.at(layer, 0, page, hd - Hq, tin, i)] = ra;
+        m.kv_pool[m.kvl.at(layer, 0, page, hd - Hq, tin, i + HALF)] = rb;
+      }
+    }
+    for (int e = tid; e < Hkv * DH; e += ROW_THREADS)
+      m.kv_pool[m.kvl.at(layer, 1, page, e / DH, tin, e % DH)] = qkv[nq + Hkv * DH + e];
+    __syncthreads();                              // (the workgroup's stores are visible to its own loads behind this)
+    for (int a = wid; a < Hq; a += ROW_THREADS / 64)
+      attn_f32_row<DH>(reinterpret_cast<const f32x4*>(qkv + a * DH), m.kv_pool, bt, m.kvl, layer, a / (Hq / Hkv), pos + 1,
+                       [&](int i, float v) { att[a * DH + i] = v; });
+    __syncthreads();
+    row_gemv<4, 2>(L.wo, att, d, nq, [&](int n, float v) { x[n] += v; });
+    norm(L.mlp_norm);
+    row_gemv<4, 4>(L.wgu, h, 2 * F, d, [&](int n, float v) { gu[n] = v; });
+    __syncthreads();
+    for (int f = tid; f < F; f += ROW_THREADS) gu[f] = gu[f] / (1.0f + expf(-gu[f])) * gu[F + f];
+    __syncthreads();
+    row_gemv<8, 2>(L.wd, gu, d, F, [&](int n, float v) { x[n] += v; });
+  }
+  norm(m.final_norm);
+  row_gemv<4, 4>(m.lm_head, h, m.vocab, d, [&](int n, float v) { logits[(size_t)r * m.vocab + n] = v; });
+}
+static size_t forward_f32_lds(int d, int F, int nq, int nqkv) { return (size_t)(2 * d + (nqkv + nq > 2 * F ? nqkv + nq : 2 * F)); }     // floats
+bool forward_f32_takes(int d, int F, int n_q_heads, int n_kv_heads, int head_dim, int vocab, int max_rows) {
+  const int nq = n_q_heads * head_dim, nqkv = nq + 2 * n_kv_heads * head_dim;
+  const size_t layer_bytes = ((size_t)nqkv * d + (size_t)nq * d + (size_t)3 * F * d) * sizeof(float);
+  const size_t head_bytes = (size_t)vocab * d * sizeof(float);
+  const bool fits = d <= 2048 && F % 4 == 0 && forward_f32_lds(d, F, nq, nqkv) <= (14u << 10);     // (and at most 2048 page ids: 64 KiB)
+  return fits && head_bytes <= (512u << 10) && max_rows <= 320 && layer_bytes <= (max_rows <= 256 ? 1280u << 10 : 1100u << 10);
+}
+void launch_forward_f32(hipStream_t st, RowCtx rc, Slots s, F32Model m, float* logits) {
+  const int nq = m.n_q_heads * m.kvl.head_dim, nqkv = nq + 2 * m.kvl.n_kv_heads * m.kvl.head_dim;
+  m.lds_floats = (int)forward_f32_lds(m.d, m.F, nq, nqkv);
+  const size_t lds = ((size_t)m.lds_floats + s.max_blocks) * sizeof(float);
+#define FWD_F32(DH) hipLaunchKernelGGL((forward_f32_kernel<DH>), dim3(rc.max_rows), dim3(ROW_THREADS), lds, st, rc, s, m, logits)
+  switch (m.kvl.head_dim) {
+    case 32: FWD_F32(32); break;
+    case 64: FWD_F32(64); break;
+    default: FWD_F32(128); break;
+  }
+#undef FWD_F32
 }
 
 }  // namespace april

@@ -49,68 +49,6 @@ __device__ inline unsigned philox4x32_10_word0(unsigned c0, unsigned c1, unsigne
   return c0;
 }
 
-// Reductions inside a wavefront on the DPP lanes of the vector unit: rotations by 8, 4, 2, 1 inside the rows of 16 lanes,
-// then the rows by scalar reads.  (A shuffle through the LDS unit is a round trip of 100 cycles and more, with 16
-// wavefronts asking at once; six of them were most of a block-wide step.)
-template <int N> __device__ inline int row_ror(int v) { return __builtin_amdgcn_update_dpp(0, v, 0x120 + N, 0xf, 0xf, false); }
-template <int N> __device__ inline double row_ror_f64(double v) {
-  union { double d; int i[2]; } x{v};
-  x.i[0] = row_ror<N>(x.i[0]);
-  x.i[1] = row_ror<N>(x.i[1]);
-  return x.d;
-}
-__device__ inline float as_f32(int v) { return __int_as_float(v); }
-// every lane: over its row of 16 lanes
-__device__ inline float row_max_f32(float v) {
-  v = fmaxf(v, as_f32(row_ror<8>(__float_as_int(v))));
-  v = fmaxf(v, as_f32(row_ror<4>(__float_as_int(v))));
-  v = fmaxf(v, as_f32(row_ror<2>(__float_as_int(v))));
-  return fmaxf(v, as_f32(row_ror<1>(__float_as_int(v))));
-}
-__device__ inline unsigned row_max_u32(unsigned v) {
-  v = max(v, (unsigned)row_ror<8>((int)v));
-  v = max(v, (unsigned)row_ror<4>((int)v));
-  v = max(v, (unsigned)row_ror<2>((int)v));
-  return max(v, (unsigned)row_ror<1>((int)v));
-}
-__device__ inline int row_min_i32(int v) {
-  v = min(v, row_ror<8>(v));
-  v = min(v, row_ror<4>(v));
-  v = min(v, row_ror<2>(v));
-  return min(v, row_ror<1>(v));
-}
-__device__ inline double row_sum_f64(double v) {
-  v += row_ror_f64<8>(v);
-  v += row_ror_f64<4>(v);
-  v += row_ror_f64<2>(v);
-  return v + row_ror_f64<1>(v);
-}
-__device__ inline double lane_f64(double v, int l) {
-  union { double d; int i[2]; } x{v};
-  x.i[0] = __builtin_amdgcn_readlane(x.i[0], l);
-  x.i[1] = __builtin_amdgcn_readlane(x.i[1], l);
-  return x.d;
-}
-// every lane: over the wavefront
-__device__ inline float wave_max_f32(float v) {
-  const int r = __float_as_int(row_max_f32(v));
-  return fmaxf(fmaxf(as_f32(__builtin_amdgcn_readlane(r, 0)), as_f32(__builtin_amdgcn_readlane(r, 16))),
-               fmaxf(as_f32(__builtin_amdgcn_readlane(r, 32)), as_f32(__builtin_amdgcn_readlane(r, 48))));
-}
-__device__ inline unsigned wave_max_u32(unsigned v) {
-  const int r = (int)row_max_u32(v);
-  return max(max((unsigned)__builtin_amdgcn_readlane(r, 0), (unsigned)__builtin_amdgcn_readlane(r, 16)),
-             max((unsigned)__builtin_amdgcn_readlane(r, 32), (unsigned)__builtin_amdgcn_readlane(r, 48)));
-}
-__device__ inline int wave_min_i32(int v) {
-  const int r = row_min_i32(v);
-  return min(min(__builtin_amdgcn_readlane(r, 0), __builtin_amdgcn_readlane(r, 16)),
-             min(__builtin_amdgcn_readlane(r, 32), __builtin_amdgcn_readlane(r, 48)));
-}
-__device__ inline double wave_sum_f64(double v) {
-  v = row_sum_f64(v);
-  return (lane_f64(v, 0) + lane_f64(v, 16)) + (lane_f64(v, 32) + lane_f64(v, 48));
-}
 // inclusive prefix sum over the lanes
 __device__ inline double wave_scan_f64(double v) {
   const int lane = threadIdx.x & 63, l16 = lane & 15;

@@ -43,3 +43,37 @@ def test_ragged_fp32_models(head_dim, n_q, n_kv, d_model, d_ffn, vocab):
                 assert np.max(np.abs(got - ref[g])) <= 1e-4, (len(r.tokens), g)
     finally:
         ap.april_destroy(ctx)
+
+
+@pytest.mark.parametrize("head_dim,n_q,n_kv,d_model,d_ffn,vocab,n", [
+    (32, 4, 4, 128, 512, 512, 24), (32, 6, 2, 72, 52, 131, 40), (64, 2, 1, 40, 4, 1, 9), (128, 2, 1, 128, 320, 700, 300)])
+def test_decode_in_one_launch_keeps_a_prefilled_rollouts_bits(head_dim, n_q, n_kv, d_model, d_ffn, vocab, n):
+    """Models whose decode pass is one launch: logits of positions reached by decoding are those of the same tokens
+    prefilled, bit for bit, alone and in a batch, across page and attention-step boundaries; and the oracle's."""
+    import paper_2509_18521_amd as ap
+    shape = ai.ModelShape(2, d_model, n_q, n_kv, head_dim, d_ffn, vocab, dtype=ai.DTYPE_FP32)
+    gen, prompt = 3, [1, 14, 15, 16, 61, 62, 63, 64, 126, 127, 190]
+    w = ai.Workload("fp32", shape, 1, 200, n, n, gen, 0.0, 0.1, gen, gen, ai.SAMPLER_GREEDY, 0, 1, 7)
+    weights = ai.make_weights(shape, w.seed)
+    rng = np.random.default_rng(d_model)
+    text = rng.integers(0, vocab, 256, dtype=np.int32)
+    dec = Decoder(shape, weights)
+    ref = dec.forward_block(text[:200], dec.new_cache())
+    got = {}
+    for shift in (0, 1):                     # shift 1: what was decoded first is now the prompt's last token
+        ctx = make_engine(w, weights, debug=True, max_inflight=n)
+        reqs = [ai.Request(i, text[:prompt[i % len(prompt)] + shift], gen - shift) for i in range(n)]
+        forced = {r.request_id: text[len(r.tokens):len(r.tokens) + gen] for r in reqs}
+        try:
+            for r in reqs[:22]:
+                ap.april_debug_watch(ctx, r.request_id, 0, gen - shift)
+            ap.april_rollout_step(ctx, req_dicts(reqs, forced), n, n, gen)
+            for r in reqs[:22]:
+                for g in range(gen - shift):
+                    at, row = len(r.tokens) + g - 1, ap.april_debug_logits(ctx, r.request_id, g, vocab)[0]
+                    assert np.max(np.abs(row - ref[at])) <= 1e-4, (len(r.tokens), g)
+                    got.setdefault(at, []).append(row)
+        finally:
+            ap.april_destroy(ctx)
+    for at, rows in got.items():
+        assert all(np.array_equal(rows[0], x) for x in rows[1:]), at
