@@ -102,16 +102,25 @@ __device__ inline void tile_epilogue(f32x16 (&acc)[NTW][MTW], int nt0, int mt0, 
 
 // Epilogue of the prefill QKV projection: rotary embedding of q and k, q to a bf16 row array, k and v to
 // their pages - what a separate pass over the fp32 projection (rope_append_kernel) did, with the same
-// operations.  A wavefront holds 128 columns (NTW = 4 tiles), which are whole heads, and both members of
-// a rotation pair sit in the same lane: tiles i and i + DH / 64, or for DH = 32 registers e and e + 8.
+// operations.  Both members of a rotation pair sit in the same lane: a wavefront of 4 weight tiles holds whole heads (tiles
+// i and i + DH / 64, or for DH = 32 registers e and e + 8), one of 2 tiles a head of 64, two of 32, or every other
+// tile of a head of 128 (0 and 2, or 1 and 3).  qkv_tile: the weight tile i of the wavefront column wc.
 // The separate pass took 232 us per 16384 rows of 32 + 2 x 8 heads of 128 (400 MB in, 335 MB out,
 // bandwidth); with it and the residual additions of the two other projections (TEPI_RESID: the norm after
 // them reads one array instead of two and writes none but its result, 130 -> 80 us) in the epilogues, prefill
 // of 21 k tokens through three such layers went from 19.0 to 18.0 ms.
-template <int MTW, int DH>
-__device__ inline void qkv_epilogue(f32x16 (&acc)[4][MTW], int nt0, int mt0, int rows, int n_tiles, int lane, const RowCtx& rc,
+template <int NTW, int DH>
+__device__ __forceinline__ int qkv_tile(int wc, int i) {
+  static_assert(NTW == 4 || NTW == 2, "whole rotation pairs");
+  return NTW * 32 < DH ? (wc >> 1) * 4 + (wc & 1) + 2 * i : wc * NTW + i;
+}
+template <int NTW, int MTW, int DH>
+__device__ inline void qkv_epilogue(f32x16 (&acc)[NTW][MTW], int wc, int mt0, int rows, int n_tiles, int lane, const RowCtx& rc,
                                     const QkvOut& qo) {
-  constexpr int TH = DH / 32, HALF = DH / 2;            // tiles per head
+  constexpr bool SPLIT = NTW * 32 < DH;
+  constexpr int TH = SPLIT ? NTW : DH / 32, HALF = DH / 2;            // tiles per head, of this wavefront
+  const int ht0 = SPLIT ? wc & 1 : 0;                   // its tile i of a head is the head's ht0 + HT i
+  constexpr int HT = SPLIT ? 2 : 1;
   const int mloc = lane & 31, hf = lane >> 5;
   const int nq = qo.n_q_heads * DH, nkv = qo.kvl.n_kv_heads * DH;
 #pragma unroll
@@ -122,12 +131,12 @@ __device__ inline void qkv_epilogue(f32x16 (&acc)[4][MTW], int nt0, int mt0, int
     const int slot = rc.row_slot[mr], pos = rc.row_pos[mr];
     const int page = qo.block_table[(size_t)slot * qo.max_blocks + (pos >> 4)], tok = pos & 15;
 #pragma unroll
-    for (int h = 0; h < 4 / TH; ++h) {
-      const int col0 = (nt0 + h * TH) * 32;             // first column of the head (wavefront-uniform)
+    for (int h = 0; h < NTW / TH; ++h) {
+      const int col0 = (qkv_tile<NTW, DH>(wc, h * TH) - ht0) * 32;   // first column of the head (wavefront-uniform)
       if (col0 >= n_tiles * 32) continue;
       if (col0 < nq + nkv) {
-        const float* cs = qo.rope_cos + (size_t)pos * HALF + 4 * hf;
-        const float* sn = qo.rope_sin + (size_t)pos * HALF + 4 * hf;
+        const float* cs = qo.rope_cos + (size_t)pos * HALF + 32 * ht0 + 4 * hf;
+        const float* sn = qo.rope_sin + (size_t)pos * HALF + 32 * ht0 + 4 * hf;
         constexpr int PAIRS = TH > 1 ? TH / 2 : 1, QN = TH > 1 ? 4 : 2;
 #pragma unroll
         for (int p = 0; p < PAIRS; ++p)
@@ -165,7 +174,7 @@ __device__ inline void qkv_epilogue(f32x16 (&acc)[4][MTW], int nt0, int mt0, int
               st8.u[2 + e] = hf ? own.u[2 + e] : got;
             }
             // page layout of K: [d / 32][token + 16 ((d % 32) / 8)][d % 8]
-            if (ok) *reinterpret_cast<bf16x8*>(dst + (is_q ? i * 32 + 8 * (q + hf) : i * 512 + 128 * (q + hf))) = st8.w;
+            if (ok) *reinterpret_cast<bf16x8*>(dst + (is_q ? (ht0 + HT * i) * 32 + 8 * (q + hf) : (ht0 + HT * i) * 512 + 128 * (q + hf))) = st8.w;
           }
       } else {
         bf16_t* dst = qo.kv_pool + qo.kvl.at(qo.layer, 1, page, (col0 - nq - nkv) / DH, tok, 0);   // [d][token]
@@ -173,7 +182,7 @@ __device__ inline void qkv_epilogue(f32x16 (&acc)[4][MTW], int nt0, int mt0, int
 #pragma unroll
           for (int i = 0; i < TH; ++i)
 #pragma unroll
-            for (int e = 0; e < 16; ++e) dst[(i * 32 + 8 * (e >> 2) + 4 * hf + (e & 3)) * 16] = (bf16_t)acc[h * TH + i][j][e];
+            for (int e = 0; e < 16; ++e) dst[((ht0 + HT * i) * 32 + 8 * (e >> 2) + 4 * hf + (e & 3)) * 16] = (bf16_t)acc[h * TH + i][j][e];
         }
       }
     }
@@ -257,11 +266,11 @@ __device__ __forceinline__ int2 tile_of_block(const RowCtx& rc, int MT) {
   return make_int2(((int)blockIdx.x / (8 * mg)) * 8 + (rem & 7), rem >> 3);
 }
 
-template <int WGM, int WGN, int MTW, int NTW, int BK, int R, int EPI, bool CHAIN, bool MOE = false>
+template <int WGM, int WGN, int MTW, int NTW, int BK, int R, int EPI, bool CHAIN, bool MOE = false, int DH = 0>
 __device__ __forceinline__ void tile_dma_body(RowCtx rc, const bf16x8* __restrict__ x, const bf16x8* __restrict__ w0,
                                               const bf16x8* __restrict__ w1, float* __restrict__ out,
                                               bf16_t* __restrict__ act, int N, int K, const TileNorm& tn,
-                                              const TileMoe& mo = TileMoe{}) {
+                                              const TileMoe& mo = TileMoe{}, const QkvOut& qo = QkvOut{}) {
   constexpr int NW = WGM * WGN, MT = WGM * MTW, NT = WGN * NTW, FR = MT + NT;
   constexpr int PER = FR * BK / NW;
   static_assert(FR * BK % NW == 0 && NW % BK == 0, "staging split");
@@ -315,6 +324,7 @@ __device__ __forceinline__ void tile_dma_body(RowCtx rc, const bf16x8* __restric
       return (ii < H ? w0 : w1) + (size_t)f * KT * 64 + lane;
     }
     int nt = bx * NT + i;
+    if constexpr (EPI == TEPI_QKV) nt = qkv_tile<NTW, DH>(bx * WGN + i / NTW, i % NTW);
     if (nt >= n_tiles) nt = n_tiles - 1;
     return w0 + (size_t)nt * KT * 64 + lane;
   };
@@ -430,6 +440,10 @@ __device__ __forceinline__ void tile_dma_body(RowCtx rc, const bf16x8* __restric
     for (int i = 0; i < NTW; ++i)
 #pragma unroll
       for (int j = 0; j < MTW; ++j) acc[i][j] = tot[CHAIN ? i : 0][CHAIN ? j : 0] + acc[i][j];
+  }
+  if constexpr (EPI == TEPI_QKV) {
+    qkv_epilogue<NTW, MTW, DH>(acc, bx * WGN + wn, m0 + wm * MTW, rows, n_tiles, lane, rc, qo);
+    return;
   }
   tile_epilogue<MTW, NTW, EPI>(acc, bx * (EPI == TEPI_SWIGLU ? NT / 2 : NT) + wn * (EPI == TEPI_SWIGLU ? NTW / 2 : NTW),
                                m0 + wm * MTW, rows, n_tiles, N, lane, out, act, scaled ? row_scale : nullptr, m0 * 32, &tn.go);
@@ -549,7 +563,7 @@ __global__ __launch_bounds__(256, 1) void gemm_big_kernel(RowCtx rc, const bf16x
   for (; s + R - 1 < n_stages; ++s) stage(s, std::true_type{});
   for (; s < n_stages; ++s) stage(s, std::false_type{});
   if constexpr (EPI == TEPI_QKV) {
-    qkv_epilogue<MTW, DH>(acc, bx * NT + wn * NTW, m0 + wm * MTW, rows, n_tiles, lane, rc, qo);
+    qkv_epilogue<NTW, MTW, DH>(acc, bx * 2 + wn, m0 + wm * MTW, rows, n_tiles, lane, rc, qo);
     return;
   }
   tile_epilogue<MTW, NTW, EPI>(acc, bx * (EPI == TEPI_SWIGLU ? NT / 2 : NT) + wn * (EPI == TEPI_SWIGLU ? NTW / 2 : NTW),
@@ -564,6 +578,12 @@ void gemm_tile_dma_kernel(RowCtx rc, const bf16x8* __restrict__ x, const bf16x8*
   TileNorm tn{};
   tn.go = go;
   tile_dma_body<WGM, WGN, MTW, NTW, BK, R, EPI, false>(rc, x, w0, w1, out, act, N, K, tn);
+}
+
+template <int WGM, int WGN, int MTW, int NTW, int BK, int R, int DH>
+__global__ __launch_bounds__(64 * WGM * WGN) __attribute__((amdgpu_waves_per_eu(2)))
+void gemm_tile_qkv_kernel(RowCtx rc, const bf16x8* __restrict__ x, const bf16x8* __restrict__ w0, int N, int K, QkvOut qo) {
+  tile_dma_body<WGM, WGN, MTW, NTW, BK, R, TEPI_QKV, false, false, DH>(rc, x, w0, nullptr, nullptr, nullptr, N, K, TileNorm{}, TileMoe{}, qo);
 }
 
 template <int WGM, int WGN, int MTW, int NTW, int BK, int R, int EPI>
@@ -669,12 +689,33 @@ void launch_gemm_tile(hipStream_t st, RowCtx rc, const bf16_t* x, const bf16_t* 
 void launch_gemm_tile_resid(hipStream_t st, RowCtx rc, const bf16_t* x, const bf16_t* Wp, float* x_res, int N, int K) {
   launch_tile<TEPI_RESID>(st, rc, x, Wp, x_res, N, K);
 }
+// QKV with the rotary epilogue.  SMALL and MID as above (64 columns per wavefront; MID one workgroup per unit), NARROW while
+// its workgroups are at most one per unit (then WIDE leaves half the chip idle; at 288 it loses 11 %), else WIDE - which alone
+// took every pass before and cost a short prompt one workgroup's walk over k.  us, WIDE | SMALL | MID | NARROW:
+//   1152 x 896 (14 + 2 x 2 heads of 64) at 37, 768, 2048, 4096 rows  24, 31, 34, 35 | 9, 9, 26, 42 | 12, 14, 16, 29 | 19, 22, 24, 26
+//   1792 x 1184 (20 + 2 x 4 of 64) at 37, 512, 2048, 4096 rows  29, 36, 39, 42 | 10, 11, 42, 70 | 15, 16, 19, 36 | 23, 27, 29, 32
+//   6144 x 2560 (32 + 2 x 8 of 128) at 37, 128, 256, 640, 1024, 1536 rows  53, 56, 59, 62, 64, 68 | 20, 21, 39, 77, 115, 171 |
+//                                                          26, 28, 29, 32, 59, 88 | 44, 45, 48, 51, 53, 76
+//   6144 x 4096 at 37, 640, 1024, 2048 rows  79, 90, 93, 119 | 30, 117, 174, 339 | 40, 49, 89, 146 | 66, 74, 79, 127
+enum QkvShape { QKV_SMALL, QKV_MID, QKV_NARROW, QKV_WIDE };
+static QkvShape qkv_shape(int units, int m_tiles) {         // units of 64 columns
+  if (small_tile(units, m_tiles)) return QKV_SMALL;
+  if (mid_tile(units, m_tiles, 256)) return QKV_MID;
+  return (long long)ceil_div(units, 2) * ceil_div(m_tiles, 8) <= 256 ? QKV_NARROW : QKV_WIDE;
+}
 bool launch_gemm_tile_qkv(hipStream_t st, RowCtx rc, const bf16_t* x, const bf16_t* Wp, int N, int K, const QkvOut& qo) {
   if (qo.kvl.mode != 1) return false;
-  dim3 grid(ceil_div(N >> 5, 8), ceil_div(ceil_div(rc.max_rows, 32), 8));
+  const int units = ceil_div(N >> 5, 2), m_tiles = ceil_div(rc.max_rows, 32);       // 64 columns
+  const QkvShape shape = qkv_shape(units, m_tiles);
+#define QKV_TILE(DH, WGN, MTW, NW, R)                                                                                  \
+  hipLaunchKernelGGL((gemm_tile_qkv_kernel<2, WGN, MTW, 2, 2, R, DH>), dim3(ceil_div(units, WGN), ceil_div(m_tiles, 2 * MTW)), \
+                     dim3(64 * NW), 0, st, rc, reinterpret_cast<const bf16x8*>(x), reinterpret_cast<const bf16x8*>(Wp), N, K, qo)
 #define QKV_LAUNCH(DH)                                                                                                 \
-  hipLaunchKernelGGL((gemm_big_kernel<TEPI_QKV, DH>), grid, dim3(256), 0, st, rc, reinterpret_cast<const bf16x8*>(x),  \
-                     reinterpret_cast<const bf16x8*>(Wp), nullptr, nullptr, nullptr, N, K, GroupOut{}, qo)
+  if (shape == QKV_SMALL) QKV_TILE(DH, 1, 1, 2, 16);                                                                           \
+  else if (shape == QKV_MID) QKV_TILE(DH, 2, 2, 4, 8);                                                                       \
+  else if (shape == QKV_NARROW) QKV_TILE(DH, 2, 4, 4, 3);                                                                       \
+  else hipLaunchKernelGGL((gemm_big_kernel<TEPI_QKV, DH>), dim3(ceil_div(N >> 5, 8), ceil_div(m_tiles, 8)), dim3(256), 0, st, rc, \
+                          reinterpret_cast<const bf16x8*>(x), reinterpret_cast<const bf16x8*>(Wp), nullptr, nullptr, nullptr, N, K, GroupOut{}, qo)
   switch (qo.kvl.head_dim) {
     case 32: QKV_LAUNCH(32); break;
     case 64: QKV_LAUNCH(64); break;
@@ -682,6 +723,7 @@ bool launch_gemm_tile_qkv(hipStream_t st, RowCtx rc, const bf16_t* x, const bf16
     default: return false;
   }
 #undef QKV_LAUNCH
+#undef QKV_TILE
   return true;
 }
 
