@@ -89,6 +89,14 @@ def test_moe_cfg5_layer_shape():
     moe_parity(w, 2, 8, min_rows=12)
 
 
+@pytest.mark.parametrize("experts,top_k", [(96, 1), (224, 6), (256, 8)])
+def test_moe_router_takes_the_oracles_experts(experts, top_k):
+    """One and a half, three and a half and four experts per lane; one and many arg-max steps."""
+    shape = ai.ModelShape(1, 128, 4, 2, 32, 0, 512, n_experts=experts, experts_per_tok=top_k, d_expert_ffn=32)
+    w = ai.Workload("moe_route", shape, 6, 24, 3, 5, 14, 2.0, 0.5, 3, 14, ai.SAMPLER_GREEDY, 0, 2, 19)
+    moe_parity(w, 2, 10, min_rows=10)
+
+
 def test_moe_resumed_equals_uninterrupted():
     shape = ai.ModelShape(2, 128, 4, 2, 32, 0, 512, n_experts=32, experts_per_tok=4, d_expert_ffn=64)
     w = ai.Workload("moe_small", shape, 8, 20, 5, 9, 30, 2.4, 0.6, 2, 30, ai.SAMPLER_GREEDY, 0, 4, 23)
