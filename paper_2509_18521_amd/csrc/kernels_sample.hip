@@ -521,13 +521,14 @@ __global__ __launch_bounds__(REC_THREADS) void sample_records_kernel(RowCtx rc, 
   float* lp_dst = update ? (s.logprob ? s.logprob + (size_t)q.slot * s.max_ctx + q.g : nullptr) : (out_logprobs ? out_logprobs + r : nullptr);
 
   // ---- first exchange: the row's maximum; greedy: its group (lowest on ties); top-k: maxima by lane ----
+  // (keys of real groups only: a group of NaN with the sign set comes below the -inf of the slots past the last group)
   float mx = -INFINITY;
   unsigned bk = 0u;
   int bi = 0x7fffffff;
   each([&](int, int i, float m, double) {
     mx = fmaxf(mx, m);
     const unsigned k = f2key(m);
-    const bool first = bi == 0x7fffffff || k > bk;            // ascending i: the first maximum stays
+    const bool first = i < n_groups && (bi == 0x7fffffff || k > bk);      // ascending i: the first maximum stays
     bk = first ? k : bk;
     bi = first ? i : bi;
   });
@@ -630,7 +631,7 @@ __global__ __launch_bounds__(REC_THREADS) void sample_records_kernel(RowCtx rc, 
         }
       }
       __syncthreads();
-      have = !sh.overflow;
+      have = !sh.overflow && sh.cnt >= k;                     // (a maximum that is a signalling NaN comes back quiet: no logit has its key)
     }
     if (!have) topk_whole_row<REC_THREADS>(lg, V, k, sh);
     draw_topk(k, sc, q.req, q.g, sh);

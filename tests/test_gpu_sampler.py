@@ -205,3 +205,49 @@ def test_records_of_every_register_count(sampler, n_groups, top_k):
         c = np.cumsum(p) / p.sum()
         if np.min(np.abs(c - u)) > 1e-9:                          # not on a step of the distribution
             assert tok[r] == order[np.argmax(c > u)], r
+
+
+@pytest.mark.parametrize("n_groups,ragged,top_k", [(1, 0, 1), (64, 0, 64), (65, 0, 50), (65, 31, 20), (1025, 0, 50), (1025, 31, 50),
+                                                   (4096, 0, 64), (4097, 0, 50), (4097, 31, 50)])
+@pytest.mark.parametrize("sampler", [ai.SAMPLER_GREEDY, ai.SAMPLER_TOPK, ai.SAMPLER_CATEGORICAL])
+def test_rows_of_nan_give_tokens_of_the_vocabulary(sampler, n_groups, ragged, top_k):
+    """NaN of either sign in the whole row, and in all of it but a few logits (fewer than k groups): a NaN with the sign set
+    comes below -inf in the order of the searches, any other above +inf.  A distribution without a sum gives its last token."""
+    import torch
+    vocab, T = 64 * n_groups - ragged, float(np.float32(0.7))
+    k = min(top_k, vocab)
+    neg, pos = np.uint32(0xffc00000).view(np.float32), np.uint32(0x7fc00000).view(np.float32)
+    logits = np.full((5, vocab), neg, dtype=np.float32)
+    logits[1] = pos
+    few = np.unique(np.array([vocab // 3, vocab // 2, vocab - 1]))
+    logits[2, few] = np.arange(len(few), dtype=np.float32) - 1.5
+    logits[3, few] = -np.inf
+    logits[4] = np.random.default_rng(n_groups).standard_normal(vocab).astype(np.float32)
+    logits[4, :vocab // 2] = neg
+    ids, idx = np.arange(5, dtype=np.int64) + 3, np.arange(5, dtype=np.int32)
+    ap, ctx = engine(vocab, sampler, top_k, T, 9)
+    try:
+        dev = torch.from_numpy(logits).cuda()
+        tok, _ = ap.april_sample_rows_logprobs(ctx, dev.data_ptr(), 5, ids, idx)
+        plain = ap.april_sample_rows(ctx, dev.data_ptr(), 5, ids, idx)
+        alone = ap.april_sample_rows_noalloc(ctx, dev.data_ptr(), 5, ids, idx)
+    finally:
+        ap.april_destroy(ctx)
+    assert np.array_equal(tok, plain) and np.array_equal(tok, alone)
+    assert tok.min() >= 0 and tok.max() < vocab
+    if sampler == ai.SAMPLER_CATEGORICAL:
+        assert all(t == vocab - 1 for t in tok)
+        return
+    bits = logits.view(np.uint32)
+    keys = np.where(bits >> 31, ~bits, bits | np.uint32(0x80000000))
+    for r in range(5):
+        order = np.lexsort((np.arange(vocab), -keys[r].astype(np.int64)))[:k]
+        if sampler == ai.SAMPLER_GREEDY or top_k <= 1:
+            # (a short last group counts as if it were filled up with -inf, which comes above a row of such NaN)
+            assert tok[r] == order[0] or (r == 0 and ragged and tok[r] == vocab // 64 * 64), r
+        elif np.isnan(logits[r, order]).any() or np.isinf(logits[r, order[0]]):
+            assert tok[r] == order[k - 1], r
+        else:
+            p = np.exp((logits[r, order].astype(np.float64) - logits[r, order[0]]) / T)
+            c, u = np.cumsum(p) / p.sum(), uniform_for(9, int(ids[r]), int(idx[r]))
+            assert np.min(np.abs(c - u)) <= 1e-9 or tok[r] == order[np.argmax(c > u)], r
