@@ -714,8 +714,8 @@ void forward(april_ctx* c, RowCtx rows, RowCtx srows, const int* gather, double 
   {
     ProfScope p(c, KC_GEMM_LMHEAD, (double)V * d * e + SB * d * e, 2.0 * SB * V * d);
     // (the categorical sampler wants fp64 exponentials, which launch_group_records takes from the logits below)
-    const GroupOut go{c->group_max, c->group_idx, c->cfg.sampler == APRIL_SAMPLER_CATEGORICAL ? nullptr : c->group_sum,
-                      1.0f / sampler_cfg(c).temperature};
+    const bool sums = c->cfg.sampler != APRIL_SAMPLER_CATEGORICAL && sampler_takes_records(sampler_cfg(c), V);
+    const GroupOut go{c->group_max, c->group_idx, sums ? c->group_sum : nullptr, 1.0f / sampler_cfg(c).temperature};
     if (c->use_mfma) {
       if (!(c->tile_gemm && launch_gemm_tile_logits(st, srows, (const bf16_t*)c->hf, c->lm_head_s, lg_out, go, V, d)))
         launch_gemm_mfma_logits(st, srows, (const bf16_t*)c->hf, c->lm_head_s, lg_out, go, V, d);
@@ -1369,19 +1369,19 @@ static int sample_rows_impl(april_ctx* c, const float* logits, int32_t n_rows, c
   const int V = c->dm.vocab, n_groups = ceil_div(V, lmhead_group_cols());
   const SamplerCfg sc = sampler_cfg(c);
   // sums: the categorical sampler's (fp64 exponentials) serve the log-probabilities too
-  const int sums = sc.kind == APRIL_SAMPLER_CATEGORICAL ? 2 : (out_logprobs ? 1 : 0);
-  const size_t row_bytes = (size_t)n_groups * (sums ? 12 : 4);
+  const bool records = sampler_takes_records(sc, V);
+  const int sums = !records ? 0 : sc.kind == APRIL_SAMPLER_CATEGORICAL ? 2 : (out_logprobs ? 1 : 0);
+  const size_t row_bytes = !records ? 1 : (size_t)n_groups * (sums ? 12 : 4);
   const int part_rows = (int)std::max<size_t>(1, std::min<size_t>({(size_t)n_rows, 16384, c->h_stage_ints * sizeof(int) / 20, ((size_t)64 << 20) / row_bytes}));
-  const size_t off_gm = sums ? (size_t)part_rows * n_groups * 8 : 0, need = off_gm + (size_t)part_rows * n_groups * 4;
+  const size_t off_gm = sums ? (size_t)part_rows * n_groups * 8 : 0, need = records ? off_gm + (size_t)part_rows * n_groups * 4 : 0;
   if (need > c->sr_ws_bytes) {
     HIPCHK(c, hipStreamSynchronize(c->stream));
     if (c->sr_ws) { hipFree(c->sr_ws); c->sr_ws = nullptr; c->sr_ws_bytes = 0; }
     if (hipMalloc((void**)&c->sr_ws, need) != hipSuccess) return fail(c, APRIL_ENOMEM, "sampler workspace (%zu bytes)", need);
     c->sr_ws_bytes = need;
   }
-  float* gm = reinterpret_cast<float*>(c->sr_ws + off_gm);
+  float* gm = records ? reinterpret_cast<float*>(c->sr_ws + off_gm) : nullptr;
   double* gs = sums ? reinterpret_cast<double*>(c->sr_ws) : nullptr;
-  const bool records = sums || sc.kind != APRIL_SAMPLER_TOPK || sc.top_k <= 1 || topk_in_groups(V, sc.top_k);
   long long* req = reinterpret_cast<long long*>(c->h_stage);
   int *gen = reinterpret_cast<int*>(req + part_rows), *tok = gen + part_rows;
   float* lp = out_logprobs ? reinterpret_cast<float*>(tok + part_rows) : nullptr;
@@ -1394,7 +1394,7 @@ static int sample_rows_impl(april_ctx* c, const float* logits, int32_t n_rows, c
     const float* lg = logits + (size_t)r0 * V;
     if (records) launch_group_records(c->stream, lg, nullptr, n, V, sums, sc.temperature, gm, gs);
     launch_sample(c->stream, RowCtx{nullptr, nullptr, nullptr, n}, c->ds, nullptr, lg, V, sc, Watch{}, 0, req, gen, tok,
-                  records ? gm : nullptr, lp, nullptr, gs);
+                  gm, lp, nullptr, gs);
     HIPCHK(c, hipStreamSynchronize(c->stream));
     memcpy(out_tokens + r0, tok, (size_t)n * 4);
     if (lp) memcpy(out_logprobs + r0, lp, (size_t)n * 4);
@@ -1424,7 +1424,7 @@ int april_sample_rows_noalloc(april_ctx* c, const float* logits, int32_t n_rows,
     return fail(c, APRIL_EINVAL, "april_sample_rows_noalloc: rows x vocab/%d = %zu exceeds the scratch (%zu)", grp, n_records, NOALLOC_MAX_GROUP_MAX);
   // (a vocabulary that 64 does not divide has no such limit: beyond the scratch the sampler reads whole rows)
   const SamplerCfg sc = sampler_cfg(c);
-  const bool use_gm = n_records <= NOALLOC_MAX_GROUP_MAX && (sc.kind != APRIL_SAMPLER_TOPK || sc.top_k <= 1 || topk_in_groups(V, sc.top_k));
+  const bool use_gm = n_records <= NOALLOC_MAX_GROUP_MAX && sampler_takes_records(sc, V);
   if (!c->scratch_dev) return fail(c, APRIL_EDEVICE, "scratch address was not resolved at april_init");
   unsigned char* sp = c->scratch_dev;
   const int sums = use_gm && sc.kind == APRIL_SAMPLER_CATEGORICAL ? 2 : 0;

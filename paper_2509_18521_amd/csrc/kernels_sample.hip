@@ -823,12 +823,10 @@ void launch_group_records(hipStream_t st, const float* logits, const int2* ctl, 
 void launch_sample(hipStream_t st, RowCtx rc, Slots s, Ctrl* ctrl, const float* logits, int vocab, SamplerCfg sc,
                    Watch w, int update, const long long* req_ids, const int* gen_idx, int* out_tokens,
                    const float* group_max, float* out_logprobs, const int* group_idx, const double* group_sum) {
-  const int n_groups = ceil_div(vocab, 64), k = sc.top_k < vocab ? (sc.top_k < MAX_TOPK ? sc.top_k : MAX_TOPK) : (vocab < MAX_TOPK ? vocab : MAX_TOPK);
-  const bool greedy = sc.kind == 0 || (sc.kind == 1 && sc.top_k <= 1);
+  const int n_groups = ceil_div(vocab, 64);
   const bool lp = update ? s.logprob != nullptr : out_logprobs != nullptr;
   // records serve what the call needs: sums for log-probabilities and the categorical sampler, groups enough for a top k
-  const bool records = group_max != nullptr && (group_sum != nullptr || (!lp && sc.kind != 2)) &&
-                       (greedy || sc.kind == 2 || (n_groups >= k && topk_in_groups(vocab, k)));
+  const bool records = group_max != nullptr && (group_sum != nullptr || (!lp && sc.kind != 2)) && sampler_takes_records(sc, vocab);
 #define SAMPLE_RECORDS(CACHED)                                                                                         \
   hipLaunchKernelGGL(sample_records_kernel<CACHED>, dim3(rc.max_rows), dim3(REC_THREADS), 0, st, rc, s, ctrl, logits, vocab, \
                      sc, w, update, req_ids, gen_idx, out_tokens, group_max, out_logprobs, group_idx, group_sum)

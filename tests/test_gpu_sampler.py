@@ -251,3 +251,30 @@ def test_rows_of_nan_give_tokens_of_the_vocabulary(sampler, n_groups, ragged, to
             p = np.exp((logits[r, order].astype(np.float64) - logits[r, order[0]]) / T)
             c, u = np.cumsum(p) / p.sum(), uniform_for(9, int(ids[r]), int(idx[r]))
             assert np.min(np.abs(c - u)) <= 1e-9 or tok[r] == order[np.argmax(c > u)], r
+
+
+@pytest.mark.parametrize("vocab,top_k", [(4032, 64), (4095, 50)])
+def test_whole_row_searches_make_no_group_records(vocab, top_k):
+    """Top-k searches that read whole rows (fewer than k groups; a short row) leave group records alone: no pass over the logits
+    for them, so no workspace either (8192 rows of them would take 2 MiB, with sums 6).  Same tokens and log-probabilities."""
+    import torch
+    n, T, seed = 8192, float(np.float32(0.8)), 3
+    logits = 2.0 * torch.randn(n, vocab, generator=torch.Generator("cuda").manual_seed(vocab), device="cuda")
+    ids, idx = np.arange(n, dtype=np.int64), np.zeros(n, dtype=np.int32)
+    ap, ctx = engine(vocab, ai.SAMPLER_TOPK, top_k, T, seed)
+    try:
+        ap.april_sample_rows_logprobs(ctx, logits.data_ptr(), 1, ids[:1], idx[:1])      # (whatever the first launch allocates)
+        torch.cuda.synchronize()
+        free = torch.cuda.mem_get_info()[0]
+        tok, lp = ap.april_sample_rows_logprobs(ctx, logits.data_ptr(), n, ids, idx)
+        plain = ap.april_sample_rows(ctx, logits.data_ptr(), n, ids, idx)
+        assert free - torch.cuda.mem_get_info()[0] < 1 << 20
+    finally:
+        ap.april_destroy(ctx)
+    assert np.array_equal(tok, plain)
+    for r in range(0, n, 331):
+        row = logits[r].cpu().numpy()
+        assert abs(float(lp[r]) - osampler.token_logprob(row, T, int(tok[r]))) < 2e-5
+        _, p = osampler.top_k_probs(row, top_k, T)
+        u = uniform_for(seed, int(ids[r]), 0)
+        assert np.min(np.abs(np.cumsum(p)[:-1] - u)) < 1e-9 or int(tok[r]) == osampler.top_k_sample(row, top_k, T, u), r
