@@ -418,10 +418,15 @@ __global__ __launch_bounds__(64 * KW4, 1) void gemm_logits_kernel(const int2* __
 // then a compute unit alone pulls about 50 GB/s from HBM, so the launch wants every unit busy with the same amount;
 // beyond that the re-reads, the activations once per n-tile group and the weights once per m-group, at L2 speed.  So the
 // tile of a workgroup grows with the rows.  us per launch, N x K in ksplit slices (rows: one side / the other):
-//   * matrices below 8 M elements, and odd n-tile counts: single tiles at three workgroups per unit up to 64 rows and, where
+//   * matrices below 8 M elements: single tiles at three workgroups per unit up to 64 rows and, where
 //     they are at most 300 per m-tile, 128; then 1 x 2.  1152 x 896 in 4 at 96 rows 3.3 / 1 x 4 4.1, 896 x 4864 in 8 at 96, 128
 //     rows 6.1, 6.8 / 1 x 2 6.4, 7.6, 1792 x 1184 in 6 (336) at 96 rows 5.0 / 1 x 2 4.7, 2 x 4 7.0.  Beyond 128 rows pairs:
 //     2 x 2 for slices below 512, else 2 x 3: 1792 x 1184 at 192 rows 6.1 / 7.0, 896 x 4864 8.7 / 7.9.
+//   * odd n-tile counts from about 6 M elements on: one n-tile, and the more m-tiles the fewer workgroups re-read the weights and
+//     the activations; per m-tile of 256 workgroups and more the narrow tile still fills the units at 96 and 128 rows.  At 128, 192,
+//     384 rows, 1 x 1 or 1 x 2 of small matrices / as here: 6176 x 4096 in 1 37.1, 34.6, 56.2 / 23.8, 31.9, 48.4; 4128 x 14336 in 2 78.0,
+//     74.7, 127 / 59.2, 71.3, 107; 2592 x 9728 in 4 26.1, 31.8, 52.9 / 25.1, 31.2, 48.0; 3104 x 2048 in 3 11.1, 12.3, 19.6 / 10.4, 12.4,
+//     16.7; 64 rows of 6176 x 4096 20.5 / 17.1.  1 x 4 for all: 23.8, 32.1, 48.4; 72.3, 71.6, 107; 29.6, 33.1, 48.0; 11.5, 12.1, 16.7.
 //   * larger ones, up to 64 rows 2 x 2 at two workgroups per unit: 6144 x 2560 in 2 at 32, 64 rows 9.1, 11.1 / 2 x 4 9.8, 11.9.
 //     96 and 128 rows 2 x 3: 12.4, 14.3 / 2 x 4 13.7, 15.0; but 2 x 4 for 128 rows of long slices that fill the units by
 //     themselves: 4096 x 14336 in 4 33.3 / 2 x 3 40.1.
@@ -450,7 +455,12 @@ void launch_gemm_mfma(hipStream_t st, RowCtx rc, const bf16_t* x, const bf16_t* 
                      reinterpret_cast<const bf16x8*>(x), reinterpret_cast<const bf16x8*>(Wp), nullptr, out,             \
                      rc.max_rows, N, K, ksplit, nullptr, partial_stride, nf)
   const bool pairs = n_tiles % 2 == 0, small = (long long)N * K < (8ll << 20);
-  if (!pairs || (small && m_tiles <= 4)) {
+  if (!pairs && m_tiles > 1 && (long long)N * K >= (m_tiles <= 4 ? 6ll << 20 : 5ll << 20) && (m_tiles > 2 || n_tiles > 128)) {
+    if (m_tiles == 2) GEMM_F32(1, 2, 8, 3);
+    else if (m_tiles <= 4 && n_tiles * ksplit >= 256) GEMM_F32(1, 2, 10, 2);
+    else if (m_tiles == 5 || m_tiles == 6) GEMM_F32(1, 3, 8, 2);
+    else GEMM_F32(1, 4, 6, 2);
+  } else if (!pairs || (small && m_tiles <= 4)) {
     if (m_tiles <= 2 || (m_tiles <= 4 && n_tiles * ksplit <= 300)) GEMM_F32(1, 1, 12, 3);
     else GEMM_F32(1, 2, 8, 3);
   } else if (m_tiles <= 2 || (small && slice < 512)) GEMM_F32(2, 2, 6, 2);

@@ -84,3 +84,8 @@ def test_a_row_keeps_its_bits_in_the_lm_head(vocab, sizes):
     (1280, 20, 4, 64, 2080, (33, 65, 97, 129, 193, 260))])    # 65 feature tiles; split-k of 2 and 3 m-tiles per workgroup
 def test_a_row_keeps_its_bits_in_small_matrices(d_model, n_q, n_kv, head_dim, d_ffn, sizes):
     check_bits(ai.ModelShape(1, d_model, n_q, n_kv, head_dim, d_ffn, 2080), 5, sizes)
+
+
+def test_a_row_keeps_its_bits_in_large_matrices_of_odd_tile_counts():
+    """QKV of 195 n-tiles in one slice, down of 81 in four: one n-tile per workgroup and one to four m-tiles, by the rows."""
+    check_bits(ai.ModelShape(1, 2592, 39 * 3, 39, 32, 2688, 2080), 5, (33, 64, 96, 120, 160, 190, 224, 300))
