@@ -489,6 +489,9 @@ void launch_gemm_mfma_logits(hipStream_t st, RowCtx rc, const bf16_t* x, const b
 //     3104 x 1184 (97 tiles) at 1, 32 rows 5.5, 6.1 / 6.9, 7.6; 9728 x 2560 (304) at 1, 16, 32 rows 21.3, 22.1, 25.0 / 23.5, 24.0,
 //     25.6; where whole ones fill more, the activations read twice as often cost more: 5120 x 4096 (160) 21.5, 25.9 / 18.7, 21.2.
 //   * several m-tiles that together are no more than a round: one each.  3072 x 2048 (96) at 64 rows 9.8 / 2 x 2 12.4.
+//   * 96 rows of more than 192 tiles, 128 of more than 152 (to 256): 2 x 3, whose first group alone is the round and takes all or most of
+//     the rows.  2 x 2 / 2 x 3 at 96 rows: 8192 x 3072 31.5 / 25.3, 6432 x 2048 (201 tiles) 18.5 / 17.3, 5120 x 4096 (160) 25.1 / 29.9; at 128:
+//     5120 x 4096 32.3 / 28.5, 5152 x 2560 (161, NEAR) 25.6 / 24.2, 7712 x 4096 (241, NEAR) 41.2 / 38.7, 4864 x 896 (152) 9.1 / 9.1.
 //   * else 2 x 2: 4864 x 896 at 64 rows two workgroups per unit 8.1 / three 8.7.  Four m-tiles at one per unit against
 //     three: 9728 x 2560 at 64, 96 rows 37.3, 42.5 / 30.7, 33.4.
 // NEAR where the weight tiles alone are more than a round of one workgroup per unit, and where their number is no multiple
@@ -507,6 +510,9 @@ void launch_gemm_mfma_swiglu(hipStream_t st, RowCtx rc, const bf16_t* x, const b
   const int tiles8 = ceil_div(n_tiles, 8) * 8, wgs = n_tiles * m_tiles;
   if (wgs <= 128 || (m_tiles == 1 && (n_tiles - 1) % 256 < 128)) GEMM_SW(1, 1, 10, 3, false, dim3(2 * n_tiles, 1, m_tiles));
   else if (m_tiles == 1 || (m_tiles <= 8 && wgs <= 256)) GEMM_SW(2, 1, 8, 3, false, dim3(n_tiles, 1, m_tiles));
+  else if (n_tiles <= 256 && ((m_tiles == 3 && n_tiles > 192) || (m_tiles == 4 && n_tiles > 152 && n_tiles % 8 == 0)))
+    GEMM_SW(2, 3, 5, 2, false, dim3(n_tiles, 1, ceil_div(m_tiles, 3)));
+  else if (n_tiles <= 256 && m_tiles == 4 && n_tiles > 152) GEMM_SW(2, 3, 5, 2, true, dim3(2 * tiles8));
   else if (m_tiles <= 2 && n_tiles <= 256) GEMM_SW(2, 2, 8, 2, false, dim3(n_tiles));
   else if (n_tiles <= 256 && n_tiles % 8 == 0) GEMM_SW(2, 2, 4, 3, false, dim3(n_tiles, 1, ceil_div(m_tiles, 2)));
   else if (n_tiles <= 256 || m_tiles <= 3) GEMM_SW(2, 2, 4, 3, true, dim3(tiles8 * ceil_div(m_tiles, 2)));

@@ -89,3 +89,9 @@ def test_a_row_keeps_its_bits_in_small_matrices(d_model, n_q, n_kv, head_dim, d_
 def test_a_row_keeps_its_bits_in_large_matrices_of_odd_tile_counts():
     """QKV of 195 n-tiles in one slice, down of 81 in four: one n-tile per workgroup and one to four m-tiles, by the rows."""
     check_bits(ai.ModelShape(1, 2592, 39 * 3, 39, 32, 2688, 2080), 5, (33, 64, 96, 120, 160, 190, 224, 300))
+
+
+@pytest.mark.parametrize("d_ffn,sizes", [(6208, (90, 96)), (4896, (100, 128)), (5120, (100, 128))])
+def test_a_row_keeps_its_bits_in_gate_up_of_three_m_tiles(d_ffn, sizes):
+    """194 tiles at 96 rows, 153 and 160 (grid order) at 128 rows: a group of three m-tiles, alone or before one of one."""
+    check_bits(ai.ModelShape(1, 128, 4, 2, 32, d_ffn, 2080), 5, sizes)
