@@ -1,5 +1,7 @@
 // Scheduler, allocator, embedding, RMSNorm, rotary + KV append, reference attention,
 // reference GEMM, SiLU*mul.  gfx950, wave64.
+#include <type_traits>
+
 #include "kernels.h"
 
 namespace april {
@@ -593,6 +595,10 @@ template void launch_attn_ref<bf16_t, true>(hipStream_t, RowCtx, Slots, const fl
 // token order: the sum's order depends on the row's own length only, in prefill and decode alike.
 // One token per trip (6 dependent shuffles, 2 exponentials and 2 loads each) took 38 us per launch
 // at 32 rows of 33-128 tokens; this takes 6.5 us (both with the 2 us that a profiler adds).
+// Registers decide how many rows a compute unit works on: 112 to 128 here.  With a step's keys and 64 values requested together (171 for
+// heads of 32, 255 of 64) two wavefronts fit a SIMD, and a whole step's address arithmetic with bounds was a third of the time.
+// us per launch, that / this: prefill of 16 384 rows, 4 heads of 32 in prompts of 32, 256, 4096 tokens 167, 350, 4045 / 82, 197, 2340,
+// 12 + 3 of 64 777, 1862, 22 900 / 348, 1053, 13 570; decode of 1 and 256 rows of 1024 tokens 56, 67 / 32, 50 and 97, 242 / 53, 149.
 // ---------------------------------------------------------------------------
 template <int DH, class Out>
 __device__ __forceinline__ void attn_f32_row(const f32x4* sq, const float* kv_pool, const int* bt, const KVLayout& L, int layer, int kvh,
@@ -608,51 +614,48 @@ __device__ __forceinline__ void attn_f32_row(const f32x4* sq, const float* kv_po
     const bool live = lane < n;
     const int page = bt[(live ? j : ctx - 1) >> 4];
     const f32x4* k = reinterpret_cast<const f32x4*>(kv_pool + L.at(layer, 0, page, kvh, (live ? j : ctx - 1) & 15, 0));
-    f32x4 kv[DH / 4];
-#pragma unroll
-    for (int c = 0; c < DH / 4; ++c) kv[c] = k[c];
-    // the values of the step are requested with its keys (heads of 64 and less: 32 or 64 registers)
-    auto value = [&](int t, int e) {                 // token t + vt of the step (t + TG - 1 lies in the page of t)
-      const int vp = __builtin_amdgcn_readlane(page, min(t, n - 1));
-      return kv_pool + L.at(layer, 1, vp, kvh, min(t + vt, n - 1) & 15, vd) + e;
-    };
-    constexpr int EARLY = DL == 1 ? 64 / TG : 0;
-    float ve[EARLY > 0 ? EARLY : 1];
-#pragma unroll
-    for (int u = 0; u < EARLY; ++u) ve[u] = *value(u * TG, 0);
     float acc[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int c = 0; c < DH / 4; ++c) {
-      const f32x4 qv = sq[c];
+    for (int c0 = 0; c0 < DH / 4; c0 += 8) {         // 32 dimensions of the keys in registers at a time
+      f32x4 kv[8];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) acc[e] = __fmaf_rn(kv[c][e], qv[e], acc[e]);
+      for (int c = 0; c < 8; ++c) kv[c] = k[c0 + c];
+#pragma unroll
+      for (int c = 0; c < 8; ++c) {
+        const f32x4 qv = sq[c0 + c];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[e] = __fmaf_rn(kv[c][e], qv[e], acc[e]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
     }
     const float sc = live ? ((acc[0] + acc[1]) + (acc[2] + acc[3])) * scale : -INFINITY;
     const float m_new = fmaxf(m, wave_max_f32(sc)), corr = expf(m - m_new), p = live ? expf(sc - m_new) : 0.f;
     l = __fmaf_rn(l, corr, wave_sum(p));
     m = m_new;
     float add[DL] = {};
-    if constexpr (EARLY > 0) {                       // (tokens past the end have probability 0 and add nothing)
+    // 16 loads of values in flight.  whole: 64 tokens, as in every step but a row's last - no bounds, constant offsets in a page
+    auto values = [&](int t0, auto whole) {
+      constexpr int U = 16;
+      float v[U][DL], pt[U];
 #pragma unroll
-      for (int u = 0; u < EARLY; ++u) {
-        const float pt = __shfl(p, u * TG + vt, 64);
-        add[0] = u * TG + vt < n ? __fmaf_rn(pt, ve[u], add[0]) : add[0];
+      for (int u = 0; u < U; ++u) {
+        const int t = t0 + u * TG, tv = whole ? t + vt : min(t + vt, n - 1);       // (t + TG - 1 lies in the page of t)
+        pt[u] = TG == 1 ? as_f32(__builtin_amdgcn_readlane(__float_as_int(p), tv)) : __shfl(p, tv, 64);
+        const float* src = kv_pool + L.at(layer, 1, __builtin_amdgcn_readlane(page, whole ? t : min(t, n - 1)), kvh, tv & 15, vd);
+#pragma unroll
+        for (int e = 0; e < DL; ++e) v[u][e] = src[e];
       }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int e = 0; e < DL; ++e) add[e] = whole || t0 + u * TG + vt < n ? __fmaf_rn(pt[u], v[u][e], add[e]) : add[e];
+    };
+    if (n == 64) {
+#pragma unroll
+      for (int t0 = 0; t0 < 64; t0 += 16 * TG) values(t0, std::true_type{});
     } else {
-      for (int t0 = 0; t0 < n; t0 += 16 * TG) {      // 16 loads in flight
-        float v[16][DL], pt[16];
-#pragma unroll
-        for (int u = 0; u < 16; ++u) {
-          pt[u] = __shfl(p, min(t0 + u * TG + vt, n - 1), 64);
-#pragma unroll
-          for (int e = 0; e < DL; ++e) v[u][e] = *value(t0 + u * TG, e);
-        }
-#pragma unroll
-        for (int u = 0; u < 16; ++u)
-#pragma unroll
-          for (int e = 0; e < DL; ++e)
-            add[e] = t0 + u * TG + vt < n ? __fmaf_rn(pt[u], v[u][e], add[e]) : add[e];
-      }
+#pragma unroll 1
+      for (int t0 = 0; t0 < n; t0 += 16 * TG) values(t0, std::false_type{});
     }
 #pragma unroll
     for (int e = 0; e < DL; ++e) {
