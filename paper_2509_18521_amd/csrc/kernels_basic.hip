@@ -873,34 +873,56 @@ __device__ __forceinline__ void row_gemv(const float* __restrict__ W, const floa
     }
   }
 }
-// out[m][n] = x[m] . W[n] with the same sums: 32 columns x 4 rows per workgroup.
+// out[m][n] = x[m] . W[n] with the same sums: 32 NC columns x 4 rows per workgroup, a lane's columns 32 apart.
+template <int NC>
 __global__ __launch_bounds__(256) void gemm_f32_dot_kernel(RowCtx rc, const float* __restrict__ x, const float* __restrict__ W,
                                                            float* __restrict__ out, int N, int K) {
-  constexpr int MT = 4;
+  constexpr int MT = 4, UNROLL = NC < 4 ? 4 : 1;
   const int rows = rows_or_zero(rc), m0 = blockIdx.y * MT;
   if (m0 >= rows) return;
-  const int l = threadIdx.x & 7, n = blockIdx.x * 32 + (int)(threadIdx.x >> 3);
-  const float* wp = W + (size_t)min(n, N - 1) * K;
-  f32x4 acc[MT];
+  const int l = threadIdx.x & 7, n = blockIdx.x * 32 * NC + (int)(threadIdx.x >> 3);
+  const float *wp[NC], *xp[MT];
 #pragma unroll
-  for (int m = 0; m < MT; ++m) acc[m] = f32x4{};
-#pragma unroll 4
+  for (int c = 0; c < NC; ++c) wp[c] = W + (size_t)min(n + 32 * c, N - 1) * K;
+#pragma unroll
+  for (int m = 0; m < MT; ++m) xp[m] = x + (size_t)min(m0 + m, rows - 1) * K;
+  f32x4 acc[MT][NC];
+#pragma unroll
+  for (int m = 0; m < MT; ++m)
+#pragma unroll
+    for (int c = 0; c < NC; ++c) acc[m][c] = f32x4{};
+#pragma unroll UNROLL
   for (int k = 4 * l; k < K; k += 32) {
-    const f32x4 w = *reinterpret_cast<const f32x4*>(wp + k);
-    f32x4 xv[MT];
+    f32x4 w[NC], xv[MT];
 #pragma unroll
-    for (int m = 0; m < MT; ++m) xv[m] = *reinterpret_cast<const f32x4*>(x + (size_t)min(m0 + m, rows - 1) * K + k);
+    for (int c = 0; c < NC; ++c) w[c] = *reinterpret_cast<const f32x4*>(wp[c] + k);
 #pragma unroll
-    for (int m = 0; m < MT; ++m) fma4(w, xv[m], acc[m]);
+    for (int m = 0; m < MT; ++m) xv[m] = *reinterpret_cast<const f32x4*>(xp[m] + k);
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+      for (int c = 0; c < NC; ++c) fma4(w[c], xv[m], acc[m][c]);
   }
 #pragma unroll
-  for (int m = 0; m < MT; ++m) {
-    const float v = sum8(acc[m]);
-    if (l == 0 && n < N && m0 + m < rows) out[(size_t)(m0 + m) * N + n] = v;
-  }
+  for (int m = 0; m < MT; ++m)
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      const float v = sum8(acc[m][c]);
+      if (l == 0 && n + 32 * c < N && m0 + m < rows) out[(size_t)(m0 + m) * N + n + 32 * c] = v;
+    }
 }
+// A weight is read again for every 4 rows, from L1: the more columns to a lane, the more products per byte of both operands, as long
+// as the workgroups still fill the chip.  us per launch, matrix instructions (gemm_f32_kernel) | 32, 64, 128 columns: 1024 x 128 at 24,
+// 96, 300, 16 384 rows 4.0, 5.7, 10.9, 443 | 2.7, 3.8, 8.0, 308 | 3.0, 3.6, 6.1, 193 | 3.7, 3.8, 5.9, 146; 256 x 256 at 300, 16 384 rows
+// 5.9, 113 | 5.5, 149 | 4.9, 94 | 4.8, 69; 128 x 512 at 300, 768, 16 384 rows 4.8, 6.5, 59 | 6.6, 9.1, 145 | 5.2, 7.7, 94 | 6.9, 7.1, 67.
 void launch_gemm_f32_dot(hipStream_t st, RowCtx rc, const float* x, const float* W, float* out, int N, int K) {
-  hipLaunchKernelGGL(gemm_f32_dot_kernel, dim3(ceil_div(N, 32), ceil_div(rc.max_rows, 4)), dim3(256), 0, st, rc, x, W, out, N, K);
+  const int m_groups = ceil_div(rc.max_rows, 4);
+  const long long units = (long long)ceil_div(N, 32) * m_groups;
+#define DOT_F32(NC) hipLaunchKernelGGL((gemm_f32_dot_kernel<NC>), dim3(ceil_div(N, 32 * NC), m_groups), dim3(256), 0, st, rc, x, W, out, N, K)
+  if (units <= 256) DOT_F32(1);
+  else if (units < 1024 || N <= 64) DOT_F32(2);
+  else DOT_F32(4);
+#undef DOT_F32
 }
 
 template <int DH>
@@ -990,7 +1012,10 @@ bool forward_f32_takes(int d, int F, int n_q_heads, int n_kv_heads, int head_dim
   const int nq = n_q_heads * head_dim, nqkv = nq + 2 * n_kv_heads * head_dim;
   const size_t layer_bytes = ((size_t)nqkv * d + (size_t)nq * d + (size_t)3 * F * d) * sizeof(float);
   const size_t head_bytes = (size_t)vocab * d * sizeof(float);
-  const bool fits = d <= 2048 && F % 4 == 0 && forward_f32_lds(d, F, nq, nqkv) <= (14u << 10);     // (and at most 2048 page ids: 64 KiB)
+  // Widths for which prefill's products lose nothing to the matrix instructions either, all of a layer's together: sums of up to
+  // about 400 terms are faster here, and a longer one (the down projection, the output projection) must not outweigh the others.
+  // At 16 384 rows 320 x 512 takes 185 us, 144 there; 16 x 6000 630, 107.  Activations then take at most 16 KiB of LDS.
+  const bool fits = F % 4 == 0 && d <= 384 && F <= 8 * d && nq <= 8 * d;
   return fits && head_bytes <= (512u << 10) && max_rows <= 320 && layer_bytes <= (max_rows <= 256 ? 1280u << 10 : 1100u << 10);
 }
 void launch_forward_f32(hipStream_t st, RowCtx rc, Slots s, F32Model m, float* logits) {

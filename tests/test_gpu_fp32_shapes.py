@@ -77,3 +77,29 @@ def test_decode_in_one_launch_keeps_a_prefilled_rollouts_bits(head_dim, n_q, n_k
             ap.april_destroy(ctx)
     for at, rows in got.items():
         assert all(np.array_equal(rows[0], x) for x in rows[1:]), at
+
+
+@pytest.mark.parametrize("head_dim,n_q,n_kv,d_model,d_ffn,vocab", [(32, 6, 2, 72, 52, 131), (64, 2, 1, 40, 4, 65), (32, 4, 4, 128, 512, 512)])
+def test_small_models_prompt_bits_do_not_depend_on_the_pass(head_dim, n_q, n_kv, d_model, d_ffn, vocab):
+    """The rows of a pass pick the columns per workgroup of its products (32, 64 and 128, with ends inside one): same sums."""
+    import paper_2509_18521_amd as ap
+    shape = ai.ModelShape(2, d_model, n_q, n_kv, head_dim, d_ffn, vocab, dtype=ai.DTYPE_FP32)
+    weights = ai.make_weights(shape, 3)
+    rng = np.random.default_rng(vocab)
+    prompts = [rng.integers(0, vocab, t, dtype=np.int32) for t in (5, 33, 64)]
+    dec = Decoder(shape, weights)
+    ref = [dec.forward_block(p, dec.new_cache())[-1] for p in prompts]
+    alone = None
+    for n in (3, 1, 12, 30, 150):
+        w = ai.Workload("fp32", shape, 1, 64, n, n, 1, 0.0, 0.1, 1, 1, ai.SAMPLER_GREEDY, 0, 1, 3)
+        ctx = make_engine(w, weights, debug=True, max_inflight=n)
+        try:
+            for i in range(n):
+                ap.april_debug_watch(ctx, i, 0, 1)
+            ap.april_rollout_step(ctx, req_dicts([ai.Request(i, prompts[i % 3], 1) for i in range(n)]), n, n, 1)
+            got = [ap.april_debug_logits(ctx, i, 0, vocab)[0] for i in range(n)]
+        finally:
+            ap.april_destroy(ctx)
+        alone = alone or got
+        for i, row in enumerate(got):
+            assert np.max(np.abs(row - ref[i % 3])) <= 1e-4 and np.array_equal(row, alone[i % 3]), (n, i)
