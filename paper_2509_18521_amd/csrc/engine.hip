@@ -113,7 +113,7 @@ struct april_ctx {
   std::vector<LayerW> layers;
   float* final_norm = nullptr;
   void* lm_head = nullptr;
-  bool f32_rows = false;               // small fp32 model: decode passes run as one launch, a workgroup per row
+  bool f32_dot = false;                // small fp32 model: every product has the sums of the one-launch decode pass
   F32Layer* d_f32_layers = nullptr;
   bf16_t* lm_head_s = nullptr;
   int64_t weight_bytes = 0, decode_weight_bytes = 0;
@@ -546,7 +546,7 @@ void forward(april_ctx* c, RowCtx rows, RowCtx srows, const int* gather, double 
   const int d = m.d_model, dh = m.head_dim, Hq = m.n_q_heads, Hkv = m.n_kv_heads, F = m.d_ffn, V = m.vocab;
   const int nq = Hq * dh, nkv = Hkv * dh, nqkv = nq + 2 * nkv;
   const double e = (double)c->esz;
-  if (c->f32_rows && gather == nullptr) {
+  if (c->f32_dot && gather == nullptr && forward_f32_pays(rows.max_rows)) {
     {
       ProfScope p(c, KC_FORWARD_F32, (double)c->decode_weight_bytes + C * 2.0 * m.n_layers * nkv * e + B * V * 4.0, 0);
       launch_forward_f32(st, rows, c->ds, F32Model{c->d_f32_layers, (const float*)c->tok_emb, c->final_norm, (const float*)c->lm_head,
@@ -587,7 +587,7 @@ void forward(april_ctx* c, RowCtx rows, RowCtx srows, const int* gather, double 
     if (tile) launch_gemm_tile(st, rc, (const bf16_t*)x, w_s, out, N, K);
     else if (c->use_mfma) launch_gemm_mfma(st, rc, (const bf16_t*)x, w_s, out, N, K, ks, stride, ssq, (int)c->m_cap, m.rms_eps);
     else if (c->bf16) launch_gemm_ref<bf16_t, true>(st, rc, (const bf16_t*)x, (const bf16_t*)w_plain, out, N, K);
-    else if (c->f32_rows) launch_gemm_f32_dot(st, rc, (const float*)x, (const float*)w_plain, out, N, K);
+    else if (c->f32_dot) launch_gemm_f32_dot(st, rc, (const float*)x, (const float*)w_plain, out, N, K);
     else launch_gemm_f32(st, rc, (const float*)x, (const float*)w_plain, out, N, K);
   };
   bool normed_by_down = false;       // the previous layer's down projection already did this layer's first norm
@@ -721,7 +721,7 @@ void forward(april_ctx* c, RowCtx rows, RowCtx srows, const int* gather, double 
         launch_gemm_mfma_logits(st, srows, (const bf16_t*)c->hf, c->lm_head_s, lg_out, go, V, d);
     }
     else if (c->bf16) launch_gemm_ref<bf16_t, true>(st, srows, (const bf16_t*)c->hf, (const bf16_t*)c->lm_head, c->logits, V, d);
-    else if (c->f32_rows) launch_gemm_f32_dot(st, srows, (const float*)c->hf, (const float*)c->lm_head, c->logits, V, d);
+    else if (c->f32_dot) launch_gemm_f32_dot(st, srows, (const float*)c->hf, (const float*)c->lm_head, c->logits, V, d);
     else launch_gemm_f32(st, srows, (const float*)c->hf, (const float*)c->lm_head, c->logits, V, d);
   }
   {
@@ -867,7 +867,7 @@ int april_init(const april_model_cfg* cfg, const april_tensor* weights, int32_t 
   c->esz = c->bf16 ? 2 : 4;
   const char* gm = getenv("APRIL_GEMM");
   c->use_mfma = c->bf16 && !(gm && !strcmp(gm, "ref"));
-  c->f32_rows = !c->bf16 && forward_f32_takes(d, F, g.n_q_heads, g.n_kv_heads, g.head_dim, V, g.max_inflight);
+  c->f32_dot = !c->bf16 && forward_f32_takes(d, F, nq, nqkv, V);
   const char* am = getenv("APRIL_ATTN");
   c->attn_mfma = c->bf16 && !(am && !strcmp(am, "ref"));
   if (moe && !(c->use_mfma && c->attn_mfma)) { delete c; return fail(nullptr, APRIL_EINVAL, "routed experts run on the MFMA path only"); }
@@ -915,7 +915,7 @@ int april_init(const april_model_cfg* cfg, const april_tensor* weights, int32_t 
   // ---- weights ------------------------------------------------------------------
   c->alloc_tag = g.pausable ? APRIL_MEM_WEIGHTS : 0;
   { int rc_w = load_weights(c, weights, n_weights); c->alloc_tag = 0; if (rc_w != APRIL_OK) return bail(rc_w); }
-  if (c->f32_rows) {
+  if (c->f32_dot) {
     // (outside the weights' region: a pause of the weights drops that region's contents, and the addresses stay)
     std::vector<F32Layer> fl;
     for (const LayerW& L : c->layers)

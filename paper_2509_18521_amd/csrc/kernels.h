@@ -266,7 +266,9 @@ void launch_attn_f32(hipStream_t st, RowCtx rc, Slots s, const float* q_rot, con
                      int layer, int n_q_heads, float* out);
 void launch_gemm_f32(hipStream_t st, RowCtx rc, const float* x, const float* W, float* out, int N, int K);
 // fp32 models of few weights: a decode pass from the tokens to the logits in one launch, a workgroup per row (K and V of
-// the new position appended), and the product that their prefill uses (its sums are the decode pass's; K % 4 == 0).
+// the new position appended), and the product that their other passes use (its sums are that pass's; K % 4 == 0).
+// Which models: by their dimensions alone, so that neither a context's capacity nor the rows of a pass change a bit of a
+// rollout.  Which decode passes take the one launch: by their rows (the same bits either way).
 struct F32Layer { const float *attn_norm, *mlp_norm, *wqkv, *wo, *wgu, *wd; };
 struct F32Model {
   const F32Layer* layers;              // device array
@@ -277,7 +279,8 @@ struct F32Model {
   float eps;
   int lds_floats;                      // (the launcher's)
 };
-bool forward_f32_takes(int d, int F, int n_q_heads, int n_kv_heads, int head_dim, int vocab, int max_rows);
+bool forward_f32_takes(int d, int F, int nq, int nqkv, int vocab);
+bool forward_f32_pays(int rows);
 void launch_forward_f32(hipStream_t st, RowCtx rc, Slots s, F32Model m, float* logits);
 void launch_gemm_f32_dot(hipStream_t st, RowCtx rc, const float* x, const float* W, float* out, int N, int K);
 

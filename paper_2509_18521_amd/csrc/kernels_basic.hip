@@ -813,9 +813,10 @@ void launch_gemm_f32(hipStream_t st, RowCtx rc, const float* x, const float* W, 
 // 24 rows) ran 22 kernels of 3-6 us for 1 MB of weights a layer.  Rows do not need each other, so here a workgroup takes a
 // row through the whole model - embedding to logits, 8 wavefronts, activations in LDS - and streams the weights from its L2 at
 // what one compute unit takes (30-50 bytes per clock).  That pays while a layer's weights take less than its launches did.
-// us per decode iteration at 1, 24, 96, 300 rows, separate launches / this: two layers of 1.05 MB 73, 85, 91, 124 / 52, 54, 59,
-// 110; four of 0.98 143, 163, 179, 239 / 113, 116, 114, 221; two of 1.24 88, 101, 107, 143 / 66, 70, 76, 146; two of 1.48
-// 80, 91, 105, 137 / 84, 91, 91, 175; two of 1.47 and a head of 1.3 82, 92, 106, 151 / 100, 103, 102, 195: the rule is forward_f32_takes.
+// us per decode iteration of two layers, contexts of 32-97 tokens, at 1, 24, 96, 256, 310 rows, separate launches / this: 1.05 MB a layer (width
+// 128, 4 heads of 32) 70, 80, 84, 100, 114 / 49, 51, 56, 61, 106; 1.21 MB (8 heads) 73, 80, 92, 110, 123 / 54, 59, 64, 69, 121; 0.88 MB (2 heads
+// of 128) 76, 86, 88, 104, 115 / 53, 56, 60, 65, 115.  Beyond a layer of about 1.3 MB or a head of 0.5 MB (1.48 MB: 80, 91, 105 /
+// 84, 91, 91; 1.47 MB with a head of 1.3: 82, 92, 106 / 100, 103, 102) the weights take longer than the launches did.
 //
 // Dot products: 8 lanes, four consecutive k each per 32, an accumulator for each of the four, added pairwise, then over the
 // lanes by a fixed tree (32 lanes to a column spend three times the instructions: the pass was bound by them, 27 bytes per
@@ -1008,16 +1009,16 @@ __global__ __launch_bounds__(ROW_THREADS) void forward_f32_kernel(RowCtx rc, Slo
   row_gemv<4, 4>(m.lm_head, h, m.vocab, d, [&](int n, float v) { logits[(size_t)r * m.vocab + n] = v; });
 }
 static size_t forward_f32_lds(int d, int F, int nq, int nqkv) { return (size_t)(2 * d + (nqkv + nq > 2 * F ? nqkv + nq : 2 * F)); }     // floats
-bool forward_f32_takes(int d, int F, int n_q_heads, int n_kv_heads, int head_dim, int vocab, int max_rows) {
-  const int nq = n_q_heads * head_dim, nqkv = nq + 2 * n_kv_heads * head_dim;
+bool forward_f32_takes(int d, int F, int nq, int nqkv, int vocab) {
   const size_t layer_bytes = ((size_t)nqkv * d + (size_t)nq * d + (size_t)3 * F * d) * sizeof(float);
   const size_t head_bytes = (size_t)vocab * d * sizeof(float);
   // Widths for which prefill's products lose nothing to the matrix instructions either, all of a layer's together: sums of up to
   // about 400 terms are faster here, and a longer one (the down projection, the output projection) must not outweigh the others.
   // At 16 384 rows 320 x 512 takes 185 us, 144 there; 16 x 6000 630, 107.  Activations then take at most 16 KiB of LDS.
   const bool fits = F % 4 == 0 && d <= 384 && F <= 8 * d && nq <= 8 * d;
-  return fits && head_bytes <= (512u << 10) && max_rows <= 320 && layer_bytes <= (max_rows <= 256 ? 1280u << 10 : 1100u << 10);
+  return fits && head_bytes <= (512u << 10) && layer_bytes <= (1280u << 10);
 }
+bool forward_f32_pays(int rows) { return rows <= 256; }       // a row per compute unit
 void launch_forward_f32(hipStream_t st, RowCtx rc, Slots s, F32Model m, float* logits) {
   const int nq = m.n_q_heads * m.kvl.head_dim, nqkv = nq + 2 * m.kvl.n_kv_heads * m.kvl.head_dim;
   m.lds_floats = (int)forward_f32_lds(m.d, m.F, nq, nqkv);

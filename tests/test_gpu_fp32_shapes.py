@@ -103,3 +103,34 @@ def test_small_models_prompt_bits_do_not_depend_on_the_pass(head_dim, n_q, n_kv,
         alone = alone or got
         for i, row in enumerate(got):
             assert np.max(np.abs(row - ref[i % 3])) <= 1e-4 and np.array_equal(row, alone[i % 3]), (n, i)
+
+
+@pytest.mark.parametrize("d_ffn", [512, 600, 800])
+def test_small_models_bits_do_not_depend_on_capacity_or_batch(d_ffn):
+    """Layers of 1.0, 1.2 and 1.4 MiB (the last beyond the one-launch pass): the same rollouts in contexts of few and many slots, alone
+    and among so many that a decode pass runs as separate launches."""
+    import paper_2509_18521_amd as ap
+    shape = ai.ModelShape(2, 128, 4, 4, 32, d_ffn, 300, dtype=ai.DTYPE_FP32)
+    weights = ai.make_weights(shape, 11)
+    rng = np.random.default_rng(d_ffn)
+    gen = 5
+    prompts = [rng.integers(0, 300, t, dtype=np.int32) for t in (1, 15, 40, 62, 70)]
+    forced = rng.integers(0, 300, (5, gen), dtype=np.int32)
+    dec = Decoder(shape, weights)
+    first = None
+    for n, slots in ((5, 5), (5, 256), (5, 257), (5, 321), (260, 260), (300, 330)):
+        w = ai.Workload("fp32", shape, 1, 70, n, n, gen, 0.0, 0.1, gen, gen, ai.SAMPLER_GREEDY, 0, 1, 11)
+        ctx = make_engine(w, weights, debug=True, max_inflight=slots)
+        try:
+            for i in range(5):
+                ap.april_debug_watch(ctx, i, 0, gen)
+            ap.april_rollout_step(ctx, req_dicts([ai.Request(i, prompts[i % 5], gen) for i in range(n)], {i: forced[i % 5] for i in range(n)}), n, n, gen)
+            got = [[ap.april_debug_logits(ctx, i, g, 300)[0] for g in range(gen)] for i in range(5)]
+        finally:
+            ap.april_destroy(ctx)
+        if first is None:
+            first = got
+            for i in range(5):
+                ref = dec.forward_block(np.concatenate([prompts[i], forced[i][:-1]]), dec.new_cache())[-gen:]
+                assert np.max(np.abs(np.array(got[i]) - ref)) <= 1e-4, i
+        assert np.array_equal(np.array(first), np.array(got)), (n, slots)
