@@ -546,7 +546,7 @@ void forward(april_ctx* c, RowCtx rows, RowCtx srows, const int* gather, double 
   const int d = m.d_model, dh = m.head_dim, Hq = m.n_q_heads, Hkv = m.n_kv_heads, F = m.d_ffn, V = m.vocab;
   const int nq = Hq * dh, nkv = Hkv * dh, nqkv = nq + 2 * nkv;
   const double e = (double)c->esz;
-  if (c->f32_dot && gather == nullptr && forward_f32_pays(rows.max_rows)) {
+  if (c->f32_dot && gather == nullptr && forward_f32_pays(rows.max_rows, c->step_max_ctx, nq)) {
     {
       ProfScope p(c, KC_FORWARD_F32, (double)c->decode_weight_bytes + C * 2.0 * m.n_layers * nkv * e + B * V * 4.0, 0);
       launch_forward_f32(st, rows, c->ds, F32Model{c->d_f32_layers, (const float*)c->tok_emb, c->final_norm, (const float*)c->lm_head,
@@ -795,14 +795,26 @@ extern "C" {
 
 const char* april_last_error(const april_ctx* ctx) { return ctx ? ctx->err.c_str() : g_init_error.c_str(); }
 
+// Bounds on the contexts of a decode iteration come in classes: the KV splits of the bf16 attention; what a small fp32 model's
+// one-launch pass takes of few rows, of many, and anything longer.
+static int ctx_class(const april_ctx* c, int ctx) {
+  if (c->attn_mfma) return std::min(c->attn_max_splits, std::max(1, ceil_div(ctx, c->attn_chunk)));
+  const int nq = c->dm.n_q_heads * c->dm.head_dim;
+  return !c->f32_dot || ctx <= forward_f32_ctx(nq, false) ? 1 : (ctx <= forward_f32_ctx(nq, true) ? 2 : 3);
+}
+static int ctx_class_bound(const april_ctx* c, int cls) {
+  if (c->attn_mfma) return cls * c->attn_chunk;
+  return !c->f32_dot || cls == 3 ? c->max_ctx : std::min(c->max_ctx, forward_f32_ctx(c->dm.n_q_heads * c->dm.head_dim, cls == 2));
+}
+
 // The graph of n_iters decode iterations (each: scheduler + forward + sampler) sized for at most
-// rows_cap live rows and gs KV splits; instantiated on first use and kept for the context's life.
+// rows_cap live rows and contexts of class gs; instantiated on first use and kept for the context's life.
 static int iter_graph(april_ctx* c, int rows_cap, int gs, int n_iters, hipGraphExec_t* out) {
   const std::pair<int, int> key{rows_cap | (n_iters << 24), gs};
   auto it = c->iter_graphs.find(key);
   if (it == c->iter_graphs.end()) {
     hipStream_t st = c->stream;
-    const int ctx_grid = c->attn_mfma ? gs * c->attn_chunk : c->max_ctx;
+    const int ctx_grid = ctx_class_bound(c, gs);
     hipGraph_t graph = nullptr;
     c->prof_now = false;
     RowCtx grc{c->d_row_slot, c->d_row_pos, reinterpret_cast<const int2*>(c->d_ctrl), rows_cap};
@@ -1073,13 +1085,13 @@ int april_init(const april_model_cfg* cfg, const april_tensor* weights, int32_t 
     TRY(dev_alloc(c, &c->dwatch.sampled, c->watch_rows_cap)); TRY(dev_alloc(c, &c->dwatch.filled, c->watch_rows_cap));
   }
   HIPTRY(hipStreamSynchronize(c->stream));
-  // Graphs of the decode iteration for every (row bound, KV splits) a step can meet, when they
+  // Graphs of the decode iteration for every (row bound, context class) a step can meet, when they
   // are few (small models, where an instantiation inside a step would show): otherwise on first use.
   if (c->use_graph) {
     std::vector<int> row_bounds;
     for (int rb = 32; rb < c->n_slots; rb += 32) row_bounds.push_back(rb);
     row_bounds.push_back(c->n_slots);
-    const int n_gs = c->attn_mfma ? c->attn_max_splits : 1;
+    const int n_gs = ctx_class(c, c->max_ctx);
     if ((int)row_bounds.size() * n_gs * (c->graph_iters > 1 ? 2 : 1) <= 48) {
       for (int rb : row_bounds)
         for (int gs = 1; gs <= n_gs; ++gs) {
@@ -1855,7 +1867,7 @@ int april_rollout_step(april_ctx* c, const april_request* new_reqs, int32_t n_ne
       *rows_cap = rb;
       *ctx_cap = std::min(c->max_ctx, ctx_prefix_max[n_alive] + it);
     };
-    // one captured graph per (row bound, KV-split bound), replayed by every iteration that fits it
+    // one captured graph per (row bound, context class), replayed by every iteration that fits it
     bool stopped = false;
     int launched = 1;
     const int chunk = 32;
@@ -1867,8 +1879,8 @@ int april_rollout_step(april_ctx* c, const april_request* new_reqs, int32_t n_ne
       for (int k = 0; k < todo; ++k) {
         int rows_cap = 0, ctx_cap = 0;
         bounds_at(launched + k + 1, &rows_cap, &ctx_cap);
-        const int gs = c->attn_mfma ? std::min(c->attn_max_splits, std::max(1, ceil_div(ctx_cap, c->attn_chunk))) : 1;
-        c->it_rows[k] = rows_cap; c->it_gs[k] = gs; c->it_ctx[k] = c->attn_mfma ? gs * c->attn_chunk : c->max_ctx;
+        const int gs = ctx_class(c, ctx_cap);
+        c->it_rows[k] = rows_cap; c->it_gs[k] = gs; c->it_ctx[k] = ctx_class_bound(c, gs);
       }
       auto profiled = [&](int it) { return c->prof_every > 0 && (it % c->prof_every) == 0; };
       for (int k = 0; k < todo; ++k) {

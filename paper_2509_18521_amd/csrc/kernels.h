@@ -268,7 +268,7 @@ void launch_gemm_f32(hipStream_t st, RowCtx rc, const float* x, const float* W, 
 // fp32 models of few weights: a decode pass from the tokens to the logits in one launch, a workgroup per row (K and V of
 // the new position appended), and the product that their other passes use (its sums are that pass's; K % 4 == 0).
 // Which models: by their dimensions alone, so that neither a context's capacity nor the rows of a pass change a bit of a
-// rollout.  Which decode passes take the one launch: by their rows (the same bits either way).
+// rollout.  Which decode passes take the one launch: by bounds on their rows and contexts (the same bits either way).
 struct F32Layer { const float *attn_norm, *mlp_norm, *wqkv, *wo, *wgu, *wd; };
 struct F32Model {
   const F32Layer* layers;              // device array
@@ -280,7 +280,8 @@ struct F32Model {
   int lds_floats;                      // (the launcher's)
 };
 bool forward_f32_takes(int d, int F, int nq, int nqkv, int vocab);
-bool forward_f32_pays(int rows);
+bool forward_f32_pays(int rows, int ctx, int nq);
+int forward_f32_ctx(int nq, bool many_rows);      // the longest contexts that it takes
 void launch_forward_f32(hipStream_t st, RowCtx rc, Slots s, F32Model m, float* logits);
 void launch_gemm_f32_dot(hipStream_t st, RowCtx rc, const float* x, const float* W, float* out, int N, int K);
 

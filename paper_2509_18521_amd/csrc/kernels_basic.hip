@@ -1018,7 +1018,16 @@ bool forward_f32_takes(int d, int F, int nq, int nqkv, int vocab) {
   const bool fits = F % 4 == 0 && d <= 384 && F <= 8 * d && nq <= 8 * d;
   return fits && head_bytes <= (512u << 10) && layer_bytes <= (1280u << 10);
 }
-bool forward_f32_pays(int rows) { return rows <= 256; }       // a row per compute unit
+// A row's heads share one compute unit here, eight at a time, and have one wavefront each across the chip as launches of their own: past some
+// length that is worth the launches, past a greater one where many rows share the chip anyway.  us per iteration of two layers at 1, 24,
+// 96, 200 rows, separate launches / this: 4 heads of 32 of 500 tokens 98, 113, 124, 137 / 81, 95, 95, 96, of 1200 136, 161, 171, 231 / 144,
+// 146, 148, 189, of 3000 239, 274, 357, - / 276, 281, 354, -; 8 of 32 of 160 tokens 80, 89, 106, 120 / 66, 77, 77, 79, of 500 100, 118, 131, 181
+// / 106, 109, 107, 144, of 1200 141, 162, 219, 282 / 169, 173, 217, 240; 16 of 32 of 160 79, 88, 103, 120 / 79, 82, 90, 90, of 500 99, 113,
+// 133, 167 / 132, 148, 149, 150; 12 of 64 of 32 tokens 80, 89, 104, 121 / 72, 76, 83, 85, of 160 93, 106, 127, 147 / 107, 121, 124, 124, of
+// 500 126, 150, 173, 243 / 206, 229, 228, 269.  Beyond 256 rows a compute unit has two: 310 rows of 32, 160, 500 tokens, 4 heads of 32, 114,
+// 125, 173 / 106, 129, 204.
+int forward_f32_ctx(int nq, bool many_rows) { return (81920 / nq < 1024 ? 81920 / nq : 1024) * (many_rows ? 3 : 1); }
+bool forward_f32_pays(int rows, int ctx, int nq) { return rows <= 256 && ctx <= forward_f32_ctx(nq, rows >= 128); }
 void launch_forward_f32(hipStream_t st, RowCtx rc, Slots s, F32Model m, float* logits) {
   const int nq = m.n_q_heads * m.kvl.head_dim, nqkv = nq + 2 * m.kvl.n_kv_heads * m.kvl.head_dim;
   m.lds_floats = (int)forward_f32_lds(m.d, m.F, nq, nqkv);

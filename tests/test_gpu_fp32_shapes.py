@@ -134,3 +134,33 @@ def test_small_models_bits_do_not_depend_on_capacity_or_batch(d_ffn):
                 ref = dec.forward_block(np.concatenate([prompts[i], forced[i][:-1]]), dec.new_cache())[-gen:]
                 assert np.max(np.abs(np.array(got[i]) - ref)) <= 1e-4, i
         assert np.array_equal(np.array(first), np.array(got)), (n, slots)
+
+
+def test_small_models_bits_do_not_depend_on_where_decode_turns_to_separate_launches():
+    """16 heads: contexts up to 160 tokens decode in one launch, up to 480 where there are many rows, longer ones in separate launches,
+    within a step.  Logits of positions around the turns: the same bits as prefilled there, alone, beside a longer rollout and among
+    many short ones, and as the oracle's."""
+    import paper_2509_18521_amd as ap
+    shape = ai.ModelShape(2, 64, 16, 4, 32, 256, 200, dtype=ai.DTYPE_FP32)
+    weights = ai.make_weights(shape, 2)
+    text = np.random.default_rng(5).integers(0, 200, 560, dtype=np.int32)
+    dec = Decoder(shape, weights)
+    ref = dec.forward_block(text[:500], dec.new_cache())
+    rows = {}
+    for prompt, gen, others in ((150, 20, []), (150, 20, [300]), (150, 20, [5] * 140), (470, 20, [5] * 140), (157, 4, []), (158, 4, []),
+                                (159, 4, []), (160, 4, []), (165, 4, []), (477, 4, []), (480, 4, [])):
+        n = 1 + len(others)
+        w = ai.Workload("fp32", shape, 1, 500, n, n, 24, 0.0, 0.1, 24, 24, ai.SAMPLER_GREEDY, 0, 1, 2)
+        ctx = make_engine(w, weights, debug=True, max_inflight=n, max_ctx=560 if others else 32768)     # (a page list of every length in LDS)
+        reqs = [ai.Request(i, text[:t], gen) for i, t in enumerate([prompt] + others)]
+        try:
+            ap.april_debug_watch(ctx, 0, 0, gen)
+            ap.april_rollout_step(ctx, req_dicts(reqs, {r.request_id: text[len(r.tokens):len(r.tokens) + gen] for r in reqs}), n, n, gen)
+            for g in range(gen):
+                got, at = ap.april_debug_logits(ctx, 0, g, 200)[0], prompt + g - 1
+                assert np.max(np.abs(got - ref[at])) <= 1e-4, (prompt, g)
+                rows.setdefault(at, []).append(got)
+        finally:
+            ap.april_destroy(ctx)
+    for at, got in rows.items():
+        assert all(np.array_equal(got[0], x) for x in got[1:]), at
