@@ -278,3 +278,35 @@ def test_whole_row_searches_make_no_group_records(vocab, top_k):
         _, p = osampler.top_k_probs(row, top_k, T)
         u = uniform_for(seed, int(ids[r]), 0)
         assert np.min(np.abs(np.cumsum(p)[:-1] - u)) < 1e-9 or int(tok[r]) == osampler.top_k_sample(row, top_k, T, u), r
+
+
+@pytest.mark.parametrize("n_groups", [4096, 4097])
+@pytest.mark.parametrize("top_k", [50, 64])
+def test_topk_lists_that_overflow_fall_back_to_the_whole_row(n_groups, top_k):
+    """More groups at the bound than the list of groups holds (1024: a constant row, a row of two values), and more candidates in
+    few groups than the list of candidates holds (2048: 40 and 100 groups full of the maximum), among ordinary rows."""
+    import torch
+    vocab, T, seed = 64 * n_groups, float(np.float32(0.8)), 21
+    rng = np.random.default_rng([n_groups, top_k])
+    logits = rng.standard_normal((6, vocab)).astype(np.float32)
+    logits[0] = 0.25
+    logits[1] = np.where(rng.random(vocab) < 0.5, 1.0, -1.0)
+    for r, full in ((2, 40), (3, 100)):
+        for g in rng.choice(n_groups, full, replace=False):
+            logits[r, 64 * g:64 * g + 64] = 6.0
+    logits[4] = 0.25
+    logits[4, -1] = 9.0                                           # the maximum in the last group, ties behind it
+    ids, idx = np.arange(6, dtype=np.int64) + 40, np.arange(6, dtype=np.int32)
+    ap, ctx = engine(vocab, ai.SAMPLER_TOPK, top_k, T, seed)
+    try:
+        dev = torch.from_numpy(logits).cuda()
+        tok, lp = ap.april_sample_rows_logprobs(ctx, dev.data_ptr(), 6, ids, idx)
+        alone = ap.april_sample_rows_noalloc(ctx, dev.data_ptr(), 6, ids, idx)
+    finally:
+        ap.april_destroy(ctx)
+    assert np.array_equal(tok, alone)
+    for r in range(6):
+        _, p = osampler.top_k_probs(logits[r], top_k, T)
+        u = uniform_for(seed, int(ids[r]), int(idx[r]))
+        assert np.min(np.abs(np.cumsum(p)[:-1] - u)) < 1e-9 or int(tok[r]) == osampler.top_k_sample(logits[r], top_k, T, u), r
+        assert abs(float(lp[r]) - osampler.token_logprob(logits[r], T, int(tok[r]))) < 2e-5, r
