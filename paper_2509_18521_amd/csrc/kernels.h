@@ -338,10 +338,11 @@ void launch_rope_table(hipStream_t st, float* cos_t, float* sin_t, int max_pos, 
 
 // --- sampler + per-rollout state update ---------------------------------------
 // Top-k search of a vocabulary with a short last group: in the groups whose maximum reaches the k-th largest one, or over the
-// whole row.  Up to 4096 logits the whole row is read once and kept in registers, and with fewer than 2 k groups most
-// of them are hot and their candidates many.  us per call for 1000 rows, whole row | groups: 20 of 2001 63 | 71, of 4095 69 |
-// 69, of 6001 78 | 71; 50 of 4095 81 | 95, of 6001 (94 groups) 90 | 94, of 8001 105 | 92; 64 of 4095 88 | 175, of 8001 (126) 112 | 103.
-inline __host__ __device__ bool topk_in_groups(int V, int k) { return V % 64 == 0 || (V > 4096 && (V + 63) / 64 >= 2 * k); }
+// whole row.  Up to 4096 logits the whole row is read once and kept in registers, and with few more than k groups most
+// of them are hot and their candidates many.  us per call for 5, 1000 rows, whole row | groups: 20 of 2001 25, 48 | 27, 50, of 4095 26, 54 |
+// 28, 50, of 6001 28, 63 | 28, 52; 50 of 4095 26, 55 | 28, 53, of 6001 (94 groups) 28, 64 | 29, 55, of 8001 32, 77 | 29, 56; 64 of 4095
+// 26, 55 | 31, 70, of 6001 28, 65 | 29, 57, of 8001 (126) 32, 78 | 29, 58: from about 1.5 k groups on they win, 2 k is the line of earlier kernels.
+inline bool topk_in_groups(int V, int k) { return V % 64 == 0 || (V > 4096 && (V + 63) / 64 >= 2 * k); }
 struct SamplerCfg {
   int kind, top_k;            // kind: 0 greedy, 1 top-k (+ nucleus), 2 categorical over the whole vocabulary
   float temperature;

@@ -29,7 +29,7 @@ void launch_shuffle_weights(hipStream_t st, const bf16_t* src, bf16_t* dst, int 
                      reinterpret_cast<bf16x8*>(dst), N, K);
 }
 
-enum { EPI_F32 = 0, EPI_SWIGLU = 1, EPI_LOGITS = 2, EPI_RESID = 3 };
+enum { EPI_F32 = 0, EPI_SWIGLU = 1, EPI_RESID = 2 };
 
 // RMSNorm folded into the GEMMs around it (decode).  The producer (EPI_RESID, the attention
 // output projection) adds its result to the residual stream in place, writes the residual times
@@ -43,7 +43,6 @@ struct NormFuse {
   int ssq_stride;        // rows per n-tile slab
   int n_ssq;             // consumer: number of slabs (= d_model / 32)
   float inv_d, eps;      // consumer
-  GroupOut go;           // EPI_LOGITS: group records
 };
 
 constexpr int KW4 = 4;       // wavefronts of a workgroup (template parameter KW); they split the k range among themselves
@@ -445,7 +444,7 @@ __global__ __launch_bounds__(64 * KW4, 1) void gemm_logits_kernel(const int2* __
 // 3.6, 4.0, 5.0; 6144 x 2560 10.6, 10.8, 14.3 / 8.3, 9.1, 12.4; 2560 x 9728 12.7, 12.9, 16.9 / 11.2, 11.7, 15.2.
 void launch_gemm_mfma(hipStream_t st, RowCtx rc, const bf16_t* x, const bf16_t* Wp, float* out, int N, int K,
                       int ksplit, size_t partial_stride, const float* ssq, int ssq_stride, float eps) {
-  const NormFuse nf{nullptr, const_cast<float*>(ssq), ssq_stride, K >> 5, 1.0f / (float)K, eps, {}};
+  const NormFuse nf{nullptr, const_cast<float*>(ssq), ssq_stride, K >> 5, 1.0f / (float)K, eps};
   const int n_tiles = N >> 5, m_tiles = ceil_div(rc.max_rows, 32), slice = K / ksplit, per_group = n_tiles / 4 * ksplit;
   const bool quads = n_tiles % 4 == 0, long_slices = quads && slice >= 1536;
   auto round_tiles = [&](int mt) { return ceil_div(ceil_div(m_tiles, mt) * per_group, 256) * mt; };
@@ -502,7 +501,7 @@ void launch_gemm_mfma_logits(hipStream_t st, RowCtx rc, const bf16_t* x, const b
 void launch_gemm_mfma_swiglu(hipStream_t st, RowCtx rc, const bf16_t* x, const bf16_t* Wg, const bf16_t* Wu,
                              bf16_t* act, int F, int K, const float* ssq, int ssq_stride, float eps) {
   const int n_tiles = F >> 5, m_tiles = ceil_div(rc.max_rows, 32);
-  NormFuse nf{nullptr, const_cast<float*>(ssq), ssq_stride, K >> 5, 1.0f / (float)K, eps, {}};
+  NormFuse nf{nullptr, const_cast<float*>(ssq), ssq_stride, K >> 5, 1.0f / (float)K, eps};
 #define GEMM_SW(NT, MT, D, OCC, NEAR, grid)                                                                            \
   hipLaunchKernelGGL((gemm_mfma_kernel<NT, MT, EPI_SWIGLU, D, OCC, NEAR, NT == 1>), grid, dim3(64 * KW4), 0, st,       \
                      rc.ctl, reinterpret_cast<const bf16x8*>(x), reinterpret_cast<const bf16x8*>(Wg),                  \
@@ -537,7 +536,7 @@ void launch_gemm_mfma_swiglu(hipStream_t st, RowCtx rc, const bf16_t* x, const b
 void launch_gemm_mfma_resid(hipStream_t st, RowCtx rc, const bf16_t* x, const bf16_t* Wp, float* x_res,
                             const float* gain, bf16_t* act, float* ssq, int ssq_stride, int N, int K) {
   const int n_tiles = N >> 5, m_tiles = ceil_div(rc.max_rows, 32);
-  const NormFuse nf{gain, ssq, ssq_stride, 0, 0.f, 0.f, {}};
+  const NormFuse nf{gain, ssq, ssq_stride, 0, 0.f, 0.f};
 #define GEMM_RESID(NT, MT, D, OCC)                                                                                      \
   hipLaunchKernelGGL((gemm_mfma_kernel<NT, MT, EPI_RESID, D, OCC, true, false>),                                        \
                      dim3(ceil_div(n_tiles / NT, 8) * 8 * ceil_div(m_tiles, MT)), dim3(64 * KW4), 0, st, rc.ctl,        \

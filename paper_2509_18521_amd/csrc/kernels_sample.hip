@@ -19,8 +19,7 @@
 
 namespace april {
 
-constexpr int ROWS_THREADS = 1024;     // workgroup of the whole-row kernel
-constexpr int REC_THREADS = 1024;      // ... and of the one that works from group records (256: 17.8 against 11.3 us for a top 50)
+constexpr int SAMPLE_THREADS = 1024;   // of a workgroup, in both kernels (256 from group records: 17.8 against 11.3 us for a top 50)
 #define MAX_TOPK 64
 #define MAX_HOT 1024
 #define MAX_CAND 2048
@@ -83,14 +82,14 @@ struct SampleShared {
 __device__ inline float block_max_f32(const float* vals, int n, SampleShared& sh) {
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   float m = -INFINITY;
-  for (int i = tid; i < n; i += ROWS_THREADS) m = fmaxf(m, vals[i]);
+  for (int i = tid; i < n; i += SAMPLE_THREADS) m = fmaxf(m, vals[i]);
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
   __syncthreads();
   if (lane == 0) sh.red_f[wid] = m;
   __syncthreads();
   if (tid == 0) {
-    for (int x = 1; x < ROWS_THREADS / 64; ++x) m = fmaxf(m, sh.red_f[x]);
+    for (int x = 1; x < SAMPLE_THREADS / 64; ++x) m = fmaxf(m, sh.red_f[x]);
     sh.max_f = m;
   }
   __syncthreads();
@@ -107,7 +106,7 @@ __device__ inline double block_sum_f64(double v, SampleShared& sh) {
   __syncthreads();
   if (tid == 0) {
     double t = sh.red_d[0];
-    for (int x = 1; x < ROWS_THREADS / 64; ++x) t += sh.red_d[x];
+    for (int x = 1; x < SAMPLE_THREADS / 64; ++x) t += sh.red_d[x];
     sh.total_d = t;
   }
   __syncthreads();
@@ -119,16 +118,15 @@ __device__ inline unsigned long long cand_pair(unsigned key, int idx) { return (
 // Key of the k-th largest of vals[0..n) (k <= n): 4 radix passes of 8 bits.  On return
 // sh.prefix = that key, sh.krem = how many entries equal to it belong to the top k,
 // sh.ntie = how many entries equal it.  All threads must call.  Up to 4 keys per thread are
-// kept in registers across the passes (n <= 4 * NT reads memory once).  NT: threads of the workgroup, here and below.
-template <int NT>
+// kept in registers across the passes (n <= 4 * SAMPLE_THREADS reads memory once).
 __device__ inline void block_kth_largest(const float* vals, int n, int k, SampleShared& sh) {
   const int tid = threadIdx.x;
-  const bool cached = n <= 4 * NT;
+  const bool cached = n <= 4 * SAMPLE_THREADS;
   unsigned ck[4] = {0u, 0u, 0u, 0u};
   if (cached) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const int i = tid + q * NT;
+      const int i = tid + q * SAMPLE_THREADS;
       if (i < n) ck[q] = f2key(vals[i]);
     }
   }
@@ -142,9 +140,9 @@ __device__ inline void block_kth_largest(const float* vals, int n, int k, Sample
     if (cached) {
 #pragma unroll
       for (int q = 0; q < 4; ++q)
-        if (tid + q * NT < n && (ck[q] & mask_hi) == prefix) atomicAdd(&sh.hist[(ck[q] >> shift) & 255u], 1u);
+        if (tid + q * SAMPLE_THREADS < n && (ck[q] & mask_hi) == prefix) atomicAdd(&sh.hist[(ck[q] >> shift) & 255u], 1u);
     } else {
-      for (int i = tid; i < n; i += NT) {
+      for (int i = tid; i < n; i += SAMPLE_THREADS) {
         const unsigned key = f2key(vals[i]);
         if ((key & mask_hi) == prefix) atomicAdd(&sh.hist[(key >> shift) & 255u], 1u);
       }
@@ -187,7 +185,7 @@ __device__ inline int block_argmax(const float* vals, int n, SampleShared& sh) {
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   unsigned bk = 0u;
   int bi = 0x7fffffff;
-  for (int i = tid; i < n; i += ROWS_THREADS) {
+  for (int i = tid; i < n; i += SAMPLE_THREADS) {
     const unsigned k = f2key(vals[i]);
     if (bi == 0x7fffffff || k > bk) { bk = k; bi = i; }     // ascending i: first maximum stays
   }
@@ -201,7 +199,7 @@ __device__ inline int block_argmax(const float* vals, int n, SampleShared& sh) {
   if (lane == 0) { sh.red_key[wid] = bk; sh.red_idx[wid] = bi; }
   __syncthreads();
   if (tid == 0) {
-    for (int x = 1; x < ROWS_THREADS / 64; ++x)
+    for (int x = 1; x < SAMPLE_THREADS / 64; ++x)
       if (sh.red_key[x] > bk || (sh.red_key[x] == bk && sh.red_idx[x] < bi)) { bk = sh.red_key[x]; bi = sh.red_idx[x]; }
     sh.choice = bi;
   }
@@ -248,7 +246,6 @@ __device__ inline double uniform_draw(const SamplerCfg& sc, long long req, int g
 }
 
 // Parity-mode capture (all threads call).
-template <int NT>
 __device__ inline void capture_row(const Watch& w, const Ctrl* ctrl, const RowState& q, const float* lg, int V, int sampled, SampleShared& sh) {
   if (w.req == nullptr || ctrl == nullptr) return;
   const int tid = threadIdx.x;
@@ -262,7 +259,7 @@ __device__ inline void capture_row(const Watch& w, const Ctrl* ctrl, const RowSt
   __syncthreads();
   const int row = sh.watch_row;
   if (row >= 0) {
-    for (int i = tid; i < V; i += NT) w.logits[(size_t)row * V + i] = lg[i];
+    for (int i = tid; i < V; i += SAMPLE_THREADS) w.logits[(size_t)row * V + i] = lg[i];
     if (tid == 0) { w.sampled[row] = sampled; w.filled[row] = 1; }
   }
 }
@@ -286,16 +283,15 @@ __device__ inline void finish_row(const Slots& s, Ctrl* ctrl, const RowState& q,
 }
 
 // Radix select of the row's top k into the candidate list (all threads call).
-template <int NT>
 __device__ inline void topk_whole_row(const float* lg, int V, int k, SampleShared& sh) {
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-  block_kth_largest<NT>(lg, V, k, sh);
+  block_kth_largest(lg, V, k, sh);
   const unsigned thr = sh.prefix;
   const int krem = (int)sh.krem, ntie = (int)sh.ntie;
   if (tid == 0) sh.cnt = 0;
   __syncthreads();
   // everything above the threshold, plus the threshold ties with the lowest indices
-  for (int i = tid; i < V; i += NT) {
+  for (int i = tid; i < V; i += SAMPLE_THREADS) {
     const unsigned key = f2key(lg[i]);
     if (key > thr || (key == thr && ntie == krem)) {
       const int p = atomicAdd(&sh.cnt, 1);
@@ -307,14 +303,14 @@ __device__ inline void topk_whole_row(const float* lg, int V, int k, SampleShare
   int last = -1;
   for (int t = 0; t < krem; ++t) {
     int best = 0x7fffffff;
-    for (int i = tid; i < V; i += NT)
+    for (int i = tid; i < V; i += SAMPLE_THREADS)
       if (i > last && f2key(lg[i]) == thr) { best = i; break; }
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) { const int o = __shfl_xor(best, off, 64); best = o < best ? o : best; }
     if (lane == 0) sh.red_idx[wid] = best;
     __syncthreads();
     if (tid == 0) {
-      for (int x = 1; x < NT / 64; ++x) best = sh.red_idx[x] < best ? sh.red_idx[x] : best;
+      for (int x = 1; x < SAMPLE_THREADS / 64; ++x) best = sh.red_idx[x] < best ? sh.red_idx[x] : best;
       const int p = sh.cnt++;
       if (p < MAX_CAND) sh.cand[p] = cand_pair(thr, best);
       sh.red_idx[0] = best;
@@ -330,7 +326,7 @@ __device__ inline void topk_whole_row(const float* lg, int V, int k, SampleShare
 // threads call; the counts (zero before) are complete behind the next barrier.
 template <class F>
 __device__ inline void count_pairs(SampleShared& sh, int n, F f) {
-  static_assert(ROWS_THREADS == 1024 && REC_THREADS == 1024, "eight groups of 128 threads");
+  static_assert(SAMPLE_THREADS == 1024, "eight groups of 128 threads");
   const int per = (n + 31) / 32 * 4, j0 = (threadIdx.x >> 7) * per, j1 = min(n, j0 + per);
   for (int e0 = 0; e0 < n; e0 += 128) {
     const int e = e0 + (threadIdx.x & 127);
@@ -358,7 +354,7 @@ __device__ inline void draw_topk(int k, const SamplerCfg& sc, long long req, int
   __syncthreads();
   count_pairs(sh, n_cand, [](unsigned long long own, unsigned long long x) { return x > own ? 1u : 0u; });
   __syncthreads();
-  for (int c = tid; c < n_cand; c += ROWS_THREADS) {
+  for (int c = tid; c < n_cand; c += SAMPLE_THREADS) {
     const unsigned long long own = sh.cand[c];
     const int rank = (int)sh.count[c];
     if (rank < k) { sh.sort_logit[rank] = key2f((unsigned)(own >> 32)); sh.sort_idx[rank] = ~(int)(unsigned)own; }
@@ -387,7 +383,7 @@ __device__ inline void draw_topk(int k, const SamplerCfg& sc, long long req, int
 // ---------------------------------------------------------------------------
 // Sampling from the whole row: logits without group records (small and ragged vocabularies, the fp32 path).
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(ROWS_THREADS) void sample_rows_kernel(RowCtx rc, Slots s, Ctrl* ctrl, const float* logits, int V,
+__global__ __launch_bounds__(SAMPLE_THREADS) void sample_rows_kernel(RowCtx rc, Slots s, Ctrl* ctrl, const float* logits, int V,
                                                                      SamplerCfg sc, Watch w, int update,
                                                                      const long long* req_ids, const int* gen_idx,
                                                                      int* out_tokens, float* out_logprobs) {
@@ -407,7 +403,7 @@ __global__ __launch_bounds__(ROWS_THREADS) void sample_rows_kernel(RowCtx rc, Sl
     // crossing of u * total finds the index.
     const float M = block_max_f32(lg, V, sh);
     const double invT = 1.0 / (double)sc.temperature;
-    const int chunk = (V + ROWS_THREADS - 1) / ROWS_THREADS;
+    const int chunk = (V + SAMPLE_THREADS - 1) / SAMPLE_THREADS;
     const int i0 = tid * chunk, i1 = (i0 + chunk < V) ? i0 + chunk : V;
     auto mass = [&](int i) { return exp(((double)lg[i] - (double)M) * invT); };
     double part = 0.0;
@@ -422,7 +418,7 @@ __global__ __launch_bounds__(ROWS_THREADS) void sample_rows_kernel(RowCtx rc, Sl
     if (lane == 63) sh.red_d[wid] = incl;
     __syncthreads();
     double before = 0.0, total = 0.0;
-    for (int x = 0; x < ROWS_THREADS / 64; ++x) {
+    for (int x = 0; x < SAMPLE_THREADS / 64; ++x) {
       if (x < wid) before += sh.red_d[x];
       total += sh.red_d[x];
     }
@@ -442,14 +438,14 @@ __global__ __launch_bounds__(ROWS_THREADS) void sample_rows_kernel(RowCtx rc, Sl
     __syncthreads();
   } else {
     const int k = sc.top_k < V ? (sc.top_k < MAX_TOPK ? sc.top_k : MAX_TOPK) : (V < MAX_TOPK ? V : MAX_TOPK);
-    for (int i = tid; i < MAX_CAND; i += ROWS_THREADS) sh.count[i] = 0u;
-    topk_whole_row<ROWS_THREADS>(lg, V, k, sh);
+    for (int i = tid; i < MAX_CAND; i += SAMPLE_THREADS) sh.count[i] = 0u;
+    topk_whole_row(lg, V, k, sh);
     draw_topk(k, sc, q.req, q.g, sh);
     __syncthreads();
   }
 
   const int sampled = sh.choice;
-  capture_row<ROWS_THREADS>(w, ctrl, q, lg, V, sampled, sh);
+  capture_row(w, ctrl, q, lg, V, sampled, sh);
   // the token that is appended: the sampler's choice, or the teacher-forced one (parity mode)
   const int tok = q.forced >= 0 ? q.forced : sampled;
   // ---- log-probability of that token under softmax(logits / T) over the whole vocabulary ----
@@ -458,7 +454,7 @@ __global__ __launch_bounds__(ROWS_THREADS) void sample_rows_kernel(RowCtx rc, Sl
     const float M = block_max_f32(lg, V, sh);
     const float invT = 1.0f / sc.temperature;
     double part = 0.0;
-    for (int i = tid; i < V; i += ROWS_THREADS) part += (double)__expf((lg[i] - M) * invT);
+    for (int i = tid; i < V; i += SAMPLE_THREADS) part += (double)__expf((lg[i] - M) * invT);
     const double Z = block_sum_f64(part, sh);
     if (tid == 0) *lp_dst = (float)((double)((lg[tok] - M) * invT) - log(Z));
   }
@@ -475,14 +471,14 @@ __global__ __launch_bounds__(ROWS_THREADS) void sample_rows_kernel(RowCtx rc, Sl
 // log-probabilities of 47 rows of 32 k logits 20.1 -> 10.4; 192 rows, categorical with log-probabilities 13.2 -> 8.3.
 // ---------------------------------------------------------------------------
 constexpr int GQ = 4;                      // records of a thread that stay in registers
-template <bool CACHED>                     // n_groups <= GQ * REC_THREADS
-__global__ __launch_bounds__(REC_THREADS) void sample_records_kernel(RowCtx rc, Slots s, Ctrl* ctrl, const float* logits, int V,
+template <bool CACHED>                     // n_groups <= GQ * SAMPLE_THREADS
+__global__ __launch_bounds__(SAMPLE_THREADS) void sample_records_kernel(RowCtx rc, Slots s, Ctrl* ctrl, const float* logits, int V,
                                                                         SamplerCfg sc, Watch w, int update,
                                                                         const long long* req_ids, const int* gen_idx,
                                                                         int* out_tokens, const float* group_max,
                                                                         float* out_logprobs, const int* group_idx,
                                                                         const double* group_sum) {
-  constexpr int W = REC_THREADS / 64;
+  constexpr int W = SAMPLE_THREADS / 64;
   const int r = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   const int n_groups = (V + 63) >> 6;
   const float* lg = logits + (size_t)r * V;
@@ -492,9 +488,9 @@ __global__ __launch_bounds__(REC_THREADS) void sample_records_kernel(RowCtx rc, 
   __shared__ SampleShared sh;
   __shared__ unsigned lane_key[W][64];
   const bool greedy = sc.kind == 0 || (sc.kind == 1 && sc.top_k <= 1), topk = !greedy && sc.kind == 1;
-  // categorical: thread t owns consecutive groups (the CDF runs in index order), else every REC_THREADS-th
-  const int chunk = (n_groups + REC_THREADS - 1) / REC_THREADS;
-  auto group_at = [&](int e) { return sc.kind == 2 ? tid * chunk + e : tid + e * REC_THREADS; };
+  // categorical: thread t owns consecutive groups (the CDF runs in index order), else every SAMPLE_THREADS-th
+  const int chunk = (n_groups + SAMPLE_THREADS - 1) / SAMPLE_THREADS;
+  auto group_at = [&](int e) { return sc.kind == 2 ? tid * chunk + e : tid + e * SAMPLE_THREADS; };
   float m_c[GQ];
   double s_c[GQ];
   if (CACHED) {
@@ -542,7 +538,7 @@ __global__ __launch_bounds__(REC_THREADS) void sample_records_kernel(RowCtx rc, 
   if (lane == 0) { sh.red_f[wid] = mx; sh.red_key[wid] = bk; sh.red_idx[wid] = bi; }
   if (tid == 0) { sh.n_hot = 0; sh.cnt = 0; sh.overflow = 0; sh.choice = V - 1; }
   if (topk)
-    for (int i = tid; i < MAX_CAND; i += REC_THREADS) sh.count[i] = 0u;
+    for (int i = tid; i < MAX_CAND; i += SAMPLE_THREADS) sh.count[i] = 0u;
   __syncthreads();
   static_assert(W == 16, "a wavefront's partial result per lane of a row");
   const float M = row_max_f32(sh.red_f[lane & (W - 1)]);
@@ -567,7 +563,8 @@ __global__ __launch_bounds__(REC_THREADS) void sample_records_kernel(RowCtx rc, 
   } else if (topk) {
     const int k = sc.top_k < V ? (sc.top_k < MAX_TOPK ? sc.top_k : MAX_TOPK) : (V < MAX_TOPK ? V : MAX_TOPK);
     // The 64 lanes' maxima are group maxima of 64 disjoint sets, so at least k groups reach the k-th largest of them:
-    // the groups that do (about twice k) hold the k-th largest group maximum.
+    // the groups that do hold the k-th largest group maximum (of 152 k logits about twice k for 50, four times k for 64, where
+    // the bound is the smallest lane's).
     unsigned lk = lane_key[0][lane];
 #pragma unroll
     for (int x = 1; x < W; ++x) { const unsigned o = lane_key[x][lane]; lk = o > lk ? o : lk; }
@@ -598,7 +595,7 @@ __global__ __launch_bounds__(REC_THREADS) void sample_records_kernel(RowCtx rc, 
         return (kx > ko ? 1u : 0u) + (kx == ko ? 0x10000u : 0u);
       });
       __syncthreads();
-      for (int c = tid; c < n0; c += REC_THREADS) {
+      for (int c = tid; c < n0; c += SAMPLE_THREADS) {
         const unsigned n = sh.count[c];
         const int above = (int)(n & 0xffffu);
         sh.count[c] = 0u;
@@ -633,7 +630,7 @@ __global__ __launch_bounds__(REC_THREADS) void sample_records_kernel(RowCtx rc, 
       __syncthreads();
       have = !sh.overflow && sh.cnt >= k;                     // (a maximum that is a signalling NaN comes back quiet: no logit has its key)
     }
-    if (!have) topk_whole_row<REC_THREADS>(lg, V, k, sh);
+    if (!have) topk_whole_row(lg, V, k, sh);
     draw_topk(k, sc, q.req, q.g, sh);
   } else {
     // ---- temperature sampling over the whole vocabulary: inverse CDF in index order ----------
@@ -689,7 +686,7 @@ __global__ __launch_bounds__(REC_THREADS) void sample_records_kernel(RowCtx rc, 
   }
   __syncthreads();
   const int sampled = sh.choice;
-  capture_row<REC_THREADS>(w, ctrl, q, lg, V, sampled, sh);
+  capture_row(w, ctrl, q, lg, V, sampled, sh);
   if (wid != 0) return;
   // the token that is appended: the sampler's choice, or the teacher-forced one (parity mode)
   const int tok = q.forced >= 0 ? q.forced : sampled;
@@ -708,8 +705,9 @@ __global__ __launch_bounds__(REC_THREADS) void sample_records_kernel(RowCtx rc, 
 // wavefront takes 4 groups per load and GR_STEPS loads in flight, so the pass streams.  (Before, one
 // thread per group walked 64 consecutive floats, and each thread of the row's workgroup 149 of them,
 // twice: a call for 192 rows of 152 k logits took 724 us with the categorical sampler and
-// log-probabilities, 94 us now; 5 rows with top-k 62 us, 42 us now.)  Rows start at any multiple of 4 bytes.  KEYS: maxima in
-// the order of f2key (NaN above everything), as the whole-row searches compare; else fmaxf.
+// log-probabilities and 62 us for 5 rows with top-k, 94 and 42 with this pass; 61 and 29 with the sampler above and without copies.)
+// Rows start at any multiple of 4 bytes.  KEYS: maxima in the order of f2key (a NaN above everything, one with its sign set below),
+// as the whole-row searches compare, a short last group as if filled up with -inf; else fmaxf.
 //
 // The exponentials of the fp64 sums bound that pass (192 rows of 152 k: 23 us without sums, 25 with fp32 ones), so they are
 // cut to what the sums need.  2^y for y <= 0: y = n + f with |f| <= 1/2 by adding and taking away 1.5 * 2^52, the Taylor
@@ -828,12 +826,12 @@ void launch_sample(hipStream_t st, RowCtx rc, Slots s, Ctrl* ctrl, const float* 
   // records serve what the call needs: sums for log-probabilities and the categorical sampler, groups enough for a top k
   const bool records = group_max != nullptr && (group_sum != nullptr || (!lp && sc.kind != 2)) && sampler_takes_records(sc, vocab);
 #define SAMPLE_RECORDS(CACHED)                                                                                         \
-  hipLaunchKernelGGL(sample_records_kernel<CACHED>, dim3(rc.max_rows), dim3(REC_THREADS), 0, st, rc, s, ctrl, logits, vocab, \
+  hipLaunchKernelGGL(sample_records_kernel<CACHED>, dim3(rc.max_rows), dim3(SAMPLE_THREADS), 0, st, rc, s, ctrl, logits, vocab, \
                      sc, w, update, req_ids, gen_idx, out_tokens, group_max, out_logprobs, group_idx, group_sum)
   if (!records)
-    hipLaunchKernelGGL(sample_rows_kernel, dim3(rc.max_rows), dim3(ROWS_THREADS), 0, st, rc, s, ctrl, logits, vocab, sc, w,
+    hipLaunchKernelGGL(sample_rows_kernel, dim3(rc.max_rows), dim3(SAMPLE_THREADS), 0, st, rc, s, ctrl, logits, vocab, sc, w,
                        update, req_ids, gen_idx, out_tokens, out_logprobs);
-  else if (n_groups <= GQ * REC_THREADS) SAMPLE_RECORDS(true);
+  else if (n_groups <= GQ * SAMPLE_THREADS) SAMPLE_RECORDS(true);
   else SAMPLE_RECORDS(false);
 #undef SAMPLE_RECORDS
 }
