@@ -1423,8 +1423,8 @@ int april_sample_rows_logprobs(april_ctx* c, const float* logits, int32_t n_rows
   return sample_rows_impl(c, logits, n_rows, request_ids, gen_index, out_tokens, out_logprobs);
 }
 
-// The same sampler for callers that must not allocate: every temporary lives in this GPU's
-// static scratch array.  No hipMalloc / hipFree here or below.
+// The same sampler for callers that must not allocate: group records in this GPU's static scratch array, row
+// keys and tokens in the context's pinned staging buffer.  No hipMalloc / hipFree here or below.
 int april_sample_rows_noalloc(april_ctx* c, const float* logits, int32_t n_rows, const int64_t* request_ids,
                               const int32_t* gen_index, int32_t* out_tokens) {
   if (!c || !logits || !request_ids || !gen_index || !out_tokens || n_rows <= 0) return APRIL_EINVAL;

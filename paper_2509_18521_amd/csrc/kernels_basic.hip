@@ -600,7 +600,9 @@ template void launch_attn_ref<bf16_t, true>(hipStream_t, RowCtx, Slots, const fl
 // us per launch, that / this: prefill of 16 384 rows, 4 heads of 32 in prompts of 32, 256, 4096 tokens 167, 350, 4045 / 82, 197, 2340,
 // 12 + 3 of 64 777, 1862, 22 900 / 348, 1053, 13 570; decode of 1 and 256 rows of 1024 tokens 56, 67 / 32, 50 and 97, 242 / 53, 149.
 // ---------------------------------------------------------------------------
-template <int DH, class Out>
+// ALONE: few wavefronts on the unit, registers to spare.  Heads of 32 then request a partial step's values together where they are more
+// than 16 loads (200 rows of 32-55 tokens: 60 -> 58 us per iteration of two layers; heads of 64, 64 loads: 62 -> 63).
+template <int DH, bool ALONE, class Out>
 __device__ __forceinline__ void attn_f32_row(const f32x4* sq, const float* kv_pool, const int* bt, const KVLayout& L, int layer, int kvh,
                                              int ctx, Out out) {
   constexpr int TG = DH < 64 ? 64 / DH : 1;        // tokens side by side in the value product
@@ -634,8 +636,8 @@ __device__ __forceinline__ void attn_f32_row(const f32x4* sq, const float* kv_po
     m = m_new;
     float add[DL] = {};
     // 16 loads of values in flight.  whole: 64 tokens, as in every step but a row's last - no bounds, constant offsets in a page
-    auto values = [&](int t0, auto whole) {
-      constexpr int U = 16;
+    auto values = [&](int t0, auto loads, auto whole) {
+      constexpr int U = decltype(loads)::value;
       float v[U][DL], pt[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
@@ -650,12 +652,16 @@ __device__ __forceinline__ void attn_f32_row(const f32x4* sq, const float* kv_po
 #pragma unroll
         for (int e = 0; e < DL; ++e) add[e] = whole || t0 + u * TG + vt < n ? __fmaf_rn(pt[u], v[u][e], add[e]) : add[e];
     };
+    using Few = std::integral_constant<int, 16>;
+    using All = std::integral_constant<int, 64 / TG>;
     if (n == 64) {
 #pragma unroll
-      for (int t0 = 0; t0 < 64; t0 += 16 * TG) values(t0, std::true_type{});
+      for (int t0 = 0; t0 < 64; t0 += 16 * TG) values(t0, Few{}, std::true_type{});
+    } else if (ALONE && TG > 1 && n > 16 * TG) {
+      values(0, All{}, std::false_type{});
     } else {
 #pragma unroll 1
-      for (int t0 = 0; t0 < n; t0 += 16 * TG) values(t0, std::false_type{});
+      for (int t0 = 0; t0 < n; t0 += 16 * TG) values(t0, Few{}, std::false_type{});
     }
 #pragma unroll
     for (int e = 0; e < DL; ++e) {
@@ -680,7 +686,7 @@ __global__ __launch_bounds__(64) void attn_f32_kernel(RowCtx rc, Slots s, const 
   if (lane < DH / 4) sq[lane] = q[lane];
   __syncthreads();
   float* dst = out + (size_t)r * Hq * DH + a * DH;
-  attn_f32_row<DH>(sq, kv_pool, s.block_table + (size_t)slot * s.max_blocks, L, layer, a / (Hq / L.n_kv_heads), ctx,
+  attn_f32_row<DH, false>(sq, kv_pool, s.block_table + (size_t)slot * s.max_blocks, L, layer, a / (Hq / L.n_kv_heads), ctx,
                    [&](int d, float v) { dst[d] = v; });
 }
 void launch_attn_f32(hipStream_t st, RowCtx rc, Slots s, const float* q_rot, const float* kv_pool, KVLayout kvl, int layer,
@@ -994,7 +1000,7 @@ __global__ __launch_bounds__(ROW_THREADS) void forward_f32_kernel(RowCtx rc, Slo
       m.kv_pool[m.kvl.at(layer, 1, page, e / DH, tin, e % DH)] = qkv[nq + Hkv * DH + e];
     __syncthreads();                              // (the workgroup's stores are visible to its own loads behind this)
     for (int a = wid; a < Hq; a += ROW_THREADS / 64)
-      attn_f32_row<DH>(reinterpret_cast<const f32x4*>(qkv + a * DH), m.kv_pool, bt, m.kvl, layer, a / (Hq / Hkv), pos + 1,
+      attn_f32_row<DH, true>(reinterpret_cast<const f32x4*>(qkv + a * DH), m.kv_pool, bt, m.kvl, layer, a / (Hq / Hkv), pos + 1,
                        [&](int i, float v) { att[a * DH + i] = v; });
     __syncthreads();
     row_gemv<4, 2>(L.wo, att, d, nq, [&](int n, float v) { x[n] += v; });
