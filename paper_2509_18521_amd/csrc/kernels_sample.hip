@@ -377,7 +377,8 @@ __device__ inline void draw_topk(int k, const SamplerCfg& sc, long long req, int
     tot = lane_f64(c, __builtin_amdgcn_readfirstlane(keep - 1));      // mass of the nucleus: renormalise by it
   }
   const unsigned long long hit = __ballot(tid < keep && c > uniform_draw(sc, req, g) * tot);
-  if (tid == 0) sh.choice = sh.sort_idx[hit ? __ffsll((long long)hit) - 1 : keep - 1];
+  // (no candidate: the maxima were signalling NaN, which come back quiet, and no logit has their key; the choice stays the last token)
+  if (tid == 0 && n > 0) sh.choice = sh.sort_idx[hit ? __ffsll((long long)hit) - 1 : keep - 1];
 }
 
 // ---------------------------------------------------------------------------
@@ -523,8 +524,8 @@ __global__ __launch_bounds__(SAMPLE_THREADS) void sample_records_kernel(RowCtx r
   int bi = 0x7fffffff;
   each([&](int, int i, float m, double) {
     mx = fmaxf(mx, m);
-    const unsigned k = f2key(m);
-    const bool first = i < n_groups && (bi == 0x7fffffff || k > bk);      // ascending i: the first maximum stays
+    const unsigned k = i < n_groups ? f2key(m) : 0u;          // (0 where a row's largest key is 0: the lowest index is a real one's)
+    const bool first = bi == 0x7fffffff || k > bk;            // ascending i: the first maximum stays
     bk = first ? k : bk;
     bi = first ? i : bi;
   });
@@ -628,7 +629,7 @@ __global__ __launch_bounds__(SAMPLE_THREADS) void sample_records_kernel(RowCtx r
         }
       }
       __syncthreads();
-      have = !sh.overflow && sh.cnt >= k;                     // (a maximum that is a signalling NaN comes back quiet: no logit has its key)
+      have = !sh.overflow;
     }
     if (!have) topk_whole_row(lg, V, k, sh);
     draw_topk(k, sc, q.req, q.g, sh);

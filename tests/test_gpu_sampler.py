@@ -212,25 +212,27 @@ def test_records_of_every_register_count(sampler, n_groups, top_k):
 @pytest.mark.parametrize("sampler", [ai.SAMPLER_GREEDY, ai.SAMPLER_TOPK, ai.SAMPLER_CATEGORICAL])
 def test_rows_of_nan_give_tokens_of_the_vocabulary(sampler, n_groups, ragged, top_k):
     """NaN of either sign in the whole row, and in all of it but a few logits (fewer than k groups): a NaN with the sign set
-    comes below -inf in the order of the searches, any other above +inf.  A distribution without a sum gives its last token."""
+    comes below -inf in the order of the searches, any other above +inf.  A distribution without a sum gives its last token.
+    A row of signalling NaN: any token."""
     import torch
     vocab, T = 64 * n_groups - ragged, float(np.float32(0.7))
     k = min(top_k, vocab)
     neg, pos = np.uint32(0xffc00000).view(np.float32), np.uint32(0x7fc00000).view(np.float32)
-    logits = np.full((5, vocab), neg, dtype=np.float32)
+    logits = np.full((6, vocab), neg, dtype=np.float32)
     logits[1] = pos
     few = np.unique(np.array([vocab // 3, vocab // 2, vocab - 1]))
     logits[2, few] = np.arange(len(few), dtype=np.float32) - 1.5
     logits[3, few] = -np.inf
     logits[4] = np.random.default_rng(n_groups).standard_normal(vocab).astype(np.float32)
     logits[4, :vocab // 2] = neg
-    ids, idx = np.arange(5, dtype=np.int64) + 3, np.arange(5, dtype=np.int32)
+    logits.view(np.uint32)[5] = 0x7f800001
+    ids, idx = np.arange(6, dtype=np.int64) + 3, np.arange(6, dtype=np.int32)
     ap, ctx = engine(vocab, sampler, top_k, T, 9)
     try:
         dev = torch.from_numpy(logits).cuda()
-        tok, _ = ap.april_sample_rows_logprobs(ctx, dev.data_ptr(), 5, ids, idx)
-        plain = ap.april_sample_rows(ctx, dev.data_ptr(), 5, ids, idx)
-        alone = ap.april_sample_rows_noalloc(ctx, dev.data_ptr(), 5, ids, idx)
+        tok, _ = ap.april_sample_rows_logprobs(ctx, dev.data_ptr(), 6, ids, idx)
+        plain = ap.april_sample_rows(ctx, dev.data_ptr(), 6, ids, idx)
+        alone = ap.april_sample_rows_noalloc(ctx, dev.data_ptr(), 6, ids, idx)
     finally:
         ap.april_destroy(ctx)
     assert np.array_equal(tok, plain) and np.array_equal(tok, alone)
