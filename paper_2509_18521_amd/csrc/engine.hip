@@ -62,7 +62,8 @@ constexpr int XFER_MOST_INTS = 1 << 18;
 struct PrefillBlock {
   int rows, nseq, n_items;
   int items() const { return 4; }                                   // after {rows, stop = 0, nseq, stop = 0}
-  int srow_slot() const { return items() + 4 * n_items; }
+  int last_items() const { return items() + 4 * n_items; }          // attention of the sequences' last rows alone
+  int srow_slot() const { return last_items() + 4 * nseq; }
   int srow_pos() const { return srow_slot() + nseq; }
   int gather() const { return srow_pos() + nseq; }
   int row_slot() const { return gather() + nseq; }
@@ -141,7 +142,7 @@ struct april_ctx {
   // prefill staging (device) + pinned host staging: one block per chunk, see PrefillBlock
   int prefill_cap = 0;
   int* d_pf = nullptr;
-  const int4* pf_items = nullptr;   // query tiles of the chunk's sequences (prefill attention), inside d_pf
+  const int4 *pf_items = nullptr, *pf_last_items = nullptr;   // query tiles of the chunk's sequences (prefill attention), inside d_pf
   int pf_n_items = 0, pf_items_cap = 0;
   bool prefill_tiled = true;     // query-tiled prefill attention (APRIL_PREFILL_ATTN=rows: one workgroup per row)
   int *d_list_a = nullptr, *d_list_b = nullptr;
@@ -540,6 +541,19 @@ SamplerCfg sampler_cfg(const april_ctx* c) {
 // prefill: the last token of each sequence, `gather` maps them into `rows`).
 // B / C: host estimates of live rows and summed context, used only for the
 // algorithmic-byte bookkeeping of profiled launches.
+// Prefill: behind the last layer's keys and values nothing reads a row but the sequences' last ones, which are sampled from.  Those
+// alone go on, packed: one layer of the model then costs a pass its norm and its key / value projection.  (The same kernels and
+// chains, so the same bits.)  Steps through few layers, all rows in the last layer / as here: two of 4096 x 14336, 7 prompts
+// of 4500-8000 tokens, 96 tokens each 90.3 / 73.6 ms; three of 2560 x 9728, 21 prompts of 1-1999 tokens 16.5 / 12.9 ms; in a model
+// of 24 or 36 layers it is that share of the prefill.  It takes two more launches (the sampling rows' norm and queries): one
+// prompt of 40, 250, 400, 600 tokens of 896 x 4864 332, 356, 379, 426 / 346, 366, 378, 405 us, of 40, 130, 160, 250 of 2560 x 9728 566, 623, 628,
+// 720 / 597, 633, 618, 679, of 40, 100, 160, 250 of 4096 x 14336 712, 725, 878, 898 / 731, 745, 828, 840.  Routed experts read fewer
+// experts for fewer rows: 10, 20, 40, 250 tokens 660, 790, 845, 937 / 611, 673, 711, 771, 40 prompts of 3 tokens 1114 / 1108.
+static bool last_layer_cut_pays(int rows, int sampling, int d_model, bool moe) {
+  const int spared = rows - sampling;
+  return moe ? spared >= 8 && rows >= 3 * sampling : spared >= (d_model >= 2048 ? 160 : 384);
+}
+
 void forward(april_ctx* c, RowCtx rows, RowCtx srows, const int* gather, double B, double C) {
   const ModelDims& m = c->dm;
   hipStream_t st = c->stream;
@@ -563,13 +577,14 @@ void forward(april_ctx* c, RowCtx rows, RowCtx srows, const int* gather, double 
   }
   // mlp_in = true: the partials are the previous layer's MLP output (for routed experts: the
   // top-k expert outputs of each row, gathered and weighted)
+  float* x_res = c->x_res;           // residual stream of the rows in work
   auto norm = [&](RowCtx rc, int n_part, const float* gain, void* out, const int* gth, double rowsB, bool mlp_in,
-                  bf16_t* out_rows = nullptr) {
+                  bf16_t* out_rows = nullptr, float* x_copy = nullptr) {
     ProfScope p(c, KC_NORM, rowsB * d * (4.0 * (2 + (n_part > 0 ? 1 : 0)) + e), 0);
     if (c->moe && mlp_in && n_part > 0)
-      launch_add_rmsnorm<bf16_t, true>(st, rc, c->x_res, c->moe_out, c->top_k_experts, 0, gain, (bf16_t*)out, d, m.rms_eps, gth, c->moe_pos, c->moe_wts);
-    else if (c->bf16) launch_add_rmsnorm<bf16_t, true>(st, rc, c->x_res, c->proj, n_part, c->proj_stride, gain, (bf16_t*)out, d, m.rms_eps, gth, nullptr, nullptr, out_rows);
-    else launch_add_rmsnorm<float, false>(st, rc, c->x_res, c->proj, n_part, c->proj_stride, gain, (float*)out, d, m.rms_eps, gth);
+      launch_add_rmsnorm<bf16_t, true>(st, rc, x_res, c->moe_out, c->top_k_experts, 0, gain, (bf16_t*)out, d, m.rms_eps, gth, c->moe_pos, c->moe_wts);
+    else if (c->bf16) launch_add_rmsnorm<bf16_t, true>(st, rc, x_res, c->proj, n_part, c->proj_stride, gain, (bf16_t*)out, d, m.rms_eps, gth, nullptr, nullptr, out_rows, x_copy);
+    else launch_add_rmsnorm<float, false>(st, rc, x_res, c->proj, n_part, c->proj_stride, gain, (float*)out, d, m.rms_eps, gth);
   };
   // Prefill rows (hundreds to thousands) go through the LDS-tiled GEMM, which needs no k-split
   // across workgroups: its consumers then read a single partial.  The choice follows the kind
@@ -579,7 +594,7 @@ void forward(april_ctx* c, RowCtx rows, RowCtx srows, const int* gather, double 
   const int sq = tile ? 1 : c->s_qkv, so = tile ? 0 : c->s_o, sd = tile && !c->moe ? 0 : c->s_down, sr = tile ? 1 : c->s_router;
   auto gemm_resid_tile = [&](int kc, const void* x, const bf16_t* w_s, int N, int K) {
     ProfScope p(c, kc, (double)N * K * e + B * K * e + B * N * 8.0, 2.0 * B * N * K);
-    launch_gemm_tile_resid(st, rows, (const bf16_t*)x, w_s, c->x_res, N, K);
+    launch_gemm_tile_resid(st, rows, (const bf16_t*)x, w_s, x_res, N, K);
   };
   auto gemm = [&](int kc, RowCtx rc, const void* x, const void* w_plain, const bf16_t* w_s, float* out, int N, int K,
                   int ks, size_t stride, double rowsB, const float* ssq = nullptr) {
@@ -590,6 +605,7 @@ void forward(april_ctx* c, RowCtx rows, RowCtx srows, const int* gather, double 
     else if (c->f32_dot) launch_gemm_f32_dot(st, rc, (const float*)x, (const float*)w_plain, out, N, K);
     else launch_gemm_f32(st, rc, (const float*)x, (const float*)w_plain, out, N, K);
   };
+  const int* gather_final = gather;
   bool normed_by_down = false;       // the previous layer's down projection already did this layer's first norm
   for (int l = 0; l < m.n_layers; ++l) {
     const LayerW& L = c->layers[l];
@@ -598,7 +614,22 @@ void forward(april_ctx* c, RowCtx rows, RowCtx srows, const int* gather, double 
     bf16_t* q16 = reinterpret_cast<bf16_t*>(c->q_rot);
     const bool pf_attn = c->attn_mfma && gather != nullptr && c->prefill_tiled;
     bool roped = false;
-    if (tile && pf_attn) {
+    if (tile && pf_attn && l + 1 == m.n_layers && last_layer_cut_pays(rows.max_rows, srows.max_rows, d, c->moe)) {
+      // Behind the last layer's keys and values only the sampling rows go on: their queries, then everything, on rows
+      // packed together.  (proj, which no prefill product writes, takes their residual stream; hf their normed rows until the final norm.)
+      bf16_t* hl = (bf16_t*)c->hf;
+      norm(srows, 0, L.attn_norm, hl, gather, srows.max_rows, false, nullptr, c->proj);
+      QkvOut qo{c->ds.block_table, c->max_blocks, c->rope_cos, c->rope_sin, q16, (bf16_t*)c->kv_pool, c->kvl, l, 0};
+      ProfScope p(c, KC_GEMM_QKV, (double)nqkv * d * e + B * d * e + 2 * B * nkv * e, 4.0 * B * nkv * d + 2.0 * srows.max_rows * nq * d);
+      launch_gemm_tile_qkv(st, rows, (const bf16_t*)c->h_act, L.wqkv_s + (size_t)nq * d, 2 * nkv, d, qo);
+      qo.n_q_heads = Hq;
+      launch_gemm_tile_qkv(st, srows, hl, L.wqkv_s, nq, d, qo);
+      roped = true;
+      x_res = c->proj;
+      rows = srows;
+      B = srows.max_rows;
+      gather_final = nullptr;
+    } else if (tile && pf_attn) {
       ProfScope p(c, KC_GEMM_QKV, (double)nqkv * d * e + B * d * e + B * nqkv * e, 2.0 * B * nqkv * d);
       roped = launch_gemm_tile_qkv(st, rows, (const bf16_t*)c->h_act, L.wqkv_s, nqkv, d,
                                    QkvOut{c->ds.block_table, c->max_blocks, c->rope_cos, c->rope_sin, q16, (bf16_t*)c->kv_pool, c->kvl, l, Hq});
@@ -617,8 +648,9 @@ void forward(april_ctx* c, RowCtx rows, RowCtx srows, const int* gather, double 
       // prefill: one workgroup per tile of query positions, the keys / values of a prompt are
       // streamed once per tile instead of once per row
       ProfScope p(c, KC_ATTN, C * 2.0 * nkv * e + B * nq * (4.0 + e), 4.0 * C * nq);
-      launch_attn_prefill(st, c->pf_items, c->pf_n_items, c->ds, q16, (const bf16_t*)c->kv_pool, c->kvl, l, Hq,
-                          (bf16_t*)c->attn_out);
+      const bool cut = rows.row_slot == srows.row_slot;
+      launch_attn_prefill(st, cut ? c->pf_last_items : c->pf_items, cut ? srows.max_rows : c->pf_n_items, c->ds, q16,
+                          (const bf16_t*)c->kv_pool, c->kvl, l, Hq, (bf16_t*)c->attn_out);
     } else if (c->attn_mfma) {
       const int gs = std::min(c->attn_max_splits, std::max(1, ceil_div(c->step_max_ctx, c->attn_chunk)));
       for (int base = 0; base < rows.max_rows; base += c->attn_ws_rows) {
@@ -709,7 +741,7 @@ void forward(april_ctx* c, RowCtx rows, RowCtx srows, const int* gather, double 
     }
   }
   const double SB = gather ? (double)srows.max_rows : B;
-  norm(srows, sd, c->final_norm, c->hf, gather, SB, true);
+  norm(srows, sd, c->final_norm, c->hf, gather_final, SB, true);
   float* lg_out = c->write_logits ? c->logits : nullptr;
   {
     ProfScope p(c, KC_GEMM_LMHEAD, (double)V * d * e + SB * d * e, 2.0 * SB * V * d);
@@ -1830,11 +1862,20 @@ int april_rollout_step(april_ctx* c, const april_request* new_reqs, int32_t n_ne
         hs[pb.srow_slot() + q] = s; hs[pb.srow_pos() + q] = nt - 1; hs[pb.gather() + q] = row + nt - 1;
         row += nt;
       }
+      // (the last layer's rows are packed: row q of it is sequence q's last, at position nt - 1)
+      int4* h_last = reinterpret_cast<int4*>(hs + pb.last_items());
+      for (int q = 0; q < nseq; ++q) {
+        const int nt = hs[pb.srow_pos() + q] + 1;
+        h_last[q] = int4{hs[pb.srow_slot() + q], q - (nt - 1), nt, nt - 1};
+      }
       // longest walks over the keys first, so that the launch drains on short ones
-      std::stable_sort(h_items, h_items + pb.n_items, [](const int4& a, const int4& b) { return a.w > b.w; });
+      auto longer = [](const int4& a, const int4& b) { return a.w > b.w; };
+      std::stable_sort(h_items, h_items + pb.n_items, longer);
+      std::stable_sort(h_last, h_last + nseq, longer);
       c->step_max_ctx = chunk_max_ctx;
       HIPCHK(c, hipMemcpyAsync(c->d_pf, hs, (size_t)pb.size() * sizeof(int), hipMemcpyHostToDevice, st));
       c->pf_items = reinterpret_cast<const int4*>(c->d_pf + pb.items());
+      c->pf_last_items = reinterpret_cast<const int4*>(c->d_pf + pb.last_items());
       c->pf_n_items = pb.n_items;
       RowCtx prc{c->d_pf + pb.row_slot(), c->d_pf + pb.row_pos(), reinterpret_cast<const int2*>(c->d_pf), rows};
       RowCtx src{c->d_pf + pb.srow_slot(), c->d_pf + pb.srow_pos(), reinterpret_cast<const int2*>(c->d_pf + 2), nseq};

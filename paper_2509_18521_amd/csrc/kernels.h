@@ -194,7 +194,7 @@ template <typename T, bool XF>
 void launch_add_rmsnorm(hipStream_t st, RowCtx rc, float* x_res, const float* partials,
                         int n_partials, size_t partial_stride, const float* gain, T* h,
                         int d, float eps, const int* gather, const int* pos_of = nullptr,
-                        const float* wts = nullptr, T* h_rows = nullptr);
+                        const float* wts = nullptr, T* h_rows = nullptr, float* x_copy = nullptr);
 
 // --- routed experts (bf16) ---------------------------------------------------------
 void launch_moe_route(hipStream_t st, RowCtx rc, const float* logits, int n_partials, size_t partial_stride,

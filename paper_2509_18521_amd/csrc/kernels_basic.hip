@@ -320,7 +320,7 @@ __global__ __launch_bounds__(256) void add_rmsnorm_kernel(RowCtx rc, float* x_re
                                                           int n_partials_rt, size_t partial_stride,
                                                           const float* gain, T* h, int d, float eps,
                                                           const int* gather, const int* pos_of,
-                                                          const float* wts, T* h_rows) {
+                                                          const float* wts, T* h_rows, float* x_copy) {
   const int r = norm_row(rc);
   ROW_GUARD(rc, r);
   const int rin = gather ? gather[r] : r;
@@ -362,6 +362,11 @@ __global__ __launch_bounds__(256) void add_rmsnorm_kernel(RowCtx rc, float* x_re
 #pragma unroll
         for (int j = 0; j < 8; ++j) xp[j] = v[c][j];
       }
+      if (x_copy != nullptr) {           // the residual rows packed (gathered ones go on by themselves)
+        float* cp = x_copy + (size_t)r * d + ch * 8;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) cp[j] = v[c][j];
+      }
 #pragma unroll
       for (int j = 0; j < 8; ++j) ss = __fmaf_rn(v[c][j], v[c][j], ss);
     }
@@ -392,10 +397,10 @@ __global__ __launch_bounds__(256) void add_rmsnorm_kernel(RowCtx rc, float* x_re
 template <typename T, bool XF>
 void launch_add_rmsnorm(hipStream_t st, RowCtx rc, float* x_res, const float* partials, int n_partials,
                         size_t partial_stride, const float* gain, T* h, int d, float eps, const int* gather,
-                        const int* pos_of, const float* wts, T* h_rows) {
+                        const int* pos_of, const float* wts, T* h_rows, float* x_copy) {
 #define ARN_CASE(NP)                                                                                          \
   hipLaunchKernelGGL((add_rmsnorm_kernel<T, XF, NP>), dim3(norm_grid(rc)), dim3(256), 0, st, rc, x_res, partials, \
-                     n_partials, partial_stride, gain, h, d, eps, gather, pos_of, wts, h_rows)
+                     n_partials, partial_stride, gain, h, d, eps, gather, pos_of, wts, h_rows, x_copy)
   switch (n_partials) {
     case 0: ARN_CASE(0); break;
     case 1: ARN_CASE(1); break;
@@ -410,8 +415,8 @@ void launch_add_rmsnorm(hipStream_t st, RowCtx rc, float* x_res, const float* pa
   }
 #undef ARN_CASE
 }
-template void launch_add_rmsnorm<float, false>(hipStream_t, RowCtx, float*, const float*, int, size_t, const float*, float*, int, float, const int*, const int*, const float*, float*);
-template void launch_add_rmsnorm<bf16_t, true>(hipStream_t, RowCtx, float*, const float*, int, size_t, const float*, bf16_t*, int, float, const int*, const int*, const float*, bf16_t*);
+template void launch_add_rmsnorm<float, false>(hipStream_t, RowCtx, float*, const float*, int, size_t, const float*, float*, int, float, const int*, const int*, const float*, float*, float*);
+template void launch_add_rmsnorm<bf16_t, true>(hipStream_t, RowCtx, float*, const float*, int, size_t, const float*, bf16_t*, int, float, const int*, const int*, const float*, bf16_t*, float*);
 
 // ---------------------------------------------------------------------------
 // Embedding gather + the first layer's RMSNorm: x_res[r] = E[token at (slot, pos)], h = rmsnorm(x_res) * gain.
