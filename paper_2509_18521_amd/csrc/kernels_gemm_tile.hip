@@ -456,26 +456,40 @@ __device__ __forceinline__ void tile_dma_body(RowCtx rc, const bf16x8* __restric
 // products of this one run, across the stage boundary too, and the copies of the stage R - 1 ahead are
 // spread over the second k-tile's products.  One barrier per stage, in its middle: it makes stage s + 1
 // readable (every wavefront has waited for its own copies of it) and the slot of stage s - 1 free.
-// Measured at 16384 rows, 8 wavefronts of 128 x 64 against this: 2 x 14336 x 4096 with SiLU 1213 -> 1328
-// TFLOP/s, 4096 x 14336 1192 -> 1329, 6144 x 4096 1126 -> 1246, 6144 x 2560 896 -> 980 (there 400 MB of
-// fp32 output are 15 % of the time); a library product of 16384^3 reaches 1555.  With the reads or copies
-// inside branches, or a burst of copies after the barrier, it was 5 % slower than the 8 wavefronts.
+// With the reads or copies inside branches, or a burst of copies after the barrier, it was 5 % slower than 8 wavefronts.
 // Same accumulator chain per element as every kernel here (k-tiles in order).  K % 32 == 0.
-template <int EPI, int DH = 0>
-__global__ __launch_bounds__(256, 1) void gemm_big_kernel(RowCtx rc, const bf16x8* __restrict__ x,
-                                                          const bf16x8* __restrict__ w0, const bf16x8* __restrict__ w1,
-                                                          float* __restrict__ out, bf16_t* __restrict__ act, int N, int K,
-                                                          GroupOut go, QkvOut qo) {
-  constexpr int MT = 8, NT = 8, MTW = 4, NTW = 4, BK = 2, R = 4, FR = MT + NT, PER = FR * BK / 4;
-  __shared__ bf16x8 lds[R][BK][FR][64];
-  const int rows = rows_or_zero(rc);
-  const int2 at = tile_of_block<EPI == TEPI_LOGITS>(rc, MT);
-  const int bx = at.x, m0 = at.y * MT;
-  if (m0 * 32 >= rows || (EPI == TEPI_LOGITS && bx * NT * 32 >= N)) return;
+// What bounds it: power.  2 x 14336 x 4096 with SiLU at 12800 rows: the matrix cores are busy 72 % of the cycles, at 1.65-1.8 GHz of
+// 2.4 (1.33 PFLOP/s; a library product of 16384^3 reaches 1.56).  The rest is in the rounds: a tile of K = 2560 takes 60 us on its
+// compute unit, the ring's filling and a SwiGLU epilogue 6 more, and a launch lasts as long as the unit with the most tiles.
+// Hence the tiles' order and the halves below.  us at 16384 rows, a grid of 256 x 256 tiles in grid order / this: gate/up of 9728 x 2560
+// 1295 / 1250, of 4864 x 896 (14500 rows) 246 / 233; output projections 2560 x 4096 437 / 363, x 9728 776 / 698 (2.5 rounds of tiles),
+// 4096 x 14336 (12800 rows) 1375 / 1250, 896 x 4864 (14500) 140 / 122.
+constexpr int BIG_R = 4, BIG_BK = 2;
+// The workgroups of a launch: `full` tiles of 256 x 256, then tiles of 256 x 128: the two halves of the last `split` tiles, and the
+// `my` pieces of a last column of 128 where the columns are an odd number of those.
+struct BigGrid {
+  int nx, my;                  // tiles of 256 columns, of 256 rows
+  int full, split, odd;
+  __host__ __device__ int halves() const { return ((split + 7) & ~7) * 2 + (odd ? my : 0); }
+};
+// The order of the tiles: groups of 6 row tiles, inside a group column after column; where the columns are a multiple of 8, row after row.
+__device__ __forceinline__ int2 big_tile(const BigGrid& g, int t) {
+  const int high = (g.nx & 7) ? 6 : 1, grp = t / (high * g.nx), in = t - grp * high * g.nx, h = min(high, g.my - grp * high), col = in / h;
+  return make_int2(col, grp * high + in - col * h);
+}
+
+// One tile of 256 rows x NTW * 64 columns.  u0: its first column in units of 128 (SwiGLU: of 64 features).
+template <int EPI, int DH, int NTW>
+__device__ __forceinline__ void big_body(const RowCtx& rc, const bf16x8* __restrict__ x, const bf16x8* __restrict__ w0,
+                                         const bf16x8* __restrict__ w1, float* __restrict__ out, bf16_t* __restrict__ act,
+                                         int N, int K, const GroupOut& go, const QkvOut& qo, bf16x8* lds_raw, int rows, int u0, int m0) {
+  constexpr int MT = 8, NT = 2 * NTW, MTW = 4, BK = BIG_BK, R = BIG_R, FR = MT + NT, PER = FR * BK / 4, READS = NTW + MTW;
+  auto lds = reinterpret_cast<bf16x8 (*)[BK][FR][64]>(lds_raw);
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave >> 1, wn = wave & 1;
   const int KT = K >> 4, n_stages = KT / BK;
   const int m_last = (rows - 1) >> 5, n_tiles = N >> 5;
+  const int nt0 = u0 * (EPI == TEPI_SWIGLU ? 2 : 4);    // first weight (feature) tile of the workgroup
   // Fragment slot t of a k-tile: activation tile m0 + t, then weight slots; weight slot i belongs to
   // wavefront column i / NTW (SwiGLU: its first half gate tiles, its second half the up tiles of the
   // same features).  Tiles past the end are clamped for the loads and never stored.
@@ -485,9 +499,11 @@ __global__ __launch_bounds__(256, 1) void gemm_big_kernel(RowCtx rc, const bf16x
     if (EPI == TEPI_SWIGLU) {
       constexpr int H = NTW / 2;
       const int col = i / NTW, ii = i % NTW;
-      return (ii < H ? w0 : w1) + (size_t)min(bx * (NT / 2) + col * H + (ii < H ? ii : ii - H), n_tiles - 1) * KT * 64;
+      return (ii < H ? w0 : w1) + (size_t)min(nt0 + col * H + (ii < H ? ii : ii - H), n_tiles - 1) * KT * 64;
     }
-    return w0 + (size_t)min(bx * NT + i, n_tiles - 1) * KT * 64;
+    int nt = nt0 + i;
+    if constexpr (EPI == TEPI_QKV) nt = qkv_tile<NTW, DH>(nt0 / NTW + i / NTW, i % NTW);
+    return w0 + (size_t)min(nt, n_tiles - 1) * KT * 64;
   };
   const int skk = wave & 1, st0 = wave >> 1;             // this wavefront copies k-tile skk of slots st0, st0 + 2, ...
   const bf16x8* src[PER];                               // wavefront-uniform: scalar registers
@@ -528,46 +544,132 @@ __global__ __launch_bounds__(256, 1) void gemm_big_kernel(RowCtx rc, const bf16x
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
   read(0, 0);
-  // One stage.  STEADY: stage s + R - 1 exists.  (Reading k-tile 0 of stage s + 1 past the end fetches a
-  // slot's old contents, which nothing uses: the code stays free of branches between the products.)
-  auto stage = [&](int s, auto steady) {
-    constexpr bool STEADY = decltype(steady)::value;
+  // One stage.  COPY: stage s + R - 1 exists.  (Reading k-tile 0 of stage s + 1 past the end fetches a slot's old contents, which nothing uses: the code
+  // stays free of branches between the products.)
+  auto stage = [&](int s, auto copying) {
+    constexpr bool COPY = decltype(copying)::value;
     read(s, 1);
     products(0);
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {                        // LDS reads between the first products: back before the last ones end
+    for (int q = 0; q < READS; ++q) {                    // LDS reads between the first products: back before the last ones end
       __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
       __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
     }
-    __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);
+    __builtin_amdgcn_sched_group_barrier(0x008, NTW * MTW - READS, 0);
     // stage s + 1 has landed when at most the copies of the stages s + 2 .. s + R - 2 are outstanding
-    wait_vector_memory<STEADY ? (R - 3) * PER : 0>();
+    wait_vector_memory<COPY ? (R - 3) * PER : 0>();
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-    if (STEADY) {
+    if (COPY) {
 #pragma unroll
       for (int u = 0; u < PER; ++u) copy(s + R - 1, u);
     }
     read(s + 1, 0);
     products(1);
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
+    for (int q = 0; q < READS; ++q) {
       __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
       __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-      if (STEADY) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+      if (COPY && q < PER) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
     }
-    __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);
+    __builtin_amdgcn_sched_group_barrier(0x008, NTW * MTW - READS, 0);
     asm volatile("" ::: "memory");
   };
   int s = 0;
   for (; s + R - 1 < n_stages; ++s) stage(s, std::true_type{});
   for (; s < n_stages; ++s) stage(s, std::false_type{});
   if constexpr (EPI == TEPI_QKV) {
-    qkv_epilogue<NTW, MTW, DH>(acc, bx * 2 + wn, m0 + wm * MTW, rows, n_tiles, lane, rc, qo);
+    qkv_epilogue<NTW, MTW, DH>(acc, nt0 / NTW + wn, m0 + wm * MTW, rows, n_tiles, lane, rc, qo);
+  } else if constexpr (EPI == TEPI_RESID) {
+    // out += result, a wavefront's 32 rows at a time: through LDS (its own part of the ring, which everyone has finished
+    // reading) into whole rows, so that an instruction reads and writes 512 (256) consecutive bytes of a row.  From the
+    // accumulators' own layout, 32 pieces of 32 bytes an instruction, this took 50 us of a round (512 KB a workgroup): 2560 x 4096
+    // at 16384 rows 397 -> 363 us, 896 x 896 at 14500 44 -> 38.  (Residual values requested during the last stages, into registers
+    // the products leave free, cost the k loop more than they gave: spills, or another schedule.)
+    constexpr int LPR = NTW * 8, RPI = 64 / LPR, PIECES = 32 / RPI, STRIDE = NTW * 32 + 4;
+    static_assert(4 * 32 * STRIDE * 4 <= (int)sizeof(bf16x8) * R * BK * FR * 64, "LDS");
+    __syncthreads();
+    float* buf = reinterpret_cast<float*>(lds_raw) + wave * 32 * STRIDE;
+    const int wnt0 = nt0 + wn * NTW, row0 = lane / LPR, c4 = (lane % LPR) * 4, mw = (m0 + wm * MTW) * 32 + row0;
+    if (wnt0 >= n_tiles) return;
+    const bool col_ok = wnt0 + (c4 >> 5) < n_tiles;
+    float* const col = out + (size_t)wnt0 * 32 + (col_ok ? c4 : 0);
+    f32x4 v[2][PIECES];
+    auto load = [&](int j) {
+#pragma unroll
+      for (int p = 0; p < PIECES; ++p) v[j & 1][p] = *reinterpret_cast<const f32x4*>(col + (size_t)min(mw + j * 32 + p * RPI, rows - 1) * N);
+    };
+    load(0);
+    load(1);
+#pragma unroll
+    for (int j = 0; j < MTW; ++j) {
+#pragma unroll
+      for (int i = 0; i < NTW; ++i)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          *reinterpret_cast<f32x4*>(buf + (lane & 31) * STRIDE + i * 32 + 8 * q + ((lane >> 5) << 2)) =
+              f32x4{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+#pragma unroll
+      for (int p = 0; p < PIECES; ++p) {
+        const int m = mw + j * 32 + p * RPI;
+        const f32x4 r = v[j & 1][p] + *reinterpret_cast<const f32x4*>(buf + (row0 + p * RPI) * STRIDE + c4);
+        if (m < rows && col_ok) *reinterpret_cast<f32x4*>(col + (size_t)m * N) = r;
+      }
+      if (j + 2 < MTW) load(j + 2);
+    }
+  } else {
+    tile_epilogue<MTW, NTW, EPI>(acc, nt0 + wn * (EPI == TEPI_SWIGLU ? NTW / 2 : NTW), m0 + wm * MTW, rows, n_tiles, N, lane, out, act,
+                                 nullptr, m0 * 32, &go);
+  }
+}
+
+template <int EPI, int DH = 0>
+__global__ __launch_bounds__(256, 1) void gemm_big_kernel(RowCtx rc, const bf16x8* __restrict__ x,
+                                                          const bf16x8* __restrict__ w0, const bf16x8* __restrict__ w1,
+                                                          float* __restrict__ out, bf16_t* __restrict__ act, int N, int K,
+                                                          GroupOut go, QkvOut qo, BigGrid g) {
+  __shared__ bf16x8 lds[BIG_R * BIG_BK * 16 * 64];
+  const int rows = rows_or_zero(rc);
+  if constexpr (EPI == TEPI_LOGITS) {
+    const int2 at = tile_of_block<true>(rc, 8);
+    if (at.y * 256 >= rows || at.x * 256 >= N) return;
+    big_body<EPI, DH, 4>(rc, x, w0, w1, out, act, N, K, go, qo, lds, rows, at.x * 2, at.y * 8);
     return;
   }
-  tile_epilogue<MTW, NTW, EPI>(acc, bx * (EPI == TEPI_SWIGLU ? NT / 2 : NT) + wn * (EPI == TEPI_SWIGLU ? NTW / 2 : NTW),
-                               m0 + wm * MTW, rows, n_tiles, N, lane, out, act, nullptr, m0 * 32, &go);
+  const int id = blockIdx.x;
+  if (id < g.full) {
+    // Workgroup ids go to the XCDs in turn.  Each XCD gets a run of the tiles, so that what its compute units hold at once
+    // shares operands; row after row with a multiple of 8 columns it keeps the same few columns by itself.
+    const int xcd = id & 7, per = g.full >> 3, more = g.full & 7;
+    const int2 at = big_tile(g, (g.nx & 7) ? xcd * per + min(xcd, more) + (id >> 3) : id);
+    if (at.y * 256 >= rows) return;
+    big_body<EPI, DH, 4>(rc, x, w0, w1, out, act, N, K, go, qo, lds, rows, at.x * 2, at.y * 8);
+  } else {
+    int h = id - g.full, u0, m0;
+    const int pairs = ((g.split + 7) & ~7) * 2;
+    if (h < pairs) {             // the halves of a tile 8 ids apart: same XCD
+      const int t = (h >> 4) * 8 + (h & 7);
+      if (t >= g.split) return;
+      const int2 at = big_tile(g, g.full + t);
+      u0 = at.x * 2 + ((h >> 3) & 1);
+      m0 = at.y * 8;
+    } else {
+      u0 = 2 * g.nx;
+      m0 = (h - pairs) * 8;
+    }
+    if (m0 * 32 >= rows) return;
+    big_body<EPI, DH, 2>(rc, x, w0, w1, out, act, N, K, go, qo, lds, rows, u0, m0);
+  }
+}
+
+// units: columns in 128 (SwiGLU: features in 64).  The tiles past the last whole round of 256 workgroups go as halves where those are
+// one round: it then lasts 0.57 of one (a wavefront of 128 x 64 reads 6 fragments for 8 products).
+static BigGrid big_grid(int units, int m_tiles) {
+  BigGrid g{units / 2, ceil_div(m_tiles, 8), 0, 0, units & 1};
+  const int tiles = g.nx * g.my, last = tiles % 256;
+  g.split = 2 * last + (g.odd ? g.my : 0) <= 256 ? last : 0;
+  g.full = tiles - g.split;
+  return g;
 }
 
 template <int WGM, int WGN, int MTW, int NTW, int BK, int R, int EPI>
@@ -639,32 +741,22 @@ bool launch_moe_tile_down(hipStream_t st, RowCtx rc, const int* cnt, const int* 
   return true;
 }
 
-// Tile shapes.  WIDE: 256 x 256 outputs on 4 wavefronts (gemm_big_kernel, 128 KiB LDS).  NARROW: 256 x 128 on 4 wavefronts, ring of 3
-// (72 KiB, two workgroups per CU) - for few or ragged weight tiles and for short batches.
-// Measured on MI355X, 8192 x (2 x 14336) x 4096 fused gate/up: NARROW 0.99, WIDE 1.3 PFLOP/s.  The choice
-// changes no result (see the header comment).
-#define TILE_WIDE(EPI) gemm_big_kernel<EPI>
-#define TILE_NARROW(EPI) gemm_tile_dma_kernel<2, 2, 4, 2, 2, 3, EPI>
-
+// Tile shapes (the choice changes no result, see the header comment).  WIDE: gemm_big_kernel, 256 x 256 outputs or 256 x 128.
 // SMALL: 64 rows x 32 columns (SwiGLU: 32 features) on 2 wavefronts, ring of 16 stages, and MID: 128 x 64 on 4,
 // ring of 12 (8), for passes of few rows: there a workgroup of the larger tiles walks k alone at two
-// stages per memory latency, whatever the rows.  SMALL while its workgroups are at most one per compute unit, MID
-// while they are at most two (SwiGLU, 128 KiB of LDS: one; at 300 workgroups it loses 13-19 %).  us, NARROW or
-// WIDE / as here: 2560 x 9728 at 37, 256, 512, 1024 rows 146, 150, 150, 153 / 45, 64, 65, 127; 896 x 4864
-// at 37, 512, 2048 rows 73, 77, 77 / 24, 24, 36; 4096 x 4096 at 128, 512 rows 65, 68 / 21, 33; gate/up of
-// 2560 x 9728 at 64, 128 rows 45, 46 / 28, 28, of 896 x 4864 at 37, 256 rows 17, 18 / 8, 12.
+// stages per memory latency, whatever the rows.  SMALL while its workgroups are at most one per compute unit, then MID
+// while its are.  us, WIDE / as here: 2560 x 9728 at 37, 256, 512 rows 146, 150, 150 / 45, 64, 65; 896 x 4864
+// at 37, 512 rows 73, 77 / 24, 24; 4096 x 4096 at 128, 512 rows 65, 68 / 21, 33; gate/up of
+// 2560 x 9728 at 64, 128 rows 45, 46 / 28, 28, of 896 x 4864 at 37, 256 rows 17, 18 / 8, 12.  MID at two workgroups per unit | WIDE:
+// 2560 x 9728 at 900, 1500 rows 131, 140 | 102, 108; 896 x 4864 at 2500, 4000 rows 71, 73 | 54, 57; 4096 x 14336 at 700 rows 185 | 147;
+// 1184 x 3104 at 2000 rows 47 | 37.
+#define TILE_WIDE(EPI) gemm_big_kernel<EPI>
 #define TILE_SMALL(EPI) gemm_tile_dma_kernel<2, 1, 1, 1, 2, 16, EPI>
 #define TILE_SMALL_SWIGLU gemm_tile_dma_kernel<2, 1, 1, 2, 2, 16, TEPI_SWIGLU>
 #define TILE_MID(EPI) gemm_tile_dma_kernel<2, 2, 2, 1, 2, 12, EPI>
 #define TILE_MID_SWIGLU gemm_tile_dma_kernel<2, 2, 2, 2, 2, 8, TEPI_SWIGLU>
 static bool small_tile(int units, int m_tiles) { return (long long)units * ceil_div(m_tiles, 2) <= 256; }
-static bool mid_tile(int units, int m_tiles, int most) { return (long long)ceil_div(units, 2) * ceil_div(m_tiles, 4) <= most; }
-
-// units: weight tiles (plain) or feature tiles (SwiGLU); per_wide: units per WIDE workgroup
-static bool wide_tile(int units, int per_wide, int m_tiles) {
-  const int wgs = ceil_div(units, per_wide) * ceil_div(m_tiles, 8);
-  return wgs >= 128 && ceil_div(units, per_wide) * per_wide * 20 <= units * 23;   // <= 15 % padding
-}
+static bool mid_tile(int units, int m_tiles) { return (long long)ceil_div(units, 2) * ceil_div(m_tiles, 4) <= 256; }
 
 template <int EPI>
 static void launch_tile(hipStream_t st, RowCtx rc, const bf16_t* x, const bf16_t* Wp, float* out, int N, int K) {
@@ -673,14 +765,11 @@ static void launch_tile(hipStream_t st, RowCtx rc, const bf16_t* x, const bf16_t
   const bf16x8* wv = reinterpret_cast<const bf16x8*>(Wp);
   if (small_tile(n_tiles, m_tiles)) {
     hipLaunchKernelGGL((TILE_SMALL(EPI)), dim3(n_tiles, ceil_div(m_tiles, 2)), dim3(128), 0, st, rc, xv, wv, nullptr, out, nullptr, N, K, GroupOut{});
-  } else if (mid_tile(n_tiles, m_tiles, 512)) {
+  } else if (mid_tile(n_tiles, m_tiles)) {
     hipLaunchKernelGGL((TILE_MID(EPI)), dim3(ceil_div(n_tiles, 2), ceil_div(m_tiles, 4)), dim3(256), 0, st, rc, xv, wv, nullptr, out, nullptr, N, K, GroupOut{});
-  } else if (wide_tile(n_tiles, 8, m_tiles)) {
-    dim3 grid(ceil_div(n_tiles, 8), ceil_div(m_tiles, 8));
-    hipLaunchKernelGGL((TILE_WIDE(EPI)), grid, dim3(256), 0, st, rc, xv, wv, nullptr, out, nullptr, N, K, GroupOut{}, QkvOut{});
   } else {
-    dim3 grid(ceil_div(n_tiles, 4), ceil_div(m_tiles, 8));
-    hipLaunchKernelGGL((TILE_NARROW(EPI)), grid, dim3(256), 0, st, rc, xv, wv, nullptr, out, nullptr, N, K, GroupOut{});
+    const BigGrid g = big_grid(ceil_div(n_tiles, 4), m_tiles);
+    hipLaunchKernelGGL((TILE_WIDE(EPI)), dim3(g.full + g.halves()), dim3(256), 0, st, rc, xv, wv, nullptr, out, nullptr, N, K, GroupOut{}, QkvOut{}, g);
   }
 }
 void launch_gemm_tile(hipStream_t st, RowCtx rc, const bf16_t* x, const bf16_t* Wp, float* out, int N, int K) {
@@ -689,33 +778,29 @@ void launch_gemm_tile(hipStream_t st, RowCtx rc, const bf16_t* x, const bf16_t* 
 void launch_gemm_tile_resid(hipStream_t st, RowCtx rc, const bf16_t* x, const bf16_t* Wp, float* x_res, int N, int K) {
   launch_tile<TEPI_RESID>(st, rc, x, Wp, x_res, N, K);
 }
-// QKV with the rotary epilogue.  SMALL and MID as above (64 columns per wavefront; MID one workgroup per unit), NARROW while
-// its workgroups are at most one per unit (then WIDE leaves half the chip idle; at 288 it loses 11 %), else WIDE - which alone
-// took every pass before and cost a short prompt one workgroup's walk over k.  us, WIDE | SMALL | MID | NARROW:
-//   1152 x 896 (14 + 2 x 2 heads of 64) at 37, 768, 2048, 4096 rows  24, 31, 34, 35 | 9, 9, 26, 42 | 12, 14, 16, 29 | 19, 22, 24, 26
-//   1792 x 1184 (20 + 2 x 4 of 64) at 37, 512, 2048, 4096 rows  29, 36, 39, 42 | 10, 11, 42, 70 | 15, 16, 19, 36 | 23, 27, 29, 32
-//   6144 x 2560 (32 + 2 x 8 of 128) at 37, 128, 256, 640, 1024, 1536 rows  53, 56, 59, 62, 64, 68 | 20, 21, 39, 77, 115, 171 |
-//                                                          26, 28, 29, 32, 59, 88 | 44, 45, 48, 51, 53, 76
-//   6144 x 4096 at 37, 640, 1024, 2048 rows  79, 90, 93, 119 | 30, 117, 174, 339 | 40, 49, 89, 146 | 66, 74, 79, 127
-enum QkvShape { QKV_SMALL, QKV_MID, QKV_NARROW, QKV_WIDE };
+// QKV with the rotary epilogue: the same rules, 64 columns per wavefront.  us, WIDE (| as tiles of 256 x 256 alone) | SMALL | MID:
+//   1152 x 896 (14 + 2 x 2 heads of 64) at 37, 768, 2048, 4096 rows  19, 22, 19, 21 (24, 31, 34, 35) | 9, 9, 26, 42 | 12, 14, 15, 29
+//   1792 x 1184 (20 + 2 x 4 of 64) at 1300, 2000, 4096 rows  23, 24, 26 (.., .., 42) | .. | 17, 18, 36
+//   6144 x 2560 (32 + 2 x 8 of 128) at 37, 256, 512, 1024, 1536 rows  (53, 59, .., 64, 66) | 20, 39, .., 115, 171 | 26, 29, 29, 59, 88
+//   6144 x 4096 at 512, 640, 1024, 2048 rows  52, 53, 57, 102 (.., 90, 93, 119) | .., 117, 174, 339 | 42, 43, 89, 146
+enum QkvShape { QKV_SMALL, QKV_MID, QKV_WIDE };
 static QkvShape qkv_shape(int units, int m_tiles) {         // units of 64 columns
   if (small_tile(units, m_tiles)) return QKV_SMALL;
-  if (mid_tile(units, m_tiles, 256)) return QKV_MID;
-  return (long long)ceil_div(units, 2) * ceil_div(m_tiles, 8) <= 256 ? QKV_NARROW : QKV_WIDE;
+  return mid_tile(units, m_tiles) ? QKV_MID : QKV_WIDE;
 }
 bool launch_gemm_tile_qkv(hipStream_t st, RowCtx rc, const bf16_t* x, const bf16_t* Wp, int N, int K, const QkvOut& qo) {
   if (qo.kvl.mode != 1) return false;
   const int units = ceil_div(N >> 5, 2), m_tiles = ceil_div(rc.max_rows, 32);       // 64 columns
   const QkvShape shape = qkv_shape(units, m_tiles);
+  const BigGrid big = big_grid(ceil_div(units, 2), m_tiles);
 #define QKV_TILE(DH, WGN, MTW, NW, R)                                                                                  \
   hipLaunchKernelGGL((gemm_tile_qkv_kernel<2, WGN, MTW, 2, 2, R, DH>), dim3(ceil_div(units, WGN), ceil_div(m_tiles, 2 * MTW)), \
                      dim3(64 * NW), 0, st, rc, reinterpret_cast<const bf16x8*>(x), reinterpret_cast<const bf16x8*>(Wp), N, K, qo)
 #define QKV_LAUNCH(DH)                                                                                                 \
   if (shape == QKV_SMALL) QKV_TILE(DH, 1, 1, 2, 16);                                                                           \
   else if (shape == QKV_MID) QKV_TILE(DH, 2, 2, 4, 8);                                                                       \
-  else if (shape == QKV_NARROW) QKV_TILE(DH, 2, 4, 4, 3);                                                                       \
-  else hipLaunchKernelGGL((gemm_big_kernel<TEPI_QKV, DH>), dim3(ceil_div(N >> 5, 8), ceil_div(m_tiles, 8)), dim3(256), 0, st, rc, \
-                          reinterpret_cast<const bf16x8*>(x), reinterpret_cast<const bf16x8*>(Wp), nullptr, nullptr, nullptr, N, K, GroupOut{}, qo)
+  else hipLaunchKernelGGL((gemm_big_kernel<TEPI_QKV, DH>), dim3(big.full + big.halves()), dim3(256), 0, st, rc, \
+                          reinterpret_cast<const bf16x8*>(x), reinterpret_cast<const bf16x8*>(Wp), nullptr, nullptr, nullptr, N, K, GroupOut{}, qo, big)
   switch (qo.kvl.head_dim) {
     case 32: QKV_LAUNCH(32); break;
     case 64: QKV_LAUNCH(64); break;
@@ -735,14 +820,11 @@ void launch_gemm_tile_swiglu(hipStream_t st, RowCtx rc, const bf16_t* x, const b
   const bf16x8* uv = reinterpret_cast<const bf16x8*>(Wu);
   if (small_tile(f_tiles, m_tiles)) {
     hipLaunchKernelGGL((TILE_SMALL_SWIGLU), dim3(f_tiles, ceil_div(m_tiles, 2)), dim3(128), 0, st, rc, xv, gv, uv, nullptr, act, F, K, GroupOut{});
-  } else if (mid_tile(f_tiles, m_tiles, 256)) {
+  } else if (mid_tile(f_tiles, m_tiles)) {
     hipLaunchKernelGGL((TILE_MID_SWIGLU), dim3(ceil_div(f_tiles, 2), ceil_div(m_tiles, 4)), dim3(256), 0, st, rc, xv, gv, uv, nullptr, act, F, K, GroupOut{});
-  } else if (wide_tile(f_tiles, 4, m_tiles)) {
-    dim3 grid(ceil_div(f_tiles, 4), ceil_div(m_tiles, 8));
-    hipLaunchKernelGGL((TILE_WIDE(TEPI_SWIGLU)), grid, dim3(256), 0, st, rc, xv, gv, uv, nullptr, act, F, K, GroupOut{}, QkvOut{});
   } else {
-    dim3 grid(ceil_div(f_tiles, 2), ceil_div(m_tiles, 8));
-    hipLaunchKernelGGL((TILE_NARROW(TEPI_SWIGLU)), grid, dim3(256), 0, st, rc, xv, gv, uv, nullptr, act, F, K, GroupOut{});
+    const BigGrid g = big_grid(ceil_div(f_tiles, 2), m_tiles);
+    hipLaunchKernelGGL((TILE_WIDE(TEPI_SWIGLU)), dim3(g.full + g.halves()), dim3(256), 0, st, rc, xv, gv, uv, nullptr, act, F, K, GroupOut{}, QkvOut{}, g);
   }
 }
 
@@ -809,7 +891,7 @@ bool launch_gemm_tile_logits(hipStream_t st, RowCtx rc, const bf16_t* x, const b
   if (rows <= 64 || (rows <= 128 && groups < 256)) LM_LAUNCH(LM_64, 2, 256, go);
   else if (!tall) LM_LAUNCH(LM_128, 4, 256, go);
   else if (K <= 2048) LM_LAUNCH(LM_256, 8, 512, go);
-  else LM_LAUNCH(TILE_WIDE(TEPI_LOGITS), 8, 256, go, QkvOut{});
+  else LM_LAUNCH(TILE_WIDE(TEPI_LOGITS), 8, 256, go, QkvOut{}, BigGrid{});
 #undef LM_64
 #undef LM_128
 #undef LM_256
