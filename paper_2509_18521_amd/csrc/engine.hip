@@ -922,11 +922,12 @@ int april_init(const april_model_cfg* cfg, const april_tensor* weights, int32_t 
   c->fuse_norm = !(fn && !strcmp(fn, "0"));
   const char* fd = getenv("APRIL_FUSE_DOWN");    // off by default: measured 5 % slower end to end on configuration 2
   c->fuse_down = fd && !strcmp(fd, "1");
-  // decode gate/up on the LDS-tiled kernel from this row bound (us per launch, skinny / tiled: 9728 features of
-  // 2560 at 96, 128 rows 35.1 / 38.0, 39.0 / 38.1; 14336 of 4096 at 64, 96 rows 53.5 / 60.9, 69 / 61.2; 4864 of
-  // 896 at 128, 256 rows 11.2 / 17.0, 14.8 / 19.2; 8960 of 1536 at 128 rows 24.8 / 25.3, 11008 of 4096 at 96 rows 53.3 / 57.7;
-  // at 64 rows 18944 of 3584 64.8 / 69.4, 28672 of 8192 201 / 183)
-  c->tile_decode_rows = g.d_ffn >= 24576 ? 64 : (g.d_ffn >= 12288 ? 96 : (g.d_ffn >= 8192 ? 128 : 0));
+  // Decode gate/up on the LDS-tiled kernel from this row bound, where its workgroups (64 features each) are about one per compute unit or
+  // many.  us per launch, skinny / tiled: 9728 features of 2560 at 32, 64, 96, 128 rows 25 / 28, 31 / 28, 33 / 32, 35 / 33; 14336 of 4096 at
+  // 32, 64, 96 rows 45 / 47, 52 / 47, 67 / 52; 8960 of 1536 at 64, 128 19 / 18, 23 / 21; 11008 of 4096 at 64 47 / 42; 8192 of 3072 at 64, 96 22 / 30,
+  // 26 / 29; 4864 of 896 at 128, 192 9 / 12, 10 / 12; 18944 of 3584 at 64 63 / 68; 28672 of 8192 at 64 201 / 176.
+  const int ff = g.d_ffn;
+  c->tile_decode_rows = ff >= 24576 ? 64 : ff > 16384 ? 96 : ff >= 8960 ? 64 : ff >= 8192 ? 128 : 0;
   if (const char* td = getenv("APRIL_TILE_DECODE_ROWS")) c->tile_decode_rows = atoi(td);   // debug switch
   if (const char* mt = getenv("APRIL_MOE_TALL_ROWS")) c->moe_tall_rows = atoi(mt);          // debug switch
   if (const char* mt = getenv("APRIL_MOE_TILE")) c->moe_tile = strcmp(mt, "0") != 0;

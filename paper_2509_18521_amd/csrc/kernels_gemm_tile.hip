@@ -12,6 +12,7 @@
 //   * every output element is one accumulator chain over k-tiles 0..K/16-1 in order, whatever
 //     the tile shape or the number of rows: results do not depend on the batch.
 // Every kernel here asks for K % 32 == 0, as april_init does of every inner dimension.
+#include <algorithm>
 #include <type_traits>
 
 #include "kernels.h"
@@ -26,7 +27,7 @@ enum { TEPI_F32 = 0, TEPI_SWIGLU = 1, TEPI_LOGITS = 2, TEPI_RESID = 3, TEPI_QKV 
 template <int MTW, int NTW, int EPI>
 __device__ inline void tile_epilogue(f32x16 (&acc)[NTW][MTW], int nt0, int mt0, int rows, int n_tiles, int N, int lane,
                                      float* __restrict__ out, bf16_t* __restrict__ act,
-                                     const float* row_scale = nullptr, int scale_m0 = 0, const GroupOut* go = nullptr) {
+                                     const float* row_scale = nullptr, const GroupOut* go = nullptr) {
   const int mloc = lane & 31, nhalf = (lane >> 5) << 2;
   if (EPI == TEPI_LOGITS) {
     // a group is an aligned pair of weight tiles (nt0 even): this wavefront holds NTW / 2 of them
@@ -80,8 +81,8 @@ __device__ inline void tile_epilogue(f32x16 (&acc)[NTW][MTW], int nt0, int mt0, 
 #pragma unroll
       for (int j = 0; j < MTW; ++j) {
         const int m = (mt0 + j) * 32 + mloc;
-        // folded RMSNorm (decode): the accumulators are scaled by the row's 1/rms first
-        const float inv = row_scale ? row_scale[m - scale_m0] : 1.0f;
+        // folded RMSNorm (decode): the accumulators are scaled by the row's 1/rms first (this lane's row of every m-tile)
+        const float inv = row_scale ? row_scale[j] : 1.0f;
         if (m < rows) {
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
@@ -207,6 +208,13 @@ __device__ inline void wait_vector_memory() {   // until at most LEFT vector-mem
 #endif
 }
 
+__device__ inline void wait_lds() {             // until no LDS operation is outstanding
+#if defined(__HIP_DEVICE_COMPILE__)
+  __builtin_amdgcn_s_waitcnt(0xc07f);
+#endif
+  asm volatile("" ::: "memory");
+}
+
 // The stage fragments are copied global -> LDS by the memory pipeline itself
 // (global_load_lds_dwordx4: each lane's 16 bytes land at consecutive LDS addresses, which is
 // exactly the fragment layout), through a ring of R stage buffers.  Nothing is staged in
@@ -221,8 +229,7 @@ __device__ inline void wait_vector_memory() {   // until at most LEFT vector-mem
 // Here one wavefront walks all of k, so it closes a chain at every quarter boundary and adds
 // it to a second accumulator set in that order: every output element gets the same bits from
 // either kernel, and the choice between them can follow the row count.  The quarter
-// boundaries must fall on stage boundaries (K % (64 * BK) == 0).  The second accumulator set
-// needs the whole register file of a SIMD, hence the separate entry without the two-waves hint.
+// boundaries must fall on stage boundaries (K % (64 * BK) == 0).
 struct TileNorm {              // RMSNorm folded into the SwiGLU epilogue (CHAIN only)
   const float* ssq;            // [n_ssq][ssq_stride] per-row sums of squares of 32-column slabs; nullptr = none
   int ssq_stride, n_ssq;
@@ -266,10 +273,10 @@ __device__ __forceinline__ int2 tile_of_block(const RowCtx& rc, int MT) {
   return make_int2(((int)blockIdx.x / (8 * mg)) * 8 + (rem & 7), rem >> 3);
 }
 
-template <int WGM, int WGN, int MTW, int NTW, int BK, int R, int EPI, bool CHAIN, bool MOE = false, int DH = 0>
+template <int WGM, int WGN, int MTW, int NTW, int BK, int R, int EPI, bool MOE = false, int DH = 0>
 __device__ __forceinline__ void tile_dma_body(RowCtx rc, const bf16x8* __restrict__ x, const bf16x8* __restrict__ w0,
                                               const bf16x8* __restrict__ w1, float* __restrict__ out,
-                                              bf16_t* __restrict__ act, int N, int K, const TileNorm& tn,
+                                              bf16_t* __restrict__ act, int N, int K, const GroupOut& go,
                                               const TileMoe& mo = TileMoe{}, const QkvOut& qo = QkvOut{}) {
   constexpr int NW = WGM * WGN, MT = WGM * MTW, NT = WGN * NTW, FR = MT + NT;
   constexpr int PER = FR * BK / NW;
@@ -279,7 +286,7 @@ __device__ __forceinline__ void tile_dma_body(RowCtx rc, const bf16x8* __restric
   __shared__ bf16x8 lds[R][BK][FR][64];
   int2 at;
   if constexpr (MOE) at = moe_tile_of_block(mo, ceil_div(N >> 5, EPI == TEPI_SWIGLU ? NT / 2 : NT));
-  else at = tile_of_block<EPI == TEPI_LOGITS || CHAIN>(rc, MT);
+  else at = tile_of_block<EPI == TEPI_LOGITS>(rc, MT);
   const int bx = at.x, by = at.y;
   int rows = rows_or_zero(rc);
   const int m0 = by * MT;
@@ -293,7 +300,7 @@ __device__ __forceinline__ void tile_dma_body(RowCtx rc, const bf16x8* __restric
     w0 += (size_t)e * mo.w_expert_stride;
     if (w1 != nullptr) w1 += (size_t)e * mo.w_expert_stride;
   } else {
-    if (m0 * 32 >= rows || (EPI == TEPI_LOGITS && bx * NT * 32 >= N) || (CHAIN && bx * (NT / 2) * 32 >= N)) return;
+    if (m0 * 32 >= rows || (EPI == TEPI_LOGITS && bx * NT * 32 >= N)) return;
   }
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave / WGN, wn = wave % WGN;
@@ -350,57 +357,12 @@ __device__ __forceinline__ void tile_dma_body(RowCtx rc, const bf16x8* __restric
   for (int i = 0; i < NTW; ++i)
 #pragma unroll
     for (int j = 0; j < MTW; ++j) acc[i][j] = f32x16{};
-  f32x16 tot[CHAIN ? NTW : 1][CHAIN ? MTW : 1];
-  int quarter = 1, next_close = CHAIN ? (KT / 4) / BK : -1;     // stage at which the next chain closes
 
 #pragma unroll
   for (int r = 0; r < R - 1; ++r)
     if (r < n_stages) issue(r);
 
-  // folded norm: 1/rms of this workgroup's rows, summed in the skinny kernel's order (wavefront w
-  // of that kernel adds the slabs w, w + 4, ...; then ((s0 + s1) + s2) + s3)
-  __shared__ float row_scale[CHAIN ? MT * 32 : 1];
-  const bool scaled = CHAIN && EPI == TEPI_SWIGLU && tn.ssq != nullptr;
-  if (scaled) {
-    for (int rl = threadIdx.x; rl < MT * 32; rl += 64 * NW) {
-      int m = m0 * 32 + rl;
-      if (m > rows - 1) m = rows - 1;
-      const float* col = tn.ssq + m;
-      float sw[4] = {0.f, 0.f, 0.f, 0.f};
-      // 32 slabs requested together (independent loads), then added in slab order: chain w sees
-      // the slabs w, w + 4, ... in increasing order
-      for (int t0 = 0; t0 < tn.n_ssq; t0 += 32) {
-        float sl[32];
-#pragma unroll
-        for (int u = 0; u < 32; ++u) {
-          const int t = t0 + u < tn.n_ssq ? t0 + u : tn.n_ssq - 1;
-          sl[u] = col[(size_t)t * tn.ssq_stride];
-        }
-#pragma unroll
-        for (int u = 0; u < 32; ++u)
-          if (t0 + u < tn.n_ssq) sw[u & 3] += sl[u];
-      }
-      float ssum = sw[0];
-#pragma unroll
-      for (int w = 1; w < 4; ++w) ssum += sw[w];
-      row_scale[rl] = 1.0f / sqrtf(__fmaf_rn(ssum, tn.inv_d, tn.eps));
-    }
-    __syncthreads();
-  }
-
   for (int s = 0; s < n_stages; ++s) {
-    if (CHAIN && s == next_close) {
-#pragma unroll
-      for (int i = 0; i < NTW; ++i)
-#pragma unroll
-        for (int j = 0; j < MTW; ++j) {
-          if (quarter == 1) tot[CHAIN ? i : 0][CHAIN ? j : 0] = acc[i][j];
-          else tot[CHAIN ? i : 0][CHAIN ? j : 0] += acc[i][j];
-          acc[i][j] = f32x16{};
-        }
-      ++quarter;
-      next_close = quarter < 4 ? (int)(((long long)KT * quarter / 4) / BK) : -1;
-    }
     // wait for this wavefront's copies of stage s (s_waitcnt vmcnt only: expcnt/lgkmcnt fields all-ones)
     constexpr int LEFT = (R - 2) * PER;
     if (s + R - 2 < n_stages) wait_vector_memory<LEFT>();
@@ -435,18 +397,12 @@ __device__ __forceinline__ void tile_dma_body(RowCtx rc, const bf16x8* __restric
     }
     asm volatile("" ::: "memory");
   }
-  if (CHAIN) {
-#pragma unroll
-    for (int i = 0; i < NTW; ++i)
-#pragma unroll
-      for (int j = 0; j < MTW; ++j) acc[i][j] = tot[CHAIN ? i : 0][CHAIN ? j : 0] + acc[i][j];
-  }
   if constexpr (EPI == TEPI_QKV) {
     qkv_epilogue<NTW, MTW, DH>(acc, bx * WGN + wn, m0 + wm * MTW, rows, n_tiles, lane, rc, qo);
     return;
   }
   tile_epilogue<MTW, NTW, EPI>(acc, bx * (EPI == TEPI_SWIGLU ? NT / 2 : NT) + wn * (EPI == TEPI_SWIGLU ? NTW / 2 : NTW),
-                               m0 + wm * MTW, rows, n_tiles, N, lane, out, act, scaled ? row_scale : nullptr, m0 * 32, &tn.go);
+                               m0 + wm * MTW, rows, n_tiles, N, lane, out, act, nullptr, &go);
 }
 
 // The large tile: 256 x 256 outputs on 4 wavefronts of 128 x 128, one per SIMD.  8 wavefronts of
@@ -479,12 +435,14 @@ __device__ __forceinline__ int2 big_tile(const BigGrid& g, int t) {
 }
 
 // One tile of 256 rows x NTW * 64 columns.  u0: its first column in units of 128 (SwiGLU: of 64 features).
-template <int EPI, int DH, int NTW>
+template <int EPI, int DH, int MTW, int NTW, bool CHAIN = false, int R = BIG_R, int WGM = 2>
 __device__ __forceinline__ void big_body(const RowCtx& rc, const bf16x8* __restrict__ x, const bf16x8* __restrict__ w0,
                                          const bf16x8* __restrict__ w1, float* __restrict__ out, bf16_t* __restrict__ act,
-                                         int N, int K, const GroupOut& go, const QkvOut& qo, bf16x8* lds_raw, int rows, int u0, int m0) {
-  constexpr int MT = 8, NT = 2 * NTW, MTW = 4, BK = BIG_BK, R = BIG_R, FR = MT + NT, PER = FR * BK / 4, READS = NTW + MTW;
+                                         int N, int K, const TileNorm& tn, const QkvOut& qo, bf16x8* lds_raw, int rows, int u0, int m0) {
+  constexpr int MT = WGM * MTW, NT = 2 * NTW, BK = BIG_BK, FR = MT + NT, PER = FR / WGM, READS = NTW + MTW, PRODUCTS = NTW * MTW;
+  static_assert(R >= 4 && (R - 2) * PER < 64 && BK == 2 && FR % WGM == 0, "ring depth, staging split");
   auto lds = reinterpret_cast<bf16x8 (*)[BK][FR][64]>(lds_raw);
+  auto slot_of = [](int s) { return (R & (R - 1)) == 0 ? s & (R - 1) : (int)((unsigned)s % (unsigned)R); };
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave >> 1, wn = wave & 1;
   const int KT = K >> 4, n_stages = KT / BK;
@@ -505,14 +463,14 @@ __device__ __forceinline__ void big_body(const RowCtx& rc, const bf16x8* __restr
     if constexpr (EPI == TEPI_QKV) nt = qkv_tile<NTW, DH>(nt0 / NTW + i / NTW, i % NTW);
     return w0 + (size_t)min(nt, n_tiles - 1) * KT * 64;
   };
-  const int skk = wave & 1, st0 = wave >> 1;             // this wavefront copies k-tile skk of slots st0, st0 + 2, ...
+  const int skk = wave & 1, st0 = wave >> 1;             // this wavefront copies k-tile skk of slots st0, st0 + WGM, ...
   const bf16x8* src[PER];                               // wavefront-uniform: scalar registers
 #pragma unroll
-  for (int u = 0; u < PER; ++u) src[u] = slot_base(st0 + 2 * u) + skk * 64;
+  for (int u = 0; u < PER; ++u) src[u] = slot_base(st0 + WGM * u) + skk * 64;
   auto copy = [&](int s, int u) {
     // scalar base + 32-bit lane offset
     copy_fragment_to_lds(reinterpret_cast<const bf16x8*>(reinterpret_cast<const char*>(src[u]) + (unsigned)(s * (BK * 1024) + lane * 16)),
-                         &lds[s & (R - 1)][skk][st0 + 2 * u][0]);
+                         &lds[slot_of(s)][skk][st0 + WGM * u][0]);
   };
 
   f32x16 acc[NTW][MTW];
@@ -520,19 +478,42 @@ __device__ __forceinline__ void big_body(const RowCtx& rc, const bf16x8* __restr
   for (int i = 0; i < NTW; ++i)
 #pragma unroll
     for (int j = 0; j < MTW; ++j) acc[i][j] = f32x16{};
+  // Folded norm: 1/rms of the workgroup's rows, summed in the skinny kernel's order (wavefront w of that kernel adds the slabs w, w + 4, ...;
+  // then ((s0 + s1) + s2) + s3).  The first 64 slabs are requested ahead of the ring's copies, so that the sum does not wait for those.
+  constexpr int SLABS = 64;
+  float* const scale_lds = reinterpret_cast<float*>(&lds[R - 1][0][0][0]);      // (no copies go there before stage 0 is under way)
+  const bool scaled = CHAIN && EPI == TEPI_SWIGLU && tn.ssq != nullptr;
+  const float* const ssq_row = scaled ? tn.ssq + min(m0 * 32 + (int)threadIdx.x, rows - 1) : nullptr;
+  float sl[CHAIN ? SLABS : 1];
+  auto request = [&](int t0) {
+#pragma unroll
+    for (int u = 0; u < SLABS; ++u) sl[u] = ssq_row[(size_t)min(t0 + u, tn.n_ssq - 1) * tn.ssq_stride];
+  };
+  if (CHAIN && scaled) request(0);
 #pragma unroll
   for (int r = 0; r < R - 1; ++r)
     if (r < n_stages) {
 #pragma unroll
       for (int u = 0; u < PER; ++u) copy(r, u);
     }
+  if (CHAIN && scaled) {
+    float sw[4] = {0.f, 0.f, 0.f, 0.f};
+    for (int t0 = 0; t0 < tn.n_ssq; t0 += SLABS) {
+      if (t0 > 0) request(t0);
+#pragma unroll
+      for (int u = 0; u < SLABS; ++u)
+        if (t0 + u < tn.n_ssq) sw[u & 3] += sl[u];
+    }
+    if ((int)threadIdx.x < MT * 32) scale_lds[threadIdx.x] = 1.0f / sqrtf(__fmaf_rn(((sw[0] + sw[1]) + sw[2]) + sw[3], tn.inv_d, tn.eps));
+    wait_lds();
+  }
   bf16x8 a[2][NTW], b[2][MTW];
   auto read = [&](int s, int kk) {
-    a[kk][0] = lds[s & (R - 1)][kk][MT + wn * NTW][lane];      // in the order the products want them
+    a[kk][0] = lds[slot_of(s)][kk][MT + wn * NTW][lane];      // in the order the products want them
 #pragma unroll
-    for (int j = 0; j < MTW; ++j) b[kk][j] = lds[s & (R - 1)][kk][wm * MTW + j][lane];
+    for (int j = 0; j < MTW; ++j) b[kk][j] = lds[slot_of(s)][kk][wm * MTW + j][lane];
 #pragma unroll
-    for (int i = 1; i < NTW; ++i) a[kk][i] = lds[s & (R - 1)][kk][MT + wn * NTW + i][lane];
+    for (int i = 1; i < NTW; ++i) a[kk][i] = lds[slot_of(s)][kk][MT + wn * NTW + i][lane];
   };
   auto products = [&](int kk) {
 #pragma unroll
@@ -543,6 +524,14 @@ __device__ __forceinline__ void big_body(const RowCtx& rc, const bf16x8* __restr
   if (n_stages > R - 2) wait_vector_memory<(R - 2) * PER>(); else wait_vector_memory<0>();
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
+  float row_scale[MTW];                                  // of this lane's rows
+#pragma unroll
+  for (int j = 0; j < MTW; ++j) row_scale[j] = 1.0f;
+  if (scaled) {
+#pragma unroll
+    for (int j = 0; j < MTW; ++j) row_scale[j] = scale_lds[(wm * MTW + j) * 32 + (lane & 31)];
+    wait_lds();
+  }
   read(0, 0);
   // One stage.  COPY: stage s + R - 1 exists.  (Reading k-tile 0 of stage s + 1 past the end fetches a slot's old contents, which nothing uses: the code
   // stays free of branches between the products.)
@@ -552,10 +541,10 @@ __device__ __forceinline__ void big_body(const RowCtx& rc, const bf16x8* __restr
     products(0);
 #pragma unroll
     for (int q = 0; q < READS; ++q) {                    // LDS reads between the first products: back before the last ones end
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      if (q < PRODUCTS) __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
       __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
     }
-    __builtin_amdgcn_sched_group_barrier(0x008, NTW * MTW - READS, 0);
+    if (PRODUCTS > READS) __builtin_amdgcn_sched_group_barrier(0x008, PRODUCTS - READS, 0);
     // stage s + 1 has landed when at most the copies of the stages s + 2 .. s + R - 2 are outstanding
     wait_vector_memory<COPY ? (R - 3) * PER : 0>();
     __builtin_amdgcn_s_barrier();
@@ -568,16 +557,37 @@ __device__ __forceinline__ void big_body(const RowCtx& rc, const bf16x8* __restr
     products(1);
 #pragma unroll
     for (int q = 0; q < READS; ++q) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      if (q < PRODUCTS) __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
       __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
       if (COPY && q < PER) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
     }
-    __builtin_amdgcn_sched_group_barrier(0x008, NTW * MTW - READS, 0);
+    if (PRODUCTS > READS) __builtin_amdgcn_sched_group_barrier(0x008, PRODUCTS - READS, 0);
     asm volatile("" ::: "memory");
   };
   int s = 0;
-  for (; s + R - 1 < n_stages; ++s) stage(s, std::true_type{});
-  for (; s < n_stages; ++s) stage(s, std::false_type{});
+  if constexpr (CHAIN) {
+    f32x16 tot[NTW][MTW];
+#pragma unroll 1
+    for (int quarter = 0; quarter < 4; ++quarter) {
+      const int end = n_stages / 4 * (quarter + 1);
+      for (; s < min(end, n_stages - R + 1); ++s) stage(s, std::true_type{});
+      for (; s < end; ++s) stage(s, std::false_type{});
+#pragma unroll
+      for (int i = 0; i < NTW; ++i)
+#pragma unroll
+        for (int j = 0; j < MTW; ++j) {
+          tot[i][j] = quarter == 0 ? acc[i][j] : tot[i][j] + acc[i][j];
+          acc[i][j] = f32x16{};
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < NTW; ++i)
+#pragma unroll
+      for (int j = 0; j < MTW; ++j) acc[i][j] = tot[i][j];
+  } else {
+    for (; s + R - 1 < n_stages; ++s) stage(s, std::true_type{});
+    for (; s < n_stages; ++s) stage(s, std::false_type{});
+  }
   if constexpr (EPI == TEPI_QKV) {
     qkv_epilogue<NTW, MTW, DH>(acc, nt0 / NTW + wn, m0 + wm * MTW, rows, n_tiles, lane, rc, qo);
   } else if constexpr (EPI == TEPI_RESID) {
@@ -619,7 +629,7 @@ __device__ __forceinline__ void big_body(const RowCtx& rc, const bf16x8* __restr
     }
   } else {
     tile_epilogue<MTW, NTW, EPI>(acc, nt0 + wn * (EPI == TEPI_SWIGLU ? NTW / 2 : NTW), m0 + wm * MTW, rows, n_tiles, N, lane, out, act,
-                                 nullptr, m0 * 32, &go);
+                                 CHAIN && EPI == TEPI_SWIGLU ? row_scale : nullptr, &tn.go);
   }
 }
 
@@ -627,15 +637,10 @@ template <int EPI, int DH = 0>
 __global__ __launch_bounds__(256, 1) void gemm_big_kernel(RowCtx rc, const bf16x8* __restrict__ x,
                                                           const bf16x8* __restrict__ w0, const bf16x8* __restrict__ w1,
                                                           float* __restrict__ out, bf16_t* __restrict__ act, int N, int K,
-                                                          GroupOut go, QkvOut qo, BigGrid g) {
+                                                          QkvOut qo, BigGrid g) {
   __shared__ bf16x8 lds[BIG_R * BIG_BK * 16 * 64];
   const int rows = rows_or_zero(rc);
-  if constexpr (EPI == TEPI_LOGITS) {
-    const int2 at = tile_of_block<true>(rc, 8);
-    if (at.y * 256 >= rows || at.x * 256 >= N) return;
-    big_body<EPI, DH, 4>(rc, x, w0, w1, out, act, N, K, go, qo, lds, rows, at.x * 2, at.y * 8);
-    return;
-  }
+  const TileNorm tn{};
   const int id = blockIdx.x;
   if (id < g.full) {
     // Workgroup ids go to the XCDs in turn.  Each XCD gets a run of the tiles, so that what its compute units hold at once
@@ -643,7 +648,7 @@ __global__ __launch_bounds__(256, 1) void gemm_big_kernel(RowCtx rc, const bf16x
     const int xcd = id & 7, per = g.full >> 3, more = g.full & 7;
     const int2 at = big_tile(g, (g.nx & 7) ? xcd * per + min(xcd, more) + (id >> 3) : id);
     if (at.y * 256 >= rows) return;
-    big_body<EPI, DH, 4>(rc, x, w0, w1, out, act, N, K, go, qo, lds, rows, at.x * 2, at.y * 8);
+    big_body<EPI, DH, 4, 4>(rc, x, w0, w1, out, act, N, K, tn, qo, lds, rows, at.x * 2, at.y * 8);
   } else {
     int h = id - g.full, u0, m0;
     const int pairs = ((g.split + 7) & ~7) * 2;
@@ -658,9 +663,38 @@ __global__ __launch_bounds__(256, 1) void gemm_big_kernel(RowCtx rc, const bf16x
       m0 = (h - pairs) * 8;
     }
     if (m0 * 32 >= rows) return;
-    big_body<EPI, DH, 2>(rc, x, w0, w1, out, act, N, K, go, qo, lds, rows, u0, m0);
+    big_body<EPI, DH, 4, 2>(rc, x, w0, w1, out, act, N, K, tn, qo, lds, rows, u0, m0);
   }
 }
+
+// The same for decode passes of many rows: MTW * 64 rows x NTW * 64 columns, the row groups of a column of tiles 8 workgroup ids apart
+// (same XCD, same moment: one read of the weights).  The first `full` columns of tiles are whole, those behind them go as halves.
+template <int EPI, int WGM, int MTW, int NTW, bool CHAIN, int OCC, int R>
+__global__ __launch_bounds__(128 * WGM, OCC) void gemm_rows_kernel(RowCtx rc, const bf16x8* __restrict__ x, const bf16x8* __restrict__ w0,
+                                                             const bf16x8* __restrict__ w1, float* __restrict__ out,
+                                                             bf16_t* __restrict__ act, int N, int K, TileNorm tn, int full) {
+  // (one array: with a second one the compiler waits for every copy in flight before it reads from this one)
+  __shared__ bf16x8 lds[R * BIG_BK * (WGM * MTW + 2 * NTW) * 64];
+  const int rows = rows_or_zero(rc), groups = ceil_div(ceil_div(rc.max_rows, 32), WGM * MTW);
+  const int whole = (full + 7) / 8 * 8 * groups, half = (int)blockIdx.x >= whole, id = (int)blockIdx.x - (half ? whole : 0);
+  const int col = id / (8 * groups) * 8 + (id & 7), m0 = (id % (8 * groups) >> 3) * WGM * MTW;
+  if (m0 * 32 >= rows) return;
+  if constexpr (NTW == 4) {
+    if (half) {
+      if ((2 * full + col) * (EPI == TEPI_SWIGLU ? 64 : 128) >= N) return;
+      big_body<EPI, 0, MTW, 2, CHAIN, R, WGM>(rc, x, w0, w1, out, act, N, K, tn, QkvOut{}, lds, rows, 2 * full + col, m0);
+      return;
+    }
+  }
+  if (col >= full) return;
+  big_body<EPI, 0, MTW, NTW, CHAIN, R, WGM>(rc, x, w0, w1, out, act, N, K, tn, QkvOut{}, lds, rows, NTW == 4 ? col * 2 : col, m0);
+}
+// The columns of tiles that stay whole, of `units` half columns: as in big_grid.
+static int rows_full(int units, int groups) {
+  const int tiles = units / 2 * groups, whole = tiles / 256 * 256 / groups;
+  return (units - 2 * whole) * groups <= 256 ? whole : (units + 1) / 2;
+}
+static int rows_grid(int units, int full, int groups) { return ((full + 7) / 8 + (units > 2 * full ? (units - 2 * full + 7) / 8 : 0)) * 8 * groups; }
 
 // units: columns in 128 (SwiGLU: features in 64).  The tiles past the last whole round of 256 workgroups go as halves where those are
 // one round: it then lasts 0.57 of one (a wavefront of 128 x 64 reads 6 fragments for 8 products).
@@ -677,23 +711,13 @@ __global__ __launch_bounds__(64 * WGM * WGN) __attribute__((amdgpu_waves_per_eu(
 void gemm_tile_dma_kernel(RowCtx rc, const bf16x8* __restrict__ x, const bf16x8* __restrict__ w0,
                           const bf16x8* __restrict__ w1, float* __restrict__ out, bf16_t* __restrict__ act, int N,
                           int K, GroupOut go) {
-  TileNorm tn{};
-  tn.go = go;
-  tile_dma_body<WGM, WGN, MTW, NTW, BK, R, EPI, false>(rc, x, w0, w1, out, act, N, K, tn);
+  tile_dma_body<WGM, WGN, MTW, NTW, BK, R, EPI>(rc, x, w0, w1, out, act, N, K, go);
 }
 
 template <int WGM, int WGN, int MTW, int NTW, int BK, int R, int DH>
 __global__ __launch_bounds__(64 * WGM * WGN) __attribute__((amdgpu_waves_per_eu(2)))
 void gemm_tile_qkv_kernel(RowCtx rc, const bf16x8* __restrict__ x, const bf16x8* __restrict__ w0, int N, int K, QkvOut qo) {
-  tile_dma_body<WGM, WGN, MTW, NTW, BK, R, TEPI_QKV, false, false, DH>(rc, x, w0, nullptr, nullptr, nullptr, N, K, TileNorm{}, TileMoe{}, qo);
-}
-
-template <int WGM, int WGN, int MTW, int NTW, int BK, int R, int EPI>
-__global__ __launch_bounds__(64 * WGM * WGN)
-void gemm_tile_chain_kernel(RowCtx rc, const bf16x8* __restrict__ x, const bf16x8* __restrict__ w0,
-                            const bf16x8* __restrict__ w1, float* __restrict__ out, bf16_t* __restrict__ act, int N,
-                            int K, TileNorm tn) {
-  tile_dma_body<WGM, WGN, MTW, NTW, BK, R, EPI, true>(rc, x, w0, w1, out, act, N, K, tn);
+  tile_dma_body<WGM, WGN, MTW, NTW, BK, R, TEPI_QKV, false, DH>(rc, x, w0, nullptr, nullptr, nullptr, N, K, GroupOut{}, TileMoe{}, qo);
 }
 
 // Routed experts in prefill: 128 packed rows (one row group of the dispatch list) x 256 weight
@@ -704,7 +728,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
 void moe_tile_kernel(RowCtx rc, const bf16x8* __restrict__ x, const bf16x8* __restrict__ w0,
                      const bf16x8* __restrict__ w1, float* __restrict__ out, bf16_t* __restrict__ act, int N, int K,
                      TileMoe mo) {
-  tile_dma_body<1, 4, 4, 2, 2, 3, EPI, false, true>(rc, x, w0, w1, out, act, N, K, TileNorm{}, mo);
+  tile_dma_body<1, 4, 4, 2, 2, 3, EPI, true>(rc, x, w0, w1, out, act, N, K, GroupOut{}, mo);
 }
 
 int moe_tile_rows() { return 128; }
@@ -769,7 +793,7 @@ static void launch_tile(hipStream_t st, RowCtx rc, const bf16_t* x, const bf16_t
     hipLaunchKernelGGL((TILE_MID(EPI)), dim3(ceil_div(n_tiles, 2), ceil_div(m_tiles, 4)), dim3(256), 0, st, rc, xv, wv, nullptr, out, nullptr, N, K, GroupOut{});
   } else {
     const BigGrid g = big_grid(ceil_div(n_tiles, 4), m_tiles);
-    hipLaunchKernelGGL((TILE_WIDE(EPI)), dim3(g.full + g.halves()), dim3(256), 0, st, rc, xv, wv, nullptr, out, nullptr, N, K, GroupOut{}, QkvOut{}, g);
+    hipLaunchKernelGGL((TILE_WIDE(EPI)), dim3(g.full + g.halves()), dim3(256), 0, st, rc, xv, wv, nullptr, out, nullptr, N, K, QkvOut{}, g);
   }
 }
 void launch_gemm_tile(hipStream_t st, RowCtx rc, const bf16_t* x, const bf16_t* Wp, float* out, int N, int K) {
@@ -800,7 +824,7 @@ bool launch_gemm_tile_qkv(hipStream_t st, RowCtx rc, const bf16_t* x, const bf16
   if (shape == QKV_SMALL) QKV_TILE(DH, 1, 1, 2, 16);                                                                           \
   else if (shape == QKV_MID) QKV_TILE(DH, 2, 2, 4, 8);                                                                       \
   else hipLaunchKernelGGL((gemm_big_kernel<TEPI_QKV, DH>), dim3(big.full + big.halves()), dim3(256), 0, st, rc, \
-                          reinterpret_cast<const bf16x8*>(x), reinterpret_cast<const bf16x8*>(Wp), nullptr, nullptr, nullptr, N, K, GroupOut{}, qo, big)
+                          reinterpret_cast<const bf16x8*>(x), reinterpret_cast<const bf16x8*>(Wp), nullptr, nullptr, nullptr, N, K, qo, big)
   switch (qo.kvl.head_dim) {
     case 32: QKV_LAUNCH(32); break;
     case 64: QKV_LAUNCH(64); break;
@@ -824,37 +848,41 @@ void launch_gemm_tile_swiglu(hipStream_t st, RowCtx rc, const bf16_t* x, const b
     hipLaunchKernelGGL((TILE_MID_SWIGLU), dim3(ceil_div(f_tiles, 2), ceil_div(m_tiles, 4)), dim3(256), 0, st, rc, xv, gv, uv, nullptr, act, F, K, GroupOut{});
   } else {
     const BigGrid g = big_grid(ceil_div(f_tiles, 2), m_tiles);
-    hipLaunchKernelGGL((TILE_WIDE(TEPI_SWIGLU)), dim3(g.full + g.halves()), dim3(256), 0, st, rc, xv, gv, uv, nullptr, act, F, K, GroupOut{}, QkvOut{}, g);
+    hipLaunchKernelGGL((TILE_WIDE(TEPI_SWIGLU)), dim3(g.full + g.halves()), dim3(256), 0, st, rc, xv, gv, uv, nullptr, act, F, K, QkvOut{}, g);
   }
 }
 
 // Decode with many rows in flight: fused gate/up + SiLU*mul with the skinny kernel's summation
 // chains (see CHAIN above) and, when ssq is set, the folded RMSNorm of that kernel.  Returns
 // false (nothing launched) when the shape does not allow it.
-// Workgroups of 64 features and all the rows up to 256: 128 (2 x 2 accumulator tiles per wavefront), 192 (a
-// quarter less matrix work and LDS traffic than the full tile would spend on rows that are not there), 256 on 8
-// wavefronts (4 wavefronts of 128 x 64 with both accumulator sets need the whole register file each: 105 against
-// 97 us).  Up to 384, several row groups beside each other (tile_of_block): of 128 rows where they all fit
-// two per compute unit, else of 192.  Beyond, of 256, or of 192 where that is less in rounds (two workgroups
-// per unit of 192 rows, one of 256): 14336 x 4096 at 512, 1024 rows 135, 264, of 192 178, 347; 9728 x 2560 at 512 rows 85, of 192 81.  us per launch, skinny kernel | here, 9728 x 2560 at 96, 128, 192, 256, 320,
-// 384 rows: 34, 40, 48, 58, 60, 70 | 38, 38, 43, 45, 52, 53; 14336 x 4096: 69, 78, 94, 119, 130, 147 | 61, 62, 70,
-// 77, 127, 128 (row groups a grid apart: 148, 137).
-// A ring deeper than 3 stages made these variants 1.8x slower (the plain kernel does not care).
+// Workgroups of 64 features and 64, 128, 256 or 384 rows, on 4 or 8 wavefronts of 32 or 64 (384: 96) rows x 64 gate / up columns.  Eight
+// wavefronts hide the barriers better than four of twice the size (256 rows 45 | 49 us), and the products of a wavefront are too few for
+// the LDS reads of the next k-tile at less than 64 rows of them; what is left is LDS traffic, 5 to 7.5 KB for 8 products.  Which rows: the least
+// cost in rounds of one workgroup per compute unit (two of 4 wavefronts of 64 rows: cost128x2), times below for one round of each.
+// us per launch, skinny kernel | 3-stage ring of one launch form before | 64 | 128 | 128, two per unit | 256 | 384 rows:
+//   9728 x 2560 (152 workgroups a row group) at 64, 96, 128 rows 31, 33, 35 | 38, 38, 38 | 28, 38, 41 | 29, 32, 33 | 31, 32, 34
+//      at 192, 256, 384 rows 48, 58, 70 | 46, 45, 53 | - | 56, 59, 60 | 47, 52, 51 | 42, 45, 75 | 52, 51, 57
+//   14336 x 4096 (224) at 64, 96, 128 rows 52, 67, 78 | 62, 60, 61 | 47, 62, - | 49, 52, 54 | 50, 56, 58
+//      at 192, 256, 320, 384 rows 94, 119, 130, 147 | 70, 78, 129, 133 | - | 86, 92, 124, 133 | 79, 86, 109, 117 | 67, 72, 122, 126 | 85, 87, 90, 93
+//   8192 x 3072 (128) at 128, 192, 256, 384 rows - | 43, 49, 51, 59 | - | 37, 35, 38, 67 | 38, 37, 40, 58 | 43, 46, 50, 50 | 54, 54, 57, 62
 bool launch_gemm_tile_swiglu_chain(hipStream_t st, RowCtx rc, const bf16_t* x, const bf16_t* Wg, const bf16_t* Wu,
                                    bf16_t* act, int F, int K, const float* ssq, int ssq_stride, float eps) {
   if (K % 128 != 0 || F % 32 != 0) return false;     // quarter boundaries on stage boundaries (BK = 2)
   const int units = ceil_div(F >> 5, 2), m_tiles = ceil_div(rc.max_rows, 32);
   const TileNorm tn{ssq, ssq_stride, K >> 5, 1.0f / (float)K, eps, {}};
-#define CHAIN_LAUNCH(WGM, MTW)                                                                                         \
-  hipLaunchKernelGGL((gemm_tile_chain_kernel<WGM, 2, MTW, 2, 2, 3, TEPI_SWIGLU>), dim3(ceil_div(units, 8) * 8 * ceil_div(m_tiles, WGM * MTW)), \
-                     dim3(64 * WGM * 2), 0, st, rc, reinterpret_cast<const bf16x8*>(x), reinterpret_cast<const bf16x8*>(Wg), \
-                     reinterpret_cast<const bf16x8*>(Wu), nullptr, act, F, K, tn)
-  if (rc.max_rows <= 128) CHAIN_LAUNCH(2, 2);
-  else if (rc.max_rows <= 192) CHAIN_LAUNCH(2, 3);
-  else if (rc.max_rows <= 256) CHAIN_LAUNCH(4, 2);
-  else if (rc.max_rows <= 384 && units * ceil_div(m_tiles, 4) <= 512) CHAIN_LAUNCH(2, 2);
-  else if (rc.max_rows <= 384 || ceil_div(units * ceil_div(m_tiles, 6), 512) * 12 < ceil_div(units * ceil_div(m_tiles, 8), 256) * 8) CHAIN_LAUNCH(2, 3);
-  else CHAIN_LAUNCH(4, 2);
+#define CHAIN_LAUNCH(WGM, MTW, OCC, R)                                                                                 \
+  hipLaunchKernelGGL((gemm_rows_kernel<TEPI_SWIGLU, WGM, MTW, 2, true, OCC, R>), dim3(rows_grid(2 * units, units, ceil_div(m_tiles, WGM * MTW))), \
+                     dim3(128 * WGM), 0, st, rc, reinterpret_cast<const bf16x8*>(x), reinterpret_cast<const bf16x8*>(Wg), \
+                     reinterpret_cast<const bf16x8*>(Wu), nullptr, act, F, K, tn, units)
+  const int rows = rc.max_rows;
+  auto rounds = [&](int group_rows, int slots) { return ceil_div(units * ceil_div(rows, group_rows), slots); };
+  const int cost128 = 100 * rounds(128, 256), cost128x2 = 153 * rounds(128, 512), cost256 = 130 * rounds(256, 256), cost384 = 172 * rounds(384, 256);
+  const int least = std::min({cost128, cost128x2, cost256, cost384});
+  if (rows <= 64) CHAIN_LAUNCH(2, 1, 2, 6);
+  else if (least == cost128) CHAIN_LAUNCH(4, 1, 1, 6);
+  else if (least == cost256) CHAIN_LAUNCH(4, 2, 1, 6);
+  else if (least == cost384) CHAIN_LAUNCH(4, 3, 1, 4);
+  else CHAIN_LAUNCH(2, 2, 2, 5);
 #undef CHAIN_LAUNCH
   return true;
 }
@@ -863,35 +891,47 @@ bool launch_gemm_tile_swiglu_chain(hipStream_t st, RowCtx rc, const bf16_t* x, c
 // tile (k-tiles in order): the choice changes no bit.  False (nothing launched): the skinny kernel is
 // the one to use.
 // The head is read once (from HBM: its bound up to about 200 rows) and every row group's workgroups run
-// beside each other (tile_of_block).  us per launch, skinny | 64 x 256 | 128 x 256 | 256 x 256 tile:
-//                 7 rows          64 rows             128 rows             192 rows        384 rows
-//   128256 x 4096 179 | 191       192 | 189 | 195     239 | 224 | 195      278 | 239       394 | 443 (500 with the row groups a grid apart)
-//   151936 x 2560 146 | 142       167 | 150 | 158     214 | 178 | 163      212 | 213       306 | 358 (394)
-//   151936 x 2048 123 | 125       137 | 131 | 139     173 | 138 | 138      163 | 177       244 | 299 (330)
-//   151936 x 896   49 | 45         56 | 49 | 53        77 | 58 | 58         79 | 101       117 | 164 (169)
-//   32032 x 1184   15 | 16         18 | 16 | 24        25 | 18 | 25         26 | 36         36 | 41
-// From 129 to 256 rows the 256-row tile: for long products (K >= 3072), and for shorter ones where two groups of 128 rows are
-// more than one workgroup per unit and the 256-column groups fill one round (129 .. 256) or their last one; from 385 to 512
-// rows for more than 64 groups (32000 x 1024, 125 groups, at 512 rows 36 | 36 | 35; 4096 x 192, 16 groups, 7.8 | - | 8.8).  Its products up to K of 2048 on 8 wavefronts.  us at 256 rows, 128 x 256 | 256 x 256 on 4 | on 8 wavefronts:
-// 50304 x 768 (197 groups) 29 | 30 | 26, x 1600 55 | 49 | 48, x 2048 65 | 59 | 62; 40960 x 768 (160) 28 | 28 | 24; 32000 x 2048
-// (125) 42 | 50 | 50; 128256 x 1024 (501) 77 | 80 | 76, x 2048 151 | 138 | 140; 151936 x 896 (594) 83 | 97 | 89, x 2560 213 |
-// 217 | 222.  At 384, 512 rows: 32000 x 4096 113, 124 | 114, 114; 151936 x 896 117, 149 | 8: 142, 145; 128256 x 4096 383, 490 | 441, 457.
+// beside each other.  Tiles of 256 columns are 2.3 rounds of 151936, 3.9 of two row groups of 128256: past whole rounds they go as halves
+// (gemm_rows_kernel).  us per launch, skinny | 64 x 256 | 128 x 256, ring of 3 | gemm_rows_kernel of 128, 192, 256 rows:
+//                 7 rows          64 rows         128 rows                   192 rows               256 (240) rows       384 rows
+//   151936 x 2560 146 | 142       167 | 150       214 | 178 | 168 | 158      212 | - | 230 | 180    - | - | 233 | 220    306 | - | 326 | 318
+//   128256 x 4096 179 | 191       192 | 189       239 | 224 | 198 | 210      278 | - | 280 | 228    - | - | - | 275      394 | - | 413 | 392
+//   151936 x 2048 123 | 125       137 | 131       173 | 138 | 142 | 136      163 | - | 188 | 150    - | - | 190 | 184    244 | - | 271 | 269
+//   151936 x 896   49 | 45         56 | 49         77 | 58 | 68 | 69          79 | - | 91 | 78       - | - | 94 | 99     117 | - | 131 | 139
+//   50304 x 2048   - | -            - | -          - | 57 | - | 44            - | - | 62 | 50        - | - | 66 | 64      - | - | 102 | 96
+//   32032 x 1184   15 | 16         18 | 16         25 | 21 | 25 | 20          26 | - | 29 | 25       - | - | 36 | -       36 | - | 41 | -
+// From 193 to 256 rows of a product shorter than 2048: 256 rows on 8 wavefronts where its 256-column groups fill one round (129 .. 256) or
+// their last one, 128 else; from 385 to 512 rows for more than 64 groups (32000 x 1024, 125 groups, at 512 rows 36 | 36 | 35; 4096 x 192, 16
+// groups, 7.8 | - | 8.8).  us at 256 rows, 128 x 256 | 256 x 256 on 4 | on 8 wavefronts:
+// 50304 x 768 (197 groups) 29 | 30 | 26, x 1600 55 | 49 | 48; 40960 x 768 (160) 28 | 28 | 24; 128256 x 1024 (501) 77 | 80 | 76;
+// 151936 x 896 (594) 83 | 97 | 89.
 bool launch_gemm_tile_logits(hipStream_t st, RowCtx rc, const bf16_t* x, const bf16_t* Wp, float* logits,
                              const GroupOut& go, int V, int K) {
   const int groups = ceil_div(V >> 5, 8), rows = rc.max_rows;            // 256-column groups
+  TileNorm lm{};
+  lm.go = go;
   if (rows <= 32 && (K >= 3072 || groups < 256)) return false;
 #define LM_LAUNCH(KERNEL, MT, THREADS, ...)                                                                              \
   hipLaunchKernelGGL((KERNEL), dim3(ceil_div(groups, 8) * 8 * ceil_div(ceil_div(rows, 32), MT)), dim3(THREADS), 0, st, rc, \
                      reinterpret_cast<const bf16x8*>(x), reinterpret_cast<const bf16x8*>(Wp), nullptr, logits, nullptr, V, K, __VA_ARGS__)
+#define LM_ROWS(MTW, R)                                                                                                \
+  do {                                                                                                                 \
+    const int units = ceil_div(V >> 5, 4), rg = ceil_div(ceil_div(rows, 32), 2 * MTW), full = rows_full(units, rg);                    \
+    hipLaunchKernelGGL((gemm_rows_kernel<TEPI_LOGITS, 2, MTW, 4, false, 1, R>), dim3(rows_grid(units, full, rg)), dim3(256), 0, st, rc, \
+                       reinterpret_cast<const bf16x8*>(x), reinterpret_cast<const bf16x8*>(Wp), nullptr, logits, nullptr, V, K, lm, full); \
+  } while (0)
 #define LM_64 gemm_tile_dma_kernel<1, 4, 2, 2, 2, 4, TEPI_LOGITS>
 #define LM_128 gemm_tile_dma_kernel<1, 4, 4, 2, 2, 3, TEPI_LOGITS>
 #define LM_256 gemm_tile_dma_kernel<2, 4, 4, 2, 2, 4, TEPI_LOGITS>
+  auto split = [&](int group_rows) { const int units = ceil_div(V >> 5, 4); return 2 * rows_full(units, ceil_div(rows, group_rows)) < units; };
   const bool full = (groups > 128 && groups <= 256) || groups % 256 == 0 || groups % 256 >= 230;
-  const bool tall = (rows > 128 && rows <= 256 && (K >= 3072 || full)) || (rows > 384 && rows <= 512 && groups > 64);
-  if (rows <= 64 || (rows <= 128 && groups < 256)) LM_LAUNCH(LM_64, 2, 256, go);
-  else if (!tall) LM_LAUNCH(LM_128, 4, 256, go);
-  else if (K <= 2048) LM_LAUNCH(LM_256, 8, 512, go);
-  else LM_LAUNCH(TILE_WIDE(TEPI_LOGITS), 8, 256, go, QkvOut{}, BigGrid{});
+  const bool tall = (rows <= 256 && full) || (rows > 384 && rows <= 512 && groups > 64);
+  if (rows <= 64) LM_LAUNCH(LM_64, 2, 256, go);
+  else if (rows <= 128 && (groups < 256 || (K >= 2048 && split(128)))) LM_ROWS(2, 5);
+  else if (rows > 128 && (rows <= 192 || (rows > 256 && rows <= 384 && K >= 2048))) LM_ROWS(3, 4);
+  else if (rows > 128 && K >= 2048 && (rows <= 256 || (tall && K > 2048))) LM_ROWS(4, 4);
+  else if (rows > 128 && tall) LM_LAUNCH(LM_256, 8, 512, go);
+  else LM_LAUNCH(LM_128, 4, 256, go);
 #undef LM_64
 #undef LM_128
 #undef LM_256

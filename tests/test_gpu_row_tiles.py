@@ -95,3 +95,11 @@ def test_a_row_keeps_its_bits_in_large_matrices_of_odd_tile_counts():
 def test_a_row_keeps_its_bits_in_gate_up_of_three_m_tiles(d_ffn, sizes):
     """194 tiles at 96 rows, 153 and 160 (grid order) at 128 rows: a group of three m-tiles, alone or before one of one."""
     check_bits(ai.ModelShape(1, 128, 4, 2, 32, d_ffn, 2080), 5, sizes)
+
+
+@pytest.mark.parametrize("d_model,d_ffn,vocab,sizes", [
+    (2048, 256, 70016, (100, 140, 230, 300)),        # LM head: whole tiles of 256 columns, then halves, by 128, 192 and 256 rows
+    (128, 9728, 2080, (64, 128, 300, 384)),          # gate/up of 152 workgroups a row group: 64 rows; two groups of 128 a unit; 4 stages of k
+    (384, 12288, 2080, (60, 250, 320, 384))])        # 192: one and two row groups of 256, of 384 rows, a ring longer than the k loop
+def test_a_row_keeps_its_bits_in_tiles_by_rounds(d_model, d_ffn, vocab, sizes):
+    check_bits(ai.ModelShape(1, d_model, 2, 1, 64, d_ffn, vocab), 12, sizes)
