@@ -113,8 +113,8 @@ def test_dense_wide_layer_many_rows(name, n_target, n_over):
     Decode launches reached (rocprofv3 kernel trace of this file): qkv and down through
     gemm_mfma_kernel<2,3 / 4,3 / 4,4,EPI_F32,...> with one to four m-groups; the output projection through
     its residual epilogue with one to three m-tiles or pairs of n-tiles; gate/up through
-    gemm_tile_chain_kernel<2,2,3,2,2,3> (192 rows; 300 rows of configuration 4 in two row groups) or, for 300 rows of
-    configuration 3, <2,2,2,2,2,3> in three; the LM head on 128- and 256-row tiles."""
+    gemm_rows_kernel on tiles of 256 rows (192), 128 (300 of configuration 3) or 384 (300 of configuration 4); the LM head
+    on 192-row tiles."""
     base = ai.WORKLOADS[name]
     shape = ai.reduced(base, n_layers=1, vocab=8192).shape
     w = ai.Workload(f"{name}_L1_{n_over}", shape, 37, 7, n_target, n_over, 5, 1.45, 0.2, 3, 5,
