@@ -561,10 +561,14 @@ void forward(april_ctx* c, RowCtx rows, RowCtx srows, const int* gather, double 
   const int nq = Hq * dh, nkv = Hkv * dh, nqkv = nq + 2 * nkv;
   const double e = (double)c->esz;
   if (c->f32_dot && gather == nullptr && forward_f32_pays(rows.max_rows, c->step_max_ctx, nq)) {
+    const SamplerCfg sc = sampler_cfg(c);
+    const bool greedy = (sc.kind == APRIL_SAMPLER_GREEDY || (sc.kind == APRIL_SAMPLER_TOPK && sc.top_k <= 1)) && !c->cfg.debug_logits;
     {
       ProfScope p(c, KC_FORWARD_F32, (double)c->decode_weight_bytes + C * 2.0 * m.n_layers * nkv * e + B * V * 4.0, 0);
       launch_forward_f32(st, rows, c->ds, F32Model{c->d_f32_layers, (const float*)c->tok_emb, c->final_norm, (const float*)c->lm_head,
-                                                   c->rope_cos, c->rope_sin, (float*)c->kv_pool, c->kvl, m.n_layers, d, F, Hq, V, m.rms_eps, 0}, c->logits);
+                                                   c->rope_cos, c->rope_sin, (float*)c->kv_pool, c->kvl, m.n_layers, d, F, Hq, V, m.rms_eps, 0}, c->logits,
+                         c->d_ctrl, greedy, sc.temperature);
+      if (greedy) return;
     }
     ProfScope p(c, KC_SAMPLE, B * V * 4.0, 0);
     launch_sample(st, srows, c->ds, c->d_ctrl, c->logits, V, sampler_cfg(c), c->cfg.debug_logits ? c->dwatch : Watch{}, 1, nullptr, nullptr, nullptr, nullptr);

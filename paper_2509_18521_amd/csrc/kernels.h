@@ -149,6 +149,61 @@ __device__ __forceinline__ void group64_record(const f32x16& a, const f32x16& b,
   }
 }
 
+// --- sampling: what its kernels and the one-launch fp32 pass share --------------
+// Order-preserving map float -> unsigned (larger float <=> larger key); -0 == +0.
+__device__ inline unsigned f2key(float f) {
+  unsigned u = __float_as_uint(f);
+  if (u == 0x80000000u) u = 0u;
+  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+}
+
+// What a sampling row works on, requested at the kernel's start: nothing behind the choice waits for memory again.
+struct RowState {
+  int slot, pos, g, limit, state, forced, group, eos, iter;
+  long long req;
+};
+__device__ inline RowState load_row(const RowCtx& rc, const Slots& s, const Ctrl* ctrl, int r, int update,
+                                    const long long* req_ids, const int* gen_idx) {
+  RowState q{-1, 0, 0, 0, 0, -1, -1, -1, 0, 0};
+  if (update) {
+    q.slot = rc.row_slot[r];
+    q.pos = rc.row_pos[r];
+    q.eos = ctrl->eos_token;
+    q.iter = ctrl->iter;
+    q.g = s.gen[q.slot];
+    q.req = s.req_id[q.slot];
+    q.limit = s.limit[q.slot];
+    q.state = s.state[q.slot];
+    if (s.group != nullptr) q.group = s.group[q.slot];
+    if (s.forced != nullptr) q.forced = s.forced[(size_t)q.slot * s.max_ctx + q.g];
+  } else {
+    // (these may lie in host memory: 2.5 us away, and a scalar load would have every wait for a scalar load wait for it)
+    int at = r;
+    asm volatile("" : "+v"(at));
+    q.req = req_ids[at];
+    q.g = gen_idx[at];
+  }
+  return q;
+}
+// Token to the caller, or appended to its rollout (one thread).
+__device__ inline void finish_row(const Slots& s, Ctrl* ctrl, const RowState& q, int r, int update, int sampled, int tok, int* out_tokens) {
+  if (!update) { out_tokens[r] = sampled; return; }
+  s.tokens[(size_t)q.slot * s.max_ctx + q.pos + 1] = tok;
+  s.gen[q.slot] = q.g + 1;
+  s.kv_len[q.slot] = q.pos + 1;
+  int stt = q.state;
+  if (stt == SLOT_PREFILL) stt = SLOT_LIVE;
+  if (q.g + 1 >= q.limit || tok == q.eos) {
+    stt = SLOT_DONE;
+    s.finish_iter[q.slot] = q.iter;
+    // what the scheduler counts toward N: the rollout, or (instance-level completion,
+    // Section 3.2.3) its group once the last member is complete
+    if (q.group < 0) atomicAdd(&ctrl->finished, 1);
+    else if (atomicSub(&s.grp_left[q.group], 1) == 1) atomicAdd(&ctrl->finished, 1);
+  }
+  s.state[q.slot] = stt;
+}
+
 // --- scheduler / allocator -------------------------------------------------
 // check_only = 1: only the "N complete => stop" test (end of a chunk of iterations).
 // row_cap / ctx_cap: the bounds the host sized this iteration's launches for (live rows, longest
@@ -282,7 +337,8 @@ struct F32Model {
 bool forward_f32_takes(int d, int F, int nq, int nqkv, int vocab);
 bool forward_f32_pays(int rows, int ctx, int nq);
 int forward_f32_ctx(int nq, bool many_rows);      // the longest contexts that it takes
-void launch_forward_f32(hipStream_t st, RowCtx rc, Slots s, F32Model m, float* logits);
+// greedy: the token of every row too, as launch_sample appends it (no logits watched); ctrl is read and counted in then
+void launch_forward_f32(hipStream_t st, RowCtx rc, Slots s, F32Model m, float* logits, Ctrl* ctrl, bool greedy, float temperature);
 void launch_gemm_f32_dot(hipStream_t st, RowCtx rc, const float* x, const float* W, float* out, int N, int K);
 
 // out[m][n] = sum_k x[m][k] W[n][k]; plain row-major W; reference path.

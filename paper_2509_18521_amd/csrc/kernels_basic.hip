@@ -938,7 +938,8 @@ void launch_gemm_f32_dot(hipStream_t st, RowCtx rc, const float* x, const float*
 }
 
 template <int DH>
-__global__ __launch_bounds__(ROW_THREADS) void forward_f32_kernel(RowCtx rc, Slots s, F32Model m, float* logits) {
+__global__ __launch_bounds__(ROW_THREADS) void forward_f32_kernel(RowCtx rc, Slots s, F32Model m, float* logits, Ctrl* ctrl, int greedy,
+                                                                  float temperature) {
   extern __shared__ __align__(16) float lds[];
   const int r = blockIdx.x;
   const int slot = rc.row_slot[r], pos = rc.row_pos[r];
@@ -1018,6 +1019,60 @@ __global__ __launch_bounds__(ROW_THREADS) void forward_f32_kernel(RowCtx rc, Slo
   }
   norm(m.final_norm);
   row_gemv<4, 4>(m.lm_head, h, m.vocab, d, [&](int n, float v) { logits[(size_t)r * m.vocab + n] = v; });
+  if (!greedy) return;
+  // The greedy token and its log-probability, here where the logits are (a launch of its own was 3 of 62 us of an iteration of 24 rows): the choice,
+  // the maximum and the sum of sample_rows_kernel, whose 1024 threads' partial sums a thread takes two of, in the same order.  (Forced
+  tokens come with watched logits, which the sampler's own kernel takes.)
+  __shared__ unsigned red_key[8];
+  __shared__ int red_idx[8], token;
+  __shared__ float red_max[8];
+  __shared__ double red_sum[16];
+  const int V = m.vocab, lane = tid & 63;
+  const float* lg = logits + (size_t)r * V;
+  const RowState q = load_row(rc, s, ctrl, r, 1, nullptr, nullptr);
+  __syncthreads();                                // (the workgroup's own logits, as its keys and values above)
+  unsigned bk = 0u;
+  int bi = 0x7fffffff;
+  float M = -INFINITY;
+  for (int i = tid; i < V; i += ROW_THREADS) {
+    const float v = lg[i];
+    const unsigned k = f2key(v);
+    if (bi == 0x7fffffff || k > bk) { bk = k; bi = i; }        // ascending i: the first maximum stays
+    M = fmaxf(M, v);
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    const unsigned ok = __shfl_xor(bk, off, 64);
+    const int oi = __shfl_xor(bi, off, 64);
+    if (ok > bk || (ok == bk && oi < bi)) { bk = ok; bi = oi; }
+  }
+  M = wave_max_f32(M);
+  if (lane == 0) { red_key[wid] = bk; red_idx[wid] = bi; red_max[wid] = M; }
+  __syncthreads();
+  for (int x = 0; x < 8; ++x) M = fmaxf(M, red_max[x]);
+  if (tid == 0) {
+    for (int x = 1; x < 8; ++x)
+      if (red_key[x] > bk || (red_key[x] == bk && red_idx[x] < bi)) { bk = red_key[x]; bi = red_idx[x]; }
+    token = bi;
+  }
+  if (s.logprob != nullptr) {
+    const float invT = 1.0f / temperature;
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+      double part = 0.0;
+      for (int i = half * ROW_THREADS + tid; i < V; i += 2 * ROW_THREADS) part += (double)__expf((lg[i] - M) * invT);
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) part += __shfl_xor(part, off, 64);
+      if (lane == 0) red_sum[half * 8 + wid] = part;
+    }
+    __syncthreads();
+    if (tid == 0) {
+      double Z = red_sum[0];
+      for (int x = 1; x < 16; ++x) Z += red_sum[x];
+      s.logprob[(size_t)q.slot * s.max_ctx + q.g] = (float)((double)((lg[token] - M) * invT) - log(Z));
+    }
+  }
+  if (tid == 0) finish_row(s, ctrl, q, r, 1, token, token, nullptr);
 }
 static size_t forward_f32_lds(int d, int F, int nq, int nqkv) { return (size_t)(2 * d + (nqkv + nq > 2 * F ? nqkv + nq : 2 * F)); }     // floats
 bool forward_f32_takes(int d, int F, int nq, int nqkv, int vocab) {
@@ -1039,11 +1094,11 @@ bool forward_f32_takes(int d, int F, int nq, int nqkv, int vocab) {
 // 125, 173 / 106, 129, 204.
 int forward_f32_ctx(int nq, bool many_rows) { return (81920 / nq < 1024 ? 81920 / nq : 1024) * (many_rows ? 3 : 1); }
 bool forward_f32_pays(int rows, int ctx, int nq) { return rows <= 256 && ctx <= forward_f32_ctx(nq, rows >= 128); }
-void launch_forward_f32(hipStream_t st, RowCtx rc, Slots s, F32Model m, float* logits) {
+void launch_forward_f32(hipStream_t st, RowCtx rc, Slots s, F32Model m, float* logits, Ctrl* ctrl, bool greedy, float temperature) {
   const int nq = m.n_q_heads * m.kvl.head_dim, nqkv = nq + 2 * m.kvl.n_kv_heads * m.kvl.head_dim;
   m.lds_floats = (int)forward_f32_lds(m.d, m.F, nq, nqkv);
   const size_t lds = ((size_t)m.lds_floats + s.max_blocks) * sizeof(float);
-#define FWD_F32(DH) hipLaunchKernelGGL((forward_f32_kernel<DH>), dim3(rc.max_rows), dim3(ROW_THREADS), lds, st, rc, s, m, logits)
+#define FWD_F32(DH) hipLaunchKernelGGL((forward_f32_kernel<DH>), dim3(rc.max_rows), dim3(ROW_THREADS), lds, st, rc, s, m, logits, ctrl, greedy ? 1 : 0, temperature)
   switch (m.kvl.head_dim) {
     case 32: FWD_F32(32); break;
     case 64: FWD_F32(64); break;

@@ -24,13 +24,6 @@ constexpr int SAMPLE_THREADS = 1024;   // of a workgroup, in both kernels (256 f
 #define MAX_HOT 1024
 #define MAX_CAND 2048
 
-// Order-preserving map float -> unsigned (larger float <=> larger key); -0 == +0.
-__device__ inline unsigned f2key(float f) {
-  unsigned u = __float_as_uint(f);
-  if (u == 0x80000000u) u = 0u;
-  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-}
-
 __device__ inline float key2f(unsigned k) { return __uint_as_float((k & 0x80000000u) ? k & 0x7fffffffu : ~k); }
 
 // Philox4x32-10 (Salmon et al., SC'11): first output word.
@@ -207,34 +200,6 @@ __device__ inline int block_argmax(const float* vals, int n, SampleShared& sh) {
   return sh.choice;
 }
 
-// What a sampling row works on, requested at the kernel's start: nothing behind the choice waits for memory again.
-struct RowState {
-  int slot, pos, g, limit, state, forced, group, eos, iter;
-  long long req;
-};
-__device__ inline RowState load_row(const RowCtx& rc, const Slots& s, const Ctrl* ctrl, int r, int update,
-                                    const long long* req_ids, const int* gen_idx) {
-  RowState q{-1, 0, 0, 0, 0, -1, -1, -1, 0, 0};
-  if (update) {
-    q.slot = rc.row_slot[r];
-    q.pos = rc.row_pos[r];
-    q.eos = ctrl->eos_token;
-    q.iter = ctrl->iter;
-    q.g = s.gen[q.slot];
-    q.req = s.req_id[q.slot];
-    q.limit = s.limit[q.slot];
-    q.state = s.state[q.slot];
-    if (s.group != nullptr) q.group = s.group[q.slot];
-    if (s.forced != nullptr) q.forced = s.forced[(size_t)q.slot * s.max_ctx + q.g];
-  } else {
-    // (these may lie in host memory: 2.5 us away, and a scalar load would have every wait for a scalar load wait for it)
-    int at = r;
-    asm volatile("" : "+v"(at));
-    q.req = req_ids[at];
-    q.g = gen_idx[at];
-  }
-  return q;
-}
 // rc.ctl may be null (the caller states the rows)
 __device__ inline int sampling_rows(const RowCtx& rc) { return rc.ctl != nullptr ? rows_or_zero(rc) : rc.max_rows; }
 
@@ -263,25 +228,6 @@ __device__ inline void capture_row(const Watch& w, const Ctrl* ctrl, const RowSt
     if (tid == 0) { w.sampled[row] = sampled; w.filled[row] = 1; }
   }
 }
-// Token to the caller, or appended to its rollout (one thread).
-__device__ inline void finish_row(const Slots& s, Ctrl* ctrl, const RowState& q, int r, int update, int sampled, int tok, int* out_tokens) {
-  if (!update) { out_tokens[r] = sampled; return; }
-  s.tokens[(size_t)q.slot * s.max_ctx + q.pos + 1] = tok;
-  s.gen[q.slot] = q.g + 1;
-  s.kv_len[q.slot] = q.pos + 1;
-  int stt = q.state;
-  if (stt == SLOT_PREFILL) stt = SLOT_LIVE;
-  if (q.g + 1 >= q.limit || tok == q.eos) {
-    stt = SLOT_DONE;
-    s.finish_iter[q.slot] = q.iter;
-    // what the scheduler counts toward N: the rollout, or (instance-level completion,
-    // Section 3.2.3) its group once the last member is complete
-    if (q.group < 0) atomicAdd(&ctrl->finished, 1);
-    else if (atomicSub(&s.grp_left[q.group], 1) == 1) atomicAdd(&ctrl->finished, 1);
-  }
-  s.state[q.slot] = stt;
-}
-
 // Radix select of the row's top k into the candidate list (all threads call).
 __device__ inline void topk_whole_row(const float* lg, int V, int k, SampleShared& sh) {
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;

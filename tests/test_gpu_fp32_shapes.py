@@ -164,3 +164,29 @@ def test_small_models_bits_do_not_depend_on_where_decode_turns_to_separate_launc
             ap.april_destroy(ctx)
     for at, got in rows.items():
         assert all(np.array_equal(got[0], x) for x in got[1:]), at
+
+
+@pytest.mark.parametrize("vocab,d_model,temperature", [(1, 8, 1.0), (63, 40, 0.7), (512, 128, 1.0), (1030, 64, 1.3)])
+def test_greedy_in_the_decode_pass_equals_the_sampler(vocab, d_model, temperature):
+    """A greedy decode pass of a small fp32 model picks the token itself, a context that watches logits leaves that to the sampler's
+    kernel: same tokens (ties included: the upper half of the vocabulary repeats the lower) and log-probabilities, bit for bit."""
+    import paper_2509_18521_amd as ap
+    shape = ai.ModelShape(2, d_model, 2, 1, 32, 36, vocab, dtype=ai.DTYPE_FP32)
+    w = ai.Workload("greedy", shape, 1, 20, 6, 9, 30, 0.0, 0.1, 3, 30, ai.SAMPLER_GREEDY, 0, 1, 3)
+    weights = ai.make_weights(shape, w.seed)
+    weights["lm_head"][vocab - vocab // 2:] = weights["lm_head"][:vocab // 2]
+    rng = np.random.default_rng(vocab)
+    reqs = [dict(request_id=i, tokens=rng.integers(0, vocab, 1 + 2 * i, dtype=np.int32), forced_len=3 + 3 * i) for i in range(9)]
+    seen = []
+    for debug in (False, True):
+        ctx = make_engine(w, weights, debug=debug, temperature=temperature, logprobs=True)
+        try:
+            res = ap.april_rollout_step(ctx, reqs, 6, 9, 30)
+            ap.april_resume(ctx, res.buffer)
+            res2 = ap.april_rollout_step(ctx, [], 3, 3, 30)
+            seen.append((list(res.request_id) + list(res2.request_id), np.concatenate(list(res.tokens) + list(res2.tokens)),
+                         np.concatenate(list(res.logprobs) + list(res2.logprobs))))
+        finally:
+            ap.april_destroy(ctx)
+    assert seen[0][0] == seen[1][0] and np.array_equal(seen[0][1], seen[1][1]) and np.array_equal(seen[0][2], seen[1][2])
+    assert np.isfinite(seen[0][2]).all() and seen[0][1].min() >= 0 and seen[0][1].max() < vocab
