@@ -1022,7 +1022,7 @@ __global__ __launch_bounds__(ROW_THREADS) void forward_f32_kernel(RowCtx rc, Slo
   if (!greedy) return;
   // The greedy token and its log-probability, here where the logits are (a launch of its own was 3 of 62 us of an iteration of 24 rows): the choice,
   // the maximum and the sum of sample_rows_kernel, whose 1024 threads' partial sums a thread takes two of, in the same order.  (Forced
-  tokens come with watched logits, which the sampler's own kernel takes.)
+  // tokens come with watched logits, which the sampler's own kernel takes.)
   __shared__ unsigned red_key[8];
   __shared__ int red_idx[8], token;
   __shared__ float red_max[8];
