@@ -215,6 +215,10 @@ __device__ inline void wait_lds() {             // until no LDS operation is out
   asm volatile("" ::: "memory");
 }
 
+// Between the halves of an exchange through LDS inside one wavefront: the hardware keeps a wavefront's LDS operations in order, and this
+// keeps the compiler from moving one lane's loads over another lane's stores, which it takes for unrelated.
+__device__ inline void wave_lds_order() { asm volatile("" ::: "memory"); }
+
 // The stage fragments are copied global -> LDS by the memory pipeline itself
 // (global_load_lds_dwordx4: each lane's 16 bytes land at consecutive LDS addresses, which is
 // exactly the fragment layout), through a ring of R stage buffers.  Nothing is staged in
@@ -619,12 +623,14 @@ __device__ __forceinline__ void big_body(const RowCtx& rc, const bf16x8* __restr
         for (int q = 0; q < 4; ++q)
           *reinterpret_cast<f32x4*>(buf + (lane & 31) * STRIDE + i * 32 + 8 * q + ((lane >> 5) << 2)) =
               f32x4{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+      wave_lds_order();
 #pragma unroll
       for (int p = 0; p < PIECES; ++p) {
         const int m = mw + j * 32 + p * RPI;
         const f32x4 r = v[j & 1][p] + *reinterpret_cast<const f32x4*>(buf + (row0 + p * RPI) * STRIDE + c4);
         if (m < rows && col_ok) *reinterpret_cast<f32x4*>(col + (size_t)m * N) = r;
       }
+      wave_lds_order();
       if (j + 2 < MTW) load(j + 2);
     }
   } else {
