@@ -99,6 +99,8 @@ def test_a_row_keeps_its_bits_in_gate_up_of_three_m_tiles(d_ffn, sizes):
 
 @pytest.mark.parametrize("d_model,d_ffn,vocab,sizes", [
     (2048, 256, 70016, (100, 140, 230, 300)),        # LM head: whole tiles of 256 columns, then halves, by 128, 192 and 256 rows
+    (2048, 256, 50304, (100, 190, 250, 300)),        # all whole, the last one past the end: 393 columns of 128 by one and two row groups
+    (2176, 128, 32032, (400, 512)),                  # 385 to 512 rows of a product longer than 2048: two row groups of 256
     (128, 9728, 2080, (64, 128, 300, 384)),          # gate/up of 152 workgroups a row group: 64 rows; two groups of 128 a unit; 4 stages of k
     (384, 12288, 2080, (60, 250, 320, 384))])        # 192: one and two row groups of 256, of 384 rows, a ring longer than the k loop
 def test_a_row_keeps_its_bits_in_tiles_by_rounds(d_model, d_ffn, vocab, sizes):
