@@ -425,12 +425,17 @@ __device__ __forceinline__ void tile_dma_body(RowCtx rc, const bf16x8* __restric
 // 1295 / 1250, of 4864 x 896 (14500 rows) 246 / 233; output projections 2560 x 4096 437 / 363, x 9728 776 / 698 (2.5 rounds of tiles),
 // 4096 x 14336 (12800 rows) 1375 / 1250, 896 x 4864 (14500) 140 / 122.
 constexpr int BIG_R = 4, BIG_BK = 2;
-// The workgroups of a launch: `full` tiles of 256 x 256, then tiles of 256 x 128: the two halves of the last `split` tiles, and the
-// `my` pieces of a last column of 128 where the columns are an odd number of those.
+// The workgroups of a launch: `full` tiles of 256 x 256, then tiles of 256 x 128: the two halves of the last `split` tiles, 8 ids apart, and
+// the `my` pieces of a last column of 128 where the columns are an odd number of those.  Halves come in sixteens; the ids that a last, partial
+// sixteen leaves over go to pieces first, so that 256 halves and pieces are 32 on every XCD.  (With those ids empty and all pieces
+// behind, up to 256 of them were 33 on some XCDs, a second round.  us in a padded grid of whole tiles | so | as here: 896 x 4864 at 8900 rows
+// 118 | 124 | 78, 640 x 2048 at 12500 rows 53 | 61 | 39, SwiGLU of 960 x 1664 at 4300 rows 40 | 46 | 32.)
 struct BigGrid {
   int nx, my;                  // tiles of 256 columns, of 256 rows
   int full, split, odd;
-  __host__ __device__ int halves() const { return ((split + 7) & ~7) * 2 + (odd ? my : 0); }
+  __host__ __device__ int pairs() const { return ((split + 7) & ~7) * 2; }       // ids of the halves
+  __host__ __device__ int spare() const { return pairs() - 2 * split; }          // those among them that are left over
+  __host__ __device__ int halves() const { return pairs() + (odd && my > spare() ? my - spare() : 0); }
 };
 // The order of the tiles: groups of 6 row tiles, inside a group column after column; where the columns are a multiple of 8, row after row.
 __device__ __forceinline__ int2 big_tile(const BigGrid& g, int t) {
@@ -656,17 +661,17 @@ __global__ __launch_bounds__(256, 1) void gemm_big_kernel(RowCtx rc, const bf16x
     if (at.y * 256 >= rows) return;
     big_body<EPI, DH, 4, 4>(rc, x, w0, w1, out, act, N, K, tn, qo, lds, rows, at.x * 2, at.y * 8);
   } else {
-    int h = id - g.full, u0, m0;
-    const int pairs = ((g.split + 7) & ~7) * 2;
-    if (h < pairs) {             // the halves of a tile 8 ids apart: same XCD
-      const int t = (h >> 4) * 8 + (h & 7);
-      if (t >= g.split) return;
+    const int h = id - g.full, t = (h >> 4) * 8 + (h & 7), half = (h >> 3) & 1;
+    int u0, m0;
+    if (t < g.split) {           // the halves of a tile 8 ids apart: same XCD
       const int2 at = big_tile(g, g.full + t);
-      u0 = at.x * 2 + ((h >> 3) & 1);
+      u0 = at.x * 2 + half;
       m0 = at.y * 8;
     } else {
+      const int piece = h < g.pairs() ? t - g.split + half * (g.spare() >> 1) : h - g.pairs() + g.spare();
+      if (!g.odd || piece >= g.my) return;
       u0 = 2 * g.nx;
-      m0 = (h - pairs) * 8;
+      m0 = piece * 8;
     }
     if (m0 * 32 >= rows) return;
     big_body<EPI, DH, 4, 2>(rc, x, w0, w1, out, act, N, K, tn, qo, lds, rows, u0, m0);

@@ -18,7 +18,8 @@ def _need_gpu():
 # 75 prompts are 2550 rows (10 row tiles), 265 are 9010 (36): all tiles as halves, or those past the first 256
 @pytest.mark.parametrize("d_model,d_ffn,n_q,n_kv,head_dim", [
     (2176, 1120, 15, 1, 128), (1056, 2112, 30, 2, 64), (416, 2080, 60, 4, 32), (128, 224, 2, 1, 32),
-    (928, 256, 2, 1, 64)])           # 29 column tiles: at 36 row tiles whole tiles of 256, whose last ends in the middle of a wavefront
+    (928, 256, 2, 1, 64),            # 29 column tiles: at 36 row tiles whole tiles of 256, whose last ends in the middle of a wavefront
+    (896, 448, 5, 1, 128)])          # 7 units everywhere: the halves' last sixteen is partial, pieces of the odd column fill it
 def test_halves_keep_the_bits(d_model, d_ffn, n_q, n_kv, head_dim):
     import paper_2509_18521_amd as ap
     shape = ai.ModelShape(2, d_model, n_q, n_kv, head_dim, d_ffn, 512)
