@@ -926,12 +926,17 @@ int april_init(const april_model_cfg* cfg, const april_tensor* weights, int32_t 
   c->fuse_norm = !(fn && !strcmp(fn, "0"));
   const char* fd = getenv("APRIL_FUSE_DOWN");    // off by default: measured 5 % slower end to end on configuration 2
   c->fuse_down = fd && !strcmp(fd, "1");
-  // Decode gate/up on the LDS-tiled kernel from this row bound, where its workgroups (64 features each) are about one per compute unit or
-  // many.  us per launch, skinny / tiled: 9728 features of 2560 at 32, 64, 96, 128 rows 25 / 28, 31 / 28, 33 / 32, 35 / 33; 14336 of 4096 at
-  // 32, 64, 96 rows 45 / 47, 52 / 47, 67 / 52; 8960 of 1536 at 64, 128 19 / 18, 23 / 21; 11008 of 4096 at 64 47 / 42; 8192 of 3072 at 64, 96 22 / 30,
-  // 26 / 29; 4864 of 896 at 128, 192 9 / 12, 10 / 12; 18944 of 3584 at 64 63 / 68; 28672 of 8192 at 64 201 / 176.
+  // Decode gate/up on the LDS-tiled kernel from this row bound: bands of d_ffn (its workgroups take 64 features), whose edges are sizes that were
+  // measured.  us per launch, skinny / tiled:
+  //   up to one workgroup per compute unit, from 64 rows: 9728 x 2560 at 32, 64, 96, 128 rows 25 / 26, 31 / 27, 33 / 31, 37 / 36; 14336 x 4096 at 32, 64, 96
+  //     45 / 48, 52 / 47, 67 / 54; 8960 x 1536 at 64, 128 19 / 18, 23 / 22; 11008 x 4096 at 64 47 / 42; 16384 x 2048 27 / 28, at 96 37 / 30;
+  //   of products shorter than 1280, where filling the ring and the epilogue are most of a launch, from 96 or 128: 12288 x 512 at 64, 128 8.8 / 10.5,
+  //     13.0 / 11.9, x 1024 13.6 / 14.5, 18.0 / 16.7, x 1280 at 64 17.2 / 17.1; 8960 x 768 at 64, 96, 128 11.0 / 12.2, 12.3 / 13.7, 14.4 / 14.0;
+  //   half a chip of workgroups, from 128: 8192 x 3072 at 96, 128, 192 26 / 34, 34 / 39, 49 / 37; below never: 4864 x 896 at 128, 256 10 / 14, 13 / 15;
+  //   more than one per unit, from 96: 18944 x 3584 at 64, 96, 192, 256 63 / 69, 78 / 77, 102 / 110, 123 / 118; 16896 x 2048 at 96, 192 42 / 43, 57 / 67;
+  //   many, from 64: 28672 x 8192 at 64, 128 195 / 173, 262 / 210.
   const int ff = g.d_ffn;
-  c->tile_decode_rows = ff >= 24576 ? 64 : ff > 16384 ? 96 : ff >= 8960 ? 64 : ff >= 8192 ? 128 : 0;
+  c->tile_decode_rows = ff >= 24576 ? 64 : ff > 16384 ? 96 : ff >= 8960 && d >= 1280 ? 64 : ff >= 12288 ? 96 : ff >= 8192 ? 128 : 0;
   if (const char* td = getenv("APRIL_TILE_DECODE_ROWS")) c->tile_decode_rows = atoi(td);   // debug switch
   if (const char* mt = getenv("APRIL_MOE_TALL_ROWS")) c->moe_tall_rows = atoi(mt);          // debug switch
   if (const char* mt = getenv("APRIL_MOE_TILE")) c->moe_tile = strcmp(mt, "0") != 0;

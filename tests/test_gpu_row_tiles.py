@@ -101,7 +101,9 @@ def test_a_row_keeps_its_bits_in_gate_up_of_three_m_tiles(d_ffn, sizes):
     (2048, 256, 70016, (100, 140, 230, 300)),        # LM head: whole tiles of 256 columns, then halves, by 128, 192 and 256 rows
     (2048, 256, 50304, (100, 190, 250, 300)),        # all whole, the last one past the end: 393 columns of 128 by one and two row groups
     (2176, 128, 32032, (400, 512)),                  # 385 to 512 rows of a product longer than 2048: two row groups of 256
-    (128, 9728, 2080, (64, 128, 300, 384)),          # gate/up of 152 workgroups a row group: 64 rows; two groups of 128 a unit; 4 stages of k
-    (384, 12288, 2080, (60, 250, 320, 384))])        # 192: one and two row groups of 256, of 384 rows, a ring longer than the k loop
+    (128, 9728, 2080, (64, 128, 300, 384)),          # gate/up of 152 workgroups a row group: two groups of 128 a unit; 4 stages of k, less than the ring
+    (384, 12288, 2080, (60, 250, 320, 384)),         # 192: one and two row groups of 256, of 384 rows
+    (1280, 9728, 2080, (40, 64, 70, 96)),            # the shortest product that turns to it at 64 rows (64-row tiles, then 128)
+    (1152, 9728, 2080, (64, 90, 128))])              # the next shorter one, at 128
 def test_a_row_keeps_its_bits_in_tiles_by_rounds(d_model, d_ffn, vocab, sizes):
     check_bits(ai.ModelShape(1, d_model, 2, 1, 64, d_ffn, vocab), 12, sizes)
