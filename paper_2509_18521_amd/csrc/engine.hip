@@ -4,6 +4,7 @@
 // buffering continuations, prioritized resumption).
 #include <algorithm>
 #include <chrono>
+#include <cmath>
 #include <cstdarg>
 #include <cstdio>
 #include <cstdlib>
@@ -536,24 +537,36 @@ SamplerCfg sampler_cfg(const april_ctx* c) {
   return SamplerCfg{c->cfg.sampler, c->cfg.top_k, T, (unsigned long long)c->cfg.seed, tp};
 }
 
+// Prefill: behind the last layer's keys and values nothing reads a row but the sequences' last ones, which are sampled from.  Those
+// alone go on, packed: one layer of the model then costs a pass its norm and its key / value projection.  (The same kernels and
+// chains, so the same bits.)  Steps through few layers, all rows in the last layer / as here: two of 4096 x 14336, 7 prompts
+// of 4500-8000 tokens, 96 tokens each 90.3 / 73.6 ms; three of 2560 x 9728, 21 prompts of 1-1999 tokens 16.5 / 12.9 ms; in a model
+// of 24 or 36 layers it is that share of the prefill.
+// It takes two more launches (the sampling rows' norm and queries, 5 to 30 us with few to 128 sequences), so the spared rows must be enough for the
+// multiply-adds of a row there.  us of a prefill of two or three layers, all rows / the sampling rows; millions of multiply-adds a row:
+//   210 (4096 x 14336): 1 x 97 tokens 568 / 582, 1 x 161 702 / 655; 96 (2560 x 9728): 1 x 97 449 / 456, 1 x 161 491 / 483, 16 x 11 535 / 538
+//   43 (2048 x 5632): 1 x 161 477 / 476, 16 x 11 512 / 528, 1 x 260 587 / 552, 16 x 21 615 / 594
+//   15 (896 x 4864): 1 x 500 642 / 649, 1 x 650 764 / 753; 11 (1024 x 2816): 1 x 500 303 / 308, 1 x 650 349 / 336, 128 x 4 757 / 768, 128 x 8 806 / 795
+//   2.7 (512 x 1408): 64 x 11 466 / 476, 128 x 8 706 / 717, 1 x 1300 342 / 333, 64 x 33 520 / 514
+//   0.7 (256 x 704): 128 x 16 800 / 822, 64 x 33 589 / 593, 1 x 2090 601 / 592; 0.2 (128 x 352): 64 x 33 452 / 467, 128 x 16 689 / 711, 16 x 300 327 / 320
+// Routed experts: fewer rows read fewer experts too.  128 of 9.4 MB, 8 a row: 1 x 9 524 / 490, 1 x 33 703 / 584, 16 x 3 796 / 755, but 64 x 3, where 64 rows
+// hit all but two, 1018 / 1039; 64 of 3.1 MB, 4 a row: 1 x 9, 17, 33 299, 302, 318 / 307, 309, 311; 16 x 3 400 / 404.
+static bool last_layer_cut_pays(const april_ctx* c, int rows, int sampling) {
+  const ModelDims& m = c->dm;
+  if (c->moe) {
+    // the experts that the spared rows alone would read: one of E is left out by a row with 1 - k / E
+    auto hit = [&](int n) { return c->n_experts * (1.0 - std::pow(1.0 - (double)c->top_k_experts / c->n_experts, n)); };
+    if ((hit(rows) - hit(sampling)) * (double)c->expert_bytes >= 128e6) return true;
+  }
+  const double per_row = (double)m.d_model * (2.0 * m.n_q_heads * m.head_dim + 3.0 * (c->moe ? c->top_k_experts * c->d_expert : m.d_ffn));
+  return rows - sampling >= (per_row >= 80e6 ? 160 : per_row >= 30e6 ? 256 : per_row >= 8e6 ? 512 : per_row >= 2e6 ? 1024 : per_row >= 5e5 ? 2048 : 4096);
+}
+
 // ---- forward pass --------------------------------------------------------------
 // rows: the tokens fed; srows: the rows that are sampled (decode: the same rows;
 // prefill: the last token of each sequence, `gather` maps them into `rows`).
 // B / C: host estimates of live rows and summed context, used only for the
 // algorithmic-byte bookkeeping of profiled launches.
-// Prefill: behind the last layer's keys and values nothing reads a row but the sequences' last ones, which are sampled from.  Those
-// alone go on, packed: one layer of the model then costs a pass its norm and its key / value projection.  (The same kernels and
-// chains, so the same bits.)  Steps through few layers, all rows in the last layer / as here: two of 4096 x 14336, 7 prompts
-// of 4500-8000 tokens, 96 tokens each 90.3 / 73.6 ms; three of 2560 x 9728, 21 prompts of 1-1999 tokens 16.5 / 12.9 ms; in a model
-// of 24 or 36 layers it is that share of the prefill.  It takes two more launches (the sampling rows' norm and queries): one
-// prompt of 40, 250, 400, 600 tokens of 896 x 4864 332, 356, 379, 426 / 346, 366, 378, 405 us, of 40, 130, 160, 250 of 2560 x 9728 566, 623, 628,
-// 720 / 597, 633, 618, 679, of 40, 100, 160, 250 of 4096 x 14336 712, 725, 878, 898 / 731, 745, 828, 840.  Routed experts read fewer
-// experts for fewer rows: 10, 20, 40, 250 tokens 660, 790, 845, 937 / 611, 673, 711, 771, 40 prompts of 3 tokens 1114 / 1108.
-static bool last_layer_cut_pays(int rows, int sampling, int d_model, bool moe) {
-  const int spared = rows - sampling;
-  return moe ? spared >= 8 && rows >= 3 * sampling : spared >= (d_model >= 2048 ? 160 : 384);
-}
-
 void forward(april_ctx* c, RowCtx rows, RowCtx srows, const int* gather, double B, double C) {
   const ModelDims& m = c->dm;
   hipStream_t st = c->stream;
@@ -619,7 +632,7 @@ void forward(april_ctx* c, RowCtx rows, RowCtx srows, const int* gather, double 
     bf16_t* q16 = reinterpret_cast<bf16_t*>(c->q_rot);
     const bool pf_attn = c->attn_mfma && gather != nullptr && c->prefill_tiled;
     bool roped = false;
-    if (tile && pf_attn && l + 1 == m.n_layers && last_layer_cut_pays(rows.max_rows, srows.max_rows, d, c->moe)) {
+    if (tile && pf_attn && l + 1 == m.n_layers && last_layer_cut_pays(c, rows.max_rows, srows.max_rows)) {
       // Behind the last layer's keys and values only the sampling rows go on: their queries, then everything, on rows
       // packed together.  (proj, which no prefill product writes, takes their residual stream; hf their normed rows until the final norm.)
       bf16_t* hl = (bf16_t*)c->hf;
