@@ -227,15 +227,10 @@ __device__ inline void wave_lds_order() { asm volatile("" ::: "memory"); }
 // "at most (R - 2) stages still outstanding" means stage s has landed; the barrier that
 // follows makes that true for every wavefront's share and also says everyone has finished
 // reading the buffer that the next copies overwrite.  Requires K % (16 * BK) == 0.
-//
-// CHAIN (decode with many rows): the skinny decode kernel sums k in four quarters (its four
-// wavefronts), each quarter its own accumulator chain, and adds them as ((q0 + q1) + q2) + q3.
-// Here one wavefront walks all of k, so it closes a chain at every quarter boundary and adds
-// it to a second accumulator set in that order: every output element gets the same bits from
-// either kernel, and the choice between them can follow the row count.  The quarter
-// boundaries must fall on stage boundaries (K % (64 * BK) == 0).
-struct TileNorm {              // RMSNorm folded into the SwiGLU epilogue (CHAIN only)
-  const float* ssq;            // [n_ssq][ssq_stride] per-row sums of squares of 32-column slabs; nullptr = none
+
+// What the epilogues of gemm_rows_kernel need beside the results.
+struct TileNorm {
+  const float* ssq;            // gate/up (CHAIN): RMSNorm folded in, [n_ssq][ssq_stride] per-row sums of squares of 32-column slabs; nullptr = none
   int ssq_stride, n_ssq;
   float inv_d, eps;
   GroupOut go;                 // LM head: group records
@@ -267,7 +262,7 @@ __device__ __forceinline__ int2 moe_tile_of_block(const TileMoe& mo, int tiles) 
   return make_int2(in % tiles, ((j / per) * 8 + xcd) * mo.near + in / tiles);
 }
 
-// (weight tile group, row group) of a workgroup.  NEAR (LM head, decode gate/up): a 1-D grid with the row groups
+// (weight tile group, row group) of a workgroup.  NEAR (LM head): a 1-D grid with the row groups
 // of one weight tile group 8 ids apart - same XCD, same moment, one HBM read instead of one per row group.
 // Else x = weight tile group, y = row group.
 template <bool NEAR>
@@ -443,7 +438,14 @@ __device__ __forceinline__ int2 big_tile(const BigGrid& g, int t) {
   return make_int2(col, grp * high + in - col * h);
 }
 
-// One tile of 256 rows x NTW * 64 columns.  u0: its first column in units of 128 (SwiGLU: of 64 features).
+// One tile of WGM * MTW * 32 rows x NTW * 64 columns.  u0: its first column in units of 128 (SwiGLU: of 64 features).
+//
+// CHAIN (decode with many rows): the skinny decode kernel sums k in four quarters (its four
+// wavefronts), each quarter its own accumulator chain, and adds them as ((q0 + q1) + q2) + q3.
+// Here one wavefront walks all of k, so it closes a chain at every quarter boundary and adds
+// it to a second accumulator set in that order: every output element gets the same bits from
+// either kernel, and the choice between them can follow the row count.  The quarter
+// boundaries must fall on stage boundaries (K % 128 == 0).
 template <int EPI, int DH, int MTW, int NTW, bool CHAIN = false, int R = BIG_R, int WGM = 2>
 __device__ __forceinline__ void big_body(const RowCtx& rc, const bf16x8* __restrict__ x, const bf16x8* __restrict__ w0,
                                          const bf16x8* __restrict__ w1, float* __restrict__ out, bf16_t* __restrict__ act,
@@ -488,7 +490,8 @@ __device__ __forceinline__ void big_body(const RowCtx& rc, const bf16x8* __restr
 #pragma unroll
     for (int j = 0; j < MTW; ++j) acc[i][j] = f32x16{};
   // Folded norm: 1/rms of the workgroup's rows, summed in the skinny kernel's order (wavefront w of that kernel adds the slabs w, w + 4, ...;
-  // then ((s0 + s1) + s2) + s3).  The first 64 slabs are requested ahead of the ring's copies, so that the sum does not wait for those.
+  // then ((s0 + s1) + s2) + s3).  The first 64 slabs (K up to 2048) are requested ahead of the ring's copies, so that their sum does not wait for
+  // those; the others (16 more at 2560, 64 at 4096) come behind the copies and wait for all of them.  Threads beyond the rows repeat the last row.
   constexpr int SLABS = 64;
   float* const scale_lds = reinterpret_cast<float*>(&lds[R - 1][0][0][0]);      // (no copies go there before stage 0 is under way)
   const bool scaled = CHAIN && EPI == TEPI_SWIGLU && tn.ssq != nullptr;
@@ -903,19 +906,27 @@ bool launch_gemm_tile_swiglu_chain(hipStream_t st, RowCtx rc, const bf16_t* x, c
 // the one to use.
 // The head is read once (from HBM: its bound up to about 200 rows) and every row group's workgroups run
 // beside each other.  Tiles of 256 columns are 2.3 rounds of 151936, 3.9 of two row groups of 128256: past whole rounds they go as halves
-// (gemm_rows_kernel).  us per launch, skinny | 64 x 256 | 128 x 256, ring of 3 | gemm_rows_kernel of 128, 192, 256 rows:
-//                 7 rows          64 rows         128 rows                   192 rows               256 (240) rows       384 rows
-//   151936 x 2560 146 | 142       167 | 150       214 | 178 | 168 | 158      212 | - | 230 | 180    - | - | 233 | 220    306 | - | 326 | 318
-//   128256 x 4096 179 | 191       192 | 189       239 | 224 | 198 | 210      278 | - | 280 | 228    - | - | - | 275      394 | - | 413 | 392
-//   151936 x 2048 123 | 125       137 | 131       173 | 138 | 142 | 136      163 | - | 188 | 150    - | - | 190 | 184    244 | - | 271 | 269
-//   151936 x 896   49 | 45         56 | 49         77 | 58 | 68 | 69          79 | - | 91 | 78       - | - | 94 | 99     117 | - | 131 | 139
-//   50304 x 2048   - | -            - | -          - | 57 | - | 44            - | - | 62 | 50        - | - | 66 | 64      - | - | 102 | 96
-//   32032 x 1184   15 | 16         18 | 16         25 | 21 | 25 | 20          26 | - | 29 | 25       - | - | 36 | -       36 | - | 41 | -
-// From 193 to 256 rows of a product shorter than 2048: 256 rows on 8 wavefronts where its 256-column groups fill one round (129 .. 256) or
-// their last one, 128 else; from 385 to 512 rows for more than 64 groups (32000 x 1024, 125 groups, at 512 rows 36 | 36 | 35; 4096 x 192, 16
-// groups, 7.8 | - | 8.8).  us at 256 rows, 128 x 256 | 256 x 256 on 4 | on 8 wavefronts:
-// 50304 x 768 (197 groups) 29 | 30 | 26, x 1600 55 | 49 | 48; 40960 x 768 (160) 28 | 28 | 24; 128256 x 1024 (501) 77 | 80 | 76;
-// 151936 x 896 (594) 83 | 97 | 89.
+// (gemm_rows_kernel).  us per launch, skinny | 64 x 256 | 128 x 256, ring of 3 | 256 x 256 on 8 wavefronts | gemm_rows_kernel of 128 | 192 | 256 rows, all
+// measured together with the weights read from HBM; * what the rule takes:
+//   151936 x 2560   7 rows 142 | 143* | 154 | 223 | 145 | 161 | 200      64   159 | 153* | 162 | 225 | 150 | 167 | 204     128  195 | 185 | 167 | 223 | 158* | 172 | 207
+//                 192      321 | 233 | 222 | 228 | 228 | 183* | 211     256   355 | 288 | 228 | 229 | 236 | 298 | 216*    384  518 | 392 | 311 | 395 | 334 | 306* | 380
+//   128256 x 4096   7      189* | 191 | 199 | 265 | 193 | 203 | 251      64   201 | 195* | 200 | 270 | 196 | 209 | 259     128  239 | 239 | 204* | 269 | 198 | 214 | 260
+//                 192      424 | 303 | 282 | 275 | 286 | 221* | 266     256   464 | 370 | 283 | 276 | 294 | 381 | 271*    384  693 | 510 | 396 | 506 | 410 | 388* | 479
+//   151936 x 2048   7      127 | 126* | 137 | 183 | 130 | 144 | 163      64   140 | 131* | 139 | 183 | 131 | 143 | 169     128  160 | 145 | 142 | 181 | 136* | 146 | 171
+//                 192      262 | 179 | 182 | 186 | 185 | 152* | 175     256   289 | 228 | 185 | 188 | 193 | 247 | 178*    384  423 | 313 | 256 | 322 | 270 | 247* | 317
+//   151936 x 896    7       58 | 56* | 62 | 94 | 65 | 76 | 93            64    64 | 60* | 63 | 93 | 67 | 74 | 90           128   79 | 71 | 67* | 92 | 69 | 76 | 91
+//                 192      111 | 87 | 86 | 96 | 100 | 78* | 93          256   129 | 111 | 91* | 96 | 105 | 130 | 95       384  174 | 151 | 123* | 156 | 145 | 135 | 170
+//   50304 x 2048    7       41* | 43 | 45 | 62 | 46 | 50 | 62            64    45 | 43* | 46 | 59 | 47 | 50 | 61           128   59 | 58 | 48 | 59 | 47* | 52 | 62
+//                 192       78 | 73 | 66 | 63 | 71 | 55* | 63           256    91 | 88 | 70 | 63 | 75 | 89 | 59*          384  124 | 107 | 100 | 114 | 98 | 92* | 113
+//   32032 x 1184    7       21* | 22 | 28 | 35 | 18 | 25 | 28            64    25 | 24* | 28 | 35 | 19 | 24 | 27           128   33 | 24 | 30 | 35 | 20* | 25 | 28
+//                 192       30 | 34 | 29 | 34 | 29 | 26* | 28           256    33 | 33 | 30* | 35 | 30 | 34 | 30          384   50 | 44 | 41* | 40 | 48 | 36 | 44
+//   50304 x 768     7       17* | 18 | 21 | 28 | 22 | 27 | 31            64    20 | 18* | 22 | 28 | 22 | 26 | 32           128   26 | 26 | 23 | 28 | 24* | 27 | 33
+//                 192       34 | 32 | 31 | 29 | 36 | 28* | 34           256    39 | 39 | 33 | 30* | 38 | 46 | 35          384   56 | 48 | 48* | 52 | 49 | 48 | 60
+// The skinny kernel reads the weights again for every 4 m-tiles, a grid apart: beyond 128 rows it is slower everywhere.  From 193 to 256 rows of a
+// product shorter than 2048: 256 rows on 8 wavefronts where its 256-column groups fill one round (129 .. 256) or their last one, else 128 (128256 x 1024, 501
+// groups, at 256 rows 81 | 82; 40960 x 768, 160 groups, 31 | 28; 50304 x 1600, 197 groups, 62 | 53); from 385 to 512 rows for more than 64 groups
+// (32000 x 1024, 125 groups, at 512 rows 41 | 39; 4096 x 192, 16 groups, 9.7 | 11.9).  Where another tile is faster than the rule's, it is by 13 % at
+// the most (50304 x 768 at 257 rows: 64 x 256), but for heads of few groups: 32032 x 1184 (128 rows at 7 and 64), 4096 x 192 (64 or 128 rows at 512).
 bool launch_gemm_tile_logits(hipStream_t st, RowCtx rc, const bf16_t* x, const bf16_t* Wp, float* logits,
                              const GroupOut& go, int V, int K) {
   const int groups = ceil_div(V >> 5, 8), rows = rc.max_rows;            // 256-column groups
