@@ -413,8 +413,8 @@ __device__ __forceinline__ void tile_dma_body(RowCtx rc, const bf16x8* __restric
 // readable (every wavefront has waited for its own copies of it) and the slot of stage s - 1 free.
 // With the reads or copies inside branches, or a burst of copies after the barrier, it was 5 % slower than 8 wavefronts.
 // Same accumulator chain per element as every kernel here (k-tiles in order).  K % 32 == 0.
-// What bounds it: power.  2 x 14336 x 4096 with SiLU at 12800 rows: the matrix cores are busy 72 % of the cycles, at 1.65-1.8 GHz of
-// 2.4 (1.33 PFLOP/s; a library product of 16384^3 reaches 1.56).  The rest is in the rounds: a tile of K = 2560 takes 60 us on its
+// What bounds it: power.  2 x 9728 x 2560 with SiLU at 32768 and 65536 rows: the matrix cores are busy 70 % of the cycles, at 1.80 and 1.56 GHz
+// of 2.4 (1.31 and 1.14 PFLOP/s; a library product of 16384^3 reaches 1.56); output and down projections 58-71 % at 1.65-1.9 GHz.  The rest is in the rounds: a tile of K = 2560 takes 60 us on its
 // compute unit, the ring's filling and a SwiGLU epilogue 6 more, and a launch lasts as long as the unit with the most tiles.
 // Hence the tiles' order and the halves below.  us at 16384 rows, a grid of 256 x 256 tiles in grid order / this: gate/up of 9728 x 2560
 // 1295 / 1250, of 4864 x 896 (14500 rows) 246 / 233; output projections 2560 x 4096 437 / 363, x 9728 776 / 698 (2.5 rounds of tiles),
